@@ -161,7 +161,7 @@ struct ivftq_index {
     bool has_coarse = false;
     std::vector<float> h_cent, h_pi, h_cb, h_tau;
     // device constants
-    DevBuf cent, cent_h, cent_l, bias, pi, pi_h, pi_l, cb, q_grid;   // cent_h/cent_l: split float16 form of cent
+    DevBuf cent, cent_h, cent_l, bias, pi, pi_h, pi_l, pit_h, pit_l, cb, q_grid;   // *_h/*_l: split float16 form (pit: of the transposed rotation)
     // list storage
     DevBuf codes, gamma, ids, d_off, d_size;
     DevBuf xnorm;          // |x| per slot, kept only for a raw metric (ivftq_set_metric)
@@ -194,7 +194,7 @@ struct ivftq_index {
     hipStream_t last_stream = nullptr;   // stream of the most recent call that took one (ivftq_reset and the host read-backs wait for it)
 
     std::vector<DevBuf*> buffers() {
-        return {&cent, &cent_h, &cent_l, &pi_h, &pi_l, &bias, &pi, &cb, &q_grid, &codes, &gamma, &ids, &xnorm, &head, &w_qnorm, &d_off, &d_size, &w_assign,
+        return {&cent, &cent_h, &cent_l, &pi_h, &pi_l, &pit_h, &pit_l, &bias, &pi, &cb, &q_grid, &codes, &gamma, &ids, &xnorm, &head, &w_qnorm, &d_off, &d_size, &w_assign,
                 &w_slot, &w_order, &w_hist, &w_count, &w_base, &w_flag, &w_best, &w_undecided, &cb_cascade, &w_keep, &w_keep_scores,
                 &w_S, &w_probe, &w_coarse, &w_z, &w_candoff, &w_scores, &w_sums, &w_counts, &w_zero, &w_rows, &w_dst, &w_obj,
                 &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_pairoff, &w_tileoff, &w_cscore,
@@ -296,6 +296,7 @@ ivftq_status upload_rotation(ivftq_index* ix) {
     HIP_TRY(hipMemcpy(ix->pi.p, padded.data(), padded.size() * sizeof(float), hipMemcpyHostToDevice));
     HIP_TRY(launch_split_rows(ix->pi.as<float>(), (int64_t)ix->dp * ix->dp, ix->pi_h.as<uint16_t>(),
                               ix->pi_l.as<uint16_t>(), nullptr));
+    HIP_TRY(launch_split_transposed(ix->pi.as<float>(), ix->dp, ix->pit_h.as<uint16_t>(), ix->pit_l.as<uint16_t>(), nullptr));
     HIP_TRY(hipStreamSynchronize(nullptr));
     return IVFTQ_OK;
 }
@@ -495,6 +496,8 @@ ivftq_status ivftq_create_refined(int d, int b_stage1, int sign_bit, int nlist, 
     if (e == hipSuccess) e = ix->pi.ensure((size_t)ix->dp * ix->dp * sizeof(float));
     if (e == hipSuccess) e = ix->pi_h.ensure((size_t)ix->dp * ix->dp * sizeof(uint16_t));
     if (e == hipSuccess) e = ix->pi_l.ensure((size_t)ix->dp * ix->dp * sizeof(uint16_t));
+    if (e == hipSuccess) e = ix->pit_h.ensure((size_t)ix->dp * ix->dp * sizeof(uint16_t));
+    if (e == hipSuccess) e = ix->pit_l.ensure((size_t)ix->dp * ix->dp * sizeof(uint16_t));
     if (e == hipSuccess) e = ix->cb.ensure(256 * sizeof(float));
     if (e == hipSuccess) e = ix->q_grid.ensure(grid_words.size() * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMemcpy(ix->q_grid.p, grid_words.data(), grid_words.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
@@ -1171,15 +1174,17 @@ struct ScopedBuf {
 // x_out[row] = reconstruction of the vector at list-order position row, ids_out its label
 ivftq_status reconstruct_all(ivftq_index* ix, float* x_out, int64_t* ids_out, hipStream_t st) {
     const int L = ix->nlist;
-    std::vector<int64_t> off(L);
-    int64_t run = 0;
-    int max_list = 0;
-    for (int l = 0; l < L; ++l) { off[l] = run; run += ix->h_size[l]; max_list = std::max(max_list, (int)ix->h_size[l]); }
     HIP_TRY(ix->w_base.ensure((size_t)2 * L * sizeof(int64_t)));
-    HIP_TRY(hipMemcpyAsync(ix->w_base.p, off.data(), (size_t)L * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    HIP_TRY(launch_reconstruct(ix->store(), L, max_list, ix->cent.as<float>(), ix->dp, ix->pi.as<float>(), ix->dp,
-                               ix->cb.as<float>(), ix->d, ix->b, ix->w_base.as<int64_t>(), x_out, ids_out, st));
-    HIP_TRY(hipStreamSynchronize(st));      // `off` is pageable host memory
+    HIP_TRY(ix->w_tileoff.ensure((size_t)(2 * L + 1) * sizeof(int32_t)));
+    ReconstructArgs a{};
+    a.store = ix->store(); a.L = L; a.sizes_host = ix->h_size.data();
+    a.cent = ix->cent.as<float>(); a.cent_pitch = ix->dp;
+    a.pit_h = ix->pit_h.as<uint16_t>(); a.pit_l = ix->pit_l.as<uint16_t>();
+    a.cb = ix->cb.as<float>(); a.d = ix->d; a.b = ix->b;
+    a.out_off = ix->w_base.as<int64_t>(); a.tile_off = ix->w_tileoff.as<int32_t>();
+    a.x_out = x_out; a.labels_out = ids_out;
+    HIP_TRY(launch_reconstruct(a, st));
+    HIP_TRY(hipStreamSynchronize(st));
     return IVFTQ_OK;
 }
 

@@ -40,6 +40,16 @@ __global__ void k_split_rows(const float* __restrict__ src, int64_t count, uint1
     lo[i] = __builtin_bit_cast(uint16_t, l);
 }
 
+// hi[c][r], lo[c][r] = split float16 form of src[r][c], n x n
+__global__ void k_split_transposed(const float* __restrict__ src, int n, uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n * n) return;
+    _Float16 h, l;
+    split_scaled(src[(i % n) * n + i / n], h, l);
+    hi[i] = __builtin_bit_cast(uint16_t, h);
+    lo[i] = __builtin_bit_cast(uint16_t, l);
+}
+
 // One 32-row tile of normalised data rows as the B operand (split form).  Returns whether the
 // row's norm is usable.
 template <int DP>
@@ -618,6 +628,11 @@ int coarse_dp(int d) {
 hipError_t launch_split_rows(const float* src, int64_t count, uint16_t* hi, uint16_t* lo, hipStream_t st) {
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, src, count, hi, lo);
+    return hipGetLastError();
+}
+
+hipError_t launch_split_transposed(const float* src, int n, uint16_t* hi, uint16_t* lo, hipStream_t st) {
+    hipLaunchKernelGGL(k_split_transposed, dim3((unsigned)((n * n + 255) / 256)), dim3(256), 0, st, src, n, hi, lo);
     return hipGetLastError();
 }
 

@@ -92,6 +92,8 @@ hipError_t launch_coarse_screened(const float* x, int64_t n, int d, const uint16
                                   unsigned long long* row_key, int* row_count, float* part, hipStream_t st);
 // hi[i], lo[i] = split float16 form of src[i]
 hipError_t launch_split_rows(const float* src, int64_t count, uint16_t* hi, uint16_t* lo, hipStream_t st);
+// hi[c][r], lo[c][r] = split float16 form of src[r][c] (n x n)
+hipError_t launch_split_transposed(const float* src, int n, uint16_t* hi, uint16_t* lo, hipStream_t st);
 
 // Pure-MFMA calibration loop: `blocks` workgroups of 4 wavefronts, each wavefront issues 32*iters
 // v_mfma_f32_32x32x16_f16.  operands: 4096*8 float16 values (any finite bits); out: blocks*256 floats.
@@ -150,11 +152,19 @@ hipError_t launch_pack_scatter(const uint8_t* codes, const uint16_t* gamma, cons
 hipError_t launch_copy_lists(const ListStore& from, const ListStore& to, int L, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 
-// x_out[out_off[l] + v] = cent_l + gamma * Pi^T C[code] for vector v of list l (rows of d floats, list
-// order), labels_out (may be null) the stored labels in the same order.  pi: fp32 [.][pi_pitch].
-hipError_t launch_reconstruct(const ListStore& store, int L, int max_list, const float* cent, int cent_pitch,
-                              const float* pi, int pi_pitch, const float* cb, int d, int b, const int64_t* out_off,
-                              float* x_out, int64_t* labels_out, hipStream_t st);
+// x_out[out_off[l] + v] = cent_l + gamma * Pi^T C[code] for vector v of list l (rows of d floats, list order),
+// labels_out (may be null) the stored labels in the same order.  pit_h / pit_l: split float16 form of Pi^T,
+// [DP][DP], DP = rot_dp(d).  out_off (L entries) and tile_off (L + 1) are scratch, filled by the call; sizes_host:
+// the list sizes as the host knows them.
+struct ReconstructArgs {
+    ListStore store; int L; const int32_t* sizes_host;
+    const float* cent; int cent_pitch;
+    const uint16_t* pit_h; const uint16_t* pit_l;
+    const float* cb; int d; int b;
+    int64_t* out_off; int32_t* tile_off;
+    float* x_out; int64_t* labels_out;
+};
+hipError_t launch_reconstruct(const ReconstructArgs& a, hipStream_t st);
 // dst[t] = src[idx[t]], rows of d floats
 hipError_t launch_gather_rows(const float* src, int d, const int64_t* idx, int64_t count, float* dst, hipStream_t st);
 

@@ -9,7 +9,10 @@
 // each segment by one wavefront.
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
+
 #include "kernels.h"
+#include "split_f16.h"
 
 namespace ivftq {
 
@@ -267,64 +270,231 @@ __global__ __launch_bounds__(64) void k_copy_rows_normalised(const float* __rest
 }
 
 // Reconstruction of stored vectors (Section "Adaptive coarse refresh", Refresh self-containedness):
-// x^ = c~_l + gamma * Pi^T C[code].  A workgroup takes 32 consecutive vectors of one list: their
-// de-quantised coordinates go to LDS as rho[k][v], then thread j accumulates output coordinate j of
-// all 32 vectors, x^_j = sum_k Pi[k][j] rho_k (row k of Pi is read coalesced across the threads, the
-// 32 values of rho[k][.] are LDS broadcasts), and rows are written whole.  Rows come out in list
-// order: list l starts at row out_off[l]; labels_out gets the stored labels in the same order.
-__global__ __launch_bounds__(256) void k_reconstruct(ListStore store, const float* __restrict__ cent, int cent_pitch,
-                                                     const float* __restrict__ pi, int pi_pitch,
-                                                     const float* __restrict__ cb, int d, int b,
-                                                     const int64_t* __restrict__ out_off,
-                                                     float* __restrict__ x_out, int64_t* __restrict__ labels_out) {
-    extern __shared__ float rho[];                     // [d][32], then 32 norms
-    float* gam = rho + (size_t)d * 32;
-    const int l = blockIdx.y;
-    const int n_l = store.list_size[l];
-    const int v0 = blockIdx.x * 32;
-    if (v0 >= n_l) return;
-    const int tid = threadIdx.x;
-    const int64_t base_slot = store.list_off[l];
+// x^ = c~_l + gamma * Pi^T C[code], rows in list order (list l starts at row out_off[l]), labels likewise.
+//
+// A contraction [vectors] x [d] . [d] x [d] whose result is written once: 4d bytes a vector against 3 * 2d^2 flop on
+// the matrix cores, so it should run at the speed of the stores.  Wavefront t of a workgroup owns the output
+// coordinates 32t .. 32t + 31 and keeps its 32 columns of Pi^T (both float16 parts) in registers for the life of the
+// workgroup; the 32 vectors of a tile are de-quantised once by all wavefronts together into LDS (split form, double
+// buffered: one barrier per tile; the next tile's packed words are in flight meanwhile) and are the row operand, so
+// that a lane holds one output coordinate of 16 vectors and every store instruction writes whole 128-byte lines.
+// For d <= 64 several tiles share a workgroup (SLABS), which keeps it at 128 threads or more.  Workgroups walk
+// contiguous ranges of tiles: one search for the list, then steps.
+// 1M x 128, b = 4: 0.94 ms with one thread per output coordinate and float32 multiply-adds,
+// 0.16 ms so (3.7 TB/s read + written).
+template <int DP>
+struct ReconCfg {
+    static constexpr int KB = DP / 16, NT = DP / 32, LDH = DP + 8;
+    static constexpr int SLABS = NT >= 4 ? 1 : (NT == 1 ? 4 : 2);
+    static constexpr int THREADS = 64 * NT * SLABS;
+    static constexpr int VEC = 32 * SLABS;                       // vectors per tile
+    static constexpr int buf_halves = SLABS * 2 * 32 * LDH;      // hi and lo rows of one tile
+    static constexpr size_t lds_bytes = (size_t)2 * buf_halves * 2 + 256 * 4 + 2 * VEC * 4;
+};
+
+// A value that kernels before this one wrote and none changes now, read through the scalar cache (the compiler would
+// use a vector load, and wait for everything in front of it, because this kernel stores to memory it cannot tell apart).
+template <class T>
+__device__ __forceinline__ T fixed(const T* p) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
+}
+
+// NW: words that can hold the 8b bits of eight codes (1 for b = 1, 2, 4; 3 for b = 7; else 2)
+template <int DP, int NW>
+__global__ __launch_bounds__(ReconCfg<DP>::THREADS) void k_reconstruct(
+    ListStore store, int L, const float* __restrict__ cent, int cent_pitch, const uint16_t* __restrict__ pit_h,
+    const uint16_t* __restrict__ pit_l, const float* __restrict__ cb, int d, int b, const int64_t* __restrict__ out_off,
+    const int32_t* __restrict__ tile_off, int tiles, float* __restrict__ x_out, int64_t* __restrict__ labels_out) {
+    using Cfg = ReconCfg<DP>;
+    constexpr int KB = Cfg::KB, LDH = Cfg::LDH, VEC = Cfg::VEC, T = Cfg::THREADS;
+    extern __shared__ unsigned char lds_raw[];
+    uint16_t* stage = reinterpret_cast<uint16_t*>(lds_raw);                       // [2][SLABS][hi, lo][32][LDH]
+    uint32_t* tab = reinterpret_cast<uint32_t*>(stage + 2 * Cfg::buf_halves);     // [2^b] hi | lo << 16
+    float* gam = reinterpret_cast<float*>(tab + 256);                             // [2][VEC] norms * 2^-20
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, jl = lane & 31;
+    const int col = 32 * (wave % Cfg::NT) + jl, my_slab = wave / Cfg::NT;
     const int words = store.words;
     const uint32_t mask = (1u << b) - 1u;
-    for (int e = tid; e < 32 * d; e += 256) {
-        const int v = e & 31, k = e >> 5;
-        float val = 0.f;
-        if (v0 + v < n_l) {
-            const int64_t slot = base_slot + v0 + v;
+
+    half8 bh[KB], bl[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+        bh[kb] = *reinterpret_cast<const half8*>(pit_h + (size_t)col * DP + 16 * kb + 8 * half);
+        bl[kb] = *reinterpret_cast<const half8*>(pit_l + (size_t)col * DP + 16 * kb + 8 * half);
+    }
+    for (int e = tid; e <= (int)mask; e += T) {
+        _Float16 h, l;
+        split_scaled(cb[e], h, l);
+        tab[e] = (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, l) << 16);
+    }
+
+    // this workgroup's tiles, and the list of the first one
+    const int per = (tiles + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int t_begin = (int)blockIdx.x * per, t_end = t_begin + per < tiles ? t_begin + per : tiles;
+    if (t_begin >= t_end) return;
+    int l = 0, hi_l = L;
+    while (hi_l - l > 1) {
+        const int mid = (l + hi_l) >> 1;
+        if (tile_off[mid] <= t_begin) l = mid; else hi_l = mid;
+    }
+
+    // A tile has VEC * (DP / 8) groups of eight coordinates, two per thread: group tid + p*T is vector (group % 32) of
+    // slab group / 32 / (DP/8), coordinates 8*chunk ..; its 8b bits start at bit 8*b*chunk and lie in at most three words.
+    // (A word index past the row's end is clamped: codes of coordinates past d meet zeros of Pi^T whatever they are.)
+    uint32_t w[2][NW];
+    uint32_t next_gam = 0;
+    int64_t next_id = 0;
+    float next_c = 0.f;
+    auto fetch = [&](int l, int n_l, int64_t base, int v0) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int e = tid + p * T, v = v0 + 32 * ((e >> 5) / (DP / 8)) + (e & 31), chunk = (e >> 5) % (DP / 8);
+            const int64_t slot = base + (v < n_l ? v : n_l - 1);
+            const int w0 = (8 * b * chunk) >> 5;
             const uint32_t* wp = store.codes + (slot >> 6) * (int64_t)words * 64 + (slot & 63);
-            const int bit = k * b, w = bit >> 5, sh = bit & 31;
-            uint32_t code = wp[(int64_t)w * 64] >> sh;
-            if (sh + b > 32) code |= wp[(int64_t)(w + 1) * 64] << (32 - sh);
-            val = cb[code & mask];
+#pragma unroll
+            for (int i = 0; i < NW; ++i) w[p][i] = wp[(w0 + i < words ? w0 + i : words - 1) * 64];
         }
-        rho[k * 32 + v] = val;
+        const int v = v0 + (tid < VEC ? tid : VEC - 1);
+        const int64_t slot = base + (v < n_l ? v : n_l - 1);
+        next_gam = store.gamma[slot];
+        next_id = store.ids[slot];
+        next_c = cent[(int64_t)l * cent_pitch + col];
+    };
+    while (t_begin >= fixed(tile_off + l + 1)) ++l;          // lists without vectors have no tile
+    int n_l = fixed(store.list_size + l), v0 = (t_begin - fixed(tile_off + l)) * VEC;
+    int64_t base = fixed(store.list_off + l), row_l = fixed(out_off + l);
+    int tile_end = fixed(tile_off + l + 1);
+    fetch(l, n_l, base, v0);
+
+    constexpr float kUnscale = 1.f / (kSplitScale * kSplitScale);
+    int buf = 0;
+    __syncthreads();                                 // the table is written
+    for (int tile = t_begin; tile < t_end; ++tile, buf ^= 1) {
+        const int64_t row0 = row_l + v0;
+        uint16_t* st = stage + buf * Cfg::buf_halves;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int e = tid + p * T, slab = (e >> 5) / (DP / 8), chunk = (e >> 5) % (DP / 8);
+            const int sh = (8 * b * chunk) & 31;
+            uint64_t bits = ((NW > 1 ? (uint64_t)w[p][NW > 1 ? 1 : 0] << 32 : 0ull) | w[p][0]) >> sh;
+            if (NW > 2 && sh) bits |= (uint64_t)w[p][NW - 1] << (64 - sh);
+            uint32_t hv[4], lv[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t e0 = tab[(uint32_t)(bits >> (2 * t * b)) & mask], e1 = tab[(uint32_t)(bits >> ((2 * t + 1) * b)) & mask];
+                hv[t] = (e0 & 0xFFFFu) | (e1 << 16);
+                lv[t] = (e0 >> 16) | (e1 & 0xFFFF0000u);
+            }
+            uint16_t* row = st + slab * (2 * 32 * LDH) + (e & 31) * LDH + 8 * chunk;
+            *reinterpret_cast<uint4*>(row) = make_uint4(hv[0], hv[1], hv[2], hv[3]);
+            *reinterpret_cast<uint4*>(row + 32 * LDH) = make_uint4(lv[0], lv[1], lv[2], lv[3]);
+        }
+        if (tid < VEC) gam[buf * VEC + tid] = kUnscale * __half2float(__ushort_as_half((uint16_t)next_gam));
+        const __amdgpu_buffer_rsrc_t lab = __builtin_amdgcn_make_buffer_rsrc(labels_out + (labels_out ? row0 : 0), 0,
+                                                                              labels_out ? min(n_l - v0, VEC) * 8 : 0, 0x00020000);
+        typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, next_id), lab, tid * 8, 0, 0);   // past the end: dropped
+        const float c = next_c;
+        const int cur_left = n_l - v0 - 32 * my_slab;
+        v0 += VEC;
+        if (tile + 1 == tile_end) {
+            if (tile + 1 < t_end) {
+                do ++l; while (tile + 1 >= fixed(tile_off + l + 1));
+                n_l = fixed(store.list_size + l);
+                base = fixed(store.list_off + l);
+                row_l = fixed(out_off + l);
+                tile_end = fixed(tile_off + l + 1);
+                v0 = 0;
+            } else {
+                v0 -= VEC;
+            }
+        }
+        fetch(l, n_l, base, v0);                     // (after the last tile: the same tile again, unused)
+        // One barrier per tile: the other buffer, written in the next round, was last read before this barrier.
+        __syncthreads();
+        const uint16_t* ah_base = st + my_slab * (2 * 32 * LDH) + jl * LDH + 8 * half;
+        const uint16_t* al_base = ah_base + 32 * LDH;
+        floatx16 acc;
+        const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            const half8 ah = *reinterpret_cast<const half8*>(ah_base + 16 * kb);
+            const half8 al = *reinterpret_cast<const half8*>(al_base + 16 * kb);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[kb], kb ? acc : zero, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[kb], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[kb], acc, 0, 0, 0);
+        }
+        // Stores through a buffer descriptor that ends with the list's rows: rows past the list (and columns past d,
+        // sent past any end) are dropped by the address check, so every tile issues the same sixteen stores.  Behind
+        // tests they could not be counted, and the wait for the next tile's words, which sit in front of them in the
+        // memory queue, would be a wait for the stores as well (0.31 ms at 1M x 128 that way).
+        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
+            x_out + (row0 + 32 * my_slab) * (int64_t)d, 0, min(max(cur_left, 0), 32) * d * 4, 0x00020000);
+        const uint32_t at0 = col < d ? (uint32_t)(4 * half * d + col) * 4u : 0x40000000u;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {                // result rows 4g .. 4g+3 of a lane: vectors 8g + 4*half ..
+            const float4 gm = *reinterpret_cast<const float4*>(gam + buf * VEC + 32 * my_slab + 8 * g + 4 * half);
+            const float gg[4] = {gm.x, gm.y, gm.z, gm.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(fmaf(gg[i], acc[4 * g + i], c)), out, at0, (8 * g + i) * d * 4, 0);
+        }
     }
-    if (tid < 32) {
-        const bool in = v0 + tid < n_l;
-        gam[tid] = in ? __half2float(__ushort_as_half(store.gamma[base_slot + v0 + tid])) : 0.f;
-        if (in && labels_out) labels_out[out_off[l] + v0 + tid] = store.ids[base_slot + v0 + tid];
-    }
+}
+
+// out_off[l] = vectors in the lists before l; tile_off[l] = tiles of `vec` vectors in them (entry L = all)
+__global__ __launch_bounds__(1024) void k_list_prefix(const int32_t* __restrict__ size, int L, int vec,
+                                                      int64_t* __restrict__ out_off, int32_t* __restrict__ tile_off) {
+    __shared__ int64_t part_n[1024];
+    __shared__ int32_t part_t[1024];
+    const int per = (L + 1023) / 1024, tid = threadIdx.x;
+    const int lo = tid * per < L ? tid * per : L, hi = lo + per < L ? lo + per : L;
+    int64_t n = 0;
+    int32_t t = 0;
+    for (int l = lo; l < hi; ++l) { n += size[l]; t += (size[l] + vec - 1) / vec; }
+    part_n[tid] = n;
+    part_t[tid] = t;
     __syncthreads();
-    const int j = tid;
-    if (j >= d) return;
-    float acc[32];
-#pragma unroll
-    for (int v = 0; v < 32; ++v) acc[v] = 0.f;
-    for (int k = 0; k < d; ++k) {
-        const float p = pi[(int64_t)k * pi_pitch + j];
-        const float4* r4 = reinterpret_cast<const float4*>(rho + k * 32);
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            const float4 r = r4[g];
-            acc[4 * g] = fmaf(p, r.x, acc[4 * g]); acc[4 * g + 1] = fmaf(p, r.y, acc[4 * g + 1]);
-            acc[4 * g + 2] = fmaf(p, r.z, acc[4 * g + 2]); acc[4 * g + 3] = fmaf(p, r.w, acc[4 * g + 3]);
-        }
+    for (int o = 1; o < 1024; o <<= 1) {
+        const int64_t an = tid >= o ? part_n[tid - o] : 0;
+        const int32_t at = tid >= o ? part_t[tid - o] : 0;
+        __syncthreads();
+        part_n[tid] += an;
+        part_t[tid] += at;
+        __syncthreads();
     }
-    const float c = cent[(int64_t)l * cent_pitch + j];
-#pragma unroll
-    for (int v = 0; v < 32; ++v)
-        if (v0 + v < n_l) x_out[(out_off[l] + v0 + v) * (int64_t)d + j] = fmaf(gam[v], acc[v], c);
+    n = part_n[tid] - n;
+    t = part_t[tid] - t;
+    for (int l = lo; l < hi; ++l) {
+        out_off[l] = n;
+        tile_off[l] = t;
+        n += size[l];
+        t += (size[l] + vec - 1) / vec;
+    }
+    if (tid == 1023) tile_off[L] = part_t[1023];
+}
+
+template <int DP, int NW>
+hipError_t run_reconstruct_nw(const ReconstructArgs& a, int cus, hipStream_t st) {
+    using Cfg = ReconCfg<DP>;
+    static LdsLimit lim;
+    const hipError_t e = lim.ensure(reinterpret_cast<const void*>(k_reconstruct<DP, NW>), Cfg::lds_bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_list_prefix, dim3(1), dim3(1024), 0, st, a.store.list_size, a.L, Cfg::VEC, a.out_off, a.tile_off);
+    int64_t tiles = 0;
+    for (int l = 0; l < a.L; ++l) tiles += (a.sizes_host[l] + Cfg::VEC - 1) / Cfg::VEC;
+    static std::atomic<int> per_cu{0};               // workgroups a compute unit holds, the same on every device of this kind
+    int fit = per_cu.load(std::memory_order_relaxed);
+    if (fit == 0) {
+        const hipError_t eo = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, reinterpret_cast<const void*>(k_reconstruct<DP, NW>), Cfg::THREADS, Cfg::lds_bytes);
+        if (eo != hipSuccess) return eo;
+        per_cu.store(fit = std::max(fit, 1), std::memory_order_relaxed);
+    }
+    const unsigned blocks = (unsigned)std::min<int64_t>(tiles, (int64_t)cus * fit);
+    hipLaunchKernelGGL((k_reconstruct<DP, NW>), dim3(blocks), dim3(Cfg::THREADS), Cfg::lds_bytes, st, a.store, a.L, a.cent, a.cent_pitch, a.pit_h,
+                       a.pit_l, a.cb, a.d, a.b, (const int64_t*)a.out_off, (const int32_t*)a.tile_off, (int)tiles, a.x_out, a.labels_out);
+    return hipGetLastError();
 }
 
 // dst[t] = src[idx[t]] for rows of d floats
@@ -358,6 +528,13 @@ __global__ __launch_bounds__(256) void k_inertia(const float* __restrict__ best,
         __syncthreads();
     }
     if (threadIdx.x == 0) *out = part[0];
+}
+
+template <int DP>
+hipError_t run_reconstruct(const ReconstructArgs& a, int cus, hipStream_t st) {
+    if (a.b == 1 || a.b == 2 || a.b == 4) return run_reconstruct_nw<DP, 1>(a, cus, st);
+    if (a.b == 7) return run_reconstruct_nw<DP, 3>(a, cus, st);
+    return run_reconstruct_nw<DP, 2>(a, cus, st);
 }
 
 }  // namespace
@@ -430,14 +607,22 @@ hipError_t launch_copy_rows_normalised(const float* x, int d, const int64_t* src
     return hipGetLastError();
 }
 
-hipError_t launch_reconstruct(const ListStore& store, int L, int max_list, const float* cent, int cent_pitch,
-                              const float* pi, int pi_pitch, const float* cb, int d, int b, const int64_t* out_off,
-                              float* x_out, int64_t* labels_out, hipStream_t st) {
-    if (max_list <= 0) return hipSuccess;
-    const size_t lds = ((size_t)d * 32 + 32) * sizeof(float);
-    hipLaunchKernelGGL(k_reconstruct, dim3((unsigned)((max_list + 31) / 32), (unsigned)L), dim3(256), lds, st, store, cent,
-                       cent_pitch, pi, pi_pitch, cb, d, b, out_off, x_out, labels_out);
-    return hipGetLastError();
+hipError_t launch_reconstruct(const ReconstructArgs& a, hipStream_t st) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    switch (rot_dp(a.d)) {
+        case 32: return run_reconstruct<32>(a, cus, st);
+        case 64: return run_reconstruct<64>(a, cus, st);
+        case 96: return run_reconstruct<96>(a, cus, st);
+        case 128: return run_reconstruct<128>(a, cus, st);
+        case 160: return run_reconstruct<160>(a, cus, st);
+        case 192: return run_reconstruct<192>(a, cus, st);
+        case 224: return run_reconstruct<224>(a, cus, st);
+        case 256: return run_reconstruct<256>(a, cus, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_gather_rows(const float* src, int d, const int64_t* idx, int64_t count, float* dst, hipStream_t st) {

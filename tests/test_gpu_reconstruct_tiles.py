@@ -1,0 +1,44 @@
+"""ivftq_reconstruct on lists whose lengths sit around the kernel's tiles of 32, 64 and 128 vectors (empty ones and runs
+of empty ones among them), for every padded width and every number of stored bits, against the definition
+x^ = c~_l + gamma * Pi^T C[code] in float64.
+
+Tolerance: every product carries a relative error of at most 2^-21 (two split float16 operands), and d of them are
+added in float32; Cauchy-Schwarz bounds the sum of their magnitudes by |C[code]| <= sqrt(d) max|C|, the rows of Pi being
+unit vectors.  So |error| <= gamma * sqrt(d) * max|C| * (2^-21 + d 2^-24), plus the rounding of the result."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+SIZES = [0, 1, 31, 0, 0, 32, 33, 63, 64, 65, 127, 128, 129, 0, 300, 1, 0]
+
+
+@pytest.mark.parametrize("d,b", [(8, 1), (32, 4), (33, 3), (64, 2), (70, 7), (96, 4), (100, 5), (128, 8), (129, 6), (160, 4), (192, 3),
+                                 (200, 7), (224, 4), (255, 5), (256, 8)])
+def test_tiles_and_widths(d, b):
+    import paper_2605_17415_amd as pkg
+    print(f"[reconstruct tiles] d={d} b={b}", flush=True)
+    rng = np.random.default_rng(1000 * d + b)
+    L, n = len(SIZES), sum(SIZES)
+    cell = rng.permutation(np.repeat(np.arange(L), SIZES)).astype(np.int32)
+    codes = rng.integers(0, 1 << b, (n, d)).astype(np.uint8)
+    gamma = rng.uniform(0.0, 1.2, n).astype(np.float16)
+    labels = rng.permutation(10 * n)[:n].astype(np.int64)
+    cent = rng.standard_normal((L, d)).astype(np.float32)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    dev = torch.device("cuda:0")
+    ix = pkg.Index(d, b, L, rotation_seed=d)
+    ix.set_coarse(cent)
+    ix.add_encoded(torch.from_numpy(cell).to(dev), torch.from_numpy(codes).to(dev), torch.from_numpy(gamma).to(dev),
+                   torch.from_numpy(labels).to(dev))
+    x, ids = ix.reconstruct()
+    torch.cuda.synchronize()
+    order = np.argsort(cell, kind="stable")
+    levels, _ = ix.get_codebook()
+    pi = ix.get_rotation().astype(np.float64)
+    want = cent[cell[order]] + gamma[order].astype(np.float64)[:, None] * (levels[codes[order]].astype(np.float64) @ pi)
+    bound = gamma[order].astype(np.float64)[:, None] * np.sqrt(d) * np.abs(levels).max() * (2.0 ** -21 + d * 2.0 ** -24) + 2.0 ** -24 * (np.abs(want) + 1)
+    np.testing.assert_array_equal(ids.cpu().numpy(), labels[order])
+    assert np.all(np.abs(x.cpu().numpy() - want) <= bound)
+    ix.close()
