@@ -172,14 +172,15 @@ struct ivftq_index {
     std::vector<int64_t> h_off, h_cap;
     std::vector<int32_t> h_size;
     int64_t pool_slots = 0;
+    PinnedBuf pin_table;   // trained centroids on their way to the host
     PinnedBuf pin;   // [L u32 batch counts | 16 B flag | 2L i64 bases | L i32 sizes], see place_rows / commit_rows
     int64_t ntotal = 0;
     // workspace
-    DevBuf w_assign, w_slot, w_order, w_hist, w_count, w_base, w_flag, w_best, w_undecided;
+    DevBuf w_assign, w_slot, w_order, w_hist, w_count, w_base, w_flag, w_undecided;
     DevBuf cb_cascade, w_keep, w_keep_scores;   // cascade search: pass-1 table (for cascade_beta), kept slots and their pass-1 scores
     int cascade_beta = 0;
     DevBuf w_S, w_probe, w_coarse, w_z, w_candoff, w_scores;
-    DevBuf w_sums, w_counts, w_zero, w_rows, w_dst, w_obj;
+    DevBuf w_sums, w_counts, w_gain, w_rows, w_dst;
     DevBuf t_cent, t_cent_h, t_cent_l, t_bias;   // k-means works on its own tables; the index's change only on success
     DevBuf w_zh, w_zl;
     DevBuf w_first, w_fscores, w_fids, w_pairs, w_pairoff, w_tileoff, w_cscore, w_cslot, w_ccnt, w_gate;
@@ -195,8 +196,8 @@ struct ivftq_index {
 
     std::vector<DevBuf*> buffers() {
         return {&cent, &cent_h, &cent_l, &pi_h, &pi_l, &pit_h, &pit_l, &bias, &pi, &cb, &q_grid, &codes, &gamma, &ids, &xnorm, &head, &w_qnorm, &d_off, &d_size, &w_assign,
-                &w_slot, &w_order, &w_hist, &w_count, &w_base, &w_flag, &w_best, &w_undecided, &cb_cascade, &w_keep, &w_keep_scores,
-                &w_S, &w_probe, &w_coarse, &w_z, &w_candoff, &w_scores, &w_sums, &w_counts, &w_zero, &w_rows, &w_dst, &w_obj,
+                &w_slot, &w_order, &w_hist, &w_count, &w_base, &w_flag, &w_undecided, &cb_cascade, &w_keep, &w_keep_scores,
+                &w_S, &w_probe, &w_coarse, &w_z, &w_candoff, &w_scores, &w_sums, &w_counts, &w_gain, &w_rows, &w_dst,
                 &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_pairoff, &w_tileoff, &w_cscore,
                 &w_cslot, &w_ccnt, &w_gate, &w_zh, &w_zl, &w_stage_s, &w_stage_i, &w_part};
     }
@@ -232,6 +233,7 @@ struct ivftq_index {
         for (ProfRec& r : prof) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
         for (DevBuf* bfr : buffers()) bfr->release();
         pin.release();
+        pin_table.release();
     }
 };
 
@@ -769,6 +771,44 @@ ivftq_status ivftq_export_list(const ivftq_index* ix, int list, int64_t* ids_hos
 
 // ---------------------------------------------------------------------------------------------
 
+}  // extern "C"
+
+namespace {
+
+// Coarse assignment of n rows (Algorithm "Encode", nearest centroid by inner product; with a bias, k-means' nearest
+// mean): screening pass plus the exact pass over the rows it left undecided.  w_flag[0] = a row without a usable
+// norm, w_flag[1] = number of undecided rows, both cleared by the caller.
+constexpr int64_t kScreenShareRows = 1 << 18;     // from here on the row tiles alone fill the chip
+ivftq_status assign_rows(ivftq_index* ix, const float* x_dev, int64_t n, const uint16_t* cent_h, const uint16_t* cent_l,
+                         const float* bias, int32_t* assign, hipStream_t st) {
+    // keys (8 bytes each) first, then the row numbers
+    HIP_TRY(ix->w_undecided.ensure((size_t)n * (sizeof(unsigned long long) + sizeof(int32_t))));
+    ScreenArgs a{};
+    a.x = x_dev; a.n = n; a.d = ix->d;
+    a.cent_h = cent_h; a.cent_l = cent_l; a.cent_pitch = ix->dp;
+    a.bias = bias; a.L = ix->nlist; a.Lpad = ix->lpad;
+    a.assign = assign; a.flag = ix->w_flag.as<int>(); a.row_count = ix->w_flag.as<int>() + 1;
+    a.row_key = ix->w_undecided.as<unsigned long long>();
+    a.row_list = reinterpret_cast<int32_t*>(a.row_key + n);
+    // short batches share the centroid stages out over several workgroups and need room for the partial results
+    if (n < kScreenShareRows) {
+        HIP_TRY(ix->w_part.ensure((size_t)n * kScreenMaxShares * 3 * sizeof(float)));
+        a.part = ix->w_part.as<float>();
+    }
+    HIP_TRY(timed(ix, st, P_ASSIGN, [&] { return launch_coarse_screened(a, st); }));
+    return IVFTQ_OK;
+}
+
+// The same against the index's own centroids.
+ivftq_status assign_to_index(ivftq_index* ix, const float* x_dev, int64_t n, int32_t* assign, hipStream_t st) {
+    HIP_TRY(launch_fill_u32(ix->w_flag.as<uint32_t>(), 2, 0u, st));
+    return assign_rows(ix, x_dev, n, ix->cent_h.as<uint16_t>(), ix->cent_l.as<uint16_t>(), nullptr, assign, st);
+}
+
+}  // namespace
+
+extern "C" {
+
 ivftq_status ivftq_train_coarse(ivftq_index* ix, const float* x_dev, int64_t n, int niter,
                                 const int64_t* init_rows_host, uint64_t seed, double* inertia_out,
                                 void* stream) {
@@ -807,10 +847,8 @@ ivftq_status ivftq_train_coarse(ivftq_index* ix, const float* x_dev, int64_t n, 
     HIP_TRY(ix->w_dst.ensure((size_t)L * sizeof(int32_t)));
     HIP_TRY(ix->w_sums.ensure(table * sizeof(float)));
     HIP_TRY(ix->w_counts.ensure((size_t)ix->lpad * sizeof(uint32_t)));
-    HIP_TRY(ix->w_zero.ensure((size_t)ix->lpad * sizeof(uint32_t)));
+    HIP_TRY(ix->w_gain.ensure(((size_t)L + 1) * sizeof(double)));
     HIP_TRY(ix->w_assign.ensure((size_t)n * sizeof(int32_t)));
-    HIP_TRY(ix->w_best.ensure((size_t)n * sizeof(float)));
-    HIP_TRY(ix->w_obj.ensure(sizeof(double)));
     HIP_TRY(ix->w_order.ensure((size_t)n * sizeof(int32_t)));
     HIP_TRY(ix->w_hist.ensure((size_t)nseg * L * sizeof(uint32_t)));
     HIP_TRY(ix->w_base.ensure((size_t)2 * L * sizeof(int64_t)));
@@ -820,29 +858,23 @@ ivftq_status ivftq_train_coarse(ivftq_index* ix, const float* x_dev, int64_t n, 
     HIP_TRY(ix->t_bias.ensure((size_t)ix->lpad * sizeof(float)));
     float* cent = ix->t_cent.as<float>();
     float* bias = ix->t_bias.as<float>();
+    uint16_t* cent_h = ix->t_cent_h.as<uint16_t>();
+    uint16_t* cent_l = ix->t_cent_l.as<uint16_t>();
     uint32_t* counts_dev = ix->w_counts.as<uint32_t>();
     int64_t* cell_base = ix->w_base.as<int64_t>();
+    int* flags = ix->w_flag.as<int>();           // [0] a row without a norm, [1] undecided rows, [2, 4) draws of the re-seeding
 
     HIP_TRY(launch_fill_u32(ix->t_cent.as<uint32_t>(), (int64_t)table, 0u, st));
-    HIP_TRY(launch_fill_u32(ix->w_zero.as<uint32_t>(), ix->lpad, 0u, st));
-    HIP_TRY(launch_fill_u32(ix->w_counts.as<uint32_t>(), ix->lpad, 0u, st));
-    HIP_TRY(launch_fill_u32(ix->w_flag.as<uint32_t>(), 1, 0u, st));
+    HIP_TRY(launch_fill_u32(ix->w_flag.as<uint32_t>(), 4, 0u, st));
     HIP_TRY(hipMemcpyAsync(ix->w_rows.p, init.data(), L * sizeof(int64_t), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(ix->w_dst.p, dst.data(), L * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_TRY(launch_copy_rows_normalised(x_dev, d, ix->w_rows.as<int64_t>(), ix->w_dst.as<int32_t>(), L, cent, pitch, st));
-    HIP_TRY(timed(ix, st, P_KMEANS_UPDATE, [&] { return launch_kmeans_update(cent, pitch, ix->w_sums.as<float>(), ix->w_zero.as<uint32_t>(),
-                                 bias, L, ix->lpad, d, st); }));
-    HIP_TRY(hipStreamSynchronize(st));
+    HIP_TRY(timed(ix, st, P_KMEANS_UPDATE, [&] { return launch_kmeans_update(cent, pitch, nullptr, nullptr, bias, cent_h, cent_l, L, ix->lpad, d, st); }));
 
-    std::vector<uint32_t> counts(L);
-    std::vector<int32_t> h_assign;
-    uint64_t rs = seed ^ 0x1234567887654321ull;
-    double inertia = std::nan("");
+    // The iterations are queued without a host wait: empty cells are re-seeded on the device, and a row without a
+    // usable norm is reported after the last one (the index has not been touched by then).
     for (int it = 0; it < niter; ++it) {
-        HIP_TRY(launch_split_rows(cent, (int64_t)table, ix->t_cent_h.as<uint16_t>(), ix->t_cent_l.as<uint16_t>(), st));
-        HIP_TRY(timed(ix, st, P_ASSIGN, [&] { return launch_coarse(0, x_dev, n, d, ix->t_cent_h.as<uint16_t>(), ix->t_cent_l.as<uint16_t>(), pitch, bias, L, ix->lpad,
-                              ix->w_assign.as<int32_t>(), ix->w_best.as<float>(), nullptr, 0,
-                              ix->w_flag.as<int>(), st); }));
+        { ivftq_status sa = assign_rows(ix, x_dev, n, cent_h, cent_l, bias, ix->w_assign.as<int32_t>(), st); if (sa != IVFTQ_OK) return sa; }
         // Sums per cell in a fixed order (two runs give the same bits): the rows are grouped by cell with the
         // stable counting sort of the append path, then one workgroup adds up the rows of a cell.
         HIP_TRY(timed(ix, st, P_SEG_HIST, [&] { return launch_segment_hist(ix->w_assign.as<int32_t>(), n, seg_len, nseg, L, ix->w_hist.as<uint32_t>(), st); }));
@@ -850,40 +882,26 @@ ivftq_status ivftq_train_coarse(ivftq_index* ix, const float* x_dev, int64_t n, 
         HIP_TRY(launch_exclusive_scan(counts_dev, L, cell_base, st));
         HIP_TRY(timed(ix, st, P_RANK, [&] { return launch_stable_rank(ix->w_assign.as<int32_t>(), n, seg_len, nseg, L, ix->w_hist.as<uint32_t>(), nullptr,
                                    nullptr, cell_base, ix->w_order.as<int32_t>(), nullptr, st); }));
+        double* gain = it == niter - 1 ? ix->w_gain.as<double>() : nullptr;
         HIP_TRY(timed(ix, st, P_KMEANS_SUMS, [&] { return launch_kmeans_cell_sums(x_dev, d, ix->w_order.as<int32_t>(), cell_base, counts_dev, L,
-                                        ix->w_sums.as<float>(), pitch, st); }));
-        HIP_TRY(timed(ix, st, P_KMEANS_UPDATE, [&] { return launch_kmeans_update(cent, pitch, ix->w_sums.as<float>(), counts_dev, bias, L, ix->lpad, d, st); }));
-        if (it == niter - 1) HIP_TRY(launch_inertia(ix->w_best.as<float>(), n, ix->w_obj.as<double>(), st));
-        HIP_TRY(hipMemcpyAsync(counts.data(), ix->w_counts.p, L * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-        int flag = 0;
-        HIP_TRY(hipMemcpyAsync(&flag, ix->w_flag.p, sizeof(int), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        if (flag) return fail(IVFTQ_ZERO_NORM, "a training row has zero or non-finite norm");
-        if (it == niter - 1) HIP_TRY(hipMemcpy(&inertia, ix->w_obj.p, sizeof(double), hipMemcpyDeviceToHost));
-
-        std::vector<int32_t> empty;
-        for (int l = 0; l < L; ++l) if (counts[l] == 0) empty.push_back(l);
-        if (!empty.empty()) {
-            // re-seed each empty cell from a member of the largest cell
-            const int big = (int)(std::max_element(counts.begin(), counts.end()) - counts.begin());
-            h_assign.resize(n);
-            HIP_TRY(hipMemcpy(h_assign.data(), ix->w_assign.p, n * sizeof(int32_t), hipMemcpyDeviceToHost));
-            std::vector<int64_t> members;
-            for (int64_t i = 0; i < n; ++i) if (h_assign[i] == big) members.push_back(i);
-            std::vector<int64_t> rows(empty.size());
-            for (size_t t = 0; t < empty.size(); ++t) rows[t] = members[splitmix(rs) % members.size()];
-            HIP_TRY(hipMemcpy(ix->w_rows.p, rows.data(), rows.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-            HIP_TRY(hipMemcpy(ix->w_dst.p, empty.data(), empty.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-            HIP_TRY(launch_copy_rows_normalised(x_dev, d, ix->w_rows.as<int64_t>(), ix->w_dst.as<int32_t>(),
-                                                (int)empty.size(), cent, pitch, st));
-            HIP_TRY(timed(ix, st, P_KMEANS_UPDATE, [&] { return launch_kmeans_update(cent, pitch, ix->w_sums.as<float>(),
-                                         ix->w_zero.as<uint32_t>(), bias, L, ix->lpad, d, st); }));
-            HIP_TRY(hipStreamSynchronize(st));
-        }
+                                        ix->w_sums.as<float>(), pitch, cent, bias, gain, st); }));
+        HIP_TRY(timed(ix, st, P_KMEANS_UPDATE, [&] { return launch_kmeans_update(cent, pitch, ix->w_sums.as<float>(), counts_dev, bias, cent_h, cent_l, L, ix->lpad, d, st); }));
+        HIP_TRY(launch_kmeans_reseed(x_dev, d, ix->w_order.as<int32_t>(), cell_base, counts_dev, L, cent, pitch, bias, cent_h, cent_l,
+                                     seed ^ 0x1234567887654321ull, reinterpret_cast<unsigned long long*>(flags + 2), flags + 1, st));
+        if (gain) HIP_TRY(launch_inertia(gain, L, n, gain + L, st));
     }
     HIP_TRY(launch_normalise_centroids(cent, pitch, bias, L, d, st));
-    std::vector<float> padded((size_t)L * pitch);
-    HIP_TRY(hipMemcpyAsync(padded.data(), cent, padded.size() * sizeof(float), hipMemcpyDeviceToHost, st));
+    // one pinned landing place for the table, the flag and the objective
+    const size_t table_bytes = (size_t)L * pitch * sizeof(float);
+    HIP_TRY(ix->pin_table.ensure(table_bytes + 16));
+    float* padded = static_cast<float*>(ix->pin_table.p);
+    double* h_inertia = reinterpret_cast<double*>(static_cast<char*>(ix->pin_table.p) + table_bytes);   // table_bytes: a multiple of 128
+    int* h_flag = reinterpret_cast<int*>(h_inertia + 1);
+    HIP_TRY(hipMemcpyAsync(padded, cent, table_bytes, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(h_flag, flags, sizeof(int), hipMemcpyDeviceToHost, st));
+    if (niter > 0) HIP_TRY(hipMemcpyAsync(h_inertia, ix->w_gain.as<double>() + L, sizeof(double), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (*h_flag) return fail(IVFTQ_ZERO_NORM, "a training row has zero or non-finite norm");
     // success: the index takes the new table over (same stream, so later calls on it see the new centroids)
     HIP_TRY(hipMemcpyAsync(ix->cent.p, cent, table * sizeof(float), hipMemcpyDeviceToDevice, st));
     HIP_TRY(launch_fill_u32(ix->bias.as<uint32_t>(), ix->lpad, 0u, st));
@@ -892,7 +910,7 @@ ivftq_status ivftq_train_coarse(ivftq_index* ix, const float* x_dev, int64_t n, 
     for (int l = 0; l < L; ++l)
         std::memcpy(&ix->h_cent[(size_t)l * d], &padded[(size_t)l * pitch], sizeof(float) * d);
     ix->has_coarse = true;
-    if (inertia_out) *inertia_out = inertia;
+    if (inertia_out) *inertia_out = niter > 0 ? *h_inertia : std::nan("");
     return IVFTQ_OK;
 }
 
@@ -965,29 +983,6 @@ ivftq_status commit_rows(ivftq_index* ix, const std::vector<int64_t>& need, int6
     return IVFTQ_OK;
 }
 
-// Coarse assignment of n rows (Algorithm "Encode", nearest centroid by inner product): screening pass
-// plus the exact pass over the rows it left undecided.  w_flag[0] = a row without a usable norm,
-// w_flag[1] = number of undecided rows.
-constexpr int64_t kScreenShareRows = 1 << 19;     // beyond this the row tiles alone fill the chip
-ivftq_status assign_rows(ivftq_index* ix, const float* x_dev, int64_t n, int32_t* assign, hipStream_t st) {
-    // keys (8 bytes each) first, then the row numbers
-    HIP_TRY(ix->w_undecided.ensure((size_t)n * (sizeof(unsigned long long) + sizeof(int32_t))));
-    // short batches share the centroid stages out over several workgroups and need room for the partial results
-    float* part = nullptr;
-    if (n <= kScreenShareRows) {
-        HIP_TRY(ix->w_part.ensure((size_t)n * kScreenMaxShares * 3 * sizeof(float)));
-        part = ix->w_part.as<float>();
-    }
-    HIP_TRY(launch_fill_u32(ix->w_flag.as<uint32_t>(), 2, 0u, st));
-    HIP_TRY(timed(ix, st, P_ASSIGN, [&] {
-        return launch_coarse_screened(x_dev, n, ix->d, ix->cent_h.as<uint16_t>(), ix->cent_l.as<uint16_t>(), ix->dp,
-                                      ix->nlist, ix->lpad, assign, ix->w_flag.as<int>(),
-                                      reinterpret_cast<int32_t*>(ix->w_undecided.as<unsigned long long>() + n),
-                                      ix->w_undecided.as<unsigned long long>(), ix->w_flag.as<int>() + 1, part, st);
-    }));
-    return IVFTQ_OK;
-}
-
 }  // namespace
 
 ivftq_status ivftq_scan_stats(ivftq_index* ix, int64_t* queries_out, int64_t* redone_out, int64_t* max_candidates_out,
@@ -1036,7 +1031,7 @@ ivftq_status ivftq_encode_only(ivftq_index* ix, const float* x_dev, int64_t n, i
     hipStream_t st = use_stream(ix, stream);
     HIP_TRY(ix->w_assign.ensure((size_t)n * sizeof(int32_t)));
     int32_t* assign = assign_dev ? assign_dev : ix->w_assign.as<int32_t>();
-    { ivftq_status sa = assign_rows(ix, x_dev, n, assign, st); if (sa != IVFTQ_OK) return sa; }
+    { ivftq_status sa = assign_to_index(ix, x_dev, n, assign, st); if (sa != IVFTQ_OK) return sa; }
     if (codes_dev || gamma_dev) {
         EncodeArgs a{};
         a.x = x_dev; a.n = n; a.d = ix->d; a.b = ix->b;
@@ -1072,8 +1067,12 @@ ivftq_status ivftq_encode_only_noalloc(ivftq_index* ix, const float* x_dev, int6
     // the scratch keeps the previous call's contents: the counters start from zero, the keys and row numbers
     // are written before they are read (one entry per listed row)
     HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(flags), 2, 0u, st));
-    HIP_TRY(launch_coarse_screened(x_dev, n, ix->d, ix->cent_h.as<uint16_t>(), ix->cent_l.as<uint16_t>(), ix->dp,
-                                   ix->nlist, ix->lpad, assign, flags, row_list, row_key, flags + 1, nullptr, st));
+    ScreenArgs sc{};
+    sc.x = x_dev; sc.n = n; sc.d = ix->d;
+    sc.cent_h = ix->cent_h.as<uint16_t>(); sc.cent_l = ix->cent_l.as<uint16_t>(); sc.cent_pitch = ix->dp;
+    sc.L = ix->nlist; sc.Lpad = ix->lpad;
+    sc.assign = assign; sc.flag = flags; sc.row_list = row_list; sc.row_key = row_key; sc.row_count = flags + 1;
+    HIP_TRY(launch_coarse_screened(sc, st));
     if (codes_dev || gamma_dev) {
         EncodeArgs a{};
         a.x = x_dev; a.n = n; a.d = ix->d; a.b = ix->b;
@@ -1100,7 +1099,7 @@ ivftq_status ivftq_encode_add(ivftq_index* ix, const float* x_dev, int64_t n, co
 
     // 1. coarse assignment
     HIP_TRY(ix->w_assign.ensure((size_t)n * sizeof(int32_t)));
-    { ivftq_status sa = assign_rows(ix, x_dev, n, ix->w_assign.as<int32_t>(), st); if (sa != IVFTQ_OK) return sa; }
+    { ivftq_status sa = assign_to_index(ix, x_dev, n, ix->w_assign.as<int32_t>(), st); if (sa != IVFTQ_OK) return sa; }
 
     // 2.-4. room for the new vectors and the stable position of every row
     std::vector<int64_t> need;
@@ -1287,8 +1286,8 @@ ivftq_status check_query_args(const ivftq_index* ix, const float* q_dev, int64_t
 ivftq_status coarse_and_probe(ivftq_index* ix, const float* q, int64_t count, int nprobe, int32_t* probe,
                               float* coarse, hipStream_t st) {
     const int64_t ldS = round_up(ix->nlist, 4);
-    HIP_TRY(timed(ix, st, P_COARSE_SCORES, [&] { return launch_coarse(1, q, count, ix->d, ix->cent_h.as<uint16_t>(), ix->cent_l.as<uint16_t>(), ix->dp, nullptr, ix->nlist, ix->lpad, nullptr,
-                          nullptr, ix->w_S.as<float>(), ldS, ix->w_flag.as<int>(), st); }));
+    HIP_TRY(timed(ix, st, P_COARSE_SCORES, [&] { return launch_coarse(q, count, ix->d, ix->cent_h.as<uint16_t>(), ix->cent_l.as<uint16_t>(), ix->dp,
+                                                                           ix->lpad, ix->w_S.as<float>(), ldS, st); }));
     SelectArgs sa{};
     sa.vals = ix->w_S.as<float>(); sa.stride = ldS; sa.rows = count; sa.k = nprobe; sa.m_fixed = ix->nlist;
     sa.out_vals = coarse; sa.out_i32 = probe;

@@ -26,7 +26,7 @@ template <int DP>
 struct CoarseCfg {
     static constexpr int KB = DP / 16;
     static constexpr int LDH = DP + 8;       // halves per LDS row: the 16-byte pad keeps b128 reads conflict free
-    static constexpr size_t lds_bytes = (size_t)2 * kTN * LDH * sizeof(uint16_t) + kTN * sizeof(float);
+    static constexpr size_t lds_bytes = (size_t)2 * kTN * LDH * sizeof(uint16_t);
 };
 
 // hi[r][c], lo[r][c] = split float16 form of src[r][c]
@@ -76,39 +76,29 @@ __device__ __forceinline__ bool load_rows(const float* __restrict__ x, int64_t r
 // R = 32-row tiles per wavefront.  VEC4: rows are read 16 bytes at a time (d % 4 == 0, x 16-byte aligned).
 template <int DP, int R, bool VEC4>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_coarse(
-    int mode, const float* __restrict__ x, int64_t n, int d, const uint16_t* __restrict__ cent_h,
-    const uint16_t* __restrict__ cent_l, int cent_pitch, const float* __restrict__ bias, int L, int Lpad,
-    int32_t* __restrict__ assign, float* __restrict__ best_out, float* __restrict__ scores,
-    int64_t ld_scores, int* __restrict__ flag) {
+    const float* __restrict__ x, int64_t n, int d, const uint16_t* __restrict__ cent_h,
+    const uint16_t* __restrict__ cent_l, int cent_pitch, int Lpad, float* __restrict__ scores, int64_t ld_scores) {
     using Cfg = CoarseCfg<DP>;
     constexpr int KB = Cfg::KB;
     extern __shared__ unsigned char lds_raw[];
     uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [TN][LDH] hi parts of the centroid tile
     uint16_t* tl = th + kTN * Cfg::LDH;                               // [TN][LDH] lo parts
-    float* tile_bias = reinterpret_cast<float*>(tl + kTN * Cfg::LDH); // [TN]
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, j = lane & 31;
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (32 * R);
 
     half8 bh[R][KB], bl[R][KB];
-    bool good[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t row = row0 + 32 * r + j;
-        good[r] = load_rows<DP>(x, row, row < n, d, VEC4 ? 1 : 0, half, bh[r], bl[r]);
-        if (row < n && !good[r] && half == 0) atomicOr(flag, 1);
+        load_rows<DP>(x, row, row < n, d, VEC4 ? 1 : 0, half, bh[r], bl[r]);
     }
-
-    float best[R];
-    int best_idx[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) { best[r] = -__builtin_inff(); best_idx[r] = 0; }
     const uint16_t* ah_base = th + j * Cfg::LDH + 8 * half;
     const uint16_t* al_base = tl + j * Cfg::LDH + 8 * half;
     constexpr float kUnscale = 1.f / (kSplitScale * kSplitScale);
 
-    // gridDim.y workgroups share the centroid stages of one row block (score mode with few rows)
+    // gridDim.y workgroups share the centroid stages of one row block (few rows)
     const int stages = Lpad / kTN, per_y = (stages + (int)gridDim.y - 1) / (int)gridDim.y;
     const int c_lo = (int)blockIdx.y * per_y * kTN;
     const int c_hi = c_lo + per_y * kTN < Lpad ? c_lo + per_y * kTN : Lpad;
@@ -121,7 +111,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             *reinterpret_cast<uint4*>(th + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(cent_h + src);
             *reinterpret_cast<uint4*>(tl + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(cent_l + src);
         }
-        if (tid < kTN) tile_bias[tid] = bias ? bias[c0 + tid] : 0.f;
         __syncthreads();
 
         floatx16 acc[R][kNT];
@@ -146,64 +135,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             }
         }
 
-        if (mode == 0 && !bias && c0 + kTN <= L) {
-            // plain inner products, whole stage inside the table: compare the raw accumulators
-            // (the argmax does not depend on the common 2^20 scale); ascending c, first maximum wins
-#pragma unroll
-            for (int t = 0; t < kNT; ++t)
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const int c = c0 + t * 32 + 8 * (q / 4) + 4 * half + (q % 4);
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        if (acc[r][t][q] > best[r]) { best[r] = acc[r][t][q]; best_idx[r] = c; }
-                }
-        } else if (mode == 0) {
-#pragma unroll
-            for (int t = 0; t < kNT; ++t)
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const int i = 8 * (q / 4) + 4 * half + (q % 4);
-                    const int c = c0 + t * 32 + i;
-                    // with a bias the comparison is in true units; without, in accumulator units
-                    const float bi = tile_bias[t * 32 + i];
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        const float v = bias ? fmaf(acc[r][t][q], kUnscale, bi) : acc[r][t][q];
-                        if (c < L && v > best[r]) { best[r] = v; best_idx[r] = c; }
-                    }
-                }
-        } else {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int64_t row = row0 + 32 * r + j;
-                if (row >= n) continue;
-#pragma unroll
-                for (int t = 0; t < kNT; ++t)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int c = c0 + t * 32 + 8 * g + 4 * half;
-                        if (c < ld_scores) {
-                            float4 o = make_float4(acc[r][t][4 * g] * kUnscale, acc[r][t][4 * g + 1] * kUnscale,
-                                                   acc[r][t][4 * g + 2] * kUnscale, acc[r][t][4 * g + 3] * kUnscale);
-                            *reinterpret_cast<float4*>(scores + row * ld_scores + c) = o;
-                        }
-                    }
-            }
-        }
-    }
-
-    if (mode == 0) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float ob = __shfl_xor(best[r], 32);
-            const int oi = __shfl_xor(best_idx[r], 32);
-            if (ob > best[r] || (ob == best[r] && oi < best_idx[r])) { best[r] = ob; best_idx[r] = oi; }
             const int64_t row = row0 + 32 * r + j;
-            if (row < n && half == 0) {
-                if (assign) assign[row] = good[r] ? best_idx[r] : -1;
-                if (best_out) best_out[row] = bias ? best[r] : best[r] * kUnscale;
-            }
+            if (row >= n) continue;
+#pragma unroll
+            for (int t = 0; t < kNT; ++t)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int c = c0 + t * 32 + 8 * g + 4 * half;
+                    if (c < ld_scores) {
+                        float4 o = make_float4(acc[r][t][4 * g] * kUnscale, acc[r][t][4 * g + 1] * kUnscale,
+                                               acc[r][t][4 * g + 2] * kUnscale, acc[r][t][4 * g + 3] * kUnscale);
+                        *reinterpret_cast<float4*>(scores + row * ld_scores + c) = o;
+                    }
+                }
         }
     }
 }
@@ -222,7 +168,9 @@ template <int DP>
 constexpr int screen_nt() { return 2; }
 
 template <int DP>
-constexpr size_t screen_lds_bytes() { return (size_t)2 * screen_nt<DP>() * 32 * CoarseCfg<DP>::LDH * sizeof(uint16_t); }
+constexpr size_t screen_lds_bytes(bool bias) {
+    return (size_t)2 * screen_nt<DP>() * 32 * (CoarseCfg<DP>::LDH * sizeof(uint16_t) + (bias ? sizeof(float) : 0));
+}
 
 // max(a, b, c) and the middle of (a, b, c) as single instructions.  Written as instructions because the
 // scores carry a tag in their low bits (below) and are never NaN, so the quieting that the compiler puts
@@ -256,10 +204,12 @@ __device__ __forceinline__ float max3_raw(float a, float b, float c) {
 
 // VEC4: rows are read 16 bytes at a time (d % 4 == 0 and x 16-byte aligned); a template parameter so that
 // each instantiation carries one loading path only (with both, the loads of the prologue spill).
-template <int DP, int R, bool VEC4>
+// BIAS: the argmax is of <x~, c> + bias_c, |c| <= 1 (k-means: c a mean of unit vectors, bias_c = -|c|^2/2).  The
+// accumulators of a tile start at 2^20 bias_c; the error of the products is bounded as without it.
+template <int DP, int R, bool VEC4, bool BIAS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 || R == 1) ? 3 : 2))) void k_coarse_screen(
     const float* __restrict__ x, int64_t n, int d, const uint16_t* __restrict__ cent_h, int cent_pitch,
-    int L, int Lpad, int32_t* __restrict__ assign, int32_t* __restrict__ row_list,
+    const float* __restrict__ bias, int L, int Lpad, int32_t* __restrict__ assign, int32_t* __restrict__ row_list,
     unsigned long long* __restrict__ row_key, int* __restrict__ row_count, float* __restrict__ part) {
     using Cfg = CoarseCfg<DP>;
     constexpr int KB = Cfg::KB;
@@ -271,6 +221,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
     const int c_lo = (int)blockIdx.y * per_y * TN < Lpad ? (int)blockIdx.y * per_y * TN : Lpad;
     const int c_hi = c_lo + per_y * TN < Lpad ? c_lo + per_y * TN : Lpad;
     uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [2][TN][LDH] hi parts of the centroids
+    float* s_bias = reinterpret_cast<float*>(th + 2 * TN * Cfg::LDH);   // [2][TN] 2^20 bias (BIAS only)
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, j = lane & 31;
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (32 * R);
@@ -293,7 +244,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
     constexpr int kChunks = TN * (DP / 8);                          // 16-byte pieces of one stage
     constexpr int kPer = (kChunks + 255) / 256;
     uint4 pre[kPer];
+    float pre_bias = 0.f;
 #define IVFTQ_SCREEN_FETCH(C0)                                                                     \
+    if (BIAS) pre_bias = bias[(C0) + (tid & (TN - 1)) < Lpad ? (C0) + (tid & (TN - 1)) : Lpad - 1];  \
     _Pragma("unroll") for (int i = 0; i < kPer; ++i) {                                              \
         int e = tid + 256 * i;                                                                      \
         e = e < kChunks ? e : kChunks - 1;                                                          \
@@ -301,14 +254,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
         const int c = (C0) + r < Lpad ? (C0) + r : Lpad - 1; /* a stage may reach past the padded rows */ \
         pre[i] = *reinterpret_cast<const uint4*>(cent_h + (int64_t)c * cent_pitch + c8 * 8);        \
     }
-#define IVFTQ_SCREEN_STORE(BUF)                                                                    \
+#define IVFTQ_SCREEN_STORE(STAGE)                                                                  \
+    if (BIAS && tid < TN) s_bias[(STAGE) * TN + tid] = pre_bias * (kSplitScale * kSplitScale);       \
     _Pragma("unroll") for (int i = 0; i < kPer; ++i) {                                              \
         const int e = tid + 256 * i;                                                                \
         if (kChunks % 256 == 0 || e < kChunks)                                                      \
-            *reinterpret_cast<uint4*>((BUF) + (e / (DP / 8)) * Cfg::LDH + (e % (DP / 8)) * 8) = pre[i]; \
+            *reinterpret_cast<uint4*>(th + (STAGE) * (TN * Cfg::LDH) + (e / (DP / 8)) * Cfg::LDH + (e % (DP / 8)) * 8) = pre[i]; \
     }
     IVFTQ_SCREEN_FETCH(c_lo)
-    IVFTQ_SCREEN_STORE(th)
+    IVFTQ_SCREEN_STORE(0)
     __syncthreads();
     int stage = 0;
     for (int c0 = c_lo; c0 < c_hi; c0 += TN, stage ^= 1) {
@@ -329,10 +283,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             floatx16 acc[R];
+            if constexpr (BIAS) {
 #pragma unroll
-            for (int r = 0; r < R; ++r)
+                for (int g = 0; g < 4; ++g) {       // accumulator 4g + i of a lane: centroid 8g + 4*half + i of the tile
+                    const float4 b4 = *reinterpret_cast<const float4*>(s_bias + stage * TN + t * 32 + 8 * g + 4 * half);
 #pragma unroll
-                for (int q = 0; q < 16; ++q) acc[r][q] = 0.f;
+                    for (int r = 0; r < R; ++r) {
+                        acc[r][4 * g] = b4.x; acc[r][4 * g + 1] = b4.y;
+                        acc[r][4 * g + 2] = b4.z; acc[r][4 * g + 3] = b4.w;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) acc[r][q] = 0.f;
+            }
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 const half8 a = kAhead ? ah[kAhead ? kb : 0]
@@ -354,7 +320,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
         // which stage the best came from is seen from whether the stage changed it
 #pragma unroll
         for (int r = 0; r < R; ++r) best_c0[r] = best[r] != prev[r] ? c0 : best_c0[r];
-        IVFTQ_SCREEN_STORE(th + (stage ^ 1) * (TN * Cfg::LDH))
+        IVFTQ_SCREEN_STORE(stage ^ 1)
         __syncthreads();
     }
 #undef IVFTQ_SCREEN_FETCH
@@ -429,7 +395,7 @@ __global__ void k_coarse_screen_join(const float* __restrict__ part, int64_t n, 
 template <int DP, bool VEC4>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_coarse_resolve(
     const float* __restrict__ x, int d, const uint16_t* __restrict__ cent_h,
-    const uint16_t* __restrict__ cent_l, int cent_pitch, int L, int Lpad, const int32_t* __restrict__ row_list,
+    const uint16_t* __restrict__ cent_l, int cent_pitch, const float* __restrict__ bias, int L, int Lpad, const int32_t* __restrict__ row_list,
     const int* __restrict__ row_count, unsigned long long* __restrict__ row_key) {
     using Cfg = CoarseCfg<DP>;
     constexpr int KB = Cfg::KB;
@@ -476,13 +442,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[kb], acc[t], 0, 0, 0);
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[kb], acc[t], 0, 0, 0);
                 }
-            // raw accumulators (the argmax does not depend on the common 2^20 scale); ascending c, first maximum wins
+            // raw accumulators (the argmax does not depend on the common 2^20 scale), or with a bias true units;
+            // ascending c, first maximum wins
 #pragma unroll
             for (int t = 0; t < kNT; ++t)
 #pragma unroll
                 for (int q = 0; q < 16; ++q) {
                     const int c = c0 + t * 32 + 8 * (q / 4) + 4 * half + (q % 4);
-                    if (c < L && acc[t][q] > best) { best = acc[t][q]; best_idx = c; }
+                    const float v = bias ? fmaf(acc[t][q], 1.f / (kSplitScale * kSplitScale), bias[c]) : acc[t][q];
+                    if (c < L && v > best) { best = v; best_idx = c; }
                 }
         }
         const float ob = __shfl_xor(best, 32);
@@ -508,57 +476,48 @@ __global__ void k_coarse_resolve_write(const int32_t* __restrict__ row_list, con
 }
 
 // RS = 32-row tiles per wavefront of the screening kernel
-template <int DP, int RS>
-hipError_t run_screened(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l, int cent_pitch,
-                        int L, int Lpad, int32_t* assign, int* flag, int32_t* row_list, unsigned long long* row_key,
-                        int* row_count, float* part, hipStream_t st) {
-    static LdsLimit lim_screen[2], lim_resolve[2];
-    const size_t lds_screen = screen_lds_bytes<DP>();
+template <int DP, int RS, bool VEC4, bool BIAS>
+hipError_t run_screened_as(const ScreenArgs& a, hipStream_t st) {
+    static LdsLimit lim_screen, lim_resolve;
+    const size_t lds_screen = screen_lds_bytes<DP>(BIAS);
     const size_t lds = (size_t)2 * kTN * CoarseCfg<DP>::LDH * sizeof(uint16_t);
-    const int vec4 = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(x) % 16 == 0);
-    hipError_t e = vec4 ? lim_screen[1].ensure(reinterpret_cast<const void*>(k_coarse_screen<DP, RS, true>), lds_screen)
-                        : lim_screen[0].ensure(reinterpret_cast<const void*>(k_coarse_screen<DP, RS, false>), lds_screen);
-    if (e == hipSuccess)
-        e = vec4 ? lim_resolve[1].ensure(reinterpret_cast<const void*>(k_coarse_resolve<DP, true>), lds)
-                 : lim_resolve[0].ensure(reinterpret_cast<const void*>(k_coarse_resolve<DP, false>), lds);
+    hipError_t e = lim_screen.ensure(reinterpret_cast<const void*>(k_coarse_screen<DP, RS, VEC4, BIAS>), lds_screen);
+    if (e == hipSuccess) e = lim_resolve.ensure(reinterpret_cast<const void*>(k_coarse_resolve<DP, VEC4>), lds);
     if (e != hipSuccess) return e;
-    const int64_t blocks_s = (n + 4 * 32 * RS - 1) / (4 * 32 * RS);
+    const int64_t blocks_s = (a.n + 4 * 32 * RS - 1) / (4 * 32 * RS);
     // A short batch gives few workgroups, each walking every centroid stage on its own (90 us at 4096
     // centroids however few rows there are): with room for the partial results the stages are shared out
     // over gridDim.y until about 1024 workgroups are in the launch, at least two stages each.
     int shares = 1;
-    if (part)
-        while (shares < kScreenMaxShares && blocks_s * shares < 1024 && (Lpad / (screen_nt<DP>() * 32)) >= 4 * shares) shares *= 2;
-    const dim3 grid_s((unsigned)blocks_s, (unsigned)shares);
-    if (vec4)
-        hipLaunchKernelGGL((k_coarse_screen<DP, RS, true>), grid_s, dim3(256), lds_screen, st, x, n, d,
-                           cent_h, cent_pitch, L, Lpad, assign, row_list, row_key, row_count, part);
-    else
-        hipLaunchKernelGGL((k_coarse_screen<DP, RS, false>), grid_s, dim3(256), lds_screen, st, x, n, d,
-                           cent_h, cent_pitch, L, Lpad, assign, row_list, row_key, row_count, part);
+    if (a.part)
+        while (shares < kScreenMaxShares && blocks_s * shares < 1024 && (a.Lpad / (screen_nt<DP>() * 32)) >= 4 * shares) shares *= 2;
+    hipLaunchKernelGGL((k_coarse_screen<DP, RS, VEC4, BIAS>), dim3((unsigned)blocks_s, (unsigned)shares), dim3(256), lds_screen, st, a.x, a.n, a.d,
+                       a.cent_h, a.cent_pitch, a.bias, a.L, a.Lpad, a.assign, a.row_list, a.row_key, a.row_count, a.part);
     if (shares > 1)
-        hipLaunchKernelGGL(k_coarse_screen_join, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const float*)part, n, shares,
-                           assign, row_list, row_key, row_count);
+        hipLaunchKernelGGL(k_coarse_screen_join, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, (const float*)a.part, a.n, shares,
+                           a.assign, a.row_list, a.row_key, a.row_count);
     // the undecided rows: about four centroid stages per workgroup, at most 512 x 16 workgroups
-    const int stages = Lpad / kTN;
+    const int stages = a.Lpad / kTN;
     const int ysplit = std::min(16, (stages + 3) / 4);
-    const int64_t row_blocks = (n + 127) / 128;
+    const int64_t row_blocks = (a.n + 127) / 128;
     const dim3 grid_r((unsigned)std::min<int64_t>(row_blocks, 512), (unsigned)ysplit);
-    if (vec4)
-        hipLaunchKernelGGL((k_coarse_resolve<DP, true>), grid_r, dim3(256), lds, st, x, d, cent_h, cent_l, cent_pitch, L, Lpad,
-                           (const int32_t*)row_list, (const int*)row_count, row_key);
-    else
-        hipLaunchKernelGGL((k_coarse_resolve<DP, false>), grid_r, dim3(256), lds, st, x, d, cent_h, cent_l, cent_pitch, L, Lpad,
-                           (const int32_t*)row_list, (const int*)row_count, row_key);
-    hipLaunchKernelGGL(k_coarse_resolve_write, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 256)), dim3(256), 0, st,
-                       (const int32_t*)row_list, (const int*)row_count, (const unsigned long long*)row_key, assign, flag);
+    hipLaunchKernelGGL((k_coarse_resolve<DP, VEC4>), grid_r, dim3(256), lds, st, a.x, a.d, a.cent_h, a.cent_l, a.cent_pitch, a.bias, a.L, a.Lpad,
+                       (const int32_t*)a.row_list, (const int*)a.row_count, a.row_key);
+    hipLaunchKernelGGL(k_coarse_resolve_write, dim3((unsigned)std::min<int64_t>((a.n + 255) / 256, 256)), dim3(256), 0, st,
+                       (const int32_t*)a.row_list, (const int*)a.row_count, (const unsigned long long*)a.row_key, a.assign, a.flag);
     return hipGetLastError();
 }
 
+template <int DP, int RS>
+hipError_t run_screened(const ScreenArgs& a, hipStream_t st) {
+    const bool vec4 = (a.d % 4 == 0) && (reinterpret_cast<uintptr_t>(a.x) % 16 == 0);
+    if (a.bias) return vec4 ? run_screened_as<DP, RS, true, true>(a, st) : run_screened_as<DP, RS, false, true>(a, st);
+    return vec4 ? run_screened_as<DP, RS, true, false>(a, st) : run_screened_as<DP, RS, false, false>(a, st);
+}
+
 template <int DP, int R>
-hipError_t run(int mode, const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l,
-               int cent_pitch, const float* bias, int L, int Lpad, int32_t* assign, float* best, float* scores,
-               int64_t ld_scores, int* flag, hipStream_t st) {
+hipError_t run(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l, int cent_pitch, int Lpad,
+               float* scores, int64_t ld_scores, hipStream_t st) {
     static LdsLimit lim[2];
     const size_t lds = CoarseCfg<DP>::lds_bytes;
     const int64_t rows_per_wg = 4 * 32 * R;
@@ -567,17 +526,16 @@ hipError_t run(int mode, const float* x, int64_t n, int d, const uint16_t* cent_
     const hipError_t e = vec4 ? lim[1].ensure(reinterpret_cast<const void*>(k_coarse<DP, R, true>), lds)
                               : lim[0].ensure(reinterpret_cast<const void*>(k_coarse<DP, R, false>), lds);
     if (e != hipSuccess) return e;
-    // score mode: every (row, centroid) result is independent, so when the rows alone do not fill
-    // the chip the centroid stages are split over gridDim.y as well
+    // every (row, centroid) result is independent, so when the rows alone do not fill the chip the
+    // centroid stages are split over gridDim.y as well
     int ysplit = 1;
-    if (mode == 1)
-        while (blocks * ysplit < 512 && ysplit * 2 <= Lpad / kTN) ysplit *= 2;
+    while (blocks * ysplit < 512 && ysplit * 2 <= Lpad / kTN) ysplit *= 2;
     if (vec4)
-        hipLaunchKernelGGL((k_coarse<DP, R, true>), dim3((unsigned)blocks, (unsigned)ysplit), dim3(256), lds, st, mode, x, n, d,
-                           cent_h, cent_l, cent_pitch, bias, L, Lpad, assign, best, scores, ld_scores, flag);
+        hipLaunchKernelGGL((k_coarse<DP, R, true>), dim3((unsigned)blocks, (unsigned)ysplit), dim3(256), lds, st, x, n, d,
+                           cent_h, cent_l, cent_pitch, Lpad, scores, ld_scores);
     else
-        hipLaunchKernelGGL((k_coarse<DP, R, false>), dim3((unsigned)blocks, (unsigned)ysplit), dim3(256), lds, st, mode, x, n, d,
-                           cent_h, cent_l, cent_pitch, bias, L, Lpad, assign, best, scores, ld_scores, flag);
+        hipLaunchKernelGGL((k_coarse<DP, R, false>), dim3((unsigned)blocks, (unsigned)ysplit), dim3(256), lds, st, x, n, d,
+                           cent_h, cent_l, cent_pitch, Lpad, scores, ld_scores);
     return hipGetLastError();
 }
 
@@ -636,27 +594,24 @@ hipError_t launch_split_transposed(const float* src, int n, uint16_t* hi, uint16
     return hipGetLastError();
 }
 
-hipError_t launch_coarse_screened(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l,
-                                  int cent_pitch, int L, int Lpad, int32_t* assign, int* flag, int32_t* row_list,
-                                  unsigned long long* row_key, int* row_count, float* part, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    switch (coarse_dp(d)) {
-#define IVFTQ_CASE(DPV, RS) \
-    case DPV: return run_screened<DPV, RS>(x, n, d, cent_h, cent_l, cent_pitch, L, Lpad, assign, flag, row_list, row_key, row_count, part, st);
-        IVFTQ_CASE(32, 2) IVFTQ_CASE(64, 2) IVFTQ_CASE(96, 2) IVFTQ_CASE(128, 2) IVFTQ_CASE(160, 2)
-        IVFTQ_CASE(192, 2) IVFTQ_CASE(208, 2) IVFTQ_CASE(224, 2) IVFTQ_CASE(256, 2)
+hipError_t launch_coarse_screened(const ScreenArgs& a, hipStream_t st) {
+    if (a.n <= 0) return hipSuccess;
+    switch (coarse_dp(a.d)) {
+#define IVFTQ_CASE(DPV) \
+    case DPV: return run_screened<DPV, 2>(a, st);
+        IVFTQ_CASE(32) IVFTQ_CASE(64) IVFTQ_CASE(96) IVFTQ_CASE(128) IVFTQ_CASE(160)
+        IVFTQ_CASE(192) IVFTQ_CASE(208) IVFTQ_CASE(224) IVFTQ_CASE(256)
 #undef IVFTQ_CASE
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_coarse(int mode, const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l,
-                         int cent_pitch, const float* bias, int L, int Lpad, int32_t* assign, float* best,
-                         float* scores, int64_t ld_scores, int* flag, hipStream_t st) {
+hipError_t launch_coarse(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l, int cent_pitch,
+                         int Lpad, float* scores, int64_t ld_scores, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     switch (coarse_dp(d)) {
 #define IVFTQ_CASE(DPV, RV) \
-    case DPV: return run<DPV, RV>(mode, x, n, d, cent_h, cent_l, cent_pitch, bias, L, Lpad, assign, best, scores, ld_scores, flag, st);
+    case DPV: return run<DPV, RV>(x, n, d, cent_h, cent_l, cent_pitch, Lpad, scores, ld_scores, st);
         IVFTQ_CASE(32, 2) IVFTQ_CASE(64, 2) IVFTQ_CASE(96, 2) IVFTQ_CASE(128, 2) IVFTQ_CASE(160, 1)
         IVFTQ_CASE(192, 1) IVFTQ_CASE(208, 1) IVFTQ_CASE(224, 1) IVFTQ_CASE(256, 1)
 #undef IVFTQ_CASE

@@ -73,23 +73,27 @@ struct ListStore {
 
 // ---- contraction kernels (split float16 MFMA) --------------------------------------------------------
 
-// mode 0: assign[i] = argmax_c (<x~_i, cent_c> + bias_c), best[i] that value (either may be null)
-// mode 1: scores[i*ld_scores + c] = <x~_i, cent_c> for c < L
-// x: n x d raw rows (normalised inside).  cent_h / cent_l: split float16 form of the centroid table
-// [Lpad][cent_pitch], zero padded, Lpad % 64 == 0 (made by launch_split_rows).
-// flag: set to 1 when a row has zero or non-finite norm (that row gets assign -1).
-hipError_t launch_coarse(int mode, const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l,
-                         int cent_pitch, const float* bias, int L, int Lpad, int32_t* assign, float* best,
-                         float* scores, int64_t ld_scores, int* flag, hipStream_t st);
-// The argmax of mode 0 (no bias) in two steps: a screening pass with the hi*hi products alone decides
-// every row whose best score is clearly ahead, the rest (listed in row_list, counted in *row_count,
-// which the caller clears) is redone with all three products.  assign as for launch_coarse.  row_list
+// scores[i*ld_scores + c] = <x~_i, cent_c> for every c below ld_scores
+// x: n x d raw rows (normalised inside; the scores of a row without a usable norm are not numbers or zero).
+// cent_h / cent_l: split float16 form of the centroid table [Lpad][cent_pitch], zero padded, Lpad % 64 == 0
+// (made by launch_split_rows).
+hipError_t launch_coarse(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l, int cent_pitch,
+                         int Lpad, float* scores, int64_t ld_scores, hipStream_t st);
+// assign[i] = argmax_c (<x~_i, cent_c> + bias_c), -1 (and *flag = 1) for a row of zero or non-finite norm, in
+// two steps: a screening pass with the hi*hi products alone decides every row whose best score is clearly
+// ahead, the rest (listed in row_list, counted in *row_count, which the caller clears) is redone with all three
+// products.  row_list
 // and row_key are scratch arrays of n entries.  part (may be null): 3 * kScreenMaxShares floats of scratch
 // per row; with it a short batch shares the centroid stages out over several workgroups per row tile.
+// bias may be null (all zero); the centroids' norms must not exceed 1.
 constexpr int kScreenMaxShares = 16;
-hipError_t launch_coarse_screened(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l,
-                                  int cent_pitch, int L, int Lpad, int32_t* assign, int* flag, int32_t* row_list,
-                                  unsigned long long* row_key, int* row_count, float* part, hipStream_t st);
+struct ScreenArgs {
+    const float* x; int64_t n; int d;
+    const uint16_t* cent_h; const uint16_t* cent_l; int cent_pitch;
+    const float* bias; int L; int Lpad;
+    int32_t* assign; int* flag; int32_t* row_list; unsigned long long* row_key; int* row_count; float* part;
+};
+hipError_t launch_coarse_screened(const ScreenArgs& a, hipStream_t st);
 // hi[i], lo[i] = split float16 form of src[i]
 hipError_t launch_split_rows(const float* src, int64_t count, uint16_t* hi, uint16_t* lo, hipStream_t st);
 // hi[c][r], lo[c][r] = split float16 form of src[r][c] (n x n)
@@ -173,19 +177,28 @@ hipError_t launch_gather_rows(const float* src, int d, const int64_t* idx, int64
 // out[l] = sum of count[l'] over l' < l (L <= kMaxList)
 hipError_t launch_exclusive_scan(const uint32_t* count, int L, int64_t* out, hipStream_t st);
 // sums[l][j] = sum of x~_ij over the rows order[base[l] .. base[l] + count[l]) of cell l, added in a fixed
-// order (bit-reproducible); rows are normalised on the fly
+// order (bit-reproducible); rows are normalised on the fly.  gain (may be null): gain[l] = <sums[l], cent[l]> +
+// count[l] * bias[l], the cell's share of the sum of best scores.
 hipError_t launch_kmeans_cell_sums(const float* x, int d, const int32_t* order, const int64_t* base,
-                                   const uint32_t* count, int L, float* sums, int pitch, hipStream_t st);
-// cent[l] = sums[l]/counts[l] for non-empty cells; bias[l] = -|cent_l|^2/2 (padding rows: bias -inf)
+                                   const uint32_t* count, int L, float* sums, int pitch, const float* cent,
+                                   const float* bias, double* gain, hipStream_t st);
+// cent[l] = sums[l]/counts[l] for non-empty cells; bias[l] = -|cent_l|^2/2 (padding rows: bias -inf); cent_h / cent_l:
+// the split float16 form of the new rows.  count may be null (every cell counts as empty: bias and split form only).
 hipError_t launch_kmeans_update(float* cent, int pitch, const float* sums, const uint32_t* counts,
-                                float* bias, int L, int Lpad, int d, hipStream_t st);
+                                float* bias, uint16_t* cent_h, uint16_t* cent_l, int L, int Lpad, int d, hipStream_t st);
+// Every empty cell becomes a copy of a random member of the largest cell (the first of them, when several are as
+// large): the t-th one, in ascending order, of the member that draw *drawn + t of the splitmix64 sequence of `seed`
+// picks; *drawn is then advanced.  order / base / count as above.  Also clears *row_count.
+hipError_t launch_kmeans_reseed(const float* x, int d, const int32_t* order, const int64_t* base, const uint32_t* count,
+                                int L, float* cent, int pitch, float* bias, uint16_t* cent_h, uint16_t* cent_l,
+                                uint64_t seed, unsigned long long* drawn, int* row_count, hipStream_t st);
 // cent[dst[t]] = normalised row src_row[t] of x
 hipError_t launch_copy_rows_normalised(const float* x, int d, const int64_t* src_row, const int32_t* dst,
                                        int count, float* cent, int pitch, hipStream_t st);
 // normalise centroid rows in place; bias <- 0 for real rows
 hipError_t launch_normalise_centroids(float* cent, int pitch, float* bias, int L, int d, hipStream_t st);
-// sum over rows of (1 - 2*best_i) in double
-hipError_t launch_inertia(const float* best, int64_t n, double* out, hipStream_t st);
+// *out = n - 2 * sum of gain[l], added in a fixed order
+hipError_t launch_inertia(const double* gain, int L, int64_t n, double* out, hipStream_t st);
 
 // ---- search -----------------------------------------------------------------------------------
 

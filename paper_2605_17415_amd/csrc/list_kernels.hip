@@ -203,56 +203,161 @@ __global__ __launch_bounds__(1024) void k_exclusive_scan(const uint32_t* __restr
 // Sum of the normalised rows of each cell, in a fixed order: workgroup l walks the rows
 // order[base[l] .. base[l] + count[l]) of its cell, wavefront w taking every fourth row from the w-th on,
 // a lane the coordinates lane, lane + 64, ...; the four partial sums are then added in the order 0, 1, 2, 3.
-// Nothing depends on scheduling, so the same input gives the same bits on every run.
+// Nothing depends on scheduling, so the same input gives the same bits on every run.  Bound by the latency of
+// gathering rows: four rows of a wavefront are read together (500k x 96 over 4096 cells: 0.12 -> 0.09 ms).
 __global__ __launch_bounds__(256) void k_kmeans_cell_sums(const float* __restrict__ x, int d,
                                                           const int32_t* __restrict__ order,
                                                           const int64_t* __restrict__ base,
                                                           const uint32_t* __restrict__ count,
-                                                          float* __restrict__ sums, int pitch) {
+                                                          float* __restrict__ sums, int pitch,
+                                                          const float* __restrict__ cent, const float* __restrict__ bias,
+                                                          double* __restrict__ gain) {
     __shared__ float part[4][kMaxD];
+    __shared__ double part_gain[4];
+    constexpr int T = kMaxD / 64, U = 4;
     const int l = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t first = base[l];
     const int cnt = (int)count[l];
-    float acc[kMaxD / 64];
+    float acc[T];
 #pragma unroll
-    for (int t = 0; t < kMaxD / 64; ++t) acc[t] = 0.f;
-    for (int p = wave; p < cnt; p += 4) {
-        const float* row = x + (int64_t)order[first + p] * d;
-        float v[kMaxD / 64];
-        float n2 = 0.f;
+    for (int t = 0; t < T; ++t) acc[t] = 0.f;
+    for (int p = wave; p < cnt; p += 4 * U) {
+        float v[U][T], n2[U];
 #pragma unroll
-        for (int t = 0; t < kMaxD / 64; ++t) {
-            const int j = lane + 64 * t;
-            v[t] = j < d ? row[j] : 0.f;
-            n2 += v[t] * v[t];
+        for (int u = 0; u < U; ++u) {
+            const int pu = p + 4 * u < cnt ? p + 4 * u : p;
+            const float* row = x + (int64_t)order[first + pu] * d;
+            n2[u] = 0.f;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int j = lane + 64 * t;
+                v[u][t] = 64 * t < d ? row[j < d ? j : d - 1] : 0.f;
+                if (j >= d) v[u][t] = 0.f;
+                n2[u] += v[u][t] * v[u][t];
+            }
         }
-        for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
-        const float nrm = sqrtf(n2);
+        for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-        for (int t = 0; t < kMaxD / 64; ++t) acc[t] += v[t] / nrm;
+            for (int u = 0; u < U; ++u) n2[u] += __shfl_xor(n2[u], o);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (p + 4 * u >= cnt) break;
+            const float nrm = sqrtf(n2[u]);
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (64 * t < d) acc[t] += v[u][t] / nrm;
+        }
     }
 #pragma unroll
-    for (int t = 0; t < kMaxD / 64; ++t) part[wave][lane + 64 * t] = acc[t];
+    for (int t = 0; t < T; ++t) part[wave][lane + 64 * t] = acc[t];
     __syncthreads();
-    for (int j = threadIdx.x; j < d; j += 256)
-        sums[(int64_t)l * pitch + j] = ((part[0][j] + part[1][j]) + part[2][j]) + part[3][j];
+    double g = 0.0;
+    for (int j = threadIdx.x; j < d; j += 256) {
+        const float s = ((part[0][j] + part[1][j]) + part[2][j]) + part[3][j];
+        sums[(int64_t)l * pitch + j] = s;
+        if (gain) g += (double)s * (double)cent[(int64_t)l * pitch + j];
+    }
+    if (gain) {                                      // uniform
+        for (int o = 32; o > 0; o >>= 1) g += __shfl_xor(g, o);
+        if (lane == 0) part_gain[wave] = g;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            gain[l] = ((part_gain[0] + part_gain[1]) + part_gain[2]) + part_gain[3] + (cnt ? (double)cnt * (double)bias[l] : 0.0);
+    }
+}
+
+// The bias of a centroid row and the row's split form, by one wavefront; the order of the sum is the same everywhere.
+__device__ __forceinline__ void finish_centroid(const float* __restrict__ row, int d, int lane, float* __restrict__ bias,
+                                                uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
+    float n2 = 0.f;
+    for (int j = lane; j < d; j += 64) {
+        const float v = row[j];
+        n2 += v * v;
+        _Float16 h, l;
+        split_scaled(v, h, l);
+        hi[j] = __builtin_bit_cast(uint16_t, h);
+        lo[j] = __builtin_bit_cast(uint16_t, l);
+    }
+    for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+    if (lane == 0) *bias = -0.5f * n2;
 }
 
 __global__ __launch_bounds__(64) void k_kmeans_update(float* __restrict__ cent, int pitch,
                                                       const float* __restrict__ sums,
                                                       const uint32_t* __restrict__ counts,
-                                                      float* __restrict__ bias, int L, int d) {
+                                                      float* __restrict__ bias, uint16_t* __restrict__ cent_h,
+                                                      uint16_t* __restrict__ cent_l, int L, int d) {
     const int l = blockIdx.x, lane = threadIdx.x;
-    if (l >= L) { if (lane == 0) bias[l] = -__builtin_inff(); return; }
-    const uint32_t c = counts[l];
-    float n2 = 0.f;
-    for (int j = lane; j < d; j += 64) {
-        float v = cent[(int64_t)l * pitch + j];
-        if (c > 0) { v = sums[(int64_t)l * pitch + j] / (float)c; cent[(int64_t)l * pitch + j] = v; }
-        n2 += v * v;
+    const int64_t at = (int64_t)l * pitch;
+    for (int j = d + lane; j < pitch; j += 64) { cent_h[at + j] = 0; cent_l[at + j] = 0; }    // padding columns
+    if (l >= L) {
+        for (int j = lane; j < d; j += 64) { cent_h[at + j] = 0; cent_l[at + j] = 0; }
+        if (lane == 0) bias[l] = -__builtin_inff();
+        return;
     }
-    for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
-    if (lane == 0) bias[l] = -0.5f * n2;
+    const uint32_t c = counts ? counts[l] : 0u;
+    if (c > 0)
+        for (int j = lane; j < d; j += 64) cent[at + j] = sums[at + j] / (float)c;            // a lane reads back its own values
+    finish_centroid(cent + at, d, lane, bias + l, cent_h + at, cent_l + at);
+}
+
+// One workgroup: most iterations have no empty cell and leave after the first look at the counts.
+__global__ __launch_bounds__(1024) void k_kmeans_reseed(const float* __restrict__ x, int d, const int32_t* __restrict__ order,
+                                                        const int64_t* __restrict__ base, const uint32_t* __restrict__ count,
+                                                        int L, float* __restrict__ cent, int pitch, float* __restrict__ bias,
+                                                        uint16_t* __restrict__ cent_h, uint16_t* __restrict__ cent_l,
+                                                        uint64_t seed, unsigned long long* __restrict__ drawn,
+                                                        int* __restrict__ row_count) {
+    __shared__ unsigned long long s_big;              // largest count, then smallest cell number
+    __shared__ uint32_t s_part[1024];
+    __shared__ uint16_t s_empty[kMaxList];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (L + 1023) / 1024, lo = tid * per < L ? tid * per : L, hi = lo + per < L ? lo + per : L;
+    if (tid == 0) { s_big = 0; *row_count = 0; }
+    uint32_t empty = 0;
+    unsigned long long big = 0;
+    for (int l = lo; l < hi; ++l) {
+        const uint32_t c = count[l];
+        empty += c == 0;
+        const unsigned long long key = ((unsigned long long)c << 32) | (0xFFFFFFFFu - (uint32_t)l);
+        big = key > big ? key : big;
+    }
+    if (!__syncthreads_or(empty != 0)) return;
+    atomicMax(&s_big, big);
+    s_part[tid] = empty;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+        const uint32_t add = tid >= o ? s_part[tid - o] : 0;
+        __syncthreads();
+        s_part[tid] += add;
+        __syncthreads();
+    }
+    uint32_t at = s_part[tid] - empty;
+    for (int l = lo; l < hi; ++l)
+        if (count[l] == 0) s_empty[at++] = (uint16_t)l;
+    __syncthreads();
+    const uint32_t total = s_part[1023];
+    const int from = (int)(0xFFFFFFFFu - (uint32_t)(s_big & 0xFFFFFFFFull));
+    const uint64_t members = s_big >> 32, before = *drawn;
+    if (members == 0) return;                         // no row has a cell (none has a usable norm): the call fails
+    __syncthreads();
+    if (tid == 0) *drawn = before + total;
+    for (uint32_t t = wave; t < total; t += 16) {
+        // draw number before + t of splitmix64 started at `seed`
+        uint64_t z = seed + (before + t + 1) * 0x9E3779B97F4A7C15ull;
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        z ^= z >> 31;
+        const float* row = x + (int64_t)order[base[from] + (int64_t)(z % members)] * d;
+        const int l = s_empty[t];
+        float n2 = 0.f;
+        for (int j = lane; j < d; j += 64) { const float v = row[j]; n2 += v * v; }
+        for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+        const float nrm = sqrtf(n2);
+        float* c = cent + (int64_t)l * pitch;
+        for (int j = lane; j < d; j += 64) c[j] = nrm > 0.f ? row[j] / nrm : 0.f;
+        finish_centroid(c, d, lane, bias + l, cent_h + (int64_t)l * pitch, cent_l + (int64_t)l * pitch);
+    }
 }
 
 __global__ __launch_bounds__(64) void k_copy_rows_normalised(const float* __restrict__ x, int d,
@@ -517,17 +622,17 @@ __global__ __launch_bounds__(64) void k_normalise_centroids(float* __restrict__ 
 }
 
 // Deterministic: one workgroup, fixed summation order.
-__global__ __launch_bounds__(256) void k_inertia(const float* __restrict__ best, int64_t n, double* out) {
+__global__ __launch_bounds__(256) void k_inertia(const double* __restrict__ gain, int L, int64_t n, double* out) {
     __shared__ double part[256];
     double s = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) s += 1.0 - 2.0 * (double)best[i];
+    for (int l = threadIdx.x; l < L; l += 256) s += gain[l];
     part[threadIdx.x] = s;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if (threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *out = part[0];
+    if (threadIdx.x == 0) *out = (double)n - 2.0 * part[0];
 }
 
 template <int DP>
@@ -588,15 +693,25 @@ hipError_t launch_exclusive_scan(const uint32_t* count, int L, int64_t* out, hip
 }
 
 hipError_t launch_kmeans_cell_sums(const float* x, int d, const int32_t* order, const int64_t* base,
-                                   const uint32_t* count, int L, float* sums, int pitch, hipStream_t st) {
+                                   const uint32_t* count, int L, float* sums, int pitch, const float* cent,
+                                   const float* bias, double* gain, hipStream_t st) {
     if (d > kMaxD) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_kmeans_cell_sums, dim3(L), dim3(256), 0, st, x, d, order, base, count, sums, pitch);
+    hipLaunchKernelGGL(k_kmeans_cell_sums, dim3(L), dim3(256), 0, st, x, d, order, base, count, sums, pitch, cent, bias, gain);
     return hipGetLastError();
 }
 
 hipError_t launch_kmeans_update(float* cent, int pitch, const float* sums, const uint32_t* counts,
-                                float* bias, int L, int Lpad, int d, hipStream_t st) {
-    hipLaunchKernelGGL(k_kmeans_update, dim3(Lpad), dim3(64), 0, st, cent, pitch, sums, counts, bias, L, d);
+                                float* bias, uint16_t* cent_h, uint16_t* cent_l, int L, int Lpad, int d, hipStream_t st) {
+    hipLaunchKernelGGL(k_kmeans_update, dim3(Lpad), dim3(64), 0, st, cent, pitch, sums, counts, bias, cent_h, cent_l, L, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_kmeans_reseed(const float* x, int d, const int32_t* order, const int64_t* base, const uint32_t* count,
+                                int L, float* cent, int pitch, float* bias, uint16_t* cent_h, uint16_t* cent_l,
+                                uint64_t seed, unsigned long long* drawn, int* row_count, hipStream_t st) {
+    if (L < 1 || L > kMaxList) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_kmeans_reseed, dim3(1), dim3(1024), 0, st, x, d, order, base, count, L, cent, pitch, bias, cent_h, cent_l, seed,
+                       drawn, row_count);
     return hipGetLastError();
 }
 
@@ -636,8 +751,8 @@ hipError_t launch_normalise_centroids(float* cent, int pitch, float* bias, int L
     return hipGetLastError();
 }
 
-hipError_t launch_inertia(const float* best, int64_t n, double* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_inertia, dim3(1), dim3(256), 0, st, best, n, out);
+hipError_t launch_inertia(const double* gain, int L, int64_t n, double* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_inertia, dim3(1), dim3(256), 0, st, gain, L, n, out);
     return hipGetLastError();
 }
 
