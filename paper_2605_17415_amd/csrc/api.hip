@@ -1379,15 +1379,16 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     const float kappa = screen_kappa(ix->d, cmax);
     // Score rows.  The batched path stores scores of the dense prefix only (it stops at the first list that
     // brings it to max(k, k*T/cap) vectors, so it is shorter than that plus the largest list); full-length
-    // rows are needed for the queries redone exactly, which take turns in gate_rows rows of the same buffer.
+    // rows (scores and columns) are needed for the queries redone exactly, which take turns in gate_rows rows of
+    // the same buffer.
     // The streaming path stores every score.  Queries per pass: as many as the workspace limit allows, since
     // every pass walks every probed list again.
     const int64_t need_max = std::max<int64_t>(k, (kPrefixFactorX2 * (int64_t)k * m_bound + 2 * cap - 1) / (2 * cap));
     const int64_t row_stride = batched ? std::min<int64_t>(m_stride, round_up64(need_max + sizes[0], 4)) : m_stride;
     int64_t qc = ix->ws_limit / (4 * std::max(row_stride, ldS));
     qc = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(qc, nq), 32768));
-    const int64_t gate_rows = std::max<int64_t>(1, std::min<int64_t>(qc, ix->ws_limit / (4 * m_stride)));
-    const int64_t score_floats = batched ? std::max(qc * row_stride, gate_rows * m_stride) : qc * m_stride;
+    const int64_t gate_rows = std::max<int64_t>(1, std::min<int64_t>(qc, ix->ws_limit / (8 * m_stride)));
+    const int64_t score_floats = batched ? std::max(qc * row_stride, gate_rows * 2 * m_stride) : qc * m_stride;
 
     HIP_TRY(ix->w_S.ensure((size_t)qc * ldS * sizeof(float)));
     HIP_TRY(ix->w_scores.ensure((size_t)score_floats * sizeof(float)));
@@ -1410,7 +1411,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         HIP_TRY(ix->w_cscore.ensure((size_t)qc * cap * sizeof(float)));
         HIP_TRY(ix->w_cslot.ensure((size_t)qc * cap * sizeof(int64_t)));
         HIP_TRY(ix->w_ccnt.ensure((size_t)qc * sizeof(int32_t)));
-        HIP_TRY(ix->w_gate.ensure((size_t)(qc + 1) * sizeof(int32_t)));
+        HIP_TRY(ix->w_gate.ensure((size_t)(2 * qc + 1) * sizeof(int32_t)));
     }
     // Streaming path with so few queries that one wavefront per score row would leave the chip idle (the
     // selection then takes longer than the scan): select per (query, list) first.  Needs what the
@@ -1433,21 +1434,21 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         if (metric) ea.norm_out = ix->w_qnorm.as<float>();
         HIP_TRY(timed(ix, st, P_ROTATE_Q, [&] { return launch_encode(2, ea, st); }));
         int32_t* first = batched ? ix->w_first.as<int32_t>() : nullptr;
+        int32_t* redo_cnt = batched ? ix->w_gate.as<int32_t>() + 1 + qc : nullptr;
         HIP_TRY(timed(ix, st, P_CAND_OFF, [&] {
             return launch_cand_offsets(ix->w_probe.as<int32_t>(), cnt, nprobe, ix->d_size.as<int32_t>(),
                                        ix->w_candoff.as<int32_t>(), k, cap, first,
-                                       batched ? ix->w_ccnt.as<int32_t>() : nullptr, batched ? ix->w_gate.as<int32_t>() : nullptr, st); }));
-        auto stream_scan = [&](const int32_t* gate, int gate_begin, int blocks_per_query, int slices = 1) {
-            return launch_list_scan(ix->w_z.as<float>(), ix->dp, ix->d, bits, cb,
-                                    ix->w_probe.as<int32_t>(), ix->w_coarse.as<float>(),
-                                    ix->w_candoff.as<int32_t>(), nprobe, codes_store, 0, cnt,
-                                    ix->w_scores.as<float>(), m_stride, nullptr, gate, gate_begin, (int)gate_rows,
-                                    blocks_per_query, slices, metric, ix->w_qnorm.as<float>(), st);
-        };
+                                       batched ? ix->w_ccnt.as<int32_t>() : nullptr, batched ? ix->w_gate.as<int32_t>() : nullptr,
+                                       batched ? redo_cnt : nullptr, st); }));
+        ListScanArgs la{};
+        la.z = ix->w_z.as<float>(); la.z_pitch = ix->dp; la.d = ix->d; la.cb = cb;
+        la.probe = ix->w_probe.as<int32_t>(); la.coarse = ix->w_coarse.as<float>();
+        la.cand_off = ix->w_candoff.as<int32_t>(); la.np = nprobe; la.store = codes_store;
+        la.scores = ix->w_scores.as<float>(); la.m_stride = m_stride;
+        la.metric = metric; la.qnorm = ix->w_qnorm.as<float>();
         SelectArgs sa{};
         sa.vals = ix->w_scores.as<float>(); sa.stride = m_stride; sa.rows = cnt; sa.k = k;
         sa.cand_off = ix->w_candoff.as<int32_t>(); sa.probe = ix->w_probe.as<int32_t>(); sa.np = nprobe;
-        sa.q_begin = 0;
         sa.list_off = ix->d_off.as<int64_t>(); sa.ids = labels;
         sa.out_vals = scores_dev + q0 * k; sa.out_i64 = ids_dev + q0 * k;
         sa.m_bound = (int)m_stride;
@@ -1475,7 +1476,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             // and, while a share of a typical list still fills two rounds, until about 8192 are (64 queries at
             // 10M x 96: scan 0.100 -> 0.070 ms)
             slices = std::max(slices, std::min<int64_t>(kStreamWorkgroups / ((int64_t)per_query * cnt), ix->ntotal / ix->nlist / 512));
-            HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return stream_scan(nullptr, 0, per_query, (int)slices); }));
+            HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, per_query, (int)slices, st); }));
             if (two_step) {
                 // a handful of rows: one wavefront per (query, list) first, then one per query over the survivors
                 SelectArgs s_a = sa, s_b = sa;
@@ -1535,12 +1536,20 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         ma.k = k; ma.out_scores = scores_dev + q0 * k; ma.out_ids = ids_dev + q0 * k;
         ma.gate = ix->w_gate.as<int32_t>();
         HIP_TRY(timed(ix, st, P_MERGE, [&] { return launch_merge(ma, cnt, st); }));
-        SelectArgs s2 = sa;
-        s2.gate = ix->w_gate.as<int32_t>(); s2.gate_rows = (int)gate_rows;
+        // The redo keeps the scores that reach the threshold, in its own arithmetic: that of the first pass differs by
+        // rounding, at most 256 * 2^-24 (a float32 sum of d <= 256 terms) + 2^-20 (split products) of |z||C| times
+        // a norm of at most 2, together below kappa / 16.
+        la.gate = ix->w_gate.as<int32_t>(); la.gate_rows = (int)gate_rows; la.m_stride = 2 * m_stride;
+        la.thresh = ba.thresh; la.thresh_stride = k; la.slack = kappa / 16.f; la.redo_cnt = redo_cnt;
+        RedoSelectArgs ra{};
+        ra.vals = la.scores; ra.stride = la.m_stride; ra.k = k; ra.gate = la.gate; ra.gate_rows = la.gate_rows;
+        ra.redo_cnt = redo_cnt; ra.cand_off = la.cand_off; ra.probe = la.probe; ra.np = nprobe;
+        ra.list_off = ix->d_off.as<int64_t>(); ra.ids = labels;
+        ra.out_vals = sa.out_vals; ra.out_i64 = sa.out_i64;
         for (int64_t g0 = 0; g0 < cnt; g0 += gate_rows) {
-            s2.gate_begin = (int)g0;
-            HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return stream_scan(ix->w_gate.as<int32_t>(), (int)g0, 8); }));
-            HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_select(1, s2, st); }));
+            la.gate_begin = ra.gate_begin = (int)g0;
+            HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, 0, 1, st); }));
+            HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_redo_select(ra, st); }));
         }
     }
     return IVFTQ_OK;

@@ -204,29 +204,46 @@ hipError_t launch_inertia(const double* gain, int L, int64_t n, double* out, hip
 
 // cand_off[q*(np+1) + p] = sum_{p'<p} list_size[probe[q][p']]
 // first (may be null): first[q] = shortest probe prefix (>= 1 cell) holding at least
-// max(k, 2*k*T/cap) vectors, T the query's candidate total; np if there is none.  With `first`, cand_cnt[q]
-// and gate[0] (each may be null) are set to zero: the counters the batched scan and its merge add to.
+// max(k, 2*k*T/cap) vectors, T the query's candidate total; np if there is none.  With `first`, cand_cnt[q],
+// gate[0] and redo_cnt[q] (each may be null) are set to zero: the counters the batched scan, its merge and the
+// exact redo add to.
 hipError_t launch_cand_offsets(const int32_t* probe, int64_t nq, int np, const int32_t* list_size,
                                int32_t* cand_off, int k, int cap, int32_t* first, int32_t* cand_cnt, int32_t* gate,
-                               hipStream_t st);
-// scores[row*m_stride + cand_off[q][p] + i] = coarse[q][p] + gamma_i * sum_j z_qj * C[code_ij]
-hipError_t launch_list_scan(const float* z, int z_pitch, int d, int b, const float* cb,
-                            const int32_t* probe, const float* coarse, const int32_t* cand_off,
-                            int np, const ListStore& store, int64_t q_begin, int64_t q_count,
-                            float* scores, int64_t m_stride, const int32_t* p_limit, const int32_t* gate,
-                            int gate_begin, int gate_rows, int blocks_per_query, int slices, int metric, const float* qnorm,
-                            hipStream_t st);
+                               int32_t* redo_cnt, hipStream_t st);
+// scores[q*m_stride + cand_off[q][p] + i] = coarse[q][p] + gamma_i * sum_j z_qj * C[code_ij]
+struct ListScanArgs {
+    const float* z; int z_pitch; int d;
+    const float* cb;
+    const int32_t* probe; const float* coarse; const int32_t* cand_off; int np;
+    ListStore store;
+    float* scores; int64_t m_stride;
+    int metric; const float* qnorm;
+    // Exact redo (gate not null): instead of all queries the entries [gate_begin, gate_begin + gate_rows) of the
+    // gate[0] queries listed in gate[1..] are scanned.  Entry g's scores that reach thresh[q*thresh_stride] -
+    // slack go, redo_cnt[q] of them in any order, to the first half of score row g - gate_begin, their columns
+    // (cand_off[q][p] + i) to its second half; half a row has to hold every candidate.
+    const int32_t* gate; int gate_begin, gate_rows;
+    const float* thresh; int thresh_stride; float slack; int32_t* redo_cnt;
+};
+constexpr int kRedoWorkgroups = 2048;   // shared out over the queries a redo launch finds
+// blocks_per_query: workgroups per query (0 = one per probe), each walking its share of the probes; slices:
+// workgroups that share every list.  (Neither matters for a redo.)
+hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int blocks_per_query, int slices, hipStream_t st);
+// The k best of every query of a redo window, by (score desc, label asc), written to its own result row; vals,
+// stride and the window as in the scan.
+struct RedoSelectArgs {
+    const float* vals; int64_t stride; int k;
+    const int32_t* gate; int gate_begin, gate_rows; const int32_t* redo_cnt;
+    const int32_t* cand_off; const int32_t* probe; int np;
+    const int64_t* list_off; const int64_t* ids;
+    float* out_vals; int64_t* out_i64;
+};
+hipError_t launch_redo_select(const RedoSelectArgs& a, hipStream_t st);
 // metric 0: the score is the estimate s^ of <q~, x~> itself.  Raw metrics (the store keeps |x|, qnorm[q] = |q|):
 // the scan writes a key that ranks like the metric and launch_metric_finish turns the selected keys into values:
 //   metric 1 (inner product): key = |x| s^,                 value = |q| key            (descending)
 //   metric 2 (squared L2):    key = 2 |x| |q| s^ - |x|^2,   value = |q|^2 - key        (ascending; missing: +inf)
 hipError_t launch_metric_finish(float* scores, int64_t nq, int k, int metric, const float* qnorm, hipStream_t st);
-// p_limit (may be null): only probes p < p_limit[q] are scanned.  gate (may be null; row = the query's index
-// without it): of the gate[0] queries listed in gate[1..] only entries [gate_begin, gate_begin + gate_rows) are
-// processed, entry g into score row g - gate_begin, so a buffer of gate_rows rows serves any number of listed
-// queries in several launches.  blocks_per_query: workgroups per query (0 = one per probe), each
-// walking its share of the probes; slices (not with a gate): workgroups that share every list.
-
 // Per row: the k largest of m values, sorted by (value desc, label asc).
 // mode 0 (probe selection): m = m_fixed for every row, label = column; writes int32 labels.
 // mode 1 (results): row q has m = cand_off[q][np] values; column -> (probe p, position) -> label
@@ -234,14 +251,12 @@ hipError_t launch_metric_finish(float* scores, int64_t nq, int k, int metric, co
 struct SelectArgs {
     const float* vals; int64_t stride; int64_t rows; int k;
     int m_fixed;
-    const int32_t* cand_off; const int32_t* probe; int np; int64_t q_begin;
+    const int32_t* cand_off; const int32_t* probe; int np;
     const int32_t* p_limit;   // mode 1: row q only has the candidates of probes p < p_limit[q] (null = all)
-    const int32_t* gate;      // null = all rows; else of the gate[0] rows listed in gate[1..] the entries
-    int gate_begin, gate_rows;   // [gate_begin, gate_begin + gate_rows) are processed, entry g reading vals row g - gate_begin
     const int64_t* list_off; const int64_t* ids;
     float* out_vals; int32_t* out_i32; int64_t* out_i64;
     int m_bound;      // mode 1: host-side upper bound of any row's length (0 = unknown); picks the kernel
-    // Selection in two steps (k <= 64, no gate): mode 2 treats `rows` = queries x np rows, row (q, p) being the
+    // Selection in two steps (k <= 64): mode 2 treats `rows` = queries x np rows, row (q, p) being the
     // stretch of probe p in score row q, and writes k (value, label) pairs per row (m_bound = longest list);
     // mode 3 selects among the m_fixed = np * k survivors of a query, whose labels it reads from lab_in.
     const int64_t* lab_in;

@@ -18,7 +18,8 @@ namespace {
 __global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict__ probe, int64_t nq, int np,
                                                       const int32_t* __restrict__ list_size, int32_t* __restrict__ cand_off,
                                                       int k, int cap, int32_t* __restrict__ first,
-                                                      int32_t* __restrict__ cand_cnt, int32_t* __restrict__ gate) {
+                                                      int32_t* __restrict__ cand_cnt, int32_t* __restrict__ gate,
+                                                      int32_t* __restrict__ redo_cnt) {
     // one wavefront per query: 64 probes at a time, running sum over the lanes
     const int lane = threadIdx.x & 63;
     const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -64,6 +65,7 @@ __global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict_
         first[q] = p1;
         // the counters of the batched scan start at zero (cleared here rather than by launches of their own)
         if (cand_cnt) cand_cnt[q] = 0;
+        if (redo_cnt) redo_cnt[q] = 0;
         if (gate && q == 0) gate[0] = 0;
     }
 }
@@ -76,32 +78,49 @@ __global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict_
 // reads its packed words with 256-byte-per-wavefront coalesced loads and sums d table entries.
 // When the table would not fit LDS (large b and d) DIRECT keeps z and C separately and multiplies
 // per coordinate instead.
-template <int B, bool DIRECT>
-__global__ __launch_bounds__(256) void k_list_scan(const float* __restrict__ z, int z_pitch, int d,
-                                                   const float* __restrict__ cb,
-                                                   const int32_t* __restrict__ probe,
-                                                   const float* __restrict__ coarse,
-                                                   const int32_t* __restrict__ cand_off, int np,
-                                                   ListStore store, int64_t q_begin,
-                                                   float* __restrict__ scores, int64_t m_stride,
-                                                   const int32_t* __restrict__ p_limit,
-                                                   const int32_t* __restrict__ gate, int gate_begin, int gate_rows,
-                                                   int metric, const float* __restrict__ qnorm) {
+//
+// REDO: only the queries that overflowed their candidate list (launch_list_scan), and only scores that reach the
+// query's threshold are kept, with their columns, in arbitrary order.  A launch mostly finds no such query or a
+// few, so all of its workgroups are shared out over those it finds: two queries of 64 lists on eight workgroups
+// each took 0.66 ms at 10M x 200, each workgroup walking eight lists alone; spread over the chip 0.02 ms.
+template <int B, bool DIRECT, bool REDO>
+__global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
     constexpr int K = 1 << B;
     extern __shared__ float lut[];     // [d][K], or z[d] followed by C[K] when DIRECT
-    // gate (may be null): of the gate[0] queries listed in gate[1..], entries [gate_begin, gate_begin +
-    // gate_rows) are processed instead of all queries, entry g writing score row g - gate_begin; the grid's
-    // y extent is then fixed and each workgroup row walks the list
-    int64_t n_rows = gridDim.y;
-    if (gate) n_rows = gate[0] < gate_begin + gate_rows ? gate[0] : gate_begin + gate_rows;
-    for (int64_t row_i = (gate ? gate_begin : 0) + blockIdx.y; row_i < n_rows; row_i += gridDim.y) {
-    const int64_t qi = gate ? gate[1 + row_i] : row_i;     // index inside this pass
-    const int64_t score_row = gate ? row_i - gate_begin : qi;
-    const int64_t q = q_begin + qi;
-    const int p_end = p_limit ? p_limit[q] : np;
-    if ((int)blockIdx.x >= p_end) continue;
-    const float qn = metric ? qnorm[q] : 1.f;
-    __syncthreads();                   // the table of the previous query is no longer read
+    const float* __restrict__ z = a.z;
+    const float* __restrict__ cb = a.cb;
+    const int32_t* __restrict__ probe = a.probe;
+    const float* __restrict__ coarse = a.coarse;
+    const int32_t* __restrict__ cand_off = a.cand_off;
+    const ListStore& store = a.store;
+    const int z_pitch = a.z_pitch, d = a.d, np = a.np, metric = a.metric;
+    // this workgroup takes the probes p_first, p_first + p_step, ... of a query and of each of those lists the
+    // rounds slice, slice + slices, ... of 256 vectors
+    int64_t row = blockIdx.y, row_step = 1, row_end = row + 1;
+    int p_first = (int)blockIdx.x, p_step = (int)gridDim.x, slice = (int)blockIdx.z, slices = (int)gridDim.z;
+    if constexpr (REDO) {
+        int n_redo = a.gate[0] - a.gate_begin;
+        if (n_redo > a.gate_rows) n_redo = a.gate_rows;
+        if (n_redo <= 0) return;
+        const int per = max(1, (int)gridDim.x / n_redo);       // workgroups per query
+        const int part = (int)blockIdx.x % per;
+        row = (int)blockIdx.x / per; row_step = (int)gridDim.x / per; row_end = n_redo;
+        if (row >= row_step) return;
+        p_step = min(per, np);
+        slices = per / p_step;
+        p_first = part % p_step;
+        slice = part / p_step;
+        if (slice >= slices) return;
+    }
+    for (; row < row_end; row += row_step) {
+    const int64_t q = REDO ? a.gate[1 + a.gate_begin + row] : row;
+    if (p_first >= np) continue;
+    const float qn = metric ? a.qnorm[q] : 1.f;
+    float reach = 0.f;
+    if constexpr (REDO) {
+        reach = a.thresh[q * a.thresh_stride] - a.slack;
+        __syncthreads();               // the table of the previous query is no longer read
+    }
 
     if constexpr (DIRECT) {
         for (int e = threadIdx.x; e < d; e += 256) lut[e] = z[q * z_pitch + e];
@@ -116,15 +135,16 @@ __global__ __launch_bounds__(256) void k_list_scan(const float* __restrict__ z, 
     };
 
     const int words = store.words;
-    for (int p = blockIdx.x; p < p_end; p += gridDim.x) {
+    for (int p = p_first; p < np; p += p_step) {
     const int l = probe[q * np + p];
     const int n_l = store.list_size[l];
     const float s_l = coarse[q * np + p];
     const int64_t base_slot = store.list_off[l];
-    float* out = scores + score_row * m_stride + cand_off[q * (np + 1) + p];
+    const int32_t col0 = cand_off[q * (np + 1) + p];
+    float* out = a.scores + row * a.m_stride + (REDO ? 0 : col0);
 
-    // a list is dealt out in rounds of 256 vectors to the gridDim.z workgroups that share it
-    for (int v = threadIdx.x + 256 * (int)blockIdx.z; v < n_l; v += 256 * (int)gridDim.z) {
+    // a list is dealt out in rounds of 256 vectors to the workgroups that share it
+    for (int v = threadIdx.x + 256 * slice; v < n_l; v += 256 * slices) {
         const int64_t slot = base_slot + v;
         const uint32_t* wp = store.codes + (slot >> 6) * words * 64 + (slot & 63);
         float acc = 0.f;
@@ -219,7 +239,21 @@ __global__ __launch_bounds__(256) void k_list_scan(const float* __restrict__ z, 
             const float xn = store.xnorm[slot];
             sc = metric == 1 ? xn * sc : fmaf(2.f * xn * qn, sc, -xn * xn);
         }
-        out[v] = sc;
+        if constexpr (REDO) {
+            const uint64_t in = __ballot(sc >= reach);           // one counter update per wavefront
+            if (in) {
+                const int lane = (int)(threadIdx.x & 63), leader = (int)__builtin_ctzll(in);
+                int at = 0;
+                if (lane == leader) at = atomicAdd(&a.redo_cnt[q], (int)__popcll(in));
+                at = __shfl(at, leader) + (int)__popcll(in & (((uint64_t)1 << lane) - 1));
+                if (sc >= reach) {
+                    out[at] = sc;
+                    out[a.m_stride / 2 + at] = __int_as_float(col0 + v);
+                }
+            }
+        } else {
+            out[v] = sc;
+        }
     }
     }
     }
@@ -268,14 +302,9 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     uint32_t* c_col = c_key + kSelCand;                               // [kSelCand] ... and their columns
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // gate (may be null): a.gate[0] rows, listed in a.gate[1..], are processed instead of all
-    int64_t n_rows = a.rows;
-    if (a.gate) n_rows = a.gate[0] < a.gate_begin + a.gate_rows ? a.gate[0] : a.gate_begin + a.gate_rows;
-    for (int64_t row_i = (a.gate ? a.gate_begin : 0) + blockIdx.x; row_i < n_rows; row_i += gridDim.x) {
-    const int64_t row = a.gate ? a.gate[1 + row_i] : row_i;
-    const float* vals = a.vals + (a.gate ? row_i - a.gate_begin : row) * a.stride;
-    const int64_t q = a.q_begin + row;
-    __syncthreads();                   // LDS of the previous row is no longer read
+    const int64_t row = blockIdx.x;
+    const float* vals = a.vals + row * a.stride;
+    const int64_t q = row;
     const int m = (MODE == 0) ? a.m_fixed
                               : a.cand_off[q * (a.np + 1) + (a.p_limit ? a.p_limit[q] : a.np)];
     const int k = a.k;
@@ -535,7 +564,6 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
         if (MODE == 0) { if (a.out_i32) a.out_i32[row * k + i] = real ? (int32_t)s_lab[i] : -1; }
         else { if (a.out_i64) a.out_i64[row * k + i] = real ? s_lab[i] : -1; }
     }
-    }
 }
 
 // ---- selection for short rows: one wavefront per row ------------------------------------------
@@ -563,12 +591,10 @@ template <int MODE, int NV, bool WIDE = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ? 4 : 1, 8))) void k_select_small(SelectArgs a) {
     __shared__ uint32_t s_work[4][256 + 64];             // per wavefront: 256 bins, 64 winning columns
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int64_t n_rows = a.rows;
-    if (a.gate) n_rows = a.gate[0] < a.gate_begin + a.gate_rows ? a.gate[0] : a.gate_begin + a.gate_rows;
-    for (int64_t row_i = (a.gate ? a.gate_begin : 0) + (int64_t)blockIdx.x * 4 + wave; row_i < n_rows; row_i += (int64_t)gridDim.x * 4) {
-    const int64_t row = a.gate ? a.gate[1 + row_i] : row_i;
+    const int64_t row = (int64_t)blockIdx.x * 4 + wave;
+    if (row >= a.rows) return;
     // MODE 2: row = (query, probe rank); the stretch of that list in the query's score row
-    const int64_t q = a.q_begin + (MODE == 2 ? row / a.np : row);
+    const int64_t q = MODE == 2 ? row / a.np : row;
     const int sub_p = MODE == 2 ? (int)(row % a.np) : 0;
     int m, sub_off = 0;
     if (MODE == 0 || MODE == 3) {
@@ -583,7 +609,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     const int k = a.k;
     const int take = m < k ? m : k;
     const float* vals = MODE == 2 ? a.vals + (row / a.np) * a.stride + sub_off
-                                  : a.vals + (a.gate ? row_i - a.gate_begin : row) * a.stride;
+                                  : a.vals + row * a.stride;
     uint32_t* hist = s_work[wave];                                      // [256]
     int* win_col = reinterpret_cast<int*>(hist + 256);                  // [64]
     const float ninf = -__builtin_inff();
@@ -930,8 +956,126 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
         if (MODE == 0) { if (a.out_i32) a.out_i32[row * k + lane] = real ? (int32_t)lab : -1; }
         else { if (a.out_i64) a.out_i64[row * k + lane] = real ? lab : -1; }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();   // the wavefront's LDS words are free for its next row
+}
+
+// ---- the k best of the queries redone exactly ----------------------------------------------------
+//
+// One workgroup per listed query; its row holds redo_cnt[q] scores in arbitrary order and the candidate columns
+// they belong to.  An entry's composite (order-preserving key of the score, then ~column) makes all entries
+// distinct: the k with the largest composites are the k best, ties going to the smaller column, whatever the
+// order they were appended in.  Up to kRedoSort entries are sorted in LDS; beyond that an eight-pass radix search
+// finds the k-th largest composite first.  Bound by the latency of its few passes; on the benchmark's searches
+// one to three queries of 10,000 come here, with 400 to 3000 entries each.
+constexpr int kRedoSort = 2048;
+static_assert(kMaxK <= kRedoSort, "the k winners are sorted in LDS");
+
+__global__ __launch_bounds__(1024) void k_redo_select(RedoSelectArgs a) {
+    __shared__ uint64_t s_comp[kRedoSort];
+    __shared__ int64_t s_lab[kRedoSort];
+    __shared__ uint32_t hist[256];
+    __shared__ uint32_t ctrl[2];
+    const int tid = threadIdx.x;
+    const int n_redo = min(a.gate[0] - a.gate_begin, a.gate_rows);
+    for (int row = blockIdx.x; row < n_redo; row += gridDim.x) {
+        const int64_t q = a.gate[1 + a.gate_begin + row];
+        const int32_t* off = a.cand_off + q * (a.np + 1);
+        const int n = a.redo_cnt[q];
+        const float* vals = a.vals + row * a.stride;
+        const float* cols = vals + a.stride / 2;
+        auto comp_of = [&](int i) -> uint64_t {
+            return ((uint64_t)order_key(vals[i]) << 32) | (uint32_t)~__float_as_uint(cols[i]);
+        };
+        const int take = n < a.k ? n : a.k;
+        uint64_t last = 0;                          // every entry of at least this composite is gathered
+        if (n > kRedoSort) {
+            uint64_t mask = 0;
+            uint32_t need = (uint32_t)take;
+            for (int shift = 56; shift >= 0; shift -= 8) {
+                __syncthreads();
+                if (tid < 256) hist[tid] = 0;
+                __syncthreads();
+                for (int i = tid; i < n; i += 1024) {
+                    const uint64_t c = comp_of(i);
+                    if ((c & mask) == last) atomicAdd(&hist[(c >> shift) & 255u], 1u);
+                }
+                __syncthreads();
+                if (tid == 0) {
+                    int dgt = 255;
+                    uint32_t above = 0;
+                    while (dgt > 0 && above + hist[dgt] < need) above += hist[dgt--];
+                    ctrl[0] = (uint32_t)dgt;
+                    ctrl[1] = need - above;
+                }
+                __syncthreads();
+                last |= (uint64_t)ctrl[0] << shift;
+                mask |= (uint64_t)255 << shift;
+                need = ctrl[1];
+            }
+        }
+        __syncthreads();
+        if (tid == 0) ctrl[0] = 0;
+        __syncthreads();
+        for (int i = tid; i < n; i += 1024) {
+            const uint64_t c = comp_of(i);
+            if (c >= last) {
+                const uint32_t at = atomicAdd(&ctrl[0], 1u);
+                if (at < (uint32_t)kRedoSort) s_comp[at] = c;
+            }
+        }
+        __syncthreads();
+        const int got = min((int)ctrl[0], kRedoSort);
+        int size = 1;
+        while (size < got) size <<= 1;
+        for (int i = got + tid; i < size; i += 1024) s_comp[i] = 0;
+        __syncthreads();
+        for (int sz = 2; sz <= size; sz <<= 1)
+            for (int stride = sz >> 1; stride > 0; stride >>= 1) {
+                for (int i = tid; i < size / 2; i += 1024) {
+                    const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+                    const uint64_t c0 = s_comp[lo], c1 = s_comp[hi];
+                    if ((c0 >= c1) != ((lo & sz) == 0)) { s_comp[lo] = c1; s_comp[hi] = c0; }
+                }
+                __syncthreads();
+            }
+        // labels of the winners, then equal scores in label order
+        int kpad = 1;
+        while (kpad < take) kpad <<= 1;
+        for (int i = tid; i < kpad; i += 1024) {
+            int64_t lab = INT64_MAX;
+            if (i < take) {
+                const int32_t col = (int32_t)~(uint32_t)s_comp[i];
+                int lo = 0, hi = a.np;              // largest p with off[p] <= col
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (off[mid] <= col) lo = mid; else hi = mid;
+                }
+                const int64_t slot = a.list_off[a.probe[q * a.np + lo]] + (col - off[lo]);
+                lab = a.ids ? a.ids[slot] : slot;
+            } else {
+                s_comp[i] = 0;
+            }
+            s_lab[i] = lab;
+        }
+        __syncthreads();
+        for (int sz = 2; sz <= kpad; sz <<= 1)
+            for (int stride = sz >> 1; stride > 0; stride >>= 1) {
+                for (int i = tid; i < kpad / 2; i += 1024) {
+                    const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+                    const uint32_t k0 = (uint32_t)(s_comp[lo] >> 32), k1 = (uint32_t)(s_comp[hi] >> 32);
+                    const int64_t l0 = s_lab[lo], l1 = s_lab[hi];
+                    if ((k0 > k1 || (k0 == k1 && l0 <= l1)) != ((lo & sz) == 0)) {
+                        const uint64_t c = s_comp[lo]; s_comp[lo] = s_comp[hi]; s_comp[hi] = c;
+                        s_lab[lo] = l1; s_lab[hi] = l0;
+                    }
+                }
+                __syncthreads();
+            }
+        for (int i = tid; i < a.k; i += 1024) {
+            const uint32_t key = i < take ? (uint32_t)(s_comp[i] >> 32) : 0u;
+            a.out_vals[q * a.k + i] = i < take ? __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key) : -__builtin_inff();
+            a.out_i64[q * a.k + i] = i < take ? s_lab[i] : -1;
+        }
+        __syncthreads();
     }
 }
 
@@ -1124,37 +1268,29 @@ hipError_t launch_rerank(const RerankArgs& a, int64_t nq, hipStream_t st) {
 
 hipError_t launch_cand_offsets(const int32_t* probe, int64_t nq, int np, const int32_t* list_size,
                                int32_t* cand_off, int k, int cap, int32_t* first, int32_t* cand_cnt, int32_t* gate,
-                               hipStream_t st) {
+                               int32_t* redo_cnt, hipStream_t st) {
     if (nq <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_cand_offsets, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, probe, nq, np,
-                       list_size, cand_off, k, cap, first, cand_cnt, gate);
+                       list_size, cand_off, k, cap, first, cand_cnt, gate, redo_cnt);
     return hipGetLastError();
 }
 
-hipError_t launch_list_scan(const float* z, int z_pitch, int d, int b, const float* cb,
-                            const int32_t* probe, const float* coarse, const int32_t* cand_off,
-                            int np, const ListStore& store, int64_t q_begin, int64_t q_count,
-                            float* scores, int64_t m_stride, const int32_t* p_limit, const int32_t* gate,
-                            int gate_begin, int gate_rows, int blocks_per_query, int slices, int metric, const float* qnorm,
-                            hipStream_t st) {
+hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int blocks_per_query, int slices, hipStream_t st) {
     if (q_count <= 0) return hipSuccess;
-    if (metric && (!qnorm || !store.xnorm)) return hipErrorInvalidValue;
-    const size_t lut_bytes = (size_t)d * (1u << b) * sizeof(float);
+    if (a.metric && (!a.qnorm || !a.store.xnorm)) return hipErrorInvalidValue;
+    const size_t lut_bytes = (size_t)a.d * (1u << b) * sizeof(float);
     const bool direct = lut_bytes > 64 * 1024;
-    const size_t lds = direct ? (size_t)(d + (1 << b)) * sizeof(float) : lut_bytes;
-    // gated: a fixed number of workgroup rows walks the list of marked queries
-    dim3 grid((unsigned)(blocks_per_query > 0 ? blocks_per_query : np), (unsigned)(gate ? std::min<int64_t>(std::min<int64_t>(q_count, gate_rows), 256) : q_count));
+    const size_t lds = direct ? (size_t)(a.d + (1 << b)) * sizeof(float) : lut_bytes;
     // slices: every list is dealt out in rounds of 256 vectors to that many workgroups (grid z, the slowest
     // dimension of the dispatch order: the launch works through the index one slice at a time)
-    if (!gate) grid.z = (unsigned)std::max(1, std::min(slices, 64));
+    dim3 grid((unsigned)(blocks_per_query > 0 ? blocks_per_query : a.np), (unsigned)q_count, (unsigned)std::max(1, std::min(slices, 64)));
+    if (a.gate) grid = dim3(kRedoWorkgroups);
 #define IVFTQ_SCAN(BV)                                                                              \
     case BV:                                                                                        \
-        if (direct)                                                                                 \
-            hipLaunchKernelGGL((k_list_scan<BV, true>), grid, dim3(256), lds, st, z, z_pitch, d, cb, probe, \
-                               coarse, cand_off, np, store, q_begin, scores, m_stride, p_limit, gate, gate_begin, gate_rows, metric, qnorm); \
-        else                                                                                        \
-            hipLaunchKernelGGL((k_list_scan<BV, false>), grid, dim3(256), lds, st, z, z_pitch, d, cb, probe, \
-                               coarse, cand_off, np, store, q_begin, scores, m_stride, p_limit, gate, gate_begin, gate_rows, metric, qnorm); \
+        if (direct && a.gate) hipLaunchKernelGGL((k_list_scan<BV, true, true>), grid, dim3(256), lds, st, a);   \
+        else if (direct) hipLaunchKernelGGL((k_list_scan<BV, true, false>), grid, dim3(256), lds, st, a);       \
+        else if (a.gate) hipLaunchKernelGGL((k_list_scan<BV, false, true>), grid, dim3(256), lds, st, a);       \
+        else hipLaunchKernelGGL((k_list_scan<BV, false, false>), grid, dim3(256), lds, st, a);                  \
         break;
     switch (b) {
         IVFTQ_SCAN(1) IVFTQ_SCAN(2) IVFTQ_SCAN(3) IVFTQ_SCAN(4)
@@ -1162,6 +1298,12 @@ hipError_t launch_list_scan(const float* z, int z_pitch, int d, int b, const flo
         default: return hipErrorInvalidValue;
     }
 #undef IVFTQ_SCAN
+    return hipGetLastError();
+}
+
+hipError_t launch_redo_select(const RedoSelectArgs& a, hipStream_t st) {
+    if (a.k < 1 || a.k > kRedoSort) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_redo_select, dim3((unsigned)std::min(a.gate_rows, 256)), dim3(1024), 0, st, a);
     return hipGetLastError();
 }
 
@@ -1180,7 +1322,7 @@ hipError_t launch_select(int mode, const SelectArgs& a_in, hipStream_t st) {
     if (a_in.rows <= 0) return hipSuccess;
     SelectArgs a = a_in;
     if (mode == 2 || mode == 3) {
-        if (a.k > 64 || a.gate || (mode == 3 && !a.lab_in)) return hipErrorInvalidValue;
+        if (a.k > 64 || (mode == 3 && !a.lab_in)) return hipErrorInvalidValue;
         const int bound = mode == 2 ? a.m_bound : a.m_fixed;
         const unsigned blocks = (unsigned)((a.rows + 3) / 4);
         if (mode == 2) {
@@ -1196,7 +1338,7 @@ hipError_t launch_select(int mode, const SelectArgs& a_in, hipStream_t st) {
     const int m_bound = mode == 0 ? a.m_fixed : a.m_bound;
     if (a.k <= 64 && m_bound > 0 && m_bound <= (mode == 0 ? kSmallMax0Shortcut : kSmallMax1)) {
         const size_t lds = 0;
-        const unsigned blocks = (unsigned)((a.gate ? std::min<int64_t>(std::min<int64_t>(a.rows, a.gate_rows), 1024) : a.rows) + 3) / 4;
+        const unsigned blocks = (unsigned)((a.rows + 3) / 4);
 #define IVFTQ_SMALL(NVV)                                                                            \
         if (mode == 0 && a.k > kShortcutTake) hipLaunchKernelGGL((k_select_small<0, NVV, true>), dim3(blocks), dim3(256), lds, st, a);  \
         else if (mode == 0) hipLaunchKernelGGL((k_select_small<0, NVV>), dim3(blocks), dim3(256), lds, st, a);  \
@@ -1210,7 +1352,7 @@ hipError_t launch_select(int mode, const SelectArgs& a_in, hipStream_t st) {
     while (kpad < a.k) kpad <<= 1;
     const int copies = (m_bound == 0 || m_bound > 8192) ? 8 : 1;
     const size_t lds = (256 * copies + 8 + 4) * 4 + (size_t)kpad * 8 + 8 + (size_t)kpad * 8 + (size_t)kSelCand * 8;
-    const unsigned wgs = (unsigned)(a.gate ? std::min<int64_t>(std::min<int64_t>(a.rows, a.gate_rows), 256) : a.rows);
+    const unsigned wgs = (unsigned)a.rows;
     if (copies == 8) {
         if (mode == 0) hipLaunchKernelGGL((k_select<0, 8>), dim3(wgs), dim3(256), lds, st, a);
         else hipLaunchKernelGGL((k_select<1, 8>), dim3(wgs), dim3(256), lds, st, a);
