@@ -183,7 +183,7 @@ struct ivftq_index {
     DevBuf w_sums, w_counts, w_gain, w_rows, w_dst;
     DevBuf t_cent, t_cent_h, t_cent_l, t_bias;   // k-means works on its own tables; the index's change only on success
     DevBuf w_zh, w_zl;
-    DevBuf w_first, w_fscores, w_fids, w_pairs, w_pairoff, w_tileoff, w_cscore, w_cslot, w_ccnt, w_gate;
+    DevBuf w_first, w_fscores, w_fids, w_pairs, w_pairoff, w_tileoff, w_tilebkt, w_cscore, w_cslot, w_ccnt, w_gate;
     DevBuf w_stage_s, w_stage_i;      // survivors of the first step of a selection in two steps
     DevBuf w_part;                    // partial results of a coarse assignment whose centroid stages are shared out
     int64_t last_batched_queries = 0;   // queries of the last pass of the most recent batched search (ivftq_scan_stats)
@@ -198,7 +198,7 @@ struct ivftq_index {
         return {&cent, &cent_h, &cent_l, &pi_h, &pi_l, &pit_h, &pit_l, &bias, &pi, &cb, &q_grid, &codes, &gamma, &ids, &xnorm, &head, &w_qnorm, &d_off, &d_size, &w_assign,
                 &w_slot, &w_order, &w_hist, &w_count, &w_base, &w_flag, &w_undecided, &cb_cascade, &w_keep, &w_keep_scores,
                 &w_S, &w_probe, &w_coarse, &w_z, &w_candoff, &w_scores, &w_sums, &w_counts, &w_gain, &w_rows, &w_dst,
-                &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_pairoff, &w_tileoff, &w_cscore,
+                &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_pairoff, &w_tileoff, &w_tilebkt, &w_cscore,
                 &w_cslot, &w_ccnt, &w_gate, &w_zh, &w_zl, &w_stage_s, &w_stage_i, &w_part};
     }
     explicit ivftq_index(const Allocator& a) : alloc(a) {
@@ -1364,13 +1364,13 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     // 170 queries, i.e. 0.41 / 1.5 / 2.7 GB streamed against an index of 0.066 / 0.58 / 1.04 GB).  Mode 2
     // asks for the batched path whatever the size of the call.
     constexpr double kBatchedGain = 2.3, kBatchedFixedBytes = 0.25e9;
-    const int tq = batch_tile_queries(ix->d, bits);
-    const int metric = ix->metric;      // a raw metric ranks by a per-vector transform of the estimate: streaming scan only
+    const int tq = kBatchTile, tq_near = batch_near_queries(ix->d);
+    const int metric = ix->metric;
     const double vec_bytes = (double)codes_store.words * 4 + 2;
     const double index_bytes = (double)ix->ntotal * vec_bytes;
     const double streamed = (double)nq * nprobe * ((double)ix->ntotal / ix->nlist) * vec_bytes;
     const double touched = index_bytes * std::min(1.0, (double)nq * nprobe / ix->nlist);
-    const bool batched = tq > 0 && nprobe > 1 && ix->search_mode != 1 && metric == IVFTQ_METRIC_COSINE &&
+    const bool batched = batch_covers(ix->d, bits) && nprobe > 1 && ix->search_mode != 1 &&
                          (ix->search_mode == 2 || streamed >= kBatchedGain * touched + kBatchedFixedBytes);
     const int cap = std::min(2048, std::max(512, 16 * k));
     // error bound of a residual sum taken from the leading float16 parts alone (threshold pass)
@@ -1398,6 +1398,8 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     HIP_TRY(ix->w_z.ensure((size_t)qc * ix->dp * sizeof(float)));
     if (metric) HIP_TRY(ix->w_qnorm.ensure((size_t)qc * sizeof(float)));
     const int64_t n_pairs = qc * nprobe;
+    const int buckets = round_up(2 * ix->nlist, 4);
+    const int64_t max_tiles = n_pairs / tq_near + 2 * ix->nlist;     // tq_near <= tq
     if (batched) {
         HIP_TRY(ix->w_zh.ensure((size_t)qc * ix->dp * sizeof(uint16_t)));
         HIP_TRY(ix->w_zl.ensure((size_t)qc * ix->dp * sizeof(uint16_t)));
@@ -1405,9 +1407,10 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         HIP_TRY(ix->w_fscores.ensure((size_t)qc * k * sizeof(float)));
         HIP_TRY(ix->w_fids.ensure((size_t)qc * k * sizeof(int64_t)));
         HIP_TRY(ix->w_pairs.ensure((size_t)n_pairs * sizeof(int32_t)));
-        HIP_TRY(ix->w_count.ensure((size_t)4 * ix->nlist * sizeof(uint32_t)));
+        HIP_TRY(ix->w_count.ensure((size_t)2 * buckets * sizeof(uint32_t)));
         HIP_TRY(ix->w_pairoff.ensure((size_t)(2 * ix->nlist + 1) * sizeof(int64_t)));
         HIP_TRY(ix->w_tileoff.ensure((size_t)(2 * ix->nlist + 1) * sizeof(int32_t)));
+        HIP_TRY(ix->w_tilebkt.ensure((size_t)max_tiles * sizeof(int32_t)));
         HIP_TRY(ix->w_cscore.ensure((size_t)qc * cap * sizeof(float)));
         HIP_TRY(ix->w_cslot.ensure((size_t)qc * cap * sizeof(int64_t)));
         HIP_TRY(ix->w_ccnt.ensure((size_t)qc * sizeof(int32_t)));
@@ -1439,7 +1442,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             return launch_cand_offsets(ix->w_probe.as<int32_t>(), cnt, nprobe, ix->d_size.as<int32_t>(),
                                        ix->w_candoff.as<int32_t>(), k, cap, first,
                                        batched ? ix->w_ccnt.as<int32_t>() : nullptr, batched ? ix->w_gate.as<int32_t>() : nullptr,
-                                       batched ? redo_cnt : nullptr, st); }));
+                                       redo_cnt, batched ? ix->w_count.as<uint32_t>() : nullptr, buckets, st); }));
         ListScanArgs la{};
         la.z = ix->w_z.as<float>(); la.z_pitch = ix->dp; la.d = ix->d; la.cb = cb;
         la.probe = ix->w_probe.as<int32_t>(); la.coarse = ix->w_coarse.as<float>();
@@ -1497,26 +1500,26 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         ix->last_batched_queries = cnt;
         const int64_t np_items = cnt * nprobe;
         HIP_TRY(timed(ix, st, P_PAIR_GROUP, [&] {
-            hipError_t e = launch_pair_grouping(ix->w_probe.as<int32_t>(), first, cnt, nprobe, ix->nlist, tq,
-                                                ix->w_count.as<uint32_t>(), ix->w_count.as<uint32_t>() + 2 * ix->nlist,
-                                                ix->w_pairoff.as<int64_t>(), ix->w_tileoff.as<int32_t>(),
+            hipError_t e = launch_pair_grouping(ix->w_probe.as<int32_t>(), first, cnt, nprobe, ix->nlist, tq_near, tq,
+                                                ix->w_count.as<uint32_t>(), ix->w_count.as<uint32_t>() + buckets,
+                                                ix->w_pairoff.as<int64_t>(), ix->w_tileoff.as<int32_t>(), ix->w_tilebkt.as<int32_t>(),
                                                 ix->w_pairs.as<int32_t>(), st);
             return e; }));
         BatchScanArgs ba{};
         ba.zh = ix->w_zh.as<uint16_t>(); ba.zl = ix->w_zl.as<uint16_t>(); ba.z_pitch = ix->dp;
         ba.cb = cb;
         ba.pairs = ix->w_pairs.as<int32_t>(); ba.pair_off = ix->w_pairoff.as<int64_t>();
-        ba.tile_off = ix->w_tileoff.as<int32_t>();
+        ba.tile_off = ix->w_tileoff.as<int32_t>(); ba.tile_bucket = ix->w_tilebkt.as<int32_t>();
+        ba.metric = metric; ba.qnorm = ix->w_qnorm.as<float>();
         ba.coarse = ix->w_coarse.as<float>();
         ba.store = codes_store; ba.np = nprobe; ba.L = ix->nlist;
         ba.cand_score = ix->w_cscore.as<float>(); ba.cand_slot = ix->w_cslot.as<int64_t>();
         ba.cand_cnt = ix->w_ccnt.as<int32_t>(); ba.cap = cap;
         ba.acc0 = kappa * kSplitScale * kSplitScale;
         ba.scores = ix->w_scores.as<float>(); ba.m_stride = row_stride; ba.cand_off = ix->w_candoff.as<int32_t>();
-        const int max_tiles = (int)(np_items / tq) + ix->nlist;
         // 2. every score of the nearest lists, then their top-k: the k-th is the query's threshold
         ba.dense = 1; ba.bucket_lo = 0; ba.bucket_hi = ix->nlist;
-        HIP_TRY(timed(ix, st, P_BATCH_FIRST, [&] { return launch_batch_scan(ba, ix->d, bits, max_tiles, st); }));
+        HIP_TRY(timed(ix, st, P_BATCH_FIRST, [&] { return launch_batch_scan(ba, ix->d, bits, (int)(np_items / tq_near) + ix->nlist, st); }));
         SelectArgs s1 = sa;
         s1.p_limit = first; s1.out_vals = ix->w_fscores.as<float>(); s1.out_i64 = ix->w_fids.as<int64_t>();
         s1.stride = row_stride; s1.m_bound = (int)row_stride;
@@ -1524,13 +1527,13 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         // 3. the other lists against the thresholds
         ba.dense = 0; ba.bucket_lo = ix->nlist; ba.bucket_hi = 2 * ix->nlist;
         ba.thresh = ix->w_fscores.as<float>() + (k - 1); ba.thresh_stride = k;
-        HIP_TRY(timed(ix, st, P_BATCH_SCAN, [&] { return launch_batch_scan(ba, ix->d, bits, max_tiles, st); }));
+        HIP_TRY(timed(ix, st, P_BATCH_SCAN, [&] { return launch_batch_scan(ba, ix->d, bits, (int)(np_items / tq) + ix->nlist, st); }));
         // 4. merge; a query whose candidate list overflowed is redone by the exact streaming scan
         MergeArgs ma{};
         ma.first_scores = ix->w_fscores.as<float>(); ma.first_ids = ix->w_fids.as<int64_t>();
         ma.cand_score = ix->w_cscore.as<float>(); ma.cand_slot = ix->w_cslot.as<int64_t>();
         ma.cand_cnt = ix->w_ccnt.as<int32_t>(); ma.cap = cap; ma.ids = labels;
-        ma.kappa = kappa;
+        ma.kappa = kappa; ma.metric = metric; ma.qnorm = ix->w_qnorm.as<float>();
         ma.z = ix->w_z.as<float>(); ma.z_pitch = ix->dp; ma.d = ix->d; ma.b = bits; ma.cb = cb;
         ma.coarse = ix->w_coarse.as<float>(); ma.np = nprobe; ma.store = codes_store;
         ma.k = k; ma.out_scores = scores_dev + q0 * k; ma.out_ids = ids_dev + q0 * k;
@@ -1551,6 +1554,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, 0, 1, st); }));
             HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_redo_select(ra, st); }));
         }
+        HIP_TRY(launch_metric_finish(scores_dev + q0 * k, cnt, k, metric, ix->w_qnorm.as<float>(), st));
     }
     return IVFTQ_OK;
 }

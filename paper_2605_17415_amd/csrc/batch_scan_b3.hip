@@ -1,0 +1,8 @@
+// Batched list scan of 3 stored bits per coordinate.
+#include "batch_scan.h"
+
+namespace ivftq {
+
+hipError_t batch_scan_b3(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st) { return run_batch_width<3>(a, dp, max_tiles, st); }
+
+}  // namespace ivftq

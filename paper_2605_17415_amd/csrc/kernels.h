@@ -205,11 +205,11 @@ hipError_t launch_inertia(const double* gain, int L, int64_t n, double* out, hip
 // cand_off[q*(np+1) + p] = sum_{p'<p} list_size[probe[q][p']]
 // first (may be null): first[q] = shortest probe prefix (>= 1 cell) holding at least
 // max(k, 2*k*T/cap) vectors, T the query's candidate total; np if there is none.  With `first`, cand_cnt[q],
-// gate[0] and redo_cnt[q] (each may be null) are set to zero: the counters the batched scan, its merge and the
-// exact redo add to.
+// gate[0], redo_cnt[q] and bucket_cnt[0 .. buckets) (each may be null) are set to zero: the counters the batched
+// scan, its merge, the exact redo and the pair grouping add to.
 hipError_t launch_cand_offsets(const int32_t* probe, int64_t nq, int np, const int32_t* list_size,
                                int32_t* cand_off, int k, int cap, int32_t* first, int32_t* cand_cnt, int32_t* gate,
-                               int32_t* redo_cnt, hipStream_t st);
+                               int32_t* redo_cnt, uint32_t* bucket_cnt, int buckets, hipStream_t st);
 // scores[q*m_stride + cand_off[q][p] + i] = coarse[q][p] + gamma_i * sum_j z_qj * C[code_ij]
 struct ListScanArgs {
     const float* z; int z_pitch; int d;
@@ -223,7 +223,7 @@ struct ListScanArgs {
     // slack go, redo_cnt[q] of them in any order, to the first half of score row g - gate_begin, their columns
     // (cand_off[q][p] + i) to its second half; half a row has to hold every candidate.
     const int32_t* gate; int gate_begin, gate_rows;
-    const float* thresh; int thresh_stride; float slack; int32_t* redo_cnt;
+    const float* thresh; int thresh_stride; float slack; int32_t* redo_cnt;      // (slack: of the score, before a raw metric's key)
 };
 constexpr int kRedoWorkgroups = 2048;   // shared out over the queries a redo launch finds
 // blocks_per_query: workgroups per query (0 = one per probe), each walking its share of the probes; slices:
@@ -243,6 +243,19 @@ hipError_t launch_redo_select(const RedoSelectArgs& a, hipStream_t st);
 // the scan writes a key that ranks like the metric and launch_metric_finish turns the selected keys into values:
 //   metric 1 (inner product): key = |x| s^,                 value = |q| key            (descending)
 //   metric 2 (squared L2):    key = 2 |x| |q| s^ - |x|^2,   value = |q|^2 - key        (ascending; missing: +inf)
+__device__ __forceinline__ float metric_key(int metric, float s, float xn, float qn) {
+    return metric == 1 ? xn * s : fmaf(2.f * xn * qn, s, -xn * xn);
+}
+// the factor from a difference of scores to the difference of their keys
+__device__ __forceinline__ float metric_scale(int metric, float xn, float qn) { return metric == 1 ? xn : 2.f * xn * qn; }
+// An upper bound of metric_key over scores of at most s and lengths in [x_min, x_max].  The inner product key is
+// linear in the length; the distance key x (2 |q| s - x) has its one maximum at x = |q| s.  The rounding of a
+// key is at most a few units in the last place of its two terms.
+__device__ __forceinline__ float metric_key_bound(int metric, float s, float x_min, float x_max, float qn) {
+    if (metric == 1) return (s >= 0.f ? x_max : x_min) * s;
+    const float x = fminf(fmaxf(qn * s, x_min), x_max);
+    return fmaf(2.f * x * qn, s, -x * x) + 0x1p-20f * (x * x + fabsf(2.f * x * qn * s));
+}
 hipError_t launch_metric_finish(float* scores, int64_t nq, int k, int metric, const float* qnorm, hipStream_t st);
 // Per row: the k largest of m values, sorted by (value desc, label asc).
 // mode 0 (probe selection): m = m_fixed for every row, label = column; writes int32 labels.
@@ -288,22 +301,28 @@ hipError_t launch_cascade_rescore(const CascadeArgs& a, int64_t nq, hipStream_t 
 
 // ---- query-batched scan ------------------------------------------------------------------------
 
-// Queries one workgroup of the batched scan takes per tile for this (d, b); 0 = shape not covered
-// (the streaming scan is used instead).
-int batch_tile_queries(int d, int b);
+// Whether the batched scan covers this (d, b); otherwise the streaming scan is used.
+bool batch_covers(int d, int b);
+// Queries per workgroup tile: kBatchTile in the threshold pass; in the dense pass, whose panel holds both parts of
+// the queries and whose lists have few of them, as many where two workgroups still share a compute unit's LDS
+// (128 coordinates), half of that beyond (10M x 200, 11 queries a list: one workgroup of 111 KB per unit before).
+constexpr int kBatchTile = 128;
+constexpr int batch_tile_near(int dp) { return dp <= 128 ? kBatchTile : kBatchTile / 2; }
+int batch_near_queries(int d);
 
 // Buckets the (query, probe) pairs: bucket l holds the pairs (q, p < first[q]) of list l, bucket
 // L + l the pairs (q, p >= first[q]).  pairs[pair_off[b] ...] holds the flat pair numbers q*np + p
-// of bucket b; tile_off[b] counts workgroup tiles of tq queries (both arrays have 2L+1 entries).
-// count and cursor are scratch arrays of 2L entries.
-hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int64_t nq, int np, int L, int tq,
+// of bucket b; tile_off[b] counts workgroup tiles of tq_near (b < L) or tq queries (both arrays have 2L+1 entries),
+// tile_bucket[t] = the bucket of tile t.  count (cleared by launch_cand_offsets) and cursor are scratch arrays of
+// round_up(2L, 4) entries, 16-byte aligned.
+hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int64_t nq, int np, int L, int tq_near, int tq,
                                 uint32_t* count, uint32_t* cursor, int64_t* pair_off, int32_t* tile_off,
-                                int32_t* pairs, hipStream_t st);
+                                int32_t* tile_bucket, int32_t* pairs, hipStream_t st);
 
 struct BatchScanArgs {
     const uint16_t* zh; const uint16_t* zl; int z_pitch;   // split rotated queries, [nq][z_pitch] halves
     const float* cb;
-    const int32_t* pairs; const int64_t* pair_off; const int32_t* tile_off;
+    const int32_t* pairs; const int64_t* pair_off; const int32_t* tile_off; const int32_t* tile_bucket;
     const float* coarse;                 // [nq*np] coarse term of each (query, probe)
     const float* thresh; int thresh_stride;   // threshold of query q at thresh[q*thresh_stride]
     ListStore store; int np; int L;
@@ -313,8 +332,15 @@ struct BatchScanArgs {
     float acc0;                          // 2^20 * kappa: start value of the threshold pass's accumulators
     // dense mode (the nearest lists): every score goes to scores[q*m_stride + cand_off[q][p] + v]
     int dense; float* scores; int64_t m_stride; const int32_t* cand_off;
+    int metric; const float* qnorm;      // scores are ranking keys of a raw metric (metric_key)
 };
 hipError_t launch_batch_scan(const BatchScanArgs& a, int d, int b, int max_tiles, hipStream_t st);
+// one bit count each, dp = panel width
+hipError_t batch_scan_b2(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
+hipError_t batch_scan_b3(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
+hipError_t batch_scan_b4(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
+hipError_t batch_scan_b5(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
+hipError_t batch_scan_b8(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
 
 constexpr int kCandProbeShift = 48;      // a candidate's probe rank sits above its slot number (slots < 2^48, ranks < 2^12)
 
@@ -328,6 +354,7 @@ struct MergeArgs {
     // candidates of the threshold pass: upper bounds u of the score (true score in [u - 2*kappa*gamma, u])
     const float* cand_score; const int64_t* cand_slot; const int32_t* cand_cnt; int cap;
     float kappa;
+    int metric; const float* qnorm;                               // as in BatchScanArgs
     const float* z; int z_pitch; int d; int b; const float* cb;   // rotated queries (float32) and levels, for re-scoring
     const float* coarse; int np;                                  // [nq][np] coarse terms
     ListStore store;

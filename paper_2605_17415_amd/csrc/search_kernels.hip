@@ -19,7 +19,8 @@ __global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict_
                                                       const int32_t* __restrict__ list_size, int32_t* __restrict__ cand_off,
                                                       int k, int cap, int32_t* __restrict__ first,
                                                       int32_t* __restrict__ cand_cnt, int32_t* __restrict__ gate,
-                                                      int32_t* __restrict__ redo_cnt) {
+                                                      int32_t* __restrict__ redo_cnt, uint32_t* __restrict__ bucket_cnt, int buckets) {
+    for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < buckets; i += (int)(gridDim.x * blockDim.x)) bucket_cnt[i] = 0u;
     // one wavefront per query: 64 probes at a time, running sum over the lanes
     const int lane = threadIdx.x & 63;
     const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
     const float qn = metric ? a.qnorm[q] : 1.f;
     float reach = 0.f;
     if constexpr (REDO) {
-        reach = a.thresh[q * a.thresh_stride] - a.slack;
+        reach = a.thresh[q * a.thresh_stride];
         __syncthreads();               // the table of the previous query is no longer read
     }
 
@@ -235,18 +236,21 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
         }
         const float g = __half2float(__ushort_as_half(store.gamma[slot]));
         float sc = s_l + g * acc;
+        float margin = a.slack;
         if (metric) {                  // ranking key of a raw metric (see launch_metric_finish)
             const float xn = store.xnorm[slot];
-            sc = metric == 1 ? xn * sc : fmaf(2.f * xn * qn, sc, -xn * xn);
+            sc = metric_key(metric, sc, xn, qn);
+            if constexpr (REDO) margin = a.slack * metric_scale(metric, xn, qn);
         }
         if constexpr (REDO) {
-            const uint64_t in = __ballot(sc >= reach);           // one counter update per wavefront
+            const bool keep = sc >= reach - margin;
+            const uint64_t in = __ballot(keep);           // one counter update per wavefront
             if (in) {
                 const int lane = (int)(threadIdx.x & 63), leader = (int)__builtin_ctzll(in);
                 int at = 0;
                 if (lane == leader) at = atomicAdd(&a.redo_cnt[q], (int)__popcll(in));
                 at = __shfl(at, leader) + (int)__popcll(in & (((uint64_t)1 << lane) - 1));
-                if (sc >= reach) {
+                if (keep) {
                     out[at] = sc;
                     out[a.m_stride / 2 + at] = __int_as_float(col0 + v);
                 }
@@ -1268,10 +1272,10 @@ hipError_t launch_rerank(const RerankArgs& a, int64_t nq, hipStream_t st) {
 
 hipError_t launch_cand_offsets(const int32_t* probe, int64_t nq, int np, const int32_t* list_size,
                                int32_t* cand_off, int k, int cap, int32_t* first, int32_t* cand_cnt, int32_t* gate,
-                               int32_t* redo_cnt, hipStream_t st) {
+                               int32_t* redo_cnt, uint32_t* bucket_cnt, int buckets, hipStream_t st) {
     if (nq <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_cand_offsets, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, probe, nq, np,
-                       list_size, cand_off, k, cap, first, cand_cnt, gate, redo_cnt);
+                       list_size, cand_off, k, cap, first, cand_cnt, gate, redo_cnt, bucket_cnt, bucket_cnt ? buckets : 0);
     return hipGetLastError();
 }
 
