@@ -183,7 +183,7 @@ struct ivftq_index {
     DevBuf w_sums, w_counts, w_gain, w_rows, w_dst;
     DevBuf t_cent, t_cent_h, t_cent_l, t_bias;   // k-means works on its own tables; the index's change only on success
     DevBuf w_zh, w_zl;
-    DevBuf w_first, w_fscores, w_fids, w_pairs, w_pairoff, w_tileoff, w_tilebkt, w_cscore, w_cslot, w_ccnt, w_gate;
+    DevBuf w_first, w_fscores, w_fids, w_pairs, w_tilebkt, w_cscore, w_cslot, w_ccnt, w_gate;
     DevBuf w_stage_s, w_stage_i;      // survivors of the first step of a selection in two steps
     DevBuf w_part;                    // partial results of a coarse assignment whose centroid stages are shared out
     int64_t last_batched_queries = 0;   // queries of the last pass of the most recent batched search (ivftq_scan_stats)
@@ -198,7 +198,7 @@ struct ivftq_index {
         return {&cent, &cent_h, &cent_l, &pi_h, &pi_l, &pit_h, &pit_l, &bias, &pi, &cb, &q_grid, &codes, &gamma, &ids, &xnorm, &head, &w_qnorm, &d_off, &d_size, &w_assign,
                 &w_slot, &w_order, &w_hist, &w_count, &w_base, &w_flag, &w_undecided, &cb_cascade, &w_keep, &w_keep_scores,
                 &w_S, &w_probe, &w_coarse, &w_z, &w_candoff, &w_scores, &w_sums, &w_counts, &w_gain, &w_rows, &w_dst,
-                &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_pairoff, &w_tileoff, &w_tilebkt, &w_cscore,
+                &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_tilebkt, &w_cscore,
                 &w_cslot, &w_ccnt, &w_gate, &w_zh, &w_zl, &w_stage_s, &w_stage_i, &w_part};
     }
     explicit ivftq_index(const Allocator& a) : alloc(a) {
@@ -1174,13 +1174,13 @@ struct ScopedBuf {
 ivftq_status reconstruct_all(ivftq_index* ix, float* x_out, int64_t* ids_out, hipStream_t st) {
     const int L = ix->nlist;
     HIP_TRY(ix->w_base.ensure((size_t)2 * L * sizeof(int64_t)));
-    HIP_TRY(ix->w_tileoff.ensure((size_t)(2 * L + 1) * sizeof(int32_t)));
+    HIP_TRY(ix->w_tilebkt.ensure((size_t)(2 * L + 1) * sizeof(int32_t)));
     ReconstructArgs a{};
     a.store = ix->store(); a.L = L; a.sizes_host = ix->h_size.data();
     a.cent = ix->cent.as<float>(); a.cent_pitch = ix->dp;
     a.pit_h = ix->pit_h.as<uint16_t>(); a.pit_l = ix->pit_l.as<uint16_t>();
     a.cb = ix->cb.as<float>(); a.d = ix->d; a.b = ix->b;
-    a.out_off = ix->w_base.as<int64_t>(); a.tile_off = ix->w_tileoff.as<int32_t>();
+    a.out_off = ix->w_base.as<int64_t>(); a.tile_off = ix->w_tilebkt.as<int32_t>();
     a.x_out = x_out; a.labels_out = ids_out;
     HIP_TRY(launch_reconstruct(a, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -1364,7 +1364,6 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     // 170 queries, i.e. 0.41 / 1.5 / 2.7 GB streamed against an index of 0.066 / 0.58 / 1.04 GB).  Mode 2
     // asks for the batched path whatever the size of the call.
     constexpr double kBatchedGain = 2.3, kBatchedFixedBytes = 0.25e9;
-    const int tq = kBatchTile, tq_near = batch_near_queries(ix->d);
     const int metric = ix->metric;
     const double vec_bytes = (double)codes_store.words * 4 + 2;
     const double index_bytes = (double)ix->ntotal * vec_bytes;
@@ -1398,8 +1397,27 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     HIP_TRY(ix->w_z.ensure((size_t)qc * ix->dp * sizeof(float)));
     if (metric) HIP_TRY(ix->w_qnorm.ensure((size_t)qc * sizeof(float)));
     const int64_t n_pairs = qc * nprobe;
-    const int buckets = round_up(2 * ix->nlist, 4);
-    const int64_t max_tiles = n_pairs / tq_near + 2 * ix->nlist;     // tq_near <= tq
+    const int buckets = 2 * ix->nlist;
+    // Tiles of the batched passes: enough of them that the last ones to finish matter little (kTilesWanted over the
+    // chip's 512 to 1024 resident workgroups), no part of a list shorter than what one round of a workgroup's
+    // wavefronts covers.
+    constexpr int64_t kTilesWanted = 8192;
+    TileShape shape{};
+    shape.tq_near = kBatchTileNear; shape.tq = kBatchTile;
+    const int64_t typical_list = std::max<int64_t>(1, ix->ntotal / ix->nlist);
+    auto part_for = [&](int64_t tiles) {
+        const int64_t cuts = std::max<int64_t>(1, kTilesWanted / std::max<int64_t>(1, tiles));
+        return (int)std::min<int64_t>(4096, std::max<int64_t>(512, round_up64(typical_list / cuts, 64)));
+    };
+    shape.part_near = part_for(std::min<int64_t>(ix->nlist, n_pairs));
+    shape.part = part_for(std::min<int64_t>(ix->nlist, n_pairs) + n_pairs / shape.tq);
+    // at most: every list's parts once, and the parts of the longest for every further query tile
+    int64_t near_tiles = n_pairs / shape.tq_near * list_parts(sizes[0], shape.part_near);
+    int64_t late_tiles = n_pairs / shape.tq * list_parts(sizes[0], shape.part);
+    for (int32_t n : ix->h_size) {
+        near_tiles += list_parts(n, shape.part_near);
+        late_tiles += list_parts(n, shape.part);
+    }
     if (batched) {
         HIP_TRY(ix->w_zh.ensure((size_t)qc * ix->dp * sizeof(uint16_t)));
         HIP_TRY(ix->w_zl.ensure((size_t)qc * ix->dp * sizeof(uint16_t)));
@@ -1407,10 +1425,8 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         HIP_TRY(ix->w_fscores.ensure((size_t)qc * k * sizeof(float)));
         HIP_TRY(ix->w_fids.ensure((size_t)qc * k * sizeof(int64_t)));
         HIP_TRY(ix->w_pairs.ensure((size_t)n_pairs * sizeof(int32_t)));
-        HIP_TRY(ix->w_count.ensure((size_t)2 * buckets * sizeof(uint32_t)));
-        HIP_TRY(ix->w_pairoff.ensure((size_t)(2 * ix->nlist + 1) * sizeof(int64_t)));
-        HIP_TRY(ix->w_tileoff.ensure((size_t)(2 * ix->nlist + 1) * sizeof(int32_t)));
-        HIP_TRY(ix->w_tilebkt.ensure((size_t)max_tiles * sizeof(int32_t)));
+        HIP_TRY(ix->w_count.ensure((size_t)(4 * buckets + 8) * sizeof(uint32_t)));
+        HIP_TRY(ix->w_tilebkt.ensure((size_t)(near_tiles + late_tiles) * sizeof(int32_t)));
         HIP_TRY(ix->w_cscore.ensure((size_t)qc * cap * sizeof(float)));
         HIP_TRY(ix->w_cslot.ensure((size_t)qc * cap * sizeof(int64_t)));
         HIP_TRY(ix->w_ccnt.ensure((size_t)qc * sizeof(int32_t)));
@@ -1442,7 +1458,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             return launch_cand_offsets(ix->w_probe.as<int32_t>(), cnt, nprobe, ix->d_size.as<int32_t>(),
                                        ix->w_candoff.as<int32_t>(), k, cap, first,
                                        batched ? ix->w_ccnt.as<int32_t>() : nullptr, batched ? ix->w_gate.as<int32_t>() : nullptr,
-                                       redo_cnt, batched ? ix->w_count.as<uint32_t>() : nullptr, buckets, st); }));
+                                       redo_cnt, batched ? ix->w_count.as<uint32_t>() : nullptr, buckets + 8, st); }));
         ListScanArgs la{};
         la.z = ix->w_z.as<float>(); la.z_pitch = ix->dp; la.d = ix->d; la.cb = cb;
         la.probe = ix->w_probe.as<int32_t>(); la.coarse = ix->w_coarse.as<float>();
@@ -1498,18 +1514,16 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
 
         // 1. (query, probe) pairs bucketed by list; the nearest lists of each query in their own buckets
         ix->last_batched_queries = cnt;
-        const int64_t np_items = cnt * nprobe;
+        PairTable pt{};
+        pt.count = ix->w_count.as<uint32_t>(); pt.totals = reinterpret_cast<int32_t*>(pt.count + buckets);
+        pt.cursor = pt.count + buckets + 8; pt.pair_off = reinterpret_cast<int32_t*>(pt.cursor + buckets); pt.tile_off = pt.pair_off + buckets;
+        pt.tile_near = ix->w_tilebkt.as<int32_t>(); pt.tile_late = pt.tile_near + near_tiles; pt.pairs = ix->w_pairs.as<int32_t>();
         HIP_TRY(timed(ix, st, P_PAIR_GROUP, [&] {
-            hipError_t e = launch_pair_grouping(ix->w_probe.as<int32_t>(), first, cnt, nprobe, ix->nlist, tq_near, tq,
-                                                ix->w_count.as<uint32_t>(), ix->w_count.as<uint32_t>() + buckets,
-                                                ix->w_pairoff.as<int64_t>(), ix->w_tileoff.as<int32_t>(), ix->w_tilebkt.as<int32_t>(),
-                                                ix->w_pairs.as<int32_t>(), st);
-            return e; }));
+            return launch_pair_grouping(ix->w_probe.as<int32_t>(), first, cnt, nprobe, ix->nlist, ix->d_size.as<int32_t>(), shape, pt, st); }));
         BatchScanArgs ba{};
         ba.zh = ix->w_zh.as<uint16_t>(); ba.zl = ix->w_zl.as<uint16_t>(); ba.z_pitch = ix->dp;
         ba.cb = cb;
-        ba.pairs = ix->w_pairs.as<int32_t>(); ba.pair_off = ix->w_pairoff.as<int64_t>();
-        ba.tile_off = ix->w_tileoff.as<int32_t>(); ba.tile_bucket = ix->w_tilebkt.as<int32_t>();
+        ba.p = pt;
         ba.metric = metric; ba.qnorm = ix->w_qnorm.as<float>();
         ba.coarse = ix->w_coarse.as<float>();
         ba.store = codes_store; ba.np = nprobe; ba.L = ix->nlist;
@@ -1518,16 +1532,16 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         ba.acc0 = kappa * kSplitScale * kSplitScale;
         ba.scores = ix->w_scores.as<float>(); ba.m_stride = row_stride; ba.cand_off = ix->w_candoff.as<int32_t>();
         // 2. every score of the nearest lists, then their top-k: the k-th is the query's threshold
-        ba.dense = 1; ba.bucket_lo = 0; ba.bucket_hi = ix->nlist;
-        HIP_TRY(timed(ix, st, P_BATCH_FIRST, [&] { return launch_batch_scan(ba, ix->d, bits, (int)(np_items / tq_near) + ix->nlist, st); }));
+        ba.dense = 1; ba.part_len = shape.part_near;
+        HIP_TRY(timed(ix, st, P_BATCH_FIRST, [&] { return launch_batch_scan(ba, ix->d, bits, st); }));
         SelectArgs s1 = sa;
         s1.p_limit = first; s1.out_vals = ix->w_fscores.as<float>(); s1.out_i64 = ix->w_fids.as<int64_t>();
         s1.stride = row_stride; s1.m_bound = (int)row_stride;
         HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_select(1, s1, st); }));
         // 3. the other lists against the thresholds
-        ba.dense = 0; ba.bucket_lo = ix->nlist; ba.bucket_hi = 2 * ix->nlist;
+        ba.dense = 0; ba.part_len = shape.part;
         ba.thresh = ix->w_fscores.as<float>() + (k - 1); ba.thresh_stride = k;
-        HIP_TRY(timed(ix, st, P_BATCH_SCAN, [&] { return launch_batch_scan(ba, ix->d, bits, (int)(np_items / tq) + ix->nlist, st); }));
+        HIP_TRY(timed(ix, st, P_BATCH_SCAN, [&] { return launch_batch_scan(ba, ix->d, bits, st); }));
         // 4. merge; a query whose candidate list overflowed is redone by the exact streaming scan
         MergeArgs ma{};
         ma.first_scores = ix->w_fscores.as<float>(); ma.first_ids = ix->w_fids.as<int64_t>();

@@ -31,61 +31,51 @@ __global__ void k_pair_count(const int32_t* __restrict__ probe, const int32_t* _
     atomicAdd(&count[probe[it] + (late ? L : 0)], 1u);
 }
 
-// Over the nb = 2L buckets: pair_off[b] = first pair of bucket b; tile_off[b] = first workgroup tile
-// of bucket b, tq_near queries a tile for the first half of the buckets, tq for the others (entry nb = totals);
-// tile_bucket[tile_off[b] + i] = b; cursor[b] = 0.  One workgroup: every thread takes a run of buckets, four at a
-// time, and the runs are put together with one scan over lanes and wavefronts (8192 buckets: 0.019 ms with a
-// 1024-wide scan in LDS and single loads).
-__global__ __launch_bounds__(1024) void k_pair_prefix(const uint32_t* __restrict__ count, int nb, int L, int tq_near, int tq,
-                                                      int64_t* __restrict__ pair_off, int32_t* __restrict__ tile_off,
-                                                      int32_t* __restrict__ tile_bucket, uint32_t* __restrict__ cursor) {
-    __shared__ uint32_t wave_c[16], wave_t[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int quads = (nb + 3) / 4, per = (quads + 1023) / 1024;
-    auto tiles_of = [&](uint32_t n, int b) -> uint32_t { const uint32_t w = b < L ? tq_near : tq; return (n + w - 1) / w; };
-    uint32_t c = 0, t = 0;
-    for (int e = 0; e < per; ++e) {
-        const int i = tid * per + e;
-        if (i >= quads) break;
-        const uint4 n = reinterpret_cast<const uint4*>(count)[i];
-        c += n.x + n.y + n.z + n.w;
-        t += tiles_of(n.x, 4 * i) + tiles_of(n.y, 4 * i + 1) + tiles_of(n.z, 4 * i + 2) + tiles_of(n.w, 4 * i + 3);
-        reinterpret_cast<uint4*>(cursor)[i] = make_uint4(0, 0, 0, 0);
-    }
-    uint32_t ic = c, it = t;                        // inclusive over the lanes
+// Every bucket gets a range of the pair array (pair_off) and of its pass's tile array (tile_off, tile_bucket), and
+// cursor[b] = 0.  One thread per bucket; a workgroup puts its buckets together with a scan and takes its ranges from
+// the totals with one atomic each, so the ranges of different workgroups lie in no particular order, which nothing
+// depends on (in bucket order, by one workgroup: 0.017 ms for 8192 buckets, the chain of its loads).
+__global__ __launch_bounds__(256) void k_pair_ranges(const int32_t* __restrict__ list_size, int nb, int L, TileShape shape, PairTable p) {
+    __shared__ uint32_t part[4][3];
+    __shared__ int32_t start[3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = (int)blockIdx.x * 256 + tid;
+    const bool in = b < nb, near = b < L;
+    const uint32_t n = in ? p.count[b] : 0u;
+    const int size = in ? list_size[near ? b : b - L] : 0;
+    if (in) p.cursor[b] = 0u;
+    const uint32_t w = near ? shape.tq_near : shape.tq;
+    const uint32_t tiles = size > 0 ? (n + w - 1) / w * list_parts(size, near ? shape.part_near : shape.part) : 0u;
+    const uint32_t own[3] = {n, near ? tiles : 0u, near ? 0u : tiles};
+    uint32_t incl[3] = {own[0], own[1], own[2]};
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t pc = __shfl_up(ic, o), pt = __shfl_up(it, o);
-        if (lane >= o) { ic += pc; it += pt; }
-    }
-    if (lane == 63) { wave_c[wave] = ic; wave_t[wave] = it; }
-    __syncthreads();
-    uint32_t rc = ic - c, rt = it - t, all_c = 0, all_t = 0;
-    for (int w = 0; w < 16; ++w) {
-        if (w < wave) { rc += wave_c[w]; rt += wave_t[w]; }
-        all_c += wave_c[w];
-        all_t += wave_t[w];
-    }
-    for (int e = 0; e < per; ++e) {
-        const int i = tid * per + e;
-        if (i >= quads) break;
-        const uint4 n4 = reinterpret_cast<const uint4*>(count)[i];
-        const uint32_t n[4] = {n4.x, n4.y, n4.z, n4.w};
+    for (int o = 1; o < 64; o <<= 1)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int b = 4 * i + u;
-            if (b >= nb) break;                     // (the counters beyond it are zero)
-            pair_off[b] = rc;
-            tile_off[b] = (int32_t)rt;
-            rc += n[u];
-            for (uint32_t k = tiles_of(n[u], b); k > 0; --k) tile_bucket[rt++] = b;
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t v = __shfl_up(incl[i], o);
+            if (lane >= o) incl[i] += v;
         }
+    if (lane == 63)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) part[wave][i] = incl[i];
+    __syncthreads();
+    if (tid < 3) start[tid] = atomicAdd(&p.totals[tid], (int32_t)(part[0][tid] + part[1][tid] + part[2][tid] + part[3][tid]));
+    __syncthreads();
+    int32_t at[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        at[i] = start[i] + (int32_t)(incl[i] - own[i]);
+        for (int w2 = 0; w2 < wave; ++w2) at[i] += (int32_t)part[w2][i];
     }
-    if (tid == 0) { pair_off[nb] = all_c; tile_off[nb] = (int32_t)all_t; }
+    if (!in) return;
+    p.pair_off[b] = at[0];
+    const int32_t t0 = near ? at[1] : at[2];
+    p.tile_off[b] = t0;
+    int32_t* to = near ? p.tile_near : p.tile_late;
+    for (uint32_t t = 0; t < tiles; ++t) to[t0 + t] = b;
 }
 
 __global__ void k_pair_scatter(const int32_t* __restrict__ probe, const int32_t* __restrict__ first, int64_t nq,
-                               int np, int L, const int64_t* __restrict__ pair_off,
+                               int np, int L, const int32_t* __restrict__ pair_off,
                                uint32_t* __restrict__ cursor, int32_t* __restrict__ pairs) {
     const int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (it >= nq * np) return;
@@ -120,7 +110,7 @@ __global__ __launch_bounds__(1024) void k_pair_count_lds(const int32_t* __restri
 
 __global__ __launch_bounds__(1024) void k_pair_scatter_lds(const int32_t* __restrict__ probe,
                                                            const int32_t* __restrict__ first, int64_t nq, int np,
-                                                           int L, const int64_t* __restrict__ pair_off,
+                                                           int L, const int32_t* __restrict__ pair_off,
                                                            uint32_t* __restrict__ cursor, int32_t* __restrict__ pairs) {
     extern __shared__ uint32_t bins[];                   // [2L] count, then first position of this workgroup's range
     for (int i = threadIdx.x; i < 2 * L; i += 1024) bins[i] = 0u;
@@ -363,44 +353,40 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
 static int batch_dp(int d) { return (d > 192 && d <= 208) ? 208 : d <= 64 ? 64 : rot_dp(d); }
 
 bool batch_covers(int d, int b) { return d <= kMaxD && ((b >= 2 && b <= 5) || b == 8); }
-int batch_near_queries(int d) { return batch_tile_near(batch_dp(d)); }
 
-hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int64_t nq, int np, int L, int tq_near, int tq,
-                               uint32_t* count, uint32_t* cursor, int64_t* pair_off, int32_t* tile_off,
-                               int32_t* tile_bucket, int32_t* pairs, hipStream_t st) {
+hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int64_t nq, int np, int L, const int32_t* list_size,
+                                const TileShape& shape, const PairTable& p, hipStream_t st) {
     const int64_t n = nq * np;
     if (n <= 0) return hipSuccess;
-    hipError_t e = hipSuccess;
-    const int nb = 2 * L;                 // launch_cand_offsets has cleared round_up(2L, 4) counters
-    if (2 * L <= kPairLdsBuckets) {
+    const bool in_lds = 2 * L <= kPairLdsBuckets;
+    const unsigned blocks = (unsigned)(in_lds ? (n + kPairChunk - 1) / kPairChunk : (n + 255) / 256);
+    const size_t lds = (size_t)2 * L * sizeof(uint32_t);
+    if (in_lds) {
         static LdsLimit lim_count, lim_scatter;
         const size_t most = (size_t)kPairLdsBuckets * sizeof(uint32_t);
-        e = lim_count.ensure(reinterpret_cast<const void*>(k_pair_count_lds), most);
+        hipError_t e = lim_count.ensure(reinterpret_cast<const void*>(k_pair_count_lds), most);
         if (e == hipSuccess) e = lim_scatter.ensure(reinterpret_cast<const void*>(k_pair_scatter_lds), most);
         if (e != hipSuccess) return e;
-        const unsigned blocks = (unsigned)((n + kPairChunk - 1) / kPairChunk);
-        const size_t lds = (size_t)2 * L * sizeof(uint32_t);
-        hipLaunchKernelGGL(k_pair_count_lds, dim3(blocks), dim3(1024), lds, st, probe, first, nq, np, L, count);
-        hipLaunchKernelGGL(k_pair_prefix, dim3(1), dim3(1024), 0, st, count, nb, L, tq_near, tq, pair_off, tile_off, tile_bucket, cursor);
-        hipLaunchKernelGGL(k_pair_scatter_lds, dim3(blocks), dim3(1024), lds, st, probe, first, nq, np, L, pair_off, cursor, pairs);
-        return hipGetLastError();
+        hipLaunchKernelGGL(k_pair_count_lds, dim3(blocks), dim3(1024), lds, st, probe, first, nq, np, L, p.count);
+    } else {
+        hipLaunchKernelGGL(k_pair_count, dim3(blocks), dim3(256), 0, st, probe, first, nq, np, L, p.count);
     }
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL(k_pair_count, dim3(blocks), dim3(256), 0, st, probe, first, nq, np, L, count);
-    hipLaunchKernelGGL(k_pair_prefix, dim3(1), dim3(1024), 0, st, count, nb, L, tq_near, tq, pair_off, tile_off, tile_bucket, cursor);
-    hipLaunchKernelGGL(k_pair_scatter, dim3(blocks), dim3(256), 0, st, probe, first, nq, np, L, pair_off, cursor, pairs);
+    hipLaunchKernelGGL(k_pair_ranges, dim3((unsigned)((2 * L + 255) / 256)), dim3(256), 0, st, list_size, 2 * L, L, shape, p);
+    if (in_lds)
+        hipLaunchKernelGGL(k_pair_scatter_lds, dim3(blocks), dim3(1024), lds, st, probe, first, nq, np, L, (const int32_t*)p.pair_off, p.cursor, p.pairs);
+    else
+        hipLaunchKernelGGL(k_pair_scatter, dim3(blocks), dim3(256), 0, st, probe, first, nq, np, L, (const int32_t*)p.pair_off, p.cursor, p.pairs);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_scan(const BatchScanArgs& a, int d, int b, int max_tiles, hipStream_t st) {
-    if (max_tiles <= 0) return hipSuccess;
+hipError_t launch_batch_scan(const BatchScanArgs& a, int d, int b, hipStream_t st) {
     if (a.metric && (!a.qnorm || !a.store.xnorm)) return hipErrorInvalidValue;
     switch (b) {
-        case 2: return batch_scan_b2(a, batch_dp(d), max_tiles, st);
-        case 3: return batch_scan_b3(a, batch_dp(d), max_tiles, st);
-        case 4: return batch_scan_b4(a, batch_dp(d), max_tiles, st);
-        case 5: return batch_scan_b5(a, batch_dp(d), max_tiles, st);
-        case 8: return batch_scan_b8(a, batch_dp(d), max_tiles, st);
+        case 2: return batch_scan_b2(a, batch_dp(d), st);
+        case 3: return batch_scan_b3(a, batch_dp(d), st);
+        case 4: return batch_scan_b4(a, batch_dp(d), st);
+        case 5: return batch_scan_b5(a, batch_dp(d), st);
+        case 8: return batch_scan_b8(a, batch_dp(d), st);
         default: return hipErrorInvalidValue;
     }
 }

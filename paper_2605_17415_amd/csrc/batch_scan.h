@@ -51,21 +51,45 @@ __device__ __forceinline__ uint64_t code_chunk(const uint32_t (&w)[NW], int kb, 
     else return (((uint64_t)w[1] << 32) | w[0]) >> sh;
 }
 
-// Which list and queries a workgroup works on.
+// Which part of which list, and which queries, one tile of a pass covers.
 struct BatchTile {
-    int l, n_l, nq_tile;
+    int l, v_lo, v_hi, nq_tile;          // vectors [v_lo, v_hi) of list l; v_lo is a multiple of 64
     int64_t pair0, base_slot;
-    __device__ __forceinline__ bool find(const BatchScanArgs& a, int tq) {
-        const int my_tile = (int)blockIdx.x + a.tile_off[a.bucket_lo];
-        if (my_tile >= a.tile_off[a.bucket_hi]) return false;
-        const int bkt = a.tile_bucket[my_tile];
+    __device__ __forceinline__ void find(const BatchScanArgs& a, int tile, int tq) {
+        const int bkt = (a.dense ? a.p.tile_near : a.p.tile_late)[tile];
         l = bkt >= a.L ? bkt - a.L : bkt;
-        pair0 = a.pair_off[bkt] + (int64_t)(my_tile - a.tile_off[bkt]) * tq;
-        const int64_t left = a.pair_off[bkt + 1] - pair0;
-        nq_tile = (int)(left < tq ? left : tq);
-        n_l = a.store.list_size[l];
+        const int n_l = a.store.list_size[l], parts = list_parts(n_l, a.part_len), rel = tile - a.p.tile_off[bkt];
+        const int len = ((n_l + parts - 1) / parts + 63) & ~63;
+        v_lo = (rel % parts) * len;
+        v_hi = v_lo + len < n_l ? v_lo + len : n_l;
+        const int skip = rel / parts * tq, left = (int)a.p.count[bkt] - skip;
+        pair0 = (int64_t)a.p.pair_off[bkt] + skip;
+        nq_tile = left < tq ? left : tq;
         base_slot = a.store.list_off[l];
-        return n_l > 0 && nq_tile > 0;
+    }
+};
+
+// The workgroups of a launch are as many as the chip holds and take tiles from a common counter until none is
+// left: tiles differ in work by the sizes of the lists and the queries that meet there, and with a workgroup per
+// tile the compute units stood idle for 22 % of the passes at 10M x 96 (waiting for the last ones), the launch
+// besides being sized for the most tiles there could be.  The next number is fetched while a tile is worked on.
+struct TileQueue {
+    const BatchScanArgs& a;
+    int* s_next;                         // [2] in LDS
+    int turn = 0, end;
+    __device__ __forceinline__ TileQueue(const BatchScanArgs& args, int* lds) : a(args), s_next(lds) {
+        end = a.p.totals[a.dense ? 1 : 2];
+        request();
+    }
+    __device__ __forceinline__ void request() {
+        if (threadIdx.x == 0) s_next[turn] = atomicAdd(&a.p.totals[a.dense ? 3 : 4], 1);
+    }
+    // the tile to work on (past `end`: none); a barrier for the workgroup
+    __device__ __forceinline__ int take() {
+        __syncthreads();
+        const int tile = s_next[turn];
+        turn ^= 1;
+        return __builtin_amdgcn_readfirstlane(tile);
     }
 };
 
@@ -75,12 +99,14 @@ template <int DP, int TQ, int NT, bool LO, class Word>
 __device__ __forceinline__ void stage_queries(const BatchScanArgs& a, const BatchTile& t, uint16_t* zh, uint16_t* zl, uint4* s_row,
                                               uint4 none, Word word) {
     constexpr int LDH = DP + 8;
-    for (int e = threadIdx.x; e < TQ; e += NT) s_row[e] = e < t.nq_tile ? word(a.pairs[t.pair0 + e]) : none;
-    for (int e = threadIdx.x; e < TQ * (DP / 8); e += NT) {           // 16-byte pieces
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));        // or what follows from it is computed once and kept in registers from tile to tile
+    for (int e = tid; e < TQ; e += NT) s_row[e] = e < t.nq_tile ? word(a.p.pairs[t.pair0 + e]) : none;
+    for (int e = tid; e < TQ * (DP / 8); e += NT) {           // 16-byte pieces
         const int r = e / (DP / 8), c8 = e % (DP / 8);
         uint4 vh = make_uint4(0, 0, 0, 0), vl = make_uint4(0, 0, 0, 0);
         if (r < t.nq_tile && c8 * 8 < a.z_pitch) {
-            const int64_t at = (int64_t)(a.pairs[t.pair0 + r] / a.np) * a.z_pitch + c8 * 8;
+            const int64_t at = (int64_t)(a.p.pairs[t.pair0 + r] / a.np) * a.z_pitch + c8 * 8;
             vh = *reinterpret_cast<const uint4*>(a.zh + at);
             if (LO) vl = *reinterpret_cast<const uint4*>(a.zl + at);
         }
@@ -147,27 +173,8 @@ void k_batch_dense(BatchScanArgs a) {
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, jl = lane & 31;
-    BatchTile t;
-    if (!t.find(a, Cfg::TQ)) return;
-    const int n_l = t.n_l, nslab = (n_l + 31) / 32, n_qt = (t.nq_tile + 31) / 32;
     constexpr float kUnscale = 1.f / (kSplitScale * kSplitScale);
 
-    // Raw words and norm of a slab are fetched one slab ahead, so that their latency hides behind the current one.
-    auto fetch = [&](int slab, uint32_t (&w)[KB][NW], uint32_t& g) {
-        const int v = slab * 32 + jl;
-        const int64_t slot = t.base_slot + (v < n_l ? v : n_l - 1);
-        fetch_words<KB, B, NW>(a.store.codes + (slot >> 6) * a.store.words * 64 + (slot & 63), a.store.words, half, w);
-        g = a.store.gamma[slot];
-    };
-    uint32_t cw[KB][NW], nw[KB][NW], cg, ng;
-    int slab = wave;
-    if (slab < nslab) fetch(slab, cw, cg);
-
-    stage_queries<DP, Cfg::TQ, NT, true>(a, t, zh, zl, s_row, make_uint4(0, 0, 0, 0), [&](int32_t it) {
-        const int32_t q = it / a.np;
-        const int64_t at = (int64_t)q * a.m_stride + a.cand_off[(int64_t)q * (a.np + 1) + (it - q * a.np)];
-        return make_uint4(__float_as_uint(a.coarse[it]), (uint32_t)at, (uint32_t)(at >> 32), a.metric ? __float_as_uint(a.qnorm[q]) : 0u);
-    });
     for (int e = tid; e < Cfg::PT; e += NT) {
         uint32_t hp = 0, lp = 0;
 #pragma unroll
@@ -181,10 +188,34 @@ void k_batch_dense(BatchScanArgs a) {
         if (Cfg::PAIR) tab[e] = make_uint2(hp, lp);
         else reinterpret_cast<uint32_t*>(tab)[e] = hp | (lp << 16);
     }
-    __syncthreads();
-
     const uint16_t* bh_base = zh + jl * Cfg::LDH + 8 * half;
     const uint16_t* bl_base = zl + jl * Cfg::LDH + 8 * half;
+    __shared__ __align__(16) int s_next[4];      // (16 bytes: the panel behind it keeps its alignment)
+    TileQueue queue(a, s_next);
+    for (int tile; (tile = queue.take()) < queue.end;) {
+    BatchTile t;
+    t.find(a, tile, Cfg::TQ);
+    const int v_lo = t.v_lo, v_hi = t.v_hi, nslab = (v_hi - v_lo + 31) / 32, n_qt = (t.nq_tile + 31) / 32;
+
+    // Raw words and norm of a slab are fetched one slab ahead, so that their latency hides behind the current one.
+    auto fetch = [&](int slab, uint32_t (&w)[KB][NW], uint32_t& g) {
+        const int v = v_lo + slab * 32 + jl;
+        const int64_t slot = t.base_slot + (v < v_hi ? v : v_hi - 1);
+        fetch_words<KB, B, NW>(a.store.codes + (slot >> 6) * a.store.words * 64 + (slot & 63), a.store.words, half, w);
+        g = a.store.gamma[slot];
+    };
+    uint32_t cw[KB][NW], nw[KB][NW], cg, ng;
+    int slab = wave;
+    if (slab < nslab) fetch(slab, cw, cg);
+
+    stage_queries<DP, Cfg::TQ, NT, true>(a, t, zh, zl, s_row, make_uint4(0, 0, 0, 0), [&](int32_t it) {
+        const int32_t q = it / a.np;
+        const int64_t at = (int64_t)q * a.m_stride + a.cand_off[(int64_t)q * (a.np + 1) + (it - q * a.np)];
+        return make_uint4(__float_as_uint(a.coarse[it]), (uint32_t)at, (uint32_t)(at >> 32), a.metric ? __float_as_uint(a.qnorm[q]) : 0u);
+    });
+    __syncthreads();
+    queue.request();
+
     while (slab < nslab) {
         const int next = slab + WAVES;
         if (next < nslab) fetch(next, nw, ng);
@@ -211,9 +242,9 @@ void k_batch_dense(BatchScanArgs a) {
             al[kb] = __builtin_bit_cast(half8, make_uint4(lv[0], lv[1], lv[2], lv[3]));
         }
         const float g = kUnscale * __half2float(__ushort_as_half((uint16_t)cg));      // 2^-20 * norm of this lane's vector
-        const int v = slab * 32 + jl;
+        const int v = v_lo + slab * 32 + jl;
         float xn = 0.f;
-        if (a.metric) xn = a.store.xnorm[t.base_slot + (v < n_l ? v : n_l - 1)];
+        if (a.metric) xn = a.store.xnorm[t.base_slot + (v < v_hi ? v : v_hi - 1)];
         for (int qt = 0; qt < n_qt; ++qt) {
             floatx16 acc;
 #pragma unroll
@@ -228,6 +259,13 @@ void k_batch_dense(BatchScanArgs a) {
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl, ah[kb], acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh, al[kb], acc, 0, 0, 0);
             }
+            // (panel reads two blocks ahead of the products, see the threshold pass)
+            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            }
             // result row r of this lane: query 8*(r/4) + 4*half + r%4 of the tile, vector jl of the slab
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -238,7 +276,7 @@ void k_batch_dense(BatchScanArgs a) {
                 const uint4 row = s_row[e];
                 float sc = fmaf(g, acc[r], __uint_as_float(row.x));
                 if (a.metric) sc = metric_key(a.metric, sc, xn, __uint_as_float(row.w));
-                if (e < t.nq_tile && v < n_l) a.scores[(int64_t)(((uint64_t)row.z << 32) | row.y) + v] = sc;
+                if (e < t.nq_tile && v < v_hi) a.scores[(int64_t)(((uint64_t)row.z << 32) | row.y) + v] = sc;
             }
         }
 #pragma unroll
@@ -248,25 +286,27 @@ void k_batch_dense(BatchScanArgs a) {
         cg = ng;
         slab = next;
     }
+    }
 }
 
 // ---- threshold pass: the other lists, only scores that can reach the query's threshold kept ------------
 //
 // The vectors are the row operand, so a lane holds one query's scores against 16 vectors and needs that query's
 // coarse term and threshold only once.  Only the leading float16 parts are multiplied (one product instead of
-// three): the accumulators start at acc0 = 2^20 * kappa, kappa bounding the error of such a sum for a unit query,
+// three): acc0 = 2^20 * kappa is added to the accumulators, kappa bounding the error of such a sum for a unit query,
 // so what is compared with the threshold and appended is an upper bound of the true score (true score in
 // [u - 2*kappa*gamma, u]); k_merge re-scores from the packed codes the few that can still matter.
 //
-// A wavefront takes a storage block of 64 vectors at a time, two row tiles, so that every panel row it reads from
-// LDS feeds two matrix instructions: with one row tile a panel read (8 LDS cycles, shared by four SIMDs) per
+// A wavefront takes a storage block of 64 vectors at a time, two row tiles (S = 2), so that every panel row it reads
+// from LDS feeds two matrix instructions: with one row tile a panel read (8 LDS cycles, shared by four SIMDs) per
 // matrix instruction (32 cycles) alone would keep LDS as busy as the matrix pipes, and the look-ups come on top.
-// RAW: scores are ranking keys of a raw metric (a template parameter: the lengths' range takes registers).
-template <int DP, int B, int NQ, int WAVES, int OCC, bool RAW>
+// S = row tiles per wavefront (one where the registers do not reach for two).  RAW: scores are ranking keys of a raw
+// metric (a template parameter: the lengths' range takes registers).
+template <int DP, int B, int NQ, int WAVES, int OCC, int S, bool RAW>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(OCC)))
 void k_batch_threshold(BatchScanArgs a) {
     using Cfg = BatchCfg<DP, B, NQ>;
-    constexpr int KB = DP / 16, NT = WAVES * 64, S = 2;
+    constexpr int KB = DP / 16, NT = WAVES * 64, VB = 32 * S;      // vectors of a block
     constexpr int NW = (B == 2 || B == 4) ? 1 : 2;
     extern __shared__ unsigned char lds_raw[];
     uint16_t* zh = reinterpret_cast<uint16_t*>(lds_raw);                       // [TQ][LDH] hi parts of the rotated queries
@@ -275,27 +315,8 @@ void k_batch_threshold(BatchScanArgs a) {
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, jl = lane & 31;
-    BatchTile t;
-    if (!t.find(a, Cfg::TQ)) return;
-    const int n_l = t.n_l, nblk = (n_l + 63) / 64, n_qt = (t.nq_tile + 31) / 32;
     constexpr float kUnscale = 1.f / (kSplitScale * kSplitScale);
 
-    // A list starts at a multiple of 64 slots and its slots reach to one, so a block's words and norms can be read
-    // whole; what lies beyond the list is replaced by NaN norms below.
-    const int words = a.store.words;
-    const uint32_t* codes = a.store.codes + (t.base_slot >> 6) * words * 64 + jl;
-    uint32_t cw[S][KB][NW];
-    int blk = wave;
-    if (blk < nblk) {
-#pragma unroll
-        for (int s = 0; s < S; ++s) fetch_words<KB, B, NW>(codes + (int64_t)blk * words * 64 + 32 * s, words, half, cw[s]);
-    }
-
-    stage_queries<DP, Cfg::TQ, NT, false>(a, t, zh, nullptr, s_row, make_uint4(0, 0x7F800000u, 0, 0), [&](int32_t it) {
-        const int32_t q = it / a.np;
-        return make_uint4(__float_as_uint(a.coarse[it]), __float_as_uint(a.thresh[(int64_t)q * a.thresh_stride]), (uint32_t)it,
-                          RAW ? __float_as_uint(a.qnorm[q]) : 0u);
-    });
     for (int e = tid; e < Cfg::PT; e += NT) {
         uint32_t hp = 0;
 #pragma unroll
@@ -303,20 +324,40 @@ void k_batch_threshold(BatchScanArgs a) {
             hp |= (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(a.cb[(e >> (i * B)) & ((1 << B) - 1)] * kSplitScale)) << (16 * i);
         tab[e] = hp;
     }
-    __syncthreads();
-
-    // acc0 in every element, kept in registers for the whole kernel (hidden from the compiler, which would
-    // otherwise write the 16 registers anew from scalars for every tile)
-    floatx16 acc_init;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc_init[r] = a.acc0;
-    asm volatile("" : "+v"(acc_init));
     const uint16_t* bh_base = zh + jl * Cfg::LDH + 8 * half;
+    const int words = a.store.words;
+    __shared__ __align__(16) int s_next[4];      // (16 bytes: the panel behind it keeps its alignment)
+    TileQueue queue(a, s_next);
+    for (int tile; (tile = queue.take()) < queue.end;) {
+    BatchTile t;
+    t.find(a, tile, Cfg::TQ);
+    const int v_lo = t.v_lo, v_hi = t.v_hi, nblk = (v_hi - v_lo + VB - 1) / VB, n_qt = (t.nq_tile + 31) / 32;
 
+    // A list starts at a multiple of 64 slots and its slots reach to one, so a block's words and norms can be read
+    // whole; what lies beyond the list is replaced by NaN norms below.
+    const uint32_t* codes = a.store.codes + ((t.base_slot + v_lo) >> 6) * words * 64 + jl;
+    uint32_t cw[S][KB][NW];
+    int blk = wave;
+    auto fetch = [&](int b) {
+        const uint32_t* at = codes + (int64_t)((b * VB) >> 6) * words * 64 + ((b * VB) & 63);
+#pragma unroll
+        for (int s = 0; s < S; ++s) fetch_words<KB, B, NW>(at + 32 * s, words, half, cw[s]);
+    };
+    if (blk < nblk) fetch(blk);
+
+    stage_queries<DP, Cfg::TQ, NT, false>(a, t, zh, nullptr, s_row, make_uint4(0, 0x7F800000u, 0, 0), [&](int32_t it) {
+        const int32_t q = it / a.np;
+        return make_uint4(__float_as_uint(a.coarse[it]), __float_as_uint(a.thresh[(int64_t)q * a.thresh_stride]), (uint32_t)it,
+                          RAW ? __float_as_uint(a.qnorm[q]) : 0u);
+    });
+    __syncthreads();
+    queue.request();
+
+    constexpr int kAhead = KB < 3 ? KB : 3;
     for (; blk < nblk; blk += WAVES) {
         // float16 norms of the lane's 16 result rows per tile: four runs of four consecutive vectors
         uint32_t cg[S][8];
-        const uint16_t* gb = a.store.gamma + t.base_slot + blk * 64 + 4 * half;
+        const uint16_t* gb = a.store.gamma + t.base_slot + v_lo + blk * VB + 4 * half;
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
@@ -346,17 +387,14 @@ void k_batch_threshold(BatchScanArgs a) {
                 ah[s][kb] = __builtin_bit_cast(half8, make_uint4(hv[0], hv[1], hv[2], hv[3]));
             }
         // the next block's words, whose registers are free now, travel while this one is multiplied
-        if (blk + WAVES < nblk) {
-#pragma unroll
-            for (int s = 0; s < S; ++s) fetch_words<KB, B, NW>(codes + (int64_t)(blk + WAVES) * words * 64 + 32 * s, words, half, cw[s]);
-        }
-        if (blk * 64 + 64 > n_l) {
+        if (blk + WAVES < nblk) fetch(blk + WAVES);
+        if (v_lo + blk * VB + VB > v_hi) {
 #pragma unroll
             for (int s = 0; s < S; ++s)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int v = blk * 64 + 32 * s + 8 * (r / 4) + 4 * half + (r % 4);
-                    if (v >= n_l) cg[s][r / 2] = (r & 1) ? ((cg[s][r / 2] & 0xFFFFu) | 0x7E000000u) : ((cg[s][r / 2] & 0xFFFF0000u) | 0x7E00u);
+                    const int v = v_lo + blk * VB + 32 * s + 8 * (r / 4) + 4 * half + (r % 4);
+                    if (v >= v_hi) cg[s][r / 2] = (r & 1) ? ((cg[s][r / 2] & 0xFFFFu) | 0x7E000000u) : ((cg[s][r / 2] & 0xFFFF0000u) | 0x7E00u);
                 }
         }
         // the largest norm among this lane's rows (packed float16 maxima, which skip the NaNs), for a raw metric
@@ -374,37 +412,37 @@ void k_batch_threshold(BatchScanArgs a) {
             if (RAW) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int v = blk * 64 + 32 * s + 8 * (r / 4) + 4 * half + (r % 4);
-                    const float xn = a.store.xnorm[t.base_slot + (v < n_l ? v : n_l - 1)];
+                    const int v = v_lo + blk * VB + 32 * s + 8 * (r / 4) + 4 * half + (r % 4);
+                    const float xn = a.store.xnorm[t.base_slot + (v < v_hi ? v : v_hi - 1)];
                     x_min[s] = fminf(x_min[s], xn);
                     x_max[s] = fmaxf(x_max[s], xn);
                 }
             }
         }
         // No row of a tile can reach the threshold unless the largest accumulator times the largest norm
-        // does: g_max >= g_r >= 0 and a_max >= max(acc_r, 0), and a correctly rounded fused multiply-add
-        // never decreases when its exact value grows, so fmaf(g_max, a_max, sq) >= fmaf(g_r, acc_r, sq).
+        // does: g_max >= g_r >= 0 and a_max >= max(acc_r, 0), and a correctly rounded sum or fused multiply-add never
+        // decreases when its exact value grows, so fmaf(g_max, a_max + acc0, sq) >= fmaf(g_r, acc_r + acc0, sq).
         auto take = [&](const floatx16& acc, int s, int qt) {
             const uint4 row = s_row[qt * 32 + jl];
             const float sq = __uint_as_float(row.x), th = __uint_as_float(row.y);
             float a_max = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; r += 2) a_max = fmaxf(fmaxf(a_max, acc[r]), acc[r + 1]);
-            float top = fmaf(g_max[s], a_max, sq);
+            float top = fmaf(g_max[s], a_max + a.acc0, sq);
             if (RAW) top = metric_key_bound(a.metric, top, x_min[s], x_max[s], __uint_as_float(row.w));
             if (top >= th) {                       // seldom: some row of this lane may reach the threshold
                 // (the first row's number is hidden from the compiler, which would otherwise prepare every row's
                 // addresses ahead of the tiles and spill them)
-                int v0 = blk * 64 + 32 * s + 4 * half;
+                int v0 = v_lo + blk * VB + 32 * s + 4 * half;
                 asm volatile("" : "+v"(v0));
                 auto key_of = [&](int r) -> float {
                     uint32_t two = cg[s][r / 2];
                     asm volatile("" : "+v"(two));   // likewise converted where it is read
                     const float g = kUnscale * __half2float(__ushort_as_half((uint16_t)((r & 1) ? (two >> 16) : (two & 0xFFFFu))));
-                    float u = fmaf(g, acc[r], sq);  // upper bound of the score; NaN never passes
+                    float u = fmaf(g, acc[r] + a.acc0, sq);  // upper bound of the score; NaN never passes
                     if (RAW) {
                         const int v = v0 + 8 * (r / 4) + (r % 4);
-                        u = metric_key(a.metric, u, a.store.xnorm[t.base_slot + (v < n_l ? v : n_l - 1)], __uint_as_float(row.w));
+                        u = metric_key(a.metric, u, a.store.xnorm[t.base_slot + (v < v_hi ? v : v_hi - 1)], __uint_as_float(row.w));
                     }
                     return u;
                 };
@@ -439,50 +477,72 @@ void k_batch_threshold(BatchScanArgs a) {
             const uint16_t* b0 = bh_base + qt * 32 * Cfg::LDH;
             floatx16 acc[S];
 #pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[s][r] = 0.f;
+#pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 const half8 h = *reinterpret_cast<const half8*>(b0 + 16 * kb);
 #pragma unroll
-                for (int s = 0; s < S; ++s) acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[s][kb], h, kb ? acc[s] : acc_init, 0, 0, 0);
+                for (int s = 0; s < S; ++s) acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[s][kb], h, acc[s], 0, 0, 0);
+            }
+            // the panel reads run kAhead blocks ahead of the products (the compiler's own order, each read right before
+            // its products, leaves the LDS latency exposed once per block)
+            __builtin_amdgcn_sched_group_barrier(0x100, kAhead + 1, 0);
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                __builtin_amdgcn_sched_group_barrier(0x008, S, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
 #pragma unroll
             for (int s = 0; s < S; ++s) take(acc[s], s, qt);
         }
     }
+    }
 }
 
 template <int DP, int B>
-hipError_t run_batch(const BatchScanArgs& a, int max_tiles, hipStream_t st) {
-    static LdsLimit lim;
+hipError_t run_batch(const BatchScanArgs& a, hipStream_t st) {
+    static ChipFill fill;
     if (a.dense) {
-        constexpr int NQ = batch_tile_near(DP) / 32;
+        constexpr int NQ = kBatchTileNear / 32;
         constexpr size_t lds = BatchCfg<DP, B, NQ>::lds_dense;
-        const hipError_t e = lim.ensure(reinterpret_cast<const void*>(k_batch_dense<DP, B, NQ, 8, 2>), lds);
+        constexpr auto dense = k_batch_dense<DP, B, NQ, 4, 2>;
+        unsigned wgs = 0;
+        const hipError_t e = fill.get(reinterpret_cast<const void*>(dense), 256, lds, &wgs);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_batch_dense<DP, B, NQ, 8, 2>), dim3((unsigned)max_tiles), dim3(512), lds, st, a);
+        hipLaunchKernelGGL(dense, dim3(wgs), dim3(256), lds, st, a);
     } else {
-        static LdsLimit lim_t[2];
-        constexpr int NQ = kBatchTile / 32, OCC = DP <= 96 && B <= 4 ? 3 : 2;       // wavefronts per SIMD that the registers allow
+        static ChipFill fill_t[2];
+        constexpr int NQ = kBatchTile / 32;
         constexpr size_t lds = BatchCfg<DP, B, NQ>::lds_threshold;
-        const hipError_t e = a.metric ? lim_t[1].ensure(reinterpret_cast<const void*>(k_batch_threshold<DP, B, NQ, 4, 2, true>), lds)
-                                      : lim_t[0].ensure(reinterpret_cast<const void*>(k_batch_threshold<DP, B, NQ, 4, OCC, false>), lds);
+        // two row tiles and wavefronts per SIMD where the registers (operands of both tiles, and the words of the
+        // next block, twice or four times as many where codes straddle words or are bytes) allow it without spills
+        constexpr int words = B == 8 ? DP / 4 : (B == 3 || B == 5) ? DP / 8 : DP / 16;
+        constexpr int S = DP + 2 * words <= 256 ? 2 : 1, S_RAW = DP + 2 * words < 200 ? 2 : 1;
+        constexpr int OCC = S == 2 && DP + words <= 102 ? 3 : 2;
+        constexpr auto plain = k_batch_threshold<DP, B, NQ, 4, OCC, S, false>;
+        constexpr auto raw = k_batch_threshold<DP, B, NQ, 4, 2, S_RAW, true>;
+        unsigned wgs = 0;
+        const hipError_t e = a.metric ? fill_t[1].get(reinterpret_cast<const void*>(raw), 256, lds, &wgs) : fill_t[0].get(reinterpret_cast<const void*>(plain), 256, lds, &wgs);
         if (e != hipSuccess) return e;
-        if (a.metric) hipLaunchKernelGGL((k_batch_threshold<DP, B, NQ, 4, 2, true>), dim3((unsigned)max_tiles), dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((k_batch_threshold<DP, B, NQ, 4, OCC, false>), dim3((unsigned)max_tiles), dim3(256), lds, st, a);
+        if (a.metric) hipLaunchKernelGGL(raw, dim3(wgs), dim3(256), lds, st, a);
+        else hipLaunchKernelGGL(plain, dim3(wgs), dim3(256), lds, st, a);
     }
     return hipGetLastError();
 }
 
 template <int B>
-hipError_t run_batch_width(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st) {
+hipError_t run_batch_width(const BatchScanArgs& a, int dp, hipStream_t st) {
     switch (dp) {
-        case 64: return run_batch<64, B>(a, max_tiles, st);
-        case 96: return run_batch<96, B>(a, max_tiles, st);
-        case 128: return run_batch<128, B>(a, max_tiles, st);
-        case 160: return run_batch<160, B>(a, max_tiles, st);
-        case 192: return run_batch<192, B>(a, max_tiles, st);
-        case 208: return run_batch<208, B>(a, max_tiles, st);
-        case 224: return run_batch<224, B>(a, max_tiles, st);
-        case 256: return run_batch<256, B>(a, max_tiles, st);
+        case 64: return run_batch<64, B>(a, st);
+        case 96: return run_batch<96, B>(a, st);
+        case 128: return run_batch<128, B>(a, st);
+        case 160: return run_batch<160, B>(a, st);
+        case 192: return run_batch<192, B>(a, st);
+        case 208: return run_batch<208, B>(a, st);
+        case 224: return run_batch<224, B>(a, st);
+        case 256: return run_batch<256, B>(a, st);
         default: return hipErrorInvalidValue;
     }
 }

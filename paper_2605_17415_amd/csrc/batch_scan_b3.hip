@@ -3,6 +3,6 @@
 
 namespace ivftq {
 
-hipError_t batch_scan_b3(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st) { return run_batch_width<3>(a, dp, max_tiles, st); }
+hipError_t batch_scan_b3(const BatchScanArgs& a, int dp, hipStream_t st) { return run_batch_width<3>(a, dp, st); }
 
 }  // namespace ivftq

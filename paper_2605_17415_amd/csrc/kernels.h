@@ -45,6 +45,34 @@ class LdsLimit {
     std::atomic<size_t> set_[kDevices] = {};
 };
 
+// Workgroups of a kernel that fill the current device (its compute units times what one of them holds), for
+// launches whose workgroups take their work from a queue; raises the dynamic-LDS limit as well.  Looked up once per
+// (kernel, device) pair like LdsLimit.
+class ChipFill {
+  public:
+    hipError_t get(const void* kernel, int threads, size_t lds, unsigned* wgs) {
+        int dev = 0, held = 0, units = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= kDevices) return hipErrorInvalidDevice;
+        *wgs = wgs_[dev].load(std::memory_order_acquire);
+        if (*wgs) return hipSuccess;
+        e = limit_.ensure(kernel, lds);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&held, kernel, threads, lds);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        if (held < 1 || units < 1) return hipErrorLaunchOutOfResources;
+        *wgs = (unsigned)(held * units);
+        wgs_[dev].store(*wgs, std::memory_order_release);
+        return hipSuccess;
+    }
+
+  private:
+    static constexpr int kDevices = 64;
+    LdsLimit limit_;
+    std::atomic<unsigned> wgs_[kDevices] = {};
+};
+
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 inline int64_t round_up64(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
@@ -303,44 +331,49 @@ hipError_t launch_cascade_rescore(const CascadeArgs& a, int64_t nq, hipStream_t 
 
 // Whether the batched scan covers this (d, b); otherwise the streaming scan is used.
 bool batch_covers(int d, int b);
-// Queries per workgroup tile: kBatchTile in the threshold pass; in the dense pass, whose panel holds both parts of
-// the queries and whose lists have few of them, as many where two workgroups still share a compute unit's LDS
-// (128 coordinates), half of that beyond (10M x 200, 11 queries a list: one workgroup of 111 KB per unit before).
-constexpr int kBatchTile = 128;
-constexpr int batch_tile_near(int dp) { return dp <= 128 ? kBatchTile : kBatchTile / 2; }
-int batch_near_queries(int d);
+// Queries per workgroup tile of the threshold pass, and of the dense pass, whose panel holds both parts of the queries
+// and whose lists have few of them (3 at 10M x 96, 11 at 10M x 200): with 64 the panel leaves room for as many
+// workgroups in a compute unit's LDS as its registers allow.
+constexpr int kBatchTile = 128, kBatchTileNear = 64;
+// Lists are cut into parts of about part_len vectors (a multiple of 64), each a tile of its own.
+struct TileShape { int tq_near, tq, part_near, part; };
+__host__ __device__ __forceinline__ int list_parts(int size, int part_len) { return size > part_len ? (size + part_len - 1) / part_len : 1; }
 
-// Buckets the (query, probe) pairs: bucket l holds the pairs (q, p < first[q]) of list l, bucket
-// L + l the pairs (q, p >= first[q]).  pairs[pair_off[b] ...] holds the flat pair numbers q*np + p
-// of bucket b; tile_off[b] counts workgroup tiles of tq_near (b < L) or tq queries (both arrays have 2L+1 entries),
-// tile_bucket[t] = the bucket of tile t.  count (cleared by launch_cand_offsets) and cursor are scratch arrays of
-// round_up(2L, 4) entries, 16-byte aligned.
-hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int64_t nq, int np, int L, int tq_near, int tq,
-                                uint32_t* count, uint32_t* cursor, int64_t* pair_off, int32_t* tile_off,
-                                int32_t* tile_bucket, int32_t* pairs, hipStream_t st);
+// The (query, probe) pairs bucketed by list: bucket l holds the pairs (q, p < first[q]) of list l (the dense pass),
+// bucket L + l the pairs (q, p >= first[q]) (the threshold pass).  pairs[pair_off[b] ...] holds the count[b] flat pair
+// numbers q*np + p of bucket b.  Its workgroup tiles, every tq_near or tq of its queries times the list_parts of its
+// list, are tile_off[b] ... of its pass's array (tile_near or tile_late), whose entries name the bucket.
+struct PairTable {
+    // cleared by launch_cand_offsets: [2L] pairs of a bucket, then 8 words totals (pairs, tiles of the dense pass, of
+    // the threshold pass, next tile of either pass)
+    uint32_t* count; int32_t* totals;
+    uint32_t* cursor; int32_t* pair_off; int32_t* tile_off;      // [2L] each; cursor is scratch
+    int32_t* tile_near; int32_t* tile_late; int32_t* pairs;
+};
+hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int64_t nq, int np, int L, const int32_t* list_size,
+                                const TileShape& shape, const PairTable& p, hipStream_t st);
 
 struct BatchScanArgs {
     const uint16_t* zh; const uint16_t* zl; int z_pitch;   // split rotated queries, [nq][z_pitch] halves
     const float* cb;
-    const int32_t* pairs; const int64_t* pair_off; const int32_t* tile_off; const int32_t* tile_bucket;
+    PairTable p; int part_len;           // part_len of this pass, as the tiles were made
     const float* coarse;                 // [nq*np] coarse term of each (query, probe)
     const float* thresh; int thresh_stride;   // threshold of query q at thresh[q*thresh_stride]
     ListStore store; int np; int L;
-    int bucket_lo, bucket_hi;            // buckets this launch covers
     // threshold mode: cand_score = upper bound of the score (see acc0), cand_slot = slot | probe rank << kCandProbeShift
     float* cand_score; int64_t* cand_slot; int32_t* cand_cnt; int cap;
-    float acc0;                          // 2^20 * kappa: start value of the threshold pass's accumulators
+    float acc0;                          // 2^20 * kappa, added to the threshold pass's accumulators
     // dense mode (the nearest lists): every score goes to scores[q*m_stride + cand_off[q][p] + v]
     int dense; float* scores; int64_t m_stride; const int32_t* cand_off;
     int metric; const float* qnorm;      // scores are ranking keys of a raw metric (metric_key)
 };
-hipError_t launch_batch_scan(const BatchScanArgs& a, int d, int b, int max_tiles, hipStream_t st);
+hipError_t launch_batch_scan(const BatchScanArgs& a, int d, int b, hipStream_t st);
 // one bit count each, dp = panel width
-hipError_t batch_scan_b2(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
-hipError_t batch_scan_b3(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
-hipError_t batch_scan_b4(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
-hipError_t batch_scan_b5(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
-hipError_t batch_scan_b8(const BatchScanArgs& a, int dp, int max_tiles, hipStream_t st);
+hipError_t batch_scan_b2(const BatchScanArgs& a, int dp, hipStream_t st);
+hipError_t batch_scan_b3(const BatchScanArgs& a, int dp, hipStream_t st);
+hipError_t batch_scan_b4(const BatchScanArgs& a, int dp, hipStream_t st);
+hipError_t batch_scan_b5(const BatchScanArgs& a, int dp, hipStream_t st);
+hipError_t batch_scan_b8(const BatchScanArgs& a, int dp, hipStream_t st);
 
 constexpr int kCandProbeShift = 48;      // a candidate's probe rank sits above its slot number (slots < 2^48, ranks < 2^12)
 
