@@ -225,18 +225,19 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
         const float x = (v - base) * scale;
         return v < base ? -1 : x < 255.f ? (int)x : 255;
     };
+    auto count_bin = [&](float lo) {             // (the lower bound of an infinite norm is no number and counts for nothing)
+        if (lo >= base) atomicAdd(&hist[bin_of(lo)], 1u);
+    };
     if (binned) {
 #pragma unroll
         for (int h = 0; h < kHeld; ++h) {
             if (tid + 256 * h >= total) break;
-            const int b = bin_of(held[h]);
-            if (b >= 0) atomicAdd(&hist[b], 1u);
+            count_bin(held[h]);
         }
         for (int i = tid + 256 * kHeld; i < total; i += 256) {
             float lo;
             (void)bounds(i, lo);
-            const int b = bin_of(lo);
-            if (b >= 0) atomicAdd(&hist[b], 1u);
+            count_bin(lo);
         }
     }
     __syncthreads();

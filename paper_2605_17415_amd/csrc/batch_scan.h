@@ -345,7 +345,8 @@ void k_batch_threshold(BatchScanArgs a) {
     };
     if (blk < nblk) fetch(blk);
 
-    stage_queries<DP, Cfg::TQ, NT, false>(a, t, zh, nullptr, s_row, make_uint4(0, 0x7F800000u, 0, 0), [&](int32_t it) {
+    // (columns beyond the tile's queries: a NaN threshold, which not even an infinite score reaches)
+    stage_queries<DP, Cfg::TQ, NT, false>(a, t, zh, nullptr, s_row, make_uint4(0, 0x7FC00000u, 0, 0), [&](int32_t it) {
         const int32_t q = it / a.np;
         return make_uint4(__float_as_uint(a.coarse[it]), __float_as_uint(a.thresh[(int64_t)q * a.thresh_stride]), (uint32_t)it,
                           RAW ? __float_as_uint(a.qnorm[q]) : 0u);

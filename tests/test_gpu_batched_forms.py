@@ -1,0 +1,95 @@
+"""The batched list scan (search mode 2) over the forms it takes: every bit count it has, dimensions that end inside and at
+the end of a block of 16, cosine and raw metrics, lists that are empty, shorter than one tile of vectors, at its edges, and
+long enough to be cut into several parts (part lengths are multiples of 64 and at least 512 vectors).  Against the
+streaming scan (mode 1) of the same index, which sums float32 products in another order.
+
+Tolerance: a score is coarse + gamma * (d products, both split float16 operands), its two evaluations apart by at most
+gamma |z| |C| (2 * 2^-21 + d 2^-24) <= 1e-4 for gamma <= 1.2, |z| = 1, |C| <= 2 and d <= 256; a raw metric scales that by |q||x|
+(twice that for a distance).  Labels may differ only where the values are that close to the k-th."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+SIZES = [0, 1, 31, 64, 65, 0, 127, 511, 512, 513, 577, 1025, 2500, 64 * 33, 900, 3]
+FORMS = [(32, 4, "cosine", 1), (50, 2, "l2", 10), (64, 3, "ip", 33), (96, 4, "l2", 10), (100, 5, "cosine", 100), (128, 8, "cosine", 10),
+         (129, 4, "ip", 7), (161, 5, "l2", 20), (200, 3, "cosine", 64), (208, 8, "ip", 10), (224, 2, "cosine", 100), (255, 8, "l2", 65), (256, 5, "ip", 20)]
+
+
+def _index(d, b, metric, rng):
+    import paper_2605_17415_amd as pkg
+    L, n = len(SIZES), sum(SIZES)
+    cell = rng.permutation(np.repeat(np.arange(L), SIZES)).astype(np.int32)
+    cent = rng.standard_normal((L, d)).astype(np.float32)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    ix = pkg.Index(d, b, L, rotation_seed=d)
+    ix.set_coarse(cent)
+    on = [torch.from_numpy(v).to("cuda:0") for v in (cell, rng.integers(0, 1 << b, (n, d)).astype(np.uint8), rng.uniform(0.2, 1.2, n).astype(np.float16))]
+    length = rng.uniform(0.5, 2.0, n).astype(np.float32)
+    if metric == "cosine":
+        ix.add_encoded(*on)
+    else:
+        ix.set_metric(pkg.binding.METRIC_IP if metric == "ip" else pkg.binding.METRIC_L2)
+        ix.add_encoded_raw(*on, torch.from_numpy(length).to("cuda:0"))
+    return ix
+
+
+@pytest.mark.parametrize("d,b,metric,k", FORMS)
+def test_batched_equals_streaming(d, b, metric, k):
+    print(f"[batched forms] d={d} b={b} {metric} k={k}", flush=True)
+    rng = np.random.default_rng(1000 * d + b)
+    ix = _index(d, b, metric, rng)
+    scale = 1.0 if metric == "cosine" else 2.0 * 2.0 if metric == "ip" else 2.0 * 2.0 * 2.0
+    for nq in (1, 33, 300):                          # 300: some list meets more than one tile of 128 queries
+        q = rng.standard_normal((nq, d)).astype(np.float32)
+        q /= np.linalg.norm(q, axis=1, keepdims=True)
+        q *= rng.uniform(0.5, 2.0, (nq, 1)).astype(np.float32)
+        qd = torch.from_numpy(q).to("cuda:0")
+        got = []
+        for mode in (1, 2):
+            ix.set_search_mode(mode)
+            s, i = ix.search(qd, 9, k)
+            torch.cuda.synchronize()
+            got.append((s.cpu().numpy(), i.cpu().numpy()))
+        (s1, i1), (s2, i2) = got
+        real = i1 >= 0
+        np.testing.assert_array_equal(real, i2 >= 0)
+        np.testing.assert_array_equal(s1[~real], s2[~real])
+        tol = 1e-4 * scale + 1e-6
+        assert np.all(np.abs(s1[real] - s2[real]) <= tol)
+        for a, c, sa in zip(i1, i2, s1):             # a label that only one side has sits at the k-th value
+            odd = np.isin(a, c, invert=True) & (a >= 0)
+            last = sa[a >= 0][-1] if (a >= 0).any() else 0.0
+            assert np.all(np.abs(sa[odd] - last) <= 2 * tol)
+    ix.close()
+
+
+def test_infinite_norm_in_a_partial_query_tile():
+    """A stored norm of +inf (only a caller's own codes can hold one) is best for every query whose sum is positive; queries
+    beyond a tile's last one get nothing appended, and the finite results of the streaming scan come back."""
+    import paper_2605_17415_amd as pkg
+    rng = np.random.default_rng(3)
+    d, L, n = 64, 4, 4000
+    cent = rng.standard_normal((L, d)).astype(np.float32)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    gamma = rng.uniform(0.2, 1.2, n).astype(np.float16)
+    gamma[rng.integers(0, n, 5)] = np.inf
+    ix = pkg.Index(d, 4, L, rotation_seed=1)
+    ix.set_coarse(cent)
+    ix.add_encoded(*[torch.from_numpy(v).to("cuda:0") for v in (rng.integers(0, L, n).astype(np.int32), rng.integers(0, 16, (n, d)).astype(np.uint8), gamma)])
+    q = torch.from_numpy(rng.standard_normal((5, d)).astype(np.float32)).to("cuda:0")
+    got = []
+    for mode in (1, 2):
+        ix.set_search_mode(mode)
+        s, i = ix.search(q, L, 20)
+        torch.cuda.synchronize()
+        got.append((s.cpu().numpy(), i.cpu().numpy()))
+    (s1, i1), (s2, i2) = got
+    for a, c in zip(i1, i2):
+        assert len(set(c.tolist())) == 20
+        assert len(set(a.tolist()) ^ set(c.tolist())) <= 2       # (a tie at the last place)
+    fin = np.isfinite(s1) & np.isfinite(s2)
+    np.testing.assert_array_equal(np.isposinf(s1), np.isposinf(s2))
+    np.testing.assert_allclose(s2[fin], s1[fin], rtol=0, atol=1e-4)
+    ix.close()
