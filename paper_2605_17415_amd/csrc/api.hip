@@ -98,11 +98,11 @@ struct PinnedBuf {
 
 // kernel classes for the optional per-launch timing
 enum ProfId { P_ASSIGN, P_COARSE_SCORES, P_ENCODE, P_ROTATE_Q, P_SEG_HIST, P_SEG_SCAN, P_RANK, P_PACK,
-              P_COPY_LISTS, P_SELECT_PROBE, P_CAND_OFF, P_LIST_SCAN, P_SELECT_TOPK, P_KMEANS_UPDATE, P_KMEANS_SUMS,
+              P_COPY_LISTS, P_SELECT_PROBE, P_LIST_SCAN, P_SELECT_TOPK, P_KMEANS_UPDATE, P_KMEANS_SUMS,
               P_PAIR_GROUP, P_BATCH_FIRST, P_BATCH_SCAN, P_MERGE, P_CASCADE, P_COUNT };
 const char* const kProfNames[P_COUNT] = {"coarse_assign", "coarse_scores", "encode_rotate_quantise_pack",
                                          "rotate_queries", "segment_hist", "segment_scan", "stable_rank",
-                                         "pack_scatter", "copy_lists", "select_probes", "cand_offsets",
+                                         "pack_scatter", "copy_lists", "select_probes",
                                          "list_scan", "select_topk", "kmeans_update", "kmeans_cell_sums", "pair_grouping",
                                          "batch_scan_nearest", "batch_scan", "merge_topk", "cascade_rescore"};
 struct ProfRec { int id; hipEvent_t a, b; };
@@ -1282,15 +1282,16 @@ ivftq_status check_query_args(const ivftq_index* ix, const float* q_dev, int64_t
     return IVFTQ_OK;
 }
 
-// coarse scores for `count` queries starting at q, then the nprobe best cells of each
+// coarse scores for `count` queries starting at q, then the nprobe best cells of each and, with `cand`, what follows from them
 ivftq_status coarse_and_probe(ivftq_index* ix, const float* q, int64_t count, int nprobe, int32_t* probe,
-                              float* coarse, hipStream_t st) {
+                              float* coarse, const CandOffsetArgs* cand, hipStream_t st) {
     const int64_t ldS = round_up(ix->nlist, 4);
     HIP_TRY(timed(ix, st, P_COARSE_SCORES, [&] { return launch_coarse(q, count, ix->d, ix->cent_h.as<uint16_t>(), ix->cent_l.as<uint16_t>(), ix->dp,
                                                                            ix->lpad, ix->w_S.as<float>(), ldS, st); }));
     SelectArgs sa{};
     sa.vals = ix->w_S.as<float>(); sa.stride = ldS; sa.rows = count; sa.k = nprobe; sa.m_fixed = ix->nlist;
     sa.out_vals = coarse; sa.out_i32 = probe;
+    if (cand) sa.cand = *cand;
     HIP_TRY(timed(ix, st, P_SELECT_PROBE, [&] { return launch_select(0, sa, st); }));
     return IVFTQ_OK;
 }
@@ -1322,7 +1323,7 @@ ivftq_status ivftq_coarse_probe(ivftq_index* ix, const float* q_dev, int64_t nq,
     for (int64_t q0 = 0; q0 < nq; q0 += qc) {
         const int64_t cnt = std::min(qc, nq - q0);
         s = coarse_and_probe(ix, q_dev + q0 * ix->d, cnt, nprobe, probe_dev ? probe_dev + q0 * nprobe : nullptr,
-                             coarse_dev ? coarse_dev + q0 * nprobe : nullptr, st);
+                             coarse_dev ? coarse_dev + q0 * nprobe : nullptr, nullptr, st);
         if (s != IVFTQ_OK) return s;
     }
     return IVFTQ_OK;
@@ -1358,7 +1359,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     // exact selection.  Batched: pairs regrouped by list and scanned on the matrix cores against a
     // threshold from each query's nearest lists.  The streaming scan's time follows the bytes it reads, once
     // per query; the batched path reads a list once per 128 queries, so its time follows the part of the
-    // index the call touches, but it is a chain of about fourteen kernels with a fixed cost of its own.
+    // index the call touches, but it is a chain of about twelve kernels with a fixed cost of its own.
     // Batched when the streamed bytes exceed kBatchedGain times the touched bytes plus kBatchedFixedBytes
     // (measured crossovers with nprobe 32 / 32 / 64 at 1M x 128, 10M x 96, 10M x 200: about 200, 380 and
     // 170 queries, i.e. 0.41 / 1.5 / 2.7 GB streamed against an index of 0.066 / 0.58 / 1.04 GB).  Mode 2
@@ -1444,7 +1445,15 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     for (int64_t q0 = 0; q0 < nq; q0 += qc) {
         const int64_t cnt = std::min(qc, nq - q0);
         const float* q = q_dev + q0 * ix->d;
-        s = coarse_and_probe(ix, q, cnt, nprobe, ix->w_probe.as<int32_t>(), ix->w_coarse.as<float>(), st);
+        CandOffsetArgs co{};
+        co.list_size = ix->d_size.as<int32_t>(); co.cand_off = ix->w_candoff.as<int32_t>(); co.k = k; co.cap = cap;
+        int32_t* first = batched ? ix->w_first.as<int32_t>() : nullptr;
+        int32_t* redo_cnt = batched ? ix->w_gate.as<int32_t>() + 1 + qc : nullptr;
+        if (batched) {
+            co.first = first; co.cand_cnt = ix->w_ccnt.as<int32_t>(); co.gate = ix->w_gate.as<int32_t>(); co.redo_cnt = redo_cnt;
+            co.bucket_cnt = ix->w_count.as<uint32_t>(); co.buckets = buckets + 8;
+        }
+        s = coarse_and_probe(ix, q, cnt, nprobe, ix->w_probe.as<int32_t>(), ix->w_coarse.as<float>(), &co, st);
         if (s != IVFTQ_OK) return s;
         EncodeArgs ea{};
         ea.x = q; ea.n = cnt; ea.d = ix->d; ea.b = ix->b;
@@ -1452,13 +1461,6 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         if (batched) { ea.zh_out = ix->w_zh.as<uint16_t>(); ea.zl_out = ix->w_zl.as<uint16_t>(); }
         if (metric) ea.norm_out = ix->w_qnorm.as<float>();
         HIP_TRY(timed(ix, st, P_ROTATE_Q, [&] { return launch_encode(2, ea, st); }));
-        int32_t* first = batched ? ix->w_first.as<int32_t>() : nullptr;
-        int32_t* redo_cnt = batched ? ix->w_gate.as<int32_t>() + 1 + qc : nullptr;
-        HIP_TRY(timed(ix, st, P_CAND_OFF, [&] {
-            return launch_cand_offsets(ix->w_probe.as<int32_t>(), cnt, nprobe, ix->d_size.as<int32_t>(),
-                                       ix->w_candoff.as<int32_t>(), k, cap, first,
-                                       batched ? ix->w_ccnt.as<int32_t>() : nullptr, batched ? ix->w_gate.as<int32_t>() : nullptr,
-                                       redo_cnt, batched ? ix->w_count.as<uint32_t>() : nullptr, buckets + 8, st); }));
         ListScanArgs la{};
         la.z = ix->w_z.as<float>(); la.z_pitch = ix->dp; la.d = ix->d; la.cb = cb;
         la.probe = ix->w_probe.as<int32_t>(); la.coarse = ix->w_coarse.as<float>();
@@ -1642,7 +1644,7 @@ ivftq_status ivftq_search_cascade(ivftq_index* ix, const float* q_dev, int64_t n
     for (int64_t q0 = 0; q0 < nq; q0 += qc) {
         const int64_t cnt = std::min(qc, nq - q0);
         s = coarse_and_probe(ix, q_dev + q0 * ix->d, cnt, nprobe, ix->w_probe.as<int32_t>() + q0 * nprobe,
-                             ix->w_coarse.as<float>() + q0 * nprobe, st);
+                             ix->w_coarse.as<float>() + q0 * nprobe, nullptr, st);
         if (s != IVFTQ_OK) return s;
     }
     EncodeArgs ea{};

@@ -235,9 +235,12 @@ hipError_t launch_inertia(const double* gain, int L, int64_t n, double* out, hip
 // max(k, 2*k*T/cap) vectors, T the query's candidate total; np if there is none.  With `first`, cand_cnt[q],
 // gate[0], redo_cnt[q] and bucket_cnt[0 .. buckets) (each may be null) are set to zero: the counters the batched
 // scan, its merge, the exact redo and the pair grouping add to.
-hipError_t launch_cand_offsets(const int32_t* probe, int64_t nq, int np, const int32_t* list_size,
-                               int32_t* cand_off, int k, int cap, int32_t* first, int32_t* cand_cnt, int32_t* gate,
-                               int32_t* redo_cnt, uint32_t* bucket_cnt, int buckets, hipStream_t st);
+struct CandOffsetArgs {
+    const int32_t* list_size; int32_t* cand_off;
+    int k; int cap; int32_t* first;
+    int32_t* cand_cnt; int32_t* gate; int32_t* redo_cnt;
+    uint32_t* bucket_cnt; int buckets;
+};
 // scores[q*m_stride + cand_off[q][p] + i] = coarse[q][p] + gamma_i * sum_j z_qj * C[code_ij]
 struct ListScanArgs {
     const float* z; int z_pitch; int d;
@@ -301,6 +304,8 @@ struct SelectArgs {
     // stretch of probe p in score row q, and writes k (value, label) pairs per row (m_bound = longest list);
     // mode 3 selects among the m_fixed = np * k survivors of a query, whose labels it reads from lab_in.
     const int64_t* lab_in;
+    // mode 0: what follows from the probes just selected (cand.cand_off null: nothing)
+    CandOffsetArgs cand;
 };
 hipError_t launch_select(int mode, const SelectArgs& a, hipStream_t st);
 
@@ -344,7 +349,7 @@ __host__ __device__ __forceinline__ int list_parts(int size, int part_len) { ret
 // numbers q*np + p of bucket b.  Its workgroup tiles, every tq_near or tq of its queries times the list_parts of its
 // list, are tile_off[b] ... of its pass's array (tile_near or tile_late), whose entries name the bucket.
 struct PairTable {
-    // cleared by launch_cand_offsets: [2L] pairs of a bucket, then 8 words totals (pairs, tiles of the dense pass, of
+    // cleared with the candidate offsets: [2L] pairs of a bucket, then 8 words totals (pairs, tiles of the dense pass, of
     // the threshold pass, next tile of either pass)
     uint32_t* count; int32_t* totals;
     uint32_t* cursor; int32_t* pair_off; int32_t* tile_off;      // [2L] each; cursor is scratch

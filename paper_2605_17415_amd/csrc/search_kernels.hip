@@ -13,14 +13,56 @@ namespace {
 
 // ---- candidate offsets -----------------------------------------------------------------------
 
-// Also, when asked: first[q] = the number of leading probes whose lists are scored densely to find
-// the query's threshold (see the kernel), or np when all probed cells together hold too few vectors.
-__global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict__ probe, int64_t nq, int np,
-                                                      const int32_t* __restrict__ list_size, int32_t* __restrict__ cand_off,
-                                                      int k, int cap, int32_t* __restrict__ first,
-                                                      int32_t* __restrict__ cand_cnt, int32_t* __restrict__ gate,
-                                                      int32_t* __restrict__ redo_cnt, uint32_t* __restrict__ bucket_cnt, int buckets) {
-    for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < buckets; i += (int)(gridDim.x * blockDim.x)) bucket_cnt[i] = 0u;
+// inclusive sum of v over the wavefront's lanes
+__device__ __forceinline__ int32_t lanes_up_to(int32_t v, int lane) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t t = __shfl_up(v, o);
+        if (lane >= o) v += t;
+    }
+    return v;
+}
+
+// The pair grouping's counters, cleared by all threads of the launch.
+__device__ __forceinline__ void clear_buckets(const CandOffsetArgs& c) {
+    for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < c.buckets; i += (int)(gridDim.x * blockDim.x)) c.bucket_cnt[i] = 0u;
+}
+
+// How many of a query's `total` candidates are scored densely to find its threshold.  Were the prefix a random
+// sample of P of the query's T candidates, its k-th score would be beaten by about k*(T-P)/P of the others;
+// P = f*k*T/cap (f = kPrefixFactorX2/2) keeps that near cap/f even then.  The nearest lists hold the best
+// candidates, so in practice far fewer pass (and a list that does overflow sends its query to the exact pass).  At
+// least k vectors, so that a threshold exists.
+__device__ __forceinline__ int64_t dense_prefix(const CandOffsetArgs& c, int32_t total) {
+    const int64_t need = (kPrefixFactorX2 * (int64_t)c.k * total + 2 * c.cap - 1) / (2 * c.cap);
+    return need < c.k ? c.k : need;
+}
+
+// one lane: the prefix of query q, and its counters of the batched scan (cleared here rather than by launches of their own)
+__device__ __forceinline__ void put_first(const CandOffsetArgs& c, int64_t q, int p1) {
+    c.first[q] = p1;
+    if (c.cand_cnt) c.cand_cnt[q] = 0;
+    if (c.redo_cnt) c.redo_cnt[q] = 0;
+    if (c.gate && q == 0) c.gate[0] = 0;
+}
+
+// The same for the probes of a query held by the lanes of a wavefront (np <= 64; `list` is ignored beyond np).
+__device__ __forceinline__ void cand_offsets_lanes(const CandOffsetArgs& c, int64_t q, int np, int list, int lane) {
+    const int32_t size = lane < np && list >= 0 ? c.list_size[list] : 0;
+    const int32_t incl = lanes_up_to(size, lane);
+    const int32_t total = __shfl(incl, 63);
+    int32_t* off = c.cand_off + q * (np + 1);
+    if (lane < np) off[lane] = incl - size;
+    if (lane == 0) off[np] = total;
+    if (!c.first) return;
+    const uint64_t reached = __ballot(lane < np && (int64_t)incl >= dense_prefix(c, total));
+    if (lane == 0) put_first(c, q, reached ? (int)__builtin_ctzll(reached) + 1 : np);
+}
+
+// For probe selections that do not end with the probes in one wavefront's lanes (more than 64 probes, or more cells
+// than the one-wavefront selection takes).
+__global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict__ probe, int64_t nq, int np, CandOffsetArgs c) {
+    clear_buckets(c);
     // one wavefront per query: 64 probes at a time, running sum over the lanes
     const int lane = threadIdx.x & 63;
     const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -28,47 +70,26 @@ __global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict_
     int32_t run = 0;
     for (int p0 = 0; p0 < np; p0 += 64) {
         const int p = p0 + lane;
-        const int32_t size = p < np ? list_size[probe[q * np + p]] : 0;
-        int32_t incl = size;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int32_t t = __shfl_up(incl, o);
-            if (lane >= o) incl += t;
-        }
-        if (p < np) cand_off[q * (np + 1) + p] = run + incl - size;
+        const int32_t size = p < np && probe[q * np + p] >= 0 ? c.list_size[probe[q * np + p]] : 0;
+        const int32_t incl = lanes_up_to(size, lane);
+        if (p < np) c.cand_off[q * (np + 1) + p] = run + incl - size;
         run += __shfl(incl, 63);
     }
-    if (lane == 0) cand_off[q * (np + 1) + np] = run;
-    if (!first) return;
-    // Were the prefix a random sample of P of the query's T candidates, its k-th score would be beaten by
-    // about k*(T-P)/P of the others; P = f*k*T/cap (f = kPrefixFactorX2/2) keeps that near cap/f even then.
-    // The nearest lists hold the best candidates, so in practice far fewer pass (and a list that does
-    // overflow sends its query to the exact pass).  At least k vectors, so that a threshold exists.
-    int64_t need = (kPrefixFactorX2 * (int64_t)k * run + 2 * cap - 1) / (2 * cap);
-    if (need < k) need = k;
+    if (lane == 0) c.cand_off[q * (np + 1) + np] = run;
+    if (!c.first) return;
     // the first p >= 1 whose lists 0 .. p-1 together reach `need` (np when none does)
+    const int64_t need = dense_prefix(c, run);
     int p1 = np;
     int32_t run2 = 0;
     for (int p0 = 0; p0 < np && p1 == np; p0 += 64) {
         const int p = p0 + lane;
-        const int32_t size = p < np ? list_size[probe[q * np + p]] : 0;
-        int32_t incl = size;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int32_t t = __shfl_up(incl, o);
-            if (lane >= o) incl += t;
-        }
+        const int32_t size = p < np && probe[q * np + p] >= 0 ? c.list_size[probe[q * np + p]] : 0;
+        const int32_t incl = lanes_up_to(size, lane);
         const uint64_t reached = __ballot(p < np && (int64_t)(run2 + incl) >= need);
         if (reached) p1 = p0 + (int)__builtin_ctzll(reached) + 1;
         run2 += __shfl(incl, 63);
     }
-    if (lane == 0) {
-        first[q] = p1;
-        // the counters of the batched scan start at zero (cleared here rather than by launches of their own)
-        if (cand_cnt) cand_cnt[q] = 0;
-        if (redo_cnt) redo_cnt[q] = 0;
-        if (gate && q == 0) gate[0] = 0;
-    }
+    if (lane == 0) put_first(c, q, p1);
 }
 
 // ---- list scan: a row of workgroups per query walks its probed lists ---------------------------
@@ -596,6 +617,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     __shared__ uint32_t s_work[4][256 + 64];             // per wavefront: 256 bins, 64 winning columns
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t row = (int64_t)blockIdx.x * 4 + wave;
+    if (MODE == 0) clear_buckets(a.cand);
     if (row >= a.rows) return;
     // MODE 2: row = (query, probe rank); the stretch of that list in the query's score row
     const int64_t q = MODE == 2 ? row / a.np : row;
@@ -960,6 +982,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
         if (MODE == 0) { if (a.out_i32) a.out_i32[row * k + lane] = real ? (int32_t)lab : -1; }
         else { if (a.out_i64) a.out_i64[row * k + lane] = real ? lab : -1; }
     }
+    // MODE 0: the candidate offsets follow from the probes while the lanes still hold them (with a launch of their own,
+    // which reads the probes back, a search of one query over 1M x 128 takes 45.2 us, so 43.9)
+    if (MODE == 0 && a.cand.cand_off) cand_offsets_lanes(a.cand, row, k, key != 0u ? (int)lab : -1, lane);
 }
 
 // ---- the k best of the queries redone exactly ----------------------------------------------------
@@ -1270,15 +1295,6 @@ hipError_t launch_rerank(const RerankArgs& a, int64_t nq, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_cand_offsets(const int32_t* probe, int64_t nq, int np, const int32_t* list_size,
-                               int32_t* cand_off, int k, int cap, int32_t* first, int32_t* cand_cnt, int32_t* gate,
-                               int32_t* redo_cnt, uint32_t* bucket_cnt, int buckets, hipStream_t st) {
-    if (nq <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cand_offsets, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, probe, nq, np,
-                       list_size, cand_off, k, cap, first, cand_cnt, gate, redo_cnt, bucket_cnt, bucket_cnt ? buckets : 0);
-    return hipGetLastError();
-}
-
 hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int blocks_per_query, int slices, hipStream_t st) {
     if (q_count <= 0) return hipSuccess;
     if (a.metric && (!a.qnorm || !a.store.xnorm)) return hipErrorInvalidValue;
@@ -1363,6 +1379,11 @@ hipError_t launch_select(int mode, const SelectArgs& a_in, hipStream_t st) {
     } else {
         if (mode == 0) hipLaunchKernelGGL((k_select<0, 1>), dim3(wgs), dim3(256), lds, st, a);
         else hipLaunchKernelGGL((k_select<1, 1>), dim3(wgs), dim3(256), lds, st, a);
+    }
+    if (mode == 0 && a.cand.cand_off) {
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_cand_offsets, dim3((unsigned)((a.rows + 3) / 4)), dim3(256), 0, st, a.out_i32, a.rows, a.k, a.cand);
     }
     return hipGetLastError();
 }
