@@ -992,17 +992,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
 // One workgroup per listed query; its row holds redo_cnt[q] scores in arbitrary order and the candidate columns
 // they belong to.  An entry's composite (order-preserving key of the score, then ~column) makes all entries
 // distinct: the k with the largest composites are the k best, ties going to the smaller column, whatever the
-// order they were appended in.  Up to kRedoSort entries are sorted in LDS; beyond that an eight-pass radix search
-// finds the k-th largest composite first.  Bound by the latency of its few passes; on the benchmark's searches
-// one to three queries of 10,000 come here, with 400 to 3000 entries each.
-constexpr int kRedoSort = 2048;
+// order they were appended in.  A radix search narrows the entries down, a byte at a time, until at most
+// max(k, kRedoFew) reach what is known of the k-th largest composite; those are gathered and sorted in LDS.  Bound by
+// the latency of its passes and of the sort's barriers; on the benchmark's searches one to three queries of 10,000
+// come here, with 400 to 3000 entries each.  Sorting up to 2048 entries outright, and all eight passes beyond, with the
+// digit looked for by one thread, took 50 us at 10M x 96 (k = 10); 13 us now, of which an empty launch is 4.5.
+constexpr int kRedoSort = 2048, kRedoFew = 128;
 static_assert(kMaxK <= kRedoSort, "the k winners are sorted in LDS");
 
 __global__ __launch_bounds__(1024) void k_redo_select(RedoSelectArgs a) {
     __shared__ uint64_t s_comp[kRedoSort];
     __shared__ int64_t s_lab[kRedoSort];
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t ctrl[2];
+    __shared__ uint32_t ctrl[3];
     const int tid = threadIdx.x;
     const int n_redo = min(a.gate[0] - a.gate_begin, a.gate_rows);
     for (int row = blockIdx.x; row < n_redo; row += gridDim.x) {
@@ -1016,9 +1018,10 @@ __global__ __launch_bounds__(1024) void k_redo_select(RedoSelectArgs a) {
         };
         const int take = n < a.k ? n : a.k;
         uint64_t last = 0;                          // every entry of at least this composite is gathered
-        if (n > kRedoSort) {
+        const int few = take > kRedoFew ? take : kRedoFew;
+        if (n > few) {
             uint64_t mask = 0;
-            uint32_t need = (uint32_t)take;
+            uint32_t need = (uint32_t)take;             // winners among the entries that share the bytes found so far
             for (int shift = 56; shift >= 0; shift -= 8) {
                 __syncthreads();
                 if (tid < 256) hist[tid] = 0;
@@ -1028,17 +1031,34 @@ __global__ __launch_bounds__(1024) void k_redo_select(RedoSelectArgs a) {
                     if ((c & mask) == last) atomicAdd(&hist[(c >> shift) & 255u], 1u);
                 }
                 __syncthreads();
-                if (tid == 0) {
-                    int dgt = 255;
-                    uint32_t above = 0;
-                    while (dgt > 0 && above + hist[dgt] < need) above += hist[dgt--];
-                    ctrl[0] = (uint32_t)dgt;
-                    ctrl[1] = need - above;
+                if (tid < 64) {                         // the digit where the running count, from above, first reaches `need`
+                    uint32_t h[4];                      // lane l owns digits 4l .. 4l+3
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) h[e] = hist[4 * tid + e];
+                    const uint32_t own = h[0] + h[1] + h[2] + h[3];
+                    uint32_t above = own;
+#pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const uint32_t t = __shfl_down(above, o);
+                        if (tid + o < 64) above += t;
+                    }
+                    above -= own;
+#pragma unroll
+                    for (int e = 3; e >= 0; --e) {
+                        if (above < need && above + h[e] >= need) {         // true for one digit only
+                            ctrl[0] = (uint32_t)(4 * tid + e);
+                            ctrl[1] = need - above;
+                            ctrl[2] = h[e];
+                        }
+                        above += h[e];
+                    }
                 }
                 __syncthreads();
                 last |= (uint64_t)ctrl[0] << shift;
                 mask |= (uint64_t)255 << shift;
                 need = ctrl[1];
+                // (all that reach `last`: the winners beyond its bytes, and every entry that shares them)
+                if ((uint32_t)take - need + ctrl[2] <= (uint32_t)few) break;
             }
         }
         __syncthreads();
