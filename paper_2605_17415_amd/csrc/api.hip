@@ -1399,27 +1399,13 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     if (metric) HIP_TRY(ix->w_qnorm.ensure((size_t)qc * sizeof(float)));
     const int64_t n_pairs = qc * nprobe;
     const int buckets = 2 * ix->nlist;
-    // Tiles of the batched passes: enough of them that the last ones to finish matter little (kTilesWanted over the
-    // chip's 512 to 1024 resident workgroups), no part of a list shorter than what one round of a workgroup's
-    // wavefronts covers.
-    constexpr int64_t kTilesWanted = 8192;
     TileShape shape{};
-    shape.tq_near = kBatchTileNear; shape.tq = kBatchTile;
-    const int64_t typical_list = std::max<int64_t>(1, ix->ntotal / ix->nlist);
-    auto part_for = [&](int64_t tiles) {
-        const int64_t cuts = std::max<int64_t>(1, kTilesWanted / std::max<int64_t>(1, tiles));
-        return (int)std::min<int64_t>(4096, std::max<int64_t>(512, round_up64(typical_list / cuts, 64)));
-    };
-    shape.part_near = part_for(std::min<int64_t>(ix->nlist, n_pairs));
-    shape.part = part_for(std::min<int64_t>(ix->nlist, n_pairs) + n_pairs / shape.tq);
-    // at most: every list's parts once, and the parts of the longest for every further query tile
-    int64_t near_tiles = n_pairs / shape.tq_near * list_parts(sizes[0], shape.part_near);
-    int64_t late_tiles = n_pairs / shape.tq * list_parts(sizes[0], shape.part);
-    for (int32_t n : ix->h_size) {
-        near_tiles += list_parts(n, shape.part_near);
-        late_tiles += list_parts(n, shape.part);
-    }
+    int64_t near_tiles = 0, late_tiles = 0;
     if (batched) {
+        shape = tile_shape(ix->ntotal, ix->nlist, n_pairs);
+        const ListRoom lists = list_room(ix->h_size.data(), ix->nlist);
+        near_tiles = tile_room(lists, qc, n_pairs, shape.tq_near);
+        late_tiles = tile_room(lists, qc, n_pairs, shape.tq);
         HIP_TRY(ix->w_zh.ensure((size_t)qc * ix->dp * sizeof(uint16_t)));
         HIP_TRY(ix->w_zl.ensure((size_t)qc * ix->dp * sizeof(uint16_t)));
         HIP_TRY(ix->w_first.ensure((size_t)qc * sizeof(int32_t)));
@@ -1427,7 +1413,8 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         HIP_TRY(ix->w_fids.ensure((size_t)qc * k * sizeof(int64_t)));
         HIP_TRY(ix->w_pairs.ensure((size_t)n_pairs * sizeof(int32_t)));
         HIP_TRY(ix->w_count.ensure((size_t)(4 * buckets + 8) * sizeof(uint32_t)));
-        HIP_TRY(ix->w_tilebkt.ensure((size_t)(near_tiles + late_tiles) * sizeof(int32_t)));
+        // (at least what ivftq_reconstruct keeps there, so that a call of it moves nothing that a recorded search uses)
+        HIP_TRY(ix->w_tilebkt.ensure((size_t)std::max<int64_t>(near_tiles + late_tiles, buckets + 1) * sizeof(int32_t)));
         HIP_TRY(ix->w_cscore.ensure((size_t)qc * cap * sizeof(float)));
         HIP_TRY(ix->w_cslot.ensure((size_t)qc * cap * sizeof(int64_t)));
         HIP_TRY(ix->w_ccnt.ensure((size_t)qc * sizeof(int32_t)));

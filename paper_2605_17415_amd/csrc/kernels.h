@@ -7,6 +7,8 @@
 #include <atomic>
 #include <cstdint>
 
+#include "search_plan.h"
+
 namespace ivftq {
 
 constexpr int kSlotsPerBlock = 64;   // vectors interleaved in one storage block (= one wavefront)
@@ -336,13 +338,6 @@ hipError_t launch_cascade_rescore(const CascadeArgs& a, int64_t nq, hipStream_t 
 
 // Whether the batched scan covers this (d, b); otherwise the streaming scan is used.
 bool batch_covers(int d, int b);
-// Queries per workgroup tile of the threshold pass, and of the dense pass, whose panel holds both parts of the queries
-// and whose lists have few of them (3 at 10M x 96, 11 at 10M x 200): with 64 the panel leaves room for as many
-// workgroups in a compute unit's LDS as its registers allow.
-constexpr int kBatchTile = 128, kBatchTileNear = 64;
-// Lists are cut into parts of about part_len vectors (a multiple of 64), each a tile of its own.
-struct TileShape { int tq_near, tq, part_near, part; };
-__host__ __device__ __forceinline__ int list_parts(int size, int part_len) { return size > part_len ? (size + part_len - 1) / part_len : 1; }
 
 // The (query, probe) pairs bucketed by list: bucket l holds the pairs (q, p < first[q]) of list l (the dense pass),
 // bucket L + l the pairs (q, p >= first[q]) (the threshold pass).  pairs[pair_off[b] ...] holds the count[b] flat pair

@@ -1,0 +1,51 @@
+// How a batched search is cut into workgroup tiles, and how much room that takes.  Plain C++, no device code.
+//
+// A recorded graph keeps the addresses of the workspace, which moves only when a call needs more of it.  So what a call is
+// given room for must not fall when it has more queries or probes (or results): after the largest call no smaller one may
+// need more.  The cut itself does not have that property (fewer pairs of query and list are cut into more parts each), so
+// the room is a bound that does.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+namespace ivftq {
+
+// Queries per workgroup tile of the threshold pass, and of the dense pass, whose panel holds both parts of the queries
+// and whose lists have few of them (3 at 10M x 96, 11 at 10M x 200): with 64 the panel leaves room for as many
+// workgroups in a compute unit's LDS as its registers allow.
+constexpr int kBatchTile = 128, kBatchTileNear = 64;
+// Lists of more than part_len vectors are cut into nearly equal parts of at most part_len, each a tile of its own.
+constexpr int kPartMin = 512, kPartMax = 4096;
+struct TileShape { int tq_near, tq, part_near, part; };
+constexpr int list_parts(int size, int part_len) { return size > part_len ? (size + part_len - 1) / part_len : 1; }
+
+// Tiles of the batched passes: enough of them that the last ones to finish matter little (kTilesWanted over the
+// chip's 512 to 1024 resident workgroups).
+constexpr int64_t kTilesWanted = 8192;
+inline int part_length(int64_t typical_list, int64_t tiles) {
+    const int64_t cuts = std::max<int64_t>(1, kTilesWanted / std::max<int64_t>(1, tiles));
+    return (int)std::min<int64_t>(kPartMax, std::max<int64_t>(kPartMin, (typical_list / cuts + 63) / 64 * 64));
+}
+inline TileShape tile_shape(int64_t ntotal, int nlist, int64_t pairs) {
+    const int64_t typical = std::max<int64_t>(1, ntotal / nlist), lists = std::min<int64_t>(nlist, pairs);
+    return {kBatchTileNear, kBatchTile, part_length(typical, lists), part_length(typical, lists + pairs / kBatchTile)};
+}
+
+// Entries that hold the tiles of a pass whose tiles take tq queries each, whatever the part length.  A list that meets c
+// queries has at most 1 + c / tq tiles for each of its parts; c adds up to `pairs` over the lists and is at most
+// `queries` in each.  list_room: what the first tile of every list takes.
+struct ListRoom { int64_t all, longest; };
+inline ListRoom list_room(const int32_t* size, int nlist) {
+    ListRoom r{0, 1};
+    for (int l = 0; l < nlist; ++l) {
+        const int parts = list_parts(size[l], kPartMin);
+        r.all += parts;
+        r.longest = std::max<int64_t>(r.longest, parts);
+    }
+    return r;
+}
+inline int64_t tile_room(const ListRoom& lists, int64_t queries, int64_t pairs, int tq) {
+    return lists.all + std::min(pairs / tq * lists.longest, queries / tq * lists.all);
+}
+
+}  // namespace ivftq

@@ -1,0 +1,91 @@
+// Driver of tests/test_search_plan.py: the room that search_plan.h gives a batched search, over a grid of calls and of
+// indexes.  Prints what is wrong, or "ok".
+#include <algorithm>
+#include <cstdio>
+#include <random>
+#include <vector>
+
+#include "search_plan.h"
+
+using namespace ivftq;
+
+namespace {
+
+std::vector<int32_t> lists(const char* kind, int nlist, int64_t total) {
+    std::mt19937_64 rng(nlist);
+    std::vector<int32_t> size(nlist);
+    for (int l = 0; l < nlist; ++l) {
+        const double mean = (double)total / nlist;
+        if (kind[0] == 's') size[l] = (int32_t)(mean * (0.7 + 0.6 * (rng() % 1000) / 1000.0));      // spread around the mean
+        if (kind[0] == 'h') size[l] = l == nlist / 2 ? (int32_t)(total - nlist) : 1;                // one hot list
+        if (kind[0] == 'e') size[l] = l % 3 == 0 ? (int32_t)(3 * mean) : 0;                          // most of them empty
+    }
+    return size;
+}
+
+// Tiles of a pass whose pairs meet list l pairs_of[l] times, as the grouping makes them.
+int64_t tiles_of(const std::vector<int32_t>& size, const std::vector<int64_t>& pairs_of, int tq, int part) {
+    int64_t t = 0;
+    for (size_t l = 0; l < size.size(); ++l)
+        if (size[l] > 0) t += (pairs_of[l] + tq - 1) / tq * list_parts(size[l], part);
+    return t;
+}
+
+}  // namespace
+
+int main() {
+    struct { const char* kind; int nlist; int64_t total; } const indexes[] = {
+        {"spread", 4000, 10'000'000}, {"spread", 2000, 10'000'000}, {"spread", 64, 20'000}, {"spread", 16384, 40'000'000},
+        {"hot", 4096, 10'000'000}, {"hot", 64, 1'000'000}, {"empty", 1000, 3'000'000}, {"spread", 300, 0}};
+    const int nq[] = {1, 2, 3, 50, 51, 63, 64, 65, 127, 128, 129, 195, 196, 387, 388, 500, 1000, 4096, 10'000, 32'767, 32'768};
+    const int np[] = {1, 2, 8, 31, 32, 33, 64};
+    std::mt19937_64 rng(5);
+    for (const auto& ix : indexes) {
+        const std::vector<int32_t> size = lists(ix.kind, ix.nlist, ix.total);
+        const ListRoom room = list_room(size.data(), ix.nlist);
+        for (int tq : {kBatchTileNear, kBatchTile}) {
+            for (size_t a = 0; a < std::size(nq); ++a)
+                for (size_t b = 0; b < std::size(np); ++b) {
+                    const int64_t here = tile_room(room, nq[a], (int64_t)nq[a] * np[b], tq);
+                    const int64_t fewer_q = a ? tile_room(room, nq[a - 1], (int64_t)nq[a - 1] * np[b], tq) : 0;
+                    const int64_t fewer_p = b ? tile_room(room, nq[a], (int64_t)nq[a] * np[b - 1], tq) : 0;
+                    if (here < fewer_q || here < fewer_p) {
+                        std::printf("%s nlist=%d tq=%d: %d queries x %d probes have room for %lld tiles, less than a smaller call (%lld, %lld)\n",
+                                    ix.kind, ix.nlist, tq, nq[a], np[b], (long long)here, (long long)fewer_q, (long long)fewer_p);
+                        return 1;
+                    }
+                }
+        }
+        // what calls really make: probes spread evenly, drawn at random, or all meeting in the longest lists
+        std::vector<int32_t> order(ix.nlist);
+        for (int l = 0; l < ix.nlist; ++l) order[l] = l;
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return size[x] > size[y]; });
+        for (int q : nq)
+            for (int p : np) {
+                const int64_t pairs = (int64_t)q * p;
+                if (p > ix.nlist || pairs > 400'000) continue;
+                const TileShape shape = tile_shape(ix.total, ix.nlist, pairs);
+                if (shape.part_near < kPartMin || shape.part < kPartMin || shape.part_near % 64 || shape.part % 64) {
+                    std::printf("%s nlist=%d: part lengths %d and %d\n", ix.kind, ix.nlist, shape.part_near, shape.part);
+                    return 1;
+                }
+                for (int how = 0; how < 3; ++how) {
+                    std::vector<int64_t> meets(ix.nlist, 0);
+                    if (how == 0) for (int64_t i = 0; i < pairs; ++i) ++meets[i % ix.nlist];
+                    if (how == 1) for (int64_t i = 0; i < pairs; ++i) { const int l = (int)(rng() % ix.nlist); if (meets[l] < q) ++meets[l]; }
+                    if (how == 2) for (int i = 0; i < p; ++i) meets[order[i]] = q;
+                    for (int near = 0; near < 2; ++near) {
+                        const int tq = near ? shape.tq_near : shape.tq;
+                        const int64_t made = tiles_of(size, meets, tq, near ? shape.part_near : shape.part), held = tile_room(room, q, pairs, tq);
+                        if (made > held) {
+                            std::printf("%s nlist=%d: %d queries x %d probes make %lld tiles, room for %lld\n", ix.kind, ix.nlist, q, p,
+                                        (long long)made, (long long)held);
+                            return 1;
+                        }
+                    }
+                }
+            }
+    }
+    std::printf("ok\n");
+    return 0;
+}
