@@ -1542,9 +1542,9 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         ma.k = k; ma.out_scores = scores_dev + q0 * k; ma.out_ids = ids_dev + q0 * k;
         ma.gate = ix->w_gate.as<int32_t>();
         HIP_TRY(timed(ix, st, P_MERGE, [&] { return launch_merge(ma, cnt, st); }));
-        // The redo keeps the scores that reach the threshold, in its own arithmetic: that of the first pass differs by
-        // rounding, at most 256 * 2^-24 (a float32 sum of d <= 256 terms) + 2^-20 (split products) of |z||C| times
-        // a norm of at most 2, together below kappa / 16.
+        // The redo keeps the scores that reach the threshold, in its own arithmetic: its sums differ from the first pass's
+        // by at most 2 * 256 * 2^-24 (two float32 sums of d <= 256 terms) + 2^-20 (split products) of |z||C|, times the
+        // norm (see redo_margin); kappa / 16 is 2^-14 |z||C|.
         la.gate = ix->w_gate.as<int32_t>(); la.gate_rows = (int)gate_rows; la.m_stride = 2 * m_stride;
         la.thresh = ba.thresh; la.thresh_stride = k; la.slack = kappa / 16.f; la.redo_cnt = redo_cnt;
         RedoSelectArgs ra{};

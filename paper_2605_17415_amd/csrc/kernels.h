@@ -252,11 +252,12 @@ struct ListScanArgs {
     float* scores; int64_t m_stride;
     int metric; const float* qnorm;
     // Exact redo (gate not null): instead of all queries the entries [gate_begin, gate_begin + gate_rows) of the
-    // gate[0] queries listed in gate[1..] are scanned.  Entry g's scores that reach thresh[q*thresh_stride] -
-    // slack go, redo_cnt[q] of them in any order, to the first half of score row g - gate_begin, their columns
-    // (cand_off[q][p] + i) to its second half; half a row has to hold every candidate.
+    // gate[0] queries listed in gate[1..] are scanned.  Entry g's scores that reach thresh[q*thresh_stride], less the
+    // rounding between the arithmetic of the threshold and this one, go, redo_cnt[q] of them in any order, to the
+    // first half of score row g - gate_begin, their columns (cand_off[q][p] + i) to its second half; half a row has to
+    // hold every candidate.
     const int32_t* gate; int gate_begin, gate_rows;
-    const float* thresh; int thresh_stride; float slack; int32_t* redo_cnt;      // (slack: of the score, before a raw metric's key)
+    const float* thresh; int thresh_stride; float slack; int32_t* redo_cnt;      // slack: the rounding of a sum, per unit of the stored norm
 };
 constexpr int kRedoWorkgroups = 2048;   // shared out over the queries a redo launch finds
 // blocks_per_query: workgroups per query (0 = one per probe), each walking its share of the probes; slices:

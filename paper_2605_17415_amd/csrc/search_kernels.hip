@@ -105,6 +105,12 @@ __global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict_
 // query's threshold are kept, with their columns, in arbitrary order.  A launch mostly finds no such query or a
 // few, so all of its workgroups are shared out over those it finds: two queries of 64 lists on eight workgroups
 // each took 0.66 ms at 10M x 200, each workgroup walking eight lists alone; spread over the chip 0.02 ms.
+//
+// redo_margin: how far a score s_l + g * sum can lie below its evaluation by the dense pass, from which the threshold
+// comes.  slack bounds the difference of the two sums; it counts for every unit of the norm, which a caller's own
+// codes may have at any size, and the sum with the coarse term is rounded at the size of that.
+__device__ __forceinline__ float redo_margin(float slack, float s_l, float g) { return slack * fmaxf(g, 1.f) + 0x1p-21f * fabsf(s_l); }
+
 template <int B, bool DIRECT, bool REDO>
 __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
     constexpr int K = 1 << B;
@@ -257,14 +263,17 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
         }
         const float g = __half2float(__ushort_as_half(store.gamma[slot]));
         float sc = s_l + g * acc;
-        float margin = a.slack;
+        float margin = 0.f;
         if (metric) {                  // ranking key of a raw metric (see launch_metric_finish)
             const float xn = store.xnorm[slot];
+            if constexpr (REDO) margin = fabsf(metric_scale(metric, xn, qn)) * redo_margin(a.slack, s_l, g);
             sc = metric_key(metric, sc, xn, qn);
-            if constexpr (REDO) margin = a.slack * metric_scale(metric, xn, qn);
+            if constexpr (REDO) margin += 0x1p-21f * fabsf(sc);
+        } else if constexpr (REDO) {
+            margin = redo_margin(a.slack, s_l, g);
         }
         if constexpr (REDO) {
-            const bool keep = sc >= reach - margin;
+            const bool keep = !(sc < reach - margin);     // (whatever is no number stays, as in a scan that keeps all)
             const uint64_t in = __ballot(keep);           // one counter update per wavefront
             if (in) {
                 const int lane = (int)(threadIdx.x & 63), leader = (int)__builtin_ctzll(in);

@@ -49,3 +49,59 @@ def test_selection_of_a_redone_query(per_list, equal, k):
         odd = np.isin(a, c, invert=True) & (a >= 0)
         assert np.all(np.abs(sa[odd] - sa[a >= 0][-1]) <= 2e-4)
     ix.close()
+
+
+@pytest.mark.parametrize("metric,norm,q_len,x_len", [("cosine", 1.0, 1.0, 1.0), ("cosine", 1e4, 1.0, 1.0), ("cosine", 6e4, 1.0, 1.0), ("ip", 1e4, 1.0, 3.0),
+                                                     ("l2", 1e4, 0.5, 2.0), ("l2", 1.0, 1e-3, 1.0), ("l2", 1.0, 1e-4, 1.0)])
+def test_threshold_survives_the_redo_at_any_norm(metric, norm, q_len, x_len):
+    """Stored norms far beyond the quantiser's own (a caller's codes may have any float16) and distances of queries much
+    shorter than the rows: the k best all sit in the nearest list, whose k-th is the threshold, and the other lists hold
+    900 copies of it per query one float16 step of the norm below, which overflow the candidate list.  The redo has to
+    find the k-th again although it sums in another order.
+
+    Tolerance: the sums differ by at most |z||C| (2 d 2^-24 + 2^-20) <= 2.7 * 8.6e-6 = 2.4e-5 per unit of the norm
+    (d = 64, |C| <= 8 * 0.33), a quarter of the copies' distance (2^-11 of a score of at least 0.2); rounding of the value itself
+    2^-22 of its terms."""
+    import paper_2605_17415_amd as pkg
+    print(f"[redo norms] {metric} norm={norm} q_len={q_len}", flush=True)
+    rng = np.random.default_rng(11)
+    d, L, b, nq, k = 64, 16, 4, 16, 10
+    cent = np.repeat(rng.standard_normal((1, d)).astype(np.float32), L, axis=0)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    pi = np.linalg.qr(rng.standard_normal((d, d)))[0].astype(np.float32)
+    ix = pkg.Index(d, b, L)
+    ix.set_coarse(cent)                              # equal cells: probed in ascending order, list 0 is the nearest
+    ix.set_rotation(pi)
+    levels, _ = ix.get_codebook()
+    q = rng.standard_normal((nq, d)).astype(np.float32)
+    q /= np.linalg.norm(q, axis=1, keepdims=True)
+    near = rng.integers(0, 1 << b, (3000, d)).astype(np.uint8)
+    est = (q.astype(np.float64) @ pi.T) @ levels[near].astype(np.float64).T
+    copies = np.repeat(near[np.argsort(-est, axis=1)[:, k - 1]], 900, axis=0)
+    codes = np.concatenate([near, copies])
+    full = np.float16(norm)
+    gamma = np.concatenate([np.full(len(near), full), np.full(len(copies), np.nextafter(full, np.float16(0)))])
+    cell = np.concatenate([np.zeros(len(near)), 1 + np.arange(len(copies)) % (L - 1)]).astype(np.int32)
+    on = [torch.from_numpy(v).to("cuda:0") for v in (cell, codes, gamma)]
+    if metric == "cosine":
+        ix.add_encoded(*on)
+    else:
+        ix.set_metric(pkg.binding.METRIC_IP if metric == "ip" else pkg.binding.METRIC_L2)
+        ix.add_encoded_raw(*on, torch.full((len(cell),), x_len, dtype=torch.float32, device="cuda:0"))
+    qd = torch.from_numpy(q * np.float32(q_len)).to("cuda:0")
+    got = []
+    for mode in (1, 2):
+        ix.set_search_mode(mode)
+        got.append([t.cpu().numpy() for t in ix.search(qd, L, k)])
+    assert ix.scan_stats()["redone_exactly"] == nq
+    (s1, i1), (s2, i2) = got
+    assert (i1 >= 0).all() and (i2 >= 0).all()
+    scale = {"cosine": 1.0, "ip": q_len * x_len, "l2": 2 * q_len * x_len}[metric]
+    offset = q_len ** 2 + x_len ** 2 if metric == "l2" else 0.0
+    tol = scale * 2.4e-5 * norm + 2.0 ** -22 * (offset + np.abs(s1).max())
+    np.testing.assert_allclose(s2, s1, rtol=0, atol=tol)
+    for a, c, sa in zip(i1, i2, s1):
+        assert len(set(c.tolist())) == k
+        odd = np.isin(a, c, invert=True)
+        assert np.all(np.abs(sa[odd] - sa[-1]) <= 2 * tol)
+    ix.close()
