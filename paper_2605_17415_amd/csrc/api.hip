@@ -1377,56 +1377,46 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     float cmax = 0.f;
     for (float v : ix->h_cb) cmax = std::max(cmax, std::fabs(v));
     const float kappa = screen_kappa(ix->d, cmax);
-    // Score rows.  The batched path stores scores of the dense prefix only (it stops at the first list that
-    // brings it to max(k, k*T/cap) vectors, so it is shorter than that plus the largest list); full-length
-    // rows (scores and columns) are needed for the queries redone exactly, which take turns in gate_rows rows of
-    // the same buffer.
-    // The streaming path stores every score.  Queries per pass: as many as the workspace limit allows, since
-    // every pass walks every probed list again.
     const int64_t need_max = std::max<int64_t>(k, (kPrefixFactorX2 * (int64_t)k * m_bound + 2 * cap - 1) / (2 * cap));
-    const int64_t row_stride = batched ? std::min<int64_t>(m_stride, round_up64(need_max + sizes[0], 4)) : m_stride;
-    int64_t qc = ix->ws_limit / (4 * std::max(row_stride, ldS));
-    qc = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(qc, nq), 32768));
-    const int64_t gate_rows = std::max<int64_t>(1, std::min<int64_t>(qc, ix->ws_limit / (8 * m_stride)));
-    const int64_t score_floats = batched ? std::max(qc * row_stride, gate_rows * 2 * m_stride) : qc * m_stride;
+    const SearchRows rows = search_rows(batched, nq, m_stride, round_up64(need_max + sizes[0], 4), ldS, ix->ws_limit);
+    const int64_t row_stride = rows.stride, qc = rows.queries, gate_rows = rows.gate_rows, held = rows.held;
 
-    HIP_TRY(ix->w_S.ensure((size_t)qc * ldS * sizeof(float)));
-    HIP_TRY(ix->w_scores.ensure((size_t)score_floats * sizeof(float)));
-    HIP_TRY(ix->w_probe.ensure((size_t)qc * nprobe * sizeof(int32_t)));
-    HIP_TRY(ix->w_coarse.ensure((size_t)qc * nprobe * sizeof(float)));
-    HIP_TRY(ix->w_candoff.ensure((size_t)qc * (nprobe + 1) * sizeof(int32_t)));
-    HIP_TRY(ix->w_z.ensure((size_t)qc * ix->dp * sizeof(float)));
-    if (metric) HIP_TRY(ix->w_qnorm.ensure((size_t)qc * sizeof(float)));
-    const int64_t n_pairs = qc * nprobe;
+    HIP_TRY(ix->w_S.ensure((size_t)held * ldS * sizeof(float)));
+    HIP_TRY(ix->w_scores.ensure((size_t)rows.floats * sizeof(float)));
+    HIP_TRY(ix->w_probe.ensure((size_t)held * nprobe * sizeof(int32_t)));
+    HIP_TRY(ix->w_coarse.ensure((size_t)held * nprobe * sizeof(float)));
+    HIP_TRY(ix->w_candoff.ensure((size_t)held * (nprobe + 1) * sizeof(int32_t)));
+    HIP_TRY(ix->w_z.ensure((size_t)held * ix->dp * sizeof(float)));
+    if (metric) HIP_TRY(ix->w_qnorm.ensure((size_t)held * sizeof(float)));
     const int buckets = 2 * ix->nlist;
     TileShape shape{};
     int64_t near_tiles = 0, late_tiles = 0;
     if (batched) {
-        shape = tile_shape(ix->ntotal, ix->nlist, n_pairs);
+        shape = tile_shape(ix->ntotal, ix->nlist, qc * nprobe);
         const ListRoom lists = list_room(ix->h_size.data(), ix->nlist);
-        near_tiles = tile_room(lists, qc, n_pairs, shape.tq_near);
-        late_tiles = tile_room(lists, qc, n_pairs, shape.tq);
-        HIP_TRY(ix->w_zh.ensure((size_t)qc * ix->dp * sizeof(uint16_t)));
-        HIP_TRY(ix->w_zl.ensure((size_t)qc * ix->dp * sizeof(uint16_t)));
-        HIP_TRY(ix->w_first.ensure((size_t)qc * sizeof(int32_t)));
-        HIP_TRY(ix->w_fscores.ensure((size_t)qc * k * sizeof(float)));
-        HIP_TRY(ix->w_fids.ensure((size_t)qc * k * sizeof(int64_t)));
-        HIP_TRY(ix->w_pairs.ensure((size_t)n_pairs * sizeof(int32_t)));
+        near_tiles = tile_room(lists, held, held * nprobe, shape.tq_near);
+        late_tiles = tile_room(lists, held, held * nprobe, shape.tq);
+        HIP_TRY(ix->w_zh.ensure((size_t)held * ix->dp * sizeof(uint16_t)));
+        HIP_TRY(ix->w_zl.ensure((size_t)held * ix->dp * sizeof(uint16_t)));
+        HIP_TRY(ix->w_first.ensure((size_t)held * sizeof(int32_t)));
+        HIP_TRY(ix->w_fscores.ensure((size_t)held * k * sizeof(float)));
+        HIP_TRY(ix->w_fids.ensure((size_t)held * k * sizeof(int64_t)));
+        HIP_TRY(ix->w_pairs.ensure((size_t)held * nprobe * sizeof(int32_t)));
         HIP_TRY(ix->w_count.ensure((size_t)(4 * buckets + 8) * sizeof(uint32_t)));
         // (at least what ivftq_reconstruct keeps there, so that a call of it moves nothing that a recorded search uses)
         HIP_TRY(ix->w_tilebkt.ensure((size_t)std::max<int64_t>(near_tiles + late_tiles, buckets + 1) * sizeof(int32_t)));
-        HIP_TRY(ix->w_cscore.ensure((size_t)qc * cap * sizeof(float)));
-        HIP_TRY(ix->w_cslot.ensure((size_t)qc * cap * sizeof(int64_t)));
-        HIP_TRY(ix->w_ccnt.ensure((size_t)qc * sizeof(int32_t)));
-        HIP_TRY(ix->w_gate.ensure((size_t)(2 * qc + 1) * sizeof(int32_t)));
+        HIP_TRY(ix->w_cscore.ensure((size_t)held * cap * sizeof(float)));
+        HIP_TRY(ix->w_cslot.ensure((size_t)held * cap * sizeof(int64_t)));
+        HIP_TRY(ix->w_ccnt.ensure((size_t)held * sizeof(int32_t)));
+        HIP_TRY(ix->w_gate.ensure((size_t)(2 * held + 1) * sizeof(int32_t)));
     }
     // Streaming path with so few queries that one wavefront per score row would leave the chip idle (the
     // selection then takes longer than the scan): select per (query, list) first.  Needs what the
     // one-wavefront kernel takes: k <= 64 and lists and survivor rows within its reach.
     const bool two_step = !batched && nq <= 64 && k <= 64 && nprobe > 1 && sizes[0] <= 16384 && (int64_t)nprobe * k <= 16384;
     if (two_step) {
-        HIP_TRY(ix->w_stage_s.ensure((size_t)qc * nprobe * k * sizeof(float)));
-        HIP_TRY(ix->w_stage_i.ensure((size_t)qc * nprobe * k * sizeof(int64_t)));
+        HIP_TRY(ix->w_stage_s.ensure((size_t)held * nprobe * k * sizeof(float)));
+        HIP_TRY(ix->w_stage_i.ensure((size_t)held * nprobe * k * sizeof(int64_t)));
     }
 
     for (int64_t q0 = 0; q0 < nq; q0 += qc) {

@@ -1,14 +1,42 @@
-// How a batched search is cut into workgroup tiles, and how much room that takes.  Plain C++, no device code.
+// How a search is cut into passes and a batched one into workgroup tiles, and how much room that takes.  Plain C++, no
+// device code.
 //
 // A recorded graph keeps the addresses of the workspace, which moves only when a call needs more of it.  So what a call is
-// given room for must not fall when it has more queries or probes (or results): after the largest call no smaller one may
-// need more.  The cut itself does not have that property (fewer pairs of query and list are cut into more parts each), so
-// the room is a bound that does.
+// given room for must not fall when it has more queries, probes or results: after the largest call no smaller one may
+// need more.  The cuts themselves do not have that property (fewer pairs of query and list are cut into more parts each;
+// shorter score rows allow longer passes), so the room is a bound that does.
 #pragma once
 #include <algorithm>
 #include <cstdint>
 
 namespace ivftq {
+
+// Passes.  The workspace limit is for the score rows; a pass takes as many queries as it allows, since every pass walks every
+// probed list again.  The batched path stores scores of the dense prefix only, rows of `prefix` floats (it stops at the
+// first list that brings it to need_max vectors, so it is shorter than that plus the largest list); full-length rows,
+// scores and columns, are needed for the queries redone exactly, which take turns in gate_rows rows of the same
+// buffer.  The streaming path stores every score.
+constexpr int64_t kPassQueries = 32768;
+struct SearchRows {
+    int64_t stride;        // floats between score rows
+    int64_t queries;       // of a pass
+    int64_t gate_rows;     // (batched)
+    int64_t held;          // rows of the arrays that have one per query of a pass
+    int64_t floats;        // of the score buffer
+};
+// row: floats of a full-length row (every candidate); coarse_row: of a row of coarse scores; limit: bytes
+inline SearchRows search_rows(bool batched, int64_t nq, int64_t row, int64_t prefix, int64_t coarse_row, int64_t limit) {
+    const int64_t most = std::min(nq, kPassQueries), room = limit / 4;
+    auto pass = [&](int64_t floats) { return std::max<int64_t>(1, std::min(most, room / floats)); };
+    SearchRows r{};
+    r.stride = batched ? std::min(row, prefix) : row;
+    r.queries = pass(std::max(r.stride, coarse_row));
+    r.gate_rows = std::min(r.queries, pass(2 * row));
+    r.held = pass(coarse_row);
+    const int64_t one = batched ? 2 * row : row;         // what a query takes when the limit does not cut the call
+    r.floats = std::min(most * one, std::max(room, one));
+    return r;
+}
 
 // Queries per workgroup tile of the threshold pass, and of the dense pass, whose panel holds both parts of the queries
 // and whose lists have few of them (3 at 10M x 96, 11 at 10M x 200): with 64 the panel leaves room for as many

@@ -31,6 +31,44 @@ int64_t tiles_of(const std::vector<int32_t>& size, const std::vector<int64_t>& p
     return t;
 }
 
+// Score rows and per-query arrays: every smaller call (fewer queries, candidates a query or a shorter prefix; streamed where
+// the larger one is batched) fits what the larger one was given, and a pass fits its own.
+int check_rows() {
+    struct Call { bool batched; int64_t nq, row, prefix; SearchRows r; };
+    const int64_t nqs[] = {1, 2, 10, 11, 26, 27, 387, 388, 5368, 10'000, 32'768, 100'000};
+    const int64_t coarse_rows[] = {16, 1024, 16'384}, limits[] = {1 << 20, 64 << 20, 4ll << 30};
+    for (int64_t limit : limits)
+        for (int64_t coarse : coarse_rows) {
+            std::vector<Call> calls;
+            for (int64_t row : {4, 1000, 9988, 10'000, 78'000, 100'004, 3'000'000})
+                for (int64_t prefix : {200, 5000, 20'000})
+                    for (int64_t nq : nqs)
+                        for (bool batched : {false, true}) calls.push_back({batched, nq, row, prefix, search_rows(batched, nq, row, prefix, coarse, limit)});
+            for (const Call& a : calls) {
+                const SearchRows& r = a.r;
+                const bool fits = r.queries >= 1 && r.queries <= a.nq && r.queries <= r.held && r.queries * r.stride <= r.floats &&
+                                  (!a.batched || (r.gate_rows >= 1 && r.gate_rows <= r.queries && r.gate_rows * 2 * a.row <= r.floats));
+                const bool limited = r.floats * 4 <= std::max(limit, 8 * a.row) && r.held * coarse * 4 <= std::max(limit, 4 * coarse);
+                if (!fits || !limited) {
+                    std::printf("limit %lld, %lld queries, rows of %lld: a pass does not fit its room\n", (long long)limit, (long long)a.nq, (long long)a.row);
+                    return 1;
+                }
+                for (const Call& b : calls) {
+                    if (b.nq > a.nq || b.row > a.row || b.prefix > a.prefix || (b.batched && !a.batched)) continue;
+                    if (b.r.floats > r.floats || b.r.held > r.held) {
+                        std::printf("limit %lld: %lld queries with rows of %lld (%s) need more than %lld with %lld (%s): %lld > %lld floats or %lld > %lld rows\n",
+                                    (long long)limit, (long long)b.nq, (long long)b.row, b.batched ? "batched" : "streamed", (long long)a.nq,
+                                    (long long)a.row, a.batched ? "batched" : "streamed", (long long)b.r.floats, (long long)r.floats,
+                                    (long long)b.r.held, (long long)r.held);
+                        return 1;
+                    }
+                }
+            }
+        }
+    std::printf("ok\n");
+    return 0;
+}
+
 }  // namespace
 
 int main() {
@@ -86,6 +124,5 @@ int main() {
                 }
             }
     }
-    std::printf("ok\n");
-    return 0;
+    return check_rows();
 }
