@@ -884,7 +884,7 @@ ivftq_status ivftq_train_coarse(ivftq_index* ix, const float* x_dev, int64_t n, 
                                    nullptr, cell_base, ix->w_order.as<int32_t>(), nullptr, st); }));
         double* gain = it == niter - 1 ? ix->w_gain.as<double>() : nullptr;
         HIP_TRY(timed(ix, st, P_KMEANS_SUMS, [&] { return launch_kmeans_cell_sums(x_dev, d, ix->w_order.as<int32_t>(), cell_base, counts_dev, L,
-                                        ix->w_sums.as<float>(), pitch, cent, bias, gain, st); }));
+                                        ix->w_sums.as<float>(), pitch, cent, gain, st); }));
         HIP_TRY(timed(ix, st, P_KMEANS_UPDATE, [&] { return launch_kmeans_update(cent, pitch, ix->w_sums.as<float>(), counts_dev, bias, cent_h, cent_l, L, ix->lpad, d, st); }));
         HIP_TRY(launch_kmeans_reseed(x_dev, d, ix->w_order.as<int32_t>(), cell_base, counts_dev, L, cent, pitch, bias, cent_h, cent_l,
                                      seed ^ 0x1234567887654321ull, reinterpret_cast<unsigned long long*>(flags + 2), flags + 1, st));

@@ -207,11 +207,11 @@ hipError_t launch_gather_rows(const float* src, int d, const int64_t* idx, int64
 // out[l] = sum of count[l'] over l' < l (L <= kMaxList)
 hipError_t launch_exclusive_scan(const uint32_t* count, int L, int64_t* out, hipStream_t st);
 // sums[l][j] = sum of x~_ij over the rows order[base[l] .. base[l] + count[l]) of cell l, added in a fixed
-// order (bit-reproducible); rows are normalised on the fly.  gain (may be null): gain[l] = <sums[l], cent[l]> +
-// count[l] * bias[l], the cell's share of the sum of best scores.
+// order (bit-reproducible); rows are normalised on the fly.  gain (may be null): gain[l] = sum over the same rows of
+// <x~_i, cent[l]> - |cent[l]|^2 / 2, the cell's share of the sum of best scores, added in double.
 hipError_t launch_kmeans_cell_sums(const float* x, int d, const int32_t* order, const int64_t* base,
                                    const uint32_t* count, int L, float* sums, int pitch, const float* cent,
-                                   const float* bias, double* gain, hipStream_t st);
+                                   double* gain, hipStream_t st);
 // cent[l] = sums[l]/counts[l] for non-empty cells; bias[l] = -|cent_l|^2/2 (padding rows: bias -inf); cent_h / cent_l:
 // the split float16 form of the new rows.  count may be null (every cell counts as empty: bias and split form only).
 hipError_t launch_kmeans_update(float* cent, int pitch, const float* sums, const uint32_t* counts,

@@ -205,22 +205,30 @@ __global__ __launch_bounds__(1024) void k_exclusive_scan(const uint32_t* __restr
 // a lane the coordinates lane, lane + 64, ...; the four partial sums are then added in the order 0, 1, 2, 3.
 // Nothing depends on scheduling, so the same input gives the same bits on every run.  Bound by the latency of
 // gathering rows: four rows of a wavefront are read together (500k x 96 over 4096 cells: 0.12 -> 0.09 ms).
+//
+// GAIN (the last iteration, of which the objective is reported): every row's <x~, c> is added up in double as well.
+// From the float32 sums it would carry their rounding, which grows with the rows of a cell and is large beside
+// the objective of tight cells (400k x 16 rows in 4 cells: 2.6e-5 of it).
+template <bool GAIN>
 __global__ __launch_bounds__(256) void k_kmeans_cell_sums(const float* __restrict__ x, int d,
                                                           const int32_t* __restrict__ order,
                                                           const int64_t* __restrict__ base,
                                                           const uint32_t* __restrict__ count,
                                                           float* __restrict__ sums, int pitch,
-                                                          const float* __restrict__ cent, const float* __restrict__ bias,
-                                                          double* __restrict__ gain) {
+                                                          const float* __restrict__ cent, double* __restrict__ gain) {
     __shared__ float part[4][kMaxD];
-    __shared__ double part_gain[4];
+    __shared__ double part_gain[4];                  // (GAIN)
     constexpr int T = kMaxD / 64, U = 4;
     const int l = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t first = base[l];
     const int cnt = (int)count[l];
-    float acc[T];
+    float acc[T], c[T];
+    double g = 0.0;
 #pragma unroll
-    for (int t = 0; t < T; ++t) acc[t] = 0.f;
+    for (int t = 0; t < T; ++t) {
+        acc[t] = 0.f;
+        c[t] = GAIN && lane + 64 * t < d ? cent[(int64_t)l * pitch + lane + 64 * t] : 0.f;
+    }
     for (int p = wave; p < cnt; p += 4 * U) {
         float v[U][T], n2[U];
 #pragma unroll
@@ -245,24 +253,26 @@ __global__ __launch_bounds__(256) void k_kmeans_cell_sums(const float* __restric
             const float nrm = sqrtf(n2[u]);
 #pragma unroll
             for (int t = 0; t < T; ++t)
-                if (64 * t < d) acc[t] += v[u][t] / nrm;
+                if (64 * t < d) {
+                    const float e = v[u][t] / nrm;
+                    acc[t] += e;
+                    if (GAIN) g += (double)e * (double)c[t];
+                }
         }
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) part[wave][lane + 64 * t] = acc[t];
     __syncthreads();
-    double g = 0.0;
-    for (int j = threadIdx.x; j < d; j += 256) {
-        const float s = ((part[0][j] + part[1][j]) + part[2][j]) + part[3][j];
-        sums[(int64_t)l * pitch + j] = s;
-        if (gain) g += (double)s * (double)cent[(int64_t)l * pitch + j];
-    }
-    if (gain) {                                      // uniform
+    for (int j = threadIdx.x; j < d; j += 256) sums[(int64_t)l * pitch + j] = ((part[0][j] + part[1][j]) + part[2][j]) + part[3][j];
+    if (GAIN) {
+        if (wave == 0) {                             // and -|c|^2 / 2 for each of them
+#pragma unroll
+            for (int t = 0; t < T; ++t) g -= 0.5 * cnt * ((double)c[t] * (double)c[t]);
+        }
         for (int o = 32; o > 0; o >>= 1) g += __shfl_xor(g, o);
         if (lane == 0) part_gain[wave] = g;
         __syncthreads();
-        if (threadIdx.x == 0)
-            gain[l] = ((part_gain[0] + part_gain[1]) + part_gain[2]) + part_gain[3] + (cnt ? (double)cnt * (double)bias[l] : 0.0);
+        if (threadIdx.x == 0) gain[l] = ((part_gain[0] + part_gain[1]) + part_gain[2]) + part_gain[3];
     }
 }
 
@@ -694,9 +704,10 @@ hipError_t launch_exclusive_scan(const uint32_t* count, int L, int64_t* out, hip
 
 hipError_t launch_kmeans_cell_sums(const float* x, int d, const int32_t* order, const int64_t* base,
                                    const uint32_t* count, int L, float* sums, int pitch, const float* cent,
-                                   const float* bias, double* gain, hipStream_t st) {
+                                   double* gain, hipStream_t st) {
     if (d > kMaxD) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_kmeans_cell_sums, dim3(L), dim3(256), 0, st, x, d, order, base, count, sums, pitch, cent, bias, gain);
+    if (gain) hipLaunchKernelGGL(k_kmeans_cell_sums<true>, dim3(L), dim3(256), 0, st, x, d, order, base, count, sums, pitch, cent, gain);
+    else hipLaunchKernelGGL(k_kmeans_cell_sums<false>, dim3(L), dim3(256), 0, st, x, d, order, base, count, sums, pitch, cent, gain);
     return hipGetLastError();
 }
 

@@ -50,6 +50,22 @@ def test_centroids_match_oracle_on_separated_groups(niter):
     ix.close()
 
 
+def test_objective_of_cells_with_many_rows():
+    """100,000 rows a cell: the objective does not carry the rounding of the cells' long float32 sums.
+
+    Tolerance: a row's <x~, c> is off by at most about 6 * 2^-24 (its norm's float32 sum of 16 squares, root and division),
+    independently of the other rows', and enters twice: relative to n rows of 0.036 each, six standard deviations are
+    6 * 2 * 3.6e-7 / (sqrt(400,000) * 0.036) = 1.9e-7.  The centroids' own rounding enters squared."""
+    X, comp = _blobs(d=16, L=4, per=100_000)
+    init = np.array([int(np.flatnonzero(comp == l)[0]) for l in range(4)], dtype=np.int64)
+    _, want_obj = orc.train_coarse(X, 4, 2, init)
+    ix = _pkg().Index(X.shape[1], 4, 4)
+    print(f"[kmeans objective] n={len(X)}", flush=True)
+    obj = ix.train_coarse(torch.from_numpy(X).to(DEV), 2, init_rows=init)
+    assert obj == pytest.approx(want_obj, rel=2e-7)
+    ix.close()
+
+
 def test_hand_case_on_the_unit_circle():
     """The planted case of the oracle's pin (six points on a circle, both initial centres in the first
     group; the 20-degree point changes cell in iteration 2), embedded in 8 dimensions."""
