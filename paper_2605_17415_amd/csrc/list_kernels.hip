@@ -543,17 +543,21 @@ __global__ __launch_bounds__(ReconCfg<DP>::THREADS) void k_reconstruct(
         // Stores through a buffer descriptor that ends with the list's rows: rows past the list (and columns past d,
         // sent past any end) are dropped by the address check, so every tile issues the same sixteen stores.  Behind
         // tests they could not be counted, and the wait for the next tile's words, which sit in front of them in the
-        // memory queue, would be a wait for the stores as well (0.31 ms at 1M x 128 that way).
+        // memory queue, would be a wait for the stores as well (0.31 ms at 1M x 128 that way).  The whole offset of a row
+        // goes through the address register: the check does not cover the scalar offset.
         const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
             x_out + (row0 + 32 * my_slab) * (int64_t)d, 0, min(max(cur_left, 0), 32) * d * 4, 0x00020000);
-        const uint32_t at0 = col < d ? (uint32_t)(4 * half * d + col) * 4u : 0x40000000u;
+        // (hidden from the compiler, which would keep the sixteen offsets in registers of their own from tile to tile)
+        uint32_t at = col < d ? (uint32_t)(4 * half * d + col) * 4u : 0x40000000u;
+        asm volatile("" : "+v"(at));
 #pragma unroll
         for (int g = 0; g < 4; ++g) {                // result rows 4g .. 4g+3 of a lane: vectors 8g + 4*half ..
             const float4 gm = *reinterpret_cast<const float4*>(gam + buf * VEC + 32 * my_slab + 8 * g + 4 * half);
             const float gg[4] = {gm.x, gm.y, gm.z, gm.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(fmaf(gg[i], acc[4 * g + i], c)), out, at0, (8 * g + i) * d * 4, 0);
+            for (int i = 0; i < 4; ++i, at += (uint32_t)d * 4u)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(fmaf(gg[i], acc[4 * g + i], c)), out, at, 0, 0);
+            at += (uint32_t)d * 16u;
         }
     }
 }

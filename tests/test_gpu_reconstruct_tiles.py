@@ -1,6 +1,6 @@
 """ivftq_reconstruct on lists whose lengths sit around the kernel's tiles of 32, 64 and 128 vectors (empty ones and runs
 of empty ones among them), for every padded width and every number of stored bits, against the definition
-x^ = c~_l + gamma * Pi^T C[code] in float64.
+x^ = c~_l + gamma * Pi^T C[code] in float64, with guard rows behind both outputs.
 
 Tolerance: every product carries a relative error of at most 2^-21 (two split float16 operands), and d of them are
 added in float32; Cauchy-Schwarz bounds the sum of their magnitudes by |C[code]| <= sqrt(d) max|C|, the rows of Pi being
@@ -32,8 +32,13 @@ def test_tiles_and_widths(d, b):
     ix.set_coarse(cent)
     ix.add_encoded(torch.from_numpy(cell).to(dev), torch.from_numpy(codes).to(dev), torch.from_numpy(gamma).to(dev),
                    torch.from_numpy(labels).to(dev))
-    x, ids = ix.reconstruct()
+    # guard rows behind the outputs: stores of a tile past its list's end are dropped, and nothing goes past the last list's
+    guard = 64
+    x, ids = torch.full((n + guard, d), -7.0, device=dev), torch.full((n + guard,), -7, dtype=torch.int64, device=dev)
+    pkg.binding._check(ix._lib.ivftq_reconstruct(ix._h, x.data_ptr(), ids.data_ptr(), None))
     torch.cuda.synchronize()
+    assert (x[n:] == -7.0).all() and (ids[n:] == -7).all()
+    x, ids = x[:n], ids[:n]
     order = np.argsort(cell, kind="stable")
     levels, _ = ix.get_codebook()
     pi = ix.get_rotation().astype(np.float64)
