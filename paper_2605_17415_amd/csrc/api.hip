@@ -1178,7 +1178,7 @@ ivftq_status reconstruct_all(ivftq_index* ix, float* x_out, int64_t* ids_out, hi
     ReconstructArgs a{};
     a.store = ix->store(); a.L = L; a.sizes_host = ix->h_size.data();
     a.cent = ix->cent.as<float>(); a.cent_pitch = ix->dp;
-    a.pit_h = ix->pit_h.as<uint16_t>(); a.pit_l = ix->pit_l.as<uint16_t>();
+    a.pi = ix->pi.as<float>(); a.pit_h = ix->pit_h.as<uint16_t>(); a.pit_l = ix->pit_l.as<uint16_t>();
     a.cb = ix->cb.as<float>(); a.d = ix->d; a.b = ix->b;
     a.out_off = ix->w_base.as<int64_t>(); a.tile_off = ix->w_tilebkt.as<int32_t>();
     a.x_out = x_out; a.labels_out = ids_out;

@@ -187,13 +187,13 @@ hipError_t launch_copy_lists(const ListStore& from, const ListStore& to, int L, 
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 
 // x_out[out_off[l] + v] = cent_l + gamma * Pi^T C[code] for vector v of list l (rows of d floats, list order),
-// labels_out (may be null) the stored labels in the same order.  pit_h / pit_l: split float16 form of Pi^T,
-// [DP][DP], DP = rot_dp(d).  out_off (L entries) and tile_off (L + 1) are scratch, filled by the call; sizes_host:
+// labels_out (may be null) the stored labels in the same order.  pi: float32 [DP][DP], DP = rot_dp(d), zero padded;
+// pit_h / pit_l: split float16 form of Pi^T.  out_off (L entries) and tile_off (L + 1) are scratch, filled by the call; sizes_host:
 // the list sizes as the host knows them.
 struct ReconstructArgs {
     ListStore store; int L; const int32_t* sizes_host;
     const float* cent; int cent_pitch;
-    const uint16_t* pit_h; const uint16_t* pit_l;
+    const float* pi; const uint16_t* pit_h; const uint16_t* pit_l;
     const float* cb; int d; int b;
     int64_t* out_off; int32_t* tile_off;
     float* x_out; int64_t* labels_out;

@@ -389,21 +389,30 @@ __global__ __launch_bounds__(64) void k_copy_rows_normalised(const float* __rest
 //
 // A contraction [vectors] x [d] . [d] x [d] whose result is written once: 4d bytes a vector against 3 * 2d^2 flop on
 // the matrix cores, so it should run at the speed of the stores.  Wavefront t of a workgroup owns the output
-// coordinates 32t .. 32t + 31 and keeps its 32 columns of Pi^T (both float16 parts) in registers for the life of the
-// workgroup; the 32 vectors of a tile are de-quantised once by all wavefronts together into LDS (split form, double
-// buffered: one barrier per tile; the next tile's packed words are in flight meanwhile) and are the row operand, so
+// coordinates 32t .. 32t + 31 and keeps its 32 columns of Pi^T (both float16 parts, or float32) in registers for the
+// life of the workgroup; the 32 vectors of a tile are de-quantised once by all wavefronts together into LDS (in the same
+// form, double buffered: one barrier per tile; the next tile's packed words are in flight meanwhile) and are the row operand, so
 // that a lane holds one output coordinate of 16 vectors and every store instruction writes whole 128-byte lines.
 // For d <= 64 several tiles share a workgroup (SLABS), which keeps it at 128 threads or more.  Workgroups walk
 // contiguous ranges of tiles: one search for the list, then steps.
-// 1M x 128, b = 4: 0.94 ms with one thread per output coordinate and float32 multiply-adds,
-// 0.16 ms so (3.7 TB/s read + written).
-template <int DP>
+// A call of 1M x 128, b = 4: 0.91 ms with one thread per output coordinate and float32 multiply-adds, 0.18 ms so (3.3 TB/s
+// read + written).
+//
+// F32: the operands are float32 (v_mfma_f32_32x32x2_f32) instead of both float16 parts, for d <= kReconF32.  With few
+// terms a sum the split form's own rounding (2^-23 of an operand, the same for every use of a level) is what counts:
+// against float64 the split results were up to 1.6 times as far off as float32 multiply-adds at d <= 60, never further
+// from 61 on, and closer the longer the sum (d = 128: 7.5e-8 against 1.03e-7).  The price, a call of 1M vectors: d = 32
+// 47 -> 59 us, d = 48 80 -> 102 us, d = 60 103 -> 122 us (with one thread per output coordinate 145, 194 and 292 us).
+constexpr int kReconF32 = 60;
+template <int DP, bool F32>
 struct ReconCfg {
     static constexpr int KB = DP / 16, NT = DP / 32, LDH = DP + 8;
     static constexpr int SLABS = NT >= 4 ? 1 : (NT == 1 ? 4 : 2);
     static constexpr int THREADS = 64 * NT * SLABS;
     static constexpr int VEC = 32 * SLABS;                       // vectors per tile
-    static constexpr int buf_halves = SLABS * 2 * 32 * LDH;      // hi and lo rows of one tile
+    static constexpr int LDF = DP + 4;                           // floats per LDS row
+    static constexpr int slab_halves = F32 ? 2 * 32 * LDF : 2 * 32 * LDH;         // float rows, or hi and lo rows
+    static constexpr int buf_halves = SLABS * slab_halves;
     static constexpr size_t lds_bytes = (size_t)2 * buf_halves * 2 + 256 * 4 + 2 * VEC * 4;
 };
 
@@ -415,32 +424,43 @@ __device__ __forceinline__ T fixed(const T* p) {
 }
 
 // NW: words that can hold the 8b bits of eight codes (1 for b = 1, 2, 4; 3 for b = 7; else 2)
-template <int DP, int NW>
-__global__ __launch_bounds__(ReconCfg<DP>::THREADS) void k_reconstruct(
-    ListStore store, int L, const float* __restrict__ cent, int cent_pitch, const uint16_t* __restrict__ pit_h,
+template <int DP, int NW, bool F32>
+__global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
+    ListStore store, int L, const float* __restrict__ cent, int cent_pitch, const float* __restrict__ pi, const uint16_t* __restrict__ pit_h,
     const uint16_t* __restrict__ pit_l, const float* __restrict__ cb, int d, int b, const int64_t* __restrict__ out_off,
     const int32_t* __restrict__ tile_off, int tiles, float* __restrict__ x_out, int64_t* __restrict__ labels_out) {
-    using Cfg = ReconCfg<DP>;
-    constexpr int KB = Cfg::KB, LDH = Cfg::LDH, VEC = Cfg::VEC, T = Cfg::THREADS;
+    using Cfg = ReconCfg<DP, F32>;
+    constexpr int KB = Cfg::KB, LDH = Cfg::LDH, LDF = Cfg::LDF, VEC = Cfg::VEC, T = Cfg::THREADS;
     extern __shared__ unsigned char lds_raw[];
-    uint16_t* stage = reinterpret_cast<uint16_t*>(lds_raw);                       // [2][SLABS][hi, lo][32][LDH]
-    uint32_t* tab = reinterpret_cast<uint32_t*>(stage + 2 * Cfg::buf_halves);     // [2^b] hi | lo << 16
-    float* gam = reinterpret_cast<float*>(tab + 256);                             // [2][VEC] norms * 2^-20
+    uint16_t* stage = reinterpret_cast<uint16_t*>(lds_raw);                       // [2][SLABS][hi, lo][32][LDH], or floats [2][SLABS][32][LDF]
+    uint32_t* tab = reinterpret_cast<uint32_t*>(stage + 2 * Cfg::buf_halves);     // [2^b] hi | lo << 16, or the float
+    float* gam = reinterpret_cast<float*>(tab + 256);                             // [2][VEC] norms (split form: * 2^-20)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, jl = lane & 31;
     const int col = 32 * (wave % Cfg::NT) + jl, my_slab = wave / Cfg::NT;
     const int words = store.words;
     const uint32_t mask = (1u << b) - 1u;
 
-    half8 bh[KB], bl[KB];
+    // the wavefront's columns of Pi^T: split form, or (F32) element 4g + i of a lane is Pi[8g + 4*half + i][col]
+    half8 bh[F32 ? 1 : KB], bl[F32 ? 1 : KB];
+    float bf[F32 ? DP / 2 : 1];
+    if constexpr (F32) {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-        bh[kb] = *reinterpret_cast<const half8*>(pit_h + (size_t)col * DP + 16 * kb + 8 * half);
-        bl[kb] = *reinterpret_cast<const half8*>(pit_l + (size_t)col * DP + 16 * kb + 8 * half);
+        for (int e = 0; e < DP / 2; ++e) bf[e] = pi[(8 * (e / 4) + 4 * half + e % 4) * DP + col];
+    } else {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            bh[kb] = *reinterpret_cast<const half8*>(pit_h + (size_t)col * DP + 16 * kb + 8 * half);
+            bl[kb] = *reinterpret_cast<const half8*>(pit_l + (size_t)col * DP + 16 * kb + 8 * half);
+        }
     }
     for (int e = tid; e <= (int)mask; e += T) {
-        _Float16 h, l;
-        split_scaled(cb[e], h, l);
-        tab[e] = (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, l) << 16);
+        if constexpr (F32) {
+            tab[e] = __float_as_uint(cb[e]);
+        } else {
+            _Float16 h, l;
+            split_scaled(cb[e], h, l);
+            tab[e] = (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, l) << 16);
+        }
     }
 
     // this workgroup's tiles, and the list of the first one
@@ -482,7 +502,7 @@ __global__ __launch_bounds__(ReconCfg<DP>::THREADS) void k_reconstruct(
     int tile_end = fixed(tile_off + l + 1);
     fetch(l, n_l, base, v0);
 
-    constexpr float kUnscale = 1.f / (kSplitScale * kSplitScale);
+    constexpr float kUnscale = F32 ? 1.f : 1.f / (kSplitScale * kSplitScale);
     int buf = 0;
     __syncthreads();                                 // the table is written
     for (int tile = t_begin; tile < t_end; ++tile, buf ^= 1) {
@@ -490,20 +510,28 @@ __global__ __launch_bounds__(ReconCfg<DP>::THREADS) void k_reconstruct(
         uint16_t* st = stage + buf * Cfg::buf_halves;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            const int e = tid + p * T, slab = (e >> 5) / (DP / 8), chunk = (e >> 5) % (DP / 8);
+            const int grp = tid + p * T, slab = (grp >> 5) / (DP / 8), chunk = (grp >> 5) % (DP / 8);
             const int sh = (8 * b * chunk) & 31;
             uint64_t bits = ((NW > 1 ? (uint64_t)w[p][NW > 1 ? 1 : 0] << 32 : 0ull) | w[p][0]) >> sh;
             if (NW > 2 && sh) bits |= (uint64_t)w[p][NW - 1] << (64 - sh);
-            uint32_t hv[4], lv[4];
+            uint32_t e[8];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint32_t e0 = tab[(uint32_t)(bits >> (2 * t * b)) & mask], e1 = tab[(uint32_t)(bits >> ((2 * t + 1) * b)) & mask];
-                hv[t] = (e0 & 0xFFFFu) | (e1 << 16);
-                lv[t] = (e0 >> 16) | (e1 & 0xFFFF0000u);
+            for (int t = 0; t < 8; ++t) e[t] = tab[(uint32_t)(bits >> (t * b)) & mask];
+            if constexpr (F32) {
+                uint32_t* row = reinterpret_cast<uint32_t*>(st + slab * Cfg::slab_halves) + (grp & 31) * LDF + 8 * chunk;
+                *reinterpret_cast<uint4*>(row) = make_uint4(e[0], e[1], e[2], e[3]);
+                *reinterpret_cast<uint4*>(row + 4) = make_uint4(e[4], e[5], e[6], e[7]);
+            } else {
+                uint32_t hv[4], lv[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    hv[t] = (e[2 * t] & 0xFFFFu) | (e[2 * t + 1] << 16);
+                    lv[t] = (e[2 * t] >> 16) | (e[2 * t + 1] & 0xFFFF0000u);
+                }
+                uint16_t* row = st + slab * Cfg::slab_halves + (grp & 31) * LDH + 8 * chunk;
+                *reinterpret_cast<uint4*>(row) = make_uint4(hv[0], hv[1], hv[2], hv[3]);
+                *reinterpret_cast<uint4*>(row + 32 * LDH) = make_uint4(lv[0], lv[1], lv[2], lv[3]);
             }
-            uint16_t* row = st + slab * (2 * 32 * LDH) + (e & 31) * LDH + 8 * chunk;
-            *reinterpret_cast<uint4*>(row) = make_uint4(hv[0], hv[1], hv[2], hv[3]);
-            *reinterpret_cast<uint4*>(row + 32 * LDH) = make_uint4(lv[0], lv[1], lv[2], lv[3]);
         }
         if (tid < VEC) gam[buf * VEC + tid] = kUnscale * __half2float(__ushort_as_half((uint16_t)next_gam));
         const __amdgpu_buffer_rsrc_t lab = __builtin_amdgcn_make_buffer_rsrc(labels_out + (labels_out ? row0 : 0), 0,
@@ -528,17 +556,31 @@ __global__ __launch_bounds__(ReconCfg<DP>::THREADS) void k_reconstruct(
         fetch(l, n_l, base, v0);                     // (after the last tile: the same tile again, unused)
         // One barrier per tile: the other buffer, written in the next round, was last read before this barrier.
         __syncthreads();
-        const uint16_t* ah_base = st + my_slab * (2 * 32 * LDH) + jl * LDH + 8 * half;
-        const uint16_t* al_base = ah_base + 32 * LDH;
         floatx16 acc;
         const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if constexpr (F32) {
+            // (a lane's four floats of a read are the terms 8g + 4*half + i of four products, as in bf)
+            const float* a_base = reinterpret_cast<const float*>(st + my_slab * Cfg::slab_halves) + jl * LDF + 4 * half;
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            const half8 ah = *reinterpret_cast<const half8*>(ah_base + 16 * kb);
-            const half8 al = *reinterpret_cast<const half8*>(al_base + 16 * kb);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[kb], kb ? acc : zero, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[kb], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[kb], acc, 0, 0, 0);
+            for (int g = 0; g < DP / 8; ++g) {
+                if (8 * g >= d) break;               // (the same for all: what follows is padding)
+                const float4 a = *reinterpret_cast<const float4*>(a_base + 8 * g);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bf[F32 ? 4 * g : 0], g ? acc : zero, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bf[F32 ? 4 * g + 1 : 0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bf[F32 ? 4 * g + 2 : 0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bf[F32 ? 4 * g + 3 : 0], acc, 0, 0, 0);
+            }
+        } else {
+            const uint16_t* ah_base = st + my_slab * Cfg::slab_halves + jl * LDH + 8 * half;
+            const uint16_t* al_base = ah_base + 32 * LDH;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                const half8 ah = *reinterpret_cast<const half8*>(ah_base + 16 * kb);
+                const half8 al = *reinterpret_cast<const half8*>(al_base + 16 * kb);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[F32 ? 0 : kb], kb ? acc : zero, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[F32 ? 0 : kb], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[F32 ? 0 : kb], acc, 0, 0, 0);
+            }
         }
         // Stores through a buffer descriptor that ends with the list's rows: rows past the list (and columns past d,
         // sent past any end) are dropped by the address check, so every tile issues the same sixteen stores.  Behind
@@ -594,11 +636,11 @@ __global__ __launch_bounds__(1024) void k_list_prefix(const int32_t* __restrict_
     if (tid == 1023) tile_off[L] = part_t[1023];
 }
 
-template <int DP, int NW>
+template <int DP, int NW, bool F32>
 hipError_t run_reconstruct_nw(const ReconstructArgs& a, int cus, hipStream_t st) {
-    using Cfg = ReconCfg<DP>;
+    using Cfg = ReconCfg<DP, F32>;
     static LdsLimit lim;
-    const hipError_t e = lim.ensure(reinterpret_cast<const void*>(k_reconstruct<DP, NW>), Cfg::lds_bytes);
+    const hipError_t e = lim.ensure(reinterpret_cast<const void*>(k_reconstruct<DP, NW, F32>), Cfg::lds_bytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_list_prefix, dim3(1), dim3(1024), 0, st, a.store.list_size, a.L, Cfg::VEC, a.out_off, a.tile_off);
     int64_t tiles = 0;
@@ -606,12 +648,12 @@ hipError_t run_reconstruct_nw(const ReconstructArgs& a, int cus, hipStream_t st)
     static std::atomic<int> per_cu{0};               // workgroups a compute unit holds, the same on every device of this kind
     int fit = per_cu.load(std::memory_order_relaxed);
     if (fit == 0) {
-        const hipError_t eo = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, reinterpret_cast<const void*>(k_reconstruct<DP, NW>), Cfg::THREADS, Cfg::lds_bytes);
+        const hipError_t eo = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, reinterpret_cast<const void*>(k_reconstruct<DP, NW, F32>), Cfg::THREADS, Cfg::lds_bytes);
         if (eo != hipSuccess) return eo;
         per_cu.store(fit = std::max(fit, 1), std::memory_order_relaxed);
     }
     const unsigned blocks = (unsigned)std::min<int64_t>(tiles, (int64_t)cus * fit);
-    hipLaunchKernelGGL((k_reconstruct<DP, NW>), dim3(blocks), dim3(Cfg::THREADS), Cfg::lds_bytes, st, a.store, a.L, a.cent, a.cent_pitch, a.pit_h,
+    hipLaunchKernelGGL((k_reconstruct<DP, NW, F32>), dim3(blocks), dim3(Cfg::THREADS), Cfg::lds_bytes, st, a.store, a.L, a.cent, a.cent_pitch, a.pi, a.pit_h,
                        a.pit_l, a.cb, a.d, a.b, (const int64_t*)a.out_off, (const int32_t*)a.tile_off, (int)tiles, a.x_out, a.labels_out);
     return hipGetLastError();
 }
@@ -649,11 +691,18 @@ __global__ __launch_bounds__(256) void k_inertia(const double* __restrict__ gain
     if (threadIdx.x == 0) *out = (double)n - 2.0 * part[0];
 }
 
+template <int DP, bool F32>
+hipError_t run_reconstruct_as(const ReconstructArgs& a, int cus, hipStream_t st) {
+    if (a.b == 1 || a.b == 2 || a.b == 4) return run_reconstruct_nw<DP, 1, F32>(a, cus, st);
+    if (a.b == 7) return run_reconstruct_nw<DP, 3, F32>(a, cus, st);
+    return run_reconstruct_nw<DP, 2, F32>(a, cus, st);
+}
+
 template <int DP>
 hipError_t run_reconstruct(const ReconstructArgs& a, int cus, hipStream_t st) {
-    if (a.b == 1 || a.b == 2 || a.b == 4) return run_reconstruct_nw<DP, 1>(a, cus, st);
-    if (a.b == 7) return run_reconstruct_nw<DP, 3>(a, cus, st);
-    return run_reconstruct_nw<DP, 2>(a, cus, st);
+    if constexpr (DP <= kReconF32) return run_reconstruct_as<DP, true>(a, cus, st);
+    else if constexpr (DP - 32 < kReconF32) return a.d <= kReconF32 ? run_reconstruct_as<DP, true>(a, cus, st) : run_reconstruct_as<DP, false>(a, cus, st);
+    else return run_reconstruct_as<DP, false>(a, cus, st);
 }
 
 }  // namespace
