@@ -130,3 +130,32 @@ def test_create_with_a_refusing_callback():
     with pytest.raises(pkg.IvftqError) as e:
         pkg.Index(64, 4, 16, allocator=al.pair())
     assert e.value.status == pkg.binding.OOM and al.live == {}
+
+
+@pytest.mark.parametrize("limit", [1 << 20, 4 << 30])
+def test_smaller_calls_request_nothing(limit):
+    """After a call no later one with fewer queries, probes or results asks for memory, whether or not the workspace limit
+    cuts the calls into passes, nor does reading the index back: a recorded search stays valid."""
+    pkg = _pkg()
+    cs = gpu_cases.get_case("d96_b3")
+    al = CountingAllocator()
+    ix = pkg.Index(cs.d, cs.b_stage1, cs.nlist, sign_bit=cs.sign_bit, allocator=al.pair())
+    ix.set_coarse(cs.cent)
+    ix.set_rotation(cs.Pi)
+    ix.set_workspace_limit(limit)
+    ix.encode_add(torch.from_numpy(cs.X).to(DEV))
+    q = torch.from_numpy(np.concatenate([cs.Q] * (1 + 700 // len(cs.Q)))[:700]).to(DEV)
+    for mode in (2, 1):
+        ix.set_search_mode(mode)
+        ix.search(q, cs.nprobe, cs.k + 30)
+        n_req = al.requests
+        for nq in (700, 699, 650, 387, 130, 129, 66):
+            for nprobe in (cs.nprobe, cs.nprobe - 1, 2):
+                for k in (cs.k + 30, cs.k, 1):
+                    ix.search(q[:nq], nprobe, k)
+                    assert al.requests == n_req, f"mode {mode}: {nq} queries, {nprobe} probes, k = {k} moved the workspace"
+        ix.reconstruct()
+        assert al.requests == n_req
+    torch.cuda.synchronize()
+    ix.close()
+    assert al.live == {}

@@ -1,7 +1,8 @@
 """The batched list scan (search mode 2) over the forms it takes: every bit count it has, dimensions that end inside and at
 the end of a block of 16, cosine and raw metrics, lists that are empty, shorter than one tile of vectors, at its edges, and
-long enough to be cut into several parts (part lengths are multiples of 64 and at least 512 vectors).  Against the
-streaming scan (mode 1) of the same index, which sums float32 products in another order.
+long enough to be cut into several parts (lists of more than 512 vectors are cut into nearly equal parts of at most that
+many), and with more than 256 results, which the merge sorts instead of counting.  Against the streaming scan (mode 1) of
+the same index, which sums float32 products in another order.
 
 Tolerance: a score is coarse + gamma * (d products, both split float16 operands), its two evaluations apart by at most
 gamma |z| |C| (2 * 2^-21 + d 2^-24) <= 1e-4 for gamma <= 1.2, |z| = 1, |C| <= 2 and d <= 256; a raw metric scales that by |q||x|
@@ -14,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 SIZES = [0, 1, 31, 64, 65, 0, 127, 511, 512, 513, 577, 1025, 2500, 64 * 33, 900, 3]
 FORMS = [(32, 4, "cosine", 1), (50, 2, "l2", 10), (64, 3, "ip", 33), (96, 4, "l2", 10), (100, 5, "cosine", 100), (128, 8, "cosine", 10),
-         (129, 4, "ip", 7), (161, 5, "l2", 20), (200, 3, "cosine", 64), (208, 8, "ip", 10), (224, 2, "cosine", 100), (255, 8, "l2", 65), (256, 5, "ip", 20)]
+         (129, 4, "ip", 7), (161, 5, "l2", 20), (200, 3, "cosine", 64), (208, 8, "ip", 10), (224, 2, "cosine", 100), (255, 8, "l2", 65), (256, 5, "ip", 20),
+         (96, 4, "l2", 300), (100, 4, "ip", 500), (64, 8, "cosine", 300)]
 
 
 def _index(d, b, metric, rng):
@@ -52,6 +54,10 @@ def test_batched_equals_streaming(d, b, metric, k):
             s, i = ix.search(qd, 9, k)
             torch.cuda.synchronize()
             got.append((s.cpu().numpy(), i.cpu().numpy()))
+        stats = ix.scan_stats()
+        assert stats["queries"] == nq                # mode 2 took the batched scan
+        if k >= 300 and nq == 300:                   # and the merge had more than k entries to order
+            assert stats["mean_candidates"] > 0 and stats["redone_exactly"] < nq
         (s1, i1), (s2, i2) = got
         real = i1 >= 0
         np.testing.assert_array_equal(real, i2 >= 0)

@@ -1,7 +1,7 @@
 """Queries redone exactly because their candidate list overflowed: the selection among what they keep, for numbers of winners
-at its edges (1, one wavefront's, kRedoFew - 1 / + 0 / + 1 = 127 ... 129, many) and for numbers of kept entries below and
-beyond the 2048 that its LDS holds, with distinct scores and with all scores of a cell equal.  Against the streaming scan
-of the same index.
+at its edges (1, one wavefront's, kRedoFew - 1 / + 0 / + 1 = 127 ... 129, many) and for numbers of kept entries around kRedoFew,
+below and beyond the 2048 that its LDS holds, with distinct scores and with all scores of a cell equal.  Against the
+streaming scan of the same index; every case is one in which the query really is redone.
 
 Tolerance: as in the other comparisons of two float32 evaluations of coarse + gamma * (d products), 1e-4 for gamma <= 1.2."""
 import numpy as np
@@ -11,8 +11,9 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("k", [1, 10, 64, 127, 128, 129, 300])
-@pytest.mark.parametrize("per_list,equal", [(120, False), (400, False), (2000, False), (2000, True)])
+# (seven lists of 120 overflow a candidate list of 512, i.e. k up to 32, but not the 1024 to 2048 of larger k)
+@pytest.mark.parametrize("per_list,equal,k", [(120, False, k) for k in (1, 10, 32)] +
+                         [(n, equal, k) for n, equal in ((400, False), (2000, False), (2000, True)) for k in (1, 10, 64, 127, 128, 129, 300)])
 def test_selection_of_a_redone_query(per_list, equal, k):
     import paper_2605_17415_amd as pkg
     print(f"[redo select] per_list={per_list} equal={equal} k={k}", flush=True)
@@ -25,13 +26,14 @@ def test_selection_of_a_redone_query(per_list, equal, k):
     pi = np.linalg.qr(rng.standard_normal((d, d)))[0].astype(np.float32)
     # the nearest cell, whose vectors the threshold comes from, holds those furthest from the first query (the lowest code
     # where its rotated coordinate is positive, else the highest); what the other cells hold beats it
-    cell = np.concatenate([np.full(1500, order[0])] + [np.full(per_list, l) for l in order[1:8]]).astype(np.int32)
+    near = 1500 if k < 300 else 4000                 # the whole dense prefix: more than k * (candidates) / capacity
+    cell = np.concatenate([np.full(near, order[0])] + [np.full(per_list, l) for l in order[1:8]]).astype(np.int32)
     codes = rng.integers(0, 1 << b, (len(cell), d)).astype(np.uint8)
-    codes[:1500] = np.where(pi @ q[0].cpu().numpy() > 0, 0, (1 << b) - 1)
+    codes[:near] = np.where(pi @ q[0].cpu().numpy() > 0, 0, (1 << b) - 1)
     gamma = rng.uniform(0.2, 1.2, len(cell)).astype(np.float16)
-    gamma[:1500] = 1.2
+    gamma[:near] = 1.2
     if equal:
-        gamma[1500:] = 0.0
+        gamma[near:] = 0.0
     ix = pkg.Index(d, b, L)
     ix.set_coarse(cent)
     ix.set_rotation(pi)
@@ -40,6 +42,7 @@ def test_selection_of_a_redone_query(per_list, equal, k):
     for mode in (1, 2):
         ix.set_search_mode(mode)
         got.append([t.cpu().numpy() for t in ix.search(q, 8, k)])
+    assert ix.scan_stats()["redone_exactly"] >= 1
     (s1, i1), (s2, i2) = got
     np.testing.assert_array_equal(s1 == -np.inf, s2 == -np.inf)
     real = np.isfinite(s1)
@@ -104,4 +107,43 @@ def test_threshold_survives_the_redo_at_any_norm(metric, norm, q_len, x_len):
         assert len(set(c.tolist())) == k
         odd = np.isin(a, c, invert=True)
         assert np.all(np.abs(sa[odd] - sa[-1]) <= 2 * tol)
+    ix.close()
+
+
+@pytest.mark.parametrize("above", [0, 116, 117, 118, 119, 120, 300])
+def test_few_kept_entries(above):
+    """About above + 10 entries reach the threshold (the 10 best of the nearest list and what other lists hold above it), around
+    the 128 from which on a radix search narrows them down; 900 copies a float16 step of the norm below it overflow the
+    candidate list."""
+    import paper_2605_17415_amd as pkg
+    print(f"[redo few] above={above}", flush=True)
+    rng = np.random.default_rng(above)
+    d, L, b, k = 64, 8, 4, 10
+    cent = np.repeat(rng.standard_normal((1, d)).astype(np.float32), L, axis=0)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    ix = pkg.Index(d, b, L, rotation_seed=3)
+    ix.set_coarse(cent)
+    levels, _ = ix.get_codebook()
+    q = rng.standard_normal((1, d)).astype(np.float32)
+    q /= np.linalg.norm(q)
+    pool = rng.integers(0, 1 << b, (4000, d)).astype(np.uint8)
+    est = levels[pool].astype(np.float64) @ (ix.get_rotation().astype(np.float64) @ q[0])
+    pool = pool[np.argsort(-est)]
+    near = pool[above:]
+    codes = np.concatenate([near, pool[:above], np.repeat(near[k - 1:k], 900, axis=0)])
+    gamma = np.ones(len(codes), np.float16)
+    gamma[len(pool):] = np.nextafter(np.float16(1), np.float16(0))
+    cell = np.zeros(len(codes), np.int32)
+    cell[len(near):] = 1 + np.arange(len(codes) - len(near)) % (L - 1)
+    ix.add_encoded(*[torch.from_numpy(v).to("cuda:0") for v in (cell, codes, gamma)])
+    got = []
+    for mode in (1, 2):
+        ix.set_search_mode(mode)
+        got.append([t.cpu().numpy() for t in ix.search(torch.from_numpy(q).to("cuda:0"), L, k)])
+    assert ix.scan_stats()["redone_exactly"] == 1
+    (s1, i1), (s2, i2) = got
+    assert (i2 >= 0).all() and len(set(i2[0].tolist())) == k
+    np.testing.assert_allclose(s2, s1, rtol=0, atol=1e-4)
+    odd = np.isin(i1[0], i2[0], invert=True)
+    assert np.all(np.abs(s1[0][odd] - s1[0][-1]) <= 2e-4)
     ix.close()
