@@ -37,6 +37,13 @@ struct BatchCfg {
     // dense pass: both parts of the panel, and table entries of both parts (two codes: 8 bytes, one code: 4)
     static constexpr size_t lds_dense = (size_t)2 * TQ * LDH * sizeof(uint16_t) + 16 * TQ + (size_t)PT * (PAIR ? 8 : 4);
     static constexpr size_t lds_threshold = (size_t)TQ * LDH * sizeof(uint16_t) + 16 * TQ + (size_t)PT * 4;
+    // Candidates of a tile held back by the threshold pass, as many as `occ` workgroups of a compute unit have room for (in
+    // whole allocation units, less the pass's static words), at most 4096.
+    static constexpr int held_back(int occ) {
+        const size_t room = 160 * 1024 / occ / 1280 * 1280 - 64, fit = (room - lds_threshold - 4 * TQ) / 8;
+        return fit < 4096 ? (int)fit / 2 * 2 : 4096;
+    }
+    static constexpr size_t lds_held_back(int occ) { return lds_threshold + 8 * (size_t)held_back(occ) + 4 * TQ; }
 };
 
 // The 8 codes of block kb that a lane de-quantises, coordinates 16*kb + 8*half + [0, 8), begin in word first_word
@@ -302,16 +309,26 @@ void k_batch_dense(BatchScanArgs a) {
 // matrix instruction (32 cycles) alone would keep LDS as busy as the matrix pipes, and the look-ups come on top.
 // S = row tiles per wavefront (one where the registers do not reach for two).  RAW: scores are ranking keys of a raw
 // metric (a template parameter: the lengths' range takes registers).
-template <int DP, int B, int NQ, int WAVES, int OCC, int S, bool RAW>
+//
+// A candidate is appended to its query's list with an update of the query's counter.  Updates of one counter from all over
+// the chip follow each other at about 0.2 us, which is what the pass takes where candidates are many and queries
+// few.  HOLD keeps the candidates of a tile in LDS and updates a counter once per tile (rows without clusters, 1M x
+// 128, inner product, 100 queries of 64 probes, k = 100, up to 1172 candidates a query: 203 -> 104 us); what does not fit is
+// appended at once.  It is left out where its registers would spill (the 96-wide panel at three wavefronts per SIMD).
+template <int DP, int B, int NQ, int WAVES, int OCC, int S, bool RAW, bool HOLD>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(OCC)))
 void k_batch_threshold(BatchScanArgs a) {
     using Cfg = BatchCfg<DP, B, NQ>;
     constexpr int KB = DP / 16, NT = WAVES * 64, VB = 32 * S;      // vectors of a block
+    constexpr int CAND = Cfg::held_back(OCC);
     constexpr int NW = (B == 2 || B == 4) ? 1 : 2;
     extern __shared__ unsigned char lds_raw[];
     uint16_t* zh = reinterpret_cast<uint16_t*>(lds_raw);                       // [TQ][LDH] hi parts of the rotated queries
     uint4* s_row = reinterpret_cast<uint4*>(zh + Cfg::TQ * Cfg::LDH);          // [TQ] coarse term, threshold, pair number, |q|
     uint32_t* tab = reinterpret_cast<uint32_t*>(s_row + Cfg::TQ);                // [PT] hi parts of a code pair, packed (or of one code)
+    uint2* s_cand = reinterpret_cast<uint2*>(tab + Cfg::PT);                     // HOLD: [CAND] score bits; column | vector of the part << 7 | place among the column's << 19
+    int* s_cnt = reinterpret_cast<int*>(s_cand + CAND);                          // HOLD: [TQ] held back per column, then their first position
+    static_assert(Cfg::TQ <= 128 && kPartMax <= 4096, "fields of a candidate held back");
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, jl = lane & 31;
@@ -326,10 +343,34 @@ void k_batch_threshold(BatchScanArgs a) {
     }
     const uint16_t* bh_base = zh + jl * Cfg::LDH + 8 * half;
     const int words = a.store.words;
-    __shared__ __align__(16) int s_next[4];      // (16 bytes: the panel behind it keeps its alignment)
+    __shared__ __align__(16) int s_next[4];      // (16 bytes: the panel behind it keeps its alignment) [2] asked for, [3] held back if that is too many
     TileQueue queue(a, s_next);
-    for (int tile; (tile = queue.take()) < queue.end;) {
-    BatchTile t;
+    if (HOLD && tid < Cfg::TQ) s_cnt[tid] = 0;
+    if (HOLD && tid == 0) { s_next[2] = 0; s_next[3] = CAND; }
+    BatchTile t{};
+    for (;;) {
+    const int tile = queue.take();
+    if (HOLD && s_next[2] > 0) {                 // what the tile before held back, whose queries are still there
+        const int held = s_next[2] <= CAND ? s_next[2] : s_next[3];      // (once one did not fit, none after it did)
+        int me = threadIdx.x;
+        asm volatile("" : "+v"(me));             // or what follows from it is computed ahead of the tiles and kept
+        if (me < Cfg::TQ && s_cnt[me] > 0) s_cnt[me] = atomicAdd(&a.cand_cnt[(int32_t)s_row[me].z / a.np], s_cnt[me]);
+        __syncthreads();
+        for (int i = me; i < held; i += NT) {
+            const uint2 c = s_cand[i];
+            const int e = (int)(c.y & 127u);
+            const int32_t it = (int32_t)s_row[e].z, q = it / a.np;
+            const int pos = s_cnt[e] + (int)(c.y >> 19);
+            if (pos < a.cap) {
+                a.cand_score[(int64_t)q * a.cap + pos] = __uint_as_float(c.x);
+                a.cand_slot[(int64_t)q * a.cap + pos] = (t.base_slot + t.v_lo + (int)((c.y >> 7) & 4095u)) | (int64_t)(it - q * a.np) << kCandProbeShift;
+            }
+        }
+        __syncthreads();
+        if (me < Cfg::TQ) s_cnt[me] = 0;
+        if (me == 0) { s_next[2] = 0; s_next[3] = CAND; }
+    }
+    if (tile >= queue.end) break;
     t.find(a, tile, Cfg::TQ);
     const int v_lo = t.v_lo, v_hi = t.v_hi, nblk = (v_hi - v_lo + VB - 1) / VB, n_qt = (t.nq_tile + 31) / 32;
 
@@ -344,7 +385,6 @@ void k_batch_threshold(BatchScanArgs a) {
         for (int s = 0; s < S; ++s) fetch_words<KB, B, NW>(at + 32 * s, words, half, cw[s]);
     };
     if (blk < nblk) fetch(blk);
-
     // (columns beyond the tile's queries: a NaN threshold, which not even an infinite score reaches)
     stage_queries<DP, Cfg::TQ, NT, false>(a, t, zh, nullptr, s_row, make_uint4(0, 0x7FC00000u, 0, 0), [&](int32_t it) {
         const int32_t q = it / a.np;
@@ -453,24 +493,38 @@ void k_batch_threshold(BatchScanArgs a) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) hit |= key_of(r) >= th ? 1u << r : 0u;
                 if (hit) {
-                    const int32_t q = (int32_t)row.z / a.np;
-                    const int64_t rank = (int64_t)((int32_t)row.z - q * a.np) << kCandProbeShift;
                     const int n_hit = (int)__popc(hit);
-                    const int pos = atomicAdd(&a.cand_cnt[q], n_hit);
-                    const int room = a.cap - pos;
-                    float* to_score = a.cand_score + (int64_t)q * a.cap + pos;
-                    int64_t* to_slot = a.cand_slot + (int64_t)q * a.cap + pos;
-                    const int64_t slot0 = (t.base_slot + v0) | rank;       // adding to the slot stays below the rank
-                    int at = 0;
+                    int held = CAND;
+                    if (HOLD) held = atomicAdd(&s_next[2], n_hit);
+                    if (HOLD && held + n_hit <= CAND) {
+                        const int e = qt * 32 + jl;
+                        uint32_t word = (uint32_t)(e | (v0 - v_lo) << 7) + ((uint32_t)atomicAdd(&s_cnt[e], n_hit) << 19);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if ((hit >> r) & 1u) {
-                            if (at < room) {
-                                to_score[at] = key_of(r);
-                                to_slot[at] = slot0 + 8 * (r / 4) + (r % 4);
+                        for (int r = 0; r < 16; ++r)
+                            if ((hit >> r) & 1u) {
+                                s_cand[held++] = make_uint2(__float_as_uint(key_of(r)), word + ((uint32_t)(8 * (r / 4) + (r % 4)) << 7));
+                                word += 1u << 19;
                             }
-                            ++at;
-                        }
+                    } else {
+                        if (HOLD) atomicMin(&s_next[3], held);
+                        const int32_t q = (int32_t)row.z / a.np;
+                        const int64_t rank = (int64_t)((int32_t)row.z - q * a.np) << kCandProbeShift;
+                        const int pos = atomicAdd(&a.cand_cnt[q], n_hit);
+                        const int room = a.cap - pos;
+                        float* to_score = a.cand_score + (int64_t)q * a.cap + pos;
+                        int64_t* to_slot = a.cand_slot + (int64_t)q * a.cap + pos;
+                        const int64_t slot0 = (t.base_slot + v0) | rank;       // adding to the slot stays below the rank
+                        int at = 0;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if ((hit >> r) & 1u) {
+                                if (at < room) {
+                                    to_score[at] = key_of(r);
+                                    to_slot[at] = slot0 + 8 * (r / 4) + (r % 4);
+                                }
+                                ++at;
+                            }
+                    }
                 }
             }
         };
@@ -516,14 +570,17 @@ hipError_t run_batch(const BatchScanArgs& a, hipStream_t st) {
     } else {
         static ChipFill fill_t[2];
         constexpr int NQ = kBatchTile / 32;
-        constexpr size_t lds = BatchCfg<DP, B, NQ>::lds_threshold;
         // two row tiles and wavefronts per SIMD where the registers (operands of both tiles, and the words of the
         // next block, twice or four times as many where codes straddle words or are bytes) allow it without spills
         constexpr int words = B == 8 ? DP / 4 : (B == 3 || B == 5) ? DP / 8 : DP / 16;
         constexpr int S = DP + 2 * words <= 256 ? 2 : 1, S_RAW = DP + 2 * words < 200 ? 2 : 1;
         constexpr int OCC = S == 2 && DP + words <= 102 ? 3 : 2;
-        constexpr auto plain = k_batch_threshold<DP, B, NQ, 4, OCC, S, false>;
-        constexpr auto raw = k_batch_threshold<DP, B, NQ, 4, 2, S_RAW, true>;
+        constexpr bool HOLD = OCC == 2 || DP <= 64;
+        using Cfg = BatchCfg<DP, B, NQ>;
+        constexpr size_t lds_plain = HOLD ? Cfg::lds_held_back(OCC) : Cfg::lds_threshold, lds_raw = Cfg::lds_held_back(2);
+        constexpr auto plain = k_batch_threshold<DP, B, NQ, 4, OCC, S, false, HOLD>;
+        constexpr auto raw = k_batch_threshold<DP, B, NQ, 4, 2, S_RAW, true, true>;
+        const size_t lds = a.metric ? lds_raw : lds_plain;
         unsigned wgs = 0;
         const hipError_t e = a.metric ? fill_t[1].get(reinterpret_cast<const void*>(raw), 256, lds, &wgs) : fill_t[0].get(reinterpret_cast<const void*>(plain), 256, lds, &wgs);
         if (e != hipSuccess) return e;

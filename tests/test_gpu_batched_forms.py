@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
 SIZES = [0, 1, 31, 64, 65, 0, 127, 511, 512, 513, 577, 1025, 2500, 64 * 33, 900, 3]
 FORMS = [(32, 4, "cosine", 1), (50, 2, "l2", 10), (64, 3, "ip", 33), (96, 4, "l2", 10), (100, 5, "cosine", 100), (128, 8, "cosine", 10),
          (129, 4, "ip", 7), (161, 5, "l2", 20), (200, 3, "cosine", 64), (208, 8, "ip", 10), (224, 2, "cosine", 100), (255, 8, "l2", 65), (256, 5, "ip", 20),
-         (96, 4, "l2", 300), (100, 4, "ip", 500), (64, 8, "cosine", 300)]
+         (96, 4, "l2", 300), (100, 4, "ip", 500), (64, 8, "cosine", 300),
+         # (a tile holds candidates back in LDS: at most 4096 at d = 64, about 900 at d = 256 with 5 bits, and these have more)
+         (64, 4, "l2", 600), (256, 5, "ip", 600)]
 
 
 def _index(d, b, metric, rng):
