@@ -265,7 +265,7 @@ ivftq_status ivftq_export_list(const ivftq_index* index, int list, int64_t* ids_
  * metric 4 more per vector). */
 int64_t ivftq_index_bytes(const ivftq_index* index);
 /* Scan strategy of ivftq_search: 0 = default (the query-batched matrix-core scan when (d, b) is one
- * of its instantiated shapes, nprobe > 1 and the call is large enough for it to pay: the bytes a
+ * of its shapes -- d >= 16 with 3, 4, 5 or 8 stored bits, d > 32 with 2 --, nprobe > 1 and the call is large enough for it to pay: the bytes a
  * per-query stream of the probed lists would read exceed 2.3 times the part of the index the call
  * touches plus 0.25 GB, a few hundred queries on a 10M-vector index; else the streaming scan, whose
  * shorter chain of kernels is faster for smaller calls), 1 = streaming scan only (a row of workgroups
@@ -280,8 +280,8 @@ ivftq_status ivftq_set_search_mode(ivftq_index* index, int mode);
  * between cosine and a raw metric needs an empty index (BAD_STATE otherwise); between IP and L2 it
  * is free.  With a raw metric: ivftq_encode_add stores |x| too, encoded vectors are appended with
  * ivftq_add_encoded_raw, ivftq_search returns metric values (L2: smallest first, missing results
- * +infinity) from the streaming scan, and ivftq_search_cascade, ivftq_reencode and
- * ivftq_refresh_coarse return IVFTQ_UNSUPPORTED. */
+ * +infinity) from either scan under the same rule as cosine (ivftq_set_search_mode), and
+ * ivftq_search_cascade, ivftq_reencode and ivftq_refresh_coarse return IVFTQ_UNSUPPORTED. */
 ivftq_status ivftq_set_metric(ivftq_index* index, int metric);
 /* ivftq_add_encoded for an index with a raw metric: xnorm_dev holds n float32 norms |x| (device). */
 ivftq_status ivftq_add_encoded_raw(ivftq_index* index, int64_t n, const int32_t* assign_dev,

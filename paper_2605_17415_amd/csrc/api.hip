@@ -1360,10 +1360,13 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     // threshold from each query's nearest lists.  The streaming scan's time follows the bytes it reads, once
     // per query; the batched path reads a list once per 128 queries, so its time follows the part of the
     // index the call touches, but it is a chain of about twelve kernels with a fixed cost of its own.
-    // Batched when the streamed bytes exceed kBatchedGain times the touched bytes plus kBatchedFixedBytes
-    // (measured crossovers with nprobe 32 / 32 / 64 at 1M x 128, 10M x 96, 10M x 200: about 200, 380 and
-    // 170 queries, i.e. 0.41 / 1.5 / 2.7 GB streamed against an index of 0.066 / 0.58 / 1.04 GB).  Mode 2
-    // asks for the batched path whatever the size of the call.
+    // Batched when the streamed bytes exceed kBatchedGain times the touched bytes plus kBatchedFixedBytes.  The
+    // constants are those of an earlier batched path (crossovers with nprobe 32 / 32 / 64 at 1M x 128, 10M x 96,
+    // 10M x 200 then: about 200, 380 and 170 queries).  On clustered rows the present one overtakes the streaming scan
+    // sooner, at about 130, 180 and 25 queries, so that calls in between take up to 1.3 times as long as they could (a
+    // length of a raw metric, 4 bytes a vector, is not counted either); on rows without clusters the line lies too
+    // low instead (1M x 128, 64 probes, k = 100: 100 queries 263 us batched, 171 streamed; even at 250).  Mode 2 asks
+    // for the batched path whatever the size of the call.
     constexpr double kBatchedGain = 2.3, kBatchedFixedBytes = 0.25e9;
     const int metric = ix->metric;
     const double vec_bytes = (double)codes_store.words * 4 + 2;

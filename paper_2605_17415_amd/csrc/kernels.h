@@ -384,7 +384,7 @@ constexpr int kCandProbeShift = 48;      // a candidate's probe rank sits above 
 inline float screen_kappa(int d, float cmax) { return (0x1p-10f + 0x1p-16f) * 1.002f * sqrtf((float)d) * cmax; }
 
 struct MergeArgs {
-    const float* first_scores; const int64_t* first_ids;     // [nq][k] from the streaming pass (exact scores)
+    const float* first_scores; const int64_t* first_ids;     // [nq][k] from the dense pass (float32-accurate scores)
     // candidates of the threshold pass: upper bounds u of the score (true score in [u - 2*kappa*gamma, u])
     const float* cand_score; const int64_t* cand_slot; const int32_t* cand_cnt; int cap;
     float kappa;
