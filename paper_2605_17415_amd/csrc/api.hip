@@ -97,11 +97,11 @@ struct PinnedBuf {
 };
 
 // kernel classes for the optional per-launch timing
-enum ProfId { P_ASSIGN, P_COARSE_SCORES, P_ENCODE, P_ROTATE_Q, P_SEG_HIST, P_SEG_SCAN, P_RANK, P_PACK,
+enum ProfId { P_ASSIGN, P_COARSE_SCORES, P_ENCODE, P_SEG_HIST, P_SEG_SCAN, P_RANK, P_PACK,
               P_COPY_LISTS, P_SELECT_PROBE, P_LIST_SCAN, P_SELECT_TOPK, P_KMEANS_UPDATE, P_KMEANS_SUMS,
               P_PAIR_GROUP, P_BATCH_FIRST, P_BATCH_SCAN, P_MERGE, P_CASCADE, P_COUNT };
 const char* const kProfNames[P_COUNT] = {"coarse_assign", "coarse_scores", "encode_rotate_quantise_pack",
-                                         "rotate_queries", "segment_hist", "segment_scan", "stable_rank",
+                                         "segment_hist", "segment_scan", "stable_rank",
                                          "pack_scatter", "copy_lists", "select_probes",
                                          "list_scan", "select_topk", "kmeans_update", "kmeans_cell_sums", "pair_grouping",
                                          "batch_scan_nearest", "batch_scan", "merge_topk", "cascade_rescore"};
@@ -1282,12 +1282,25 @@ ivftq_status check_query_args(const ivftq_index* ix, const float* q_dev, int64_t
     return IVFTQ_OK;
 }
 
-// coarse scores for `count` queries starting at q, then the nprobe best cells of each and, with `cand`, what follows from them
-ivftq_status coarse_and_probe(ivftq_index* ix, const float* q, int64_t count, int nprobe, int32_t* probe,
-                              float* coarse, const CandOffsetArgs* cand, hipStream_t st) {
+// Where the rotated queries of a call go: float32, in split float16 form, and their lengths (the last three optional).
+struct RotatedQueries {
+    float* z; uint16_t* zh; uint16_t* zl; float* norm;
+};
+
+// coarse scores for `count` queries starting at q and, with `rot`, the rotated queries, then the nprobe best cells of each
+// and, with `cand`, what follows from them
+ivftq_status coarse_and_probe(ivftq_index* ix, const float* q, int64_t count, int nprobe, int32_t* probe, float* coarse,
+                              const RotatedQueries* rot, const CandOffsetArgs* cand, hipStream_t st) {
     const int64_t ldS = round_up(ix->nlist, 4);
-    HIP_TRY(timed(ix, st, P_COARSE_SCORES, [&] { return launch_coarse(q, count, ix->d, ix->cent_h.as<uint16_t>(), ix->cent_l.as<uint16_t>(), ix->dp,
-                                                                           ix->lpad, ix->w_S.as<float>(), ldS, st); }));
+    CoarseArgs ca{};
+    ca.x = q; ca.n = count; ca.d = ix->d;
+    ca.cent_h = ix->cent_h.as<uint16_t>(); ca.cent_l = ix->cent_l.as<uint16_t>(); ca.pitch = ix->dp; ca.Lpad = ix->lpad;
+    ca.scores = ix->w_S.as<float>(); ca.ld_scores = ldS;
+    if (rot) {
+        ca.pi_h = ix->pi_h.as<uint16_t>(); ca.pi_l = ix->pi_l.as<uint16_t>();
+        ca.z_out = rot->z; ca.zh_out = rot->zh; ca.zl_out = rot->zl; ca.norm_out = rot->norm;
+    }
+    HIP_TRY(timed(ix, st, P_COARSE_SCORES, [&] { return launch_coarse(ca, st); }));
     SelectArgs sa{};
     sa.vals = ix->w_S.as<float>(); sa.stride = ldS; sa.rows = count; sa.k = nprobe; sa.m_fixed = ix->nlist;
     sa.out_vals = coarse; sa.out_i32 = probe;
@@ -1323,7 +1336,7 @@ ivftq_status ivftq_coarse_probe(ivftq_index* ix, const float* q_dev, int64_t nq,
     for (int64_t q0 = 0; q0 < nq; q0 += qc) {
         const int64_t cnt = std::min(qc, nq - q0);
         s = coarse_and_probe(ix, q_dev + q0 * ix->d, cnt, nprobe, probe_dev ? probe_dev + q0 * nprobe : nullptr,
-                             coarse_dev ? coarse_dev + q0 * nprobe : nullptr, nullptr, st);
+                             coarse_dev ? coarse_dev + q0 * nprobe : nullptr, nullptr, nullptr, st);
         if (s != IVFTQ_OK) return s;
     }
     return IVFTQ_OK;
@@ -1434,14 +1447,12 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             co.first = first; co.cand_cnt = ix->w_ccnt.as<int32_t>(); co.gate = ix->w_gate.as<int32_t>(); co.redo_cnt = redo_cnt;
             co.bucket_cnt = ix->w_count.as<uint32_t>(); co.buckets = buckets + 8;
         }
-        s = coarse_and_probe(ix, q, cnt, nprobe, ix->w_probe.as<int32_t>(), ix->w_coarse.as<float>(), &co, st);
+        RotatedQueries rq{};
+        rq.z = ix->w_z.as<float>();
+        if (batched) { rq.zh = ix->w_zh.as<uint16_t>(); rq.zl = ix->w_zl.as<uint16_t>(); }
+        if (metric) rq.norm = ix->w_qnorm.as<float>();
+        s = coarse_and_probe(ix, q, cnt, nprobe, ix->w_probe.as<int32_t>(), ix->w_coarse.as<float>(), &rq, &co, st);
         if (s != IVFTQ_OK) return s;
-        EncodeArgs ea{};
-        ea.x = q; ea.n = cnt; ea.d = ix->d; ea.b = ix->b;
-        ea.pi_h = ix->pi_h.as<uint16_t>(); ea.pi_l = ix->pi_l.as<uint16_t>(); ea.zout = ix->w_z.as<float>();
-        if (batched) { ea.zh_out = ix->w_zh.as<uint16_t>(); ea.zl_out = ix->w_zl.as<uint16_t>(); }
-        if (metric) ea.norm_out = ix->w_qnorm.as<float>();
-        HIP_TRY(timed(ix, st, P_ROTATE_Q, [&] { return launch_encode(2, ea, st); }));
         ListScanArgs la{};
         la.z = ix->w_z.as<float>(); la.z_pitch = ix->dp; la.d = ix->d; la.cb = cb;
         la.probe = ix->w_probe.as<int32_t>(); la.coarse = ix->w_coarse.as<float>();
@@ -1624,14 +1635,12 @@ ivftq_status ivftq_search_cascade(ivftq_index* ix, const float* q_dev, int64_t n
     HIP_TRY(ix->w_S.ensure((size_t)qc * ldS * sizeof(float)));
     for (int64_t q0 = 0; q0 < nq; q0 += qc) {
         const int64_t cnt = std::min(qc, nq - q0);
+        RotatedQueries rq{};
+        rq.z = ix->w_z.as<float>() + q0 * ix->dp;
         s = coarse_and_probe(ix, q_dev + q0 * ix->d, cnt, nprobe, ix->w_probe.as<int32_t>() + q0 * nprobe,
-                             ix->w_coarse.as<float>() + q0 * nprobe, nullptr, st);
+                             ix->w_coarse.as<float>() + q0 * nprobe, &rq, nullptr, st);
         if (s != IVFTQ_OK) return s;
     }
-    EncodeArgs ea{};
-    ea.x = q_dev; ea.n = nq; ea.d = ix->d; ea.b = ix->b;
-    ea.pi_h = ix->pi_h.as<uint16_t>(); ea.pi_l = ix->pi_l.as<uint16_t>(); ea.zout = ix->w_z.as<float>();
-    HIP_TRY(timed(ix, st, P_ROTATE_Q, [&] { return launch_encode(2, ea, st); }));
     CascadeArgs ca{};
     ca.z = ix->w_z.as<float>(); ca.z_pitch = ix->dp; ca.d = ix->d; ca.b = ix->b;
     ca.cb = ix->cb.as<float>();

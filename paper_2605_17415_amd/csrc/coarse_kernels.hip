@@ -29,6 +29,9 @@ struct CoarseCfg {
     static constexpr size_t lds_bytes = (size_t)2 * kTN * LDH * sizeof(uint16_t);
 };
 
+// stages of a call of k_coarse: the centroid table's, then those of Pi
+__host__ __device__ constexpr int coarse_stages(const CoarseArgs& a) { return a.Lpad / kTN + (a.pi_h ? (a.pitch + kTN - 1) / kTN : 0); }
+
 // hi[r][c], lo[r][c] = split float16 form of src[r][c]
 __global__ void k_split_rows(const float* __restrict__ src, int64_t count, uint16_t* __restrict__ hi,
                              uint16_t* __restrict__ lo) {
@@ -51,16 +54,17 @@ __global__ void k_split_transposed(const float* __restrict__ src, int n, uint16_
 }
 
 // One 32-row tile of normalised data rows as the B operand (split form).  Returns whether the
-// row's norm is usable.
+// row's norm is usable; norm (may be null) receives it, 0 for one that is not.
 template <int DP>
 __device__ __forceinline__ bool load_rows(const float* __restrict__ x, int64_t row, bool valid, int d, int vec4,
-                                          int half, half8 (&bh)[DP / 16], half8 (&bl)[DP / 16]) {
+                                          int half, half8 (&bh)[DP / 16], half8 (&bl)[DP / 16], float* norm = nullptr) {
     constexpr int KB = DP / 16;
     float v[KB][8];
     load_row_blocks<KB>(x + (valid ? row : 0) * (int64_t)d, valid, d, vec4, half, v);
     const float n2 = row_norm2<KB>(v);
     const bool good = (n2 > 0.f) && (n2 < __builtin_inff());
     const float inv = good ? 1.f / sqrtf(n2) : 0.f;     // one division per row, then multiplies
+    if (norm) *norm = good ? sqrtf(n2) : 0.f;
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -73,43 +77,50 @@ __device__ __forceinline__ bool load_rows(const float* __restrict__ x, int64_t r
     return good;
 }
 
+// Scores of every row against every centroid and, with a.pi_h, the rotated rows: to this kernel Pi is a few more
+// stages of 64 table rows whose products are stored elsewhere.  (A launch of its own for the rotation cost every search
+// 5 us, and 12 to 28 us from 256 queries on, where each of its few workgroups walked all of Pi by itself.)
+// Workgroup (x, y) takes the row block x and the stages [y * per_y, y * per_y + per_y) of both tables together.
 // R = 32-row tiles per wavefront.  VEC4: rows are read 16 bytes at a time (d % 4 == 0, x 16-byte aligned).
 template <int DP, int R, bool VEC4>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_coarse(
-    const float* __restrict__ x, int64_t n, int d, const uint16_t* __restrict__ cent_h,
-    const uint16_t* __restrict__ cent_l, int cent_pitch, int Lpad, float* __restrict__ scores, int64_t ld_scores) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_coarse(CoarseArgs a, int per_y) {
     using Cfg = CoarseCfg<DP>;
     constexpr int KB = Cfg::KB;
     extern __shared__ unsigned char lds_raw[];
-    uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [TN][LDH] hi parts of the centroid tile
+    uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [TN][LDH] hi parts of the table's rows
     uint16_t* tl = th + kTN * Cfg::LDH;                               // [TN][LDH] lo parts
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, j = lane & 31;
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (32 * R);
+    const int cent_stages = a.Lpad / kTN, stages = coarse_stages(a);
+    const int s_lo = (int)blockIdx.y * per_y, s_hi = s_lo + per_y < stages ? s_lo + per_y : stages;
 
     half8 bh[R][KB], bl[R][KB];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t row = row0 + 32 * r + j;
-        load_rows<DP>(x, row, row < n, d, VEC4 ? 1 : 0, half, bh[r], bl[r]);
+        float norm;
+        load_rows<DP>(a.x, row, row < a.n, a.d, VEC4 ? 1 : 0, half, bh[r], bl[r], &norm);
+        if (a.norm_out && s_lo == 0 && half == 0 && row < a.n) a.norm_out[row] = norm;
     }
     const uint16_t* ah_base = th + j * Cfg::LDH + 8 * half;
     const uint16_t* al_base = tl + j * Cfg::LDH + 8 * half;
     constexpr float kUnscale = 1.f / (kSplitScale * kSplitScale);
 
-    // gridDim.y workgroups share the centroid stages of one row block (few rows)
-    const int stages = Lpad / kTN, per_y = (stages + (int)gridDim.y - 1) / (int)gridDim.y;
-    const int c_lo = (int)blockIdx.y * per_y * kTN;
-    const int c_hi = c_lo + per_y * kTN < Lpad ? c_lo + per_y * kTN : Lpad;
-    for (int c0 = c_lo; c0 < c_hi; c0 += kTN) {
+    for (int s = s_lo; s < s_hi; ++s) {
+        const bool rotate = s >= cent_stages;
+        const int c0 = (rotate ? s - cent_stages : s) * kTN;
+        const uint16_t* src_h = rotate ? a.pi_h : a.cent_h;
+        const uint16_t* src_l = rotate ? a.pi_l : a.cent_l;
+        const int last = (rotate ? a.pitch : a.Lpad) - 1;            // Pi has `pitch` rows, not a whole number of stages
         __syncthreads();
-        // stage TN centroid rows (hi and lo) into LDS, 16 bytes at a time
+        // stage TN rows of the table (hi and lo) into LDS, 16 bytes at a time
         for (int e = tid; e < kTN * (DP / 8); e += 256) {
             const int r = e / (DP / 8), c8 = e % (DP / 8);
-            const int64_t src = (int64_t)(c0 + r) * cent_pitch + c8 * 8;
-            *reinterpret_cast<uint4*>(th + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(cent_h + src);
-            *reinterpret_cast<uint4*>(tl + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(cent_l + src);
+            const int64_t src = (int64_t)(c0 + r < last ? c0 + r : last) * a.pitch + c8 * 8;
+            *reinterpret_cast<uint4*>(th + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(src_h + src);
+            *reinterpret_cast<uint4*>(tl + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(src_l + src);
         }
         __syncthreads();
 
@@ -138,16 +149,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int64_t row = row0 + 32 * r + j;
-            if (row >= n) continue;
+            if (row >= a.n) continue;
 #pragma unroll
             for (int t = 0; t < kNT; ++t)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int c = c0 + t * 32 + 8 * g + 4 * half;
-                    if (c < ld_scores) {
-                        float4 o = make_float4(acc[r][t][4 * g] * kUnscale, acc[r][t][4 * g + 1] * kUnscale,
-                                               acc[r][t][4 * g + 2] * kUnscale, acc[r][t][4 * g + 3] * kUnscale);
-                        *reinterpret_cast<float4*>(scores + row * ld_scores + c) = o;
+                    const float4 o = make_float4(acc[r][t][4 * g] * kUnscale, acc[r][t][4 * g + 1] * kUnscale,
+                                                 acc[r][t][4 * g + 2] * kUnscale, acc[r][t][4 * g + 3] * kUnscale);
+                    if (!rotate) {
+                        if (c < a.ld_scores) *reinterpret_cast<float4*>(a.scores + row * a.ld_scores + c) = o;
+                    } else if (c < a.pitch) {
+                        const int64_t at = row * a.pitch + c;
+                        *reinterpret_cast<float4*>(a.z_out + at) = o;
+                        if (a.zh_out) {
+                            const float z[4] = {o.x, o.y, o.z, o.w};
+                            uint16_t h[4], l[4];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                _Float16 hi, lo;
+                                split_scaled(z[e], hi, lo);
+                                h[e] = __builtin_bit_cast(uint16_t, hi);
+                                l[e] = __builtin_bit_cast(uint16_t, lo);
+                            }
+                            *reinterpret_cast<uint2*>(a.zh_out + at) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+                            *reinterpret_cast<uint2*>(a.zl_out + at) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
+                        }
                     }
                 }
         }
@@ -517,28 +544,33 @@ hipError_t run_screened(const ScreenArgs& a, hipStream_t st) {
     return vec4 ? run_screened_as<DP, RS, true, false>(a, st) : run_screened_as<DP, RS, false, false>(a, st);
 }
 
-template <int DP, int R>
-hipError_t run(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l, int cent_pitch, int Lpad,
-               float* scores, int64_t ld_scores, hipStream_t st) {
-    static LdsLimit lim[2];
-    const size_t lds = CoarseCfg<DP>::lds_bytes;
-    const int64_t rows_per_wg = 4 * 32 * R;
-    const int64_t blocks = (n + rows_per_wg - 1) / rows_per_wg;
-    const int vec4 = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(x) % 16 == 0);
-    const hipError_t e = vec4 ? lim[1].ensure(reinterpret_cast<const void*>(k_coarse<DP, R, true>), lds)
-                              : lim[0].ensure(reinterpret_cast<const void*>(k_coarse<DP, R, false>), lds);
+template <int DP, int R, bool VEC4>
+hipError_t run_as(const CoarseArgs& a, hipStream_t st) {
+    static ChipFill fill;
+    constexpr size_t lds = CoarseCfg<DP>::lds_bytes;
+    unsigned held = 0;
+    const hipError_t e = fill.get(reinterpret_cast<const void*>(k_coarse<DP, R, VEC4>), 256, lds, &held);
     if (e != hipSuccess) return e;
-    // every (row, centroid) result is independent, so when the rows alone do not fill the chip the
-    // centroid stages are split over gridDim.y as well
-    int ysplit = 1;
-    while (blocks * ysplit < 512 && ysplit * 2 <= Lpad / kTN) ysplit *= 2;
-    if (vec4)
-        hipLaunchKernelGGL((k_coarse<DP, R, true>), dim3((unsigned)blocks, (unsigned)ysplit), dim3(256), lds, st, x, n, d,
-                           cent_h, cent_l, cent_pitch, Lpad, scores, ld_scores);
-    else
-        hipLaunchKernelGGL((k_coarse<DP, R, false>), dim3((unsigned)blocks, (unsigned)ysplit), dim3(256), lds, st, x, n, d,
-                           cent_h, cent_l, cent_pitch, Lpad, scores, ld_scores);
+    const int64_t blocks = (a.n + 4 * 32 * R - 1) / (4 * 32 * R);
+    // Every (row, table row) result is independent, so the stages of a row block can be shared out as one likes.  A
+    // workgroup of s stages takes about s + 1 stage times (its rows are read, normalised and split first), and
+    // the launch as many rounds of them as it has workgroups for the places on the chip: the split with the fewest stage
+    // times in all, the finer one of equals.
+    const int stages = coarse_stages(a);
+    int per_y = 1;
+    int64_t least = INT64_MAX;
+    for (int s = 1; s <= stages; ++s) {
+        const int64_t wgs = blocks * ((stages + s - 1) / s), cost = (wgs + held - 1) / held * (s + 1);
+        if (cost < least) { least = cost; per_y = s; }
+    }
+    hipLaunchKernelGGL((k_coarse<DP, R, VEC4>), dim3((unsigned)blocks, (unsigned)((stages + per_y - 1) / per_y)), dim3(256), lds, st, a, per_y);
     return hipGetLastError();
+}
+
+template <int DP, int R>
+hipError_t run(const CoarseArgs& a, hipStream_t st) {
+    const bool vec4 = (a.d % 4 == 0) && (reinterpret_cast<uintptr_t>(a.x) % 16 == 0);
+    return vec4 ? run_as<DP, R, true>(a, st) : run_as<DP, R, false>(a, st);
 }
 
 // Calibration of the float16 matrix pipe: nothing but v_mfma_f32_32x32x16_f16 on operands held in
@@ -608,12 +640,11 @@ hipError_t launch_coarse_screened(const ScreenArgs& a, hipStream_t st) {
     }
 }
 
-hipError_t launch_coarse(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l, int cent_pitch,
-                         int Lpad, float* scores, int64_t ld_scores, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    switch (coarse_dp(d)) {
+hipError_t launch_coarse(const CoarseArgs& a, hipStream_t st) {
+    if (a.n <= 0) return hipSuccess;
+    switch (coarse_dp(a.d)) {
 #define IVFTQ_CASE(DPV, RV) \
-    case DPV: return run<DPV, RV>(x, n, d, cent_h, cent_l, cent_pitch, Lpad, scores, ld_scores, st);
+    case DPV: return run<DPV, RV>(a, st);
         IVFTQ_CASE(32, 2) IVFTQ_CASE(64, 2) IVFTQ_CASE(96, 2) IVFTQ_CASE(128, 2) IVFTQ_CASE(160, 1)
         IVFTQ_CASE(192, 1) IVFTQ_CASE(208, 1) IVFTQ_CASE(224, 1) IVFTQ_CASE(256, 1)
 #undef IVFTQ_CASE

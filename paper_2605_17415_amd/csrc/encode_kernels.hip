@@ -1,7 +1,6 @@
 // Residual rotation, Lloyd-Max quantisation and bit-packing in one kernel (Section "Architecture",
 // Indexing: r = x~ - c~_l, rotate by Pi, normalise Pi r, quantise each coordinate; Bit accounting:
-// b*d code bits and a float16 norm per vector), plus the query-side rotation z = Pi q~ (Section
-// "Architecture", Search).
+// b*d code bits and a float16 norm per vector).
 //
 // The rotation is a d x d contraction on the matrix cores (v_mfma_f32_32x32x16_f16 on split float16
 // operands with float32 accumulation, see split_f16.h).  A wavefront owns 32*R rows; their unit
@@ -50,13 +49,13 @@ inline int pack_pitch(int words) { return (words + 1) | 1; }   // odd and > word
 template <int DP>
 size_t encode_lds_bytes(int mode, int pack_b, int cells, int words, int head_words) {
     size_t bytes = EncCfg<DP>::pi_bytes;
-    if (mode != 2) bytes += (size_t)cells * 8;
+    bytes += (size_t)cells * 8;
     if (mode == 0 && pack_b == 0) bytes += (size_t)4 * 32 * EncCfg<DP>::R * pack_pitch(words) * 4;
     if (mode == 0 && pack_b == 0 && head_words > 0) bytes += (size_t)4 * 32 * EncCfg<DP>::R * pack_pitch(head_words) * 4;
     return bytes;
 }
 
-// MODE 0: encode and store into the lists; 1: encode into flat arrays; 2: rotate queries only.  A template
+// MODE 0: encode and store into the lists; 1: encode into flat arrays.  A template
 // parameter, so that each instantiation carries its own path only.  PACK_B (mode 0): 4 or 8 = the index
 // stores that many bits per coordinate and no plane of top bits, words are put together in registers;
 // 0 = any b, through LDS.
@@ -110,24 +109,19 @@ void k_encode(EncodeArgs a, int flags) {
         const float n2 = row_norm2<KB>(v);
         const bool good = (n2 > 0.f) && (n2 < __builtin_inff());
         const float inv_n = good ? 1.f / sqrtf(n2) : 0.f;   // one division per row, then multiplies
-        gamma[r] = 0.f;
         xnorm[r] = good ? sqrtf(n2) : 0.f;
-        if (mode == 2 && a.norm_out && valid[r] && half == 0) a.norm_out[row_of[r]] = xnorm[r];
-        float to_unit = inv_n;
-        if (mode != 2) {
-            const int cell = cell_of[r];
-            float c[KB][8];
-            load_row_blocks<KB>(a.cent + (int64_t)(cell < 0 ? 0 : cell) * a.cent_pitch, true, DP, 1, half, c);
+        const int cell = cell_of[r];
+        float c[KB][8];
+        load_row_blocks<KB>(a.cent + (int64_t)(cell < 0 ? 0 : cell) * a.cent_pitch, true, DP, 1, half, c);
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[kb][e] = fmaf(v[kb][e], inv_n, -c[kb][e]);      // r = x~ - c~
-            const float g = sqrtf(row_norm2<KB>(v));
-            // The rotation acts on the unit residual: the quantiser input does not depend on the scale
-            // of r, and a unit vector keeps the split float16 form accurate however small r is.
-            to_unit = (g > 1e-30f) ? 1.f / g : 0.f;   // a zero residual quantises as rho = 0
-            gamma[r] = cell >= 0 ? g : 0.f;
-        }
+            for (int e = 0; e < 8; ++e) v[kb][e] = fmaf(v[kb][e], inv_n, -c[kb][e]);      // r = x~ - c~
+        const float g = sqrtf(row_norm2<KB>(v));
+        // The rotation acts on the unit residual: the quantiser input does not depend on the scale
+        // of r, and a unit vector keeps the split float16 form accurate however small r is.
+        const float to_unit = (g > 1e-30f) ? 1.f / g : 0.f;   // a zero residual quantises as rho = 0
+        gamma[r] = cell >= 0 ? g : 0.f;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -144,11 +138,10 @@ void k_encode(EncodeArgs a, int flags) {
     }
 
     // ---- LDS set-up: quantiser grid, cleared packing words, first tile of Pi
-    if (mode != 2)
-        for (int e = tid; e < a.q_cells; e += 256) {      // boundaries in accumulator units
-            const float2 ent = a.q_grid[e];
-            grid_s[e] = make_float2(ent.x * (kSplitScale * kSplitScale), ent.y);
-        }
+    for (int e = tid; e < a.q_cells; e += 256) {          // boundaries in accumulator units
+        const float2 ent = a.q_grid[e];
+        grid_s[e] = make_float2(ent.x * (kSplitScale * kSplitScale), ent.y);
+    }
     uint32_t* my_pack = pack_s + (size_t)wave * (32 * R) * pitch;
     uint32_t* my_head = pack_s + (size_t)4 * (32 * R) * pitch + (size_t)wave * (32 * R) * pitch_h;
     if (via_lds) {
@@ -222,110 +215,83 @@ void k_encode(EncodeArgs a, int flags) {
         }
         if (t + 1 < NT) { IVFTQ_STORE_TILE((t + 1) & 1) }   // that buffer was last read before the previous barrier
 
-        if (mode == 2) {
+        // d is within 32 of the padded width: only the last tile can hold padding, and only there can a
+        // word lie past the row's last one
+        const bool ragged = t == NT - 1 && 32 * t + 32 > d;
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if (!valid[r]) continue;
+        for (int r = 0; r < R; ++r) {
+            uint32_t chunk[4];                     // the four codes of group g, b bits each
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float4 o = make_float4(acc[r][4 * g] * kUnscale, acc[r][4 * g + 1] * kUnscale,
-                                                 acc[r][4 * g + 2] * kUnscale, acc[r][4 * g + 3] * kUnscale);
-                    const int64_t at = row_of[r] * (int64_t)DP + t * 32 + 8 * g + 4 * half;
-                    *reinterpret_cast<float4*>(a.zout + at) = o;
-                    if (a.zh_out) {
-                        const float z[4] = {o.x, o.y, o.z, o.w};
-                        uint16_t h[4], l[4];
+            for (int g = 0; g < 4; ++g) {
+                const int c0 = 32 * t + 8 * g + 4 * half;
+                uint32_t code[4];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            _Float16 hi, lo;
-                            split_scaled(z[e], hi, lo);
-                            h[e] = __builtin_bit_cast(uint16_t, hi);
-                            l[e] = __builtin_bit_cast(uint16_t, lo);
+                for (int e = 0; e < 4; ++e) {
+                    const float av = acc[r][4 * g + e];
+                    const float at = __builtin_amdgcn_fmed3f(fmaf(av, q_scale, q_offset), 0.f, q_last);
+                    const float2 ent = grid_s[(int)at];
+                    code[e] = (uint32_t)__float_as_int(ent.y) + (av >= ent.x ? 1u : 0u);
+                    if (ragged && c0 + e >= d) code[e] = 0u;
+                }
+                if (mode == 1) {
+                    if (a.codes_flat && valid[r]) {
+                        uint8_t* out = a.codes_flat + row_of[r] * (int64_t)d + c0;
+                        if (!ragged && codes4) {
+                            *reinterpret_cast<uint32_t*>(out) = code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (c0 + e < d) out[e] = (uint8_t)code[e];
                         }
-                        *reinterpret_cast<uint2*>(a.zh_out + at) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
-                        *reinterpret_cast<uint2*>(a.zl_out + at) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
+                    }
+                    continue;
+                }
+                // four codes = 4b bits at bit c0*b of the row's little-endian bit string
+                chunk[g] = code[0] | (code[1] << b) | (code[2] << (2 * b)) | (code[3] << (3 * b));
+                if (via_lds) {
+                    const int bit = c0 * b;
+                    const int sh = bit & 31;
+                    uint32_t* wp = my_pack + (32 * r + j) * pitch + (bit >> 5);
+                    const uint32_t lo = chunk[g] << sh;
+                    const uint32_t hi = sh ? chunk[g] >> (32 - sh) : 0u;
+                    if (lo) atomicOr(wp, lo);
+                    if (hi) atomicOr(wp + 1, hi);
+                    if (head_words) {      // the same four codes cut down to their top beta bits, packed likewise
+                        const int hs = a.store.head_shift;
+                        const uint32_t ch = (code[0] >> hs) | ((code[1] >> hs) << beta) | ((code[2] >> hs) << (2 * beta)) |
+                                            ((code[3] >> hs) << (3 * beta));
+                        const int hbit = c0 * beta, hsh = hbit & 31;
+                        uint32_t* hp = my_head + (32 * r + j) * pitch_h + (hbit >> 5);
+                        const uint32_t hlo = ch << hsh;
+                        const uint32_t hhi = hsh ? ch >> (32 - hsh) : 0u;
+                        if (hlo) atomicOr(hp, hlo);
+                        if (hhi) atomicOr(hp + 1, hhi);
                     }
                 }
             }
-        } else {
-            // d is within 32 of the padded width: only the last tile can hold padding, and only there can a
-            // word lie past the row's last one
-            const bool ragged = t == NT - 1 && 32 * t + 32 > d;
+            if (MODE == 0 && PACK_B == 4) {
+                // Word 4t + g of a row = group g of half 0 (low 16 bits) and of half 1 (high 16 bits).
+                // v_permlane32_swap(a, b) gives lanes 0..31 (a, a of lane + 32) and lanes 32..63 (b of
+                // lane - 32, b): with a = group g and b = group g + 2 a lane of half h ends up with both
+                // parts of word 4t + g + 2h.
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                uint32_t chunk[4];                     // the four codes of group g, b bits each
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int c0 = 32 * t + 8 * g + 4 * half;
-                    uint32_t code[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float av = acc[r][4 * g + e];
-                        const float at = __builtin_amdgcn_fmed3f(fmaf(av, q_scale, q_offset), 0.f, q_last);
-                        const float2 ent = grid_s[(int)at];
-                        code[e] = (uint32_t)__float_as_int(ent.y) + (av >= ent.x ? 1u : 0u);
-                        if (ragged && c0 + e >= d) code[e] = 0u;
-                    }
-                    if (mode == 1) {
-                        if (a.codes_flat && valid[r]) {
-                            uint8_t* out = a.codes_flat + row_of[r] * (int64_t)d + c0;
-                            if (!ragged && codes4) {
-                                *reinterpret_cast<uint32_t*>(out) = code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
-                            } else {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    if (c0 + e < d) out[e] = (uint8_t)code[e];
-                            }
-                        }
-                        continue;
-                    }
-                    // four codes = 4b bits at bit c0*b of the row's little-endian bit string
-                    chunk[g] = code[0] | (code[1] << b) | (code[2] << (2 * b)) | (code[3] << (3 * b));
-                    if (via_lds) {
-                        const int bit = c0 * b;
-                        const int sh = bit & 31;
-                        uint32_t* wp = my_pack + (32 * r + j) * pitch + (bit >> 5);
-                        const uint32_t lo = chunk[g] << sh;
-                        const uint32_t hi = sh ? chunk[g] >> (32 - sh) : 0u;
-                        if (lo) atomicOr(wp, lo);
-                        if (hi) atomicOr(wp + 1, hi);
-                        if (head_words) {      // the same four codes cut down to their top beta bits, packed likewise
-                            const int hs = a.store.head_shift;
-                            const uint32_t ch = (code[0] >> hs) | ((code[1] >> hs) << beta) | ((code[2] >> hs) << (2 * beta)) |
-                                                ((code[3] >> hs) << (3 * beta));
-                            const int hbit = c0 * beta, hsh = hbit & 31;
-                            uint32_t* hp = my_head + (32 * r + j) * pitch_h + (hbit >> 5);
-                            const uint32_t hlo = ch << hsh;
-                            const uint32_t hhi = hsh ? ch >> (32 - hsh) : 0u;
-                            if (hlo) atomicOr(hp, hlo);
-                            if (hhi) atomicOr(hp + 1, hhi);
-                        }
-                    }
+                for (int g = 0; g < 2; ++g) {
+                    const auto sw = __builtin_amdgcn_permlane32_swap(chunk[g], chunk[g + 2], false, false);
+                    const uint32_t word = sw[0] | (sw[1] << 16);
+                    const int w = 4 * t + g + 2 * half;
+                    if (direct_dst[r] && (t < NT - 1 || w < words)) direct_dst[r][(int64_t)w * 64] = word;
                 }
-                if (MODE == 0 && PACK_B == 4) {
-                    // Word 4t + g of a row = group g of half 0 (low 16 bits) and of half 1 (high 16 bits).
-                    // v_permlane32_swap(a, b) gives lanes 0..31 (a, a of lane + 32) and lanes 32..63 (b of
-                    // lane - 32, b): with a = group g and b = group g + 2 a lane of half h ends up with both
-                    // parts of word 4t + g + 2h.
+            } else if (MODE == 0 && PACK_B == 8) {
 #pragma unroll
-                    for (int g = 0; g < 2; ++g) {
-                        const auto sw = __builtin_amdgcn_permlane32_swap(chunk[g], chunk[g + 2], false, false);
-                        const uint32_t word = sw[0] | (sw[1] << 16);
-                        const int w = 4 * t + g + 2 * half;
-                        if (direct_dst[r] && (t < NT - 1 || w < words)) direct_dst[r][(int64_t)w * 64] = word;
-                    }
-                } else if (MODE == 0 && PACK_B == 8) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {      // a group is a whole word: 8t + 2g + half
-                        const int w = 8 * t + 2 * g + half;
-                        if (direct_dst[r] && (t < NT - 1 || w < words)) direct_dst[r][(int64_t)w * 64] = chunk[g];
-                    }
+                for (int g = 0; g < 4; ++g) {      // a group is a whole word: 8t + 2g + half
+                    const int w = 8 * t + 2 * g + half;
+                    if (direct_dst[r] && (t < NT - 1 || w < words)) direct_dst[r][(int64_t)w * 64] = chunk[g];
                 }
             }
         }
         if (t + 1 < NT) __syncthreads();
     }
-    if (mode == 2 || (MODE == 0 && !via_lds)) return;
+    if (MODE == 0 && !via_lds) return;
 
     if (mode == 1) {
 #pragma unroll
@@ -594,7 +560,6 @@ hipError_t run(int mode, const EncodeArgs& a, hipStream_t st) {
         return run_mode<DP, 0, 0>(a, st);
     }
     if (mode == 1) return run_mode<DP, 1, 0>(a, st);
-    if (mode == 2) return run_mode<DP, 2, 0>(a, st);
     return hipErrorInvalidValue;
 }
 
@@ -602,7 +567,7 @@ hipError_t run(int mode, const EncodeArgs& a, hipStream_t st) {
 
 hipError_t launch_encode(int mode, const EncodeArgs& a, hipStream_t st) {
     if (a.n <= 0) return hipSuccess;
-    if (mode != 2 && (a.q_cells < 1 || !a.q_grid)) return hipErrorInvalidValue;
+    if (a.q_cells < 1 || !a.q_grid) return hipErrorInvalidValue;
     switch (rot_dp(a.d)) {
         case 32: return run<32>(mode, a, st);
         case 64: return run<64>(mode, a, st);

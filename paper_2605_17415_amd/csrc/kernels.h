@@ -103,12 +103,20 @@ struct ListStore {
 
 // ---- contraction kernels (split float16 MFMA) --------------------------------------------------------
 
-// scores[i*ld_scores + c] = <x~_i, cent_c> for every c below ld_scores
-// x: n x d raw rows (normalised inside; the scores of a row without a usable norm are not numbers or zero).
-// cent_h / cent_l: split float16 form of the centroid table [Lpad][cent_pitch], zero padded, Lpad % 64 == 0
+// scores[i*ld_scores + c] = <x~_i, cent_c> for every c below ld_scores and, with pi_h, the rotated rows z_i = Pi x~_i.
+// x: n x d raw rows (normalised inside; what a row without a usable norm gets are not numbers or zero).
+// cent_h / cent_l: split float16 form of the centroid table [Lpad][pitch], zero padded, Lpad % 64 == 0
 // (made by launch_split_rows).
-hipError_t launch_coarse(const float* x, int64_t n, int d, const uint16_t* cent_h, const uint16_t* cent_l, int cent_pitch,
-                         int Lpad, float* scores, int64_t ld_scores, hipStream_t st);
+struct CoarseArgs {
+    const float* x; int64_t n; int d;
+    const uint16_t* cent_h; const uint16_t* cent_l; int pitch; int Lpad;      // pitch = rot_dp(d)
+    float* scores; int64_t ld_scores;
+    const uint16_t* pi_h; const uint16_t* pi_l;   // split float16 form of Pi, [pitch][pitch], zero padded (null: no rotation)
+    float* z_out;                                 // [n][pitch]
+    uint16_t* zh_out; uint16_t* zl_out;           // optional: split float16 form of z
+    float* norm_out;                              // optional: |x_i| of every row, 0 where it is not usable
+};
+hipError_t launch_coarse(const CoarseArgs& a, hipStream_t st);
 // assign[i] = argmax_c (<x~_i, cent_c> + bias_c), -1 (and *flag = 1) for a row of zero or non-finite norm, in
 // two steps: a screening pass with the hi*hi products alone decides every row whose best score is clearly
 // ahead, the rest (listed in row_list, counted in *row_count, which the caller clears) is redone with all three
@@ -136,12 +144,11 @@ hipError_t launch_mfma_peak(const uint16_t* operands, float* out, int blocks, in
 // Rotation family.  pi_h/pi_l: split form of Pi, [DP][DP] zero padded, DP = rot_dp(d).
 // mode 0: residual -> rotate -> quantise -> pack into the list store at slot[row]
 // mode 1: same, but write unpacked codes / fp16 norms to flat arrays (any may be null)
-// mode 2: z_i = Pi x~_i written to zout[i*DP + j] (no centroid, no quantiser)
 // q_grid: the quantiser's uniform-grid index (host_math.h), q_cells entries of (boundary, index bits).
 // order_cell (mode 0): position p of the batch in list order holds row order_cell[p].x, which belongs to list
 // order_cell[p].y and goes to slot list_base[l] + p - batch_base[l] (neighbouring lanes store to neighbouring
-// slots, and neither the cell nor the slot of a row has to be fetched by row number).  Modes 1 and 2 take the
-// rows in input order and read assign[row].
+// slots, and neither the cell nor the slot of a row has to be fetched by row number).  Mode 1 takes the
+// rows in input order and reads assign[row].
 struct EncodeArgs {
     const float* x; int64_t n; int d; int b;
     const float* cent; int cent_pitch;
@@ -153,12 +160,7 @@ struct EncodeArgs {
     ListStore store; const int64_t* labels; int64_t label_base;
     // mode 1
     uint8_t* codes_flat; uint16_t* gamma_flat;
-    // mode 2
-    float* zout;
-    uint16_t* zh_out; uint16_t* zl_out;   // optional: split float16 form of 1024*z (see split_scaled)
-    float* norm_out;                      // optional (mode 2): |x_i| of every input row
 };
-
 
 hipError_t launch_encode(int mode, const EncodeArgs& a, hipStream_t st);
 
