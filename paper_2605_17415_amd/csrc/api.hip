@@ -184,7 +184,7 @@ struct ivftq_index {
     DevBuf t_cent, t_cent_h, t_cent_l, t_bias;   // k-means works on its own tables; the index's change only on success
     DevBuf w_zh, w_zl;
     DevBuf w_first, w_fscores, w_fids, w_pairs, w_tilebkt, w_cscore, w_cslot, w_ccnt, w_gate;
-    DevBuf w_stage_s, w_stage_i;      // survivors of the first step of a selection in two steps
+    DevBuf w_blk;                     // block maxima of the streaming scan
     DevBuf w_part;                    // partial results of a coarse assignment whose centroid stages are shared out
     int64_t last_batched_queries = 0;   // queries of the last pass of the most recent batched search (ivftq_scan_stats)
     int search_mode = 0;   // 0 auto, 1 streaming scan only, 2 batched scan whenever the shape allows
@@ -199,7 +199,7 @@ struct ivftq_index {
                 &w_slot, &w_order, &w_hist, &w_count, &w_base, &w_flag, &w_undecided, &cb_cascade, &w_keep, &w_keep_scores,
                 &w_S, &w_probe, &w_coarse, &w_z, &w_candoff, &w_scores, &w_sums, &w_counts, &w_gain, &w_rows, &w_dst,
                 &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_tilebkt, &w_cscore,
-                &w_cslot, &w_ccnt, &w_gate, &w_zh, &w_zl, &w_stage_s, &w_stage_i, &w_part};
+                &w_cslot, &w_ccnt, &w_gate, &w_zh, &w_zl, &w_blk, &w_part};
     }
     explicit ivftq_index(const Allocator& a) : alloc(a) {
         for (DevBuf* bfr : buffers()) bfr->al = &alloc;
@@ -1427,14 +1427,8 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         HIP_TRY(ix->w_ccnt.ensure((size_t)held * sizeof(int32_t)));
         HIP_TRY(ix->w_gate.ensure((size_t)(2 * held + 1) * sizeof(int32_t)));
     }
-    // Streaming path with so few queries that one wavefront per score row would leave the chip idle (the
-    // selection then takes longer than the scan): select per (query, list) first.  Needs what the
-    // one-wavefront kernel takes: k <= 64 and lists and survivor rows within its reach.
-    const bool two_step = !batched && nq <= 64 && k <= 64 && nprobe > 1 && sizes[0] <= 16384 && (int64_t)nprobe * k <= 16384;
-    if (two_step) {
-        HIP_TRY(ix->w_stage_s.ensure((size_t)held * nprobe * k * sizeof(float)));
-        HIP_TRY(ix->w_stage_i.ensure((size_t)held * nprobe * k * sizeof(int64_t)));
-    }
+    // block maxima of the streaming scan, a 64th of its scores (rows.floats holds those of a pass) and up to one more per probe
+    HIP_TRY(ix->w_blk.ensure((size_t)(rows.floats / 64 + held * (nprobe + 1)) * sizeof(uint32_t)));
 
     for (int64_t q0 = 0; q0 < nq; q0 += qc) {
         const int64_t cnt = std::min(qc, nq - q0);
@@ -1489,20 +1483,14 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             // and, while a share of a typical list still fills two rounds, until about 8192 are (64 queries at
             // 10M x 96: scan 0.100 -> 0.070 ms)
             slices = std::max(slices, std::min<int64_t>(kStreamWorkgroups / ((int64_t)per_query * cnt), ix->ntotal / ix->nlist / 512));
+            la.blk_max = ix->w_blk.as<uint32_t>(); la.blk_stride = block_index((int)m_stride, nprobe);
+            // scores that are no numbers (a query that is none itself): last among the results where one wavefront
+            // or two steps used to select them, else first
+            la.nan_last = k <= 64 && (m_stride <= 16384 || (nq <= 64 && nprobe > 1 && sizes[0] <= 16384 && (int64_t)nprobe * k <= 16384));
             HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, per_query, (int)slices, st); }));
-            if (two_step) {
-                // a handful of rows: one wavefront per (query, list) first, then one per query over the survivors
-                SelectArgs s_a = sa, s_b = sa;
-                s_a.rows = cnt * nprobe; s_a.m_bound = sizes[0];
-                s_a.out_vals = ix->w_stage_s.as<float>(); s_a.out_i64 = ix->w_stage_i.as<int64_t>();
-                s_b.vals = ix->w_stage_s.as<float>(); s_b.stride = (int64_t)nprobe * k; s_b.m_fixed = nprobe * k;
-                s_b.lab_in = ix->w_stage_i.as<int64_t>();
-                HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_select(2, s_a, st); }));
-                HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_select(3, s_b, st); }));
-            } else {
-                HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_select(1, sa, st); }));
-            }
-            HIP_TRY(launch_metric_finish(scores_dev + q0 * k, cnt, k, metric, ix->w_qnorm.as<float>(), st));
+            sa.blk_max = la.blk_max; sa.blk_stride = la.blk_stride; sa.nan_last = la.nan_last;
+            sa.metric = metric; sa.qnorm = la.qnorm;
+            HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_select(1, sa, st); }));
             continue;
         }
 
@@ -1557,12 +1545,12 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         ra.redo_cnt = redo_cnt; ra.cand_off = la.cand_off; ra.probe = la.probe; ra.np = nprobe;
         ra.list_off = ix->d_off.as<int64_t>(); ra.ids = labels;
         ra.out_vals = sa.out_vals; ra.out_i64 = sa.out_i64;
+        ra.metric = metric; ra.qnorm = ma.qnorm;
         for (int64_t g0 = 0; g0 < cnt; g0 += gate_rows) {
             la.gate_begin = ra.gate_begin = (int)g0;
             HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, 0, 1, st); }));
             HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_redo_select(ra, st); }));
         }
-        HIP_TRY(launch_metric_finish(scores_dev + q0 * k, cnt, k, metric, ix->w_qnorm.as<float>(), st));
     }
     return IVFTQ_OK;
 }

@@ -28,7 +28,7 @@ __global__ void k_pair_count(const int32_t* __restrict__ probe, const int32_t* _
     const int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (it >= nq * np) return;
     const int late = (int)(it % np) >= first[it / np];
-    atomicAdd(&count[probe[it] + (late ? L : 0)], 1u);
+    if (probe[it] >= 0) atomicAdd(&count[probe[it] + (late ? L : 0)], 1u);      // (no cell: a query whose scores are no numbers)
 }
 
 // Every bucket gets a range of the pair array (pair_off) and of its pass's tile array (tile_off, tile_bucket), and
@@ -81,7 +81,7 @@ __global__ void k_pair_scatter(const int32_t* __restrict__ probe, const int32_t*
     if (it >= nq * np) return;
     const int late = (int)(it % np) >= first[it / np];
     const int bkt = probe[it] + (late ? L : 0);
-    pairs[pair_off[bkt] + atomicAdd(&cursor[bkt], 1u)] = (int32_t)it;
+    if (probe[it] >= 0) pairs[pair_off[bkt] + atomicAdd(&cursor[bkt], 1u)] = (int32_t)it;
 }
 
 // The same two steps with the counters privatised in LDS: a workgroup takes kPairChunk consecutive
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(1024) void k_pair_count_lds(const int32_t* __restri
     const int64_t end = begin + kPairChunk < total ? begin + kPairChunk : total;
     for (int64_t it = begin + threadIdx.x; it < end; it += 1024) {
         const int late = (int)(it % np) >= first[it / np];
-        atomicAdd(&bins[probe[it] + (late ? L : 0)], 1u);
+        if (probe[it] >= 0) atomicAdd(&bins[probe[it] + (late ? L : 0)], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * L; i += 1024)
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(1024) void k_pair_scatter_lds(const int32_t* __rest
     const int64_t end = begin + kPairChunk < total ? begin + kPairChunk : total;
     for (int64_t it = begin + threadIdx.x; it < end; it += 1024) {
         const int late = (int)(it % np) >= first[it / np];
-        atomicAdd(&bins[probe[it] + (late ? L : 0)], 1u);
+        if (probe[it] >= 0) atomicAdd(&bins[probe[it] + (late ? L : 0)], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * L; i += 1024) {
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(1024) void k_pair_scatter_lds(const int32_t* __rest
     for (int64_t it = begin + threadIdx.x; it < end; it += 1024) {
         const int late = (int)(it % np) >= first[it / np];
         const int bkt = probe[it] + (late ? L : 0);
-        pairs[pair_off[bkt] + atomicAdd(&bins[bkt], 1u)] = (int32_t)it;
+        if (probe[it] >= 0) pairs[pair_off[bkt] + atomicAdd(&bins[bkt], 1u)] = (int32_t)it;
     }
 }
 
@@ -169,11 +169,13 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
         if (tid == 0) a.gate[1 + atomicAdd(&a.gate[0], 1)] = (int32_t)q;
         return;
     }
+    const float qn = a.metric ? a.qnorm[q] : 1.f;
+    auto put = [&](int i, float key, int64_t lab) {
+        a.out_scores[q * a.k + i] = a.metric ? metric_value(a.metric, key, qn) : key;
+        a.out_ids[q * a.k + i] = lab;
+    };
     if (cnt == 0) {                              // nothing beat the threshold: the first pass's k best stand as they are
-        for (int i = tid; i < a.k; i += 256) {
-            a.out_scores[q * a.k + i] = a.first_scores[q * a.k + i];
-            a.out_ids[q * a.k + i] = a.first_ids[q * a.k + i];
-        }
+        for (int i = tid; i < a.k; i += 256) put(i, a.first_scores[q * a.k + i], a.first_ids[q * a.k + i]);
         return;
     }
     const int total = a.k + cnt;
@@ -188,7 +190,6 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
     for (int j = tid; j < (1 << a.b); j += 256) s_cb[j] = a.cb[j];
     hist[tid] = 0;
     if (tid == 0) { s_bin = 0; s_found = 0; }
-    const float qn = a.metric ? a.qnorm[q] : 1.f;
     constexpr int64_t kSlotMask = ((int64_t)1 << kCandProbeShift) - 1;
     constexpr int kHeld = 8;                     // lower bounds of a thread's first entries, kept between the two passes
     float held[kHeld];
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
         }
     }
     __syncthreads();
-    for (int i = found + tid; i < a.k; i += 256) { a.out_scores[q * a.k + i] = -__builtin_inff(); a.out_ids[q * a.k + i] = -1; }
+    for (int i = found + tid; i < a.k; i += 256) put(i, -__builtin_inff(), -1);
     if (found <= kMergeCount) {
         if (tid < found) {
             const uint32_t key = p_key[tid];
@@ -316,10 +317,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
                 const int64_t lj = p_lab[j];
                 rank += (kj > key || (kj == key && (lj < lab || (lj == lab && j < tid)))) ? 1 : 0;
             }
-            if (rank < a.k) {
-                a.out_scores[q * a.k + rank] = okey_value(key);
-                a.out_ids[q * a.k + rank] = lab;
-            }
+            if (rank < a.k) put(rank, okey_value(key), lab);
         }
         return;
     }
@@ -340,10 +338,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
             }
             __syncthreads();
         }
-    for (int i = tid; i < a.k && i < found; i += 256) {
-        a.out_scores[q * a.k + i] = okey_value(p_key[i]);
-        a.out_ids[q * a.k + i] = p_lab[i];
-    }
+    for (int i = tid; i < a.k && i < found; i += 256) put(i, okey_value(p_key[i]), p_lab[i]);
 }
 
 }  // namespace

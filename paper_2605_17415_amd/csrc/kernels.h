@@ -245,6 +245,9 @@ struct CandOffsetArgs {
     int32_t* cand_cnt; int32_t* gate; int32_t* redo_cnt;
     uint32_t* bucket_cnt; int buckets;
 };
+// Where the block maxima of a query's probe p begin when `col` candidates precede it.  Every probe has one place more than
+// the 64-column groups its candidates touch at most, so that its blocks, counted from its first candidate, fit.
+__host__ __device__ constexpr int block_index(int col, int p) { return (col >> 6) + p; }
 // scores[q*m_stride + cand_off[q][p] + i] = coarse[q][p] + gamma_i * sum_j z_qj * C[code_ij]
 struct ListScanArgs {
     const float* z; int z_pitch; int d;
@@ -253,6 +256,9 @@ struct ListScanArgs {
     ListStore store;
     float* scores; int64_t m_stride;
     int metric; const float* qnorm;
+    // blk_max[q*blk_stride + block_index(cand_off[q][p], p) + b] = order-preserving key of the best score of block b (64
+    // vectors) of probe p (null: not wanted); nan_last: what is no number counts as the smallest
+    uint32_t* blk_max; int64_t blk_stride; bool nan_last;
     // Exact redo (gate not null): instead of all queries the entries [gate_begin, gate_begin + gate_rows) of the
     // gate[0] queries listed in gate[1..] are scanned.  Entry g's scores that reach thresh[q*thresh_stride], less the
     // rounding between the arithmetic of the threshold and this one, go, redo_cnt[q] of them in any order, to the
@@ -273,10 +279,11 @@ struct RedoSelectArgs {
     const int32_t* cand_off; const int32_t* probe; int np;
     const int64_t* list_off; const int64_t* ids;
     float* out_vals; int64_t* out_i64;
+    int metric; const float* qnorm;               // results are written as values of the metric
 };
 hipError_t launch_redo_select(const RedoSelectArgs& a, hipStream_t st);
 // metric 0: the score is the estimate s^ of <q~, x~> itself.  Raw metrics (the store keeps |x|, qnorm[q] = |q|):
-// the scan writes a key that ranks like the metric and launch_metric_finish turns the selected keys into values:
+// the scan writes a key that ranks like the metric and whatever writes a call's results turns the selected keys into values:
 //   metric 1 (inner product): key = |x| s^,                 value = |q| key            (descending)
 //   metric 2 (squared L2):    key = 2 |x| |q| s^ - |x|^2,   value = |q|^2 - key        (ascending; missing: +inf)
 __device__ __forceinline__ float metric_key(int metric, float s, float xn, float qn) {
@@ -292,7 +299,8 @@ __device__ __forceinline__ float metric_key_bound(int metric, float s, float x_m
     const float x = fminf(fmaxf(qn * s, x_min), x_max);
     return fmaf(2.f * x * qn, s, -x * x) + 0x1p-20f * (x * x + fabsf(2.f * x * qn * s));
 }
-hipError_t launch_metric_finish(float* scores, int64_t nq, int k, int metric, const float* qnorm, hipStream_t st);
+// (a missing result's key is -inf: it stays so as an inner product, and becomes +inf as a distance)
+__device__ __forceinline__ float metric_value(int metric, float key, float qn) { return metric == 1 ? qn * key : qn * qn - key; }
 // Per row: the k largest of m values, sorted by (value desc, label asc).
 // mode 0 (probe selection): m = m_fixed for every row, label = column; writes int32 labels.
 // mode 1 (results): row q has m = cand_off[q][np] values; column -> (probe p, position) -> label
@@ -305,10 +313,9 @@ struct SelectArgs {
     const int64_t* list_off; const int64_t* ids;
     float* out_vals; int32_t* out_i32; int64_t* out_i64;
     int m_bound;      // mode 1: host-side upper bound of any row's length (0 = unknown); picks the kernel
-    // Selection in two steps (k <= 64): mode 2 treats `rows` = queries x np rows, row (q, p) being the
-    // stretch of probe p in score row q, and writes k (value, label) pairs per row (m_bound = longest list);
-    // mode 3 selects among the m_fixed = np * k survivors of a query, whose labels it reads from lab_in.
-    const int64_t* lab_in;
+    const uint32_t* blk_max; int64_t blk_stride;      // mode 1: as the scan left them (null: not there)
+    bool nan_last;                                    // mode 1: what is no number is no result
+    int metric; const float* qnorm;                   // mode 1: the values are ranking keys, written as values of the metric
     // mode 0: what follows from the probes just selected (cand.cand_off null: nothing)
     CandOffsetArgs cand;
 };

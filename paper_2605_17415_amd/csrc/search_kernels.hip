@@ -59,38 +59,36 @@ __device__ __forceinline__ void cand_offsets_lanes(const CandOffsetArgs& c, int6
     if (lane == 0) put_first(c, q, reached ? (int)__builtin_ctzll(reached) + 1 : np);
 }
 
-// For probe selections that do not end with the probes in one wavefront's lanes (more than 64 probes, or more cells
-// than the one-wavefront selection takes).
-__global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict__ probe, int64_t nq, int np, CandOffsetArgs c) {
-    clear_buckets(c);
-    // one wavefront per query: 64 probes at a time, running sum over the lanes
-    const int lane = threadIdx.x & 63;
-    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (q >= nq) return;
+// And for any number of probes, whose cells are in LDS: 64 at a time, `incl` ([np], LDS) takes the running sums.
+__device__ __forceinline__ void cand_offsets_wave(const CandOffsetArgs& c, int64_t q, int np, const int32_t* cell, int32_t* incl, int lane) {
+    int32_t* off = c.cand_off + q * (np + 1);
     int32_t run = 0;
     for (int p0 = 0; p0 < np; p0 += 64) {
-        const int p = p0 + lane;
-        const int32_t size = p < np && probe[q * np + p] >= 0 ? c.list_size[probe[q * np + p]] : 0;
-        const int32_t incl = lanes_up_to(size, lane);
-        if (p < np) c.cand_off[q * (np + 1) + p] = run + incl - size;
-        run += __shfl(incl, 63);
+        const int p = p0 + lane, list = p < np ? cell[p] : -1;
+        const int32_t size = list >= 0 ? c.list_size[list] : 0;
+        const int32_t upto = run + lanes_up_to(size, lane);
+        if (p < np) { off[p] = upto - size; incl[p] = upto; }
+        run = __shfl(upto, 63);
     }
-    if (lane == 0) c.cand_off[q * (np + 1) + np] = run;
+    if (lane == 0) off[np] = run;
     if (!c.first) return;
-    // the first p >= 1 whose lists 0 .. p-1 together reach `need` (np when none does)
+    // the first p >= 1 whose lists 0 .. p-1 together reach `need` (np when none does); a lane reads what it wrote
     const int64_t need = dense_prefix(c, run);
     int p1 = np;
-    int32_t run2 = 0;
     for (int p0 = 0; p0 < np && p1 == np; p0 += 64) {
-        const int p = p0 + lane;
-        const int32_t size = p < np && probe[q * np + p] >= 0 ? c.list_size[probe[q * np + p]] : 0;
-        const int32_t incl = lanes_up_to(size, lane);
-        const uint64_t reached = __ballot(p < np && (int64_t)(run2 + incl) >= need);
+        const uint64_t reached = __ballot(p0 + lane < np && (int64_t)incl[p0 + lane] >= need);
         if (reached) p1 = p0 + (int)__builtin_ctzll(reached) + 1;
-        run2 += __shfl(incl, 63);
     }
     if (lane == 0) put_first(c, q, p1);
 }
+
+// Order-preserving key of a score; with nan_last whatever is no number gets the smallest one, 0.
+__device__ __forceinline__ uint32_t order_key(float f) {
+    const uint32_t u = __float_as_uint(f);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ uint32_t order_key(float f, bool nan_last) { return nan_last && f != f ? 0u : order_key(f); }
+__device__ __forceinline__ float order_value(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key); }
 
 // ---- list scan: a row of workgroups per query walks its probed lists ---------------------------
 //
@@ -111,6 +109,8 @@ __global__ __launch_bounds__(256) void k_cand_offsets(const int32_t* __restrict_
 // codes may have at any size, and the sum with the coarse term is rounded at the size of that.
 __device__ __forceinline__ float redo_margin(float slack, float s_l, float g) { return slack * fmaxf(g, 1.f) + 0x1p-21f * fabsf(s_l); }
 
+// With a.blk_max every block of 64 vectors of a list leaves the key of its best score beside the scores, so that the
+// selection reads a 64th of the row and then the few blocks that can hold a result (block_index).
 template <int B, bool DIRECT, bool REDO>
 __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
     constexpr int K = 1 << B;
@@ -165,15 +165,26 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
     const int words = store.words;
     for (int p = p_first; p < np; p += p_step) {
     const int l = probe[q * np + p];
-    const int n_l = store.list_size[l];
+    const int n_l = l < 0 ? 0 : store.list_size[l];     // (no cell: a query whose scores are no numbers)
     const float s_l = coarse[q * np + p];
-    const int64_t base_slot = store.list_off[l];
+    const int64_t base_slot = l < 0 ? 0 : store.list_off[l];
     const int32_t col0 = cand_off[q * (np + 1) + p];
     float* out = a.scores + row * a.m_stride + (REDO ? 0 : col0);
+    const int lane = (int)(threadIdx.x & 63);
+    uint32_t* blk = nullptr;
+    if (!REDO && a.blk_max) {
+        blk = a.blk_max + row * a.blk_stride + block_index(col0, p);
+        // places between this list's blocks and the next one's hold nothing
+        const int own = block_index(cand_off[q * (np + 1) + p + 1], p + 1) - block_index(col0, p);
+        const int b = (n_l + 63) / 64 + (int)threadIdx.x;
+        if (slice == 0 && b < own) blk[b] = 0u;
+    }
 
     // a list is dealt out in rounds of 256 vectors to the workgroups that share it
-    for (int v = threadIdx.x + 256 * slice; v < n_l; v += 256 * slices) {
-        const int64_t slot = base_slot + v;
+    for (int v0 = 256 * slice + (int)(threadIdx.x & ~63u); v0 < n_l; v0 += 256 * slices) {
+        const int v = v0 + lane;
+        const bool in_list = v < n_l;
+        const int64_t slot = base_slot + (in_list ? v : n_l - 1);
         const uint32_t* wp = store.codes + (slot >> 6) * words * 64 + (slot & 63);
         float acc = 0.f;
         // A row is walked in chunks of 32 coordinates = B packed words, whose codes sit at bit positions known at
@@ -273,10 +284,10 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
             margin = redo_margin(a.slack, s_l, g);
         }
         if constexpr (REDO) {
-            const bool keep = !(sc < reach - margin);     // (whatever is no number stays, as in a scan that keeps all)
+            const bool keep = in_list && !(sc < reach - margin);     // (whatever is no number stays, as in a scan that keeps all)
             const uint64_t in = __ballot(keep);           // one counter update per wavefront
             if (in) {
-                const int lane = (int)(threadIdx.x & 63), leader = (int)__builtin_ctzll(in);
+                const int leader = (int)__builtin_ctzll(in);
                 int at = 0;
                 if (lane == leader) at = atomicAdd(&a.redo_cnt[q], (int)__popcll(in));
                 at = __shfl(at, leader) + (int)__popcll(in & (((uint64_t)1 << lane) - 1));
@@ -286,35 +297,66 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
                 }
             }
         } else {
-            out[v] = sc;
+            if (in_list) out[v] = sc;
+            if (blk) {
+                uint32_t key = in_list ? order_key(sc, a.nan_last) : 0u;
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) key = max(key, (uint32_t)__shfl_xor(key, o));
+                if (lane == 0) blk[v0 >> 6] = key;
+            }
         }
     }
     }
     }
 }
 
-// Selected ranking keys of a raw metric -> metric values (keys of missing results are -inf).
-__global__ void k_metric_finish(float* __restrict__ scores, int64_t nq, int k, int metric, const float* __restrict__ qnorm) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nq * k) return;
-    const float qn = qnorm[i / k], key = scores[i];
-    scores[i] = metric == 1 ? qn * key : qn * qn - key;       // -inf stays -inf (inner product) or becomes +inf (distance)
-}
-
 // ---- selection: k largest of a row ------------------------------------------------------------
 //
-// Exact radix selection on an order-preserving 32-bit key (four 8-bit digits, most significant
-// first), then the survivors are labelled and sorted by (value desc, label asc) with a bitonic
-// network in LDS.  Among values equal to the k-th one, those with the smallest column are kept.
-
-__device__ __forceinline__ uint32_t order_key(float f) {
-    const uint32_t u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
+// One workgroup per row, exact, on an order-preserving 32-bit key.  Keys equal to the k-th largest are kept in column
+// order; the winners are labelled and ordered by (value desc, label asc).
+//
+// Short cut (up to kSelTake winners).  The row is split into parts, of which the largest keys are known: the parts are the
+// blocks of 64 columns whose maxima the scan left (blk_max), or the columns dealt out round-robin to the 256 threads.
+// Every thread holds the largest of its share of these maxima; at least `take` keys reach the take-th largest of the 256,
+// `bound` (found by bisection on the key's bits, but for the lowest, each wavefront by itself).  All keys that reach it are
+// gathered, about -256 ln(1 - take/256) whatever the row looks like where the columns are dealt out (127 for 100 winners,
+// 355 for 192).  With block maxima the row itself is not read but for the about as many blocks that reach the bound, whose
+// columns are dealt out for a second one (many of their keys can reach the first: a near list of which every vector is
+// better than the best of the far ones).  The order of the keys follows from counting, for each, the ones before it.
+// The k best of 78,000 scores (10M x 96, 32 probes, 16 queries) took two launches of 25 and 7 us that read every score.
+// Bound by latency: a handful of dependent reads, so what counts is that each is one round for all threads.
+// Otherwise (more winners, or more than kSelCand keys reach the bound) an exact radix search, four 8-bit digits,
+// most significant first.
 constexpr int kSelU = 8;        // groups of 64 columns loaded together by k_select
 constexpr int kSelSmallU = 8;   // and by k_select_small beyond its registers
-constexpr int kSelCand = 512;   // most keys the short cut of k_select sorts directly
+constexpr int kSelCand = 512;   // most keys the short cut of k_select orders
+constexpr int kSelTake = 192;   // most winners it is used for
+constexpr int kSelHeld = 16;    // columns (or block maxima) a thread keeps in registers between its two passes
+constexpr int kSelBlocks = 512; // most blocks it gathers from
+constexpr int kSelOffs = 256;   // most probes whose offsets are staged in LDS
+
+// A lower bound of the take-th largest of the 256 keys at `maxima`, less than 2^10 below it (0 when there are fewer).  For
+// few winners of the 64 keys that are the largest of four each, which is another such bound and hardly lower (30 keys
+// of a row dealt out reach it for 24 winners instead of 25) at a quarter of the steps.
+__device__ __forceinline__ uint32_t kth_of_maxima(const uint32_t* maxima, int take, int lane) {
+    const uint4 m4 = *reinterpret_cast<const uint4*>(maxima + 4 * lane);
+    uint32_t bound = 0;
+    if (take <= 24) {
+        const uint32_t one = max(max(m4.x, m4.y), max(m4.z, m4.w));
+        for (int bit = 31; bit >= 10; --bit) {
+            const uint32_t test = bound | (1u << bit);
+            if (__popcll(__ballot(one >= test)) >= take) bound = test;
+        }
+        return bound;
+    }
+    for (int bit = 31; bit >= 10; --bit) {
+        const uint32_t test = bound | (1u << bit);
+        const int cnt = __popcll(__ballot(m4.x >= test)) + __popcll(__ballot(m4.y >= test)) +
+                        __popcll(__ballot(m4.z >= test)) + __popcll(__ballot(m4.w >= test));
+        if (cnt >= take) bound = test;
+    }
+    return bound;
+}
 
 // COPIES: counters per digit in the histogram (a power of two; 8 pays for long rows, 1 for short ones, where
 // clearing and summing the copies costs more than the collisions they avoid).
@@ -322,6 +364,7 @@ template <int MODE, int COPIES>
 __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     constexpr int kHistCopies = COPIES;
     extern __shared__ unsigned char smem[];
+    __shared__ int32_t s_off[kSelOffs + 1];
     int kpad = 1;
     while (kpad < a.k) kpad <<= 1;
     // kHistCopies counters per digit, chosen by lane: keys of one row often share their leading byte, and
@@ -332,15 +375,21 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     uint32_t* s_key = wave_cnt + 4;                                   // [kpad]
     uint32_t* s_col = s_key + kpad;                                   // [kpad]
     int64_t* s_lab = reinterpret_cast<int64_t*>(s_col + kpad);   // [kpad], 8-byte aligned: 268 + 2*kpad words
-    uint32_t* c_key = reinterpret_cast<uint32_t*>(s_lab + kpad);      // [kSelCand] keys of the short cut ...
-    uint32_t* c_col = c_key + kSelCand;                               // [kSelCand] ... and their columns
+    uint64_t* c_ent = reinterpret_cast<uint64_t*>(s_lab + kpad);      // [kSelCand + 8] key << 32 | ~column of the short cut; before that its maxima ...
+    int2* c_blk = reinterpret_cast<int2*>(c_ent + kSelCand + 8);      // [kSelBlocks] ... and the blocks that reach the bound
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (MODE == 0) clear_buckets(a.cand);
     const int64_t row = blockIdx.x;
     const float* vals = a.vals + row * a.stride;
     const int64_t q = row;
-    const int m = (MODE == 0) ? a.m_fixed
-                              : a.cand_off[q * (a.np + 1) + (a.p_limit ? a.p_limit[q] : a.np)];
+    const int32_t* off = MODE == 0 ? nullptr : a.cand_off + q * (a.np + 1);
+    const int n_off = MODE == 0 ? 0 : a.p_limit ? a.p_limit[q] : a.np;
+    const int m = MODE == 0 ? a.m_fixed : off[n_off];
+    const bool nan_last = a.nan_last, staged = a.np <= kSelOffs;
+    if (MODE == 1 && staged)
+        for (int p = tid; p <= a.np; p += 256) s_off[p] = off[p];
+    auto off_at = [&](int p) -> int32_t { return staged ? s_off[p] : off[p]; };
     const int k = a.k;
     const int take = m < k ? m : k;
 
@@ -352,88 +401,133 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     const int w_end = (w_begin + chunk < m) ? w_begin + chunk : m;
     uint32_t prefix = 0, mask = 0;
     uint32_t need = (uint32_t)take;
-    // Short cut.  Every thread takes the largest key of the columns tid, tid + 256, ...; at least `take`
-    // values reach the take-th largest of these 256 maxima, so it is a lower bound of the take-th largest
-    // value, and with the columns dealt out round-robin about -256 ln(1 - take/256) values reach it
-    // whatever the row looks like (127 for take = 100, 355 for 192; beyond that too many).  Those are gathered and sorted by (key desc, column asc): the first
-    // `take` of them are the winners the radix search below would pick (same rule for keys equal to the
-    // last one).  Two reads of the row instead of six; if more than kSelCand values reach the bound the
-    // radix search runs after all.
     bool picked = false;
-    if (take > 0 && m > k && take <= 192 && m >= 2048) {
-        uint32_t best = 0;            // below every key of a number
-        for (int i0 = 0; i0 < m; i0 += 256 * kSelU) {
-            float v[kSelU];
+    if (tid == 0) { ctrl[5] = 0; ctrl[6] = 0; }
+    const int n_blk = MODE == 1 && a.blk_max ? block_index(m, n_off) : 0;
+    // (few blocks for many winners: their maxima say little)
+    const bool by_block = n_blk >= 2 * take && m > kSelCand;
+    if (take > 0 && ((take <= kSelTake && m > k) || m <= kSelCand)) {
+        // (one base pointer and loads without a branch between them, so that all of a thread's are in flight together)
+        const uint32_t* src = by_block ? a.blk_max + row * a.blk_stride : reinterpret_cast<const uint32_t*>(vals);
+        const int parts = by_block ? n_blk : m;
+        auto key_of = [&](uint32_t raw) -> uint32_t { return by_block ? raw : order_key(__uint_as_float(raw), nan_last); };
+        uint32_t* maxima = reinterpret_cast<uint32_t*>(c_ent);
+        uint32_t held[kSelHeld], bound = 0;
+        if (parts <= 1024) {
 #pragma unroll
-            for (int u = 0; u < kSelU; ++u) {
-                const int i = i0 + 256 * u + tid;
-                v[u] = vals[i < m ? i : m - 1];
-            }
+            for (int u = 0; u < 4; ++u) held[u] = src[min(256 * u + tid, parts - 1)];
+        } else {
 #pragma unroll
-            for (int u = 0; u < kSelU; ++u) {
-                const uint32_t key = order_key(v[u]);
-                if (i0 + 256 * u + tid < m && key > best) best = key;
-            }
+            for (int u = 0; u < kSelHeld; ++u) held[u] = src[min(256 * u + tid, parts - 1)];
         }
-        c_key[tid] = best;
-        if (tid == 0) { ctrl[4] = 0; ctrl[5] = 0; }
-        __syncthreads();
-        // rank of this thread's maximum among the 256 (larger first, thread number breaks ties)
-        uint32_t rank = 0;
-        for (int j = 0; j < 256; j += 4) {
-            const uint4 o = *reinterpret_cast<const uint4*>(c_key + j);
-            rank += (o.x > best || (o.x == best && j < tid)) ? 1u : 0u;
-            rank += (o.y > best || (o.y == best && j + 1 < tid)) ? 1u : 0u;
-            rank += (o.z > best || (o.z == best && j + 2 < tid)) ? 1u : 0u;
-            rank += (o.w > best || (o.w == best && j + 3 < tid)) ? 1u : 0u;
-        }
-        if (rank == (uint32_t)take - 1u) ctrl[4] = best;
-        __syncthreads();
-        const uint32_t bound = ctrl[4];
-        __syncthreads();               // the maxima are no longer read: c_key is filled anew
-        for (int i0 = 0; i0 < m; i0 += 256 * kSelU) {
-            float v[kSelU];
+        if (parts > kSelCand || by_block) {
+            uint32_t best = 0;
 #pragma unroll
-            for (int u = 0; u < kSelU; ++u) {
-                const int i = i0 + 256 * u + tid;
-                v[u] = vals[i < m ? i : m - 1];
-            }
+            for (int u = 0; u < kSelHeld; ++u) best = 256 * u + tid < parts ? max(best, key_of(held[u])) : best;
+            for (int i0 = 256 * kSelHeld; i0 < parts; i0 += 256 * kSelU) {
+                uint32_t v[kSelU];
 #pragma unroll
-            for (int u = 0; u < kSelU; ++u) {
-                const int i = i0 + 256 * u + tid;
-                const uint32_t key = order_key(v[u]);
-                if (i < m && key >= bound) {
-                    const uint32_t pos = atomicAdd(&ctrl[5], 1u);
-                    if (pos < (uint32_t)kSelCand) { c_key[pos] = key; c_col[pos] = (uint32_t)i; }
-                }
+                for (int u = 0; u < kSelU; ++u) v[u] = src[min(i0 + 256 * u + tid, parts - 1)];
+#pragma unroll
+                for (int u = 0; u < kSelU; ++u) best = i0 + 256 * u + tid < parts ? max(best, key_of(v[u])) : best;
             }
-        }
-        __syncthreads();
-        const uint32_t found = ctrl[5];
-        if (found <= (uint32_t)kSelCand) {          // uniform over the workgroup
-            int cpad = 1;
-            while (cpad < (int)found) cpad <<= 1;
-            for (int i = (int)found + tid; i < cpad; i += 256) { c_key[i] = 0u; c_col[i] = 0xFFFFFFFFu; }
+            maxima[tid] = best;
             __syncthreads();
-            for (int size = 2; size <= cpad; size <<= 1) {
-                for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                    for (int i = tid; i < cpad / 2; i += 256) {
-                        const int lo_i = 2 * i - (i & (stride - 1));
-                        const int hi_i = lo_i + stride;
-                        const bool up = ((lo_i & size) == 0);
-                        const uint32_t k0 = c_key[lo_i], k1 = c_key[hi_i];
-                        const uint32_t c0 = c_col[lo_i], c1 = c_col[hi_i];
-                        const bool first_before = (k0 > k1) || (k0 == k1 && c0 <= c1);
-                        if (first_before != up) {
-                            c_key[lo_i] = k1; c_key[hi_i] = k0;
-                            c_col[lo_i] = c1; c_col[hi_i] = c0;
-                        }
-                    }
-                    __syncthreads();
-                }
+            bound = kth_of_maxima(maxima, take, lane);
+        }
+        __syncthreads();               // the maxima are no longer read: the entries take their place
+        auto gather = [&](uint32_t key, int col) {
+            const uint32_t pos = atomicAdd(&ctrl[5], 1u);
+            if (pos < (uint32_t)kSelCand) c_ent[pos] = (uint64_t)key << 32 | (uint32_t)~col;
+        };
+        auto pass = [&](uint32_t raw, int i) {
+            const uint32_t key = key_of(raw);
+            if (i >= parts || key < bound) return;
+            if (!by_block) {
+                gather(key, i);
+            } else {
+                const uint32_t pos = atomicAdd(&ctrl[6], 1u);
+                if (pos < (uint32_t)kSelBlocks) c_blk[pos].x = i;
             }
-            for (int i = tid; i < take; i += 256) { s_key[i] = c_key[i]; s_col[i] = c_col[i]; }
-            picked = true;
+        };
+#pragma unroll
+        for (int u = 0; u < kSelHeld; ++u) {
+            if (256 * u >= parts) break;
+            pass(held[u], 256 * u + tid);
+        }
+        for (int i0 = 256 * kSelHeld; i0 < parts; i0 += 256 * kSelU) {
+            uint32_t v[kSelU];
+#pragma unroll
+            for (int u = 0; u < kSelU; ++u) v[u] = src[min(i0 + 256 * u + tid, parts - 1)];
+#pragma unroll
+            for (int u = 0; u < kSelU; ++u) pass(v[u], i0 + 256 * u + tid);
+        }
+        __syncthreads();
+        if (by_block && ctrl[6] <= (uint32_t)kSelBlocks) {
+            const int n = (int)ctrl[6];
+            // first column of a block, and how many it has
+            for (int b = tid; b < n; b += 256) {
+                const int i = c_blk[b].x;
+                int lo = 0, hi = n_off;                 // largest p with block_index(off(p), p) <= i
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (block_index(off_at(mid), mid) <= i) lo = mid; else hi = mid;
+                }
+                const int c0 = off_at(lo) + (i - block_index(off_at(lo), lo)) * 64;
+                c_blk[b] = make_int2(c0, off_at(lo + 1) - c0);
+            }
+            __syncthreads();
+            // kSelHeld blocks of a wavefront at a time, the first of them kept in registers
+            float v[kSelHeld];
+            int col[kSelHeld];                          // (-1: none)
+            auto read = [&](int b0) {
+#pragma unroll
+                for (int e = 0; e < kSelHeld; ++e) {
+                    const int b = b0 + 4 * e;
+                    const int2 c = c_blk[b < n ? b : 0];
+                    col[e] = b < n && lane < c.y ? c.x + lane : -1;
+                    v[e] = vals[max(col[e], 0)];
+                }
+            };
+            auto for_keys = [&](auto use) {
+                for (int b0 = wave; b0 < n; b0 += 4 * kSelHeld) {
+                    if (b0 != wave || n > 4 * kSelHeld) read(b0);
+#pragma unroll
+                    for (int e = 0; e < kSelHeld; ++e) {
+                        if (b0 + 4 * e >= n) break;
+                        if (col[e] >= 0) use(order_key(v[e], nan_last), col[e]);
+                    }
+                }
+            };
+            read(wave);
+            uint32_t best = 0;
+            for_keys([&](uint32_t key, int) { best = max(best, key); });
+            maxima[tid] = best;
+            __syncthreads();
+            bound = max(bound, kth_of_maxima(maxima, take, lane));
+            __syncthreads();
+            for_keys([&](uint32_t key, int c) { if (key >= bound) gather(key, c); });
+            __syncthreads();
+        }
+        const int found = (int)ctrl[5];
+        picked = found <= kSelCand && (!by_block || ctrl[6] <= (uint32_t)kSelBlocks);      // uniform over the workgroup
+        if (picked) {
+            // place of every gathered key in (key desc, column asc) order
+            // (the loads of eight entries in flight together: the loop is their latency and nothing else)
+            if (tid < 8) c_ent[found + tid] = 0;
+            __syncthreads();
+            for (int i = tid; i < found; i += 256) {
+                const uint64_t me = c_ent[i];
+                int rank = 0;
+                for (int j = 0; j < found; j += 8) {
+                    uint64_t o[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[e] = c_ent[j + e];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) rank += o[e] > me ? 1 : 0;
+                }
+                if (rank < take) { s_key[rank] = (uint32_t)(me >> 32); s_col[rank] = ~(uint32_t)me; }
+            }
         }
         __syncthreads();
     }
@@ -456,7 +550,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
                 }
 #pragma unroll
                 for (int u = 0; u < kSelU; ++u) {
-                    const uint32_t key = order_key(v[u]);
+                    const uint32_t key = order_key(v[u], nan_last);
                     if (i0 + 64 * u + lane < w_end && (key & mask) == prefix)
                         atomicAdd(&hist[((key >> shift) & 255u) * kHistCopies + (lane & (kHistCopies - 1))], 1u);
                 }
@@ -518,7 +612,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
 #pragma unroll
             for (int u = 0; u < kSelU; ++u) {
                 const int i = i0 + 64 * u + lane;
-                const uint32_t key = order_key(v[u]);
+                const uint32_t key = order_key(v[u], nan_last);
                 const bool above = i < w_end && (all || key > prefix);
                 const bool tie = i < w_end && !all && key == prefix;
                 if (above) {
@@ -538,7 +632,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
             uint32_t key = 0;
             bool tie = false;
             if (i < w_end) {
-                key = order_key(vals[i]);
+                key = order_key(vals[i], nan_last);
                 tie = !all && key == prefix;
             }
             const uint64_t bal = __ballot(tie);
@@ -558,45 +652,72 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
         if (MODE == 0) {
             s_lab[i] = (int64_t)col;
         } else {
-            const int32_t* off = a.cand_off + q * (a.np + 1);
-            int lo = 0, hi = a.np;          // largest p with off[p] <= col
+            int lo = 0, hi = n_off;         // largest p with off[p] <= col
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
-                if (off[mid] <= (int32_t)col) lo = mid; else hi = mid;
+                if (off_at(mid) <= (int32_t)col) lo = mid; else hi = mid;
             }
             const int l = a.probe[q * a.np + lo];
-            const int64_t slot = a.list_off[l] + ((int32_t)col - off[lo]);
+            const int64_t slot = a.list_off[l] + ((int32_t)col - off_at(lo));
             s_lab[i] = a.ids ? a.ids[slot] : slot;       // without a label table the slot itself is the result
         }
     }
     __syncthreads();
 
-    // bitonic sort, descending key then ascending label; empty entries (key 0, label max) sink
-    for (int size = 2; size <= kpad; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < kpad / 2; i += 256) {
-                const int lo_i = 2 * i - (i & (stride - 1));
-                const int hi_i = lo_i + stride;
-                const bool up = ((lo_i & size) == 0);
-                const uint32_t k0 = s_key[lo_i], k1 = s_key[hi_i];
-                const int64_t l0 = s_lab[lo_i], l1 = s_lab[hi_i];
-                const bool first_before = (k0 > k1) || (k0 == k1 && l0 <= l1);   // lo already precedes hi
-                if (first_before != up) {
-                    s_key[lo_i] = k1; s_key[hi_i] = k0;
-                    s_lab[lo_i] = l1; s_lab[hi_i] = l0;
-                    const uint32_t c0 = s_col[lo_i]; s_col[lo_i] = s_col[hi_i]; s_col[hi_i] = c0;
+    // order by (key desc, label asc); empty entries (key 0, label max) sink
+    auto put = [&](int i, uint32_t key, int64_t lab) {
+        const bool real = i < take && key != 0u;
+        float v = real ? order_value(key) : -__builtin_inff();
+        if (MODE == 1 && a.metric) v = metric_value(a.metric, v, a.qnorm[q]);
+        if (a.out_vals) a.out_vals[row * k + i] = v;
+        if (MODE == 0) { if (a.out_i32) a.out_i32[row * k + i] = real ? (int32_t)lab : -1; }
+        else { if (a.out_i64) a.out_i64[row * k + i] = real ? lab : -1; }
+        if (MODE == 0) s_col[i] = real ? (uint32_t)lab : 0xFFFFFFFFu;
+    };
+    if (kpad <= 256) {
+        const uint32_t key = tid < take ? s_key[tid] : 0u;
+        // (the short cut's winners are in this order already but for equal keys)
+        const bool tie = tid + 1 < take && key == s_key[tid + 1];
+        if (__syncthreads_or(tie || !picked)) {
+            const int64_t lab = tid < kpad ? s_lab[tid] : 0;
+            int rank = tid;                          // an empty place
+            if (tid < take) {
+                rank = 0;
+#pragma unroll 4
+                for (int j = 0; j < take; ++j) {
+                    const uint32_t kj = s_key[j];
+                    const int64_t lj = s_lab[j];
+                    rank += (int)(kj > key) | ((int)(kj == key) & ((int)(lj < lab) | ((int)(lj == lab) & (int)(j < tid))));
                 }
             }
-            __syncthreads();
+            if (tid < k) put(rank, key, lab);
+        } else if (tid < k) {
+            put(tid, key, s_lab[tid]);
         }
+    } else {
+        for (int size = 2; size <= kpad; size <<= 1) {
+            for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                for (int i = tid; i < kpad / 2; i += 256) {
+                    const int lo_i = 2 * i - (i & (stride - 1));
+                    const int hi_i = lo_i + stride;
+                    const bool up = ((lo_i & size) == 0);
+                    const uint32_t k0 = s_key[lo_i], k1 = s_key[hi_i];
+                    const int64_t l0 = s_lab[lo_i], l1 = s_lab[hi_i];
+                    const bool first_before = (k0 > k1) || (k0 == k1 && l0 <= l1);   // lo already precedes hi
+                    if (first_before != up) {
+                        s_key[lo_i] = k1; s_key[hi_i] = k0;
+                        s_lab[lo_i] = l1; s_lab[hi_i] = l0;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        for (int i = tid; i < k; i += 256) put(i, s_key[i], s_lab[i]);
     }
-
-    for (int i = tid; i < k; i += 256) {
-        const bool real = i < take;
-        const float v = real ? vals[s_col[i]] : -__builtin_inff();
-        if (a.out_vals) a.out_vals[row * k + i] = v;
-        if (MODE == 0) { if (a.out_i32) a.out_i32[row * k + i] = real ? (int32_t)s_lab[i] : -1; }
-        else { if (a.out_i64) a.out_i64[row * k + i] = real ? s_lab[i] : -1; }
+    // mode 0: the candidate offsets follow from the probes, which are in LDS (the running sums take the place of the labels)
+    if (MODE == 0 && a.cand.cand_off) {
+        __syncthreads();
+        if (wave == 0) cand_offsets_wave(a.cand, row, k, reinterpret_cast<const int32_t*>(s_col), reinterpret_cast<int32_t*>(s_lab), lane);
     }
 }
 
@@ -610,9 +731,6 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
 // every pass takes them from registers; columns beyond that (long rows are rare) are re-read from
 // memory in each pass.  A wavefront needs little LDS, so many rows are in flight per compute unit.  A final bitonic pass over the lanes orders the winners by (value desc, label asc).
 
-// MODE 2 and 3 are the two halves of a selection in two steps, for calls with so few rows that one wavefront
-// per row would leave the chip idle: MODE 2 takes the k best of every (query, probed list) stretch of a score
-// row, with labels, MODE 3 the k best of a query's np * k survivors (labels looked up, not computed).
 constexpr int kSmallM = 16384;
 constexpr int kShortcutTake = 32;     // the lane-maxima short cut pays up to this many winners (beyond, too many keys reach the bound)
 
@@ -628,27 +746,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     const int64_t row = (int64_t)blockIdx.x * 4 + wave;
     if (MODE == 0) clear_buckets(a.cand);
     if (row >= a.rows) return;
-    // MODE 2: row = (query, probe rank); the stretch of that list in the query's score row
-    const int64_t q = MODE == 2 ? row / a.np : row;
-    const int sub_p = MODE == 2 ? (int)(row % a.np) : 0;
-    int m, sub_off = 0;
-    if (MODE == 0 || MODE == 3) {
-        m = a.m_fixed;
-    } else if (MODE == 1) {
-        m = a.cand_off[q * (a.np + 1) + (a.p_limit ? a.p_limit[q] : a.np)];
-    } else {
-        const int32_t* off = a.cand_off + q * (a.np + 1);
-        sub_off = off[sub_p];
-        m = (a.p_limit && sub_p >= a.p_limit[q]) ? 0 : off[sub_p + 1] - sub_off;
-    }
+    const int64_t q = row;
+    const int m = MODE == 0 ? a.m_fixed : a.cand_off[q * (a.np + 1) + (a.p_limit ? a.p_limit[q] : a.np)];
     const int k = a.k;
     const int take = m < k ? m : k;
-    const float* vals = MODE == 2 ? a.vals + (row / a.np) * a.stride + sub_off
-                                  : a.vals + row * a.stride;
+    const float* vals = a.vals + row * a.stride;
     uint32_t* hist = s_work[wave];                                      // [256]
     int* win_col = reinterpret_cast<int*>(hist + 256);                  // [64]
     const float ninf = -__builtin_inff();
-    auto key_of = [](float v) -> uint32_t { return v != v ? 0u : order_key(v); };   // NaN sorts last
+    auto key_of = [](float v) -> uint32_t { return order_key(v, true); };
 
     win_col[lane] = -1;
     uint32_t keys[NV];                                   // key of column e*64 + lane (unused beyond m)
@@ -920,16 +1026,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     // labels, then order equal values by label
     int64_t lab = INT64_MAX;
     if (out_c >= 0) {
-        if (MODE == 0) {
-            lab = out_c;
-        } else if (MODE == 2) {
-            const int64_t slot = a.list_off[a.probe[q * a.np + sub_p]] + out_c;
-            lab = a.ids ? a.ids[slot] : slot;
-        } else if (MODE == 3) {
-            lab = a.lab_in[row * a.m_fixed + out_c];
-        } else {
-            lab = 0;      // placeholder, resolved below by the whole wavefront
-        }
+        lab = MODE == 0 ? out_c : 0;      // (mode 1: a placeholder, resolved below by the whole wavefront)
     }
     if (MODE == 1) {
         // probe rank of each winner: the last p with cand_off[p] <= column.  Up to 256 probes the row of
@@ -968,7 +1065,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     // order the winners by (value desc, label asc): a bitonic network over the first nsort >= take lanes
     // (the others hold nothing); the value travels as its key and is decoded at the end
     uint32_t key = out_c >= 0 ? key_of(out_v) : 0u;
-    if (MODE == 3 && lab < 0) key = 0u;              // a survivor slot that the first step left empty
     const int nsort = take <= 8 ? 8 : take <= 16 ? 16 : take <= 32 ? 32 : 64;
 #pragma unroll
     for (int size = 2; size <= 64; size <<= 1) {
@@ -984,7 +1080,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
             if (!keep) { key = ok; lab = ol; }
         }
     }
-    out_v = __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);     // inverse of order_key
+    out_v = order_value(key);
     if (lane < k) {
         const bool real = key != 0u;
         if (a.out_vals) a.out_vals[row * k + lane] = real ? out_v : ninf;
@@ -1130,7 +1226,8 @@ __global__ __launch_bounds__(1024) void k_redo_select(RedoSelectArgs a) {
             }
         for (int i = tid; i < a.k; i += 1024) {
             const uint32_t key = i < take ? (uint32_t)(s_comp[i] >> 32) : 0u;
-            a.out_vals[q * a.k + i] = i < take ? __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key) : -__builtin_inff();
+            const float v = i < take ? order_value(key) : -__builtin_inff();
+            a.out_vals[q * a.k + i] = a.metric ? metric_value(a.metric, v, a.qnorm[q]) : v;
             a.out_i64[q * a.k + i] = i < take ? s_lab[i] : -1;
         }
         __syncthreads();
@@ -1356,36 +1453,23 @@ hipError_t launch_redo_select(const RedoSelectArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_metric_finish(float* scores, int64_t nq, int k, int metric, const float* qnorm, hipStream_t st) {
-    if (nq <= 0 || metric == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_metric_finish, dim3((unsigned)((nq * k + 255) / 256)), dim3(256), 0, st, scores, nq, k, metric, qnorm);
-    return hipGetLastError();
-}
-
 // Longest row the one-wavefront-per-row kernel takes.  Probe selection (mode 0, every row has m_fixed values):
 // its short cuts (up to 64 winners) beat the workgroup-per-row kernel well beyond the columns it holds in
 // registers (10,000 rows over 4096 cells: 0.069 ms for 32 winners, against 0.145 ms); result rows (mode 1)
 // are mostly much shorter than their bound.
 constexpr int kSmallMax0Shortcut = 8192, kSmallMax1 = kSmallM;
+// Up to that many rows a workgroup each is faster all the same, the launch being bound by the latency of one row (probes of
+// 16 / 256 / 1000 queries over 4096 / 4096 / 1000 cells: 9.3 / 12.3 / 7.7 us, with one wavefront each 15.9 / 20.9 /
+// 8.9; 10,000 over 4096: 71 against 63).
+constexpr int64_t kSelFewRows = 2048;
 hipError_t launch_select(int mode, const SelectArgs& a_in, hipStream_t st) {
     if (a_in.rows <= 0) return hipSuccess;
     SelectArgs a = a_in;
-    if (mode == 2 || mode == 3) {
-        if (a.k > 64 || (mode == 3 && !a.lab_in)) return hipErrorInvalidValue;
-        const int bound = mode == 2 ? a.m_bound : a.m_fixed;
-        const unsigned blocks = (unsigned)((a.rows + 3) / 4);
-        if (mode == 2) {
-            if (bound <= 1536) hipLaunchKernelGGL((k_select_small<2, 16>), dim3(blocks), dim3(256), 0, st, a);
-            else hipLaunchKernelGGL((k_select_small<2, 32>), dim3(blocks), dim3(256), 0, st, a);
-        } else {
-            if (bound <= 1536) hipLaunchKernelGGL((k_select_small<3, 16>), dim3(blocks), dim3(256), 0, st, a);
-            else hipLaunchKernelGGL((k_select_small<3, 32>), dim3(blocks), dim3(256), 0, st, a);
-        }
-        return hipGetLastError();
-    }
     // short rows and small k: the one-wavefront-per-row kernel
     const int m_bound = mode == 0 ? a.m_fixed : a.m_bound;
-    if (a.k <= 64 && m_bound > 0 && m_bound <= (mode == 0 ? kSmallMax0Shortcut : kSmallMax1)) {
+    const bool small = a.k <= 64 && m_bound > 0 && m_bound <= (mode == 0 ? kSmallMax0Shortcut : kSmallMax1);
+    if (!a.blk_max) a.nan_last = small;      // (what is no number is no cell and no result, as the one-wavefront kernel has it)
+    if (small && !a.blk_max && a.rows > kSelFewRows) {
         const size_t lds = 0;
         const unsigned blocks = (unsigned)((a.rows + 3) / 4);
 #define IVFTQ_SMALL(NVV)                                                                            \
@@ -1400,7 +1484,7 @@ hipError_t launch_select(int mode, const SelectArgs& a_in, hipStream_t st) {
     int kpad = 1;
     while (kpad < a.k) kpad <<= 1;
     const int copies = (m_bound == 0 || m_bound > 8192) ? 8 : 1;
-    const size_t lds = (256 * copies + 8 + 4) * 4 + (size_t)kpad * 8 + 8 + (size_t)kpad * 8 + (size_t)kSelCand * 8;
+    const size_t lds = (256 * copies + 8 + 4) * 4 + (size_t)kpad * 8 + (size_t)kpad * 8 + (size_t)(kSelCand + 8 + kSelBlocks) * 8;
     const unsigned wgs = (unsigned)a.rows;
     if (copies == 8) {
         if (mode == 0) hipLaunchKernelGGL((k_select<0, 8>), dim3(wgs), dim3(256), lds, st, a);
@@ -1408,11 +1492,6 @@ hipError_t launch_select(int mode, const SelectArgs& a_in, hipStream_t st) {
     } else {
         if (mode == 0) hipLaunchKernelGGL((k_select<0, 1>), dim3(wgs), dim3(256), lds, st, a);
         else hipLaunchKernelGGL((k_select<1, 1>), dim3(wgs), dim3(256), lds, st, a);
-    }
-    if (mode == 0 && a.cand.cand_off) {
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_cand_offsets, dim3((unsigned)((a.rows + 3) / 4)), dim3(256), 0, st, a.out_i32, a.rows, a.k, a.cand);
     }
     return hipGetLastError();
 }

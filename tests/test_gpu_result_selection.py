@@ -1,0 +1,85 @@
+"""Selection of the results of a streaming search (mode 1) from the block maxima that its scan leaves: lists that are empty,
+around whole blocks of 64 and long, so that a query has few blocks or many next to its results; 1 to 193 results (192 is the
+most the short cut takes, 24 / 25 the line between its two bounds); many equal scores; more probes than are staged in LDS.
+Against float64 scores of every candidate.  A score is coarse + gamma * (a float32 sum of d products), so it is within
+gamma |z| |C| d 2^-24 < 1e-5 of float64 for the gamma <= 1.2, |C| <= 2 and d = 48 used here, plus the 2e-7 of the coarse term."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5
+D, B = 48, 4
+
+
+def _index(sizes, rng, tied, **kw):
+    import paper_2605_17415_amd as pkg
+    L, n = len(sizes), int(sum(sizes))
+    cell = rng.permutation(np.repeat(np.arange(L), sizes)).astype(np.int32)
+    cent = rng.standard_normal((L, D)).astype(np.float32)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    codes = rng.integers(0, 1 << B, (n, D)).astype(np.uint8)
+    gamma = rng.uniform(0.2, 1.2, n).astype(np.float16)
+    if tied:                                         # a handful of different vectors, over and over
+        codes, gamma = codes[rng.integers(0, 5, n)], np.full(n, 0.5, np.float16)
+    ix = pkg.Index(D, B, L, rotation_seed=5)
+    ix.set_coarse(cent)
+    ix.add_encoded(*[torch.from_numpy(v).to("cuda:0") for v in (cell, codes, gamma)])
+    return ix, cell, cent, codes, gamma
+
+
+def _scores(ix, q, cell, cent, codes, gamma):
+    q = q.astype(np.float64) / np.linalg.norm(q.astype(np.float64), axis=1, keepdims=True)
+    level = ix.get_codebook()[0].astype(np.float64)[codes]
+    z = q @ ix.get_rotation().astype(np.float64).T
+    return (q @ cent.astype(np.float64).T)[:, cell] + gamma.astype(np.float64) * (z @ level.T)
+
+
+@pytest.mark.parametrize("shape,nprobe,tied", [("edges", 9, False), ("edges", 20, False), ("edges", 20, True), ("long", 4, False), ("long", 4, True),
+                                               ("few", 3, False), ("many", 300, False)])
+@pytest.mark.parametrize("k", [1, 10, 24, 25, 100, 192, 193])
+def test_streaming_results(shape, nprobe, tied, k):
+    rng = np.random.default_rng(len(shape) + 10 * nprobe + k)
+    sizes = {"edges": [0, 1, 63, 64, 65, 0, 127, 128, 129, 0, 0, 191, 255, 256, 257, 300, 511, 512, 513, 64],
+             "long": [6000, 1, 0, 70, 4097, 3000], "few": [40, 0, 3], "many": rng.integers(0, 200, 320).tolist()}[shape]
+    print(f"[selection] {shape} nprobe={nprobe} tied={tied} k={k}", flush=True)
+    ix, cell, cent, codes, gamma = _index(sizes, rng, tied)
+    ix.set_search_mode(1)
+    for nq in (1, 66):
+        q = rng.standard_normal((nq, D)).astype(np.float32)
+        qd = torch.from_numpy(q).to("cuda:0")
+        probe = ix.coarse_probe(qd, nprobe)[0].cpu().numpy()
+        got_s, got_i = [t.cpu().numpy() for t in ix.search(qd, nprobe, k)]
+        true = _scores(ix, q, cell, cent, codes, gamma)
+        for r in range(nq):
+            cand = np.flatnonzero(np.isin(cell, probe[r]))
+            take = min(k, len(cand))
+            ids = got_i[r, :take]
+            assert len(set(ids.tolist())) == take and set(ids.tolist()) <= set(cand.tolist())
+            assert (got_i[r, take:] == -1).all() and np.isneginf(got_s[r, take:]).all()
+            np.testing.assert_allclose(got_s[r, :take], true[r, ids], rtol=0, atol=TOL)
+            np.testing.assert_allclose(got_s[r, :take], np.sort(true[r, cand])[::-1][:take], rtol=0, atol=TOL)
+            same = got_s[r, :take][:-1] == got_s[r, :take][1:]
+            assert (np.diff(got_s[r, :take]) <= 0).all() and (np.diff(ids)[same] > 0).all()
+    ix.close()
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("nq", [5, 300])
+def test_a_query_without_a_norm_leaves_the_others_alone(mode, nq):
+    """infinite and zero queries: no results for the first, coarse term 0 for the second, and nobody else's change"""
+    rng = np.random.default_rng(nq)
+    ix, *_ = _index([300] * 16, rng, False)
+    ix.set_search_mode(mode)
+    q = rng.standard_normal((nq, D)).astype(np.float32)
+    want = [t.cpu().numpy() for t in ix.search(torch.from_numpy(q).to("cuda:0"), 4, 10)]
+    q[1, 3] = np.inf
+    q[nq - 2] = 0.0
+    got = [t.cpu().numpy() for t in ix.search(torch.from_numpy(q).to("cuda:0"), 4, 10)]
+    others = np.setdiff1d(np.arange(nq), [1, nq - 2])
+    np.testing.assert_array_equal(got[0][others], want[0][others])
+    np.testing.assert_array_equal(got[1][others], want[1][others])
+    assert (got[1][1] == -1).all() and np.isneginf(got[0][1]).all()
+    assert (got[0][nq - 2] == 0.0).all()
+    ix.close()
