@@ -12,6 +12,8 @@
 // Arithmetic: both operands are used in split float16 form (split_f16.h) on
 // v_mfma_f32_32x32x16_f16 with float32 accumulation, so a score differs from the float32 dot
 // product by about 2e-7, well inside the 1e-5 near-tie allowance, at the float16 matrix rate.
+#include <type_traits>
+
 #include "kernels.h"
 #include "split_f16.h"
 
@@ -83,7 +85,7 @@ __device__ __forceinline__ bool load_rows(const float* __restrict__ x, int64_t r
 // Workgroup (x, y) takes the row block x and the stages [y * per_y, y * per_y + per_y) of both tables together.
 // R = 32-row tiles per wavefront.  VEC4: rows are read 16 bytes at a time (d % 4 == 0, x 16-byte aligned).
 template <int DP, int R, bool VEC4>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_coarse(CoarseArgs a, int per_y) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 ? 3 : 2))) void k_coarse(CoarseArgs a, int per_y) {
     using Cfg = CoarseCfg<DP>;
     constexpr int KB = Cfg::KB;
     extern __shared__ unsigned char lds_raw[];
@@ -96,10 +98,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int cent_stages = a.Lpad / kTN, stages = coarse_stages(a);
     const int s_lo = (int)blockIdx.y * per_y, s_hi = s_lo + per_y < stages ? s_lo + per_y : stages;
 
+    // A stage's rows (hi and lo) travel global memory -> registers while the stage before is multiplied and stored, the first
+    // one's while the data rows are read, then registers -> LDS, 16 bytes at a time.  (Up to 128 coordinates: one query 28.9 -> 26.4 us,
+    // 16 over 10M x 96 55.3 -> 52.8.  Beyond that the registers cost a wavefront per SIMD, and a stage is read when the one before is done.)
+    constexpr bool kAhead = DP <= 128;
+    constexpr int kPieces = kTN * (DP / 8), kPer = (kPieces + 255) / 256;
+    typedef uint32_t piece __attribute__((ext_vector_type(4)));
+    piece pre_h[kAhead ? kPer : 1], pre_l[kAhead ? kPer : 1];      // (a native vector: arrays of uint4 went through scratch memory)
+#define IVFTQ_COARSE_FETCH(S)                                                                                    \
+    {                                                                                                            \
+        const bool rot_ = (S) >= cent_stages;                                                                    \
+        const int c0_ = (rot_ ? (S) - cent_stages : (S)) * kTN;                                                  \
+        const uint16_t* src_h_ = rot_ ? a.pi_h : a.cent_h;                                                       \
+        const uint16_t* src_l_ = rot_ ? a.pi_l : a.cent_l;                                                       \
+        const int last_ = (rot_ ? a.pitch : a.Lpad) - 1;      /* Pi has `pitch` rows, not a whole number of stages */ \
+        _Pragma("unroll") for (int i = 0; i < kPer; ++i) {                                                       \
+            const int e_ = tid + 256 * i < kPieces ? tid + 256 * i : kPieces - 1, r_ = c0_ + e_ / (DP / 8);      \
+            const int64_t src_ = (int64_t)(r_ < last_ ? r_ : last_) * a.pitch + e_ % (DP / 8) * 8;               \
+            pre_h[i] = *reinterpret_cast<const piece*>(src_h_ + src_);                                           \
+            pre_l[i] = *reinterpret_cast<const piece*>(src_l_ + src_);                                           \
+        }                                                                                                        \
+    }
+    if constexpr (kAhead) IVFTQ_COARSE_FETCH(s_lo)
+
     half8 bh[R][KB], bl[R][KB];
+    bool any[R];                         // (whether the tile has a row at all: a few queries leave most tiles without)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t row = row0 + 32 * r + j;
+        any[r] = !kAhead || row0 + 32 * r < a.n;
+        if (!any[r]) continue;
         float norm;
         load_rows<DP>(a.x, row, row < a.n, a.d, VEC4 ? 1 : 0, half, bh[r], bl[r], &norm);
         if (a.norm_out && s_lo == 0 && half == 0 && row < a.n) a.norm_out[row] = norm;
@@ -111,18 +139,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     for (int s = s_lo; s < s_hi; ++s) {
         const bool rotate = s >= cent_stages;
         const int c0 = (rotate ? s - cent_stages : s) * kTN;
-        const uint16_t* src_h = rotate ? a.pi_h : a.cent_h;
-        const uint16_t* src_l = rotate ? a.pi_l : a.cent_l;
-        const int last = (rotate ? a.pitch : a.Lpad) - 1;            // Pi has `pitch` rows, not a whole number of stages
         __syncthreads();
-        // stage TN rows of the table (hi and lo) into LDS, 16 bytes at a time
-        for (int e = tid; e < kTN * (DP / 8); e += 256) {
-            const int r = e / (DP / 8), c8 = e % (DP / 8);
-            const int64_t src = (int64_t)(c0 + r < last ? c0 + r : last) * a.pitch + c8 * 8;
-            *reinterpret_cast<uint4*>(th + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(src_h + src);
-            *reinterpret_cast<uint4*>(tl + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(src_l + src);
+        if constexpr (kAhead) {
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                const int e = tid + 256 * i;
+                if (kPieces % 256 == 0 || e < kPieces) {
+                    *reinterpret_cast<piece*>(th + e / (DP / 8) * Cfg::LDH + e % (DP / 8) * 8) = pre_h[i];
+                    *reinterpret_cast<piece*>(tl + e / (DP / 8) * Cfg::LDH + e % (DP / 8) * 8) = pre_l[i];
+                }
+            }
+        } else {
+            const uint16_t* src_h = rotate ? a.pi_h : a.cent_h;
+            const uint16_t* src_l = rotate ? a.pi_l : a.cent_l;
+            const int last = (rotate ? a.pitch : a.Lpad) - 1;
+            for (int e = tid; e < kPieces; e += 256) {
+                const int r = e / (DP / 8), c8 = e % (DP / 8);
+                const int64_t src = (int64_t)(c0 + r < last ? c0 + r : last) * a.pitch + c8 * 8;
+                *reinterpret_cast<uint4*>(th + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(src_h + src);
+                *reinterpret_cast<uint4*>(tl + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(src_l + src);
+            }
         }
         __syncthreads();
+        if constexpr (kAhead)
+            if (s + 1 < s_hi) IVFTQ_COARSE_FETCH(s + 1)
+        if (row0 >= a.n) continue;
 
         floatx16 acc[R][kNT];
 #pragma unroll
@@ -131,20 +172,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             for (int t = 0; t < kNT; ++t)
 #pragma unroll
                 for (int q = 0; q < 16; ++q) acc[r][t][q] = 0.f;
+        auto multiply = [&](auto tiles) {
+            constexpr int RR = decltype(tiles)::value;
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
+            for (int kb = 0; kb < KB; ++kb) {
 #pragma unroll
-            for (int t = 0; t < kNT; ++t) {
-                const half8 ah = *reinterpret_cast<const half8*>(ah_base + t * 32 * Cfg::LDH + 16 * kb);
-                const half8 al = *reinterpret_cast<const half8*>(al_base + t * 32 * Cfg::LDH + 16 * kb);
+                for (int t = 0; t < kNT; ++t) {
+                    const half8 ah = *reinterpret_cast<const half8*>(ah_base + t * 32 * Cfg::LDH + 16 * kb);
+                    const half8 al = *reinterpret_cast<const half8*>(al_base + t * 32 * Cfg::LDH + 16 * kb);
 #pragma unroll
-                for (int r = 0; r < R; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[r][kb], acc[r][t], 0, 0, 0);
+                    for (int r = 0; r < RR; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[r][kb], acc[r][t], 0, 0, 0);
 #pragma unroll
-                for (int r = 0; r < R; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[r][kb], acc[r][t], 0, 0, 0);
+                    for (int r = 0; r < RR; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[r][kb], acc[r][t], 0, 0, 0);
 #pragma unroll
-                for (int r = 0; r < R; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[r][kb], acc[r][t], 0, 0, 0);
+                    for (int r = 0; r < RR; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[r][kb], acc[r][t], 0, 0, 0);
+                }
             }
-        }
+        };
+        if (R == 1 || any[R - 1]) multiply(std::integral_constant<int, R>{});
+        else multiply(std::integral_constant<int, 1>{});
 
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -180,6 +226,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         }
     }
 }
+
+#undef IVFTQ_COARSE_FETCH
 
 // Screening pass of the argmax: only the hi*hi products (one MFMA per block instead of three).  With
 // unit vectors the result is off by at most (2^-10 + 2^-22) * sum|a_j b_j| <= 9.8e-4 plus float32
