@@ -778,7 +778,8 @@ namespace {
 // Coarse assignment of n rows (Algorithm "Encode", nearest centroid by inner product; with a bias, k-means' nearest
 // mean): screening pass plus the exact pass over the rows it left undecided.  w_flag[0] = a row without a usable
 // norm, w_flag[1] = number of undecided rows, both cleared by the caller.
-constexpr int64_t kScreenShareRows = 1 << 18;     // from here on the row tiles alone fill the chip
+// Room (12 MB) for the partial results of rows whose centroid stages are shared out; a call of fewer rows takes less.
+constexpr int64_t kScreenPartEntries = 1 << 20;
 ivftq_status assign_rows(ivftq_index* ix, const float* x_dev, int64_t n, const uint16_t* cent_h, const uint16_t* cent_l,
                          const float* bias, int32_t* assign, hipStream_t st) {
     // keys (8 bytes each) first, then the row numbers
@@ -790,11 +791,9 @@ ivftq_status assign_rows(ivftq_index* ix, const float* x_dev, int64_t n, const u
     a.assign = assign; a.flag = ix->w_flag.as<int>(); a.row_count = ix->w_flag.as<int>() + 1;
     a.row_key = ix->w_undecided.as<unsigned long long>();
     a.row_list = reinterpret_cast<int32_t*>(a.row_key + n);
-    // short batches share the centroid stages out over several workgroups and need room for the partial results
-    if (n < kScreenShareRows) {
-        HIP_TRY(ix->w_part.ensure((size_t)n * kScreenMaxShares * 3 * sizeof(float)));
-        a.part = ix->w_part.as<float>();
-    }
+    a.part_entries = std::min<int64_t>(round_up64(n, 256) * kScreenMaxShares, kScreenPartEntries);
+    HIP_TRY(ix->w_part.ensure((size_t)a.part_entries * 3 * sizeof(float)));
+    a.part = ix->w_part.as<float>();
     HIP_TRY(timed(ix, st, P_ASSIGN, [&] { return launch_coarse_screened(a, st); }));
     return IVFTQ_OK;
 }

@@ -285,21 +285,25 @@ template <int DP, int R, bool VEC4, bool BIAS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 || R == 1) ? 3 : 2))) void k_coarse_screen(
     const float* __restrict__ x, int64_t n, int d, const uint16_t* __restrict__ cent_h, int cent_pitch,
     const float* __restrict__ bias, int L, int Lpad, int32_t* __restrict__ assign, int32_t* __restrict__ row_list,
-    unsigned long long* __restrict__ row_key, int* __restrict__ row_count, float* __restrict__ part) {
+    unsigned long long* __restrict__ row_key, int* __restrict__ row_count, float* __restrict__ part, int whole, int shares) {
     using Cfg = CoarseCfg<DP>;
     constexpr int KB = Cfg::KB;
     extern __shared__ unsigned char lds_raw[];
     constexpr int NT = screen_nt<DP>(), TN = NT * 32;
-    // gridDim.y > 1 (short batches): workgroup (x, y) takes the y-th share of the centroid stages and leaves
-    // (best, second best, index) of every row in `part`; k_coarse_screen_join puts the shares together
-    const int n_stages = Lpad / TN, per_y = (n_stages + (int)gridDim.y - 1) / (int)gridDim.y;
-    const int c_lo = (int)blockIdx.y * per_y * TN < Lpad ? (int)blockIdx.y * per_y * TN : Lpad;
-    const int c_hi = c_lo + per_y * TN < Lpad ? c_lo + per_y * TN : Lpad;
+    // The first `whole` row blocks are one workgroup's each.  Every later one is shared by `shares` workgroups: each takes its
+    // share of the centroid stages and leaves (best, second best, index) of every row in `part`, where
+    // k_coarse_screen_join puts them together.
+    const bool split = (int)blockIdx.x >= whole;
+    const int rest = (int)blockIdx.x - whole;
+    const int block = split ? whole + rest / shares : (int)blockIdx.x, share = split ? rest % shares : 0;
+    const int n_stages = Lpad / TN, per_share = split ? (n_stages + shares - 1) / shares : n_stages;
+    const int c_lo = share * per_share * TN < Lpad ? share * per_share * TN : Lpad;
+    const int c_hi = c_lo + per_share * TN < Lpad ? c_lo + per_share * TN : Lpad;
     uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [2][TN][LDH] hi parts of the centroids
     float* s_bias = reinterpret_cast<float*>(th + 2 * TN * Cfg::LDH);   // [2][TN] 2^20 bias (BIAS only)
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, j = lane & 31;
-    const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (32 * R);
+    const int64_t row0 = ((int64_t)block * 4 + wave) * (32 * R);
 
     half8 bh[R][KB];
     bool good[R];
@@ -411,9 +415,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
         const float b2 = fmaxf(best[r], ob);
         if (ob > best[r]) idx = oi;
         const int64_t row = row0 + 32 * r + j;
-        if (gridDim.y > 1) {
+        if (split) {
             if (row < n && half == 0) {
-                float* pp = part + (row * (int64_t)gridDim.y + blockIdx.y) * 3;
+                float* pp = part + ((row - (int64_t)whole * (4 * 32 * R)) * shares + share) * 3;
                 pp[0] = b2;
                 pp[1] = s2;
                 pp[2] = __int_as_float(good[r] ? idx : -1 - idx);
@@ -434,17 +438,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
 #undef IVFTQ_SCREEN_TAKE
 
 // Shares of a row's screening pass put together: the best of the bests, and as second best the largest of
-// every share's second best and of the bests that lost; then the same decision as in the kernel itself.
-__global__ void k_coarse_screen_join(const float* __restrict__ part, int64_t n, int shares, int32_t* __restrict__ assign,
+// every share's second best and of the bests that lost; then the same decision as in the kernel itself.  `part` starts
+// at the row first_row.
+__global__ void k_coarse_screen_join(const float* __restrict__ part, int64_t first_row, int64_t n, int shares, int32_t* __restrict__ assign,
                                      int32_t* __restrict__ row_list, unsigned long long* __restrict__ row_key,
                                      int* __restrict__ row_count) {
-    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, row = first_row + at;
     if (row >= n) return;
     float best = kScreenNone, second = kScreenNone;
     int idx = 0;
     bool good = true;
     for (int y = 0; y < shares; ++y) {
-        const float* pp = part + (row * shares + y) * 3;
+        const float* pp = part + (at * shares + y) * 3;
         const float b = pp[0], s2 = pp[1];
         int i = __float_as_int(pp[2]);
         if (i < 0) { good = false; i = -1 - i; }
@@ -555,23 +560,40 @@ __global__ void k_coarse_resolve_write(const int32_t* __restrict__ row_list, con
 // RS = 32-row tiles per wavefront of the screening kernel
 template <int DP, int RS, bool VEC4, bool BIAS>
 hipError_t run_screened_as(const ScreenArgs& a, hipStream_t st) {
-    static LdsLimit lim_screen, lim_resolve;
+    static LdsLimit lim_resolve;
+    static ChipFill fill;
     const size_t lds_screen = screen_lds_bytes<DP>(BIAS);
     const size_t lds = (size_t)2 * kTN * CoarseCfg<DP>::LDH * sizeof(uint16_t);
-    hipError_t e = lim_screen.ensure(reinterpret_cast<const void*>(k_coarse_screen<DP, RS, VEC4, BIAS>), lds_screen);
-    if (e == hipSuccess) e = lim_resolve.ensure(reinterpret_cast<const void*>(k_coarse_resolve<DP, VEC4, BIAS>), lds);
+    hipError_t e = lim_resolve.ensure(reinterpret_cast<const void*>(k_coarse_resolve<DP, VEC4, BIAS>), lds);
     if (e != hipSuccess) return e;
-    const int64_t blocks_s = (a.n + 4 * 32 * RS - 1) / (4 * 32 * RS);
-    // A short batch gives few workgroups, each walking every centroid stage on its own (90 us at 4096
-    // centroids however few rows there are): with room for the partial results the stages are shared out
-    // over gridDim.y until about 1024 workgroups are in the launch, at least two stages each.
+    constexpr int kBlockRows = 4 * 32 * RS;
+    unsigned held = 0, units = 0;
+    e = fill.get(reinterpret_cast<const void*>(k_coarse_screen<DP, RS, VEC4, BIAS>), 256, lds_screen, &held, &units);
+    if (e != hipSuccess) return e;
+    // Rounds of row blocks that fill the chip are a workgroup a block.  The blocks of a last round, or of a short batch, are
+    // shared out over the centroid stages where that is faster, given room for the partial results.  Measured (96 to
+    // 200 coordinates, 1024 and 4096 centroids, 500 to 500,000 rows, 1 to 16 shares): with m workgroups a compute unit a
+    // stage takes as m, one alone as 1.5; reading and splitting a workgroup's rows takes 4 stages, and the joining launch
+    // 3 us, about 350 / DP of them.  Both sides, us a call: 4096 centroids, 262,147 rows x 200 (one block of 1025 left over) 659
+    // whole, 558 in 16 shares; 170,000 x 200 472 and 379 (3); 65,000 x 96 103 and 79 (2); 100,000 x 96 116 and 120 (3); with
+    // 500 rows x 96 81 and 28 (16).  A finer split has to be cheaper by a 25th.
+    const int64_t blocks = (a.n + kBlockRows - 1) / kBlockRows;
+    const int64_t rest = blocks % held, n_stages = a.Lpad / (screen_nt<DP>() * 32);
     int shares = 1;
-    if (a.part)
-        while (shares < kScreenMaxShares && blocks_s * shares < 1024 && (a.Lpad / (screen_nt<DP>() * 32)) >= 4 * shares) shares *= 2;
-    hipLaunchKernelGGL((k_coarse_screen<DP, RS, VEC4, BIAS>), dim3((unsigned)blocks_s, (unsigned)shares), dim3(256), lds_screen, st, a.x, a.n, a.d,
-                       a.cent_h, a.cent_pitch, a.bias, a.L, a.Lpad, a.assign, a.row_list, a.row_key, a.row_count, a.part);
-    if (shares > 1)
-        hipLaunchKernelGGL(k_coarse_screen_join, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, (const float*)a.part, a.n, shares,
+    auto cost = [&](int64_t s) {           // in tenths of a stage
+        const int64_t m = (rest * s + units - 1) / units;
+        return (m <= 1 ? 15 : 10 * m) * ((n_stages + s - 1) / s + 4) + (s > 1 ? 3500 / DP : 0);
+    };
+    if (a.part && rest) {
+        int64_t least = cost(1);
+        for (int s = 2; s <= kScreenMaxShares && 2 * s <= n_stages && rest * kBlockRows * s <= a.part_entries; ++s)
+            if (25 * cost(s) < 24 * least) { least = cost(s); shares = s; }
+    }
+    const int64_t whole = shares > 1 ? blocks - rest : blocks, first = whole * kBlockRows;
+    hipLaunchKernelGGL((k_coarse_screen<DP, RS, VEC4, BIAS>), dim3((unsigned)(whole + (blocks - whole) * shares)), dim3(256), lds_screen, st, a.x, a.n, a.d,
+                       a.cent_h, a.cent_pitch, a.bias, a.L, a.Lpad, a.assign, a.row_list, a.row_key, a.row_count, a.part, (int)whole, shares);
+    if (first < a.n)
+        hipLaunchKernelGGL(k_coarse_screen_join, dim3((unsigned)((a.n - first + 255) / 256)), dim3(256), 0, st, (const float*)a.part, first, a.n, shares,
                            a.assign, a.row_list, a.row_key, a.row_count);
     // the undecided rows: about four centroid stages per workgroup, at most 512 x 16 workgroups
     const int stages = a.Lpad / kTN;

@@ -52,27 +52,30 @@ class LdsLimit {
 // (kernel, device) pair like LdsLimit.
 class ChipFill {
   public:
-    hipError_t get(const void* kernel, int threads, size_t lds, unsigned* wgs) {
+    hipError_t get(const void* kernel, int threads, size_t lds, unsigned* wgs, unsigned* compute_units = nullptr) {
         int dev = 0, held = 0, units = 0;
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= kDevices) return hipErrorInvalidDevice;
-        *wgs = wgs_[dev].load(std::memory_order_acquire);
-        if (*wgs) return hipSuccess;
-        e = limit_.ensure(kernel, lds);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&held, kernel, threads, lds);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        if (held < 1 || units < 1) return hipErrorLaunchOutOfResources;
-        *wgs = (unsigned)(held * units);
-        wgs_[dev].store(*wgs, std::memory_order_release);
+        uint64_t known = known_[dev].load(std::memory_order_acquire);
+        if (!known) {
+            e = limit_.ensure(kernel, lds);
+            if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&held, kernel, threads, lds);
+            if (e == hipSuccess) e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev);
+            if (e != hipSuccess) return e;
+            if (held < 1 || units < 1) return hipErrorLaunchOutOfResources;
+            known = (uint64_t)units << 32 | (uint32_t)(held * units);
+            known_[dev].store(known, std::memory_order_release);
+        }
+        *wgs = (unsigned)known;
+        if (compute_units) *compute_units = (unsigned)(known >> 32);
         return hipSuccess;
     }
 
   private:
     static constexpr int kDevices = 64;
     LdsLimit limit_;
-    std::atomic<unsigned> wgs_[kDevices] = {};
+    std::atomic<uint64_t> known_[kDevices] = {};        // compute units << 32 | workgroups
 };
 
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
@@ -121,15 +124,15 @@ hipError_t launch_coarse(const CoarseArgs& a, hipStream_t st);
 // two steps: a screening pass with the hi*hi products alone decides every row whose best score is clearly
 // ahead, the rest (listed in row_list, counted in *row_count, which the caller clears) is redone with all three
 // products.  row_list
-// and row_key are scratch arrays of n entries.  part (may be null): 3 * kScreenMaxShares floats of scratch
-// per row; with it a short batch shares the centroid stages out over several workgroups per row tile.
+// and row_key are scratch arrays of n entries.  part (may be null): scratch of part_entries x 3 floats; with it the
+// rows of a last, partly filled round of workgroups and those of a short batch are shared by up to kScreenMaxShares workgroups.
 // bias may be null (all zero); the centroids' norms must not exceed 1.
 constexpr int kScreenMaxShares = 16;
 struct ScreenArgs {
     const float* x; int64_t n; int d;
     const uint16_t* cent_h; const uint16_t* cent_l; int cent_pitch;
     const float* bias; int L; int Lpad;
-    int32_t* assign; int* flag; int32_t* row_list; unsigned long long* row_key; int* row_count; float* part;
+    int32_t* assign; int* flag; int32_t* row_list; unsigned long long* row_key; int* row_count; float* part; int64_t part_entries;
 };
 hipError_t launch_coarse_screened(const ScreenArgs& a, hipStream_t st);
 // hi[i], lo[i] = split float16 form of src[i]
