@@ -36,14 +36,28 @@ struct BatchCfg {
     static constexpr int PT = PAIR ? 1 << (2 * B) : 1 << B;
     // dense pass: both parts of the panel, and table entries of both parts (two codes: 8 bytes, one code: 4)
     static constexpr size_t lds_dense = (size_t)2 * TQ * LDH * sizeof(uint16_t) + 16 * TQ + (size_t)PT * (PAIR ? 8 : 4);
-    static constexpr size_t lds_threshold = (size_t)TQ * LDH * sizeof(uint16_t) + 16 * TQ + (size_t)PT * 4;
-    // Candidates of a tile held back by the threshold pass, as many as `occ` workgroups of a compute unit have room for (in
-    // whole allocation units, less the pass's static words), at most 4096.
+    // LDS of a workgroup when a compute unit holds `occ` of them (in whole allocation units, less the passes' static words)
+    static constexpr size_t room(int occ) { return 160 * 1024 / occ / 1280 * 1280 - 64; }
+    // Threshold pass.  The table is kept in several copies, entry e's c-th at e * copies + c, and a lane reads copy lane %
+    // copies: the 64 lanes of a look-up, each with a code pair of its own, collide on fewer banks.  Clocks of a compute unit per
+    // look-up by two workgroups: 1 copy 7.5, 2 8.1, 4 6.6, 8 6.0, 16 4.4, 32 4.4.  As many as there is room for beside 400 candidates
+    // held back, at most 16 (pass of 256 queries over 10M x 200 304 -> 280 us, 10,000 over 10M x 96 247 -> 240).  The dense pass
+    // keeps one: the room would cost it workgroups (10M x 96 with 16 copies 234 -> 305 us), and where it does not
+    // (10M x 200, 8 copies) they changed nothing.
+    static constexpr size_t panel_threshold = (size_t)TQ * LDH * sizeof(uint16_t) + 16 * TQ, table_threshold = (size_t)PT * 4;
+    static constexpr int copies_threshold(int occ, bool hold) {
+        for (int c = 16; c > 2; c /= 2)
+            if (panel_threshold + (hold ? 8 * 400 + 4 * TQ : 0) + c * table_threshold <= room(occ)) return c;
+        return 1;
+    }
+    // Candidates of a tile held back: what is left of the room, at most 4096.
     static constexpr int held_back(int occ) {
-        const size_t room = 160 * 1024 / occ / 1280 * 1280 - 64, fit = (room - lds_threshold - 4 * TQ) / 8;
+        const size_t fit = (room(occ) - panel_threshold - copies_threshold(occ, true) * table_threshold - 4 * TQ) / 8;
         return fit < 4096 ? (int)fit / 2 * 2 : 4096;
     }
-    static constexpr size_t lds_held_back(int occ) { return lds_threshold + 8 * (size_t)held_back(occ) + 4 * TQ; }
+    static constexpr size_t lds_threshold(int occ, bool hold) {
+        return panel_threshold + copies_threshold(occ, hold) * table_threshold + (hold ? 8 * (size_t)held_back(occ) + 4 * TQ : 0);
+    }
 };
 
 // The 8 codes of block kb that a lane de-quantises, coordinates 16*kb + 8*half + [0, 8), begin in word first_word
@@ -325,8 +339,9 @@ void k_batch_threshold(BatchScanArgs a) {
     extern __shared__ unsigned char lds_raw[];
     uint16_t* zh = reinterpret_cast<uint16_t*>(lds_raw);                       // [TQ][LDH] hi parts of the rotated queries
     uint4* s_row = reinterpret_cast<uint4*>(zh + Cfg::TQ * Cfg::LDH);          // [TQ] coarse term, threshold, pair number, |q|
-    uint32_t* tab = reinterpret_cast<uint32_t*>(s_row + Cfg::TQ);                // [PT] hi parts of a code pair, packed (or of one code)
-    uint2* s_cand = reinterpret_cast<uint2*>(tab + Cfg::PT);                     // HOLD: [CAND] score bits; column | vector of the part << 7 | place among the column's << 19
+    uint32_t* tab = reinterpret_cast<uint32_t*>(s_row + Cfg::TQ);                // [PT][TC] hi parts of a code pair, packed (or of one code)
+    constexpr int TC = Cfg::copies_threshold(OCC, HOLD);
+    uint2* s_cand = reinterpret_cast<uint2*>(tab + Cfg::PT * TC);                     // HOLD: [CAND] score bits; column | vector of the part << 7 | place among the column's << 19
     int* s_cnt = reinterpret_cast<int*>(s_cand + CAND);                          // HOLD: [TQ] held back per column, then their first position
     static_assert(Cfg::TQ <= 128 && kPartMax <= 4096, "fields of a candidate held back");
 
@@ -334,14 +349,15 @@ void k_batch_threshold(BatchScanArgs a) {
     const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, jl = lane & 31;
     constexpr float kUnscale = 1.f / (kSplitScale * kSplitScale);
 
-    for (int e = tid; e < Cfg::PT; e += NT) {
+    for (int e = tid; e < Cfg::PT * TC; e += NT) {
         uint32_t hp = 0;
 #pragma unroll
         for (int i = 0; i < (Cfg::PAIR ? 2 : 1); ++i)
-            hp |= (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(a.cb[(e >> (i * B)) & ((1 << B) - 1)] * kSplitScale)) << (16 * i);
+            hp |= (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(a.cb[(e / TC >> (i * B)) & ((1 << B) - 1)] * kSplitScale)) << (16 * i);
         tab[e] = hp;
     }
     const uint16_t* bh_base = zh + jl * Cfg::LDH + 8 * half;
+    const uint32_t* mine = tab + tid % TC;
     const int words = a.store.words;
     __shared__ __align__(16) int s_next[4];      // (16 bytes: the panel behind it keeps its alignment) [2] asked for, [3] held back if that is too many
     TileQueue queue(a, s_next);
@@ -418,10 +434,10 @@ void k_batch_threshold(BatchScanArgs a) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if constexpr (Cfg::PAIR) {
-                        hv[i] = tab[(uint32_t)(chunk >> (2 * B * i)) & (uint32_t)(Cfg::PT - 1)];
+                        hv[i] = mine[((uint32_t)(chunk >> (2 * B * i)) & (uint32_t)(Cfg::PT - 1)) * TC];
                     } else {
-                        const uint32_t e0 = tab[(uint32_t)(chunk >> (2 * B * i)) & (uint32_t)(Cfg::PT - 1)];
-                        const uint32_t e1 = tab[(uint32_t)(chunk >> (2 * B * i + B)) & (uint32_t)(Cfg::PT - 1)];
+                        const uint32_t e0 = mine[((uint32_t)(chunk >> (2 * B * i)) & (uint32_t)(Cfg::PT - 1)) * TC];
+                        const uint32_t e1 = mine[((uint32_t)(chunk >> (2 * B * i + B)) & (uint32_t)(Cfg::PT - 1)) * TC];
                         hv[i] = e0 | (e1 << 16);
                     }
                 }
@@ -577,7 +593,7 @@ hipError_t run_batch(const BatchScanArgs& a, hipStream_t st) {
         constexpr int OCC = S == 2 && DP + words <= 102 ? 3 : 2;
         constexpr bool HOLD = OCC == 2 || DP <= 64;
         using Cfg = BatchCfg<DP, B, NQ>;
-        constexpr size_t lds_plain = HOLD ? Cfg::lds_held_back(OCC) : Cfg::lds_threshold, lds_raw = Cfg::lds_held_back(2);
+        constexpr size_t lds_plain = Cfg::lds_threshold(OCC, HOLD), lds_raw = Cfg::lds_threshold(2, true);
         constexpr auto plain = k_batch_threshold<DP, B, NQ, 4, OCC, S, false, HOLD>;
         constexpr auto raw = k_batch_threshold<DP, B, NQ, 4, 2, S_RAW, true, true>;
         const size_t lds = a.metric ? lds_raw : lds_plain;
