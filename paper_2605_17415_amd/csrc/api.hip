@@ -355,12 +355,11 @@ ivftq_status check_index(const ivftq_index* ix) {
     return IVFTQ_OK;
 }
 
-// Rows per segment of the stable counting sort (one wavefront ranks a segment, one histogram row of L counters
-// per segment): as many segments as keep the chip busy (up to 4096), at least 128 rows each, and at most
-// 16M counters in all.
-int64_t segment_length(int64_t n, int L) {
-    const int64_t max_segments = std::max<int64_t>(64, std::min<int64_t>(4096, ((int64_t)16 << 20) / L));
-    return round_up64(std::max<int64_t>((n + max_segments - 1) / max_segments, 128), 64);
+// Rows per segment of the stable counting sort (one workgroup ranks a segment, one histogram row of L counters per
+// segment, written once and read twice): kRankRows, and more where that would be more than kMaxSegments segments.
+int64_t segment_length(int64_t n) {
+    const int64_t rows = (n + kMaxSegments - 1) / kMaxSegments;
+    return std::max<int64_t>(1, (rows + kRankRows - 1) / kRankRows) * kRankRows;
 }
 
 // The stream a call works on; remembered so that calls without a stream argument know what to wait for.
@@ -840,7 +839,7 @@ ivftq_status ivftq_train_coarse(ivftq_index* ix, const float* x_dev, int64_t n, 
 
     // The iterations run on tables of their own (t_*): the index keeps its centroids until training has succeeded.
     const size_t table = (size_t)ix->lpad * pitch;
-    const int64_t seg_len = segment_length(n, L);
+    const int64_t seg_len = segment_length(n);
     const int nseg = (int)((n + seg_len - 1) / seg_len);
     HIP_TRY(ix->w_rows.ensure((size_t)L * sizeof(int64_t)));
     HIP_TRY(ix->w_dst.ensure((size_t)L * sizeof(int32_t)));
@@ -923,7 +922,7 @@ namespace {
 ivftq_status place_rows(ivftq_index* ix, const int32_t* assign, int64_t n, bool zero_norm_flag, bool want_order,
                         std::vector<int64_t>& need, hipStream_t st) {
     const int L = ix->nlist;
-    const int64_t seg_len = segment_length(n, L);
+    const int64_t seg_len = segment_length(n);
     const int nseg = (int)((n + seg_len - 1) / seg_len);
     HIP_TRY(ix->w_hist.ensure((size_t)nseg * L * sizeof(uint32_t)));
     HIP_TRY(ix->w_count.ensure((size_t)L * sizeof(uint32_t)));

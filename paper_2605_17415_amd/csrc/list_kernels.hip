@@ -6,7 +6,7 @@
 // batch rows of the same list), so that list order equals arrival order and results never depend
 // on scheduling.  That is a stable counting sort by cell number, done in three small kernels:
 // per-segment histograms, a column-wise running sum over segments, and an in-order rank inside
-// each segment by one wavefront.
+// each segment by one workgroup.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -18,68 +18,80 @@ namespace ivftq {
 
 namespace {
 
-__global__ __launch_bounds__(256) void k_segment_hist(const int32_t* __restrict__ assign, int64_t n,
-                                                      int64_t seg_len, int L, uint32_t* __restrict__ seg_hist) {
+__global__ __launch_bounds__(1024) void k_segment_hist(const int32_t* __restrict__ assign, int64_t n,
+                                                       int64_t seg_len, int L, uint32_t* __restrict__ seg_hist) {
     extern __shared__ uint32_t hist[];
-    for (int l = threadIdx.x; l < L; l += 256) hist[l] = 0;
+    for (int l = threadIdx.x; l < L; l += 1024) hist[l] = 0;
     __syncthreads();
     const int64_t begin = (int64_t)blockIdx.x * seg_len;
     const int64_t end = begin + seg_len < n ? begin + seg_len : n;
-    for (int64_t i = begin + threadIdx.x; i < end; i += 256) {
-        const int a = assign[i];
-        if (a >= 0 && a < L) atomicAdd(&hist[a], 1u);
+    for (int64_t i = begin + threadIdx.x; i < end; i += 4096) {          // four loads in flight
+        int a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = i + 1024 * u < end ? assign[i + 1024 * u] : -1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (a[u] >= 0 && a[u] < L) atomicAdd(&hist[a[u]], 1u);
     }
     __syncthreads();
-    for (int l = threadIdx.x; l < L; l += 256) seg_hist[(int64_t)blockIdx.x * L + l] = hist[l];
+    for (int l = threadIdx.x; l < L; l += 1024) seg_hist[(int64_t)blockIdx.x * L + l] = hist[l];
 }
 
 // Column-wise exclusive running sum over segments.  A workgroup takes 16 lists; its 1024 threads split the
-// segments into 64 parts (a sixteen-lane group per part), so each of the two passes over a column is 64 wide
-// and a launch has L/16 workgroups.
+// segments into 64 parts (a sixteen-lane group per part) of at most kMaxSegments / 64, which a thread keeps in
+// registers, all its loads in flight; a launch has L/16 workgroups.
 __global__ __launch_bounds__(1024) void k_segment_scan(uint32_t* __restrict__ seg_hist, int nseg, int L,
                                                        uint32_t* __restrict__ batch_count) {
+    constexpr int C = kMaxSegments / 64;
     __shared__ uint32_t part_sum[64][16];
     const int li = threadIdx.x & 15, part = threadIdx.x >> 4;
     const int l = blockIdx.x * 16 + li;
     const int chunk = (nseg + 63) / 64;
     const int s0 = part * chunk < nseg ? part * chunk : nseg;
     const int s1 = (s0 + chunk < nseg) ? s0 + chunk : nseg;
-    uint32_t sum = 0;
-    if (l < L)
-        for (int s = s0; s < s1; ++s) sum += seg_hist[(int64_t)s * L + l];
+    uint32_t v[C], sum = 0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = l < L && s0 + c < s1 ? seg_hist[(int64_t)(s0 + c) * L + l] : 0u;
+#pragma unroll
+    for (int c = 0; c < C; ++c) sum += v[c];
     part_sum[part][li] = sum;
     __syncthreads();
     uint32_t run = 0;
     for (int p = 0; p < part; ++p) run += part_sum[p][li];
     if (l < L) {
-        for (int s = s0; s < s1; ++s) {
-            const uint32_t t = seg_hist[(int64_t)s * L + l];
-            seg_hist[(int64_t)s * L + l] = run;
-            run += t;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (s0 + c < s1) seg_hist[(int64_t)(s0 + c) * L + l] = run;
+            run += v[c];
         }
         if (part == 63) batch_count[l] = run;
     }
 }
 
-// One wavefront walks its segment 64 rows at a time, in order.
-__global__ __launch_bounds__(64) void k_stable_rank(const int32_t* __restrict__ assign, int64_t n,
-                                                    int64_t seg_len, int L,
-                                                    const uint32_t* __restrict__ seg_hist,
-                                                    const int64_t* __restrict__ list_base,
-                                                    int64_t* __restrict__ slot,
-                                                    const int64_t* __restrict__ batch_base,
-                                                    int32_t* __restrict__ order, int2* __restrict__ order_cell) {
+// A workgroup walks its segment 1024 rows at a time.  Its sixteen wavefronts find the equal cell numbers among
+// their own 64 rows on their own, then add to the segment's counters in turn, in row order.  Bound by latency: a turn
+// is one LDS atomic (the first row of a cell in a wavefront adds for all of them) and a barrier; the next rows'
+// cell numbers are fetched before the turns.  (One wavefront per segment, segments of 128 rows: as many counters as
+// 64 MB at 500,000 rows x 4096 cells, written once, read twice: the sort took 111 us an iteration of k-means.)
+__global__ __launch_bounds__(kRankRows) void k_stable_rank(const int32_t* __restrict__ assign, int64_t n,
+                                                           int64_t seg_len, int L,
+                                                           const uint32_t* __restrict__ seg_hist,
+                                                           const int64_t* __restrict__ list_base,
+                                                           int64_t* __restrict__ slot,
+                                                           const int64_t* __restrict__ batch_base,
+                                                           int32_t* __restrict__ order, int2* __restrict__ order_cell) {
     extern __shared__ uint32_t cnt[];
-    const int lane = threadIdx.x;
-    for (int l = lane; l < L; l += 64) cnt[l] = seg_hist[(int64_t)blockIdx.x * L + l];
-    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t begin = (int64_t)blockIdx.x * seg_len;
     const int64_t end = begin + seg_len < n ? begin + seg_len : n;
+    int next = begin + threadIdx.x < end ? assign[begin + threadIdx.x] : -1;
+    for (int l = threadIdx.x; l < L; l += kRankRows) cnt[l] = seg_hist[(int64_t)blockIdx.x * L + l];
+    __syncthreads();
     const int nbits = 32 - __builtin_clz((unsigned)L);                      // bits of the numbers 0 .. L
-    for (int64_t g = begin; g < end; g += 64) {
-        const int64_t i = g + lane;
-        int key = (i < end) ? assign[i] : -1;
-        if (key >= L) key = -1;
+    for (int64_t g = begin; g < end; g += kRankRows) {
+        const int64_t i = g + threadIdx.x;
+        const int key = next >= L ? -1 : next;
+        next = i + kRankRows < end ? assign[i + kRankRows] : -1;
         // lanes holding the same cell number: one ballot per bit of the number narrows the set (rows without a
         // cell carry the number L, which no other row has)
         const uint32_t kbits = (uint32_t)(key >= 0 ? key : L);
@@ -89,20 +101,20 @@ __global__ __launch_bounds__(64) void k_stable_rank(const int32_t* __restrict__ 
             const uint64_t bal = __ballot(set);
             same &= set ? bal : ~bal;
         }
-        const int lower = __popcll(same & ((1ull << lane) - 1ull));        // earlier rows of this group in the same cell
-        const bool later = (same >> lane) > 1ull;                          // a later row of the group is in it too
+        const int lower = __popcll(same & ((1ull << lane) - 1ull));        // earlier rows of this wavefront in the same cell
         uint32_t base = 0;
+        for (int turn = 0; turn < kRankRows / 64; ++turn) {
+            if (wave == turn && key >= 0 && lower == 0) base = atomicAdd(&cnt[key], (uint32_t)__popcll(same));
+            __syncthreads();
+        }
+        base = __shfl(base, (int)__builtin_ctzll(same));                   // a lane is in its own set: never empty
         if (key >= 0) {
-            base = cnt[key];
             if (slot) slot[i] = list_base[key] + (int64_t)(base + lower);
             if (order) order[batch_base[key] + (int64_t)(base + lower)] = (int32_t)i;
             if (order_cell) order_cell[batch_base[key] + (int64_t)(base + lower)] = make_int2((int)i, key);
         } else if (i < end && slot) {
             slot[i] = -1;
         }
-        __syncthreads();
-        if (key >= 0 && !later) cnt[key] = base + lower + 1;
-        __syncthreads();
     }
 }
 
@@ -709,11 +721,12 @@ hipError_t run_reconstruct(const ReconstructArgs& a, int cus, hipStream_t st) {
 
 hipError_t launch_segment_hist(const int32_t* assign, int64_t n, int64_t seg_len, int nseg, int L,
                                uint32_t* seg_hist, hipStream_t st) {
-    hipLaunchKernelGGL(k_segment_hist, dim3(nseg), dim3(256), (size_t)L * 4, st, assign, n, seg_len, L, seg_hist);
+    hipLaunchKernelGGL(k_segment_hist, dim3(nseg), dim3(1024), (size_t)L * 4, st, assign, n, seg_len, L, seg_hist);
     return hipGetLastError();
 }
 
 hipError_t launch_segment_scan(uint32_t* seg_hist, int nseg, int L, uint32_t* batch_count, hipStream_t st) {
+    if (nseg > kMaxSegments) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_segment_scan, dim3((L + 15) / 16), dim3(1024), 0, st, seg_hist, nseg, L, batch_count);
     return hipGetLastError();
 }
@@ -721,7 +734,7 @@ hipError_t launch_segment_scan(uint32_t* seg_hist, int nseg, int L, uint32_t* ba
 hipError_t launch_stable_rank(const int32_t* assign, int64_t n, int64_t seg_len, int nseg, int L,
                               const uint32_t* seg_hist, const int64_t* list_base, int64_t* slot,
                               const int64_t* batch_base, int32_t* order, int2* order_cell, hipStream_t st) {
-    hipLaunchKernelGGL(k_stable_rank, dim3(nseg), dim3(64), (size_t)L * 4, st, assign, n, seg_len, L,
+    hipLaunchKernelGGL(k_stable_rank, dim3(nseg), dim3(kRankRows), (size_t)L * 4, st, assign, n, seg_len, L,
                        seg_hist, list_base, slot, batch_base, order, order_cell);
     return hipGetLastError();
 }
