@@ -212,26 +212,48 @@ __global__ __launch_bounds__(1024) void k_exclusive_scan(const uint32_t* __restr
     for (int l = lo; l < hi; ++l) { out[l] = run; run += count[l]; }
 }
 
+// The sum of a value over a wavefront, in every lane: lanes 32 apart first, then 16, 8, ... 1, as a butterfly of exchanges
+// adds them (an addition does not depend on the order of its two sides), without a trip through the LDS unit: once the
+// values repeat every 2 s lanes, turning a row of sixteen by s is the exchange over a distance of s.
+template <int S>
+__device__ __forceinline__ float add_turned(float v) {
+    const int i = __builtin_bit_cast(int, v);
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0x120 + S, 0xf, 0xf, false));   // row_ror:S
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    unsigned a = __builtin_bit_cast(unsigned, v);
+    const auto h = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    const unsigned h0 = h[0], h1 = h[1];         // (a bit cast of an element of a vector casts the first one, whichever is named)
+    v = __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1);
+    a = __builtin_bit_cast(unsigned, v);
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const unsigned r0 = r[0], r1 = r[1];
+    v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+    return add_turned<1>(add_turned<2>(add_turned<4>(add_turned<8>(v))));
+}
+
 // Sum of the normalised rows of each cell, in a fixed order: workgroup l walks the rows
 // order[base[l] .. base[l] + count[l]) of its cell, wavefront w taking every fourth row from the w-th on,
 // a lane the coordinates lane, lane + 64, ...; the four partial sums are then added in the order 0, 1, 2, 3.
 // Nothing depends on scheduling, so the same input gives the same bits on every run.  Bound by the latency of
-// gathering rows: four rows of a wavefront are read together (500k x 96 over 4096 cells: 0.12 -> 0.09 ms).
+// gathering rows: a wavefront reads its next 64 row numbers together and then eight rows together, and adds up
+// their squares without LDS (500,000 x 96 over 4096 cells, ten iterations of training: 6355 -> 6019 us).
 //
 // GAIN (the last iteration, of which the objective is reported): every row's <x~, c> is added up in double as well.
 // From the float32 sums it would carry their rounding, which grows with the rows of a cell and is large beside
 // the objective of tight cells (400k x 16 rows in 4 cells: 2.6e-5 of it).
-template <bool GAIN>
+// T: coordinates of a lane.
+template <bool GAIN, int T>
 __global__ __launch_bounds__(256) void k_kmeans_cell_sums(const float* __restrict__ x, int d,
                                                           const int32_t* __restrict__ order,
                                                           const int64_t* __restrict__ base,
                                                           const uint32_t* __restrict__ count,
                                                           float* __restrict__ sums, int pitch,
                                                           const float* __restrict__ cent, double* __restrict__ gain) {
-    __shared__ float part[4][kMaxD];
+    __shared__ float part[4][64 * T];
     __shared__ double part_gain[4];                  // (GAIN)
-    constexpr int T = kMaxD / 64, U = 4;
-    const int l = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    constexpr int U = 8;
+    const int l = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t first = base[l];
     const int cnt = (int)count[l];
     float acc[T], c[T];
@@ -241,35 +263,41 @@ __global__ __launch_bounds__(256) void k_kmeans_cell_sums(const float* __restric
         acc[t] = 0.f;
         c[t] = GAIN && lane + 64 * t < d ? cent[(int64_t)l * pitch + lane + 64 * t] : 0.f;
     }
-    for (int p = wave; p < cnt; p += 4 * U) {
-        float v[U][T], n2[U];
+    for (int p64 = wave; p64 < cnt; p64 += 4 * 64) {
+        const int mine = order[first + (p64 + 4 * lane < cnt ? p64 + 4 * lane : p64)];      // past the end: a row of the cell
+        const int rows = (cnt - p64 + 3) / 4 < 64 ? (cnt - p64 + 3) / 4 : 64;
+        for (int r = 0; r < rows; r += U) {
+            float v[U][T], n2[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int pu = p + 4 * u < cnt ? p + 4 * u : p;
-            const float* row = x + (int64_t)order[first + pu] * d;
-            n2[u] = 0.f;
+            for (int u = 0; u < U; ++u) {
+                const float* row = x + (int64_t)__builtin_amdgcn_readlane(mine, r + u) * d;
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int j = lane + 64 * t;
-                v[u][t] = 64 * t < d ? row[j < d ? j : d - 1] : 0.f;
-                if (j >= d) v[u][t] = 0.f;
-                n2[u] += v[u][t] * v[u][t];
+                for (int t = 0; t < T; ++t) {
+                    const int j = lane + 64 * t;
+                    v[u][t] = row[j < d ? j : d - 1];
+                }
             }
-        }
-        for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-            for (int u = 0; u < U; ++u) n2[u] += __shfl_xor(n2[u], o);
+            for (int u = 0; u < U; ++u) {
+                n2[u] = 0.f;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (p + 4 * u >= cnt) break;
-            const float nrm = sqrtf(n2[u]);
+                for (int t = 0; t < T; ++t) {
+                    if (lane + 64 * t >= d) v[u][t] = 0.f;
+                    n2[u] += v[u][t] * v[u][t];
+                }
+                n2[u] = wave_sum(n2[u]);
+            }
 #pragma unroll
-            for (int t = 0; t < T; ++t)
-                if (64 * t < d) {
+            for (int u = 0; u < U; ++u) {
+                if (r + u >= rows) break;
+                const float nrm = sqrtf(n2[u]);
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
                     const float e = v[u][t] / nrm;
                     acc[t] += e;
                     if (GAIN) g += (double)e * (double)c[t];
                 }
+            }
         }
     }
 #pragma unroll
@@ -772,8 +800,13 @@ hipError_t launch_kmeans_cell_sums(const float* x, int d, const int32_t* order, 
                                    const uint32_t* count, int L, float* sums, int pitch, const float* cent,
                                    double* gain, hipStream_t st) {
     if (d > kMaxD) return hipErrorInvalidValue;
-    if (gain) hipLaunchKernelGGL(k_kmeans_cell_sums<true>, dim3(L), dim3(256), 0, st, x, d, order, base, count, sums, pitch, cent, gain);
-    else hipLaunchKernelGGL(k_kmeans_cell_sums<false>, dim3(L), dim3(256), 0, st, x, d, order, base, count, sums, pitch, cent, gain);
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(L), dim3(256), 0, st, x, d, order, base, count, sums, pitch, cent, gain); };
+    switch ((d + 63) / 64) {
+        case 1: gain ? go(k_kmeans_cell_sums<true, 1>) : go(k_kmeans_cell_sums<false, 1>); break;
+        case 2: gain ? go(k_kmeans_cell_sums<true, 2>) : go(k_kmeans_cell_sums<false, 2>); break;
+        case 3: gain ? go(k_kmeans_cell_sums<true, 3>) : go(k_kmeans_cell_sums<false, 3>); break;
+        default: gain ? go(k_kmeans_cell_sums<true, 4>) : go(k_kmeans_cell_sums<false, 4>); break;
+    }
     return hipGetLastError();
 }
 

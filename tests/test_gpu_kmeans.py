@@ -50,6 +50,29 @@ def test_centroids_match_oracle_on_separated_groups(niter):
     ix.close()
 
 
+@pytest.mark.parametrize("d", [33, 64, 65, 96, 128, 130, 192, 193, 256])
+def test_sums_of_cells_of_every_size(d):
+    """Every number of coordinates a lane can hold, cells of one row, of a few, around 8 and 64 rows a wavefront, and more.
+
+    Tolerance: a sum of m unit rows, added in four parts one row at a time, is off by at most about m/4 * 2^-24 of its length in
+    the worst case and by the root of that usually; 1200 rows: 1.1e-6, below CENTROID_TOL."""
+    size = [1, 2, 3, 4, 5, 31, 32, 33, 255, 256, 257, 261, 511, 1200]
+    rs = np.random.Generator(np.random.Philox(key=[d, 22]))
+    dirs = np.linalg.qr(rs.standard_normal((d, d)))[0][:len(size)]
+    comp = np.repeat(np.arange(len(size)), size)
+    X = (dirs[comp] + 0.3 / np.sqrt(d) * rs.standard_normal((len(comp), d))) * rs.uniform(0.5, 3.0, size=(len(comp), 1))
+    perm = rs.permutation(len(X))
+    X, comp = X[perm].astype(np.float32), comp[perm]
+    init = np.array([int(np.flatnonzero(comp == l)[0]) for l in range(len(size))], dtype=np.int64)
+    want, want_obj = orc.train_coarse(X, len(size), 1, init)
+    ix = _pkg().Index(d, 4, len(size))
+    print(f"[kmeans cell sizes] d={d}", flush=True)
+    obj = ix.train_coarse(torch.from_numpy(X).to(DEV), 1, init_rows=init)
+    np.testing.assert_allclose(ix.get_coarse().astype(np.float64), want, rtol=0, atol=CENTROID_TOL)
+    assert obj == pytest.approx(want_obj, rel=2e-6)
+    ix.close()
+
+
 def test_objective_of_cells_with_many_rows():
     """100,000 rows a cell: the objective does not carry the rounding of the cells' long float32 sums.
 
