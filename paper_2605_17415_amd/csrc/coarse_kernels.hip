@@ -31,6 +31,20 @@ struct CoarseCfg {
     static constexpr size_t lds_bytes = (size_t)2 * kTN * LDH * sizeof(uint16_t);
 };
 
+// LDS rows of k_coarse.  Where a compute unit holds three workgroups only without the padding (208 coordinates), the rows go without it
+// and 16-byte piece c of row r lies at c ^ (r / 8 & 1) instead: the pitch is then 8 words past a multiple of 16, so that
+// sixteen rows read at one piece fall on all 64 banks, as with the padding.  (10,000 queries x 4096 cells x 200, two workgroups with
+// padding 143 us, three without 114.)
+template <int DP>
+struct ScoresCfg {
+    static constexpr size_t kLds = 160 * 1024, bare = (size_t)2 * kTN * DP * sizeof(uint16_t);
+    static constexpr bool turned = 3 * CoarseCfg<DP>::lds_bytes > kLds && 3 * bare <= kLds;
+    static constexpr int LDH = turned ? DP : CoarseCfg<DP>::LDH;
+    static constexpr size_t lds_bytes = turned ? bare : CoarseCfg<DP>::lds_bytes;
+    static_assert(!turned || DP % 32 == 16, "bank layout");
+    static __device__ __forceinline__ int at(int r, int c) { return r * LDH + (turned ? c ^ ((r >> 3) & 1) : c) * 8; }
+};
+
 // stages of a call of k_coarse: the centroid table's, then those of Pi
 __host__ __device__ constexpr int coarse_stages(const CoarseArgs& a) { return a.Lpad / kTN + (a.pi_h ? (a.pitch + kTN - 1) / kTN : 0); }
 
@@ -84,16 +98,18 @@ __device__ __forceinline__ bool load_rows(const float* __restrict__ x, int64_t r
 // 5 us, and 12 to 28 us from 256 queries on, where each of its few workgroups walked all of Pi by itself.)
 // Workgroup (x, y) takes the row block x and the stages [y * per_y, y * per_y + per_y) of both tables together.
 // R = 32-row tiles per wavefront.  VEC4: rows are read 16 bytes at a time (d % 4 == 0, x 16-byte aligned).
-template <int DP, int R, bool VEC4>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 ? 3 : 2))) void k_coarse(CoarseArgs a, int per_y) {
-    using Cfg = CoarseCfg<DP>;
-    constexpr int KB = Cfg::KB;
+// ACROSS: the data rows are the row operand, so that a lane holds 16 rows' scores against one table row and the 32 lanes of a half
+// store 128 bytes in a row; else a lane holds one row's scores and stores 16 bytes at a time, 32 rows apart from lane to lane.
+template <int DP, int R, bool VEC4, bool ACROSS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 || ScoresCfg<DP>::turned ? 3 : 2))) void k_coarse(CoarseArgs a, int per_y) {
+    using Cfg = ScoresCfg<DP>;
+    constexpr int KB = DP / 16;
     extern __shared__ unsigned char lds_raw[];
     uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [TN][LDH] hi parts of the table's rows
     uint16_t* tl = th + kTN * Cfg::LDH;                               // [TN][LDH] lo parts
 
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, j = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, j = lane & 31;
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (32 * R);
     const int cent_stages = a.Lpad / kTN, stages = coarse_stages(a);
     const int s_lo = (int)blockIdx.y * per_y, s_hi = s_lo + per_y < stages ? s_lo + per_y : stages;
@@ -132,8 +148,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 ? 
         load_rows<DP>(a.x, row, row < a.n, a.d, VEC4 ? 1 : 0, half, bh[r], bl[r], &norm);
         if (a.norm_out && s_lo == 0 && half == 0 && row < a.n) a.norm_out[row] = norm;
     }
-    const uint16_t* ah_base = th + j * Cfg::LDH + 8 * half;
-    const uint16_t* al_base = tl + j * Cfg::LDH + 8 * half;
+    const uint16_t* ah_base = th + Cfg::at(j, half);       // (pieces 2 kb + half of rows j and 32 + j: the same turn)
+    const uint16_t* al_base = tl + Cfg::at(j, half);
     constexpr float kUnscale = 1.f / (kSplitScale * kSplitScale);
 
     for (int s = s_lo; s < s_hi; ++s) {
@@ -145,8 +161,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 ? 
             for (int i = 0; i < kPer; ++i) {
                 const int e = tid + 256 * i;
                 if (kPieces % 256 == 0 || e < kPieces) {
-                    *reinterpret_cast<piece*>(th + e / (DP / 8) * Cfg::LDH + e % (DP / 8) * 8) = pre_h[i];
-                    *reinterpret_cast<piece*>(tl + e / (DP / 8) * Cfg::LDH + e % (DP / 8) * 8) = pre_l[i];
+                    *reinterpret_cast<piece*>(th + Cfg::at(e / (DP / 8), e % (DP / 8))) = pre_h[i];
+                    *reinterpret_cast<piece*>(tl + Cfg::at(e / (DP / 8), e % (DP / 8))) = pre_l[i];
                 }
             }
         } else {
@@ -156,8 +172,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 ? 
             for (int e = tid; e < kPieces; e += 256) {
                 const int r = e / (DP / 8), c8 = e % (DP / 8);
                 const int64_t src = (int64_t)(c0 + r < last ? c0 + r : last) * a.pitch + c8 * 8;
-                *reinterpret_cast<uint4*>(th + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(src_h + src);
-                *reinterpret_cast<uint4*>(tl + r * Cfg::LDH + c8 * 8) = *reinterpret_cast<const uint4*>(src_l + src);
+                *reinterpret_cast<uint4*>(th + Cfg::at(r, c8)) = *reinterpret_cast<const uint4*>(src_h + src);
+                *reinterpret_cast<uint4*>(tl + Cfg::at(r, c8)) = *reinterpret_cast<const uint4*>(src_l + src);
             }
         }
         __syncthreads();
@@ -172,6 +188,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 ? 
             for (int t = 0; t < kNT; ++t)
 #pragma unroll
                 for (int q = 0; q < 16; ++q) acc[r][t][q] = 0.f;
+        auto product = [](half8 table, half8 row, floatx16 c) {
+            return ACROSS ? __builtin_amdgcn_mfma_f32_32x32x16_f16(row, table, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_f16(table, row, c, 0, 0, 0);
+        };
         auto multiply = [&](auto tiles) {
             constexpr int RR = decltype(tiles)::value;
 #pragma unroll
@@ -181,48 +200,91 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 ? 
                     const half8 ah = *reinterpret_cast<const half8*>(ah_base + t * 32 * Cfg::LDH + 16 * kb);
                     const half8 al = *reinterpret_cast<const half8*>(al_base + t * 32 * Cfg::LDH + 16 * kb);
 #pragma unroll
-                    for (int r = 0; r < RR; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[r][kb], acc[r][t], 0, 0, 0);
+                    for (int r = 0; r < RR; ++r) acc[r][t] = product(ah, bh[r][kb], acc[r][t]);
 #pragma unroll
-                    for (int r = 0; r < RR; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[r][kb], acc[r][t], 0, 0, 0);
+                    for (int r = 0; r < RR; ++r) acc[r][t] = product(ah, bl[r][kb], acc[r][t]);
 #pragma unroll
-                    for (int r = 0; r < RR; ++r) acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[r][kb], acc[r][t], 0, 0, 0);
+                    for (int r = 0; r < RR; ++r) acc[r][t] = product(al, bh[r][kb], acc[r][t]);
                 }
             }
         };
         if (R == 1 || any[R - 1]) multiply(std::integral_constant<int, R>{});
         else multiply(std::integral_constant<int, 1>{});
 
+        if constexpr (!ACROSS) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t row = row0 + 32 * r + j;
-            if (row >= a.n) continue;
+            for (int r = 0; r < R; ++r) {
+                const int64_t row = row0 + 32 * r + j;
+                if (row >= a.n) continue;
 #pragma unroll
-            for (int t = 0; t < kNT; ++t)
+                for (int t = 0; t < kNT; ++t)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int c = c0 + t * 32 + 8 * g + 4 * half;
-                    const float4 o = make_float4(acc[r][t][4 * g] * kUnscale, acc[r][t][4 * g + 1] * kUnscale,
-                                                 acc[r][t][4 * g + 2] * kUnscale, acc[r][t][4 * g + 3] * kUnscale);
-                    if (!rotate) {
-                        if (c < a.ld_scores) *reinterpret_cast<float4*>(a.scores + row * a.ld_scores + c) = o;
-                    } else if (c < a.pitch) {
-                        const int64_t at = row * a.pitch + c;
-                        *reinterpret_cast<float4*>(a.z_out + at) = o;
-                        if (a.zh_out) {
-                            const float z[4] = {o.x, o.y, o.z, o.w};
-                            uint16_t h[4], l[4];
+                    for (int g = 0; g < 4; ++g) {
+                        const int c = c0 + t * 32 + 8 * g + 4 * half;
+                        const float4 o = make_float4(acc[r][t][4 * g] * kUnscale, acc[r][t][4 * g + 1] * kUnscale,
+                                                     acc[r][t][4 * g + 2] * kUnscale, acc[r][t][4 * g + 3] * kUnscale);
+                        if (!rotate) {
+                            if (c < a.ld_scores) *reinterpret_cast<float4*>(a.scores + row * a.ld_scores + c) = o;
+                        } else if (c < a.pitch) {
+                            const int64_t at = row * a.pitch + c;
+                            *reinterpret_cast<float4*>(a.z_out + at) = o;
+                            if (a.zh_out) {
+                                const float z[4] = {o.x, o.y, o.z, o.w};
+                                uint16_t h[4], l[4];
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                _Float16 hi, lo;
-                                split_scaled(z[e], hi, lo);
-                                h[e] = __builtin_bit_cast(uint16_t, hi);
-                                l[e] = __builtin_bit_cast(uint16_t, lo);
+                                for (int e = 0; e < 4; ++e) {
+                                    _Float16 hi, lo;
+                                    split_scaled(z[e], hi, lo);
+                                    h[e] = __builtin_bit_cast(uint16_t, hi);
+                                    l[e] = __builtin_bit_cast(uint16_t, lo);
+                                }
+                                *reinterpret_cast<uint2*>(a.zh_out + at) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+                                *reinterpret_cast<uint2*>(a.zl_out + at) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
                             }
-                            *reinterpret_cast<uint2*>(a.zh_out + at) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
-                            *reinterpret_cast<uint2*>(a.zl_out + at) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
                         }
                     }
+            }
+        } else {
+            // result row q of a lane: row 8 (q / 4) + 4 half + q % 4 of the tile
+            const int width = rotate ? a.pitch : a.ld_scores;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int64_t rest = a.n - (row0 + 32 * r);
+                int left = (rest < 32 ? (int)rest : 32) - 4 * half;            // rows of the tile from this half's first on
+#pragma unroll
+                for (int t = 0; t < kNT; ++t) {
+                    const int c = c0 + t * 32 + j;
+                    if (c >= width) continue;
+                    const uint32_t own = (uint32_t)(4 * half * width + j);
+                    int64_t at = (row0 + 32 * r) * width + c0 + t * 32;        // (the same for all lanes)
+                    asm volatile("" : "+s"(at), "+v"(left));     // or what follows for all rows and tiles is worked out ahead and spilled
+                    if (!rotate) {
+                        float* out = a.scores + at;
+#pragma unroll
+                        for (int q = 0; q < 16; ++q) {
+                            if (8 * (q / 4) >= rest) break;
+                            if (8 * (q / 4) + q % 4 < left) out[own] = acc[r][t][q] * kUnscale;
+                            out += q % 4 == 3 ? 5 * width : width;
+                        }
+                        continue;
+                    }
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) {
+                        if (8 * (q / 4) >= rest) break;
+                        if (8 * (q / 4) + q % 4 < left) {
+                            const float o = acc[r][t][q] * kUnscale;
+                            (a.z_out + at)[own] = o;
+                            if (a.zh_out) {
+                                _Float16 hi, lo;
+                                split_scaled(o, hi, lo);
+                                (a.zh_out + at)[own] = __builtin_bit_cast(uint16_t, hi);
+                                (a.zl_out + at)[own] = __builtin_bit_cast(uint16_t, lo);
+                            }
+                        }
+                        at += q % 4 == 3 ? 5 * width : width;
+                    }
                 }
+            }
         }
     }
 }
@@ -614,12 +676,12 @@ hipError_t run_screened(const ScreenArgs& a, hipStream_t st) {
     return vec4 ? run_screened_as<DP, RS, true, false>(a, st) : run_screened_as<DP, RS, false, false>(a, st);
 }
 
-template <int DP, int R, bool VEC4>
+template <int DP, int R, bool VEC4, bool ACROSS>
 hipError_t run_as(const CoarseArgs& a, hipStream_t st) {
     static ChipFill fill;
-    constexpr size_t lds = CoarseCfg<DP>::lds_bytes;
+    constexpr size_t lds = ScoresCfg<DP>::lds_bytes;
     unsigned held = 0;
-    const hipError_t e = fill.get(reinterpret_cast<const void*>(k_coarse<DP, R, VEC4>), 256, lds, &held);
+    const hipError_t e = fill.get(reinterpret_cast<const void*>(k_coarse<DP, R, VEC4, ACROSS>), 256, lds, &held);
     if (e != hipSuccess) return e;
     const int64_t blocks = (a.n + 4 * 32 * R - 1) / (4 * 32 * R);
     // Every (row, table row) result is independent, so the stages of a row block can be shared out as one likes.  A
@@ -633,14 +695,19 @@ hipError_t run_as(const CoarseArgs& a, hipStream_t st) {
         const int64_t wgs = blocks * ((stages + s - 1) / s), cost = (wgs + held - 1) / held * (s + 1);
         if (cost < least) { least = cost; per_y = s; }
     }
-    hipLaunchKernelGGL((k_coarse<DP, R, VEC4>), dim3((unsigned)blocks, (unsigned)((stages + per_y - 1) / per_y)), dim3(256), lds, st, a, per_y);
+    hipLaunchKernelGGL((k_coarse<DP, R, VEC4, ACROSS>), dim3((unsigned)blocks, (unsigned)((stages + per_y - 1) / per_y)), dim3(256), lds, st, a, per_y);
     return hipGetLastError();
 }
 
 template <int DP, int R>
 hipError_t run(const CoarseArgs& a, hipStream_t st) {
     const bool vec4 = (a.d % 4 == 0) && (reinterpret_cast<uintptr_t>(a.x) % 16 == 0);
-    return vec4 ? run_as<DP, R, true>(a, st) : run_as<DP, R, false>(a, st);
+    // Stores of whole lines are four times as many instructions, most of them for rows that a small call does not have:
+    // without against with them, a call of 16 queries over 10M x 96 53.7 us against 54.8, 200 over 20,000 x 64 134 against 137, 256 over
+    // 10M x 200 and 1000 over 1M x 100 the same; 10,000 over 10M x 96 704 against 698, 10M x 200 1814 against 1775 (of which
+    // the third workgroup of ScoresCfg is a part).
+    if (a.n > 1024) return vec4 ? run_as<DP, R, true, true>(a, st) : run_as<DP, R, false, true>(a, st);
+    return vec4 ? run_as<DP, R, true, false>(a, st) : run_as<DP, R, false, false>(a, st);
 }
 
 // Calibration of the float16 matrix pipe: nothing but v_mfma_f32_32x32x16_f16 on operands held in
