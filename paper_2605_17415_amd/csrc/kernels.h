@@ -170,7 +170,8 @@ hipError_t launch_encode(int mode, const EncodeArgs& a, hipStream_t st);
 // ---- list bookkeeping -------------------------------------------------------------------------
 
 constexpr int kRankRows = 1024;        // rows that a workgroup of the stable counting sort ranks at a time
-constexpr int kMaxSegments = 512;      // segments of a batch: the workgroups of 1024 threads that the chip holds
+constexpr int kMaxSegments = 512;      // segments of a batch: the workgroups of 1024 threads that the chip holds (1024 of 512 threads:
+                                       // training on 500,000 x 96 5838 -> 5933 us, 10M x 96 built and searched the same)
 
 // seg_hist[s*L + l] = number of rows of segment s assigned to list l (rows with assign < 0 skipped)
 hipError_t launch_segment_hist(const int32_t* assign, int64_t n, int64_t seg_len, int nseg, int L,
