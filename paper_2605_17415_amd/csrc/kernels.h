@@ -306,8 +306,12 @@ __device__ __forceinline__ float metric_key_bound(int metric, float s, float x_m
     const float x = fminf(fmaxf(qn * s, x_min), x_max);
     return fmaf(2.f * x * qn, s, -x * x) + 0x1p-20f * (x * x + fabsf(2.f * x * qn * s));
 }
-// (a missing result's key is -inf: it stays so as an inner product, and becomes +inf as a distance)
-__device__ __forceinline__ float metric_value(int metric, float key, float qn) { return metric == 1 ? qn * key : qn * qn - key; }
+// (a missing result's key is -inf: it stays so as an inner product, also for a query without a usable norm, whose qn is 0,
+// and becomes +inf as a distance)
+__device__ __forceinline__ float metric_value(int metric, float key, float qn) {
+    if (metric == 1) return key > -__builtin_inff() ? qn * key : -__builtin_inff();
+    return qn * qn - key;
+}
 // Per row: the k largest of m values, sorted by (value desc, label asc).
 // mode 0 (probe selection): m = m_fixed for every row, label = column; writes int32 labels.
 // mode 1 (results): row q has m = cand_off[q][np] values; column -> (probe p, position) -> label

@@ -83,3 +83,35 @@ def test_a_query_without_a_norm_leaves_the_others_alone(mode, nq):
     assert (got[1][1] == -1).all() and np.isneginf(got[0][1]).all()
     assert (got[0][nq - 2] == 0.0).all()
     ix.close()
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+@pytest.mark.parametrize("k", [10, 1300])
+def test_missing_results_of_raw_metrics(mode, metric, k):
+    """Places without a result hold -inf (inner product) or +inf (distance), never what is no number, also where the query has no usable
+    norm: an infinite query has no results at all, a zero one the same values for all, and 1300 are more than four lists of 300 hold."""
+    import paper_2605_17415_amd as pkg
+    rng = np.random.default_rng(mode + k)
+    L, n, nq = 16, 4800, 70
+    cent = rng.standard_normal((L, D)).astype(np.float32)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    ix = pkg.Index(D, B, L, rotation_seed=5)
+    ix.set_metric(pkg.binding.METRIC_IP if metric == "ip" else pkg.binding.METRIC_L2)
+    ix.set_coarse(cent)
+    xnorm = rng.uniform(0.5, 2.0, n).astype(np.float32)
+    ix.add_encoded_raw(*[torch.from_numpy(v).to("cuda:0") for v in ((np.arange(n) % L).astype(np.int32), rng.integers(0, 1 << B, (n, D)).astype(np.uint8),
+                                                                  rng.uniform(0.2, 1.2, n).astype(np.float16), xnorm)])
+    ix.set_search_mode(mode)
+    q = rng.standard_normal((nq, D)).astype(np.float32)
+    q[1, 3] = np.inf
+    q[2] = 0.0
+    print(f"[missing results] mode={mode} {metric} k={k}", flush=True)
+    s, i = (t.cpu().numpy() for t in ix.search(torch.from_numpy(q).to("cuda:0"), 4, k))
+    real = min(k, 1200)
+    for r in range(nq):
+        have = 0 if r == 1 else real
+        assert (i[r, :have] >= 0).all() and (i[r, have:] == -1).all()
+        assert np.isfinite(s[r, :have]).all() and (s[r, have:] == (-np.inf if metric == "ip" else np.inf)).all()
+    np.testing.assert_allclose(s[2, :real], 0.0 if metric == "ip" else xnorm[i[2, :real]] ** 2, rtol=1e-6, atol=0)
+    ix.close()
