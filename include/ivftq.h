@@ -237,6 +237,8 @@ ivftq_status ivftq_refresh_coarse(ivftq_index* index, int64_t sample_n, int nite
  * and ids_dev[nq x k] (int64 labels) of the k largest estimated inner products <q~, x~> among the
  * vectors of the nprobe cells with the largest <q~, c~_l>.  Equal scores are ordered by label.
  * Queries with fewer than k candidates are padded with label -1 and score -infinity.
+ * A query that holds an infinity or a NaN has no cells and no results; a candidate whose score is no
+ * number (stored codes of the caller's own with an infinite norm) is no result.
  * Asynchronous on `stream`; uses workspace owned by the index, which only grows: once a call of the
  * same (nq, nprobe, k) has run on the index as it stands, further calls allocate nothing, do not
  * synchronise with the host and issue kernel launches only, so they may be recorded into a HIP graph.
@@ -248,7 +250,8 @@ ivftq_status ivftq_search(ivftq_index* index, const float* q_dev, int64_t nq, in
 
 /* The first two steps of search on their own: probe_dev[nq x nprobe] int32 cell numbers ordered
  * by decreasing <q~, c~_l> (ties: smaller cell first) and coarse_dev[nq x nprobe] those inner
- * products.  Either output may be NULL.  Asynchronous. */
+ * products (-1 and -infinity for a query that holds an infinity or a NaN).  Either output may be NULL.
+ * Asynchronous. */
 ivftq_status ivftq_coarse_probe(ivftq_index* index, const float* q_dev, int64_t nq, int nprobe,
                                 int32_t* probe_dev, float* coarse_dev, void* stream);
 

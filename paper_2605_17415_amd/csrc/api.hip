@@ -1482,11 +1482,8 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             // 10M x 96: scan 0.100 -> 0.070 ms)
             slices = std::max(slices, std::min<int64_t>(kStreamWorkgroups / ((int64_t)per_query * cnt), ix->ntotal / ix->nlist / 512));
             la.blk_max = ix->w_blk.as<uint32_t>(); la.blk_stride = block_index((int)m_stride, nprobe);
-            // scores that are no numbers (a query that is none itself): last among the results where one wavefront
-            // or two steps used to select them, else first
-            la.nan_last = k <= 64 && (m_stride <= 16384 || (nq <= 64 && nprobe > 1 && sizes[0] <= 16384 && (int64_t)nprobe * k <= 16384));
             HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, per_query, (int)slices, st); }));
-            sa.blk_max = la.blk_max; sa.blk_stride = la.blk_stride; sa.nan_last = la.nan_last;
+            sa.blk_max = la.blk_max; sa.blk_stride = la.blk_stride;
             sa.metric = metric; sa.qnorm = la.qnorm;
             HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_select(1, sa, st); }));
             continue;

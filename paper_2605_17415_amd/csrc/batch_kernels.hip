@@ -148,9 +148,10 @@ __global__ __launch_bounds__(1024) void k_pair_scatter_lds(const int32_t* __rest
 // overflowed is appended to the gate list.  Bound by latency: passes over a few hundred values in LDS and one
 // dependent gather per survivor.  (Sorting all entries by u, then the survivors by score: 0.21 ms instead of
 // 0.13 for 4096 queries with 385 candidates each, k = 50.)
+// (0: no number, which is no result)
 __device__ __forceinline__ uint32_t okey(float f) {
     const uint32_t u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return f != f ? 0u : (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
 __device__ __forceinline__ float okey_value(uint32_t k) { return __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k); }
@@ -307,6 +308,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
     }
     __syncthreads();
     for (int i = found + tid; i < a.k; i += 256) put(i, -__builtin_inff(), -1);
+    auto put_key = [&](int i, uint32_t key, int64_t lab) { put(i, key ? okey_value(key) : -__builtin_inff(), key ? lab : -1); };
     if (found <= kMergeCount) {
         if (tid < found) {
             const uint32_t key = p_key[tid];
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
                 const int64_t lj = p_lab[j];
                 rank += (kj > key || (kj == key && (lj < lab || (lj == lab && j < tid)))) ? 1 : 0;
             }
-            if (rank < a.k) put(rank, okey_value(key), lab);
+            if (rank < a.k) put_key(rank, key, lab);
         }
         return;
     }
@@ -338,7 +340,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
             }
             __syncthreads();
         }
-    for (int i = tid; i < a.k && i < found; i += 256) put(i, okey_value(p_key[i]), p_lab[i]);
+    for (int i = tid; i < a.k && i < found; i += 256) put_key(i, p_key[i], p_lab[i]);
 }
 
 }  // namespace

@@ -264,8 +264,8 @@ struct ListScanArgs {
     float* scores; int64_t m_stride;
     int metric; const float* qnorm;
     // blk_max[q*blk_stride + block_index(cand_off[q][p], p) + b] = order-preserving key of the best score of block b (64
-    // vectors) of probe p (null: not wanted); nan_last: what is no number counts as the smallest
-    uint32_t* blk_max; int64_t blk_stride; bool nan_last;
+    // vectors) of probe p (null: not wanted)
+    uint32_t* blk_max; int64_t blk_stride;
     // Exact redo (gate not null): instead of all queries the entries [gate_begin, gate_begin + gate_rows) of the
     // gate[0] queries listed in gate[1..] are scanned.  Entry g's scores that reach thresh[q*thresh_stride], less the
     // rounding between the arithmetic of the threshold and this one, go, redo_cnt[q] of them in any order, to the
@@ -325,7 +325,6 @@ struct SelectArgs {
     float* out_vals; int32_t* out_i32; int64_t* out_i64;
     int m_bound;      // mode 1: host-side upper bound of any row's length (0 = unknown); picks the kernel
     const uint32_t* blk_max; int64_t blk_stride;      // mode 1: as the scan left them (null: not there)
-    bool nan_last;                                    // mode 1: what is no number is no result
     int metric; const float* qnorm;                   // mode 1: the values are ranking keys, written as values of the metric
     // mode 0: what follows from the probes just selected (cand.cand_off null: nothing)
     CandOffsetArgs cand;

@@ -83,12 +83,11 @@ __device__ __forceinline__ void cand_offsets_wave(const CandOffsetArgs& c, int64
     if (lane == 0) put_first(c, q, p1);
 }
 
-// Order-preserving key of a score; with nan_last whatever is no number gets the smallest one, 0.
+// Order-preserving key of a score; whatever is no number gets 0, which no score has: it is no cell and no result.
 __device__ __forceinline__ uint32_t order_key(float f) {
     const uint32_t u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return f != f ? 0u : (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
-__device__ __forceinline__ uint32_t order_key(float f, bool nan_last) { return nan_last && f != f ? 0u : order_key(f); }
 __device__ __forceinline__ float order_value(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key); }
 
 // ---- list scan: a row of workgroups per query walks its probed lists ---------------------------
@@ -285,7 +284,7 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
             margin = redo_margin(a.slack, s_l, g);
         }
         if constexpr (REDO) {
-            const bool keep = in_list && !(sc < reach - margin);     // (whatever is no number stays, as in a scan that keeps all)
+            const bool keep = in_list && sc == sc && !(sc < reach - margin);     // (a margin that is no number keeps what is one)
             const uint64_t in = __ballot(keep);           // one counter update per wavefront
             if (in) {
                 const int leader = (int)__builtin_ctzll(in);
@@ -300,7 +299,7 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
         } else {
             if (in_list) out[v] = sc;
             if (blk) {
-                uint32_t key = in_list ? order_key(sc, a.nan_last) : 0u;
+                uint32_t key = in_list ? order_key(sc) : 0u;
 #pragma unroll
                 for (int o = 32; o > 0; o >>= 1) key = max(key, (uint32_t)__shfl_xor(key, o));
                 if (lane == 0) blk[v0 >> 6] = key;
@@ -387,7 +386,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     const int32_t* off = MODE == 0 ? nullptr : a.cand_off + q * (a.np + 1);
     const int n_off = MODE == 0 ? 0 : a.p_limit ? a.p_limit[q] : a.np;
     const int m = MODE == 0 ? a.m_fixed : off[n_off];
-    const bool nan_last = a.nan_last, staged = a.np <= kSelOffs;
+    const bool staged = a.np <= kSelOffs;
     if (MODE == 1 && staged)
         for (int p = tid; p <= a.np; p += 256) s_off[p] = off[p];
     auto off_at = [&](int p) -> int32_t { return staged ? s_off[p] : off[p]; };
@@ -411,7 +410,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
         // (one base pointer and loads without a branch between them, so that all of a thread's are in flight together)
         const uint32_t* src = by_block ? a.blk_max + row * a.blk_stride : reinterpret_cast<const uint32_t*>(vals);
         const int parts = by_block ? n_blk : m;
-        auto key_of = [&](uint32_t raw) -> uint32_t { return by_block ? raw : order_key(__uint_as_float(raw), nan_last); };
+        auto key_of = [&](uint32_t raw) -> uint32_t { return by_block ? raw : order_key(__uint_as_float(raw)); };
         uint32_t* maxima = reinterpret_cast<uint32_t*>(c_ent);
         uint32_t held[kSelHeld], bound = 0;
         if (parts <= 1024) {
@@ -496,7 +495,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
 #pragma unroll
                     for (int e = 0; e < kSelHeld; ++e) {
                         if (b0 + 4 * e >= n) break;
-                        if (col[e] >= 0) use(order_key(v[e], nan_last), col[e]);
+                        if (col[e] >= 0) use(order_key(v[e]), col[e]);
                     }
                 }
             };
@@ -551,7 +550,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
                 }
 #pragma unroll
                 for (int u = 0; u < kSelU; ++u) {
-                    const uint32_t key = order_key(v[u], nan_last);
+                    const uint32_t key = order_key(v[u]);
                     if (i0 + 64 * u + lane < w_end && (key & mask) == prefix)
                         atomicAdd(&hist[((key >> shift) & 255u) * kHistCopies + (lane & (kHistCopies - 1))], 1u);
                 }
@@ -613,7 +612,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
 #pragma unroll
             for (int u = 0; u < kSelU; ++u) {
                 const int i = i0 + 64 * u + lane;
-                const uint32_t key = order_key(v[u], nan_last);
+                const uint32_t key = order_key(v[u]);
                 const bool above = i < w_end && (all || key > prefix);
                 const bool tie = i < w_end && !all && key == prefix;
                 if (above) {
@@ -633,7 +632,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
             uint32_t key = 0;
             bool tie = false;
             if (i < w_end) {
-                key = order_key(vals[i], nan_last);
+                key = order_key(vals[i]);
                 tie = !all && key == prefix;
             }
             const uint64_t bal = __ballot(tie);
@@ -755,7 +754,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     uint32_t* hist = s_work[wave];                                      // [256]
     int* win_col = reinterpret_cast<int*>(hist + 256);                  // [64]
     const float ninf = -__builtin_inff();
-    auto key_of = [](float v) -> uint32_t { return order_key(v, true); };
+    auto key_of = [](float v) -> uint32_t { return order_key(v); };
 
     win_col[lane] = -1;
     uint32_t keys[NV];                                   // key of column e*64 + lane (unused beyond m)
@@ -1299,7 +1298,7 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
                 if (lane == 0 && c < size) {
                     const bool ok = id[u] >= 0 && xx > 0.f && qq > 0.f;
                     const float sc = ok ? xy / sqrtf(xx * qq) : -__builtin_inff();
-                    s_key[c] = (ok && sc == sc) ? order_key(sc) : 0u;
+                    s_key[c] = ok ? order_key(sc) : 0u;
                     s_val[c] = sc;
                     s_lab[c] = ok ? id[u] : INT64_MAX;
                 }
@@ -1399,8 +1398,8 @@ __global__ __launch_bounds__(256) void k_cascade_rescore(CascadeArgs a) {
                 bool hit = false;
                 if (p < a.np) {
                     const int l = a.probe[q * a.np + p];
-                    const int64_t off = a.store.list_off[l];
-                    hit = slot >= off && slot < off + a.store.list_size[l];
+                    const int64_t off = l < 0 ? 0 : a.store.list_off[l];
+                    hit = l >= 0 && slot >= off && slot < off + a.store.list_size[l];
                 }
                 const unsigned long long m = __ballot(hit);
                 if (m) p_found = base + __ffsll((long long)m) - 1;
@@ -1425,7 +1424,7 @@ __global__ __launch_bounds__(256) void k_cascade_rescore(CascadeArgs a) {
             const bool ok = p_found >= 0;
             float sc = -__builtin_inff();
             if (ok) sc = a.coarse[q * a.np + p_found] + __half2float(__ushort_as_half(a.store.gamma[slot])) * acc;
-            s_key[c] = (ok && sc == sc) ? order_key(sc) : 0u;
+            s_key[c] = ok ? order_key(sc) : 0u;
             s_val[c] = sc;
             s_lab[c] = ok ? a.ids[slot] : INT64_MAX;
         }
@@ -1523,13 +1522,11 @@ constexpr int kSmallMax0Shortcut = 8192, kSmallMax1 = kSmallM;
 // 16 / 256 / 1000 queries over 4096 / 4096 / 1000 cells: 9.3 / 12.3 / 7.7 us, with one wavefront each 15.9 / 20.9 /
 // 8.9; 10,000 over 4096: 71 against 63).
 constexpr int64_t kSelFewRows = 2048;
-hipError_t launch_select(int mode, const SelectArgs& a_in, hipStream_t st) {
-    if (a_in.rows <= 0) return hipSuccess;
-    SelectArgs a = a_in;
+hipError_t launch_select(int mode, const SelectArgs& a, hipStream_t st) {
+    if (a.rows <= 0) return hipSuccess;
     // short rows and small k: the one-wavefront-per-row kernel
     const int m_bound = mode == 0 ? a.m_fixed : a.m_bound;
     const bool small = a.k <= 64 && m_bound > 0 && m_bound <= (mode == 0 ? kSmallMax0Shortcut : kSmallMax1);
-    if (!a.blk_max) a.nan_last = small;      // (what is no number is no cell and no result, as the one-wavefront kernel has it)
     if (small && !a.blk_max && a.rows > kSelFewRows) {
         const size_t lds = 0;
         const unsigned blocks = (unsigned)((a.rows + 3) / 4);

@@ -115,3 +115,54 @@ def test_missing_results_of_raw_metrics(mode, metric, k):
         assert np.isfinite(s[r, :have]).all() and (s[r, have:] == (-np.inf if metric == "ip" else np.inf)).all()
     np.testing.assert_allclose(s[2, :real], 0.0 if metric == "ip" else xnorm[i[2, :real]] ** 2, rtol=1e-6, atol=0)
     ix.close()
+
+
+@pytest.mark.parametrize("nprobe", [10, 70])
+@pytest.mark.parametrize("nq", [64, 65, 3000])
+def test_a_query_that_is_no_number_has_no_cells_and_no_results(nprobe, nq):
+    """whichever kernels a call's size leads to: 10 or 70 probes, 10 to 100 results, rows of up to 28,000 candidates, few queries or many"""
+    rng = np.random.default_rng(nq + nprobe)
+    ix, *_ = _index([400] * 100, rng, False)
+    q = rng.standard_normal((nq, D)).astype(np.float32)
+    q[7, 5], q[nq - 1, 0] = np.inf, np.nan
+    bad = [7, nq - 1]
+    qd = torch.from_numpy(q).to("cuda:0")
+    print(f"[no number] nprobe={nprobe} nq={nq}", flush=True)
+    probe, coarse = (t.cpu().numpy() for t in ix.coarse_probe(qd, nprobe))
+    assert (probe[bad] == -1).all() and np.isneginf(coarse[bad]).all()
+    good = np.delete(np.arange(nq), bad)
+    assert (probe[good] >= 0).all()
+    for mode in (1, 2):
+        ix.set_search_mode(mode)
+        for k in (10, 64, 100):
+            s, i = (t.cpu().numpy() for t in ix.search(qd, nprobe, k))
+            assert (i[bad] == -1).all() and np.isneginf(s[bad]).all()
+            assert (i[good] >= 0).all() and np.isfinite(s[good]).all()
+    s, i = (t.cpu().numpy() for t in ix.search_cascade(qd, nprobe, 10, 2, 100))
+    assert (i[bad] == -1).all() and np.isneginf(s[bad]).all() and (i[good] >= 0).all()
+    ix.close()
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("k", [10, 100, 300])
+def test_a_distance_that_is_no_number_is_no_result(mode, k):
+    """Squared distance to a stored length of +inf: its ranking key is inf - inf for some of the queries and comes last, so the results are
+    those of the finite vectors, for any number of results and from either scan."""
+    import paper_2605_17415_amd as pkg
+    rng = np.random.default_rng(k)
+    L, n, nq = 4, 4000, 40
+    cent = rng.standard_normal((L, D)).astype(np.float32)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    ix = pkg.Index(D, B, L, rotation_seed=1)
+    ix.set_metric(pkg.binding.METRIC_L2)
+    ix.set_coarse(cent)
+    xnorm = rng.uniform(0.5, 2.0, n).astype(np.float32)
+    far = rng.choice(n, 20, replace=False)
+    xnorm[far] = np.inf
+    ix.add_encoded_raw(*[torch.from_numpy(v).to("cuda:0") for v in (rng.integers(0, L, n).astype(np.int32), rng.integers(0, 1 << B, (n, D)).astype(np.uint8),
+                                                                  rng.uniform(0.2, 1.2, n).astype(np.float16), xnorm)])
+    ix.set_search_mode(mode)
+    print(f"[infinite length] mode={mode} k={k}", flush=True)
+    s, i = (t.cpu().numpy() for t in ix.search(torch.from_numpy(rng.standard_normal((nq, D)).astype(np.float32)).to("cuda:0"), L, k))
+    assert np.isfinite(s).all() and (i >= 0).all() and not np.isin(i, far).any()
+    ix.close()
