@@ -159,7 +159,7 @@ __device__ __forceinline__ float okey_value(uint32_t k) { return __uint_as_float
 constexpr int kMergeCount = 256;        // most survivors placed by counting; beyond that a bitonic network sorts them
 
 __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
-    extern __shared__ unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t hist[256];
     __shared__ float s_wmax[4];
     __shared__ int s_bin, s_found;

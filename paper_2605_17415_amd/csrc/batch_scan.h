@@ -186,7 +186,7 @@ void k_batch_dense(BatchScanArgs a) {
     using Cfg = BatchCfg<DP, B, NQ>;
     constexpr int KB = DP / 16, NT = WAVES * 64;
     constexpr int NW = (B == 2 || B == 4) ? 1 : 2;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* zh = reinterpret_cast<uint16_t*>(lds_raw);                       // [TQ][LDH] hi parts of the rotated queries
     uint16_t* zl = zh + Cfg::TQ * Cfg::LDH;                                      // [TQ][LDH] lo parts
     uint4* s_row = reinterpret_cast<uint4*>(zl + Cfg::TQ * Cfg::LDH);          // [TQ] coarse term, first score's place (2 words), |q|
@@ -336,7 +336,7 @@ void k_batch_threshold(BatchScanArgs a) {
     constexpr int KB = DP / 16, NT = WAVES * 64, VB = 32 * S;      // vectors of a block
     constexpr int CAND = Cfg::held_back(OCC);
     constexpr int NW = (B == 2 || B == 4) ? 1 : 2;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* zh = reinterpret_cast<uint16_t*>(lds_raw);                       // [TQ][LDH] hi parts of the rotated queries
     uint4* s_row = reinterpret_cast<uint4*>(zh + Cfg::TQ * Cfg::LDH);          // [TQ] coarse term, threshold, pair number, |q|
     uint32_t* tab = reinterpret_cast<uint32_t*>(s_row + Cfg::TQ);                // [PT][TC] hi parts of a code pair, packed (or of one code)

@@ -104,7 +104,7 @@ template <int DP, int R, bool VEC4, bool ACROSS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 || ScoresCfg<DP>::turned ? 3 : 2))) void k_coarse(CoarseArgs a, int per_y) {
     using Cfg = ScoresCfg<DP>;
     constexpr int KB = DP / 16;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [TN][LDH] hi parts of the table's rows
     uint16_t* tl = th + kTN * Cfg::LDH;                               // [TN][LDH] lo parts
 
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
     unsigned long long* __restrict__ row_key, int* __restrict__ row_count, float* __restrict__ part, int whole, int shares) {
     using Cfg = CoarseCfg<DP>;
     constexpr int KB = Cfg::KB;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     constexpr int NT = screen_nt<DP>(), TN = NT * 32;
     // The first `whole` row blocks are one workgroup's each.  Every later one is shared by `shares` workgroups: each takes its
     // share of the centroid stages and leaves (best, second best, index) of every row in `part`, where
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int* __restrict__ row_count, unsigned long long* __restrict__ row_key) {
     using Cfg = CoarseCfg<DP>;
     constexpr int KB = Cfg::KB;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [TN][LDH] hi parts of the centroid tile
     uint16_t* tl = th + kTN * Cfg::LDH;                               // [TN][LDH] lo parts
     const int tid = threadIdx.x;

@@ -66,7 +66,7 @@ void k_encode(EncodeArgs a, int flags) {
     constexpr bool via_lds = MODE == 0 && PACK_B == 0;
     using Cfg = EncCfg<DP>;
     constexpr int KB = Cfg::KB, NT = Cfg::NT, R = Cfg::R, LDH = Cfg::LDH, PF = Cfg::PF;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* stage = reinterpret_cast<uint16_t*>(lds_raw);                    // [2][hi,lo][32][LDH]
     float2* grid_s = reinterpret_cast<float2*>(lds_raw + Cfg::pi_bytes);        // [cells] (boundary, index bits)
     uint32_t* pack_s = reinterpret_cast<uint32_t*>(lds_raw + Cfg::pi_bytes + (size_t)a.q_cells * 8);
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 96 ? 
 void k_encode_resident(EncodeArgs a, int64_t tiles) {
     using Cfg = EncCfg<DP>;
     constexpr int KB = Cfg::KB, NT = Cfg::NT, LDH = Cfg::LDH, b = PACK_B;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* pi_hs = reinterpret_cast<uint16_t*>(lds_raw);                   // [DP][LDH] leading parts
     uint16_t* pi_ls = pi_hs + DP * LDH;                                        // [DP][LDH] trailing parts
     float2* grid_s = reinterpret_cast<float2*>(lds_raw + (size_t)2 * DP * LDH * sizeof(uint16_t));

@@ -452,7 +452,7 @@ __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
     const int32_t* __restrict__ tile_off, int tiles, float* __restrict__ x_out, int64_t* __restrict__ labels_out) {
     using Cfg = ReconCfg<DP, F32>;
     constexpr int KB = Cfg::KB, LDH = Cfg::LDH, LDF = Cfg::LDF, VEC = Cfg::VEC, T = Cfg::THREADS;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* stage = reinterpret_cast<uint16_t*>(lds_raw);                       // [2][SLABS][hi, lo][32][LDH], or floats [2][SLABS][32][LDF]
     uint32_t* tab = reinterpret_cast<uint32_t*>(stage + 2 * Cfg::buf_halves);     // [2^b] hi | lo << 16, or the float
     float* gam = reinterpret_cast<float*>(tab + 256);                             // [2][VEC] norms (split form: * 2^-20)

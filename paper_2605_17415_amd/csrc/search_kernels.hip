@@ -363,7 +363,7 @@ __device__ __forceinline__ uint32_t kth_of_maxima(const uint32_t* maxima, int ta
 template <int MODE, int COPIES>
 __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     constexpr int kHistCopies = COPIES;
-    extern __shared__ unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int32_t s_off[kSelOffs + 1];
     int kpad = 1;
     while (kpad < a.k) kpad <<= 1;
@@ -1241,10 +1241,12 @@ __global__ __launch_bounds__(1024) void k_redo_select(RedoSelectArgs a) {
 // the latency of gathering rows: a wavefront reads the labels of its next 64 candidates together and then four rows together
 // (T: coordinates of a lane); 4096 queries x 50 rows of 128: 66 us with one row at a time and a sort by one barrier a step, 48 now.
 // Up to 256 candidates are placed by counting the ones that go before (by the wavefronts that have one: by all four, the
-// reads of LDS alone made it 100 us), more are sorted.
+// reads of LDS alone made it 100 us), more are sorted.  4096 queries x 100 coordinates, sorted by one barrier a step, one row at
+// a time, against now: 50 candidates 62 and 45 us, 128 110 and 99, 200 202 and 181, 256 207 and 207, 300 (sorted) 391 and 257.  The
+// labels have to lie at multiples of 8: 4 bytes off, 200 candidates took 284 us, 256 315.
 template <int T>
 __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
-    extern __shared__ unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem[];
     constexpr int U = 4;
     int size = 1;
     while (size < a.r) size <<= 1;
@@ -1374,7 +1376,7 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
 // holds the slot (lanes over the query's probes), then lane j sums the coordinates j, j+64, ... from
 // the packed words; the workgroup sorts (score desc, label asc) in LDS and emits the k best.
 __global__ __launch_bounds__(256) void k_cascade_rescore(CascadeArgs a) {
-    extern __shared__ unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem[];
     int size = 1;
     while (size < a.n_keep) size <<= 1;
     uint32_t* s_key = reinterpret_cast<uint32_t*>(smem);

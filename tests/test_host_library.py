@@ -194,3 +194,17 @@ def test_create_reports_oom_when_the_allocator_callback_refuses():
     with pytest.raises(pkg.IvftqError) as e:
         pkg.Index(96, 4, 64, allocator=(alloc_cb, free_cb))
     assert e.value.status == pkg.binding.OOM
+
+
+def test_dynamic_lds_of_several_types_is_aligned():
+    """A dynamic LDS block of bytes is cut up into arrays of up to 16-byte elements, so it has to begin at a multiple of 16 whatever
+    static LDS words a kernel has before it; declared as plain bytes it may begin at any address behind them."""
+    csrc = os.path.join(ROOT, "paper_2605_17415_amd", "csrc")
+    blocks = []
+    for name in sorted(os.listdir(csrc)):
+        for line in open(os.path.join(csrc, name)):
+            if re.search(r"extern\s+__shared__.*\bchar\b", line):
+                blocks.append((name, line.strip()))
+    assert len(blocks) >= 10
+    for name, line in blocks:
+        assert "__align__(16)" in line, f"{name}: {line}"
