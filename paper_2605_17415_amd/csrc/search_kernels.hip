@@ -330,6 +330,8 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
 constexpr int kSelU = 8;        // groups of 64 columns loaded together by k_select
 constexpr int kSelSmallU = 8;   // and by k_select_small beyond its registers
 constexpr int kSelCand = 512;   // most keys the short cut of k_select orders
+constexpr int kSelAll = 128;    // most columns of a row that is ordered whole (as for 512, the square of whose number that takes: probes of
+                                // 2048 queries over 512 cells, 20 us with a bound for 128 columns and more, 33 without one)
 constexpr int kSelTake = 192;   // most winners it is used for
 constexpr int kSelHeld = 16;    // columns (or block maxima) a thread keeps in registers between its two passes
 constexpr int kSelBlocks = 512; // most blocks it gathers from
@@ -406,7 +408,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     const int n_blk = MODE == 1 && a.blk_max ? block_index(m, n_off) : 0;
     // (few blocks for many winners: their maxima say little)
     const bool by_block = n_blk >= 2 * take && m > kSelCand;
-    if (take > 0 && ((take <= kSelTake && m > k) || m <= kSelCand)) {
+    if (take > 0 && ((take <= kSelTake && m > k) || m <= kSelAll)) {
         // (one base pointer and loads without a branch between them, so that all of a thread's are in flight together)
         const uint32_t* src = by_block ? a.blk_max + row * a.blk_stride : reinterpret_cast<const uint32_t*>(vals);
         const int parts = by_block ? n_blk : m;
@@ -420,7 +422,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
 #pragma unroll
             for (int u = 0; u < kSelHeld; ++u) held[u] = src[min(256 * u + tid, parts - 1)];
         }
-        if (parts > kSelCand || by_block) {
+        if (parts > kSelAll || by_block) {
             uint32_t best = 0;
 #pragma unroll
             for (int u = 0; u < kSelHeld; ++u) best = 256 * u + tid < parts ? max(best, key_of(held[u])) : best;
@@ -674,11 +676,12 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
         else { if (a.out_i64) a.out_i64[row * k + i] = real ? lab : -1; }
         if (MODE == 0) s_col[i] = real ? (uint32_t)lab : 0xFFFFFFFFu;
     };
-    if (kpad <= 256) {
+    if (kpad <= 256 && picked) {
         const uint32_t key = tid < take ? s_key[tid] : 0u;
-        // (the short cut's winners are in this order already but for equal keys)
+        // (the short cut's winners are in this order already but for equal keys; counting orders those.  Winners of the radix search
+        // are in no order: 200 of them counted made a call of 10,000 queries x 2500 candidates 445 us, 409 with the network below)
         const bool tie = tid + 1 < take && key == s_key[tid + 1];
-        if (__syncthreads_or(tie || !picked)) {
+        if (__syncthreads_or(tie)) {
             const int64_t lab = tid < kpad ? s_lab[tid] : 0;
             int rank = tid;                          // an empty place
             if (tid < take) {
@@ -1515,30 +1518,26 @@ hipError_t launch_redo_select(const RedoSelectArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Longest row the one-wavefront-per-row kernel takes.  Probe selection (mode 0, every row has m_fixed values):
-// its short cuts (up to 64 winners) beat the workgroup-per-row kernel well beyond the columns it holds in
-// registers (10,000 rows over 4096 cells: 0.069 ms for 32 winners, against 0.145 ms); result rows (mode 1)
-// are mostly much shorter than their bound.
-constexpr int kSmallMax0Shortcut = 8192, kSmallMax1 = kSmallM;
-// Up to that many rows a workgroup each is faster all the same, the launch being bound by the latency of one row (probes of
-// 16 / 256 / 1000 queries over 4096 / 4096 / 1000 cells: 9.3 / 12.3 / 7.7 us, with one wavefront each 15.9 / 20.9 /
-// 8.9; 10,000 over 4096: 71 against 63).
-constexpr int64_t kSelFewRows = 2048;
+// Longest row the one-wavefront-per-row kernel takes, for up to 64 winners: of cells (mode 0, every row has m_fixed) and of
+// results (mode 1, mostly much shorter than their bound).
+constexpr int kSmallMax0 = 8192, kSmallMax1 = kSmallM;
+// Up to that many rows of at most m values a workgroup each is faster all the same, the launch being bound by the latency of one row.
+// Coarse scores and probe selection together, 32 coordinates, 32 probes, workgroup and wavefront, us: 1024 queries x 512 cells 16.0 and
+// 15.7, 1000 cells 15.8 and 16.1, 4096 cells 24.3 and 29.6; 2048 queries x 512 cells 20.0 and 17.3, 1000 cells 22.6 and 19.2, 2000 cells 28.0
+// and 25.9, 4096 cells 35.8 and 37.7; 10,000 queries x 1000 cells 61.5 and 39.1 (x 4096 90.4 and 95.8: the line could lie higher there).
+constexpr int64_t few_rows(int m) { return m <= 2048 ? 1024 : 2048; }
 hipError_t launch_select(int mode, const SelectArgs& a, hipStream_t st) {
     if (a.rows <= 0) return hipSuccess;
     // short rows and small k: the one-wavefront-per-row kernel
     const int m_bound = mode == 0 ? a.m_fixed : a.m_bound;
-    const bool small = a.k <= 64 && m_bound > 0 && m_bound <= (mode == 0 ? kSmallMax0Shortcut : kSmallMax1);
-    if (small && !a.blk_max && a.rows > kSelFewRows) {
-        const size_t lds = 0;
-        const unsigned blocks = (unsigned)((a.rows + 3) / 4);
-#define IVFTQ_SMALL(NVV)                                                                            \
-        if (mode == 0 && a.k > kShortcutTake) hipLaunchKernelGGL((k_select_small<0, NVV, true>), dim3(blocks), dim3(256), lds, st, a);  \
-        else if (mode == 0) hipLaunchKernelGGL((k_select_small<0, NVV>), dim3(blocks), dim3(256), lds, st, a);  \
-        else if (a.k > kShortcutTake) hipLaunchKernelGGL((k_select_small<1, NVV, true>), dim3(blocks), dim3(256), lds, st, a);  \
-        else hipLaunchKernelGGL((k_select_small<1, NVV>), dim3(blocks), dim3(256), lds, st, a);
-        if (m_bound <= 1536 || mode == 1) { IVFTQ_SMALL(16) } else { IVFTQ_SMALL(32) }
-#undef IVFTQ_SMALL
+    const bool small = a.k <= 64 && m_bound > 0 && m_bound <= (mode == 0 ? kSmallMax0 : kSmallMax1);
+    if (small && !a.blk_max && a.rows > few_rows(m_bound)) {
+        const dim3 blocks((unsigned)((a.rows + 3) / 4));
+        const bool wide = a.k > kShortcutTake;
+        const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, blocks, dim3(256), 0, st, a); };
+        if (mode == 1) wide ? go(k_select_small<1, 16, true>) : go(k_select_small<1, 16>);
+        else if (m_bound <= 1536) wide ? go(k_select_small<0, 16, true>) : go(k_select_small<0, 16>);
+        else wide ? go(k_select_small<0, 32, true>) : go(k_select_small<0, 32>);
         return hipGetLastError();
     }
     int kpad = 1;

@@ -13,12 +13,14 @@ TOL = 1e-5
 D, B = 48, 4
 
 
-def _index(sizes, rng, tied, **kw):
+def _index(sizes, rng, tied, same_cells=False):
     import paper_2605_17415_amd as pkg
     L, n = len(sizes), int(sum(sizes))
     cell = rng.permutation(np.repeat(np.arange(L), sizes)).astype(np.int32)
     cent = rng.standard_normal((L, D)).astype(np.float32)
     cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    if same_cells:                                   # the same coarse term everywhere
+        cent[:] = cent[0]
     codes = rng.integers(0, 1 << B, (n, D)).astype(np.uint8)
     gamma = rng.uniform(0.2, 1.2, n).astype(np.float16)
     if tied:                                         # a handful of different vectors, over and over
@@ -165,4 +167,67 @@ def test_a_distance_that_is_no_number_is_no_result(mode, k):
     print(f"[infinite length] mode={mode} k={k}", flush=True)
     s, i = (t.cpu().numpy() for t in ix.search(torch.from_numpy(rng.standard_normal((nq, D)).astype(np.float32)).to("cuda:0"), L, k))
     assert np.isfinite(s).all() and (i >= 0).all() and not np.isin(i, far).any()
+    ix.close()
+
+
+def _check_results(got_s, got_i, true, cell, probe, k, rows):
+    for r in rows:
+        cand = np.flatnonzero(np.isin(cell, probe[r]))
+        take = min(k, len(cand))
+        ids = got_i[r, :take]
+        assert len(set(ids.tolist())) == take and np.isin(ids, cand).all()
+        assert (got_i[r, take:] == -1).all() and np.isneginf(got_s[r, take:]).all()
+        np.testing.assert_allclose(got_s[r, :take], true[r, ids], rtol=0, atol=TOL)
+        np.testing.assert_allclose(got_s[r, :take], np.sort(true[r, cand])[::-1][:take], rtol=0, atol=TOL)
+        same = got_s[r, :take][:-1] == got_s[r, :take][1:]
+        assert (np.diff(got_s[r, :take]) <= 0).all() and (np.diff(ids)[same] > 0).all()
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("tied", [False, True])
+@pytest.mark.parametrize("k", [1, 10, 32, 33, 64, 65, 200, 256])
+def test_results_of_many_queries(mode, tied, k):
+    """Above 1024 rows of up to 2048 candidates, and above 2048 longer ones, up to 64 results are selected by one wavefront a row; more,
+    and smaller calls, by a workgroup a row (from 193 on by its radix search).  One query is infinite."""
+    rng = np.random.default_rng(k + 7 * mode + tied)
+    ix, cell, cent, codes, gamma = _index([0, 1, 63, 64, 65, 0, 127, 128, 129, 0, 0, 191, 255, 256, 257, 300, 511, 512, 513, 64], rng, tied)
+    ix.set_search_mode(mode)
+    print(f"[many queries] mode={mode} tied={tied} k={k}", flush=True)
+    for nq, nprobe in ((1025, 4), (2049, 20)):
+        q = rng.standard_normal((nq, D)).astype(np.float32)
+        q[5, 2] = np.inf
+        qd = torch.from_numpy(q).to("cuda:0")
+        probe = ix.coarse_probe(qd, nprobe)[0].cpu().numpy()
+        s, i = (t.cpu().numpy() for t in ix.search(qd, nprobe, k))
+        assert (i[5] == -1).all() and np.isneginf(s[5]).all()
+        q[5, 2] = 0.0
+        some = np.setdiff1d(rng.integers(0, nq, 60), [5])
+        true = np.zeros((nq, len(cell)))
+        true[some] = _scores(ix, q[some], cell, cent, codes, gamma)
+        _check_results(s, i, true, cell, probe, k, some)
+    ix.close()
+
+
+@pytest.mark.parametrize("shape,tied", [("edges", False), ("edges", True), ("equal", True), ("longest", False), ("longest", True)])
+@pytest.mark.parametrize("k", [1, 10, 24, 25, 100, 192, 193])
+def test_results_of_long_rows(shape, tied, k):
+    """Rows whose results are selected through block maxima (up to 192 results, 12,288 candidates and more): lists around whole blocks;
+    more than 512 blocks whose best scores are equal, where the selection goes back to the whole row; more than 262,144 candidates,
+    whose block maxima no longer fit a thread's registers."""
+    rng = np.random.default_rng(len(shape) + k + 3 * tied)
+    sizes = {"edges": [0, 1, 63, 64, 65, 0, 127, 128, 129, 0, 0, 191, 255, 256, 257, 300, 511, 512, 513, 64] * 8,
+             "equal": [6000] * 8, "longest": [6000] * 50}[shape]
+    ix, cell, cent, codes, gamma = _index(sizes, rng, tied, same_cells=shape == "equal")       # (equal: some 9600 vectors share a score)
+    ix.set_search_mode(1)
+    print(f"[long rows] {shape} tied={tied} k={k}", flush=True)
+    for nq in (1, 3) if shape == "longest" else (1, 66):
+        q = rng.standard_normal((nq, D)).astype(np.float32)
+        qd = torch.from_numpy(q).to("cuda:0")
+        nprobe = len(sizes)
+        probe = ix.coarse_probe(qd, nprobe)[0].cpu().numpy()
+        s, i = (t.cpu().numpy() for t in ix.search(qd, nprobe, k))
+        some = np.arange(nq) if nq < 4 else rng.integers(0, nq, 10)
+        true = np.zeros((nq, len(cell)))
+        true[some] = _scores(ix, q[some], cell, cent, codes, gamma)
+        _check_results(s, i, true, cell, probe, k, some)
     ix.close()

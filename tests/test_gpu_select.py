@@ -57,3 +57,41 @@ def test_probe_selection_with_exact_ties(L, nprobe):
                 assert ca < cb, f"query {qi}: tied cells {ca}, {cb} out of order"
     print(f"  rows whose set differs within the tolerance of the cut: {swaps} of {nq}", flush=True)
     ix.close()
+
+
+@pytest.mark.parametrize("L,nprobe,nq,different", [
+    (4096, 8, 2049, 2048), (4096, 32, 2049, 2048), (4096, 33, 2049, 2048), (4096, 64, 2049, 2048), (8000, 64, 2050, 4000), (2500, 50, 2051, 1250),
+    (1200, 10, 1025, 600), (1200, 48, 1027, 600), (100, 10, 1025, 50), (2048, 20, 1025, 1024), (2049, 20, 2048, 1025),
+    (4096, 10, 2049, 5), (4096, 50, 2049, 5), (1000, 64, 1030, 3),                         # (hundreds of equal scores at the cut)
+    (127, 20, 300, 64), (128, 64, 300, 7), (129, 64, 300, 7), (129, 100, 300, 65), (300, 8, 300, 3), (512, 200, 300, 256), (513, 30, 300, 5)])
+def test_probes_of_every_kernel_with_exact_ties(L, nprobe, nq, different):
+    """The one-wavefront kernel, which takes over above 1024 rows of up to 2048 cells and above 2048 longer ones, with its short cuts for up to
+    32 and 64 winners and its radix search (hundreds of equal scores); the workgroup kernel around the 128 cells that it orders
+    whole.  Cell i is a copy of cell i - different: a copy is never listed without, nor before, the cell that it copies."""
+    import paper_2605_17415_amd as pkg
+    d = 32
+    rs = np.random.Generator(np.random.Philox(key=[L + nq, nprobe]))
+    base = rs.standard_normal((different, d))
+    base = (base / np.linalg.norm(base, axis=1, keepdims=True)).astype(np.float32)
+    of = np.arange(L) % different
+    Q = rs.standard_normal((nq, d)).astype(np.float32)
+    Q[nq // 2, 3] = np.inf
+    ix = pkg.Index(d, 4, L)
+    ix.set_coarse(base[of])
+    print(f"[select] L={L} nprobe={nprobe} nq={nq} different={different}", flush=True)
+    probe, coarse = (t.cpu().numpy() for t in ix.coarse_probe(torch.from_numpy(Q).to(DEV), nprobe))
+    assert (probe[nq // 2] == -1).all() and np.isneginf(coarse[nq // 2]).all()
+    keep = np.arange(nq) != nq // 2
+    probe, coarse, Q = probe[keep], coarse[keep], Q[keep]
+    S = (orc.normalize_rows(Q) @ orc.normalize_rows(base).T)[:, of]
+    rows = np.arange(nq - 1)[:, None]
+    want = np.sort(S, axis=1)[:, ::-1][:, :nprobe]
+    np.testing.assert_allclose(coarse, want, rtol=0, atol=TOL)
+    np.testing.assert_allclose(S[rows, probe], want, rtol=0, atol=TOL)
+    assert np.all(np.diff(coarse, axis=1) <= 0)
+    assert np.all((np.diff(coarse, axis=1) < 0) | (np.diff(probe, axis=1) > 0)), "tied cells out of order"
+    listed = np.zeros((nq - 1, L), bool)
+    listed[rows, probe] = True
+    assert np.all(listed.sum(1) == nprobe), "a cell is listed twice"
+    assert np.all(listed[:, :-different] | ~listed[:, different:]), "a copy is listed without the cell that it copies"
+    ix.close()
