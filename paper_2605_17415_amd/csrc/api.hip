@@ -1481,7 +1481,14 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             // and, while a share of a typical list still fills two rounds, until about 8192 are (64 queries at
             // 10M x 96: scan 0.100 -> 0.070 ms)
             slices = std::max(slices, std::min<int64_t>(kStreamWorkgroups / ((int64_t)per_query * cnt), ix->ntotal / ix->nlist / 512));
-            la.blk_max = ix->w_blk.as<uint32_t>(); la.blk_stride = block_index((int)m_stride, nprobe);
+            // Block maxima: the scan pays for them with every 64 vectors that it reads, the selection's gain is the latency of reading
+            // long rows.  So for long rows, where a call has few of them and the selection can use them (up to 192 results).  Search with
+            // them and without, us, k = 10, 4 bits x 96: 1 query, 7800 candidates 25 and 25, 15,600 25 and 31, 62,000 29 and 59;
+            // 256 queries, 15,600 75 and 74, 31,000 112 and 117, 62,000 184 and 199; 1024 queries, 31,000 332 and 324; 8 bits x 64:
+            // 64 queries, 31,000 94 and 101; 256, 31,000 285 and 271, 62,000 442 and 426; 8000, 15,600 2588 and 2240.
+            if (k <= kSelTake && typical >= kBlockMaximaRow && cnt <= typical / 200) {
+                la.blk_max = ix->w_blk.as<uint32_t>(); la.blk_stride = block_index((int)m_stride, nprobe);
+            }
             HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, per_query, (int)slices, st); }));
             sa.blk_max = la.blk_max; sa.blk_stride = la.blk_stride;
             sa.metric = metric; sa.qnorm = la.qnorm;

@@ -332,7 +332,6 @@ constexpr int kSelSmallU = 8;   // and by k_select_small beyond its registers
 constexpr int kSelCand = 512;   // most keys the short cut of k_select orders
 constexpr int kSelAll = 128;    // most columns of a row that is ordered whole (as for 512, the square of whose number that takes: probes of
                                 // 2048 queries over 512 cells, 20 us with a bound for 128 columns and more, 33 without one)
-constexpr int kSelTake = 192;   // most winners it is used for
 constexpr int kSelHeld = 16;    // columns (or block maxima) a thread keeps in registers between its two passes
 constexpr int kSelBlocks = 512; // most blocks it gathers from
 constexpr int kSelOffs = 256;   // most probes whose offsets are staged in LDS
