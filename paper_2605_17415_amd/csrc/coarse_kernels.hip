@@ -101,7 +101,7 @@ __device__ __forceinline__ bool load_rows(const float* __restrict__ x, int64_t r
 // ACROSS: the data rows are the row operand, so that a lane holds 16 rows' scores against one table row and the 32 lanes of a half
 // store 128 bytes in a row; else a lane holds one row's scores and stores 16 bytes at a time, 32 rows apart from lane to lane.
 template <int DP, int R, bool VEC4, bool ACROSS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP <= 64 || ScoresCfg<DP>::turned ? 3 : 2))) void k_coarse(CoarseArgs a, int per_y) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ScoresCfg<DP>::turned ? 3 : 2))) void k_coarse(CoarseArgs a, int per_y) {
     using Cfg = ScoresCfg<DP>;
     constexpr int KB = DP / 16;
     extern __shared__ __align__(16) unsigned char lds_raw[];
