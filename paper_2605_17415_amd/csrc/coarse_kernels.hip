@@ -702,11 +702,11 @@ hipError_t run_as(const CoarseArgs& a, hipStream_t st) {
 template <int DP, int R>
 hipError_t run(const CoarseArgs& a, hipStream_t st) {
     const bool vec4 = (a.d % 4 == 0) && (reinterpret_cast<uintptr_t>(a.x) % 16 == 0);
-    // Stores of whole lines are four times as many instructions, most of them for rows that a small call does not have:
-    // without against with them, a call of 16 queries over 10M x 96 53.7 us against 54.8, 200 over 20,000 x 64 134 against 137, 256 over
-    // 10M x 200 and 1000 over 1M x 100 the same; 10,000 over 10M x 96 704 against 698, 10M x 200 1814 against 1775 (of which
-    // the third workgroup of ScoresCfg is a part).
-    if (a.n > 1024) return vec4 ? run_as<DP, R, true, true>(a, st) : run_as<DP, R, false, true>(a, st);
+    // Stores of whole lines are four times as many instructions, most of them for rows that a small call does not have, and pay
+    // where there are many scores to store.  Coarse scores and 8 probes, without against with them, us: 4096 queries x 1024 cells x 32 23.8
+    // and 25.3, x 96 27.4 and 28.8; 10,000 x 1024 x 32 37.0 and 38.5, x 96 43.6 and 41.5; 30,000 x 1024 x 32 69 and 67; 4096 x 4096 x 96
+    // 50.7 and 49.3; 10,000 x 4096 x 96 98.9 and 95.6; 30,000 x 4096 x 96 299 and 276, x 200 565 and 396.
+    if (a.n * a.Lpad > (int64_t)8 << 20) return vec4 ? run_as<DP, R, true, true>(a, st) : run_as<DP, R, false, true>(a, st);
     return vec4 ? run_as<DP, R, true, false>(a, st) : run_as<DP, R, false, false>(a, st);
 }
 

@@ -1,5 +1,5 @@
-"""GPU: coarse scores and rotated queries have the same bits whichever operand the queries are (small calls: the column one, more than
-1024 queries: the row one), at every panel width, with queries that end inside a tile and a number of cells that is no
+"""GPU: coarse scores and rotated queries have the same bits whichever operand the queries are (small calls: the column one, from 8M scores
+on: the row one), at every panel width, with queries that end inside a tile and a number of cells that is no
 multiple of anything; and the scores agree with float64.
 
 Tolerance: a dot product of unit vectors in split float16 form is within 2e-6 of float64."""
@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,L,nq", [(20, 67, 1025), (64, 70, 1026), (96, 133, 1300), (100, 1000, 1055), (128, 65, 1057), (150, 70, 1025), (192, 64, 1060), (200, 333, 1281),
-                                    (208, 70, 1025), (224, 66, 1100), (255, 70, 1027), (256, 129, 1536)])
+                                    (208, 70, 1025), (224, 66, 1100), (255, 70, 1027), (256, 129, 1536),
+                                    (20, 4033, 2110), (64, 2050, 4070), (96, 4096, 2049), (100, 4095, 2081), (128, 1025, 7720), (150, 4040, 2075),
+                                    (192, 4097, 2056), (200, 3333, 2501), (208, 4000, 2101), (224, 1026, 7720), (255, 4010, 2091), (256, 2049, 3999)])
 def test_same_bits_in_large_and_small_calls(d, L, nq):
     import paper_2605_17415_amd as pkg
     rng = np.random.default_rng(d + L)
