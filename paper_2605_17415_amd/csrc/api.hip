@@ -1525,6 +1525,13 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         // 3. the other lists against the thresholds
         ba.dense = 0; ba.part_len = shape.part;
         ba.thresh = ix->w_fscores.as<float>() + (k - 1); ba.thresh_stride = k;
+        {
+            // (rows without clusters append up to about half of what a query has room for, spread over its lists: 150 of 512 for 10 results,
+            // 240 for 30, 840 to 960 of 1600 for 100)
+            const int64_t pairs = cnt * nprobe, lists = std::min<int64_t>(ix->nlist, pairs);
+            ba.dequantised = (lists + pairs / shape.tq) * std::max<int64_t>(1, ix->ntotal / ix->nlist) * ix->d;
+            ba.tile_candidates = std::min<int64_t>(shape.tq, (pairs + lists - 1) / lists) * (cap / 2) / nprobe;
+        }
         HIP_TRY(timed(ix, st, P_BATCH_SCAN, [&] { return launch_batch_scan(ba, ix->d, bits, st); }));
         // 4. merge; a query whose candidate list overflowed is redone by the exact streaming scan
         MergeArgs ma{};

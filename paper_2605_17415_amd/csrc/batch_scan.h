@@ -28,6 +28,12 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
 namespace {
 
+// Copies of the table of code pairs in a threshold pass that is worth them (run_batch).  Entry e's c-th lies at e * copies + c and a
+// lane reads copy lane % copies, so that the 64 lanes of a look-up, each with a pair of its own, collide on fewer banks.
+// Clocks of a compute unit per look-up by two workgroups, 256 entries: 1 copy 7.5, 2 8.1, 4 6.6, 8 6.0, 16 4.4, 32 4.4.
+constexpr int kTableCopies = 16;
+constexpr int64_t kCopiesFrom = 400'000'000;       // coordinates de-quantised by a pass from which their making is paid back
+
 template <int DP, int B, int NQ>
 struct BatchCfg {
     static constexpr int TQ = NQ * 32;
@@ -38,26 +44,17 @@ struct BatchCfg {
     static constexpr size_t lds_dense = (size_t)2 * TQ * LDH * sizeof(uint16_t) + 16 * TQ + (size_t)PT * (PAIR ? 8 : 4);
     // LDS of a workgroup when a compute unit holds `occ` of them (in whole allocation units, less the passes' static words)
     static constexpr size_t room(int occ) { return 160 * 1024 / occ / 1280 * 1280 - 64; }
-    // Threshold pass.  The table is kept in several copies, entry e's c-th at e * copies + c, and a lane reads copy lane %
-    // copies: the 64 lanes of a look-up, each with a code pair of its own, collide on fewer banks.  Clocks of a compute unit per
-    // look-up by two workgroups: 1 copy 7.5, 2 8.1, 4 6.6, 8 6.0, 16 4.4, 32 4.4.  As many as there is room for beside 400 candidates
-    // held back, at most 16 (pass of 256 queries over 10M x 200 304 -> 280 us, 10,000 over 10M x 96 247 -> 240).  The dense pass
-    // keeps one: the room would cost it workgroups (10M x 96 with 16 copies 234 -> 305 us), and where it does not
-    // (10M x 200, 8 copies) they changed nothing.
+    // Threshold pass: hi parts of the panel, the table, perhaps in several copies, and (hold) candidates of a tile held back in
+    // what is left of the room, at most 4096.
     static constexpr size_t panel_threshold = (size_t)TQ * LDH * sizeof(uint16_t) + 16 * TQ, table_threshold = (size_t)PT * 4;
-    static constexpr int copies_threshold(int occ, bool hold) {
-        for (int c = 16; c > 2; c /= 2)
-            if (panel_threshold + (hold ? 8 * 400 + 4 * TQ : 0) + c * table_threshold <= room(occ)) return c;
-        return 1;
-    }
-    // Candidates of a tile held back: what is left of the room, at most 4096.
-    static constexpr int held_back(int occ) {
-        const size_t fit = (room(occ) - panel_threshold - copies_threshold(occ, true) * table_threshold - 4 * TQ) / 8;
+    static constexpr int held_back(int occ, int copies) {
+        const size_t fit = (room(occ) - panel_threshold - copies * table_threshold - 4 * TQ) / 8;
         return fit < 4096 ? (int)fit / 2 * 2 : 4096;
     }
-    static constexpr size_t lds_threshold(int occ, bool hold) {
-        return panel_threshold + copies_threshold(occ, hold) * table_threshold + (hold ? 8 * (size_t)held_back(occ) + 4 * TQ : 0);
+    static constexpr size_t lds_threshold(int occ, bool hold, int copies) {
+        return panel_threshold + copies * table_threshold + (hold ? 8 * (size_t)held_back(occ, copies) + 4 * TQ : 0);
     }
+    static constexpr bool copies_fit(int occ, bool hold) { return lds_threshold(occ, false, kTableCopies) + (hold ? 8 * 400 + 4 * TQ : 0) <= room(occ); }
 };
 
 // The 8 codes of block kb that a lane de-quantises, coordinates 16*kb + 8*half + [0, 8), begin in word first_word
@@ -329,18 +326,18 @@ void k_batch_dense(BatchScanArgs a) {
 // few.  HOLD keeps the candidates of a tile in LDS and updates a counter once per tile (rows without clusters, 1M x
 // 128, inner product, 100 queries of 64 probes, k = 100, up to 1172 candidates a query: 203 -> 104 us); what does not fit is
 // appended at once.  It is left out where its registers would spill (the 96-wide panel at three wavefronts per SIMD).
-template <int DP, int B, int NQ, int WAVES, int OCC, int S, bool RAW, bool HOLD>
+// TC: copies of the table.
+template <int DP, int B, int NQ, int WAVES, int OCC, int S, bool RAW, bool HOLD, int TC>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(OCC)))
 void k_batch_threshold(BatchScanArgs a) {
     using Cfg = BatchCfg<DP, B, NQ>;
     constexpr int KB = DP / 16, NT = WAVES * 64, VB = 32 * S;      // vectors of a block
-    constexpr int CAND = Cfg::held_back(OCC);
+    constexpr int CAND = Cfg::held_back(OCC, TC);
     constexpr int NW = (B == 2 || B == 4) ? 1 : 2;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* zh = reinterpret_cast<uint16_t*>(lds_raw);                       // [TQ][LDH] hi parts of the rotated queries
     uint4* s_row = reinterpret_cast<uint4*>(zh + Cfg::TQ * Cfg::LDH);          // [TQ] coarse term, threshold, pair number, |q|
     uint32_t* tab = reinterpret_cast<uint32_t*>(s_row + Cfg::TQ);                // [PT][TC] hi parts of a code pair, packed (or of one code)
-    constexpr int TC = Cfg::copies_threshold(OCC, HOLD);
     uint2* s_cand = reinterpret_cast<uint2*>(tab + Cfg::PT * TC);                     // HOLD: [CAND] score bits; column | vector of the part << 7 | place among the column's << 19
     int* s_cnt = reinterpret_cast<int*>(s_cand + CAND);                          // HOLD: [TQ] held back per column, then their first position
     static_assert(Cfg::TQ <= 128 && kPartMax <= 4096, "fields of a candidate held back");
@@ -584,7 +581,7 @@ hipError_t run_batch(const BatchScanArgs& a, hipStream_t st) {
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(dense, dim3(wgs), dim3(256), lds, st, a);
     } else {
-        static ChipFill fill_t[2];
+        static ChipFill fill_t[3];
         constexpr int NQ = kBatchTile / 32;
         // two row tiles and wavefronts per SIMD where the registers (operands of both tiles, and the words of the
         // next block, twice or four times as many where codes straddle words or are bytes) allow it without spills
@@ -593,15 +590,27 @@ hipError_t run_batch(const BatchScanArgs& a, hipStream_t st) {
         constexpr int OCC = S == 2 && DP + words <= 102 ? 3 : 2;
         constexpr bool HOLD = OCC == 2 || DP <= 64;
         using Cfg = BatchCfg<DP, B, NQ>;
-        constexpr size_t lds_plain = Cfg::lds_threshold(OCC, HOLD), lds_raw = Cfg::lds_threshold(2, true);
-        constexpr auto plain = k_batch_threshold<DP, B, NQ, 4, OCC, S, false, HOLD>;
-        constexpr auto raw = k_batch_threshold<DP, B, NQ, 4, 2, S_RAW, true, true>;
-        const size_t lds = a.metric ? lds_raw : lds_plain;
-        unsigned wgs = 0;
-        const hipError_t e = a.metric ? fill_t[1].get(reinterpret_cast<const void*>(raw), 256, lds, &wgs) : fill_t[0].get(reinterpret_cast<const void*>(plain), 256, lds, &wgs);
+        // Copies of the table (4 bits: 256 entries; a table of 64 has no two entries on one bank, one of 1024 leaves too little
+        // room): a workgroup makes them once, 1 to 2 us, which only a long pass pays back, and they take room from the candidates held
+        // back, which rows without clusters need.  So where the pass is long and what such rows would leave in a tile fits all
+        // the same.  Pass with copies and without, us, 64 probes of 3M x 200: 256 queries 124 and 129, 10,000 474 and 495; 32 of 3M x 96:
+        // 256 queries 88 and 86, 10,000 148 and 150; 24 of 400,000 x 128: 300 queries 27.5 and 26.4; 400,000 rows without clusters,
+        // 4000 queries, k = 100: x 192 266 and 218, x 208 295 and 222, x 224 340 and 250.
+        constexpr bool kCopied = B == 4 && Cfg::copies_fit(OCC, HOLD);
+        constexpr int TC = kCopied ? kTableCopies : 1;
+        const bool copied = kCopied && !a.metric && a.dequantised >= kCopiesFrom && (!HOLD || a.tile_candidates <= Cfg::held_back(OCC, TC));
+        constexpr auto plain = k_batch_threshold<DP, B, NQ, 4, OCC, S, false, HOLD, 1>, with_copies = k_batch_threshold<DP, B, NQ, 4, OCC, S, false, HOLD, TC>;
+        constexpr auto raw = k_batch_threshold<DP, B, NQ, 4, 2, S_RAW, true, true, 1>;
+        const auto go = [&](ChipFill& fill, auto kernel, size_t lds) -> hipError_t {
+            unsigned wgs = 0;
+            const hipError_t e = fill.get(reinterpret_cast<const void*>(kernel), 256, lds, &wgs);
+            if (e == hipSuccess) hipLaunchKernelGGL(kernel, dim3(wgs), dim3(256), lds, st, a);
+            return e;
+        };
+        const hipError_t e = a.metric ? go(fill_t[1], raw, Cfg::lds_threshold(2, true, 1))
+                             : copied ? go(fill_t[2], with_copies, Cfg::lds_threshold(OCC, HOLD, TC))
+                                      : go(fill_t[0], plain, Cfg::lds_threshold(OCC, HOLD, 1));
         if (e != hipSuccess) return e;
-        if (a.metric) hipLaunchKernelGGL(raw, dim3(wgs), dim3(256), lds, st, a);
-        else hipLaunchKernelGGL(plain, dim3(wgs), dim3(256), lds, st, a);
     }
     return hipGetLastError();
 }

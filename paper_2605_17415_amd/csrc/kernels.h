@@ -385,6 +385,7 @@ struct BatchScanArgs {
     // threshold mode: cand_score = upper bound of the score (see acc0), cand_slot = slot | probe rank << kCandProbeShift
     float* cand_score; int64_t* cand_slot; int32_t* cand_cnt; int cap;
     float acc0;                          // 2^20 * kappa, added to the threshold pass's accumulators
+    int64_t dequantised, tile_candidates;     // threshold mode: coordinates that the pass looks up, and what rows without clusters would append in a tile
     // dense mode (the nearest lists): every score goes to scores[q*m_stride + cand_off[q][p] + v]
     int dense; float* scores; int64_t m_stride; const int32_t* cand_off;
     int metric; const float* qnorm;      // scores are ranking keys of a raw metric (metric_key)

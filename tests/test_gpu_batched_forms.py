@@ -130,3 +130,34 @@ def test_scores_no_further_off_than_streamed(d, b):
         rms.append(np.sqrt(np.mean((s - want) ** 2)))
     assert rms[1] <= 1.015 * rms[0]
     ix.close()
+
+
+@pytest.mark.parametrize("d", [33, 64, 96, 100, 128, 150, 192, 200, 224, 256])
+def test_long_passes_give_the_bits_of_short_ones(d):
+    """From 400 million looked-up coordinates on, a threshold pass of 4-bit codes keeps its table in sixteen copies (at every width but
+    256, where they do not fit): 4000 queries of 128 lists in one call, and the first 70 and last 33 in calls of their own, on codes without
+    clusters, so that there are candidates to hold back and append."""
+    import paper_2605_17415_amd as pkg
+    rng = np.random.default_rng(d)
+    L, nq, nprobe, k = 256, 4000, 128, 10
+    panel = min(p for p in (64, 96, 128, 160, 192, 208, 224, 256) if p >= d)
+    typical = int(4.2e8 / ((L + nq * nprobe // 128) * d)) + 1
+    n = typical * L
+    print(f"[long pass] d={d} panel={panel} n={n}", flush=True)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d)
+    ix = pkg.Index(d, 4, L, rotation_seed=3)
+    cent = rng.standard_normal((L, d)).astype(np.float32)
+    ix.set_coarse(cent / np.linalg.norm(cent, axis=1, keepdims=True))
+    ix.add_encoded(torch.randint(0, L, (n,), generator=g, device="cuda:0", dtype=torch.int32), torch.randint(0, 16, (n, d), generator=g, device="cuda:0", dtype=torch.uint8),
+                   (0.3 + 0.5 * torch.rand(n, generator=g, device="cuda:0")).to(torch.float16))
+    ix.set_search_mode(2)
+    q = torch.randn((nq, d), generator=g, device="cuda:0")
+    whole = [t.cpu().numpy() for t in ix.search(q, nprobe, k)]
+    stats = ix.scan_stats()
+    assert stats["queries"] == nq and stats["mean_candidates"] >= 1      # (that is 4000 held back and more; a few a query in the first widths)
+    for lo, hi in ((0, 70), (nq - 33, nq)):
+        part = [t.cpu().numpy() for t in ix.search(q[lo:hi].contiguous(), nprobe, k)]
+        np.testing.assert_array_equal(part[0], whole[0][lo:hi])
+        np.testing.assert_array_equal(part[1], whole[1][lo:hi])
+    ix.close()
