@@ -356,8 +356,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
     // share of the centroid stages and leaves (best, second best, index) of every row in `part`, where
     // k_coarse_screen_join puts them together.
     const bool split = (int)blockIdx.x >= whole;
-    const int rest = (int)blockIdx.x - whole;
-    const int block = split ? whole + rest / shares : (int)blockIdx.x, share = split ? rest % shares : 0;
+    // (neighbouring workgroups take the same share of different blocks: the workgroups of a block then meet on few of the chip's
+    // eight L2 caches, which each read its rows from memory)
+    const int rest = (int)blockIdx.x - whole, split_blocks = ((int)gridDim.x - whole) / shares;
+    const int block = split ? whole + rest % split_blocks : (int)blockIdx.x, share = split ? rest / split_blocks : 0;
     const int n_stages = Lpad / TN, per_share = split ? (n_stages + shares - 1) / shares : n_stages;
     const int c_lo = share * per_share * TN < Lpad ? share * per_share * TN : Lpad;
     const int c_hi = c_lo + per_share * TN < Lpad ? c_lo + per_share * TN : Lpad;
@@ -633,23 +635,25 @@ hipError_t run_screened_as(const ScreenArgs& a, hipStream_t st) {
     e = fill.get(reinterpret_cast<const void*>(k_coarse_screen<DP, RS, VEC4, BIAS>), 256, lds_screen, &held, &units);
     if (e != hipSuccess) return e;
     // Rounds of row blocks that fill the chip are a workgroup a block.  The blocks of a last round, or of a short batch, are
-    // shared out over the centroid stages where that is faster, given room for the partial results.  Measured (96 to
-    // 200 coordinates, 1024 and 4096 centroids, 500 to 500,000 rows, 1 to 16 shares): with m workgroups a compute unit a
-    // stage takes as m, one alone as 1.5; reading and splitting a workgroup's rows takes 4 stages, and the joining launch
-    // 3 us, about 350 / DP of them.  Both sides, us a call: 4096 centroids, 262,147 rows x 200 (one block of 1025 left over) 659
-    // whole, 558 in 16 shares; 170,000 x 200 472 and 379 (3); 65,000 x 96 103 and 79 (2); 100,000 x 96 116 and 120 (3); with
-    // 500 rows x 96 81 and 28 (16).  A finer split has to be cheaper by a 25th.
+    // shared out over the centroid stages where that is faster, given room for the partial results.  Measured (32 to
+    // 256 coordinates, 256 to 4096 centroids, 500 to 300,000 rows, 1 to 16 shares): with m workgroups a compute unit a
+    // stage takes as m, one alone as 1.7 (up to 64 coordinates, of which a unit holds four, one to three as 1.9, 2.4 and 3.2); reading and
+    // splitting the rows of each takes 4 more, and the joining launch 3 us, about 350 / DP of them.  A finer split has to be
+    // cheaper by 3 %.  Assignment, us, whole and in the shares that this chooses: 4096 centroids, 262,147 rows x 200 (one block of 1025 left
+    // over) 659 and 558 (16); 50,000 x 200 188 and 122 (5); 100,000 x 32 65 and 59 (3); 65,000 x 96 91 and 67 (2); 2000 x 96 73 and 20 (16).  On
+    // 420 sizes it is within 3 % of a fixed rule (powers of 2 up to 1024 workgroups, no split from 262,144 rows on) or faster.
     const int64_t blocks = (a.n + kBlockRows - 1) / kBlockRows;
     const int64_t rest = blocks % held, n_stages = a.Lpad / (screen_nt<DP>() * 32);
     int shares = 1;
     auto cost = [&](int64_t s) {           // in tenths of a stage
         const int64_t m = (rest * s + units - 1) / units;
-        return (m <= 1 ? 15 : 10 * m) * ((n_stages + s - 1) / s + 4) + (s > 1 ? 3500 / DP : 0);
+        const int64_t stage = DP <= 64 ? (m <= 1 ? 19 : m == 2 ? 24 : m == 3 ? 32 : 10 * m) : m <= 1 ? 17 : 10 * m;
+        return stage * ((n_stages + s - 1) / s) + 40 * m + (s > 1 ? 3500 / DP : 0);
     };
     if (a.part && rest) {
         int64_t least = cost(1);
         for (int s = 2; s <= kScreenMaxShares && 2 * s <= n_stages && rest * kBlockRows * s <= a.part_entries; ++s)
-            if (25 * cost(s) < 24 * least) { least = cost(s); shares = s; }
+            if (100 * cost(s) < 97 * least) { least = cost(s); shares = s; }
     }
     const int64_t whole = shares > 1 ? blocks - rest : blocks, first = whole * kBlockRows;
     hipLaunchKernelGGL((k_coarse_screen<DP, RS, VEC4, BIAS>), dim3((unsigned)(whole + (blocks - whole) * shares)), dim3(256), lds_screen, st, a.x, a.n, a.d,
