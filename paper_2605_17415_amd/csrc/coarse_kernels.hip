@@ -356,11 +356,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DP <= 128 
     // share of the centroid stages and leaves (best, second best, index) of every row in `part`, where
     // k_coarse_screen_join puts them together.
     const bool split = (int)blockIdx.x >= whole;
-    // (neighbouring workgroups take the same share of different blocks: the workgroups of a block then meet on few of the chip's
-    // eight L2 caches, which each read its rows from memory)
-    const int rest = (int)blockIdx.x - whole, split_blocks = ((int)gridDim.x - whole) / shares;
-    const int block = split ? whole + rest % split_blocks : (int)blockIdx.x, share = split ? rest / split_blocks : 0;
-    const int n_stages = Lpad / TN, per_share = split ? (n_stages + shares - 1) / shares : n_stages;
+    // Eight blocks at a time, share by share: every eighth workgroup runs on the same one of the chip's eight parts, so that the
+    // workgroups of a block meet in one L2 cache and its rows are read from memory once.  (Next to each other: 2000 rows x 96
+    // over 4096 cells 21.2 us instead of 20.)
+    const int n_stages = Lpad / TN;
+    int block = (int)blockIdx.x, share = 0, per_share = n_stages;
+    if (split) {
+        const int rest = block - whole, split_blocks = ((int)gridDim.x - whole) / shares;
+        const int eight = rest / (8 * shares) * 8, in_eight = rest - eight * shares, side = split_blocks - eight < 8 ? split_blocks - eight : 8;
+        block = whole + eight + in_eight % side;
+        share = in_eight / side;
+        per_share = (n_stages + shares - 1) / shares;
+    }
     const int c_lo = share * per_share * TN < Lpad ? share * per_share * TN : Lpad;
     const int c_hi = c_lo + per_share * TN < Lpad ? c_lo + per_share * TN : Lpad;
     uint16_t* th = reinterpret_cast<uint16_t*>(lds_raw);            // [2][TN][LDH] hi parts of the centroids
