@@ -1482,11 +1482,13 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
             // 10M x 96: scan 0.100 -> 0.070 ms)
             slices = std::max(slices, std::min<int64_t>(kStreamWorkgroups / ((int64_t)per_query * cnt), ix->ntotal / ix->nlist / 512));
             // Block maxima: the scan pays for them with every 64 vectors that it reads, the selection's gain is the latency of reading
-            // long rows.  So for long rows, where a call has few of them and the selection can use them (up to 192 results).  Search with
-            // them and without, us, k = 10, 4 bits x 96: 1 query, 7800 candidates 25 and 25, 15,600 25 and 31, 62,000 29 and 59;
+            // long rows, the longer the more results there are (two blocks a result and more are read again).  So for long rows, where a
+            // call has few of them and the selection can use them (up to 192 results).  Search with them and without, us, 4 bits x 96, 9
+            // queries: k = 10, 7000 candidates 25.2 and 25.3, 10,000 25.1 and 26.4, 12,000 25.5 and 28.2; k = 47, 10,000 28.0 and 27.7, 12,000
+            // 28.3 and 29.4; k = 100, 12,000 34.1 and 30.3.  k = 10: 1 query, 15,600 25 and 31, 62,000 29 and 59;
             // 256 queries, 15,600 75 and 74, 31,000 112 and 117, 62,000 184 and 199; 1024 queries, 31,000 332 and 324; 8 bits x 64:
             // 64 queries, 31,000 94 and 101; 256, 31,000 285 and 271, 62,000 442 and 426; 8000, 15,600 2588 and 2240.
-            if (k <= kSelTake && typical >= kBlockMaximaRow && cnt <= typical / 200) {
+            if (k <= kSelTake && typical >= kBlockMaximaRow + (int64_t)k * k && cnt <= typical / 200) {
                 la.blk_max = ix->w_blk.as<uint32_t>(); la.blk_stride = block_index((int)m_stride, nprobe);
             }
             HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, per_query, (int)slices, st); }));

@@ -253,7 +253,7 @@ struct CandOffsetArgs {
     uint32_t* bucket_cnt; int buckets;
 };
 constexpr int kSelTake = 192;                   // most winners that the workgroup selection's short cut, which alone reads block maxima, is for
-constexpr int64_t kBlockMaximaRow = 12288;      // candidates of a typical row from which a small streaming call leaves block maxima
+constexpr int64_t kBlockMaximaRow = 8192;       // candidates of a typical row, besides k * k, from which a small streaming call leaves block maxima
 // Where the block maxima of a query's probe p begin when `col` candidates precede it.  Every probe has one place more than
 // the 64-column groups its candidates touch at most, so that its blocks, counted from its first candidate, fit.
 __host__ __device__ constexpr int block_index(int col, int p) { return (col >> 6) + p; }

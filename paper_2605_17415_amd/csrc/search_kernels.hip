@@ -405,7 +405,8 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     bool picked = false;
     if (tid == 0) { ctrl[5] = 0; ctrl[6] = 0; }
     const int n_blk = MODE == 1 && a.blk_max ? block_index(m, n_off) : 0;
-    // (few blocks for many winners: their maxima say little)
+    // (few blocks for many winners: their maxima say little.  100 winners of 12,000 candidates, 200 blocks: 34 us a call through the
+    // blocks, 30 from the scores)
     const bool by_block = n_blk >= 2 * take && m > kSelCand;
     if (take > 0 && ((take <= kSelTake && m > k) || m <= kSelAll)) {
         // (one base pointer and loads without a branch between them, so that all of a thread's are in flight together)

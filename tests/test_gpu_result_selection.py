@@ -211,7 +211,7 @@ def test_results_of_many_queries(mode, tied, k):
 @pytest.mark.parametrize("shape,tied", [("edges", False), ("edges", True), ("equal", True), ("longest", False), ("longest", True)])
 @pytest.mark.parametrize("k", [1, 10, 24, 25, 100, 192, 193])
 def test_results_of_long_rows(shape, tied, k):
-    """Rows whose results are selected through block maxima (up to 192 results, 12,288 candidates and more): lists around whole blocks;
+    """Rows whose results are selected through block maxima (up to 192 results, from 8192 candidates and the square of the number of results on): lists around whole blocks;
     more than 512 blocks whose best scores are equal, where the selection goes back to the whole row; more than 262,144 candidates,
     whose block maxima no longer fit a thread's registers."""
     rng = np.random.default_rng(len(shape) + k + 3 * tied)
