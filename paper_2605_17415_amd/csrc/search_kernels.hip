@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
         const float g = __half2float(__ushort_as_half(store.gamma[slot]));
         float sc = s_l + g * acc;
         float margin = 0.f;
-        if (metric) {                  // ranking key of a raw metric (see launch_metric_finish)
+        if (metric) {                  // ranking key of a raw metric (metric_value turns the selected ones into values)
             const float xn = store.xnorm[slot];
             if constexpr (REDO) margin = fabsf(metric_scale(metric, xn, qn)) * redo_margin(a.slack, s_l, g);
             sc = metric_key(metric, sc, xn, qn);

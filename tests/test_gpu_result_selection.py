@@ -1,7 +1,7 @@
-"""Selection of the results of a streaming search (mode 1) from the block maxima that its scan leaves: lists that are empty,
-around whole blocks of 64 and long, so that a query has few blocks or many next to its results; 1 to 193 results (192 is the
-most the short cut takes, 24 / 25 the line between its two bounds); many equal scores; more probes than are staged in LDS.
-Against float64 scores of every candidate.  A score is coarse + gamma * (a float32 sum of d products), so it is within
+"""Selection of search results: of a streaming search from its scores, around lists that are empty, near whole blocks of 64 and long, or
+through the block maxima that the scan leaves for few, long rows; 1 to 193 results (192 is the most the workgroup kernel's short cut
+takes, 24 / 25 the line between its two bounds); many equal scores; more probes than are staged in LDS; many queries, from either
+scan; queries and scores that are no numbers.  Against float64 scores of every candidate.  A score is coarse + gamma * (a float32 sum of d products), so it is within
 gamma |z| |C| d 2^-24 < 1e-5 of float64 for the gamma <= 1.2, |C| <= 2 and d = 48 used here, plus the 2e-7 of the coarse term."""
 import numpy as np
 import pytest

@@ -1,6 +1,5 @@
-"""ivftq_search in its default mode across the call sizes where the streaming path changes strategy (selection in
-two steps up to 64 queries, one selection per query beyond; lists shared out over more workgroups the fewer
-queries there are), against the oracle on the same stored codes, and the same queries answered identically
+"""ivftq_search in its default mode across the call sizes where the streaming path changes strategy (lists shared out over
+more workgroups the fewer queries there are, results selected through block maxima where a call has few, long rows), against the oracle on the same stored codes, and the same queries answered identically
 (labels, scores to rounding) whatever call they arrive in.  (Calls large enough for the default mode to take the
 query-batched scan are in test_gpu_large_lists.py and the full-size tests.)"""
 import numpy as np
