@@ -1242,11 +1242,12 @@ __global__ __launch_bounds__(1024) void k_redo_select(RedoSelectArgs a) {
 // One workgroup per query: each wavefront takes every fourth candidate and computes <q, x> / (|q| |x|) from the raw
 // rows, then the workgroup orders by (score desc, label asc) and emits the k best, dropping repeated labels.  Bound by
 // the latency of gathering rows: a wavefront reads the labels of its next 64 candidates together and then four rows together
-// (T: coordinates of a lane); 4096 queries x 50 rows of 128: 66 us with one row at a time and a sort by one barrier a step, 48 now.
+// (T: coordinates of a lane); 4096 queries x 50 rows of 128: 63 us with one row at a time and a sort by one barrier a step, 40 now.
 // Up to 256 candidates are placed by counting the ones that go before (by the wavefronts that have one: by all four, the
 // reads of LDS alone made it 100 us), more are sorted.  4096 queries x 100 coordinates, sorted by one barrier a step, one row at
-// a time, against now: 50 candidates 62 and 45 us, 128 110 and 99, 200 202 and 181, 256 207 and 207, 300 (sorted) 391 and 257.  The
-// labels have to lie at multiples of 8: 4 bytes off, 200 candidates took 284 us, 256 315.
+// a time, against now: 50 candidates 63 and 40 us, 128 113 and 84, 200 210 and 158, 256 225 and 180, 300 (sorted) 391 and 257; one
+// query, 256 candidates 55 and 34 (62 with && and || in the counting loops).  The labels have to lie at multiples of 8: 4 bytes off, 200
+// candidates took 284 us, 256 315.
 template <int T>
 __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1318,9 +1319,9 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
         const int64_t lab = tid < a.r ? s_lab[tid] : INT64_MAX;
         // the same label again has the same score: all but the first are taken out
         const int look = 64 * wave < a.r ? a.r : 0;        // (a wavefront without a candidate places none)
-        bool again = false;
+        int again = 0;       // (no && and || around the reads of LDS: each is a branch and a wait of its own)
 #pragma unroll 8
-        for (int i = 0; i < look; ++i) again |= i < tid && s_lab[i] == lab;
+        for (int i = 0; i < look; ++i) again |= (int)(i < tid) & (int)(s_lab[i] == lab);
         __syncthreads();
         const bool counts = key != 0u && !again;
         if (tid < a.r && !counts) s_key[tid] = 0u;
@@ -1330,7 +1331,7 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
 #pragma unroll 8
         for (int i = 0; i < look; ++i) {
             const uint32_t ki = s_key[i];
-            place += ki > key || (ki == key && s_lab[i] < lab) ? 1 : 0;
+            place += (int)(ki > key) | ((int)(ki == key) & (int)(s_lab[i] < lab));
         }
         if (counts && place < a.k) {
             a.out_scores[q * a.k + place] = s_val[tid];
