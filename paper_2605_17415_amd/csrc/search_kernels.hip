@@ -86,7 +86,7 @@ __device__ __forceinline__ void cand_offsets_wave(const CandOffsetArgs& c, int64
 // Order-preserving key of a score; whatever is no number gets 0, which no score has: it is no cell and no result.
 __device__ __forceinline__ uint32_t order_key(float f) {
     const uint32_t u = __float_as_uint(f);
-    return f != f ? 0u : (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return f != f ? 0u : u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);      // (all bits of a negative one, the sign of another)
 }
 __device__ __forceinline__ float order_value(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key); }
 
@@ -364,7 +364,8 @@ __device__ __forceinline__ uint32_t kth_of_maxima(const uint32_t* maxima, int ta
 
 // COPIES: counters per digit in the histogram (a power of two; 8 pays for long rows, 1 for short ones, where
 // clearing and summing the copies costs more than the collisions they avoid).
-template <int MODE, int COPIES>
+// SHORT: with the short cut, whose LDS and registers calls of more winners do without.
+template <int MODE, int COPIES, bool SHORT>
 __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     constexpr int kHistCopies = COPIES;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -411,7 +412,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     // (few blocks for many winners: their maxima say little.  100 winners of 12,000 candidates, 200 blocks: 34 us a call through the
     // blocks, 30 from the scores)
     const bool by_block = n_blk >= 2 * take && m > kSelCand;
-    if (take > 0 && ((take <= kSelTake && m > k) || m <= kSelAll)) {
+    if (SHORT && take > 0 && ((take <= kSelTake && m > k) || m <= kSelAll)) {
         // (one base pointer and loads without a branch between them, so that all of a thread's are in flight together)
         const uint32_t* src = by_block ? a.blk_max + row * a.blk_stride : reinterpret_cast<const uint32_t*>(vals);
         const int parts = by_block ? n_blk : m;
@@ -1547,15 +1548,15 @@ hipError_t launch_select(int mode, const SelectArgs& a, hipStream_t st) {
     int kpad = 1;
     while (kpad < a.k) kpad <<= 1;
     const int copies = (m_bound == 0 || m_bound > 8192) ? 8 : 1;
-    const size_t lds = (256 * copies + 8 + 4) * 4 + (size_t)kpad * 8 + (size_t)kpad * 8 + (size_t)(kSelCand + 8 + kSelBlocks) * 8;
-    const unsigned wgs = (unsigned)a.rows;
-    if (copies == 8) {
-        if (mode == 0) hipLaunchKernelGGL((k_select<0, 8>), dim3(wgs), dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((k_select<1, 8>), dim3(wgs), dim3(256), lds, st, a);
-    } else {
-        if (mode == 0) hipLaunchKernelGGL((k_select<0, 1>), dim3(wgs), dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((k_select<1, 1>), dim3(wgs), dim3(256), lds, st, a);
-    }
+    // Long rows of which more are wanted than the short cut takes: its LDS and registers cost a workgroup of five on a compute unit.  Selection
+    // with them and without, us: 753 of 345,657 for 1150 queries 2294 and 1757, 1000 of 28,000 222 and 150.  (Rows of up to 8192 keep the
+    // form for all: those of at most 128 are ordered whole.)
+    const bool plain = copies == 8 && a.k > kSelTake;
+    const size_t lds = (256 * copies + 8 + 4) * 4 + (size_t)kpad * 16 + (plain ? 0 : (size_t)(kSelCand + 8 + kSelBlocks) * 8);
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(256), lds, st, a); };
+    if (plain) mode == 0 ? go(k_select<0, 8, false>) : go(k_select<1, 8, false>);
+    else if (copies == 8) mode == 0 ? go(k_select<0, 8, true>) : go(k_select<1, 8, true>);
+    else mode == 0 ? go(k_select<0, 1, true>) : go(k_select<1, 1, true>);
     return hipGetLastError();
 }
 
