@@ -1373,9 +1373,9 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     // index the call touches, but it is a chain of about twelve kernels with a fixed cost of its own.
     // Batched when the streamed bytes exceed kBatchedGain times the touched bytes plus kBatchedFixedBytes.  The
     // constants are those of an earlier batched path (crossovers with nprobe 32 / 32 / 64 at 1M x 128, 10M x 96,
-    // 10M x 200 then: about 200, 380 and 170 queries).  On clustered rows the present paths cross at about 130, 220 and
-    // 50 queries, so that calls in between take up to 1.5 times as long as they could (160 queries at 10M x 200: 613 us
-    // streamed, 418 batched; 320 at 10M x 96 326 and 260; a raw metric's length, 4 bytes a vector, is not counted either); on rows
+    // 10M x 200 then: about 200, 380 and 170 queries).  On clustered rows the present paths cross at about 150, 255 and
+    // 65 queries, so that calls in between take up to 1.5 times as long as they could (160 queries at 10M x 200: 578 us
+    // streamed, 417 batched; 320 at 10M x 96 326 and 260; a raw metric's length, 4 bytes a vector, is not counted either); on rows
     // without clusters the line lies too low instead (1M x 128, 64 probes, k = 100: 100 queries 190 us batched, 129 streamed; even
     // at 200).  Mode 2 asks for the batched path whatever the size of the call.
     constexpr double kBatchedGain = 2.3, kBatchedFixedBytes = 0.25e9;
