@@ -63,6 +63,7 @@ def test_probe_selection_with_exact_ties(L, nprobe):
     (4096, 8, 2049, 2048), (4096, 32, 2049, 2048), (4096, 33, 2049, 2048), (4096, 64, 2049, 2048), (8000, 64, 2050, 4000), (2500, 50, 2051, 1250),
     (1200, 10, 1025, 600), (1200, 48, 1027, 600), (100, 10, 1025, 50), (2048, 20, 1025, 1024), (2049, 20, 2048, 1025),
     (4096, 10, 2049, 5), (4096, 50, 2049, 5), (1000, 64, 1030, 3),                         # (hundreds of equal scores at the cut)
+    (8193, 193, 70, 4000), (8193, 300, 70, 9), (8192, 193, 70, 9),          # (the radix search alone: more than 192 of more than 8192)
     (127, 20, 300, 64), (128, 64, 300, 7), (129, 64, 300, 7), (129, 100, 300, 65), (300, 8, 300, 3), (512, 200, 300, 256), (513, 30, 300, 5)])
 def test_probes_of_every_kernel_with_exact_ties(L, nprobe, nq, different):
     """The one-wavefront kernel, which takes over above 1024 rows of up to 2048 cells and above 2048 longer ones, with its short cuts for up to
