@@ -1406,17 +1406,17 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     TileShape shape{};
     int64_t near_tiles = 0, late_tiles = 0;
     if (batched) {
-        shape = tile_shape(ix->ntotal, ix->nlist, qc * nprobe);
+        shape = tile_shape(ix->ntotal, ix->nlist, qc * nprobe, batch_tile(ix->d, bits));
         const ListRoom lists = list_room(ix->h_size.data(), ix->nlist);
-        near_tiles = tile_room(lists, held, held * nprobe, shape.tq_near);
-        late_tiles = tile_room(lists, held, held * nprobe, shape.tq);
+        near_tiles = tile_room(lists, held, held * nprobe, kBatchTileNear);
+        late_tiles = tile_room(lists, held, held * nprobe, kBatchTile);
         HIP_TRY(ix->w_zh.ensure((size_t)held * ix->dp * sizeof(uint16_t)));
         HIP_TRY(ix->w_zl.ensure((size_t)held * ix->dp * sizeof(uint16_t)));
         HIP_TRY(ix->w_first.ensure((size_t)held * sizeof(int32_t)));
         HIP_TRY(ix->w_fscores.ensure((size_t)held * k * sizeof(float)));
         HIP_TRY(ix->w_fids.ensure((size_t)held * k * sizeof(int64_t)));
         HIP_TRY(ix->w_pairs.ensure((size_t)held * nprobe * sizeof(int32_t)));
-        HIP_TRY(ix->w_count.ensure((size_t)(4 * buckets + 8) * sizeof(uint32_t)));
+        HIP_TRY(ix->w_count.ensure((size_t)(4 * buckets + kPairTotals) * sizeof(uint32_t)));
         // (at least what ivftq_reconstruct keeps there, so that a call of it moves nothing that a recorded search uses)
         HIP_TRY(ix->w_tilebkt.ensure((size_t)std::max<int64_t>(near_tiles + late_tiles, buckets + 1) * sizeof(int32_t)));
         HIP_TRY(ix->w_cscore.ensure((size_t)held * cap * sizeof(float)));
@@ -1436,7 +1436,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         int32_t* redo_cnt = batched ? ix->w_gate.as<int32_t>() + 1 + qc : nullptr;
         if (batched) {
             co.first = first; co.cand_cnt = ix->w_ccnt.as<int32_t>(); co.gate = ix->w_gate.as<int32_t>(); co.redo_cnt = redo_cnt;
-            co.bucket_cnt = ix->w_count.as<uint32_t>(); co.buckets = buckets + 8;
+            co.bucket_cnt = ix->w_count.as<uint32_t>(); co.buckets = buckets + kPairTotals;
         }
         RotatedQueries rq{};
         rq.z = ix->w_z.as<float>();
@@ -1501,7 +1501,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         ix->last_batched_queries = cnt;
         PairTable pt{};
         pt.count = ix->w_count.as<uint32_t>(); pt.totals = reinterpret_cast<int32_t*>(pt.count + buckets);
-        pt.cursor = pt.count + buckets + 8; pt.pair_off = reinterpret_cast<int32_t*>(pt.cursor + buckets); pt.tile_off = pt.pair_off + buckets;
+        pt.cursor = pt.count + buckets + kPairTotals; pt.pair_off = reinterpret_cast<int32_t*>(pt.cursor + buckets); pt.tile_off = pt.pair_off + buckets;
         pt.tile_near = ix->w_tilebkt.as<int32_t>(); pt.tile_late = pt.tile_near + near_tiles; pt.pairs = ix->w_pairs.as<int32_t>();
         HIP_TRY(timed(ix, st, P_PAIR_GROUP, [&] {
             return launch_pair_grouping(ix->w_probe.as<int32_t>(), first, cnt, nprobe, ix->nlist, ix->d_size.as<int32_t>(), shape, pt, st); }));
@@ -1526,13 +1526,6 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         // 3. the other lists against the thresholds
         ba.dense = 0; ba.part_len = shape.part;
         ba.thresh = ix->w_fscores.as<float>() + (k - 1); ba.thresh_stride = k;
-        {
-            // (rows without clusters append up to about half of what a query has room for, spread over its lists: 150 of 512 for 10 results,
-            // 240 for 30, 840 to 960 of 1600 for 100)
-            const int64_t pairs = cnt * nprobe, lists = std::min<int64_t>(ix->nlist, pairs);
-            ba.dequantised = (lists + pairs / shape.tq) * std::max<int64_t>(1, ix->ntotal / ix->nlist) * ix->d;
-            ba.tile_candidates = std::min<int64_t>(shape.tq, (pairs + lists - 1) / lists) * (cap / 2) / nprobe;
-        }
         HIP_TRY(timed(ix, st, P_BATCH_SCAN, [&] { return launch_batch_scan(ba, ix->d, bits, st); }));
         // 4. merge; a query whose candidate list overflowed is redone by the exact streaming scan
         MergeArgs ma{};

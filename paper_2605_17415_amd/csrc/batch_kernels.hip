@@ -345,11 +345,6 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
 
 }  // namespace
 
-// Panel width of the batched scan for rows of d coordinates: the padded width of the rotated queries (a multiple
-// of 32), at least 64, except that 193 ... 208 coordinates take 13 blocks of 16 rather than 14 (d = 200: a
-// fourteenth less to de-quantise and multiply).
-static int batch_dp(int d) { return (d > 192 && d <= 208) ? 208 : d <= 64 ? 64 : rot_dp(d); }
-
 // The split float16 operands of the dense pass carry a level to 2^-23.  Over few terms, or with four levels that recur all
 // the time, that rounding does not average out: root mean square error of the returned scores against float64, next to
 // the streaming scan's, 1.03 at d = 10 and 1.02 at d = 32 with 2 bits, 1.02 at d = 8 with 4 and at d = 12 with 3, but 0.93

@@ -360,14 +360,28 @@ hipError_t launch_cascade_rescore(const CascadeArgs& a, int64_t nq, hipStream_t 
 
 // Whether the batched scan covers this (d, b); otherwise the streaming scan is used.
 bool batch_covers(int d, int b);
+// Panel width of the batched scan for rows of d coordinates: the padded width of the rotated queries (a multiple
+// of 32), at least 64, except that 193 ... 208 coordinates take 13 blocks of 16 rather than 14 (d = 200: a
+// fourteenth less to de-quantise and multiply).
+constexpr int batch_dp(int d) { return (d > 192 && d <= 208) ? 208 : d <= 64 ? 64 : (d + 31) / 32 * 32; }
+// Row tiles of 32 queries that a wavefront of the threshold pass holds in registers: up to four, as many as fit beside their accumulators and
+// a slab's words.
+constexpr int batch_query_tiles(int dp, int b) {
+    const int kb = dp / 16, words = kb * (b == 2 || b == 4 ? 1 : 2);
+    return 4 * (4 * kb + 16) + 2 * words <= 180 ? 4 : 3 * 4 * kb + words <= 180 ? 3 : 2;
+}
+constexpr int batch_tile(int d, int b) { return 32 * batch_query_tiles(batch_dp(d), b); }
 
 // The (query, probe) pairs bucketed by list: bucket l holds the pairs (q, p < first[q]) of list l (the dense pass),
 // bucket L + l the pairs (q, p >= first[q]) (the threshold pass).  pairs[pair_off[b] ...] holds the count[b] flat pair
 // numbers q*np + p of bucket b.  Its workgroup tiles, every tq_near or tq of its queries times the list_parts of its
 // list, are tile_off[b] ... of its pass's array (tile_near or tile_late), whose entries name the bucket.
+// Updates of one counter from all over the chip follow each other at about 14 ns, so the tiles of a pass are dealt out to kTileQueues
+// queues, tile t to queue t % kTileQueues, each served by the workgroups of its number (on one of the chip's eight parts).
+constexpr int kTileQueues = 16, kPairTotals = 32 + 2 * kTileQueues * 32;
 struct PairTable {
-    // cleared with the candidate offsets: [2L] pairs of a bucket, then 8 words totals (pairs, tiles of the dense pass, of
-    // the threshold pass, next tile of either pass)
+    // cleared with the candidate offsets: [2L] pairs of a bucket, then kPairTotals words: totals (pairs, tiles of the dense pass, of
+    // the threshold pass) and from word 32 on the next tiles of either pass, kTileQueues counters a cache line apart
     uint32_t* count; int32_t* totals;
     uint32_t* cursor; int32_t* pair_off; int32_t* tile_off;      // [2L] each; cursor is scratch
     int32_t* tile_near; int32_t* tile_late; int32_t* pairs;
@@ -385,7 +399,6 @@ struct BatchScanArgs {
     // threshold mode: cand_score = upper bound of the score (see acc0), cand_slot = slot | probe rank << kCandProbeShift
     float* cand_score; int64_t* cand_slot; int32_t* cand_cnt; int cap;
     float acc0;                          // 2^20 * kappa, added to the threshold pass's accumulators
-    int64_t dequantised, tile_candidates;     // threshold mode: coordinates that the pass looks up, and what rows without clusters would append in a tile
     // dense mode (the nearest lists): every score goes to scores[q*m_stride + cand_off[q][p] + v]
     int dense; float* scores; int64_t m_stride; const int32_t* cand_off;
     int metric; const float* qnorm;      // scores are ranking keys of a raw metric (metric_key)

@@ -38,25 +38,24 @@ inline SearchRows search_rows(bool batched, int64_t nq, int64_t row, int64_t pre
     return r;
 }
 
-// Queries per workgroup tile of the threshold pass, and of the dense pass, whose panel holds both parts of the queries
-// and whose lists have few of them (3 at 10M x 96, 11 at 10M x 200): with 64 the panel leaves room for as many
-// workgroups in a compute unit's LDS as its registers allow.
-constexpr int kBatchTile = 128, kBatchTileNear = 64;
+// Queries per workgroup tile: of the dense pass, and of the threshold pass the fewest that any form of it takes (which the room is
+// counted by: batch_tile of kernels.h says how many a form takes).
+constexpr int kBatchTile = 64, kBatchTileNear = 32;
 // Lists of more than part_len vectors are cut into nearly equal parts of at most part_len, each a tile of its own.
-constexpr int kPartMin = 512, kPartMax = 4096;
+constexpr int kPartMin = 256, kPartMax = 4096;
 struct TileShape { int tq_near, tq, part_near, part; };
 constexpr int list_parts(int size, int part_len) { return size > part_len ? (size + part_len - 1) / part_len : 1; }
 
 // Tiles of the batched passes: enough of them that the last ones to finish matter little (kTilesWanted over the
 // chip's 512 to 1024 resident workgroups).
-constexpr int64_t kTilesWanted = 8192;
+constexpr int64_t kTilesWanted = 32768;
 inline int part_length(int64_t typical_list, int64_t tiles) {
     const int64_t cuts = std::max<int64_t>(1, kTilesWanted / std::max<int64_t>(1, tiles));
     return (int)std::min<int64_t>(kPartMax, std::max<int64_t>(kPartMin, (typical_list / cuts + 63) / 64 * 64));
 }
-inline TileShape tile_shape(int64_t ntotal, int nlist, int64_t pairs) {
+inline TileShape tile_shape(int64_t ntotal, int nlist, int64_t pairs, int tq = kBatchTile) {
     const int64_t typical = std::max<int64_t>(1, ntotal / nlist), lists = std::min<int64_t>(nlist, pairs);
-    return {kBatchTileNear, kBatchTile, part_length(typical, lists), part_length(typical, lists + pairs / kBatchTile)};
+    return {kBatchTileNear, tq, part_length(typical, lists), part_length(typical, lists + pairs / tq)};
 }
 
 // Entries that hold the tiles of a pass whose tiles take tq queries each, whatever the part length.  A list that meets c
