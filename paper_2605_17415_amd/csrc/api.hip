@@ -1422,7 +1422,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         HIP_TRY(ix->w_cscore.ensure((size_t)held * cap * sizeof(float)));
         HIP_TRY(ix->w_cslot.ensure((size_t)held * cap * sizeof(int64_t)));
         HIP_TRY(ix->w_ccnt.ensure((size_t)held * sizeof(int32_t)));
-        HIP_TRY(ix->w_gate.ensure((size_t)(2 * held + 1) * sizeof(int32_t)));
+        HIP_TRY(ix->w_gate.ensure((size_t)(3 * held + 1) * sizeof(int32_t)));
     }
     // block maxima of the streaming scan, a 64th of its scores (rows.floats holds those of a pass) and up to one more per probe
     HIP_TRY(ix->w_blk.ensure((size_t)(rows.floats / 64 + held * (nprobe + 1)) * sizeof(uint32_t)));
@@ -1435,7 +1435,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         int32_t* first = batched ? ix->w_first.as<int32_t>() : nullptr;
         int32_t* redo_cnt = batched ? ix->w_gate.as<int32_t>() + 1 + qc : nullptr;
         if (batched) {
-            co.first = first; co.cand_cnt = ix->w_ccnt.as<int32_t>(); co.gate = ix->w_gate.as<int32_t>(); co.redo_cnt = redo_cnt;
+            co.first = first; co.cand_cnt = ix->w_ccnt.as<int32_t>(); co.gate = ix->w_gate.as<int32_t>(); co.redo_cnt = redo_cnt; co.redo_done = redo_cnt + qc;
             co.bucket_cnt = ix->w_count.as<uint32_t>(); co.buckets = buckets + kPairTotals;
         }
         RotatedQueries rq{};
@@ -1542,18 +1542,9 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         // by at most 2 * 256 * 2^-24 (two float32 sums of d <= 256 terms) + 2^-20 (split products) of |z||C|, times the
         // norm (see redo_margin); kappa / 16 is 2^-14 |z||C|.
         la.gate = ix->w_gate.as<int32_t>(); la.gate_rows = (int)gate_rows; la.m_stride = 2 * m_stride;
-        la.thresh = ba.thresh; la.thresh_stride = k; la.slack = kappa / 16.f; la.redo_cnt = redo_cnt;
-        RedoSelectArgs ra{};
-        ra.vals = la.scores; ra.stride = la.m_stride; ra.k = k; ra.gate = la.gate; ra.gate_rows = la.gate_rows;
-        ra.redo_cnt = redo_cnt; ra.cand_off = la.cand_off; ra.probe = la.probe; ra.np = nprobe;
-        ra.list_off = ix->d_off.as<int64_t>(); ra.ids = labels;
-        ra.out_vals = sa.out_vals; ra.out_i64 = sa.out_i64;
-        ra.metric = metric; ra.qnorm = ma.qnorm;
-        for (int64_t g0 = 0; g0 < cnt; g0 += gate_rows) {
-            la.gate_begin = ra.gate_begin = (int)g0;
-            HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, 0, 1, st); }));
-            HIP_TRY(timed(ix, st, P_SELECT_TOPK, [&] { return launch_redo_select(ra, st); }));
-        }
+        la.thresh = ba.thresh; la.thresh_stride = k; la.slack = kappa / 16.f; la.redo_cnt = redo_cnt; la.redo_done = redo_cnt + qc;
+        la.k = k; la.ids = labels; la.out_vals = sa.out_vals; la.out_i64 = sa.out_i64;
+        HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, 0, 1, st); }));
     }
     return IVFTQ_OK;
 }

@@ -244,12 +244,12 @@ hipError_t launch_inertia(const double* gain, int L, int64_t n, double* out, hip
 // cand_off[q*(np+1) + p] = sum_{p'<p} list_size[probe[q][p']]
 // first (may be null): first[q] = shortest probe prefix (>= 1 cell) holding at least
 // max(k, 2*k*T/cap) vectors, T the query's candidate total; np if there is none.  With `first`, cand_cnt[q],
-// gate[0], redo_cnt[q] and bucket_cnt[0 .. buckets) (each may be null) are set to zero: the counters the batched
+// gate[0], redo_cnt[q], redo_done[q] and bucket_cnt[0 .. buckets) (each may be null) are set to zero: the counters the batched
 // scan, its merge, the exact redo and the pair grouping add to.
 struct CandOffsetArgs {
     const int32_t* list_size; int32_t* cand_off;
     int k; int cap; int32_t* first;
-    int32_t* cand_cnt; int32_t* gate; int32_t* redo_cnt;
+    int32_t* cand_cnt; int32_t* gate; int32_t* redo_cnt; int32_t* redo_done;
     uint32_t* bucket_cnt; int buckets;
 };
 constexpr int kSelTake = 192;                   // most winners that the workgroup selection's short cut, which alone reads block maxima, is for
@@ -268,29 +268,20 @@ struct ListScanArgs {
     // blk_max[q*blk_stride + block_index(cand_off[q][p], p) + b] = order-preserving key of the best score of block b (64
     // vectors) of probe p (null: not wanted)
     uint32_t* blk_max; int64_t blk_stride;
-    // Exact redo (gate not null): instead of all queries the entries [gate_begin, gate_begin + gate_rows) of the
-    // gate[0] queries listed in gate[1..] are scanned.  Entry g's scores that reach thresh[q*thresh_stride], less the
-    // rounding between the arithmetic of the threshold and this one, go, redo_cnt[q] of them in any order, to the
-    // first half of score row g - gate_begin, their columns (cand_off[q][p] + i) to its second half; half a row has to
-    // hold every candidate.
-    const int32_t* gate; int gate_begin, gate_rows;
-    const float* thresh; int thresh_stride; float slack; int32_t* redo_cnt;      // slack: the rounding of a sum, per unit of the stored norm
+    // Exact redo (gate not null): instead of all queries the gate[0] listed in gate[1..] are scanned.  A query's scores that reach
+    // thresh[q*thresh_stride], less the rounding between the arithmetic of the threshold and this one, go, redo_cnt[q] of them in any order, to the
+    // first half of one of gate_rows score rows, their columns (cand_off[q][p] + i) to its second half; half a row has to
+    // hold every candidate.  redo_done[q] counts the workgroups that have finished their share; the last one writes the k best, by (score
+    // desc, label asc), to the query's result row, as values of the metric.
+    const int32_t* gate; int gate_rows;
+    const float* thresh; int thresh_stride; float slack; int32_t* redo_cnt; int32_t* redo_done;      // slack: the rounding of a sum, per unit of the stored norm
+    int k; const int64_t* ids;
+    float* out_vals; int64_t* out_i64;
 };
-constexpr int kRedoWorkgroups = 2048;   // shared out over the queries a redo launch finds
+constexpr int kRedoWorkgroups = 512, kRedoThreads = 1024;   // shared out over the queries a redo launch finds
 // blocks_per_query: workgroups per query (0 = one per probe), each walking its share of the probes; slices:
 // workgroups that share every list.  (Neither matters for a redo.)
 hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int blocks_per_query, int slices, hipStream_t st);
-// The k best of every query of a redo window, by (score desc, label asc), written to its own result row; vals,
-// stride and the window as in the scan.
-struct RedoSelectArgs {
-    const float* vals; int64_t stride; int k;
-    const int32_t* gate; int gate_begin, gate_rows; const int32_t* redo_cnt;
-    const int32_t* cand_off; const int32_t* probe; int np;
-    const int64_t* list_off; const int64_t* ids;
-    float* out_vals; int64_t* out_i64;
-    int metric; const float* qnorm;               // results are written as values of the metric
-};
-hipError_t launch_redo_select(const RedoSelectArgs& a, hipStream_t st);
 // metric 0: the score is the estimate s^ of <q~, x~> itself.  Raw metrics (the store keeps |x|, qnorm[q] = |q|):
 // the scan writes a key that ranks like the metric and whatever writes a call's results turns the selected keys into values:
 //   metric 1 (inner product): key = |x| s^,                 value = |q| key            (descending)

@@ -43,7 +43,7 @@ __device__ __forceinline__ int64_t dense_prefix(const CandOffsetArgs& c, int32_t
 __device__ __forceinline__ void put_first(const CandOffsetArgs& c, int64_t q, int p1) {
     c.first[q] = p1;
     if (c.cand_cnt) c.cand_cnt[q] = 0;
-    if (c.redo_cnt) c.redo_cnt[q] = 0;
+    if (c.redo_cnt) c.redo_cnt[q] = c.redo_done[q] = 0;
     if (c.gate && q == 0) c.gate[0] = 0;
 }
 
@@ -90,6 +90,144 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 }
 __device__ __forceinline__ float order_value(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key); }
 
+// ---- the k best of a query redone exactly ---------------------------------------------------------
+//
+// By one workgroup, from redo_cnt[q] scores in arbitrary order at `vals` and the candidate columns
+// they belong to.  An entry's composite (order-preserving key of the score, then ~column) makes all entries
+// distinct: the k with the largest composites are the k best, ties going to the smaller column, whatever the
+// order they were appended in.  A radix search narrows the entries down, a byte at a time, until at most
+// max(k, kRedoFew) reach what is known of the k-th largest composite; those are gathered and sorted in LDS.  Bound by
+// the latency of its passes and of the sort's barriers; on the benchmark's searches one to three queries of 10,000
+// come here, with 400 to 3000 entries each.  Sorting up to 2048 entries outright, and all eight passes beyond, with the
+// digit looked for by one thread, took 50 us at 10M x 96 (k = 10); 13 us with the radix search.
+constexpr int kRedoSort = 2048, kRedoFew = 128;
+static_assert(kMaxK <= kRedoSort, "the k winners are sorted in LDS");
+constexpr size_t kRedoLds = kRedoSort * 16 + 256 * 4 + 16;
+
+template <int NT>
+__device__ __forceinline__ void redo_select(const ListScanArgs& a, int64_t q, const float* vals, unsigned char* lds) {
+    uint64_t* s_comp = reinterpret_cast<uint64_t*>(lds);              // [kRedoSort]
+    int64_t* s_lab = reinterpret_cast<int64_t*>(s_comp + kRedoSort);  // [kRedoSort]
+    uint32_t* hist = reinterpret_cast<uint32_t*>(s_lab + kRedoSort);  // [256]
+    uint32_t* ctrl = hist + 256;                                      // [3]
+    const int tid = threadIdx.x;
+    const int32_t* off = a.cand_off + q * (a.np + 1);
+    const int n = __hip_atomic_load(&a.redo_cnt[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const float* cols = vals + a.m_stride / 2;
+    auto comp_of = [&](int i) -> uint64_t {
+        return ((uint64_t)order_key(vals[i]) << 32) | (uint32_t)~__float_as_uint(cols[i]);
+    };
+    const int take = n < a.k ? n : a.k;
+    uint64_t last = 0;                          // every entry of at least this composite is gathered
+    const int few = take > kRedoFew ? take : kRedoFew;
+    if (n > few) {
+        uint64_t mask = 0;
+        uint32_t need = (uint32_t)take;             // winners among the entries that share the bytes found so far
+        for (int shift = 56; shift >= 0; shift -= 8) {
+            __syncthreads();
+            if (tid < 256) hist[tid] = 0;
+            __syncthreads();
+            for (int i = tid; i < n; i += NT) {
+                const uint64_t c = comp_of(i);
+                if ((c & mask) == last) atomicAdd(&hist[(c >> shift) & 255u], 1u);
+            }
+            __syncthreads();
+            if (tid < 64) {                         // the digit where the running count, from above, first reaches `need`
+                uint32_t h[4];                      // lane l owns digits 4l .. 4l+3
+#pragma unroll
+                for (int e = 0; e < 4; ++e) h[e] = hist[4 * tid + e];
+                const uint32_t own = h[0] + h[1] + h[2] + h[3];
+                uint32_t above = own;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t t = __shfl_down(above, o);
+                    if (tid + o < 64) above += t;
+                }
+                above -= own;
+#pragma unroll
+                for (int e = 3; e >= 0; --e) {
+                    if (above < need && above + h[e] >= need) {         // true for one digit only
+                        ctrl[0] = (uint32_t)(4 * tid + e);
+                        ctrl[1] = need - above;
+                        ctrl[2] = h[e];
+                    }
+                    above += h[e];
+                }
+            }
+            __syncthreads();
+            last |= (uint64_t)ctrl[0] << shift;
+            mask |= (uint64_t)255 << shift;
+            need = ctrl[1];
+            // (all that reach `last`: the winners beyond its bytes, and every entry that shares them)
+            if ((uint32_t)take - need + ctrl[2] <= (uint32_t)few) break;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) ctrl[0] = 0;
+    __syncthreads();
+    for (int i = tid; i < n; i += NT) {
+        const uint64_t c = comp_of(i);
+        if (c >= last) {
+            const uint32_t at = atomicAdd(&ctrl[0], 1u);
+            if (at < (uint32_t)kRedoSort) s_comp[at] = c;
+        }
+    }
+    __syncthreads();
+    const int got = min((int)ctrl[0], kRedoSort);
+    int size = 1;
+    while (size < got) size <<= 1;
+    for (int i = got + tid; i < size; i += NT) s_comp[i] = 0;
+    __syncthreads();
+    for (int sz = 2; sz <= size; sz <<= 1)
+        for (int stride = sz >> 1; stride > 0; stride >>= 1) {
+            for (int i = tid; i < size / 2; i += NT) {
+                const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+                const uint64_t c0 = s_comp[lo], c1 = s_comp[hi];
+                if ((c0 >= c1) != ((lo & sz) == 0)) { s_comp[lo] = c1; s_comp[hi] = c0; }
+            }
+            __syncthreads();
+        }
+    // labels of the winners, then equal scores in label order
+    int kpad = 1;
+    while (kpad < take) kpad <<= 1;
+    for (int i = tid; i < kpad; i += NT) {
+        int64_t lab = INT64_MAX;
+        if (i < take) {
+            const int32_t col = (int32_t)~(uint32_t)s_comp[i];
+            int lo = 0, hi = a.np;              // largest p with off[p] <= col
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (off[mid] <= col) lo = mid; else hi = mid;
+            }
+            const int64_t slot = a.store.list_off[a.probe[q * a.np + lo]] + (col - off[lo]);
+            lab = a.ids ? a.ids[slot] : slot;
+        } else {
+            s_comp[i] = 0;
+        }
+        s_lab[i] = lab;
+    }
+    __syncthreads();
+    for (int sz = 2; sz <= kpad; sz <<= 1)
+        for (int stride = sz >> 1; stride > 0; stride >>= 1) {
+            for (int i = tid; i < kpad / 2; i += NT) {
+                const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+                const uint32_t k0 = (uint32_t)(s_comp[lo] >> 32), k1 = (uint32_t)(s_comp[hi] >> 32);
+                const int64_t l0 = s_lab[lo], l1 = s_lab[hi];
+                if ((k0 > k1 || (k0 == k1 && l0 <= l1)) != ((lo & sz) == 0)) {
+                    const uint64_t c = s_comp[lo]; s_comp[lo] = s_comp[hi]; s_comp[hi] = c;
+                    s_lab[lo] = l1; s_lab[hi] = l0;
+                }
+            }
+            __syncthreads();
+        }
+    for (int i = tid; i < a.k; i += NT) {
+        const uint32_t key = i < take ? (uint32_t)(s_comp[i] >> 32) : 0u;
+        const float v = i < take ? order_value(key) : -__builtin_inff();
+        a.out_vals[q * a.k + i] = a.metric ? metric_value(a.metric, v, a.qnorm[q]) : v;
+        a.out_i64[q * a.k + i] = i < take ? s_lab[i] : -1;
+    }
+}
+
 // ---- list scan: a row of workgroups per query walks its probed lists ---------------------------
 //
 // The query's rotated coordinates and the 2^b centroid values are combined once per workgroup
@@ -102,7 +240,11 @@ __device__ __forceinline__ float order_value(uint32_t key) { return __uint_as_fl
 // REDO: only the queries that overflowed their candidate list (launch_list_scan), and only scores that reach the
 // query's threshold are kept, with their columns, in arbitrary order.  A launch mostly finds no such query or a
 // few, so all of its workgroups are shared out over those it finds: two queries of 64 lists on eight workgroups
-// each took 0.66 ms at 10M x 200, each workgroup walking eight lists alone; spread over the chip 0.02 ms.
+// each took 0.66 ms at 10M x 200, each workgroup walking eight lists alone; spread over the chip 0.02 ms.  The last workgroup to
+// finish its share of a query selects its results.  When there are more such queries than rows, every workgroup takes queries by itself, one
+// after the other in a row of its own.  (Full-length rows are few, 1500 for 10,000 queries x 64 probes of 10M x 200; with a scan and a
+// selection for every turn of them, most of them empty, the redo of a query or none took 64 us there, and 56 for 32 probes of 10M x 96;
+// one launch takes 28, or 4 when it finds nothing.)
 //
 // redo_margin: how far a score s_l + g * sum can lie below its evaluation by the dense pass, from which the threshold
 // comes.  slack bounds the difference of the two sums; it counts for every unit of the norm, which a caller's own
@@ -114,8 +256,8 @@ __device__ __forceinline__ float redo_margin(float slack, float s_l, float g) { 
 // time, and with lanes past a list's end kept for the exchange, lists of few vectors took up to 15 % longer (3008 queries x 44 lists of 4
 // 91 us instead of 79, 5461 x 54 of 17 252 instead of 232).
 template <int B, bool DIRECT, bool REDO, bool BLK>
-__global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
-    constexpr int K = 1 << B;
+__global__ __launch_bounds__(REDO ? kRedoThreads : 256) void k_list_scan(ListScanArgs a) {
+    constexpr int K = 1 << B, NT = REDO ? kRedoThreads : 256;
     extern __shared__ float lut[];     // [d][K], or z[d] followed by C[K] when DIRECT
     const float* __restrict__ z = a.z;
     const float* __restrict__ cb = a.cb;
@@ -128,13 +270,13 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
     // rounds slice, slice + slices, ... of 256 vectors
     int64_t row = blockIdx.y, row_step = 1, row_end = row + 1;
     int p_first = (int)blockIdx.x, p_step = (int)gridDim.x, slice = (int)blockIdx.z, slices = (int)gridDim.z;
+    int64_t buffer = row;              // score row
     if constexpr (REDO) {
-        int n_redo = a.gate[0] - a.gate_begin;
-        if (n_redo > a.gate_rows) n_redo = a.gate_rows;
+        const int n_redo = a.gate[0], rows = min(a.gate_rows, (int)gridDim.x);
         if (n_redo <= 0) return;
-        const int per = max(1, (int)gridDim.x / n_redo);       // workgroups per query
+        const int per = n_redo <= rows ? max(1, (int)gridDim.x / n_redo) : 1;       // workgroups per query
         const int part = (int)blockIdx.x % per;
-        row = (int)blockIdx.x / per; row_step = (int)gridDim.x / per; row_end = n_redo;
+        row = buffer = (int)blockIdx.x / per; row_step = min((int)gridDim.x / per, rows); row_end = n_redo;
         if (row >= row_step) return;
         p_step = min(per, np);
         slices = per / p_step;
@@ -143,7 +285,8 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
         if (slice >= slices) return;
     }
     for (; row < row_end; row += row_step) {
-    const int64_t q = REDO ? a.gate[1 + a.gate_begin + row] : row;
+    if constexpr (!REDO) buffer = row;
+    const int64_t q = REDO ? a.gate[1 + row] : row;
     if (p_first >= np) continue;
     const float qn = metric ? a.qnorm[q] : 1.f;
     float reach = 0.f;
@@ -153,10 +296,10 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
     }
 
     if constexpr (DIRECT) {
-        for (int e = threadIdx.x; e < d; e += 256) lut[e] = z[q * z_pitch + e];
-        for (int e = threadIdx.x; e < K; e += 256) lut[d + e] = cb[e];
+        for (int e = threadIdx.x; e < d; e += NT) lut[e] = z[q * z_pitch + e];
+        for (int e = threadIdx.x; e < K; e += NT) lut[d + e] = cb[e];
     } else {
-        for (int e = threadIdx.x; e < d * K; e += 256) lut[e] = z[q * z_pitch + (e >> B)] * cb[e & (K - 1)];
+        for (int e = threadIdx.x; e < d * K; e += NT) lut[e] = z[q * z_pitch + (e >> B)] * cb[e & (K - 1)];
     }
     __syncthreads();
     auto term = [&](int j, uint32_t code) -> float {
@@ -171,7 +314,7 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
     const float s_l = coarse[q * np + p];
     const int64_t base_slot = store.list_off[cell];
     const int32_t col0 = cand_off[q * (np + 1) + p];
-    float* out = a.scores + row * a.m_stride + (REDO ? 0 : col0);
+    float* out = a.scores + buffer * a.m_stride + (REDO ? 0 : col0);
     const int lane = (int)(threadIdx.x & 63);
     uint32_t* blk = nullptr;
     if constexpr (BLK) {
@@ -182,8 +325,8 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
         if (slice == 0 && b < own) blk[b] = 0u;
     }
 
-    // a list is dealt out in rounds of 256 vectors to the workgroups that share it
-    for (int v0 = 256 * slice + (int)(threadIdx.x & ~63u); v0 < n_l; v0 += 256 * slices) {
+    // a list is dealt out in rounds of a vector per thread to the workgroups that share it
+    for (int v0 = NT * slice + (int)(threadIdx.x & ~63u); v0 < n_l; v0 += NT * slices) {
         const int v = v0 + lane;
         const bool in_list = v < n_l;
         if (!REDO && !BLK && !in_list) break;
@@ -295,8 +438,8 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
                 if (lane == leader) at = atomicAdd(&a.redo_cnt[q], (int)__popcll(in));
                 at = __shfl(at, leader) + (int)__popcll(in & (((uint64_t)1 << lane) - 1));
                 if (keep) {
-                    out[at] = sc;
-                    out[a.m_stride / 2 + at] = __int_as_float(col0 + v);
+                    __hip_atomic_store(out + at, sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(out + a.m_stride / 2 + at, __int_as_float(col0 + v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
         } else {
@@ -309,6 +452,22 @@ __global__ __launch_bounds__(256) void k_list_scan(ListScanArgs a) {
             }
         }
     }
+    }
+    if constexpr (REDO) {
+        // What every workgroup kept has to be there for the one that comes last, maybe on another part of the chip with an L2 cache
+        // of its own: the stores went through to memory (agent scope), each wavefront waits for its own, then one thread
+        // counts for the workgroup.  (With a fence instead, which writes the L2 cache back, by every wavefront: 160 us a redo.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        unsigned char* lds = reinterpret_cast<unsigned char*>(lut);
+        int* s_last = reinterpret_cast<int*>(lds + kRedoLds) - 1;         // (behind the selection's three control words)
+        if (threadIdx.x == 0) *s_last = atomicAdd(&a.redo_done[q], 1) == p_step * slices - 1;
+        __syncthreads();
+        if (*s_last != 0) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            __syncthreads();
+            redo_select<NT>(a, q, a.scores + buffer * a.m_stride, lds);
+        }
     }
     }
 }
@@ -1099,148 +1258,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     if (MODE == 0 && a.cand.cand_off) cand_offsets_lanes(a.cand, row, k, key != 0u ? (int)lab : -1, lane);
 }
 
-// ---- the k best of the queries redone exactly ----------------------------------------------------
-//
-// One workgroup per listed query; its row holds redo_cnt[q] scores in arbitrary order and the candidate columns
-// they belong to.  An entry's composite (order-preserving key of the score, then ~column) makes all entries
-// distinct: the k with the largest composites are the k best, ties going to the smaller column, whatever the
-// order they were appended in.  A radix search narrows the entries down, a byte at a time, until at most
-// max(k, kRedoFew) reach what is known of the k-th largest composite; those are gathered and sorted in LDS.  Bound by
-// the latency of its passes and of the sort's barriers; on the benchmark's searches one to three queries of 10,000
-// come here, with 400 to 3000 entries each.  Sorting up to 2048 entries outright, and all eight passes beyond, with the
-// digit looked for by one thread, took 50 us at 10M x 96 (k = 10); 13 us now, of which an empty launch is 4.5.
-constexpr int kRedoSort = 2048, kRedoFew = 128;
-static_assert(kMaxK <= kRedoSort, "the k winners are sorted in LDS");
-
-__global__ __launch_bounds__(1024) void k_redo_select(RedoSelectArgs a) {
-    __shared__ uint64_t s_comp[kRedoSort];
-    __shared__ int64_t s_lab[kRedoSort];
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t ctrl[3];
-    const int tid = threadIdx.x;
-    const int n_redo = min(a.gate[0] - a.gate_begin, a.gate_rows);
-    for (int row = blockIdx.x; row < n_redo; row += gridDim.x) {
-        const int64_t q = a.gate[1 + a.gate_begin + row];
-        const int32_t* off = a.cand_off + q * (a.np + 1);
-        const int n = a.redo_cnt[q];
-        const float* vals = a.vals + row * a.stride;
-        const float* cols = vals + a.stride / 2;
-        auto comp_of = [&](int i) -> uint64_t {
-            return ((uint64_t)order_key(vals[i]) << 32) | (uint32_t)~__float_as_uint(cols[i]);
-        };
-        const int take = n < a.k ? n : a.k;
-        uint64_t last = 0;                          // every entry of at least this composite is gathered
-        const int few = take > kRedoFew ? take : kRedoFew;
-        if (n > few) {
-            uint64_t mask = 0;
-            uint32_t need = (uint32_t)take;             // winners among the entries that share the bytes found so far
-            for (int shift = 56; shift >= 0; shift -= 8) {
-                __syncthreads();
-                if (tid < 256) hist[tid] = 0;
-                __syncthreads();
-                for (int i = tid; i < n; i += 1024) {
-                    const uint64_t c = comp_of(i);
-                    if ((c & mask) == last) atomicAdd(&hist[(c >> shift) & 255u], 1u);
-                }
-                __syncthreads();
-                if (tid < 64) {                         // the digit where the running count, from above, first reaches `need`
-                    uint32_t h[4];                      // lane l owns digits 4l .. 4l+3
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) h[e] = hist[4 * tid + e];
-                    const uint32_t own = h[0] + h[1] + h[2] + h[3];
-                    uint32_t above = own;
-#pragma unroll
-                    for (int o = 1; o < 64; o <<= 1) {
-                        const uint32_t t = __shfl_down(above, o);
-                        if (tid + o < 64) above += t;
-                    }
-                    above -= own;
-#pragma unroll
-                    for (int e = 3; e >= 0; --e) {
-                        if (above < need && above + h[e] >= need) {         // true for one digit only
-                            ctrl[0] = (uint32_t)(4 * tid + e);
-                            ctrl[1] = need - above;
-                            ctrl[2] = h[e];
-                        }
-                        above += h[e];
-                    }
-                }
-                __syncthreads();
-                last |= (uint64_t)ctrl[0] << shift;
-                mask |= (uint64_t)255 << shift;
-                need = ctrl[1];
-                // (all that reach `last`: the winners beyond its bytes, and every entry that shares them)
-                if ((uint32_t)take - need + ctrl[2] <= (uint32_t)few) break;
-            }
-        }
-        __syncthreads();
-        if (tid == 0) ctrl[0] = 0;
-        __syncthreads();
-        for (int i = tid; i < n; i += 1024) {
-            const uint64_t c = comp_of(i);
-            if (c >= last) {
-                const uint32_t at = atomicAdd(&ctrl[0], 1u);
-                if (at < (uint32_t)kRedoSort) s_comp[at] = c;
-            }
-        }
-        __syncthreads();
-        const int got = min((int)ctrl[0], kRedoSort);
-        int size = 1;
-        while (size < got) size <<= 1;
-        for (int i = got + tid; i < size; i += 1024) s_comp[i] = 0;
-        __syncthreads();
-        for (int sz = 2; sz <= size; sz <<= 1)
-            for (int stride = sz >> 1; stride > 0; stride >>= 1) {
-                for (int i = tid; i < size / 2; i += 1024) {
-                    const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
-                    const uint64_t c0 = s_comp[lo], c1 = s_comp[hi];
-                    if ((c0 >= c1) != ((lo & sz) == 0)) { s_comp[lo] = c1; s_comp[hi] = c0; }
-                }
-                __syncthreads();
-            }
-        // labels of the winners, then equal scores in label order
-        int kpad = 1;
-        while (kpad < take) kpad <<= 1;
-        for (int i = tid; i < kpad; i += 1024) {
-            int64_t lab = INT64_MAX;
-            if (i < take) {
-                const int32_t col = (int32_t)~(uint32_t)s_comp[i];
-                int lo = 0, hi = a.np;              // largest p with off[p] <= col
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (off[mid] <= col) lo = mid; else hi = mid;
-                }
-                const int64_t slot = a.list_off[a.probe[q * a.np + lo]] + (col - off[lo]);
-                lab = a.ids ? a.ids[slot] : slot;
-            } else {
-                s_comp[i] = 0;
-            }
-            s_lab[i] = lab;
-        }
-        __syncthreads();
-        for (int sz = 2; sz <= kpad; sz <<= 1)
-            for (int stride = sz >> 1; stride > 0; stride >>= 1) {
-                for (int i = tid; i < kpad / 2; i += 1024) {
-                    const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
-                    const uint32_t k0 = (uint32_t)(s_comp[lo] >> 32), k1 = (uint32_t)(s_comp[hi] >> 32);
-                    const int64_t l0 = s_lab[lo], l1 = s_lab[hi];
-                    if ((k0 > k1 || (k0 == k1 && l0 <= l1)) != ((lo & sz) == 0)) {
-                        const uint64_t c = s_comp[lo]; s_comp[lo] = s_comp[hi]; s_comp[hi] = c;
-                        s_lab[lo] = l1; s_lab[hi] = l0;
-                    }
-                }
-                __syncthreads();
-            }
-        for (int i = tid; i < a.k; i += 1024) {
-            const uint32_t key = i < take ? (uint32_t)(s_comp[i] >> 32) : 0u;
-            const float v = i < take ? order_value(key) : -__builtin_inff();
-            a.out_vals[q * a.k + i] = a.metric ? metric_value(a.metric, v, a.qnorm[q]) : v;
-            a.out_i64[q * a.k + i] = i < take ? s_lab[i] : -1;
-        }
-        __syncthreads();
-    }
-}
-
 // ---- re-ranking on raw vectors (Section "Architecture", Search: optional) -----------------------
 //
 // One workgroup per query: each wavefront takes every fourth candidate and computes <q, x> / (|q| |x|) from the raw
@@ -1496,12 +1513,14 @@ hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int b
     if (a.metric && (!a.qnorm || !a.store.xnorm)) return hipErrorInvalidValue;
     const size_t lut_bytes = (size_t)a.d * (1u << b) * sizeof(float);
     const bool direct = lut_bytes > 64 * 1024;
-    const size_t lds = direct ? (size_t)(a.d + (1 << b)) * sizeof(float) : lut_bytes;
+    size_t lds = direct ? (size_t)(a.d + (1 << b)) * sizeof(float) : lut_bytes;
+    if (a.gate) lds = std::max(lds, kRedoLds);
     // slices: every list is dealt out in rounds of 256 vectors to that many workgroups (grid z, the slowest
     // dimension of the dispatch order: the launch works through the index one slice at a time)
     dim3 grid((unsigned)(blocks_per_query > 0 ? blocks_per_query : a.np), (unsigned)q_count, (unsigned)std::max(1, std::min(slices, 64)));
     if (a.gate) grid = dim3(kRedoWorkgroups);
-    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), lds, st, a); };
+    if (a.gate && (a.k < 1 || a.k > kRedoSort)) return hipErrorInvalidValue;
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(a.gate ? kRedoThreads : 256), lds, st, a); };
 #define IVFTQ_SCAN(BV)                                                                              \
     case BV:                                                                                        \
         if (a.gate) direct ? go(k_list_scan<BV, true, true, false>) : go(k_list_scan<BV, false, true, false>);                \
@@ -1514,12 +1533,6 @@ hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int b
         default: return hipErrorInvalidValue;
     }
 #undef IVFTQ_SCAN
-    return hipGetLastError();
-}
-
-hipError_t launch_redo_select(const RedoSelectArgs& a, hipStream_t st) {
-    if (a.k < 1 || a.k > kRedoSort) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_redo_select, dim3((unsigned)std::min(a.gate_rows, 256)), dim3(1024), 0, st, a);
     return hipGetLastError();
 }
 

@@ -14,7 +14,7 @@ namespace ivftq {
 // Passes.  The workspace limit is for the score rows; a pass takes as many queries as it allows, since every pass walks every
 // probed list again.  The batched path stores scores of the dense prefix only, rows of `prefix` floats (it stops at the
 // first list that brings it to need_max vectors, so it is shorter than that plus the largest list); full-length rows,
-// scores and columns, are needed for the queries redone exactly, which take turns in gate_rows rows of the same
+// scores and columns, are needed for the queries redone exactly, which have gate_rows rows of the same
 // buffer.  The streaming path stores every score.
 constexpr int64_t kPassQueries = 32768;
 struct SearchRows {
