@@ -183,7 +183,7 @@ struct ivftq_index {
     DevBuf w_sums, w_counts, w_gain, w_rows, w_dst;
     DevBuf t_cent, t_cent_h, t_cent_l, t_bias;   // k-means works on its own tables; the index's change only on success
     DevBuf w_zh, w_zl;
-    DevBuf w_first, w_fscores, w_fids, w_pairs, w_tilebkt, w_cscore, w_cslot, w_ccnt, w_gate;
+    DevBuf w_first, w_fscores, w_fids, w_pairs, w_rank, w_tilebkt, w_cscore, w_cslot, w_ccnt, w_gate;
     DevBuf w_blk;                     // block maxima of the streaming scan
     DevBuf w_part;                    // partial results of a coarse assignment whose centroid stages are shared out
     int64_t last_batched_queries = 0;   // queries of the last pass of the most recent batched search (ivftq_scan_stats)
@@ -198,7 +198,7 @@ struct ivftq_index {
         return {&cent, &cent_h, &cent_l, &pi_h, &pi_l, &pit_h, &pit_l, &bias, &pi, &cb, &q_grid, &codes, &gamma, &ids, &xnorm, &head, &w_qnorm, &d_off, &d_size, &w_assign,
                 &w_slot, &w_order, &w_hist, &w_count, &w_base, &w_flag, &w_undecided, &cb_cascade, &w_keep, &w_keep_scores,
                 &w_S, &w_probe, &w_coarse, &w_z, &w_candoff, &w_scores, &w_sums, &w_counts, &w_gain, &w_rows, &w_dst,
-                &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_tilebkt, &w_cscore,
+                &t_cent, &t_cent_h, &t_cent_l, &t_bias, &w_first, &w_fscores, &w_fids, &w_pairs, &w_rank, &w_tilebkt, &w_cscore,
                 &w_cslot, &w_ccnt, &w_gate, &w_zh, &w_zl, &w_blk, &w_part};
     }
     explicit ivftq_index(const Allocator& a) : alloc(a) {
@@ -1298,6 +1298,7 @@ ivftq_status coarse_and_probe(ivftq_index* ix, const float* q, int64_t count, in
         ca.pi_h = ix->pi_h.as<uint16_t>(); ca.pi_l = ix->pi_l.as<uint16_t>();
         ca.z_out = rot->z; ca.zh_out = rot->zh; ca.zl_out = rot->zl; ca.norm_out = rot->norm;
     }
+    if (cand && cand->bucket_cnt) { ca.clear = cand->bucket_cnt; ca.clear_n = 2 * ix->nlist + kPairTotals; }
     HIP_TRY(timed(ix, st, P_COARSE_SCORES, [&] { return launch_coarse(ca, st); }));
     SelectArgs sa{};
     sa.vals = ix->w_S.as<float>(); sa.stride = ldS; sa.rows = count; sa.k = nprobe; sa.m_fixed = ix->nlist;
@@ -1416,6 +1417,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         HIP_TRY(ix->w_fscores.ensure((size_t)held * k * sizeof(float)));
         HIP_TRY(ix->w_fids.ensure((size_t)held * k * sizeof(int64_t)));
         HIP_TRY(ix->w_pairs.ensure((size_t)held * nprobe * sizeof(int32_t)));
+        HIP_TRY(ix->w_rank.ensure((size_t)held * nprobe * sizeof(int32_t)));
         HIP_TRY(ix->w_count.ensure((size_t)(4 * buckets + kPairTotals) * sizeof(uint32_t)));
         // (at least what ivftq_reconstruct keeps there, so that a call of it moves nothing that a recorded search uses)
         HIP_TRY(ix->w_tilebkt.ensure((size_t)std::max<int64_t>(near_tiles + late_tiles, buckets + 1) * sizeof(int32_t)));
@@ -1436,7 +1438,8 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         int32_t* redo_cnt = batched ? ix->w_gate.as<int32_t>() + 1 + qc : nullptr;
         if (batched) {
             co.first = first; co.cand_cnt = ix->w_ccnt.as<int32_t>(); co.gate = ix->w_gate.as<int32_t>(); co.redo_cnt = redo_cnt; co.redo_done = redo_cnt + qc;
-            co.bucket_cnt = ix->w_count.as<uint32_t>(); co.buckets = buckets + kPairTotals;
+            co.bucket_cnt = ix->w_count.as<uint32_t>(); co.L = ix->nlist;
+            if (pairs_counted_early(cnt, nprobe, ix->nlist)) co.rank = ix->w_rank.as<int32_t>();
         }
         RotatedQueries rq{};
         rq.z = ix->w_z.as<float>();
@@ -1504,7 +1507,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         pt.cursor = pt.count + buckets + kPairTotals; pt.pair_off = reinterpret_cast<int32_t*>(pt.cursor + buckets); pt.tile_off = pt.pair_off + buckets;
         pt.tile_near = ix->w_tilebkt.as<int32_t>(); pt.tile_late = pt.tile_near + near_tiles; pt.pairs = ix->w_pairs.as<int32_t>();
         HIP_TRY(timed(ix, st, P_PAIR_GROUP, [&] {
-            return launch_pair_grouping(ix->w_probe.as<int32_t>(), first, cnt, nprobe, ix->nlist, ix->d_size.as<int32_t>(), shape, pt, st); }));
+            return launch_pair_grouping(ix->w_probe.as<int32_t>(), first, co.rank, cnt, nprobe, ix->nlist, ix->d_size.as<int32_t>(), shape, pt, st); }));
         BatchScanArgs ba{};
         ba.zh = ix->w_zh.as<uint16_t>(); ba.zl = ix->w_zl.as<uint16_t>(); ba.z_pitch = ix->dp;
         ba.cb = cb;

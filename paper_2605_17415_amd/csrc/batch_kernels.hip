@@ -84,7 +84,17 @@ __global__ void k_pair_scatter(const int32_t* __restrict__ probe, const int32_t*
     if (probe[it] >= 0) pairs[pair_off[bkt] + atomicAdd(&cursor[bkt], 1u)] = (int32_t)it;
 }
 
-// The same two steps with the counters privatised in LDS: a workgroup takes kPairChunk consecutive
+// The second step alone, where the probe selection has counted the pairs and left each one's place in its bucket.  (Counting in a launch of
+// its own and a second round of updates of the buckets took 9 us more for 1000 queries x 16 probes, 20 for 10,000 x 64.)
+__global__ __launch_bounds__(256) void k_pair_place(const int32_t* __restrict__ probe, const int32_t* __restrict__ first, const int32_t* __restrict__ rank,
+                                                    int64_t n, int np, int L, const int32_t* __restrict__ pair_off, int32_t* __restrict__ pairs) {
+    const int64_t it = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (it >= n) return;
+    const int l = probe[it], at = rank[it], q = (int)it / np;
+    if (l >= 0) pairs[pair_off[l + ((int)it - q * np >= first[q] ? L : 0)] + at] = (int32_t)it;
+}
+
+// Both steps with the counters privatised in LDS: a workgroup takes kPairChunk consecutive
 // pairs, counts them per bucket in LDS, and touches each global counter once per bucket it met
 // (thousands of pairs hit the same few thousand counters, so per-pair global atomics serialise).
 // In the scatter step that one global atomic reserves the workgroup's range inside the bucket.
@@ -351,10 +361,18 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
 // to 0.99 at d = 16 to 32 with 3 or more bits and below that with more coordinates (0.82 at d = 256).
 bool batch_covers(int d, int b) { return d >= 16 && d <= kMaxD && ((b >= 3 && b <= 5) || b == 8 || (b == 2 && d > 32)); }
 
-hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int64_t nq, int np, int L, const int32_t* list_size,
+hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, const int32_t* rank, int64_t nq, int np, int L, const int32_t* list_size,
                                 const TileShape& shape, const PairTable& p, hipStream_t st) {
     const int64_t n = nq * np;
     if (n <= 0) return hipSuccess;
+    const auto ranges = [&] {
+        hipLaunchKernelGGL(k_pair_ranges, dim3((unsigned)((2 * L + 255) / 256)), dim3(256), 0, st, list_size, 2 * L, L, shape, p);
+    };
+    if (rank) {
+        ranges();
+        hipLaunchKernelGGL(k_pair_place, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, probe, first, rank, n, np, L, (const int32_t*)p.pair_off, p.pairs);
+        return hipGetLastError();
+    }
     const bool in_lds = 2 * L <= kPairLdsBuckets;
     const unsigned blocks = (unsigned)(in_lds ? (n + kPairChunk - 1) / kPairChunk : (n + 255) / 256);
     const size_t lds = (size_t)2 * L * sizeof(uint32_t);
@@ -365,14 +383,13 @@ hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int6
         if (e == hipSuccess) e = lim_scatter.ensure(reinterpret_cast<const void*>(k_pair_scatter_lds), most);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_pair_count_lds, dim3(blocks), dim3(1024), lds, st, probe, first, nq, np, L, p.count);
+        ranges();
+        hipLaunchKernelGGL(k_pair_scatter_lds, dim3(blocks), dim3(1024), lds, st, probe, first, nq, np, L, (const int32_t*)p.pair_off, p.cursor, p.pairs);
     } else {
         hipLaunchKernelGGL(k_pair_count, dim3(blocks), dim3(256), 0, st, probe, first, nq, np, L, p.count);
-    }
-    hipLaunchKernelGGL(k_pair_ranges, dim3((unsigned)((2 * L + 255) / 256)), dim3(256), 0, st, list_size, 2 * L, L, shape, p);
-    if (in_lds)
-        hipLaunchKernelGGL(k_pair_scatter_lds, dim3(blocks), dim3(1024), lds, st, probe, first, nq, np, L, (const int32_t*)p.pair_off, p.cursor, p.pairs);
-    else
+        ranges();
         hipLaunchKernelGGL(k_pair_scatter, dim3(blocks), dim3(256), 0, st, probe, first, nq, np, L, (const int32_t*)p.pair_off, p.cursor, p.pairs);
+    }
     return hipGetLastError();
 }
 

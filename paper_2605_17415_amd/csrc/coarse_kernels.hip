@@ -111,6 +111,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ScoresCfg<D
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, j = lane & 31;
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (32 * R);
+    for (int i = (int)((blockIdx.y * gridDim.x + blockIdx.x) * 256) + tid; i < a.clear_n; i += (int)(gridDim.x * gridDim.y * 256)) a.clear[i] = 0u;
     const int cent_stages = a.Lpad / kTN, stages = coarse_stages(a);
     const int s_lo = (int)blockIdx.y * per_y, s_hi = s_lo + per_y < stages ? s_lo + per_y : stages;
 

@@ -118,6 +118,7 @@ struct CoarseArgs {
     float* z_out;                                 // [n][pitch]
     uint16_t* zh_out; uint16_t* zl_out;           // optional: split float16 form of z
     float* norm_out;                              // optional: |x_i| of every row, 0 where it is not usable
+    uint32_t* clear; int clear_n;                 // words that the launch sets to zero (counters of the kernels after it)
 };
 hipError_t launch_coarse(const CoarseArgs& a, hipStream_t st);
 // assign[i] = argmax_c (<x~_i, cent_c> + bias_c), -1 (and *flag = 1) for a row of zero or non-finite norm, in
@@ -244,13 +245,14 @@ hipError_t launch_inertia(const double* gain, int L, int64_t n, double* out, hip
 // cand_off[q*(np+1) + p] = sum_{p'<p} list_size[probe[q][p']]
 // first (may be null): first[q] = shortest probe prefix (>= 1 cell) holding at least
 // max(k, 2*k*T/cap) vectors, T the query's candidate total; np if there is none.  With `first`, cand_cnt[q],
-// gate[0], redo_cnt[q], redo_done[q] and bucket_cnt[0 .. buckets) (each may be null) are set to zero: the counters the batched
-// scan, its merge, the exact redo and the pair grouping add to.
+// gate[0], redo_cnt[q] and redo_done[q] (each may be null) are set to zero: the counters the batched
+// scan, its merge and the exact redo add to; and with `rank`, rank[q*np+p] is how many pairs were in the bucket of pair (q, p) before it
+// (bucket_cnt counts them; see PairTable).
 struct CandOffsetArgs {
     const int32_t* list_size; int32_t* cand_off;
     int k; int cap; int32_t* first;
     int32_t* cand_cnt; int32_t* gate; int32_t* redo_cnt; int32_t* redo_done;
-    uint32_t* bucket_cnt; int buckets;
+    uint32_t* bucket_cnt; int32_t* rank; int L;
 };
 constexpr int kSelTake = 192;                   // most winners that the workgroup selection's short cut, which alone reads block maxima, is for
 constexpr int64_t kBlockMaximaRow = 8192;       // candidates of a typical row, besides k * k, from which a small streaming call leaves block maxima
@@ -371,13 +373,19 @@ constexpr int batch_tile(int d, int b) { return 32 * batch_query_tiles(batch_dp(
 // queues, tile t to queue t % kTileQueues, each served by the workgroups of its number (on one of the chip's eight parts).
 constexpr int kTileQueues = 16, kPairTotals = 32 + 2 * kTileQueues * 32;
 struct PairTable {
-    // cleared with the candidate offsets: [2L] pairs of a bucket, then kPairTotals words: totals (pairs, tiles of the dense pass, of
+    // cleared with the coarse scores: [2L] pairs of a bucket, then kPairTotals words: totals (pairs, tiles of the dense pass, of
     // the threshold pass) and from word 32 on the next tiles of either pass, kTileQueues counters a cache line apart
     uint32_t* count; int32_t* totals;
     uint32_t* cursor; int32_t* pair_off; int32_t* tile_off;      // [2L] each; cursor is scratch
     int32_t* tile_near; int32_t* tile_late; int32_t* pairs;
 };
-hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, int64_t nq, int np, int L, const int32_t* list_size,
+// Whether the probe selection counts the buckets' pairs itself: where they are few, for its updates of counters, about five in a nanosecond
+// over all of them and 14 ns apart on one of them, come on top of it; else they are counted in LDS, in two launches that take 10 us and
+// more.  Probe selection and grouping, counted early and not, us: 1000 queries x 16 probes of 1000 cells 18.7 and 26, 256 x 64 of 4096 21
+// and 29, 10,000 x 32 of 4096 82 and 86, 4096 x 32 of 1024 51 and 32.
+inline bool pairs_counted_early(int64_t nq, int np, int L) { return nq * np <= std::min<int64_t>(32768, (int64_t)256 * L); }
+// rank (may be null): as the probe selection left it, with the counts
+hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, const int32_t* rank, int64_t nq, int np, int L, const int32_t* list_size,
                                 const TileShape& shape, const PairTable& p, hipStream_t st);
 
 struct BatchScanArgs {

@@ -24,9 +24,9 @@ __device__ __forceinline__ int32_t lanes_up_to(int32_t v, int lane) {
     return v;
 }
 
-// The pair grouping's counters, cleared by all threads of the launch.
-__device__ __forceinline__ void clear_buckets(const CandOffsetArgs& c) {
-    for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < c.buckets; i += (int)(gridDim.x * blockDim.x)) c.bucket_cnt[i] = 0u;
+// The place of pair (q, p) of cell `list` in its bucket: the query's nearest p1 lists in one, the others in another.
+__device__ __forceinline__ void count_pair(const CandOffsetArgs& c, int64_t q, int np, int p, int p1, int list) {
+    if (c.rank && p < np && list >= 0) c.rank[q * np + p] = (int32_t)atomicAdd(&c.bucket_cnt[list + (p >= p1 ? c.L : 0)], 1u);
 }
 
 // How many of a query's `total` candidates are scored densely to find its threshold.  Were the prefix a random
@@ -57,7 +57,9 @@ __device__ __forceinline__ void cand_offsets_lanes(const CandOffsetArgs& c, int6
     if (lane == 0) off[np] = total;
     if (!c.first) return;
     const uint64_t reached = __ballot(lane < np && (int64_t)incl >= dense_prefix(c, total));
-    if (lane == 0) put_first(c, q, reached ? (int)__builtin_ctzll(reached) + 1 : np);
+    const int p1 = reached ? (int)__builtin_ctzll(reached) + 1 : np;
+    count_pair(c, q, np, lane, p1, list);
+    if (lane == 0) put_first(c, q, p1);
 }
 
 // And for any number of probes, whose cells are in LDS: 64 at a time, `incl` ([np], LDS) takes the running sums.
@@ -80,6 +82,7 @@ __device__ __forceinline__ void cand_offsets_wave(const CandOffsetArgs& c, int64
         const uint64_t reached = __ballot(p0 + lane < np && (int64_t)incl[p0 + lane] >= need);
         if (reached) p1 = p0 + (int)__builtin_ctzll(reached) + 1;
     }
+    for (int p = lane; p < np; p += 64) count_pair(c, q, np, p, p1, cell[p]);
     if (lane == 0) put_first(c, q, p1);
 }
 
@@ -543,7 +546,6 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
     int2* c_blk = reinterpret_cast<int2*>(c_ent + kSelCand + 8);      // [kSelBlocks] ... and the blocks that reach the bound
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (MODE == 0) clear_buckets(a.cand);
     const int64_t row = blockIdx.x;
     const float* vals = a.vals + row * a.stride;
     const int64_t q = row;
@@ -910,7 +912,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     __shared__ uint32_t s_work[4][256 + 64];             // per wavefront: 256 bins, 64 winning columns
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t row = (int64_t)blockIdx.x * 4 + wave;
-    if (MODE == 0) clear_buckets(a.cand);
     if (row >= a.rows) return;
     const int64_t q = row;
     const int m = MODE == 0 ? a.m_fixed : a.cand_off[q * (a.np + 1) + (a.p_limit ? a.p_limit[q] : a.np)];
