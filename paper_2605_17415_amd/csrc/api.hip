@@ -876,10 +876,10 @@ ivftq_status ivftq_train_coarse(ivftq_index* ix, const float* x_dev, int64_t n, 
         // Sums per cell in a fixed order (two runs give the same bits): the rows are grouped by cell with the
         // stable counting sort of the append path, then one workgroup adds up the rows of a cell.
         HIP_TRY(timed(ix, st, P_SEG_HIST, [&] { return launch_segment_hist(ix->w_assign.as<int32_t>(), n, seg_len, nseg, L, ix->w_hist.as<uint32_t>(), st); }));
-        HIP_TRY(timed(ix, st, P_SEG_SCAN, [&] { return launch_segment_scan(ix->w_hist.as<uint32_t>(), nseg, L, counts_dev, st); }));
+        HIP_TRY(timed(ix, st, P_SEG_SCAN, [&] { return launch_segment_scan(ix->w_hist.as<uint32_t>(), nseg, L, counts_dev, nullptr, nullptr, st); }));
         HIP_TRY(launch_exclusive_scan(counts_dev, L, cell_base, st));
         HIP_TRY(timed(ix, st, P_RANK, [&] { return launch_stable_rank(ix->w_assign.as<int32_t>(), n, seg_len, nseg, L, ix->w_hist.as<uint32_t>(), nullptr,
-                                   nullptr, cell_base, ix->w_order.as<int32_t>(), nullptr, st); }));
+                                   nullptr, cell_base, ix->w_order.as<int32_t>(), nullptr, nullptr, nullptr, st); }));
         double* gain = it == niter - 1 ? ix->w_gain.as<double>() : nullptr;
         HIP_TRY(timed(ix, st, P_KMEANS_SUMS, [&] { return launch_kmeans_cell_sums(x_dev, d, ix->w_order.as<int32_t>(), cell_base, counts_dev, L,
                                         ix->w_sums.as<float>(), pitch, cent, gain, st); }));
@@ -925,21 +925,20 @@ ivftq_status place_rows(ivftq_index* ix, const int32_t* assign, int64_t n, bool 
     const int64_t seg_len = segment_length(n);
     const int nseg = (int)((n + seg_len - 1) / seg_len);
     HIP_TRY(ix->w_hist.ensure((size_t)nseg * L * sizeof(uint32_t)));
-    HIP_TRY(ix->w_count.ensure((size_t)L * sizeof(uint32_t)));
-    HIP_TRY(ix->w_base.ensure((size_t)2 * L * sizeof(int64_t)));
+    HIP_TRY(ix->w_base.ensure((size_t)L * (2 * sizeof(int64_t) + sizeof(int32_t))));
     if (want_order) HIP_TRY(ix->w_order.ensure((size_t)n * sizeof(int2)));
     HIP_TRY(timed(ix, st, P_SEG_HIST, [&] { return launch_segment_hist(assign, n, seg_len, nseg, L, ix->w_hist.as<uint32_t>(), st); }));
-    HIP_TRY(timed(ix, st, P_SEG_SCAN, [&] { return launch_segment_scan(ix->w_hist.as<uint32_t>(), nseg, L, ix->w_count.as<uint32_t>(), st); }));
     // pinned staging: [L u32 batch counts | 16 B flag | 2L i64 bases | L i32 list sizes]
     const size_t off_flag = (size_t)round_up(L, 4) * sizeof(uint32_t), off_base = off_flag + 16;
     const size_t off_size = off_base + (size_t)2 * L * sizeof(int64_t);
     HIP_TRY(ix->pin.ensure(off_size + (size_t)L * sizeof(int32_t)));
     char* pin = static_cast<char*>(ix->pin.p);
-    const uint32_t* count = reinterpret_cast<const uint32_t*>(pin);
-    const int* flag = reinterpret_cast<const int*>(pin + off_flag);
+    uint32_t* count = reinterpret_cast<uint32_t*>(pin);
+    int* flag = reinterpret_cast<int*>(pin + off_flag);
     int64_t* base = reinterpret_cast<int64_t*>(pin + off_base);   // [0, L): first free slot of each list; [L, 2L): first position in the batch order
-    HIP_TRY(hipMemcpyAsync(pin, ix->w_count.p, L * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(pin + off_flag, ix->w_flag.p, sizeof(int), hipMemcpyDeviceToHost, st));
+    int32_t* sizes = reinterpret_cast<int32_t*>(pin + off_size);
+    // (the kernel writes the counts and the flag to host memory)
+    HIP_TRY(timed(ix, st, P_SEG_SCAN, [&] { return launch_segment_scan(ix->w_hist.as<uint32_t>(), nseg, L, count, ix->w_flag.as<int>(), flag, st); }));
     // The one host synchronisation of an append: the host decides here whether the lists have room.
     // It also means every earlier use of the staging buffer by this stream has completed.
     HIP_TRY(hipStreamSynchronize(st));
@@ -960,23 +959,28 @@ ivftq_status place_rows(ivftq_index* ix, const int32_t* assign, int64_t n, bool 
         base[l] = ix->h_off[l] + ix->h_size[l];
         base[L + l] = run;
         run += count[l];
+        sizes[l] = (int32_t)need[l];
     }
-    HIP_TRY(hipMemcpyAsync(ix->w_base.p, base, (size_t)2 * L * sizeof(int64_t), hipMemcpyHostToDevice, st));
+    // (the new sizes go along; the kernel that ranks the rows puts them in place)
+    HIP_TRY(hipMemcpyAsync(ix->w_base.p, base, (size_t)L * (2 * sizeof(int64_t) + sizeof(int32_t)), hipMemcpyHostToDevice, st));
     // encode_add takes the rows in list order and derives their slots from the position (order_cell); add_encoded
     // packs in input order and needs the slot of every row
     HIP_TRY(timed(ix, st, P_RANK, [&] { return launch_stable_rank(assign, n, seg_len, nseg, L, ix->w_hist.as<uint32_t>(), ix->w_base.as<int64_t>(),
                                want_order ? nullptr : ix->w_slot.as<int64_t>(), ix->w_base.as<int64_t>() + L,
-                               nullptr, want_order ? ix->w_order.as<int2>() : nullptr, st); }));
+                               nullptr, want_order ? ix->w_order.as<int2>() : nullptr,
+                               reinterpret_cast<const int32_t*>(ix->w_base.as<int64_t>() + 2 * L), ix->d_size.as<int32_t>(), st); }));
     return IVFTQ_OK;
 }
 
-// Records the new list sizes; the device copy is updated in stream order (no host wait).
-ivftq_status commit_rows(ivftq_index* ix, const std::vector<int64_t>& need, int64_t n, hipStream_t st) {
-    const int L = ix->nlist;
-    const size_t off_size = (size_t)round_up(L, 4) * sizeof(uint32_t) + 16 + (size_t)2 * L * sizeof(int64_t);
-    int32_t* sizes = reinterpret_cast<int32_t*>(static_cast<char*>(ix->pin.p) + off_size);   // allocated by place_rows
-    for (int l = 0; l < L; ++l) sizes[l] = ix->h_size[l] = (int32_t)need[l];
-    HIP_TRY(hipMemcpyAsync(ix->d_size.p, sizes, (size_t)L * sizeof(int32_t), hipMemcpyHostToDevice, st));
+// Records the new list sizes, which the device has from place_rows; if the rows could not be stored after all (`stored`), the device gets the
+// old ones back.
+ivftq_status commit_rows(ivftq_index* ix, const std::vector<int64_t>& need, int64_t n, hipError_t stored, hipStream_t st) {
+    if (stored != hipSuccess) {
+        (void)hipMemcpyAsync(ix->d_size.p, ix->h_size.data(), (size_t)ix->nlist * sizeof(int32_t), hipMemcpyHostToDevice, st);
+        (void)hipStreamSynchronize(st);
+        HIP_TRY(stored);
+    }
+    for (int l = 0; l < ix->nlist; ++l) ix->h_size[l] = (int32_t)need[l];
     ix->ntotal += n;
     return IVFTQ_OK;
 }
@@ -1114,8 +1118,7 @@ ivftq_status ivftq_encode_add(ivftq_index* ix, const float* x_dev, int64_t n, co
     a.list_base = ix->w_base.as<int64_t>();
     a.batch_base = ix->w_base.as<int64_t>() + L;
     a.labels = ids_dev; a.label_base = ix->ntotal;
-    HIP_TRY(timed(ix, st, P_ENCODE, [&] { return launch_encode(0, a, st); }));
-    return commit_rows(ix, need, n, st);
+    return commit_rows(ix, need, n, timed(ix, st, P_ENCODE, [&] { return launch_encode(0, a, st); }), st);
 }
 
 namespace {
@@ -1134,9 +1137,8 @@ ivftq_status add_encoded_rows(ivftq_index* ix, int64_t n, const int32_t* assign_
     std::vector<int64_t> need;
     ivftq_status s = place_rows(ix, assign_dev, n, false, false, need, st);
     if (s != IVFTQ_OK) return s;
-    HIP_TRY(timed(ix, st, P_PACK, [&] { return launch_pack_scatter(codes_dev, gamma_dev, xnorm_dev, ids_dev, ix->ntotal, ix->w_slot.as<int64_t>(), n, ix->d,
-                                ix->b, ix->store(), st); }));
-    return commit_rows(ix, need, n, st);
+    return commit_rows(ix, need, n, timed(ix, st, P_PACK, [&] { return launch_pack_scatter(codes_dev, gamma_dev, xnorm_dev, ids_dev, ix->ntotal,
+                                ix->w_slot.as<int64_t>(), n, ix->d, ix->b, ix->store(), st); }), st);
 }
 
 }  // namespace

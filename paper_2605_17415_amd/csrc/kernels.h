@@ -178,15 +178,18 @@ constexpr int kMaxSegments = 512;      // segments of a batch: the workgroups of
 hipError_t launch_segment_hist(const int32_t* assign, int64_t n, int64_t seg_len, int nseg, int L,
                                uint32_t* seg_hist, hipStream_t st);
 // in place: seg_hist[s][l] <- sum_{s'<s} seg_hist[s'][l];  batch_count[l] <- column total
-hipError_t launch_segment_scan(uint32_t* seg_hist, int nseg, int L, uint32_t* batch_count, hipStream_t st);
+// (batch_count may be host memory; flag, may be null: a word copied to flag_out)
+hipError_t launch_segment_scan(uint32_t* seg_hist, int nseg, int L, uint32_t* batch_count, const int* flag, int* flag_out, hipStream_t st);
 // slot[i] = list_base[l] + (rank of row i among the batch rows of list l, in input order); slot and
 // list_base may be null when only the order is wanted.
 // order (may be null): the batch's rows grouped by list, lists ascending, input order inside a list:
 // order[batch_base[l] + rank] = i, with batch_base the exclusive running sum of the batch's rows per list.
 // order_cell (may be null): the same order with the list beside the row, order_cell[...] = (i, l).
+// new_size (may be null): list_size[l] = new_size[l].
 hipError_t launch_stable_rank(const int32_t* assign, int64_t n, int64_t seg_len, int nseg, int L,
                               const uint32_t* seg_hist, const int64_t* list_base, int64_t* slot,
-                              const int64_t* batch_base, int32_t* order, int2* order_cell, hipStream_t st);
+                              const int64_t* batch_base, int32_t* order, int2* order_cell,
+                              const int32_t* new_size, int32_t* list_size, hipStream_t st);
 // pack already-quantised rows (codes: n x d bytes, one bin number each) into their storage slots
 // xnorm (may be null): raw norms of the rows, stored when the store keeps them
 hipError_t launch_pack_scatter(const uint8_t* codes, const uint16_t* gamma, const float* xnorm, const int64_t* labels,
