@@ -422,8 +422,8 @@ __global__ __launch_bounds__(64) void k_copy_rows_normalised(const float* __rest
 // that a lane holds one output coordinate of 16 vectors and every store instruction writes whole 128-byte lines.
 // For d <= 64 several tiles share a workgroup (SLABS), which keeps it at 128 threads or more.  Workgroups walk
 // contiguous ranges of tiles: one search for the list, then steps.
-// A call of 1M x 128, b = 4: 0.91 ms with one thread per output coordinate and float32 multiply-adds, 0.18 ms so (3.3 TB/s
-// read + written).
+// A call of 1M x 128, b = 4: 0.91 ms with one thread per output coordinate and float32 multiply-adds, 0.16 ms so; the kernel
+// takes 114 us of it (5.2 TB/s read + written), the rest is the wait that ends the call.
 //
 // F32: the operands are float32 (v_mfma_f32_32x32x2_f32) instead of both float16 parts, for d <= kReconF32.  With few
 // terms a sum the split form's own rounding (2^-23 of an operand, the same for every use of a level) is what counts:
@@ -440,7 +440,7 @@ struct ReconCfg {
     static constexpr int LDF = DP + 4;                           // floats per LDS row
     static constexpr int slab_halves = F32 ? 2 * 32 * LDF : 2 * 32 * LDH;         // float rows, or hi and lo rows
     static constexpr int buf_halves = SLABS * slab_halves;
-    static constexpr size_t lds_bytes = (size_t)2 * buf_halves * 2 + 256 * 4 + 2 * VEC * 4;
+    static constexpr size_t lds_bytes = (size_t)2 * buf_halves * 2 + 256 * 8 + 2 * VEC * 4;
 };
 
 // A value that kernels before this one wrote and none changes now, read through the scalar cache (the compiler would
@@ -460,9 +460,11 @@ __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
     constexpr int KB = Cfg::KB, LDH = Cfg::LDH, LDF = Cfg::LDF, VEC = Cfg::VEC, T = Cfg::THREADS;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     uint16_t* stage = reinterpret_cast<uint16_t*>(lds_raw);                       // [2][SLABS][hi, lo][32][LDH], or floats [2][SLABS][32][LDF]
-    uint32_t* tab = reinterpret_cast<uint32_t*>(stage + 2 * Cfg::buf_halves);     // [2^b] hi | lo << 16, or the float
-    float* gam = reinterpret_cast<float*>(tab + 256);                             // [2][VEC] norms (split form: * 2^-20)
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, jl = lane & 31;
+    // [2^b] hi | lo << 16, or the float; PAIR (b = 1, 2, 4): [2^2b] both parts of two levels, (hi pair, lo pair)
+    constexpr bool PAIR = NW == 1 && !F32;
+    uint32_t* tab = reinterpret_cast<uint32_t*>(stage + 2 * Cfg::buf_halves);
+    float* gam = reinterpret_cast<float*>(tab + 512);                             // [2][VEC] norms (split form: * 2^-20)
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, jl = lane & 31;
     const int col = 32 * (wave % Cfg::NT) + jl, my_slab = wave / Cfg::NT;
     const int words = store.words;
     const uint32_t mask = (1u << b) - 1u;
@@ -480,8 +482,14 @@ __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
             bl[kb] = *reinterpret_cast<const half8*>(pit_l + (size_t)col * DP + 16 * kb + 8 * half);
         }
     }
-    for (int e = tid; e <= (int)mask; e += T) {
-        if constexpr (F32) {
+    for (int e = tid; e < (PAIR ? 1 << 2 * b : (int)mask + 1); e += T) {
+        if constexpr (PAIR) {
+            _Float16 h0, l0, h1, l1;
+            split_scaled(cb[e & mask], h0, l0);
+            split_scaled(cb[e >> b], h1, l1);
+            reinterpret_cast<uint2*>(tab)[e] = make_uint2((uint32_t)__builtin_bit_cast(uint16_t, h0) | (uint32_t)__builtin_bit_cast(uint16_t, h1) << 16,
+                                                          (uint32_t)__builtin_bit_cast(uint16_t, l0) | (uint32_t)__builtin_bit_cast(uint16_t, l1) << 16);
+        } else if constexpr (F32) {
             tab[e] = __float_as_uint(cb[e]);
         } else {
             _Float16 h, l;
@@ -539,6 +547,23 @@ __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
         for (int p = 0; p < 2; ++p) {
             const int grp = tid + p * T, slab = (grp >> 5) / (DP / 8), chunk = (grp >> 5) % (DP / 8);
             const int sh = (8 * b * chunk) & 31;
+            if constexpr (PAIR) {
+                // (hi, lo) of one pair and of the next become (hi, hi) and (lo, lo) by an exchange: four registers in a row to store
+                const uint32_t codes = w[p][0] >> sh, both = (1u << 2 * b) - 1u;
+                uint32_t r[8];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const uint2 v = reinterpret_cast<const uint2*>(tab)[(codes >> (2 * b * t)) & both];
+                    r[2 * t] = v.x;
+                    r[2 * t + 1] = v.y;
+                }
+#pragma unroll
+                for (int t = 0; t < 8; t += 4) asm("v_swap_b32 %0, %1" : "+v"(r[t + 1]), "+v"(r[t + 2]));
+                uint16_t* row = st + slab * Cfg::slab_halves + (grp & 31) * LDH + 8 * chunk;
+                *reinterpret_cast<uint4*>(row) = make_uint4(r[0], r[1], r[4], r[5]);
+                *reinterpret_cast<uint4*>(row + 32 * LDH) = make_uint4(r[2], r[3], r[6], r[7]);
+                continue;
+            }
             uint64_t bits = ((NW > 1 ? (uint64_t)w[p][NW > 1 ? 1 : 0] << 32 : 0ull) | w[p][0]) >> sh;
             if (NW > 2 && sh) bits |= (uint64_t)w[p][NW - 1] << (64 - sh);
             uint32_t e[8];
@@ -614,8 +639,12 @@ __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
         // tests they could not be counted, and the wait for the next tile's words, which sit in front of them in the
         // memory queue, would be a wait for the stores as well (0.31 ms at 1M x 128 that way).  The whole offset of a row
         // goes through the address register: the check does not cover the scalar offset.
-        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
-            x_out + (row0 + 32 * my_slab) * (int64_t)d, 0, min(max(cur_left, 0), 32) * d * 4, 0x00020000);
+        // (the descriptor is the same for a wavefront, which has to be said: taken for a lane's own, every store became a loop over the
+        // descriptors that the lanes might have: kernel 153 us for 1M x 128, 114 now.  The stores go past the caches, 4 % of a call.)
+        const uint64_t to = reinterpret_cast<uint64_t>(x_out + (row0 + 32 * my_slab) * (int64_t)d);
+        const uint32_t to_lo = __builtin_amdgcn_readfirstlane((uint32_t)to), to_hi = __builtin_amdgcn_readfirstlane((uint32_t)(to >> 32));
+        const int to_bytes = __builtin_amdgcn_readfirstlane(min(max(cur_left, 0), 32) * d * 4);
+        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)to_hi << 32 | to_lo), 0, to_bytes, 0x00020000);
         // (hidden from the compiler, which would keep the sixteen offsets in registers of their own from tile to tile)
         uint32_t at = col < d ? (uint32_t)(4 * half * d + col) * 4u : 0x40000000u;
         asm volatile("" : "+v"(at));
@@ -625,7 +654,7 @@ __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
             const float gg[4] = {gm.x, gm.y, gm.z, gm.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i, at += (uint32_t)d * 4u)
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(fmaf(gg[i], acc[4 * g + i], c)), out, at, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(fmaf(gg[i], acc[4 * g + i], c)), out, at, 0, 2);
             at += (uint32_t)d * 16u;
         }
     }
