@@ -1420,7 +1420,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         HIP_TRY(ix->w_fids.ensure((size_t)held * k * sizeof(int64_t)));
         HIP_TRY(ix->w_pairs.ensure((size_t)held * nprobe * sizeof(int32_t)));
         HIP_TRY(ix->w_rank.ensure((size_t)held * nprobe * sizeof(int32_t)));
-        HIP_TRY(ix->w_count.ensure((size_t)(4 * buckets + kPairTotals) * sizeof(uint32_t)));
+        HIP_TRY(ix->w_count.ensure((size_t)((3 + kPairRecord) * buckets + kPairTotals + 4) * sizeof(uint32_t)));
         // (at least what ivftq_reconstruct keeps there, so that a call of it moves nothing that a recorded search uses)
         HIP_TRY(ix->w_tilebkt.ensure((size_t)std::max<int64_t>(near_tiles + late_tiles, buckets + 1) * sizeof(int32_t)));
         HIP_TRY(ix->w_cscore.ensure((size_t)held * cap * sizeof(float)));
@@ -1506,10 +1506,11 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         ix->last_batched_queries = cnt;
         PairTable pt{};
         pt.count = ix->w_count.as<uint32_t>(); pt.totals = reinterpret_cast<int32_t*>(pt.count + buckets);
-        pt.cursor = pt.count + buckets + kPairTotals; pt.pair_off = reinterpret_cast<int32_t*>(pt.cursor + buckets); pt.tile_off = pt.pair_off + buckets;
+        pt.cursor = pt.count + buckets + kPairTotals; pt.pair_off = reinterpret_cast<int32_t*>(pt.cursor + buckets);
+        pt.record = reinterpret_cast<int32_t*>(pt.count) + round_up(3 * buckets + kPairTotals, 4);      // (16 bytes at a time)
         pt.tile_near = ix->w_tilebkt.as<int32_t>(); pt.tile_late = pt.tile_near + near_tiles; pt.pairs = ix->w_pairs.as<int32_t>();
         HIP_TRY(timed(ix, st, P_PAIR_GROUP, [&] {
-            return launch_pair_grouping(ix->w_probe.as<int32_t>(), first, co.rank, cnt, nprobe, ix->nlist, ix->d_size.as<int32_t>(), shape, pt, st); }));
+            return launch_pair_grouping(ix->w_probe.as<int32_t>(), first, co.rank, cnt, nprobe, ix->nlist, ix->d_size.as<int32_t>(), ix->d_off.as<int64_t>(), shape, pt, st); }));
         BatchScanArgs ba{};
         ba.zh = ix->w_zh.as<uint16_t>(); ba.zl = ix->w_zl.as<uint16_t>(); ba.z_pitch = ix->dp;
         ba.cb = cb;

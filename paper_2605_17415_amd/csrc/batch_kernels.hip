@@ -31,17 +31,19 @@ __global__ void k_pair_count(const int32_t* __restrict__ probe, const int32_t* _
     if (probe[it] >= 0) atomicAdd(&count[probe[it] + (late ? L : 0)], 1u);      // (no cell: a query whose scores are no numbers)
 }
 
-// Every bucket gets a range of the pair array (pair_off) and of its pass's tile array (tile_off, tile_bucket), and
+// Every bucket gets a range of the pair array (pair_off) and of its pass's tile array, its record, and
 // cursor[b] = 0.  One thread per bucket; a workgroup puts its buckets together with a scan and takes its ranges from
 // the totals with one atomic each, so the ranges of different workgroups lie in no particular order, which nothing
 // depends on (in bucket order, by one workgroup: 0.017 ms for 8192 buckets, the chain of its loads).
-__global__ __launch_bounds__(256) void k_pair_ranges(const int32_t* __restrict__ list_size, int nb, int L, TileShape shape, PairTable p) {
+__global__ __launch_bounds__(256) void k_pair_ranges(const int32_t* __restrict__ list_size, const int64_t* __restrict__ list_off, int nb,
+                                                     int L, TileShape shape, PairTable p) {
     __shared__ uint32_t part[4][3];
     __shared__ int32_t start[3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = (int)blockIdx.x * 256 + tid;
     const bool in = b < nb, near = b < L;
     const uint32_t n = in ? p.count[b] : 0u;
     const int size = in ? list_size[near ? b : b - L] : 0;
+    const int64_t slot = in ? list_off[near ? b : b - L] : 0;
     if (in) p.cursor[b] = 0u;
     const uint32_t w = near ? shape.tq_near : shape.tq;
     const uint32_t tiles = size > 0 ? (n + w - 1) / w * list_parts(size, near ? shape.part_near : shape.part) : 0u;
@@ -69,7 +71,9 @@ __global__ __launch_bounds__(256) void k_pair_ranges(const int32_t* __restrict__
     if (!in) return;
     p.pair_off[b] = at[0];
     const int32_t t0 = near ? at[1] : at[2];
-    p.tile_off[b] = t0;
+    int4* rec = reinterpret_cast<int4*>(p.record + (int64_t)b * kPairRecord);
+    rec[0] = make_int4(size, t0, (int)n, at[0]);
+    rec[1] = make_int4((int)(uint32_t)slot, (int)(slot >> 32), 0, 0);
     int32_t* to = near ? p.tile_near : p.tile_late;
     for (uint32_t t = 0; t < tiles; ++t) to[t0 + t] = b;
 }
@@ -361,12 +365,12 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
 // to 0.99 at d = 16 to 32 with 3 or more bits and below that with more coordinates (0.82 at d = 256).
 bool batch_covers(int d, int b) { return d >= 16 && d <= kMaxD && ((b >= 3 && b <= 5) || b == 8 || (b == 2 && d > 32)); }
 
-hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, const int32_t* rank, int64_t nq, int np, int L, const int32_t* list_size,
+hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, const int32_t* rank, int64_t nq, int np, int L, const int32_t* list_size, const int64_t* list_off,
                                 const TileShape& shape, const PairTable& p, hipStream_t st) {
     const int64_t n = nq * np;
     if (n <= 0) return hipSuccess;
     const auto ranges = [&] {
-        hipLaunchKernelGGL(k_pair_ranges, dim3((unsigned)((2 * L + 255) / 256)), dim3(256), 0, st, list_size, 2 * L, L, shape, p);
+        hipLaunchKernelGGL(k_pair_ranges, dim3((unsigned)((2 * L + 255) / 256)), dim3(256), 0, st, list_size, list_off, 2 * L, L, shape, p);
     };
     if (rank) {
         ranges();

@@ -125,30 +125,37 @@ struct BatchTile {
     int v_lo, v_hi, nq_tile;             // vectors [v_lo, v_hi) of a list; v_lo is a multiple of 64
     int pair0;
     int64_t base_slot;
-    __device__ __forceinline__ void find(const BatchScanArgs& a, int tile, int bkt, int tq) {
-        const int l = bkt >= a.L ? bkt - a.L : bkt;
-        const int n_l = a.store.list_size[l], parts = list_parts(n_l, a.part_len), rel = tile - a.p.tile_off[bkt];
-        const int len = ((n_l + parts - 1) / parts + 63) & ~63;
+    // size, ...: of the record of the tile's bucket
+    __device__ __forceinline__ void set(int tile, int part_len, int tq, int size, int first_tile, int count, int first_pair, int slot_lo, int slot_hi) {
+        const int parts = list_parts(size, part_len), rel = tile - first_tile;
+        const int len = ((size + parts - 1) / parts + 63) & ~63;
         v_lo = (rel % parts) * len;
-        v_hi = v_lo + len < n_l ? v_lo + len : n_l;
-        const int skip = rel / parts * tq, left = (int)a.p.count[bkt] - skip;
-        pair0 = a.p.pair_off[bkt] + skip;
+        v_hi = v_lo + len < size ? v_lo + len : size;
+        const int skip = rel / parts * tq, left = count - skip;
+        pair0 = first_pair + skip;
         nq_tile = left < tq ? left : tq;
-        base_slot = a.store.list_off[l];
+        base_slot = (int64_t)(((uint64_t)(uint32_t)slot_hi << 32) | (uint32_t)slot_lo);
     }
 };
 
 // The workgroups of a launch are as many as the chip holds and every wavefront takes tiles of its own until none is left, the first two
-// by its number, the others from the counter of its workgroup's queue: tiles differ in work by the sizes of the lists and the queries that meet there.  No
-// wavefront waits for another: finding a tile's list, pairs and queries is a chain of four dependent reads, 2 to 3 us, under which the
-// other wavefronts of the SIMD go on (with a tile to a workgroup, whose wavefronts met at a barrier and waited for the counter, half of
-// all wavefront cycles went by waiting).  A tile's number is asked for two tiles ahead and its bucket one tile ahead.
+// by its number, the others from the counter of its workgroup's queue: tiles differ in work by the sizes of the lists and the queries that
+// meet there.  No wavefront waits for another (with a tile to a workgroup, whose wavefronts met at a barrier and waited for the counter,
+// half of all wavefront cycles went by waiting).  Finding a tile's bucket, record, pairs and queries is a chain of five dependent reads of
+// 0.7 us and more; all but the last are made while the tiles before it are worked on: its number is asked for two tiles ahead, its bucket
+// one tile ahead, and record and pairs between the slabs of the tile before.
+// TQ: queries of a tile.
+template <int TQ>
 struct TileQueue {
     const BatchScanArgs& a;
     const int32_t* bucket_of;
     int32_t* counter;
-    int tile, bkt, end;                  // the tile to work on (past `end`: none)
-    int next, asked, asked_bkt, q, given;        // queue, and its tiles given by number
+    BatchTile t;                         // the tile to work on
+    int tile, end;                       // its number (past `end`: none)
+    int next, asked, q, given;           // queue, and its tiles given by number
+    int phase = 0;                       // of the next tile: 0 its bucket asked for, 1 its record, 2 its pairs
+    int32_t known[(TQ + 63) / 64];       // in turn its bucket, its record, the pairs of queries lane and 64 + lane
+    BatchTile tn;
     __device__ __forceinline__ TileQueue(const BatchScanArgs& args, int wave, int waves) : a(args) {
         bucket_of = a.dense ? a.p.tile_near : a.p.tile_late;
         end = a.p.totals[a.dense ? 1 : 2];
@@ -157,10 +164,10 @@ struct TileQueue {
         const int servers = ((int)gridDim.x - q + kTileQueues - 1) / kTileQueues * waves;        // wavefronts
         const int me = (int)blockIdx.x / kTileQueues * waves + wave;
         given = 2 * servers;
-        tile = nth(me);
-        next = nth(me + servers);
-        bkt = tile < end ? bucket_of[tile] : 0;
-        ask();
+        next = nth(me);
+        asked = servers + me - given;    // (the second tile by number, as if asked for)
+        if (next < end) known[0] = bucket_of[next];
+        advance();
     }
     // the j-th tile of the queue: one of each kTileQueues tiles, another one each time (the parts of a list, of which the last is the
     // shortest, follow each other)
@@ -171,14 +178,43 @@ struct TileQueue {
         asm volatile("" : "+v"(lane));
         if (lane == 0) {
             asked = atomicAdd(counter + lane, 1);
-            asked_bkt = bucket_of[(next < end ? next : 0) + lane];
+            known[0] = bucket_of[(next < end ? next : 0) + lane];
+        }
+    }
+    // between slabs; the answers are used some slabs later: they come behind the words on their way, for which the wait would be too
+    __device__ __forceinline__ void between(int slab) {
+        if (slab == 2 || slab == 8) step();
+    }
+    __device__ __forceinline__ void step() {
+        if (phase >= 2 || next >= end) return;
+        int lane = (int)(threadIdx.x & 63);
+        asm volatile("" : "+v"(lane));
+        if (phase++ == 0) {
+            known[0] = (a.p.record + (int64_t)__builtin_amdgcn_readfirstlane(known[0]) * kPairRecord)[lane & (kPairRecord - 1)];
+        } else {
+            auto word = [&](int i) { return __builtin_amdgcn_readlane(known[0], i); };
+            tn.set(next, a.part_len, TQ, word(0), word(1), word(2), word(3), word(4), word(5));
+#pragma unroll
+            for (int i = 0; i < (TQ + 63) / 64; ++i) known[i] = (a.p.pairs + tn.pair0)[min(64 * i + lane, tn.nq_tile - 1)];
         }
     }
     __device__ __forceinline__ void advance() {
+        while (phase < 2 && next < end) step();
         tile = next;
-        bkt = __builtin_amdgcn_readfirstlane(asked_bkt);
+        t = tn;
         next = nth(__builtin_amdgcn_readfirstlane(asked) + given);
-        if (tile < end) ask();
+        phase = 2;
+    }
+    // pair of query e of the tile (some other one beyond its last); before `proceed`
+    __device__ __forceinline__ int32_t pair_of(int e) const {
+        int32_t p = __shfl(known[0], e & 63);
+        if (TQ > 64 && e >= 64) p = __shfl(known[(TQ + 63) / 64 - 1], e & 63);
+        return p;
+    }
+    // once the tile's pairs are no longer asked for
+    __device__ __forceinline__ void proceed() {
+        phase = 0;
+        ask();
     }
 };
 
@@ -296,9 +332,8 @@ void k_batch_dense(BatchScanArgs a) {
     const int words = a.store.words;
     const GroupWords<DP, B, NW> from(words, lane);
     __syncthreads();
-    for (TileQueue queue(a, wave, WAVES); queue.tile < queue.end; queue.advance()) {
-    BatchTile t;
-    t.find(a, queue.tile, queue.bkt, TQ);
+    for (TileQueue<TQ> queue(a, wave, WAVES); queue.tile < queue.end; queue.advance()) {
+    const BatchTile t = queue.t;
     const int n_v = t.v_hi - t.v_lo, nslab = (n_v + 31) / 32;
     // A list starts at a multiple of 64 slots and its slots reach to one, so a slab's words and norms can be read whole.
     const uint32_t* codes = a.store.codes + ((t.base_slot + t.v_lo) >> 6) * words * 64;
@@ -333,8 +368,7 @@ void k_batch_dense(BatchScanArgs a) {
         global_float* to[N][4];
 #pragma unroll
         for (int n = 0; n < N; ++n) {
-            auto pair = [&](int e) { return a.p.pairs[t.pair0 + (e < t.nq_tile ? e : 0)]; };
-            const int64_t row = (int64_t)(pair(16 * n + 4 * (jl % 4) + jl / 4) / a.np) * a.z_pitch + 8 * quarter;      // (row 4 h + i: query 4 i + h)
+            const int64_t row = (int64_t)(queue.pair_of(16 * n + 4 * (jl % 4) + jl / 4) / a.np) * a.z_pitch + 8 * quarter;      // (row 4 h + i: query 4 i + h)
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 qh[n][kb] = ql[n][kb] = half8{};
@@ -345,12 +379,13 @@ void k_batch_dense(BatchScanArgs a) {
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int32_t it = pair(16 * n + 4 * i + quarter), q = it / a.np;
+                const int32_t it = queue.pair_of(16 * n + 4 * i + quarter), q = it / a.np;
                 coarse[n][i] = a.coarse[it];
                 to[n][i] = (global_float*)(a.scores + (int64_t)q * a.m_stride + a.cand_off[(int64_t)q * (a.np + 1) + (it - q * a.np)] + t.v_lo);
                 qn[n][i] = RAW ? a.qnorm[q] : 0.f;
             }
         }
+        queue.proceed();
 
         auto scan = [&](int slab, Ahead& f) {
             // A block's words make room for those of the same block AHEAD slabs on as soon as they are looked up.
@@ -413,6 +448,7 @@ void k_batch_dense(BatchScanArgs a) {
         for (int slab = 0; slab < nslab; slab += AHEAD) {
             scan(slab, ahead[0]);
             if (AHEAD > 1 && slab + 1 < nslab) scan(slab + 1, ahead[AHEAD - 1]);
+            queue.between(slab);
         }
     };
     if (t.nq_tile > 16) scan_tile(std::integral_constant<int, 2>{});
@@ -488,9 +524,8 @@ void k_batch_threshold(BatchScanArgs a) {
     for (int e = lane; e < TQ; e += 64) s_cnt[e] = 0;
     if (lane == 0) { s_held[0] = 0; s_held[1] = CAND; }
     __syncthreads();
-    for (TileQueue queue(a, wave, WAVES); queue.tile < queue.end; queue.advance()) {
-    BatchTile t;
-    t.find(a, queue.tile, queue.bkt, TQ);
+    for (TileQueue<TQ> queue(a, wave, WAVES); queue.tile < queue.end; queue.advance()) {
+    const BatchTile t = queue.t;
     const int n_v = t.v_hi - t.v_lo, nslab = (n_v + 31) / 32, n_qt = (t.nq_tile + 31) / 32;
     // A list starts at a multiple of 64 slots and its slots reach to one, so a slab's words and norms can be read whole; the norms of
     // what lies beyond the list count as no numbers.
@@ -518,12 +553,13 @@ void k_batch_threshold(BatchScanArgs a) {
 #pragma unroll
         for (int n = 0; n < N; ++n) {
             const int e = 32 * n + jl;
-            const int32_t it = a.p.pairs[t.pair0 + (e < t.nq_tile ? e : 0)], q = it / a.np;
+            const int32_t it = queue.pair_of(e), q = it / a.np;
             load_query<DP>(a.zh + (int64_t)q * a.z_pitch + 8 * half, a.z_pitch, qh[n]);
             // (columns beyond the tile's queries: a NaN threshold, which not even an infinite score reaches; both halves write the same)
             s_row[e] = make_uint4(__float_as_uint(a.coarse[it]), e < t.nq_tile ? __float_as_uint(a.thresh[(int64_t)q * a.thresh_stride]) : 0x7FC00000u,
                                   (uint32_t)it, RAW ? __float_as_uint(a.qnorm[q]) : 0u);
         }
+        queue.proceed();
         wave_sync();
         auto scan_slab = [&](int slab, Ahead& f) {
             // A block's words make room for those of the same block AHEAD slabs on as soon as they are looked up.
@@ -630,6 +666,7 @@ void k_batch_threshold(BatchScanArgs a) {
         for (int slab = 0; slab < nslab; slab += AHEAD) {
             scan_slab(slab, ahead[0]);
             if (AHEAD > 1 && slab + 1 < nslab) scan_slab(slab + 1, ahead[AHEAD - 1]);
+            queue.between(slab);
         }
     };
     if (NQ >= 4 && n_qt == 4) scan(std::integral_constant<int, NQ >= 4 ? 4 : 1>{});

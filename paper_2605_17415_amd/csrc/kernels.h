@@ -371,15 +371,18 @@ constexpr int batch_tile(int d, int b) { return 32 * batch_query_tiles(batch_dp(
 // The (query, probe) pairs bucketed by list: bucket l holds the pairs (q, p < first[q]) of list l (the dense pass),
 // bucket L + l the pairs (q, p >= first[q]) (the threshold pass).  pairs[pair_off[b] ...] holds the count[b] flat pair
 // numbers q*np + p of bucket b.  Its workgroup tiles, every tq_near or tq of its queries times the list_parts of its
-// list, are tile_off[b] ... of its pass's array (tile_near or tile_late), whose entries name the bucket.
+// list, follow each other in its pass's array (tile_near or tile_late), whose entries name the bucket.
 // Updates of one counter from all over the chip follow each other at about 14 ns, so the tiles of a pass are dealt out to kTileQueues
 // queues, tile t to queue t % kTileQueues, each served by the workgroups of its number (on one of the chip's eight parts).
+constexpr int kPairRecord = 8;       // words of a bucket's record
 constexpr int kTileQueues = 16, kPairTotals = 32 + 2 * kTileQueues * 32;
 struct PairTable {
     // cleared with the coarse scores: [2L] pairs of a bucket, then kPairTotals words: totals (pairs, tiles of the dense pass, of
     // the threshold pass) and from word 32 on the next tiles of either pass, kTileQueues counters a cache line apart
     uint32_t* count; int32_t* totals;
-    uint32_t* cursor; int32_t* pair_off; int32_t* tile_off;      // [2L] each; cursor is scratch
+    uint32_t* cursor; int32_t* pair_off;      // [2L] each; cursor is scratch
+    // [2L] what a tile of a bucket has to know: its list's vectors, its first tile, its pairs, the first of them, its list's first slot (2 words)
+    int32_t* record;
     int32_t* tile_near; int32_t* tile_late; int32_t* pairs;
 };
 // Whether the probe selection counts the buckets' pairs itself: where they are few, for its updates of counters, about five in a nanosecond
@@ -388,7 +391,7 @@ struct PairTable {
 // and 29, 10,000 x 32 of 4096 82 and 86, 4096 x 32 of 1024 51 and 32.
 inline bool pairs_counted_early(int64_t nq, int np, int L) { return nq * np <= std::min<int64_t>(32768, (int64_t)256 * L); }
 // rank (may be null): as the probe selection left it, with the counts
-hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, const int32_t* rank, int64_t nq, int np, int L, const int32_t* list_size,
+hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, const int32_t* rank, int64_t nq, int np, int L, const int32_t* list_size, const int64_t* list_off,
                                 const TileShape& shape, const PairTable& p, hipStream_t st);
 
 struct BatchScanArgs {
