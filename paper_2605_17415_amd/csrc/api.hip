@@ -1372,23 +1372,28 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
     // Scan strategy.  Streaming: a row of workgroups per query walks its probed lists, every score written,
     // exact selection.  Batched: pairs regrouped by list and scanned on the matrix cores against a
     // threshold from each query's nearest lists.  The streaming scan's time follows the bytes it reads, once
-    // per query; the batched path reads a list once per 128 queries, so its time follows the part of the
-    // index the call touches, but it is a chain of about twelve kernels with a fixed cost of its own.
-    // Batched when the streamed bytes exceed kBatchedGain times the touched bytes plus kBatchedFixedBytes.  The
-    // constants are those of an earlier batched path (crossovers with nprobe 32 / 32 / 64 at 1M x 128, 10M x 96,
-    // 10M x 200 then: about 200, 380 and 170 queries).  On clustered rows the present paths cross at about 150, 255 and
-    // 65 queries, so that calls in between take up to 1.5 times as long as they could (160 queries at 10M x 200: 578 us
-    // streamed, 417 batched; 320 at 10M x 96 326 and 260; a raw metric's length, 4 bytes a vector, is not counted either); on rows
-    // without clusters the line lies too low instead (1M x 128, 64 probes, k = 100: 100 queries 190 us batched, 129 streamed; even
-    // at 200).  Mode 2 asks for the batched path whatever the size of the call.
-    constexpr double kBatchedGain = 2.3, kBatchedFixedBytes = 0.25e9;
+    // per query; the batched path reads a list once per 64 to 128 queries, so its time follows the part of the
+    // index the call touches, but it is a chain of nine kernels with a fixed cost of its own.
+    // Batched when the streamed bytes exceed kBatchedGain times the touched bytes plus kBatchedFixedBytes, a line from an earlier
+    // batched path, or when the time of the streamed look-ups exceeds that of the touched ones by kBatchedFixed.  (Neither depends on the
+    // number of results: a call with more of them must not be streamed where one with fewer is batched, because the larger call has to leave
+    // room for the smaller.)  Queries where the two paths cross on clustered rows, on rows without clusters, and the line: 1M x 128,
+    // 32 probes 45, 195 and 195 (k = 10), 64 probes, k = 100 -, 200 and 98; 10M x 96, 32 probes 110, 185 and 254 (370 by bytes alone: 280
+    // queries 275 us streamed, 191 batched); 10M x 200, 64 probes, k = 100 below 24, about 108 and 94 (170: 140 queries 517 and 299); 2M x 64,
+    // 8 bits, 16 probes 55, 87 and 236 (350).  So calls between 45 queries and the line still take up to 1.5 times as long as they could on
+    // clustered rows, and on unclustered ones beyond it with many results the other way round.  Mode 2 asks for the batched path whatever
+    // the size of the call.
+    constexpr double kBatchedGain = 2.3, kBatchedFixedBytes = 0.25e9, kBatchedFixed = 110.0;      // the last in us
     const int metric = ix->metric;
     const double vec_bytes = (double)codes_store.words * 4 + 2;
     const double index_bytes = (double)ix->ntotal * vec_bytes;
     const double streamed = (double)nq * nprobe * ((double)ix->ntotal / ix->nlist) * vec_bytes;
     const double touched = index_bytes * std::min(1.0, (double)nq * nprobe / ix->nlist);
+    // coordinates looked up in a microsecond, streamed and batched (a table of 256 levels a coordinate is slow to stream with)
+    const double stream_rate = bits == 8 ? 2.5e6 : 8.8e6, batch_rate = bits == 8 ? 4.5e6 : 9e6, coords = ix->d / vec_bytes;
     const bool batched = batch_covers(ix->d, bits) && nprobe > 1 && ix->search_mode != 1 &&
-                         (ix->search_mode == 2 || streamed >= kBatchedGain * touched + kBatchedFixedBytes);
+                         (ix->search_mode == 2 || streamed >= kBatchedGain * touched + kBatchedFixedBytes ||
+                          streamed * coords / stream_rate >= touched * coords / batch_rate + kBatchedFixed);
     const int cap = std::min(2048, std::max(512, 16 * k));
     // error bound of a residual sum taken from the leading float16 parts alone (threshold pass)
     float cmax = 0.f;
