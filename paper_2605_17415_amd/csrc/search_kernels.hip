@@ -501,6 +501,18 @@ constexpr int kSelHeld = 16;    // columns (or block maxima) a thread keeps in r
 constexpr int kSelBlocks = 512; // most blocks it gathers from
 constexpr int kSelOffs = 256;   // most probes whose offsets are staged in LDS
 
+// Both kinds of selection below run over a row's values twice: for the largest of a thread's share, and for those that reach the bound.  A key
+// made of every value, a range test and an address for each were about 26 vector instructions a value.  So values are compared as floats,
+// two to an instruction the first time, keys are made of those that pass, and full rounds of loads do without range tests (10,000 queries
+// at 10M x 96: k best of the nearest lists 68 -> 56 us, 32 of 4096 cells 61.5 -> 59.5, the call 600 -> 583; one query at 1M x 128 25.9 -> 25.5).
+// Values that are no number have the lowest key and no part in the comparison of floats, but that a share of nothing else counts as -inf: such
+// a bound may be reached by fewer keys than winners are wanted, and then the radix search takes over.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // A lower bound of the take-th largest of the 256 keys at `maxima`, less than 2^10 below it (0 when there are fewer).  For
 // few winners of the 64 keys that are the largest of four each, which is another such bound and hardly lower (30 keys
 // of a row dealt out reach it for 24 winners instead of 25) at a quarter of the steps.
@@ -577,7 +589,6 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
         // (one base pointer and loads without a branch between them, so that all of a thread's are in flight together)
         const uint32_t* src = by_block ? a.blk_max + row * a.blk_stride : reinterpret_cast<const uint32_t*>(vals);
         const int parts = by_block ? n_blk : m;
-        auto key_of = [&](uint32_t raw) -> uint32_t { return by_block ? raw : order_key(__uint_as_float(raw)); };
         uint32_t* maxima = reinterpret_cast<uint32_t*>(c_ent);
         uint32_t held[kSelHeld], bound = 0;
         if (parts <= 1024) {
@@ -587,18 +598,49 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
 #pragma unroll
             for (int u = 0; u < kSelHeld; ++u) held[u] = src[min(256 * u + tid, parts - 1)];
         }
-        if (parts > kSelAll || by_block) {
-            uint32_t best = 0;
+        auto read_on = [&](int i0, uint32_t (&v)[kSelU]) {
+            if (i0 + 256 * kSelU <= parts) {
 #pragma unroll
-            for (int u = 0; u < kSelHeld; ++u) best = 256 * u + tid < parts ? max(best, key_of(held[u])) : best;
-            for (int i0 = 256 * kSelHeld; i0 < parts; i0 += 256 * kSelU) {
-                uint32_t v[kSelU];
+                for (int u = 0; u < kSelU; ++u) v[u] = (src + i0 + 256 * u)[(uint32_t)tid];
+            } else {
 #pragma unroll
                 for (int u = 0; u < kSelU; ++u) v[u] = src[min(i0 + 256 * u + tid, parts - 1)];
-#pragma unroll
-                for (int u = 0; u < kSelU; ++u) best = i0 + 256 * u + tid < parts ? max(best, key_of(v[u])) : best;
             }
-            maxima[tid] = best;
+        };
+        if (parts > kSelAll || by_block) {
+            if (by_block) {
+                uint32_t best = 0;
+#pragma unroll
+                for (int u = 0; u < kSelHeld; ++u) best = 256 * u + tid < parts ? max(best, held[u]) : best;
+                for (int i0 = 256 * kSelHeld; i0 < parts; i0 += 256 * kSelU) {
+                    uint32_t v[kSelU];
+                    read_on(i0, v);
+#pragma unroll
+                    for (int u = 0; u < kSelU; ++u) best = i0 + 256 * u + tid < parts ? max(best, v[u]) : best;
+                }
+                maxima[tid] = best;
+            } else {
+                float best = -__builtin_inff();
+                auto fold = [&](int i0, const uint32_t* v) {
+                    if (i0 + 256 * kSelU <= parts) {
+#pragma unroll
+                        for (int u = 0; u < kSelU; u += 2) best = max3(best, __uint_as_float(v[u]), __uint_as_float(v[u + 1]));
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < kSelU; ++u)
+                            best = i0 + 256 * u + tid < parts && __uint_as_float(v[u]) > best ? __uint_as_float(v[u]) : best;
+                    }
+                };
+                static_assert(kSelHeld == 2 * kSelU, "two rounds held");
+                fold(0, held);
+                if (256 * kSelU < parts) fold(256 * kSelU, held + kSelU);
+                for (int i0 = 256 * kSelHeld; i0 < parts; i0 += 256 * kSelU) {
+                    uint32_t v[kSelU];
+                    read_on(i0, v);
+                    fold(i0, v);
+                }
+                maxima[tid] = tid < parts ? order_key(best) : 0u;
+            }
             __syncthreads();
             bound = kth_of_maxima(maxima, take, lane);
         }
@@ -607,12 +649,13 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
             const uint32_t pos = atomicAdd(&ctrl[5], 1u);
             if (pos < (uint32_t)kSelCand) c_ent[pos] = (uint64_t)key << 32 | (uint32_t)~col;
         };
+        const float least = order_value(bound);          // (no number where there is no bound: every value goes on)
         auto pass = [&](uint32_t raw, int i) {
-            const uint32_t key = key_of(raw);
-            if (i >= parts || key < bound) return;
             if (!by_block) {
-                gather(key, i);
-            } else {
+                if (__uint_as_float(raw) < least) return;
+                const uint32_t key = order_key(__uint_as_float(raw));
+                if (i < parts && key >= bound) gather(key, i);
+            } else if (i < parts && raw >= bound) {
                 const uint32_t pos = atomicAdd(&ctrl[6], 1u);
                 if (pos < (uint32_t)kSelBlocks) c_blk[pos].x = i;
             }
@@ -624,8 +667,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
         }
         for (int i0 = 256 * kSelHeld; i0 < parts; i0 += 256 * kSelU) {
             uint32_t v[kSelU];
-#pragma unroll
-            for (int u = 0; u < kSelU; ++u) v[u] = src[min(i0 + 256 * u + tid, parts - 1)];
+            read_on(i0, v);
 #pragma unroll
             for (int u = 0; u < kSelU; ++u) pass(v[u], i0 + 256 * u + tid);
         }
@@ -677,7 +719,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
             __syncthreads();
         }
         const int found = (int)ctrl[5];
-        picked = found <= kSelCand && (!by_block || ctrl[6] <= (uint32_t)kSelBlocks);      // uniform over the workgroup
+        picked = found >= take && found <= kSelCand && (!by_block || ctrl[6] <= (uint32_t)kSelBlocks);      // uniform over the workgroup
         if (picked) {
             // place of every gathered key in (key desc, column asc) order
             // (the loads of eight entries in flight together: the loop is their latency and nothing else)
@@ -910,7 +952,7 @@ template <int MODE, int NV, bool WIDE = false>
 // MODE 1 lose from the same limit)
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ? 4 : 1, 8))) void k_select_small(SelectArgs a) {
     __shared__ uint32_t s_work[4][256 + 64];             // per wavefront: 256 bins, 64 winning columns
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t row = (int64_t)blockIdx.x * 4 + wave;
     if (row >= a.rows) return;
     const int64_t q = row;
@@ -924,12 +966,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     auto key_of = [](float v) -> uint32_t { return order_key(v); };
 
     win_col[lane] = -1;
-    uint32_t keys[NV];                                   // key of column e*64 + lane (unused beyond m)
+    float held[NV];                                      // column e*64 + lane (unused beyond m)
+    if (NV * 64 <= m) {
 #pragma unroll
-    for (int e = 0; e < NV; ++e) {
-        const int i = e * 64 + lane;
-        keys[e] = key_of(vals[i < m ? i : 0]);
+        for (int e = 0; e < NV; ++e) held[e] = (vals + e * 64)[(uint32_t)lane];
+    } else {
+#pragma unroll
+        for (int e = 0; e < NV; ++e) held[e] = vals[e * 64 + lane < m ? e * 64 + lane : 0];
     }
+    auto read_on = [&](int i0, float (&v)[kSelSmallU]) {
+        if (i0 + 64 * kSelSmallU <= m) {
+#pragma unroll
+            for (int u = 0; u < kSelSmallU; ++u) v[u] = (vals + i0 + 64 * u)[(uint32_t)lane];
+        } else {
+#pragma unroll
+            for (int u = 0; u < kSelSmallU; ++u) { const int i = i0 + 64 * u + lane; v[u] = vals[i < m ? i : m - 1]; }
+        }
+    };
+    // the largest of N columns' values and of `best`, every STEP-th of them from column FIRST on
+    auto fold = [&](auto n, auto first, auto step, int i0, const float* v, float best) {
+        constexpr int N = decltype(n)::value, FIRST = decltype(first)::value, STEP = decltype(step)::value;
+        if (i0 + 64 * N <= m) {
+#pragma unroll
+            for (int e = FIRST; e < N; e += 2 * STEP) best = max3(best, v[e], v[e + STEP]);
+        } else {
+#pragma unroll
+            for (int e = FIRST; e < N; e += STEP) best = i0 + 64 * e + lane < m && v[e] > best ? v[e] : best;
+        }
+        return best;
+    };
+    const std::integral_constant<int, NV> all{};
+    const std::integral_constant<int, kSelSmallU> more{};
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 1> c1{};
+    const std::integral_constant<int, 2> c2{};
 
     // Short cut.  The take-th largest of the 64 lane maxima is reached by at least `take` keys (one per lane
     // that holds such a maximum), so every winner is among the keys that reach it; there are seldom many more
@@ -937,20 +1007,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     // asc) and the first `take` are the winners: the same set as the radix search below would pick.
     bool done = false;
     if (take > 0 && take <= kShortcutTake) {
-        uint32_t lane_max = 0u;
-#pragma unroll
-        for (int e = 0; e < NV; ++e) lane_max = (e * 64 + lane < m && keys[e] > lane_max) ? keys[e] : lane_max;
+        float lane_max = fold(all, c0, c1, 0, held, ninf);
         for (int i0 = NV * 64; i0 < m; i0 += 64 * kSelSmallU) {
             float v[kSelSmallU];
-#pragma unroll
-            for (int u = 0; u < kSelSmallU; ++u) { const int i = i0 + 64 * u + lane; v[u] = vals[i < m ? i : m - 1]; }
-#pragma unroll
-            for (int u = 0; u < kSelSmallU; ++u) {
-                const uint32_t key = key_of(v[u]);
-                lane_max = (i0 + 64 * u + lane < m && key > lane_max) ? key : lane_max;
-            }
+            read_on(i0, v);
+            lane_max = fold(more, c0, c1, i0, v, lane_max);
         }
-        uint32_t sorted = lane_max;                      // the lane maxima in descending order over the lanes
+        uint32_t sorted = lane < m ? key_of(lane_max) : 0u;                      // the lane maxima in descending order over the lanes
 #pragma unroll
         for (int size = 2; size <= 64; size <<= 1) {
 #pragma unroll
@@ -966,7 +1029,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
             uint32_t* c_key = hist;                      // [64] keys that reach it, [64] their columns
             int* c_col = reinterpret_cast<int*>(hist + 64);
             uint32_t count = 0;
-            auto collect = [&](int i, uint32_t key) {
+            const float least = order_value(reach);
+            auto collect = [&](int i, float v) {
+                if (__ballot(!(v < least)) == 0) return;
+                const uint32_t key = key_of(v);
                 const bool in = i < m && key >= reach;
                 const uint64_t b = __ballot(in);
                 const uint32_t pos = count + (uint32_t)__popcll(b & (((uint64_t)1 << lane) - 1));
@@ -975,18 +1041,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
             };
 #pragma unroll
             for (int e = 0; e < NV; ++e)
-                if (e * 64 < m) collect(e * 64 + lane, keys[e]);
+                if (e * 64 < m) collect(e * 64 + lane, held[e]);
             for (int i0 = NV * 64; i0 < m && count <= 64u; i0 += 64 * kSelSmallU) {
                 float v[kSelSmallU];
-#pragma unroll
-                for (int u = 0; u < kSelSmallU; ++u) { const int i = i0 + 64 * u + lane; v[u] = vals[i < m ? i : m - 1]; }
+                read_on(i0, v);
 #pragma unroll
                 for (int u = 0; u < kSelSmallU; ++u)
-                    if (i0 + 64 * u < m) collect(i0 + 64 * u + lane, key_of(v[u]));
+                    if (i0 + 64 * u < m) collect(i0 + 64 * u + lane, v[u]);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if (count <= 64u) {
+            if (count >= (uint32_t)take && count <= 64u) {
                 uint32_t ck = lane < (int)count ? c_key[lane] : 0u;
                 int cc = lane < (int)count ? c_col[lane] : INT32_MAX;
 #pragma unroll
@@ -1014,26 +1079,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
     // compacted into LDS and every one counts the keys that precede it in (key desc, column asc) order, which is
     // its place among the winners.
     if (WIDE && !done && take > kShortcutTake && take <= 64) {
-        uint32_t gm0 = 0u, gm1 = 0u;
-#pragma unroll
-        for (int e = 0; e < NV; ++e) {
-            const bool in = e * 64 + lane < m;
-            if (e & 1) gm1 = (in && keys[e] > gm1) ? keys[e] : gm1;
-            else gm0 = (in && keys[e] > gm0) ? keys[e] : gm0;
-        }
-        static_assert(NV % 2 == 0 && kSelSmallU % 2 == 0, "block parity below");
+        static_assert(NV % 4 == 0 && kSelSmallU % 4 == 0, "pairs of blocks of either parity");
+        float max0 = fold(all, c0, c2, 0, held, ninf), max1 = fold(all, c1, c2, 0, held, ninf);
         for (int i0 = NV * 64; i0 < m; i0 += 64 * kSelSmallU) {
             float v[kSelSmallU];
-#pragma unroll
-            for (int u = 0; u < kSelSmallU; ++u) { const int i = i0 + 64 * u + lane; v[u] = vals[i < m ? i : m - 1]; }
-#pragma unroll
-            for (int u = 0; u < kSelSmallU; ++u) {
-                const uint32_t key = key_of(v[u]);
-                const bool in = i0 + 64 * u + lane < m;
-                if (u & 1) gm1 = (in && key > gm1) ? key : gm1;
-                else gm0 = (in && key > gm0) ? key : gm0;
-            }
+            read_on(i0, v);
+            max0 = fold(more, c0, c2, i0, v, max0);
+            max1 = fold(more, c1, c2, i0, v, max1);
         }
+        const uint32_t gm0 = lane < m ? key_of(max0) : 0u, gm1 = lane + 64 < m ? key_of(max1) : 0u;
         uint32_t reach = 0u;
         for (int bit = 31; bit >= 0; --bit) {
             const uint32_t test = reach | (1u << bit);
@@ -1044,7 +1098,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
             uint32_t* c_key = hist;                      // [128] keys that reach it, [128] their columns
             int* c_col = reinterpret_cast<int*>(hist + 128);
             uint32_t count = 0;
-            auto collect = [&](int i, uint32_t key) {
+            const float least = order_value(reach);
+            auto collect = [&](int i, float v) {
+                if (__ballot(!(v < least)) == 0) return;
+                const uint32_t key = key_of(v);
                 const bool in = i < m && key >= reach;
                 const uint64_t b = __ballot(in);
                 const uint32_t pos = count + (uint32_t)__popcll(b & (((uint64_t)1 << lane) - 1));
@@ -1053,18 +1110,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
             };
 #pragma unroll
             for (int e = 0; e < NV; ++e)
-                if (e * 64 < m) collect(e * 64 + lane, keys[e]);
+                if (e * 64 < m) collect(e * 64 + lane, held[e]);
             for (int i0 = NV * 64; i0 < m && count <= 128u; i0 += 64 * kSelSmallU) {
                 float v[kSelSmallU];
-#pragma unroll
-                for (int u = 0; u < kSelSmallU; ++u) { const int i = i0 + 64 * u + lane; v[u] = vals[i < m ? i : m - 1]; }
+                read_on(i0, v);
 #pragma unroll
                 for (int u = 0; u < kSelSmallU; ++u)
-                    if (i0 + 64 * u < m) collect(i0 + 64 * u + lane, key_of(v[u]));
+                    if (i0 + 64 * u < m) collect(i0 + 64 * u + lane, v[u]);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if (count <= 128u) {
+            if (count >= (uint32_t)take && count <= 128u) {
                 const int n_c = (int)count;
                 const bool has0 = lane < n_c, has1 = lane + 64 < n_c;
                 const uint32_t k0 = has0 ? c_key[lane] : 0u, k1 = has1 ? c_key[lane + 64] : 0u;
@@ -1085,6 +1141,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 0 ?
         }
     }
     if (!done) {
+    uint32_t keys[NV];
+#pragma unroll
+    for (int e = 0; e < NV; ++e) keys[e] = key_of(held[e]);
     // radix search for the take-th largest key
     uint32_t prefix = 0, mask = 0, need = (uint32_t)take;
     // Leading bytes that every key of the row shares (scores of one query usually share sign and exponent)

@@ -96,3 +96,11 @@ def test_probes_of_every_kernel_with_exact_ties(L, nprobe, nq, different):
     assert np.all(listed.sum(1) == nprobe), "a cell is listed twice"
     assert np.all(listed[:, :-different] | ~listed[:, different:]), "a copy is listed without the cell that it copies"
     ix.close()
+
+
+@pytest.mark.parametrize("L,nprobe,nq", [
+    (1535, 10, 1025), (1536, 40, 1025), (1537, 10, 1025), (2559, 32, 2049), (2560, 10, 2049), (2561, 40, 2049),      # 8 groups of 64 after 1024 or 2048
+    (2047, 10, 300), (2049, 100, 300), (4097, 10, 300), (6143, 100, 70), (6144, 10, 70), (6145, 100, 70)])           # 8 groups of 256
+def test_probes_at_the_edges_of_full_rounds(L, nprobe, nq):
+    """One column fewer than fills a round of loads, which then tests every column's range, exactly as many, and one more."""
+    test_probes_of_every_kernel_with_exact_ties(L, nprobe, nq, L // 2 + 1)
