@@ -271,7 +271,7 @@ struct SlabWords {
 // groups of 16 to a slab, the column operand, de-quantised block by block into the products that use them, so that LDS serves
 // nothing but the look-ups.  A lane holds a vector's scores against every fourth query, so that a tile of at most four queries, rows 0, 4, 8
 // and 12, stores 64 bytes of each with one instruction.
-// Bound by memory: at 10M x 96 (10,000 queries, 32 probes) the pass reads 0.5 GB and writes 0.3 in 163 us, 5.0 TB/s where a large copy
+// Bound by memory: at 10M x 96 (10,000 queries, 32 probes) the pass reads 0.5 GB and writes 0.3 in 157 us, 5.1 TB/s where a large copy
 // moves 4.8; at 10M x 200 (64 probes, k = 100) 1.14 and 0.47 GB in 420 us, 3.8 TB/s.  With the queries in LDS, 32 x 32 products, a tile to
 // a workgroup and one counter for all tiles 240 and 610 us.
 // RAW: scores are ranking keys of a raw metric.
@@ -478,7 +478,7 @@ __device__ __forceinline__ int slab_max(int v) {
 // The queries, up to NQ tiles of 32, are held in registers, so that LDS serves nothing but the look-ups: a block of 16 coordinates of 32
 // vectors is de-quantised (4 look-ups, 8 LDS clocks shared by four SIMDs) into NQ matrix instructions (32 clocks each).  At 10M x 200 (10,000
 // queries, 64 probes) the matrix pipe is busy half of the cycles, at the 1.8 GHz the chip holds under this load: 740 us, where queries in
-// LDS, read for every product, took 870; at 10M x 96 (32 probes) 243 us, a third of the cycles: the rest goes into finding tiles, and what a
+// LDS, read for every product, took 870; at 10M x 96 (32 probes) 235 us, a third of the cycles: the rest goes into finding tiles, and what a
 // slab and a row tile take besides their products.
 // RAW: scores are ranking keys of a raw metric.
 //

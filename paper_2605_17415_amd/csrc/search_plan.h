@@ -46,8 +46,9 @@ constexpr int kPartMin = 256, kPartMax = 4096;
 struct TileShape { int tq_near, tq, part_near, part; };
 constexpr int list_parts(int size, int part_len) { return size > part_len ? (size + part_len - 1) / part_len : 1; }
 
-// Tiles of the batched passes: enough of them that the last ones to finish matter little (kTilesWanted over the
-// chip's 512 to 1024 resident workgroups).
+// Tiles of the batched passes, which 2048 to 3072 resident wavefronts take: enough of them that the last ones to finish matter little, but a
+// tile reads its queries and costs reads that follow each other, about 4 us.  The whole call with 16384 and 32768, us: 10,000 queries at
+// 10M x 200 1574 and 1503, at 10M x 96 597 and 583, 256 queries at 10M x 200 350 and 357; 65536 were slower than 32768.
 constexpr int64_t kTilesWanted = 32768;
 inline int part_length(int64_t typical_list, int64_t tiles) {
     const int64_t cuts = std::max<int64_t>(1, kTilesWanted / std::max<int64_t>(1, tiles));
