@@ -467,6 +467,10 @@ __device__ __forceinline__ int slab_max(int v) {
     return max((int)r0, (int)r1);
 }
 
+// Integers in the order of floats that are numbers, and back.
+__device__ __forceinline__ int ordered_bits(float f) { return __float_as_int(f) ^ (__float_as_int(f) >> 31 & 0x7FFFFFFF); }
+__device__ __forceinline__ float ordered_float(int i) { return __int_as_float(i ^ (i >> 31 & 0x7FFFFFFF)); }
+
 // ---- threshold pass: the other lists, only scores that can reach the query's threshold kept ------------
 //
 // The vectors are the row operand, so a lane holds one query's scores against 16 vectors and needs that query's
@@ -573,8 +577,9 @@ void k_batch_threshold(BatchScanArgs a) {
             };
 #pragma unroll
             for (int kb = 0; kb < EARLY && kb < KB; ++kb) look(kb);
-            // 2^-20 * norm of vector jl; the largest of the slab, for a raw metric also the range of the vectors' lengths (numbers that
-            // are not negative have the order of their bits)
+            // 2^-20 * norm of vector jl; the largest of the slab (numbers that are not negative have the order of their bits), for a raw
+            // metric also the range of the vectors' lengths.  A length that is no number makes its own score none and leaves the range as
+            // it is: as the slab's largest it would hide the others'.
             const bool in_part = slab * 32 + jl < n_v;
             const float g_own = in_part ? kUnscale * __half2float(__ushort_as_half((uint16_t)f.g16)) : __builtin_nanf("");
             s_g[jl] = g_own;
@@ -582,8 +587,9 @@ void k_batch_threshold(BatchScanArgs a) {
             float x_min = 0.f, x_max = 0.f;
             if (RAW) {
                 s_x[jl] = f.xn;
-                x_min = __int_as_float(~slab_max(in_part ? ~__float_as_int(f.xn) : INT32_MIN));
-                x_max = __int_as_float(slab_max(in_part ? __float_as_int(f.xn) : 0));
+                const bool counts = in_part && f.xn == f.xn;
+                x_min = ordered_float(~slab_max(~ordered_bits(counts ? f.xn : __builtin_inff())));
+                x_max = __int_as_float(slab_max(max(__float_as_int(counts ? f.xn : 0.f), 0)));
             }
             fetch_norm(next, f);
             wave_sync();

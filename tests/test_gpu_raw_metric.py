@@ -148,3 +148,42 @@ def test_raw_metric_on_unit_inputs_is_the_cosine_search():
         ix.close()
     assert (out[0][1] == out[1][1]).mean() > 0.995
     np.testing.assert_allclose(out[1][0], out[0][0], rtol=2e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+@pytest.mark.parametrize("d,b", [(40, 4), (96, 4), (128, 3), (200, 4), (256, 8)])
+def test_a_length_that_is_no_number_hides_no_other_vector(metric, d, b):
+    """One vector of every 32 has a NaN for a length, with either sign: it is no result itself, and the others are found by the
+    batched scan, which looks at the range of the lengths of 32 vectors at a time, as by the streaming scan.
+
+    Tolerance: two evaluations of a score lie at most gamma |z| |C| (2 * 2^-21 + d 2^-24) <= 1e-4 apart for gamma <= 1.2, |C| <= 2, d <= 256;
+    times |q| |x| <= 3 for an inner product, twice that for a distance."""
+    pkg = _pkg()
+    print(f"[NaN lengths] {metric} d={d} b={b}", flush=True)
+    rng = np.random.default_rng(d + b)
+    sizes = [33, 256, 257, 1000, 31, 640]
+    L, n, k, nq = len(sizes), sum(sizes), 10, 40
+    cent = rng.standard_normal((L, d)).astype(np.float32)
+    ix = pkg.Index(d, b, L, rotation_seed=d)
+    ix.set_metric(pkg.binding.METRIC_IP if metric == "ip" else pkg.binding.METRIC_L2)
+    ix.set_coarse(cent / np.linalg.norm(cent, axis=1, keepdims=True))
+    cell = np.repeat(np.arange(L), sizes).astype(np.int32)          # (list order is input order: every slab of a list has one)
+    length = rng.uniform(0.5, 2.0, n).astype(np.float32)
+    none = np.concatenate([np.arange(int(rng.integers(0, min(32, s))), s, 32) + at for s, at in zip(sizes, np.cumsum([0] + sizes))])
+    length[none] = np.array([np.nan, -np.nan], np.float32)[np.arange(len(none)) % 2]
+    rows = (cell, rng.integers(0, 1 << b, (n, d)).astype(np.uint8), rng.uniform(0.2, 1.2, n).astype(np.float16), length)
+    ix.add_encoded_raw(*[torch.from_numpy(v).to(DEV) for v in rows])
+    q = rng.standard_normal((nq, d)).astype(np.float32)
+    q *= 1.5 / np.linalg.norm(q, axis=1, keepdims=True)
+    got = []
+    for mode in (1, 2):
+        ix.set_search_mode(mode)
+        got.append([t.cpu().numpy() for t in ix.search(torch.from_numpy(q).to(DEV), L, k)])
+    assert ix.scan_stats()["queries"] == nq
+    (s1, i1), (s2, i2) = got
+    tol = 3e-4 if metric == "ip" else 6e-4
+    assert (i1 >= 0).all() and not np.isin(i1, none).any() and not np.isin(i2, none).any()
+    np.testing.assert_allclose(s2, s1, rtol=0, atol=tol)
+    for a, c, sa in zip(i1, i2, s1):                                 # a label that only one side has sits at the k-th value
+        assert np.all(np.abs(sa[np.isin(a, c, invert=True)] - sa[-1]) <= 2 * tol)
+    ix.close()
