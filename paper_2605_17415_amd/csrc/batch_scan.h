@@ -82,11 +82,11 @@ struct Table {
         }
     }
     // ... and as operands: both parts (BOTH) or the leading ones.  (hi, lo) of one pair and of the next become (hi, hi) and (lo, lo) by
-    // an exchange, so that four registers in a row are an operand.
+    // an exchange, so that four registers in a row are an operand.  A matrix instruction must not follow a write of its operands by fewer
+    // than two states; the compiler does not look into assembly for that, so the wait belongs to the exchange.
     static __device__ __forceinline__ void operands(Raw& r, half8& hi, half8& lo) {
         if constexpr (PAIR && BOTH) {
-#pragma unroll
-            for (int i = 0; i < 8; i += 4) asm("v_swap_b32 %0, %1" : "+v"(r.w[i + 1]), "+v"(r.w[i + 2]));
+            asm("v_swap_b32 %0, %1\n\tv_swap_b32 %2, %3\n\ts_nop 1" : "+v"(r.w[1]), "+v"(r.w[2]), "+v"(r.w[5]), "+v"(r.w[6]));
             hi = __builtin_bit_cast(half8, make_uint4(r.w[0], r.w[1], r.w[4], r.w[5]));
             lo = __builtin_bit_cast(half8, make_uint4(r.w[2], r.w[3], r.w[6], r.w[7]));
         } else if constexpr (PAIR) {
