@@ -1555,7 +1555,12 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         la.gate = ix->w_gate.as<int32_t>(); la.gate_rows = (int)gate_rows; la.m_stride = 2 * m_stride;
         la.thresh = ba.thresh; la.thresh_stride = k; la.slack = kappa / 16.f; la.redo_cnt = redo_cnt; la.redo_done = redo_cnt + qc;
         la.k = k; la.ids = labels; la.out_vals = sa.out_vals; la.out_i64 = sa.out_i64;
-        HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, 0, 1, st); }));
+        const int64_t window = redo_window(cnt, gate_rows);
+        la.gate_count = (int)window;
+        for (int64_t g0 = 0; g0 < cnt; g0 += window) {
+            la.gate_begin = (int)g0;
+            HIP_TRY(timed(ix, st, P_LIST_SCAN, [&] { return launch_list_scan(la, bits, cnt, 0, 1, st); }));
+        }
     }
     return IVFTQ_OK;
 }

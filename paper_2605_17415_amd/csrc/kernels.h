@@ -273,17 +273,18 @@ struct ListScanArgs {
     // blk_max[q*blk_stride + block_index(cand_off[q][p], p) + b] = order-preserving key of the best score of block b (64
     // vectors) of probe p (null: not wanted)
     uint32_t* blk_max; int64_t blk_stride;
-    // Exact redo (gate not null): instead of all queries the gate[0] listed in gate[1..] are scanned.  A query's scores that reach
+    // Exact redo (gate not null): instead of all queries the entries [gate_begin, gate_begin + gate_count) of the
+    // gate[0] queries listed in gate[1..] are scanned.  A query's scores that reach
     // thresh[q*thresh_stride], less the rounding between the arithmetic of the threshold and this one, go, redo_cnt[q] of them in any order, to the
     // first half of one of gate_rows score rows, their columns (cand_off[q][p] + i) to its second half; half a row has to
     // hold every candidate.  redo_done[q] counts the workgroups that have finished their share; the last one writes the k best, by (score
     // desc, label asc), to the query's result row, as values of the metric.
-    const int32_t* gate; int gate_rows;
+    const int32_t* gate; int gate_begin, gate_count, gate_rows;      // gate_rows: at least gate_count or kRedoWorkgroups (redo_window)
     const float* thresh; int thresh_stride; float slack; int32_t* redo_cnt; int32_t* redo_done;      // slack: the rounding of a sum, per unit of the stored norm
     int k; const int64_t* ids;
     float* out_vals; int64_t* out_i64;
 };
-constexpr int kRedoWorkgroups = 512, kRedoThreads = 1024;   // shared out over the queries a redo launch finds
+constexpr int kRedoThreads = 1024;      // of each of the kRedoWorkgroups workgroups
 // blocks_per_query: workgroups per query (0 = one per probe), each walking its share of the probes; slices:
 // workgroups that share every list.  (Neither matters for a redo.)
 hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int blocks_per_query, int slices, hipStream_t st);

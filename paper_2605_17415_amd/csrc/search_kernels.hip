@@ -244,7 +244,7 @@ __device__ __forceinline__ void redo_select(const ListScanArgs& a, int64_t q, co
 // query's threshold are kept, with their columns, in arbitrary order.  A launch mostly finds no such query or a
 // few, so all of its workgroups are shared out over those it finds: two queries of 64 lists on eight workgroups
 // each took 0.66 ms at 10M x 200, each workgroup walking eight lists alone; spread over the chip 0.02 ms.  The last workgroup to
-// finish its share of a query selects its results.  When there are more such queries than rows, every workgroup takes queries by itself, one
+// finish its share of a query selects its results.  When there are more such queries than workgroups, every workgroup takes queries by itself, one
 // after the other in a row of its own.  (Full-length rows are few, 1500 for 10,000 queries x 64 probes of 10M x 200; with a scan and a
 // selection for every turn of them, most of them empty, the redo of a query or none took 64 us there, and 56 for 32 probes of 10M x 96;
 // one launch takes 28, or 4 when it finds nothing.)
@@ -275,11 +275,11 @@ __global__ __launch_bounds__(REDO ? kRedoThreads : 256) void k_list_scan(ListSca
     int p_first = (int)blockIdx.x, p_step = (int)gridDim.x, slice = (int)blockIdx.z, slices = (int)gridDim.z;
     int64_t buffer = row;              // score row
     if constexpr (REDO) {
-        const int n_redo = a.gate[0], rows = min(a.gate_rows, (int)gridDim.x);
+        const int n_redo = min(a.gate[0] - a.gate_begin, a.gate_count);
         if (n_redo <= 0) return;
-        const int per = n_redo <= rows ? max(1, (int)gridDim.x / n_redo) : 1;       // workgroups per query
+        const int per = max(1, (int)gridDim.x / n_redo);       // workgroups per query
         const int part = (int)blockIdx.x % per;
-        row = buffer = (int)blockIdx.x / per; row_step = min((int)gridDim.x / per, rows); row_end = n_redo;
+        row = buffer = (int)blockIdx.x / per; row_step = (int)gridDim.x / per; row_end = n_redo;
         if (row >= row_step) return;
         p_step = min(per, np);
         slices = per / p_step;
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(REDO ? kRedoThreads : 256) void k_list_scan(ListSca
     }
     for (; row < row_end; row += row_step) {
     if constexpr (!REDO) buffer = row;
-    const int64_t q = REDO ? a.gate[1 + row] : row;
+    const int64_t q = REDO ? a.gate[1 + a.gate_begin + row] : row;
     if (p_first >= np) continue;
     const float qn = metric ? a.qnorm[q] : 1.f;
     float reach = 0.f;
@@ -1579,7 +1579,7 @@ hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int b
     // dimension of the dispatch order: the launch works through the index one slice at a time)
     dim3 grid((unsigned)(blocks_per_query > 0 ? blocks_per_query : a.np), (unsigned)q_count, (unsigned)std::max(1, std::min(slices, 64)));
     if (a.gate) grid = dim3(kRedoWorkgroups);
-    if (a.gate && (a.k < 1 || a.k > kRedoSort)) return hipErrorInvalidValue;
+    if (a.gate && (a.k < 1 || a.k > kRedoSort || a.gate_rows < std::min(a.gate_count, kRedoWorkgroups))) return hipErrorInvalidValue;
     const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(a.gate ? kRedoThreads : 256), lds, st, a); };
 #define IVFTQ_SCAN(BV)                                                                              \
     case BV:                                                                                        \

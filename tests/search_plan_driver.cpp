@@ -53,6 +53,19 @@ int check_rows() {
                     std::printf("limit %lld, %lld queries, rows of %lld: a pass does not fit its room\n", (long long)limit, (long long)a.nq, (long long)a.row);
                     return 1;
                 }
+                // the exact redo of `n` of a pass's queries, launch by launch: as many score rows as there are, and most workgroups at work
+                for (int64_t n : {(int64_t)1, r.gate_rows - 1, r.gate_rows, r.gate_rows + 1, r.queries}) {
+                    const int64_t window = redo_window(r.queries, r.gate_rows);
+                    for (int64_t g0 = 0; a.batched && n <= r.queries && g0 < std::min(n, r.queries); g0 += window) {
+                        const int64_t here = std::min(n - g0, window), per = std::max<int64_t>(1, kRedoWorkgroups / here);
+                        const int64_t in_turn = std::min(here, kRedoWorkgroups / per);
+                        if (in_turn > r.gate_rows || 2 * in_turn * per < kRedoWorkgroups) {
+                            std::printf("%lld queries redone in %lld rows: %lld at a time by %lld workgroups each\n", (long long)n, (long long)r.gate_rows,
+                                        (long long)in_turn, (long long)per);
+                            return 1;
+                        }
+                    }
+                }
                 for (const Call& b : calls) {
                     if (b.nq > a.nq || b.row > a.row || b.prefix > a.prefix || (b.batched && !a.batched)) continue;
                     if (b.r.floats > r.floats || b.r.held > r.held) {

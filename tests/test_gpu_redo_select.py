@@ -147,3 +147,44 @@ def test_few_kept_entries(above):
     odd = np.isin(i1[0], i2[0], invert=True)
     assert np.all(np.abs(s1[0][odd] - s1[0][-1]) <= 2e-4)
     ix.close()
+
+
+@pytest.mark.parametrize("nq,limit", [(600, 4 << 30), (513, 4 << 30), (512, 4 << 30), (300, 1 << 20), (600, 3 << 20), (600, 17 << 20)])
+def test_more_redone_queries_than_rows_or_workgroups(nq, limit):
+    """Every query of the call is redone: in one launch, with as many score rows as queries or workgroups (512), or in launches for as
+    many queries as a small workspace has rows for (30, 91 and 518 rows; the last is one launch again).
+
+    Tolerance: as above."""
+    import paper_2605_17415_amd as pkg
+    print(f"[redo many] nq={nq} limit={limit}", flush=True)
+    rng = np.random.default_rng(nq)
+    d, L, b, k, near, per_list = 64, 16, 4, 10, 1500, 400
+    cent = rng.standard_normal((L, d)).astype(np.float32)
+    cent /= np.linalg.norm(cent, axis=1, keepdims=True)
+    base = rng.standard_normal(d)
+    q = torch.from_numpy((base + 0.02 * rng.standard_normal((nq, d))).astype(np.float32)).to("cuda:0")
+    order = np.argsort(-(cent @ base))
+    pi = np.linalg.qr(rng.standard_normal((d, d)))[0].astype(np.float32)
+    cell = np.concatenate([np.full(near, order[0])] + [np.full(per_list, l) for l in order[1:8]]).astype(np.int32)
+    codes = rng.integers(0, 1 << b, (len(cell), d)).astype(np.uint8)
+    codes[:near] = np.where(pi @ base > 0, 0, (1 << b) - 1)          # the nearest cell's are the furthest from the queries
+    gamma = rng.uniform(0.2, 1.2, len(cell)).astype(np.float16)
+    gamma[:near] = 1.2
+    ix = pkg.Index(d, b, L)
+    ix.set_coarse(cent)
+    ix.set_rotation(pi)
+    ix.add_encoded(*[torch.from_numpy(v).to("cuda:0") for v in (cell, codes, gamma)])
+    ix.set_search_mode(1)
+    s1, i1 = [t.cpu().numpy() for t in ix.search(q, 8, k)]
+    ix.set_search_mode(2)
+    ix.set_workspace_limit(limit)
+    for _ in range(2):
+        s2, i2 = [t.cpu().numpy() for t in ix.search(q, 8, k)]
+        stats = ix.scan_stats()
+        assert stats["redone_exactly"] == stats["queries"] > 0
+        assert (i1 >= 0).all() and (i2 >= 0).all()
+        np.testing.assert_allclose(s2, s1, rtol=0, atol=1e-4)
+        for a, c, sa in zip(i1, i2, s1):
+            assert len(set(c.tolist())) == k
+            assert np.all(np.abs(sa[np.isin(a, c, invert=True)] - sa[-1]) <= 2e-4)
+    ix.close()
