@@ -284,7 +284,7 @@ struct ListScanArgs {
     int k; const int64_t* ids;
     float* out_vals; int64_t* out_i64;
 };
-constexpr int kRedoThreads = 1024;      // of each of the kRedoWorkgroups workgroups
+constexpr int kRedoThreads = 512;      // of each of the kRedoWorkgroups workgroups
 // blocks_per_query: workgroups per query (0 = one per probe), each walking its share of the probes; slices:
 // workgroups that share every list.  (Neither matters for a redo.)
 hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int blocks_per_query, int slices, hipStream_t st);

@@ -247,7 +247,9 @@ __device__ __forceinline__ void redo_select(const ListScanArgs& a, int64_t q, co
 // finish its share of a query selects its results.  When there are more such queries than workgroups, every workgroup takes queries by itself, one
 // after the other in a row of its own.  (Full-length rows are few, 1500 for 10,000 queries x 64 probes of 10M x 200; with a scan and a
 // selection for every turn of them, most of them empty, the redo of a query or none took 64 us there, and 56 for 32 probes of 10M x 96;
-// one launch takes 28, or 4 when it finds nothing.)
+// one launch takes 28, or 4 when it finds nothing.)  Workgroups are small and few enough in registers that the chip holds all of them at once:
+// with half as many of 1024 threads, 71 registers a lane and so one to a compute unit, a query of many was selected while others waited for
+// a place (4000 queries x 32 probes, 400,000 x 16, 176 of them redone: 147 us, now 81; two launches took 79).
 //
 // redo_margin: how far a score s_l + g * sum can lie below its evaluation by the dense pass, from which the threshold
 // comes.  slack bounds the difference of the two sums; it counts for every unit of the norm, which a caller's own
@@ -259,7 +261,7 @@ __device__ __forceinline__ float redo_margin(float slack, float s_l, float g) { 
 // time, and with lanes past a list's end kept for the exchange, lists of few vectors took up to 15 % longer (3008 queries x 44 lists of 4
 // 91 us instead of 79, 5461 x 54 of 17 252 instead of 232).
 template <int B, bool DIRECT, bool REDO, bool BLK>
-__global__ __launch_bounds__(REDO ? kRedoThreads : 256) void k_list_scan(ListScanArgs a) {
+__global__ __launch_bounds__(REDO ? kRedoThreads : 256) __attribute__((amdgpu_waves_per_eu(!REDO ? 1 : B <= 4 || DIRECT ? 8 : B <= 6 ? 6 : 5, 8))) void k_list_scan(ListScanArgs a) {
     constexpr int K = 1 << B, NT = REDO ? kRedoThreads : 256;
     extern __shared__ float lut[];     // [d][K], or z[d] followed by C[K] when DIRECT
     const float* __restrict__ z = a.z;
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(REDO ? kRedoThreads : 256) void k_list_scan(ListSca
     if constexpr (REDO) {
         const int n_redo = min(a.gate[0] - a.gate_begin, a.gate_count);
         if (n_redo <= 0) return;
-        const int per = max(1, (int)gridDim.x / n_redo);       // workgroups per query
+        const int per = min(512, max(1, (int)gridDim.x / n_redo));       // workgroups per query (each costs its counter 14 ns)
         const int part = (int)blockIdx.x % per;
         row = buffer = (int)blockIdx.x / per; row_step = (int)gridDim.x / per; row_end = n_redo;
         if (row >= row_step) return;

@@ -42,9 +42,9 @@ inline SearchRows search_rows(bool batched, int64_t nq, int64_t row, int64_t pre
 // selected.  Where the rows are as many as the workgroups, every workgroup has one and one launch looks after all `queries` of a
 // pass, however many of them turn out to be redone.  With fewer, workgroups without a row would stand idle as soon as more queries are
 // redone than there are rows, so there is a launch for as many queries as there are rows and all workgroups share each of them (40 queries
-// redone in two rows, 64 lists of 20,000: 42.5 ms by one launch, 1.17 by launches for two queries each; an empty launch
+// redone in two rows, 64 lists of 20,000: 42.5 ms by one launch, 0.98 by launches for two queries each; an empty launch
 // takes 2 us).
-constexpr int kRedoWorkgroups = 512;
+constexpr int kRedoWorkgroups = 1024;
 constexpr int64_t redo_window(int64_t queries, int64_t gate_rows) {
     return gate_rows >= std::min<int64_t>(kRedoWorkgroups, queries) ? queries : gate_rows;
 }

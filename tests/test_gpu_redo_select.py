@@ -149,10 +149,10 @@ def test_few_kept_entries(above):
     ix.close()
 
 
-@pytest.mark.parametrize("nq,limit", [(600, 4 << 30), (513, 4 << 30), (512, 4 << 30), (300, 1 << 20), (600, 3 << 20), (600, 17 << 20)])
+@pytest.mark.parametrize("nq,limit", [(1200, 4 << 30), (1025, 4 << 30), (1024, 4 << 30), (513, 4 << 30), (300, 1 << 20), (600, 3 << 20), (1200, 36 << 20)])
 def test_more_redone_queries_than_rows_or_workgroups(nq, limit):
-    """Every query of the call is redone: in one launch, with as many score rows as queries or workgroups (512), or in launches for as
-    many queries as a small workspace has rows for (30, 91 and 518 rows; the last is one launch again).
+    """Every query of the call is redone: in one launch, with as many score rows as queries or workgroups (1024), or in launches for as
+    many queries as a small workspace has rows for (30, 91 and 1097 rows; the last is one launch again).
 
     Tolerance: as above."""
     import paper_2605_17415_amd as pkg
