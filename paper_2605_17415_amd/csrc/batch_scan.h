@@ -161,17 +161,14 @@ struct TileQueue {
         end = a.p.totals[a.dense ? 1 : 2];
         q = (int)blockIdx.x % kTileQueues;
         counter = a.p.totals + 32 + ((a.dense ? 0 : kTileQueues) + q) * 32;
-        const int servers = ((int)gridDim.x - q + kTileQueues - 1) / kTileQueues * waves;        // wavefronts
+        const int servers = queue_servers((int)gridDim.x, q) * waves;        // wavefronts
         const int me = (int)blockIdx.x / kTileQueues * waves + wave;
         given = 2 * servers;
-        next = nth(me);
+        next = queue_tile(q, me);
         asked = servers + me - given;    // (the second tile by number, as if asked for)
         if (next < end) known[0] = bucket_of[next];
         advance();
     }
-    // the j-th tile of the queue: one of each kTileQueues tiles, another one each time (the parts of a list, of which the last is the
-    // shortest, follow each other)
-    __device__ __forceinline__ int nth(int j) const { return j * kTileQueues + (q + 5 * j) % kTileQueues; }
     // (through registers of the lanes' own, or the compiler waits for the answers where they are asked for)
     __device__ __forceinline__ void ask() {
         int lane = (int)(threadIdx.x & 63);
@@ -202,7 +199,7 @@ struct TileQueue {
         while (phase < 2 && next < end) step();
         tile = next;
         t = tn;
-        next = nth(__builtin_amdgcn_readfirstlane(asked) + given);
+        next = queue_tile(q, __builtin_amdgcn_readfirstlane(asked) + given);
         phase = 2;
     }
     // pair of query e of the tile (some other one beyond its last); before `proceed`
@@ -719,7 +716,7 @@ hipError_t run_batch(const BatchScanArgs& a, hipStream_t st) {
     const auto go = [&](ChipFill& own, auto kernel, int occ, size_t lds) -> hipError_t {
         unsigned wgs = 0;
         const hipError_t e = own.get(reinterpret_cast<const void*>(kernel), 64 * waves_of(occ), lds, &wgs);
-        if (e == hipSuccess) hipLaunchKernelGGL(kernel, dim3(wgs), dim3(64 * waves_of(occ)), lds, st, a);
+        if (e == hipSuccess) hipLaunchKernelGGL(kernel, dim3((unsigned)tile_workgroups((int)wgs)), dim3(64 * waves_of(occ)), lds, st, a);
         return e;
     };
     constexpr int OCC = Form::OCC, NQ = Form::NQ;

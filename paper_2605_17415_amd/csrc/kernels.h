@@ -373,10 +373,9 @@ constexpr int batch_tile(int d, int b) { return 32 * batch_query_tiles(batch_dp(
 // bucket L + l the pairs (q, p >= first[q]) (the threshold pass).  pairs[pair_off[b] ...] holds the count[b] flat pair
 // numbers q*np + p of bucket b.  Its workgroup tiles, every tq_near or tq of its queries times the list_parts of its
 // list, follow each other in its pass's array (tile_near or tile_late), whose entries name the bucket.
-// Updates of one counter from all over the chip follow each other at about 14 ns, so the tiles of a pass are dealt out to kTileQueues
-// queues, tile t to queue t % kTileQueues, each served by the workgroups of its number (on one of the chip's eight parts).
+// Each of the kTileQueues queues that the tiles of a pass are dealt out to has a counter.
 constexpr int kPairRecord = 8;       // words of a bucket's record
-constexpr int kTileQueues = 16, kPairTotals = 32 + 2 * kTileQueues * 32;
+constexpr int kPairTotals = 32 + 2 * kTileQueues * 32;
 struct PairTable {
     // cleared with the coarse scores: [2L] pairs of a bucket, then kPairTotals words: totals (pairs, tiles of the dense pass, of
     // the threshold pass) and from word 32 on the next tiles of either pass, kTileQueues counters a cache line apart

@@ -70,6 +70,16 @@ inline TileShape tile_shape(int64_t ntotal, int nlist, int64_t pairs, int tq = k
     return {kBatchTileNear, tq, part_length(typical, lists), part_length(typical, lists + pairs / tq)};
 }
 
+// The tiles of a pass are dealt out to kTileQueues queues, each served by the workgroups of its number: updates of one counter from all over
+// the chip follow each other at about 14 ns.  A launch has as many workgroups as the chip holds (`resident`), and one for every queue
+// where that were fewer.
+constexpr int kTileQueues = 16;
+constexpr int tile_workgroups(int resident) { return std::max(resident, kTileQueues); }
+constexpr int queue_servers(int workgroups, int queue) { return (workgroups - queue + kTileQueues - 1) / kTileQueues; }
+// the j-th tile of a queue: one of each kTileQueues tiles, another one each time (the parts of a list, of which the last is the
+// shortest, follow each other)
+constexpr int queue_tile(int queue, int j) { return j * kTileQueues + (queue + 5 * j) % kTileQueues; }
+
 // Entries that hold the tiles of a pass whose tiles take tq queries each, whatever the part length.  A list that meets c
 // queries has at most 1 + c / tq tiles for each of its parts; c adds up to `pairs` over the lists and is at most
 // `queries` in each.  list_room: what the first tile of every list takes.

@@ -82,6 +82,27 @@ int check_rows() {
     return 0;
 }
 
+// The tiles of a pass: every one in one queue's order once, and every queue with a workgroup.
+int check_queues() {
+    for (int resident : {1, 2, 8, 15, 16, 17, 20, 64, 256, 512})
+        for (int q = 0; q < kTileQueues; ++q)
+            if (queue_servers(tile_workgroups(resident), q) < 1) {
+                std::printf("queue %d of a chip that holds %d workgroups is served by none\n", q, resident);
+                return 1;
+            }
+    for (int tiles : {0, 1, 15, 16, 17, 1000, 32768}) {
+        std::vector<int> seen(tiles, 0);
+        for (int q = 0; q < kTileQueues; ++q)
+            for (int j = 0; queue_tile(q, j) < tiles; ++j) ++seen[queue_tile(q, j)];
+        for (int t = 0; t < tiles; ++t)
+            if (seen[t] != 1) {
+                std::printf("tile %d of %d is taken %d times\n", t, tiles, seen[t]);
+                return 1;
+            }
+    }
+    return 0;
+}
+
 }  // namespace
 
 int main() {
@@ -137,5 +158,5 @@ int main() {
                 }
             }
     }
-    return check_rows();
+    return check_queues() ? 1 : check_rows();
 }

@@ -7,6 +7,8 @@ with shorter rows has longer passes, and one with as many bytes may round to mor
 The exact redo's launches are checked to find a score row for every query that they share out at a time, and enough queries or
 workgroups a query to have work for at least half of the workgroups.
 
+Tiles are dealt out to queues: every tile to one, and every queue has a workgroup, on a chip that holds fewer workgroups than queues too.
+
 The grid holds the calls at which cutting lists more finely for fewer pairs would need more tiles than the larger call has
 (10M vectors, 32 probes: 387 | 388 queries over 4000 lists, 195 | 196 over 2000) and an index with one hot list."""
 import os
