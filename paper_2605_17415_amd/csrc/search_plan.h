@@ -65,7 +65,7 @@ inline int part_length(int64_t typical_list, int64_t tiles) {
     const int64_t cuts = std::max<int64_t>(1, kTilesWanted / std::max<int64_t>(1, tiles));
     return (int)std::min<int64_t>(kPartMax, std::max<int64_t>(kPartMin, (typical_list / cuts + 63) / 64 * 64));
 }
-inline TileShape tile_shape(int64_t ntotal, int nlist, int64_t pairs, int tq = kBatchTile) {
+inline TileShape tile_shape(int64_t ntotal, int nlist, int64_t pairs, int tq) {
     const int64_t typical = std::max<int64_t>(1, ntotal / nlist), lists = std::min<int64_t>(nlist, pairs);
     return {kBatchTileNear, tq, part_length(typical, lists), part_length(typical, lists + pairs / tq)};
 }

@@ -136,7 +136,8 @@ int main() {
             for (int p : np) {
                 const int64_t pairs = (int64_t)q * p;
                 if (p > ix.nlist || pairs > 400'000) continue;
-                const TileShape shape = tile_shape(ix.total, ix.nlist, pairs);
+                for (int width : {64, 96, 128}) {                   // queries of a tile of the threshold pass, by its form
+                const TileShape shape = tile_shape(ix.total, ix.nlist, pairs, width);
                 if (shape.part_near < kPartMin || shape.part < kPartMin || shape.part_near % 64 || shape.part % 64) {
                     std::printf("%s nlist=%d: part lengths %d and %d\n", ix.kind, ix.nlist, shape.part_near, shape.part);
                     return 1;
@@ -148,13 +149,16 @@ int main() {
                     if (how == 2) for (int i = 0; i < p; ++i) meets[order[i]] = q;
                     for (int near = 0; near < 2; ++near) {
                         const int tq = near ? shape.tq_near : shape.tq;
-                        const int64_t made = tiles_of(size, meets, tq, near ? shape.part_near : shape.part), held = tile_room(room, q, pairs, tq);
+                        // (the room is counted by the fewest queries that any form takes)
+                        const int64_t made = tiles_of(size, meets, tq, near ? shape.part_near : shape.part);
+                        const int64_t held = tile_room(room, q, pairs, near ? kBatchTileNear : kBatchTile);
                         if (made > held) {
-                            std::printf("%s nlist=%d: %d queries x %d probes make %lld tiles, room for %lld\n", ix.kind, ix.nlist, q, p,
-                                        (long long)made, (long long)held);
+                            std::printf("%s nlist=%d: %d queries x %d probes make %lld tiles of %d, room for %lld\n", ix.kind, ix.nlist, q, p,
+                                        (long long)made, tq, (long long)held);
                             return 1;
                         }
                     }
+                }
                 }
             }
     }
