@@ -704,9 +704,9 @@ void k_batch_threshold(BatchScanArgs a) {
 
 template <int DP, int B>
 struct BatchForm {
-    static constexpr int KB = DP / 16, NW = (B == 2 || B == 4) ? 1 : 2;
     static constexpr int NQ = batch_query_tiles(DP, B);
     static constexpr int OCC = 2;
+    static_assert(32 * NQ >= kBatchTile, "the room for tiles is counted by the fewest queries of one");
 };
 
 template <int DP, int B>

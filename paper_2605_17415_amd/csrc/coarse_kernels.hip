@@ -310,14 +310,7 @@ constexpr size_t screen_lds_bytes(bool bias) {
     return (size_t)2 * screen_nt<DP>() * 32 * (CoarseCfg<DP>::LDH * sizeof(uint16_t) + (bias ? sizeof(float) : 0));
 }
 
-// max(a, b, c) and the middle of (a, b, c) as single instructions.  Written as instructions because the
-// scores carry a tag in their low bits (below) and are never NaN, so the quieting that the compiler puts
-// in front of a float maximum of an unknown bit pattern would be one wasted operation per score.
-__device__ __forceinline__ float max3_raw(float a, float b, float c) {
-    float o;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(o) : "v"(a), "v"(b), "v"(c));
-    return o;
-}
+// (The scores carry a tag in their low bits and are never NaN: max3 of kernels.h, and the middle of three as the compiler's builtin.)
 
 // The 16 scores of tile position t that a lane holds, four at a time.  The position (t, q) replaces
 // the low 6 bits of the float32 pattern (a change below 2^-17 of the score's size), so that maxima and
@@ -333,10 +326,10 @@ __device__ __forceinline__ float max3_raw(float a, float b, float c) {
                 if (MASKED) v[i] = (c0 + t * 32 + 2 * q + 4 * half + i < L) ? v[i] : kScreenNone;           \
             }                                                                                               \
             const float m0 = __builtin_amdgcn_fmed3f(best[r], v[0], v[1]);                                  \
-            const float b1 = max3_raw(best[r], v[0], v[1]);                                                 \
+            const float b1 = max3(best[r], v[0], v[1]);                                                 \
             const float m1 = __builtin_amdgcn_fmed3f(b1, v[2], v[3]);                                       \
-            best[r] = max3_raw(b1, v[2], v[3]);                                                             \
-            second[r] = max3_raw(second[r], m0, m1);                                                        \
+            best[r] = max3(b1, v[2], v[3]);                                                             \
+            second[r] = max3(second[r], m0, m1);                                                        \
         }                                                                                                   \
     }
 

@@ -288,6 +288,13 @@ constexpr int kRedoThreads = 512;      // of each of the kRedoWorkgroups workgro
 // blocks_per_query: workgroups per query (0 = one per probe), each walking its share of the probes; slices:
 // workgroups that share every list.  (Neither matters for a redo.)
 hipError_t launch_list_scan(const ListScanArgs& a, int b, int64_t q_count, int blocks_per_query, int slices, hipStream_t st);
+// The largest of three values in one instruction; what is no number has no part in it.  Written as one because the compiler quiets every operand of a
+// float maximum whose bits it knows nothing of first, an operation a value.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 // metric 0: the score is the estimate s^ of <q~, x~> itself.  Raw metrics (the store keeps |x|, qnorm[q] = |q|):
 // the scan writes a key that ranks like the metric and whatever writes a call's results turns the selected keys into values:
 //   metric 1 (inner product): key = |x| s^,                 value = |q| key            (descending)

@@ -509,12 +509,6 @@ constexpr int kSelOffs = 256;   // most probes whose offsets are staged in LDS
 // at 10M x 96: k best of the nearest lists 68 -> 56 us, 32 of 4096 cells 61.5 -> 59.5, the call 600 -> 583; one query at 1M x 128 25.9 -> 25.5).
 // Values that are no number have the lowest key and no part in the comparison of floats, but that a share of nothing else counts as -inf: such
 // a bound may be reached by fewer keys than winners are wanted, and then the radix search takes over.
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
 // A lower bound of the take-th largest of the 256 keys at `maxima`, less than 2^10 below it (0 when there are fewer).  For
 // few winners of the 64 keys that are the largest of four each, which is another such bound and hardly lower (30 keys
 // of a row dealt out reach it for 24 winners instead of 25) at a quarter of the steps.
