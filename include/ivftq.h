@@ -270,7 +270,8 @@ int64_t ivftq_index_bytes(const ivftq_index* index);
 /* Scan strategy of ivftq_search: 0 = default (the query-batched matrix-core scan when (d, b) is one
  * of its shapes -- d >= 16 with 3, 4, 5 or 8 stored bits, d > 32 with 2 --, nprobe > 1 and the call is large enough for it to pay: the bytes a
  * per-query stream of the probed lists would read exceed 2.3 times the part of the index the call
- * touches plus 0.25 GB, a few hundred queries on a 10M-vector index; else the streaming scan, whose
+ * touches plus 0.25 GB, or its look-ups of coordinates are estimated to take 110 us longer than those of
+ * the touched part, a hundred to a few hundred queries on a 10M-vector index; else the streaming scan, whose
  * shorter chain of kernels is faster for smaller calls), 1 = streaming scan only (a row of workgroups
  * per query walks its probed lists), 2 = the batched scan wherever the shape allows, whatever the
  * size of the call.  Results obey the same contract in every mode. */

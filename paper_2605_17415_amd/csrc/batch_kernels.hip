@@ -5,7 +5,7 @@
 // In a large query batch each inverted list is probed by many queries (Q * nprobe / nlist of them
 // on average), so the scan of one list against all of its queries is a dense contraction:
 // [vectors of the list] x [d] times [d] x [queries probing the list].  The (query, probe) pairs are
-// regrouped by list here, a workgroup of the scan takes one list and a tile of its queries, scores that reach the
+// regrouped by list here, a wavefront of the scan takes a part of one list and a tile of its queries, scores that reach the
 // query's threshold (the k-th best score of its nearest lists, found beforehand) land in a short per-query
 // candidate list, and the merge puts those and the nearest lists' k best together.
 #include <hip/hip_fp16.h>

@@ -2,7 +2,7 @@
 // translation units batch_scan_b*.hip, which compile the widths of one bit count each.
 //
 // A wavefront takes a part of one list and up to TQ of the queries that probe it.  The rotated queries are one MFMA operand and stay in
-// registers; the vectors, 32 at a time, are the other, de-quantised through a table in LDS block by block into the products that use
+// registers (but for what some wide forms spill, see batch_query_tiles); the vectors, 32 at a time, are the other, de-quantised through a table in LDS block by block into the products that use
 // them.
 //
 // Arithmetic: both operands are used in split float16 form, 1024*v = hi + lo with hi = fp16(1024 v)
@@ -142,8 +142,10 @@ struct BatchTile {
 // by its number, the others from the counter of its workgroup's queue: tiles differ in work by the sizes of the lists and the queries that
 // meet there.  No wavefront waits for another (with a tile to a workgroup, whose wavefronts met at a barrier and waited for the counter,
 // half of all wavefront cycles went by waiting).  Finding a tile's bucket, record, pairs and queries is a chain of five dependent reads of
-// 0.7 us and more; all but the last are made while the tiles before it are worked on: its number is asked for two tiles ahead, its bucket
-// one tile ahead, and record and pairs between the slabs of the tile before.
+// 0.7 us and more; most are made while the tiles before it are worked on: its number is asked for two tiles ahead, its bucket
+// one tile ahead, the record after slab 2 of the tile before and the pairs after its slab 8.  A tile of the shortest part, 256 vectors, has slabs 0 to 7,
+// so there the pairs are read between the tiles.  What is asked for comes behind the words of vectors on their way, so the wait for it is one for
+// those too.
 // TQ: queries of a tile.
 template <int TQ>
 struct TileQueue {
@@ -178,7 +180,7 @@ struct TileQueue {
             known[0] = bucket_of[(next < end ? next : 0) + lane];
         }
     }
-    // between slabs; the answers are used some slabs later: they come behind the words on their way, for which the wait would be too
+    // between slabs
     __device__ __forceinline__ void between(int slab) {
         if (slab == 2 || slab == 8) step();
     }
@@ -268,8 +270,8 @@ struct SlabWords {
 // groups of 16 to a slab, the column operand, de-quantised block by block into the products that use them, so that LDS serves
 // nothing but the look-ups.  A lane holds a vector's scores against every fourth query, so that a tile of at most four queries, rows 0, 4, 8
 // and 12, stores 64 bytes of each with one instruction.
-// Bound by memory: at 10M x 96 (10,000 queries, 32 probes) the pass reads 0.5 GB and writes 0.3 in 157 us, 5.1 TB/s where a large copy
-// moves 4.8; at 10M x 200 (64 probes, k = 100) 1.14 and 0.47 GB in 420 us, 3.8 TB/s.  With the queries in LDS, 32 x 32 products, a tile to
+// Bound by memory: at 10M x 96 (10,000 queries, 32 probes) the pass reads 0.52 GB and writes 0.12 in 147 to 150 us, 4.3 TB/s where a large copy
+// moves 4.8; at 10M x 200 (64 probes, k = 100) 1.48 and 0.54 GB in 402 to 409 us, 5.0 TB/s.  With the queries in LDS, 32 x 32 products, a tile to
 // a workgroup and one counter for all tiles 240 and 610 us.
 // RAW: scores are ranking keys of a raw metric.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -299,8 +301,9 @@ struct GroupWords {
     }
 };
 
-// Registers that the dense pass takes for n row tiles of queries (operands, accumulators, places), blocks in flight, and words of `ahead`
-// slabs.
+// About the registers that the dense pass takes for n row tiles of queries (operands, accumulators, places), blocks in flight, and words of
+// `ahead` slabs.  (64 coordinates of other than 8 bits: 64 bytes of looked-up operands a lane go through scratch memory in all but two forms; 256 of
+// 8 bits spill 27 registers, 65 with a raw metric, 3, 5 and other 8-bit forms up to 15.)
 constexpr int dense_registers(int dp, int b, bool raw, int n, int ahead) {
     const int kb = (dp + 31) / 32, nw = b == 2 || b == 4 ? 1 : 2;
     return n * (8 * kb + 8 + (raw ? 16 : 12)) + 32 + ahead * (2 * kb * nw + (raw ? 4 : 2)) + 38;
@@ -341,6 +344,7 @@ void k_batch_dense(BatchScanArgs a) {
     auto scan_tile = [&](auto tiles) {
         constexpr int N = decltype(tiles)::value;
         // Words and norms of a slab on their way: two slabs ahead of the products, or one where the registers do not reach for two.
+        // (After every AHEAD slabs the compiler waits for all that is on its way, to move the last norm to another register.)
         constexpr int AHEAD = dense_registers(DP, B, RAW, N, 2) <= (OCC == 3 ? 168 : 256) ? 2 : 1;
         struct Ahead { uint32_t w[2][KB][NW], g16[2]; float xn[2]; } ahead[AHEAD];
         auto fetch_norms = [&](int slab, Ahead& f) {
@@ -478,14 +482,13 @@ __device__ __forceinline__ float ordered_float(int i) { return __int_as_float(i 
 //
 // The queries, up to NQ tiles of 32, are held in registers, so that LDS serves nothing but the look-ups: a block of 16 coordinates of 32
 // vectors is de-quantised (4 look-ups, 8 LDS clocks shared by four SIMDs) into NQ matrix instructions (32 clocks each).  At 10M x 200 (10,000
-// queries, 64 probes) the matrix pipe is busy half of the cycles, at the 1.8 GHz the chip holds under this load: 740 us, where queries in
-// LDS, read for every product, took 870; at 10M x 96 (32 probes) 235 us, a third of the cycles: the rest goes into finding tiles, and what a
+// queries, 64 probes) the matrix pipe is busy half of the cycles, at the 1.8 GHz the chip holds under this load: 765 to 795 us, where queries in
+// LDS, read for every product, took 870; at 10M x 96 (32 probes) 235 to 240 us, a third of the cycles: the rest goes into finding tiles, and what a
 // slab and a row tile take besides their products.
 // RAW: scores are ranking keys of a raw metric.
 //
-// A candidate is appended to its query's list with an update of the query's counter.  Updates of one counter from all over
-// the chip follow each other at about 0.2 us, which is what the pass takes where candidates are many and queries
-// few.  So the candidates of a tile are held back in LDS and a counter is updated once per tile (rows without clusters, 1M x
+// A candidate is appended to its query's list with an update of the query's counter, whose answer its stores wait for.  Where candidates
+// are many and queries few, such updates are what the pass takes.  So the candidates of a tile are held back in LDS and a counter is updated once per tile (rows without clusters, 1M x
 // 128, inner product, 100 queries of 64 probes, k = 100, up to 1172 candidates a query: 203 -> 104 us); what does not fit is
 // appended at once.
 template <int DP, int B, int NQ, int OCC>

@@ -368,8 +368,11 @@ bool batch_covers(int d, int b);
 // of 32), at least 64, except that 193 ... 208 coordinates take 13 blocks of 16 rather than 14 (d = 200: a
 // fourteenth less to de-quantise and multiply).
 constexpr int batch_dp(int d) { return (d > 192 && d <= 208) ? 208 : d <= 64 ? 64 : (d + 31) / 32 * 32; }
-// Row tiles of 32 queries that a wavefront of the threshold pass holds in registers: up to four, as many as fit beside their accumulators and
-// a slab's words.
+// Row tiles of 32 queries that a wavefront of the threshold pass holds in registers: up to four, as many as about fit beside their
+// accumulators and a slab's words.  Not all of them fit: of 256 registers, 192 coordinates spill 9 to 17, 208 with 2 and 4 bits 16 and 13
+// (with 3, 5 and 8, which have two row tiles, none), 224 with 3, 5 and 8 and 256 with 8 bits 4 to 9, and raw metrics, which keep the
+// range of the lengths too, up to 26 from 160 coordinates on.  With 208 coordinates of 4 bits one operand is read back in every
+// slab; two row tiles, without spills, are slower all the same (10,000 queries at 10M x 200: pass 794 us instead of 766).
 constexpr int batch_query_tiles(int dp, int b) {
     const int kb = dp / 16, words = kb * (b == 2 || b == 4 ? 1 : 2);
     return 4 * (4 * kb + 16) + 2 * words <= 180 ? 4 : 3 * 4 * kb + words <= 180 ? 3 : 2;
@@ -378,7 +381,7 @@ constexpr int batch_tile(int d, int b) { return 32 * batch_query_tiles(batch_dp(
 
 // The (query, probe) pairs bucketed by list: bucket l holds the pairs (q, p < first[q]) of list l (the dense pass),
 // bucket L + l the pairs (q, p >= first[q]) (the threshold pass).  pairs[pair_off[b] ...] holds the count[b] flat pair
-// numbers q*np + p of bucket b.  Its workgroup tiles, every tq_near or tq of its queries times the list_parts of its
+// numbers q*np + p of bucket b.  Its tiles, every tq_near or tq of its queries times the list_parts of its
 // list, follow each other in its pass's array (tile_near or tile_late), whose entries name the bucket.
 // Each of the kTileQueues queues that the tiles of a pass are dealt out to has a counter.
 constexpr int kPairRecord = 8;       // words of a bucket's record

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(1024) void k_segment_hist(const int32_t* __restrict
 // segments into 64 parts (a sixteen-lane group per part) of at most kMaxSegments / 64, which a thread keeps in
 // registers, all its loads in flight; a launch has L/16 workgroups.  batch_count may be host memory that the device can
 // write, and flag a word that goes behind the counts there: the host waits for the kernel and nothing else.  (With two copies here, which are
-// launches of their own, and one more for the new sizes after the encoding, 20,000 rows built and searched took 126 us, 98 now.)
+// launches of their own, and one more for the new sizes after the encoding, 20,000 rows built and searched took 131 to 135 us, 97 to 103 now, on another machine 110 and 102.)
 __global__ __launch_bounds__(1024) void k_segment_scan(uint32_t* __restrict__ seg_hist, int nseg, int L,
                                                        uint32_t* __restrict__ batch_count, const int* __restrict__ flag, int* __restrict__ flag_out) {
     if (flag && blockIdx.x == 0 && threadIdx.x == 0) *flag_out = *flag;

@@ -460,8 +460,11 @@ __global__ __launch_bounds__(REDO ? kRedoThreads : 256) __attribute__((amdgpu_wa
     }
     if constexpr (REDO) {
         // What every workgroup kept has to be there for the one that comes last, maybe on another part of the chip with an L2 cache
-        // of its own: the stores went through to memory (agent scope), each wavefront waits for its own, then one thread
-        // counts for the workgroup.  (With a fence instead, which writes the L2 cache back, by every wavefront: 160 us a redo.)
+        // of its own.  The language orders that by a release alone, which here means writing the L2 cache back, although nothing of this
+        // lies in it: stores of agent scope go through it to memory, and a wavefront's wait ends when its own are there.  So each wavefront
+        // waits for its stores, in a statement that the compiler moves no store across, the workgroup meets, and one thread counts for
+        // it.  That holds for gfx950, which this is written for.  (A fence by every wavefront: 160 us a redo; a release by the counting
+        // thread alone: 37 instead of 28.5 for few queries at 10M x 96, the call 3 % slower, 93 instead of 82 for 176 of 4000.)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         unsigned char* lds = reinterpret_cast<unsigned char*>(lut);

@@ -1,4 +1,4 @@
-// How a search is cut into passes and a batched one into workgroup tiles, and how much room that takes.  Plain C++, no
+// How a search is cut into passes and a batched one into tiles, and how much room that takes.  Plain C++, no
 // device code.
 //
 // A recorded graph keeps the addresses of the workspace, which moves only when a call needs more of it.  So what a call is
@@ -49,7 +49,7 @@ constexpr int64_t redo_window(int64_t queries, int64_t gate_rows) {
     return gate_rows >= std::min<int64_t>(kRedoWorkgroups, queries) ? queries : gate_rows;
 }
 
-// Queries per workgroup tile: of the dense pass, and of the threshold pass the fewest that any form of it takes (which the room is
+// Queries per tile, which is a wavefront's work: of the dense pass, and of the threshold pass the fewest that any form of it takes (which the room is
 // counted by: batch_tile of kernels.h says how many a form takes).
 constexpr int kBatchTile = 64, kBatchTileNear = 32;
 // Lists of more than part_len vectors are cut into nearly equal parts of at most part_len, each a tile of its own.
