@@ -83,8 +83,9 @@ struct Table {
     }
     // ... and as operands: both parts (BOTH) or the leading ones.  (hi, lo) of one pair and of the next become (hi, hi) and (lo, lo) by
     // an exchange, so that four registers in a row are an operand.  A matrix instruction must not follow a write of its operands by fewer
-    // than two states; the compiler does not look into assembly for that, so the wait belongs to the exchange.
-    static __device__ __forceinline__ void operands(Raw& r, half8& hi, half8& lo) {
+    // than two states; the compiler does not look into assembly for that, so the wait belongs to the exchange.  (By value: with the entries of
+    // a block that is looked up once in a slab, exchanged in place through a reference, the compiler kept them in scratch memory.)
+    static __device__ __forceinline__ void operands(Raw r, half8& hi, half8& lo) {
         if constexpr (PAIR && BOTH) {
             asm("v_swap_b32 %0, %1\n\tv_swap_b32 %2, %3\n\ts_nop 1" : "+v"(r.w[1]), "+v"(r.w[2]), "+v"(r.w[5]), "+v"(r.w[6]));
             hi = __builtin_bit_cast(half8, make_uint4(r.w[0], r.w[1], r.w[4], r.w[5]));
@@ -302,8 +303,7 @@ struct GroupWords {
 };
 
 // About the registers that the dense pass takes for n row tiles of queries (operands, accumulators, places), blocks in flight, and words of
-// `ahead` slabs.  (64 coordinates of other than 8 bits: 64 bytes of looked-up operands a lane go through scratch memory in all but two forms; 256 of
-// 8 bits spill 27 registers, 65 with a raw metric, 3, 5 and other 8-bit forms up to 15.)
+// `ahead` slabs.  (256 coordinates of 8 bits spill 27 registers, 65 with a raw metric, 3, 5 and other 8-bit forms up to 15.)
 constexpr int dense_registers(int dp, int b, bool raw, int n, int ahead) {
     const int kb = (dp + 31) / 32, nw = b == 2 || b == 4 ? 1 : 2;
     return n * (8 * kb + 8 + (raw ? 16 : 12)) + 32 + ahead * (2 * kb * nw + (raw ? 4 : 2)) + 38;
