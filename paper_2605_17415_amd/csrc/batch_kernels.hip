@@ -34,12 +34,18 @@ __global__ void k_pair_count(const int32_t* __restrict__ probe, const int32_t* _
 // Every bucket gets a range of the pair array (pair_off) and of its pass's tile array, its record, and
 // cursor[b] = 0.  One thread per bucket; a workgroup puts its buckets together with a scan and takes its ranges from
 // the totals with one atomic each, so the ranges of different workgroups lie in no particular order, which nothing
-// depends on (in bucket order, by one workgroup: 0.017 ms for 8192 buckets, the chain of its loads).
+// depends on (in bucket order, by one workgroup: 0.017 ms for 8192 buckets, the chain of its loads).  A thread writes the first kOwnTiles
+// tiles of its bucket, wavefronts the rest: a few long lists that meet many queries have a thousand and more each (33 lists, 9699
+// queries x 5 probes: 44 us by a thread each, 11 so).
+constexpr uint32_t kOwnTiles = 16;
 __global__ __launch_bounds__(256) void k_pair_ranges(const int32_t* __restrict__ list_size, const int64_t* __restrict__ list_off, int nb,
                                                      int L, TileShape shape, PairTable p) {
     __shared__ uint32_t part[4][3];
     __shared__ int32_t start[3];
+    __shared__ int4 many[256];
+    __shared__ int n_many;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = (int)blockIdx.x * 256 + tid;
+    if (tid == 0) n_many = 0;
     const bool in = b < nb, near = b < L;
     const uint32_t n = in ? p.count[b] : 0u;
     const int size = in ? list_size[near ? b : b - L] : 0;
@@ -68,14 +74,23 @@ __global__ __launch_bounds__(256) void k_pair_ranges(const int32_t* __restrict__
         at[i] = start[i] + (int32_t)(incl[i] - own[i]);
         for (int w2 = 0; w2 < wave; ++w2) at[i] += (int32_t)part[w2][i];
     }
-    if (!in) return;
-    p.pair_off[b] = at[0];
     const int32_t t0 = near ? at[1] : at[2];
-    int4* rec = reinterpret_cast<int4*>(p.record + (int64_t)b * kPairRecord);
-    rec[0] = make_int4(size, t0, (int)n, at[0]);
-    rec[1] = make_int4((int)(uint32_t)slot, (int)(slot >> 32), 0, 0);
     int32_t* to = near ? p.tile_near : p.tile_late;
-    for (uint32_t t = 0; t < tiles; ++t) to[t0 + t] = b;
+    if (in) {
+        p.pair_off[b] = at[0];
+        int4* rec = reinterpret_cast<int4*>(p.record + (int64_t)b * kPairRecord);
+        rec[0] = make_int4(size, t0, (int)n, at[0]);
+        rec[1] = make_int4((int)(uint32_t)slot, (int)(slot >> 32), 0, 0);
+        for (uint32_t t = 0; t < min(tiles, kOwnTiles); ++t) to[t0 + t] = b;
+    }
+    // the others of the buckets with more: a wavefront a bucket
+    if (tiles > kOwnTiles) many[atomicAdd(&n_many, 1)] = make_int4(t0, (int)tiles, b, 0);
+    __syncthreads();
+    for (int i = wave; i < n_many; i += 4) {
+        const int4 m = many[i];
+        int32_t* at_bucket = (m.z < L ? p.tile_near : p.tile_late) + m.x;
+        for (int t = (int)kOwnTiles + lane; t < m.y; t += 64) at_bucket[t] = m.z;
+    }
 }
 
 __global__ void k_pair_scatter(const int32_t* __restrict__ probe, const int32_t* __restrict__ first, int64_t nq,

@@ -35,3 +35,30 @@ def test_query_counts_at_tile_edges(d, b):
         for a, c, sa in zip(i1, i2, s1):             # a label that only one side has sits at the k-th value
             assert np.all(np.abs(sa[np.isin(a, c, invert=True)] - sa[-1]) <= 2e-4)
     ix.close()
+
+
+@pytest.mark.parametrize("nq", [255, 600, 2000])
+def test_lists_with_many_tiles(nq):
+    """Few lists that every query probes: a list has up to 20 parts for each of 63 tiles of queries, more tiles than a thread writes by itself,
+    one list just as many (16) and others fewer."""
+    import paper_2605_17415_amd as pkg
+    print(f"[many tiles] nq={nq}", flush=True)
+    rng = np.random.default_rng(nq)
+    d, b, sizes = 64, 4, [3000, 257, 64, 31, 5000, 1, 1024]
+    L, n = len(sizes), sum(sizes)
+    cent = rng.standard_normal((L, d)).astype(np.float32)
+    ix = pkg.Index(d, b, L, rotation_seed=1)
+    ix.set_coarse(cent / np.linalg.norm(cent, axis=1, keepdims=True))
+    cell = rng.permutation(np.repeat(np.arange(L), sizes)).astype(np.int32)
+    ix.add_encoded(*[torch.from_numpy(v).to("cuda:0") for v in (cell, rng.integers(0, 1 << b, (n, d)).astype(np.uint8), rng.uniform(0.2, 1.2, n).astype(np.float16))])
+    q = torch.from_numpy(rng.standard_normal((nq, d)).astype(np.float32)).to("cuda:0")
+    got = []
+    for mode in (1, 2):
+        ix.set_search_mode(mode)
+        got.append([t.cpu().numpy() for t in ix.search(q, L, 10)])
+    assert ix.scan_stats()["queries"] == nq
+    (s1, i1), (s2, i2) = got
+    assert np.all(np.abs(s1 - s2) <= 1e-4) and (i1 >= 0).all() and (i2 >= 0).all()
+    for a, c, sa in zip(i1, i2, s1):
+        assert np.all(np.abs(sa[np.isin(a, c, invert=True)] - sa[-1]) <= 2e-4)
+    ix.close()
