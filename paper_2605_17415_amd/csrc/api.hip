@@ -1417,7 +1417,7 @@ ivftq_status search_core(ivftq_index* ix, const float* q_dev, int64_t nq, int np
         shape = tile_shape(ix->ntotal, ix->nlist, qc * nprobe, batch_tile(ix->d, bits));
         const ListRoom lists = list_room(ix->h_size.data(), ix->nlist);
         near_tiles = tile_room(lists, held, held * nprobe, kBatchTileNear);
-        late_tiles = tile_room(lists, held, held * nprobe, kBatchTile);
+        late_tiles = late_tile_room(lists, list_room(ix->h_size.data(), ix->nlist, kPartFine), fine_pairs(ix->ntotal, ix->nlist), held, held * nprobe);
         HIP_TRY(ix->w_zh.ensure((size_t)held * ix->dp * sizeof(uint16_t)));
         HIP_TRY(ix->w_zl.ensure((size_t)held * ix->dp * sizeof(uint16_t)));
         HIP_TRY(ix->w_first.ensure((size_t)held * sizeof(int32_t)));

@@ -710,6 +710,7 @@ struct BatchForm {
     static constexpr int NQ = batch_query_tiles(DP, B);
     static constexpr int OCC = 2;
     static_assert(32 * NQ >= kBatchTile, "the room for tiles is counted by the fewest queries of one");
+    static_assert(32 * NQ <= kBatchTileMost, "and which calls have few of them by the most");
 };
 
 template <int DP, int B>

@@ -53,7 +53,7 @@ constexpr int64_t redo_window(int64_t queries, int64_t gate_rows) {
 // counted by: batch_tile of kernels.h says how many a form takes).
 constexpr int kBatchTile = 64, kBatchTileNear = 32;
 // Lists of more than part_len vectors are cut into nearly equal parts of at most part_len, each a tile of its own.
-constexpr int kPartMin = 256, kPartMax = 4096;
+constexpr int kPartMin = 256, kPartMax = 4096, kPartFine = 64;
 struct TileShape { int tq_near, tq, part_near, part; };
 constexpr int list_parts(int size, int part_len) { return size > part_len ? (size + part_len - 1) / part_len : 1; }
 
@@ -65,9 +65,29 @@ inline int part_length(int64_t typical_list, int64_t tiles) {
     const int64_t cuts = std::max<int64_t>(1, kTilesWanted / std::max<int64_t>(1, tiles));
     return (int)std::min<int64_t>(kPartMax, std::max<int64_t>(kPartMin, (typical_list / cuts + 63) / 64 * 64));
 }
+// Parts of kPartMin leave wavefronts without a tile where lists are few or short and meet few queries, and most of their tiles are one query
+// tile high.  So the threshold pass's parts get shorter, down to kPartFine, as long as all tiles find a wavefront at once: the pass, us, with
+// parts of 256 and so, 1700 queries x 5 probes of 130 lists of 1050 (48 coordinates, no clusters) 83 and 43, 391 x 43 of 300 of 233 (192) 58 and 36, 1000 x 32
+// of 256 of 234 (128, 8 bits) 84 and 56, 500 x 20 of 200 of 300 (256) 73 and 36, 400 x 16 of 300 of 333 (96, clustered) 9.9 and 8.3.  With tiles for a
+// wavefront and a few more 200 x 16 of 500 of 500 (200) took 41 instead of 28, 26 so.  (Cut further than that, calls that had as many tiles as
+// wavefronts lost: parts of 128 instead of 256 for all, 400 x 64 of 512 of 781 5 to 12 % of the call.)
+constexpr int64_t kTilesFew = 2048;
+inline int part_late(int64_t typical_list, int64_t tiles) {
+    const int part = part_length(typical_list, tiles);
+    const int64_t cuts = kTilesFew / std::max<int64_t>(1, tiles);
+    if (cuts < 2 || cuts <= list_parts((int)typical_list, kPartMin)) return part;
+    return (int)std::min<int64_t>(part, std::max<int64_t>(kPartFine, (typical_list / cuts + 32) / 64 * 64));
+}
 inline TileShape tile_shape(int64_t ntotal, int nlist, int64_t pairs, int tq) {
     const int64_t typical = std::max<int64_t>(1, ntotal / nlist), lists = std::min<int64_t>(nlist, pairs);
-    return {kBatchTileNear, tq, part_length(typical, lists), part_length(typical, lists + pairs / tq)};
+    return {kBatchTileNear, tq, part_length(typical, lists), part_late(typical, lists + pairs / tq)};
+}
+// The most pairs with which calls can have so few tiles, whatever a tile takes.  (Tiles are counted as lists, of which few pairs meet as many, and a
+// tile's share of the pairs: no more than kTilesFew / 2 and, by the parts of a list, fewer.)
+constexpr int kBatchTileMost = 128;
+inline int64_t fine_pairs(int64_t ntotal, int nlist) {
+    const int64_t most = kTilesFew / std::max(2, list_parts((int)std::max<int64_t>(1, ntotal / nlist), kPartMin));
+    return nlist >= most ? most : most * kBatchTileMost;
 }
 
 // The tiles of a pass are dealt out to kTileQueues queues, each served by the workgroups of its number: updates of one counter from all over
@@ -84,10 +104,10 @@ constexpr int queue_tile(int queue, int j) { return j * kTileQueues + (queue + 5
 // queries has at most 1 + c / tq tiles for each of its parts; c adds up to `pairs` over the lists and is at most
 // `queries` in each.  list_room: what the first tile of every list takes.
 struct ListRoom { int64_t all, longest; };
-inline ListRoom list_room(const int32_t* size, int nlist) {
+inline ListRoom list_room(const int32_t* size, int nlist, int part_len = kPartMin) {
     ListRoom r{0, 1};
     for (int l = 0; l < nlist; ++l) {
-        const int parts = list_parts(size[l], kPartMin);
+        const int parts = list_parts(size[l], part_len);
         r.all += parts;
         r.longest = std::max<int64_t>(r.longest, parts);
     }
@@ -95,6 +115,12 @@ inline ListRoom list_room(const int32_t* size, int nlist) {
 }
 inline int64_t tile_room(const ListRoom& lists, int64_t queries, int64_t pairs, int tq) {
     return lists.all + std::min(pairs / tq * lists.longest, queries / tq * lists.all);
+}
+// The threshold pass: of calls with up to few_pairs pairs the parts may be kPartFine, fine the room of such.
+inline int64_t late_tile_room(const ListRoom& lists, const ListRoom& fine, int64_t few_pairs, int64_t queries, int64_t pairs) {
+    const int64_t q = std::min(queries, few_pairs), p = std::min(pairs, few_pairs);
+    return std::max(tile_room(lists, queries, pairs, kBatchTile),
+                    std::min(fine.all, p * fine.longest) + std::min(p / kBatchTile * fine.longest, q / kBatchTile * fine.all));
 }
 
 }  // namespace ivftq

@@ -114,13 +114,17 @@ int main() {
     std::mt19937_64 rng(5);
     for (const auto& ix : indexes) {
         const std::vector<int32_t> size = lists(ix.kind, ix.nlist, ix.total);
-        const ListRoom room = list_room(size.data(), ix.nlist);
+        const ListRoom room = list_room(size.data(), ix.nlist), fine = list_room(size.data(), ix.nlist, kPartFine);
+        const int64_t few = fine_pairs(ix.total, ix.nlist);
         for (int tq : {kBatchTileNear, kBatchTile}) {
+            auto room_of = [&](int64_t q, int64_t pairs) {
+                return tq == kBatchTileNear ? tile_room(room, q, pairs, tq) : late_tile_room(room, fine, few, q, pairs);
+            };
             for (size_t a = 0; a < std::size(nq); ++a)
                 for (size_t b = 0; b < std::size(np); ++b) {
-                    const int64_t here = tile_room(room, nq[a], (int64_t)nq[a] * np[b], tq);
-                    const int64_t fewer_q = a ? tile_room(room, nq[a - 1], (int64_t)nq[a - 1] * np[b], tq) : 0;
-                    const int64_t fewer_p = b ? tile_room(room, nq[a], (int64_t)nq[a] * np[b - 1], tq) : 0;
+                    const int64_t here = room_of(nq[a], (int64_t)nq[a] * np[b]);
+                    const int64_t fewer_q = a ? room_of(nq[a - 1], (int64_t)nq[a - 1] * np[b]) : 0;
+                    const int64_t fewer_p = b ? room_of(nq[a], (int64_t)nq[a] * np[b - 1]) : 0;
                     if (here < fewer_q || here < fewer_p) {
                         std::printf("%s nlist=%d tq=%d: %d queries x %d probes have room for %lld tiles, less than a smaller call (%lld, %lld)\n",
                                     ix.kind, ix.nlist, tq, nq[a], np[b], (long long)here, (long long)fewer_q, (long long)fewer_p);
@@ -138,7 +142,8 @@ int main() {
                 if (p > ix.nlist || pairs > 400'000) continue;
                 for (int width : {64, 96, 128}) {                   // queries of a tile of the threshold pass, by its form
                 const TileShape shape = tile_shape(ix.total, ix.nlist, pairs, width);
-                if (shape.part_near < kPartMin || shape.part < kPartMin || shape.part_near % 64 || shape.part % 64) {
+                const bool few_tiles = pairs <= few;
+                if (shape.part_near < kPartMin || shape.part < (few_tiles ? kPartFine : kPartMin) || shape.part_near % 64 || shape.part % 64) {
                     std::printf("%s nlist=%d: part lengths %d and %d\n", ix.kind, ix.nlist, shape.part_near, shape.part);
                     return 1;
                 }
@@ -151,7 +156,7 @@ int main() {
                         const int tq = near ? shape.tq_near : shape.tq;
                         // (the room is counted by the fewest queries that any form takes)
                         const int64_t made = tiles_of(size, meets, tq, near ? shape.part_near : shape.part);
-                        const int64_t held = tile_room(room, q, pairs, near ? kBatchTileNear : kBatchTile);
+                        const int64_t held = near ? tile_room(room, q, pairs, kBatchTileNear) : late_tile_room(room, fine, few, q, pairs);
                         if (made > held) {
                             std::printf("%s nlist=%d: %d queries x %d probes make %lld tiles of %d, room for %lld\n", ix.kind, ix.nlist, q, p,
                                         (long long)made, tq, (long long)held);
