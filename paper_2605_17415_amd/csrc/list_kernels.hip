@@ -451,7 +451,10 @@ __device__ __forceinline__ T fixed(const T* p) {
 }
 
 // NW: words that can hold the 8b bits of eight codes (1 for b = 1, 2, 4; 3 for b = 7; else 2)
-template <int DP, int NW, bool F32>
+// PAST: stores go past the caches, where every wavefront's share of a row is whole pieces of 64 bytes: pieces that wavefronts share have to
+// meet in a cache.  1M rows, past the caches and not, us: 128 coordinates 143 and 171, 112 141 and 181, 80 103 and 120, 256 407 and 486; but
+// 100 206 and 174, 124 238 and 201, 68 186 and 121, 250 578 and 480, 200 356 and 358.  (One kernel with a branch: 160 245 instead of 231.)
+template <int DP, int NW, bool F32, bool PAST>
 __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
     ListStore store, int L, const float* __restrict__ cent, int cent_pitch, const float* __restrict__ pi, const uint16_t* __restrict__ pit_h,
     const uint16_t* __restrict__ pit_l, const float* __restrict__ cb, int d, int b, const int64_t* __restrict__ out_off,
@@ -640,7 +643,7 @@ __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
         // memory queue, would be a wait for the stores as well (0.31 ms at 1M x 128 that way).  The whole offset of a row
         // goes through the address register: the check does not cover the scalar offset.
         // (the descriptor is the same for a wavefront, which has to be said: taken for a lane's own, every store became a loop over the
-        // descriptors that the lanes might have: kernel 153 us for 1M x 128, 114 now.  The stores go past the caches, 4 % of a call.)
+        // descriptors that the lanes might have: kernel 153 us for 1M x 128, 114 now)
         const uint64_t to = reinterpret_cast<uint64_t>(x_out + (row0 + 32 * my_slab) * (int64_t)d);
         const uint32_t to_lo = __builtin_amdgcn_readfirstlane((uint32_t)to), to_hi = __builtin_amdgcn_readfirstlane((uint32_t)(to >> 32));
         const int to_bytes = __builtin_amdgcn_readfirstlane(min(max(cur_left, 0), 32) * d * 4);
@@ -654,7 +657,7 @@ __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
             const float gg[4] = {gm.x, gm.y, gm.z, gm.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i, at += (uint32_t)d * 4u)
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(fmaf(gg[i], acc[4 * g + i], c)), out, at, 0, 2);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(fmaf(gg[i], acc[4 * g + i], c)), out, at, 0, PAST ? 2 : 0);
             at += (uint32_t)d * 16u;
         }
     }
@@ -692,11 +695,11 @@ __global__ __launch_bounds__(1024) void k_list_prefix(const int32_t* __restrict_
     if (tid == 1023) tile_off[L] = part_t[1023];
 }
 
-template <int DP, int NW, bool F32>
-hipError_t run_reconstruct_nw(const ReconstructArgs& a, int cus, hipStream_t st) {
+template <int DP, int NW, bool F32, bool PAST>
+hipError_t run_reconstruct_as(const ReconstructArgs& a, int cus, hipStream_t st) {
     using Cfg = ReconCfg<DP, F32>;
     static LdsLimit lim;
-    const hipError_t e = lim.ensure(reinterpret_cast<const void*>(k_reconstruct<DP, NW, F32>), Cfg::lds_bytes);
+    const hipError_t e = lim.ensure(reinterpret_cast<const void*>(k_reconstruct<DP, NW, F32, PAST>), Cfg::lds_bytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_list_prefix, dim3(1), dim3(1024), 0, st, a.store.list_size, a.L, Cfg::VEC, a.out_off, a.tile_off);
     int64_t tiles = 0;
@@ -704,14 +707,20 @@ hipError_t run_reconstruct_nw(const ReconstructArgs& a, int cus, hipStream_t st)
     static std::atomic<int> per_cu{0};               // workgroups a compute unit holds, the same on every device of this kind
     int fit = per_cu.load(std::memory_order_relaxed);
     if (fit == 0) {
-        const hipError_t eo = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, reinterpret_cast<const void*>(k_reconstruct<DP, NW, F32>), Cfg::THREADS, Cfg::lds_bytes);
+        const hipError_t eo = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, reinterpret_cast<const void*>(k_reconstruct<DP, NW, F32, PAST>), Cfg::THREADS, Cfg::lds_bytes);
         if (eo != hipSuccess) return eo;
         per_cu.store(fit = std::max(fit, 1), std::memory_order_relaxed);
     }
     const unsigned blocks = (unsigned)std::min<int64_t>(tiles, (int64_t)cus * fit);
-    hipLaunchKernelGGL((k_reconstruct<DP, NW, F32>), dim3(blocks), dim3(Cfg::THREADS), Cfg::lds_bytes, st, a.store, a.L, a.cent, a.cent_pitch, a.pi, a.pit_h,
+    hipLaunchKernelGGL((k_reconstruct<DP, NW, F32, PAST>), dim3(blocks), dim3(Cfg::THREADS), Cfg::lds_bytes, st, a.store, a.L, a.cent, a.cent_pitch, a.pi, a.pit_h,
                        a.pit_l, a.cb, a.d, a.b, (const int64_t*)a.out_off, (const int32_t*)a.tile_off, (int)tiles, a.x_out, a.labels_out);
     return hipGetLastError();
+}
+
+template <int DP, int NW, bool F32>
+hipError_t run_reconstruct_nw(const ReconstructArgs& a, int cus, hipStream_t st) {
+    return a.d % 16 == 0 && reinterpret_cast<uintptr_t>(a.x_out) % 64 == 0 ? run_reconstruct_as<DP, NW, F32, true>(a, cus, st)
+                                                                           : run_reconstruct_as<DP, NW, F32, false>(a, cus, st);
 }
 
 // dst[t] = src[idx[t]] for rows of d floats
