@@ -71,19 +71,23 @@ inline int part_length(int64_t typical_list, int64_t tiles) {
 // of 256 of 234 (128, 8 bits) 84 and 56, 500 x 20 of 200 of 300 (256) 73 and 36, 400 x 16 of 300 of 333 (96, clustered) 9.9 and 8.3.  With tiles for a
 // wavefront and a few more 200 x 16 of 500 of 500 (200) took 41 instead of 28, 26 so.  (Cut further than that, calls that had as many tiles as
 // wavefronts lost: parts of 128 instead of 256 for all, 400 x 64 of 512 of 781 5 to 12 % of the call.)
+// (Lists are of different sizes and popularity: three quarters of the wavefronts are aimed at.)
 constexpr int64_t kTilesFew = 2048;
-inline int part_late(int64_t typical_list, int64_t tiles) {
-    const int part = part_length(typical_list, tiles);
-    const int64_t cuts = kTilesFew / std::max<int64_t>(1, tiles);
+// whole: tiles if no list were cut, a list's last one half full; part: as for many tiles
+inline int part_late(int64_t typical_list, int64_t whole, int part) {
+    const int64_t cuts = kTilesFew * 3 / 4 / std::max<int64_t>(1, whole);
     if (cuts < 2 || cuts <= list_parts((int)typical_list, kPartMin)) return part;
-    return (int)std::min<int64_t>(part, std::max<int64_t>(kPartFine, (typical_list / cuts + 32) / 64 * 64));
+    int fine = (int)std::max<int64_t>(kPartFine, (typical_list / cuts + 32) / 64 * 64);
+    while (fine < part && whole * list_parts((int)typical_list, fine) > kTilesFew) fine += 64;
+    return std::min(part, fine);
 }
 inline TileShape tile_shape(int64_t ntotal, int nlist, int64_t pairs, int tq) {
-    const int64_t typical = std::max<int64_t>(1, ntotal / nlist), lists = std::min<int64_t>(nlist, pairs);
-    return {kBatchTileNear, tq, part_length(typical, lists), part_late(typical, lists + pairs / tq)};
+    const int64_t typical = std::max<int64_t>(1, ntotal / nlist), lists = std::max<int64_t>(1, std::min<int64_t>(nlist, pairs));
+    const int64_t whole = std::max(lists, pairs / tq + lists / 2);
+    return {kBatchTileNear, tq, part_length(typical, lists), part_late(typical, whole, part_length(typical, lists + pairs / tq))};
 }
-// The most pairs with which calls can have so few tiles, whatever a tile takes.  (Tiles are counted as lists, of which few pairs meet as many, and a
-// tile's share of the pairs: no more than kTilesFew / 2 and, by the parts of a list, fewer.)
+// The most pairs with which calls can have so few tiles, whatever a tile takes: a list that is met, of which few pairs make as many, is a
+// tile or more, and so are a tile's queries of pairs.
 constexpr int kBatchTileMost = 128;
 inline int64_t fine_pairs(int64_t ntotal, int nlist) {
     const int64_t most = kTilesFew / std::max(2, list_parts((int)std::max<int64_t>(1, ntotal / nlist), kPartMin));
