@@ -144,7 +144,7 @@ struct BatchTile {
 // meet there.  No wavefront waits for another (with a tile to a workgroup, whose wavefronts met at a barrier and waited for the counter,
 // half of all wavefront cycles went by waiting).  Finding a tile's bucket, record, pairs and queries is a chain of five dependent reads of
 // 0.7 us and more; most are made while the tiles before it are worked on: its number is asked for two tiles ahead, its bucket
-// one tile ahead, the record after slab 2 of the tile before and the pairs after its slab 8.  A tile of the shortest part, 256 vectors, has slabs 0 to 7,
+// one tile ahead, the record after slab 2 of the tile before and the pairs after its slab 8.  A tile of 256 vectors, which most have, has slabs 0 to 7,
 // so there the pairs are read between the tiles.  What is asked for comes behind the words of vectors on their way, so the wait for it is one for
 // those too.
 // TQ: queries of a tile.
@@ -468,10 +468,6 @@ __device__ __forceinline__ int slab_max(int v) {
     return max((int)r0, (int)r1);
 }
 
-// Integers in the order of floats that are numbers, and back.
-__device__ __forceinline__ int ordered_bits(float f) { return __float_as_int(f) ^ (__float_as_int(f) >> 31 & 0x7FFFFFFF); }
-__device__ __forceinline__ float ordered_float(int i) { return __int_as_float(i ^ (i >> 31 & 0x7FFFFFFF)); }
-
 // ---- threshold pass: the other lists, only scores that can reach the query's threshold kept ------------
 //
 // The vectors are the row operand, so a lane holds one query's scores against 16 vectors and needs that query's
@@ -588,8 +584,8 @@ void k_batch_threshold(BatchScanArgs a) {
             if (RAW) {
                 s_x[jl] = f.xn;
                 const bool counts = in_part && f.xn == f.xn;
-                x_min = ordered_float(~slab_max(~ordered_bits(counts ? f.xn : __builtin_inff())));
-                x_max = __int_as_float(slab_max(max(__float_as_int(counts ? f.xn : 0.f), 0)));
+                x_min = __int_as_float(~slab_max(counts ? ~__float_as_int(f.xn) : INT32_MIN));
+                x_max = __int_as_float(slab_max(counts ? __float_as_int(f.xn) : 0));
             }
             fetch_norm(next, f);
             wave_sync();
