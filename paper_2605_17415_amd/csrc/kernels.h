@@ -399,8 +399,9 @@ struct PairTable {
 // in a nanosecond over all of them and 14 ns and more apart on one of them, come on top of it; else they are counted in LDS, in two launches
 // that take 10 us and more.  Probe selection and grouping, counted early and not, us: 1000 queries x 16 probes of 1000 cells 18.7 and 26, 256 x 64
 // of 4096 21 and 29, 1200 x 16 of 600 24 and 27, 10,000 x 32 of 4096 82 and 86, 4096 x 32 of 1024 51 and 32; by pairs a list, 8 probes of 128
-// cells: 16 15 and 17, 32 20.7 and 20.8 and a launch, 64 26 and 22, 128 41 and 24, 250 64 and 27.
-inline bool pairs_counted_early(int64_t nq, int np, int L) { return nq * np <= std::min<int64_t>(32768, (int64_t)32 * L); }
+// cells: 16 15 and 17, 32 20.7 and 20.8, 64 26 and 22, 128 41 and 24, 250 64 and 27, where one launch fewer saves the call 4 to 6 more (218 x 65 of 388
+// 119 and 125, 240 x 72 of 290 83 and 87).
+inline bool pairs_counted_early(int64_t nq, int np, int L) { return nq * np <= std::min<int64_t>(32768, (int64_t)64 * L); }
 // rank (may be null): as the probe selection left it, with the counts
 hipError_t launch_pair_grouping(const int32_t* probe, const int32_t* first, const int32_t* rank, int64_t nq, int np, int L, const int32_t* list_size, const int64_t* list_off,
                                 const TileShape& shape, const PairTable& p, hipStream_t st);
