@@ -451,9 +451,11 @@ __device__ __forceinline__ T fixed(const T* p) {
 }
 
 // NW: words that can hold the 8b bits of eight codes (1 for b = 1, 2, 4; 3 for b = 7; else 2)
-// PAST: stores go past the caches, where every wavefront's share of a row is whole pieces of 64 bytes: pieces that wavefronts share have to
-// meet in a cache.  1M rows, past the caches and not, us: 128 coordinates 143 and 171, 112 141 and 181, 80 103 and 120, 256 407 and 486; but
-// 100 206 and 174, 124 238 and 201, 68 186 and 121, 250 578 and 480, 200 356 and 358.  (One kernel with a branch: 160 245 instead of 231.)
+// PAST: stores go past the caches, where every wavefront's share of a row is whole pieces of 64 bytes, or of 32 in wide rows: pieces that
+// wavefronts share have to meet in a cache.  1M rows, past the caches and not, us: 128 coordinates 143 and 171, 112 141 and 181, 80 103 and 120,
+// 256 407 and 486; but 100 206 and 174, 124 238 and 201, 68 186 and 121, 72 168 and 122, 104 190 and 177, 250 578 and 480.  Of 8 coordinates and no
+// 16, the time of the latter over the former at 1M and 300,000 rows: 168 1.17 and 0.96, 184 1.17 and 1.04, 200 1.02 and 1.03, 232 1.02 and 1.08, 248
+// 1.07 and 1.08.  (One kernel with a branch: 160 245 instead of 231.)
 template <int DP, int NW, bool F32, bool PAST>
 __global__ __launch_bounds__((ReconCfg<DP, F32>::THREADS)) void k_reconstruct(
     ListStore store, int L, const float* __restrict__ cent, int cent_pitch, const float* __restrict__ pi, const uint16_t* __restrict__ pit_h,
@@ -719,7 +721,7 @@ hipError_t run_reconstruct_as(const ReconstructArgs& a, int cus, hipStream_t st)
 
 template <int DP, int NW, bool F32>
 hipError_t run_reconstruct_nw(const ReconstructArgs& a, int cus, hipStream_t st) {
-    return a.d % 16 == 0 && reinterpret_cast<uintptr_t>(a.x_out) % 64 == 0 ? run_reconstruct_as<DP, NW, F32, true>(a, cus, st)
+    return a.d % (a.d > 160 ? 8 : 16) == 0 && reinterpret_cast<uintptr_t>(a.x_out) % 64 == 0 ? run_reconstruct_as<DP, NW, F32, true>(a, cus, st)
                                                                            : run_reconstruct_as<DP, NW, F32, false>(a, cus, st);
 }
 
