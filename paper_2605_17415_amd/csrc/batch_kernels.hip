@@ -36,7 +36,7 @@ __global__ void k_pair_count(const int32_t* __restrict__ probe, const int32_t* _
 // the totals with one atomic each, so the ranges of different workgroups lie in no particular order, which nothing
 // depends on (in bucket order, by one workgroup: 0.017 ms for 8192 buckets, the chain of its loads).  A thread writes the first kOwnTiles
 // tiles of its bucket, wavefronts the rest: a few long lists that meet many queries have a thousand and more each (33 lists, 9699
-// queries x 5 probes: 44 us by a thread each, 11 so).
+// queries x 5 probes: 44 us by a thread each, 14 so).
 constexpr uint32_t kOwnTiles = 64;
 __global__ __launch_bounds__(256) void k_pair_ranges(const int32_t* __restrict__ list_size, const int64_t* __restrict__ list_off, int nb,
                                                      int L, TileShape shape, PairTable p) {

@@ -39,8 +39,8 @@ def test_query_counts_at_tile_edges(d, b):
 
 @pytest.mark.parametrize("nq", [255, 600, 2000])
 def test_lists_with_many_tiles(nq):
-    """Few lists that every query probes: a list has up to 20 parts for each of 63 tiles of queries, more tiles than a thread writes by itself,
-    one list just as many (16) and others fewer."""
+    """Few lists that every query probes: a list has up to 20 parts for each of 63 tiles of queries, more tiles than a thread writes by itself (64),
+    and other lists fewer."""
     import paper_2605_17415_amd as pkg
     print(f"[many tiles] nq={nq}", flush=True)
     rng = np.random.default_rng(nq)
